@@ -308,10 +308,10 @@ int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const vo
  * (unchanged if that is all zero) and q[x] <- 0, q renormalised; when no child is accepted the
  * bonus token is the inverse-CDF sample of p with the next uniform.  uniforms [M+1] fp32 in
  * [0,1), consumed in order.  marginals [B,V] fp32 as given to tree_build.
- *   Four small launches ahead of the walk prepare the root's row (softmax numerators and their
- *   (e, q) pairs sorted by q/e) on many CUs when the root has 6 children or more; the walk
- *   itself is one workgroup; one small launch after it draws the bonus token (bonus is valid
- *   when it has run, like every output: in stream order).
+ *   One launch of up to 64 workgroups, each with a slice of the vocabulary, that exchange their parts of
+ *   every vocabulary-wide sum in the workspace and walk the tree in step.  A workgroup that waits for another's
+ *   part longer than a second of wall clock gives up: the data flag is raised and the kernel ends
+ *   (the workspace is then to be zero-filled before its next use).
  * ------------------------------------------------------------------------------------------- */
 size_t btv_tree_accept_workspace(int M, int V, int stochastic);
 int btv_tree_accept_greedy(const void *logits, int dtype, const int32_t *parent, const int32_t *token,

@@ -1,5 +1,5 @@
-// Acceptance walk on the GPU (gfx950): target argmax per tree row, greedy walk, and the
-// token-level rejection walk at temperature 1.
+// Greedy acceptance on the GPU (gfx950): target argmax per tree row and the walk; also straight from the hidden states.
+// (The rejection walk at temperature 1 is in stochastic.hip.)
 //
 // App. C "Acceptance" / Sec. 3.1: the committed tokens are the longest root-to-node path the
 // target itself would have produced.  Rows of `logits`: 0 = root, 1+i = node i.
@@ -795,892 +795,6 @@ int lm_head_dispatch(const uint16_t *H, const uint16_t *W, int R, int h, int V, 
     return btv_fail(BTV_EINVAL, "no LM-head kernel for %d rows", R);
 }
 
-// ------------------------------------------------------------------------------------------------
-// Stochastic walk: one workgroup of 1024 threads; p and q live in the workspace (fp32), every
-// vocabulary-wide sum is accumulated in fp64.
-// ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum(double x, double *sh, int tid)
-{
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-    __syncthreads();
-    if ((tid & 63) == 0) sh[tid >> 6] = x;
-    __syncthreads();
-    double s = 0.0;
-    for (int w = 0; w < 16; ++w) s += sh[w];
-    return s;
-}
-
-__device__ __forceinline__ float block_max(float x, float *sh, int tid)
-{
-    for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    __syncthreads();
-    if ((tid & 63) == 0) sh[tid >> 6] = x;
-    __syncthreads();
-    float s = sh[0];
-    for (int w = 1; w < 16; ++w) s = fmaxf(s, sh[w]);
-    return s;
-}
-
-// Sum of x over the wavefront, returned in every lane: quad swaps, row mirrors, then the row totals travel down the
-// rows (DPP moves of the two halves; lanes a step does not write add zero).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double x)
-{
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, true);
-    return x + __longlong_as_double(((long long)(uint32_t)hi << 32) | (long long)(uint32_t)lo);
-}
-__device__ __forceinline__ double wave_sum_f64(double x)
-{
-    x = dpp_add<0xB1, 0xF>(x);      // quad_perm [1,0,3,2]
-    x = dpp_add<0x4E, 0xF>(x);      // quad_perm [2,3,0,1]
-    x = dpp_add<0x141, 0xF>(x);     // row_half_mirror
-    x = dpp_add<0x140, 0xF>(x);     // row_mirror: every lane holds its row's total
-    x = dpp_add<0x142, 0xA>(x);     // row_bcast15 into rows 1 and 3
-    x = dpp_add<0x143, 0xC>(x);     // row_bcast31 into rows 2 and 3: lane 63 holds the total
-    const long long b = __double_as_longlong(x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
-    return __longlong_as_double(((long long)hi << 32) | (long long)lo);
-}
-
-template <bool BF16>
-__device__ __forceinline__ float load_logit(const void *logits, size_t idx)
-{
-    if (BF16) return __uint_as_float((uint32_t)static_cast<const uint16_t *>(logits)[idx] << 16);
-    return static_cast<const float *>(logits)[idx];
-}
-
-// Nothing is rewritten per rejection.  With e[v] = exp(logit[v] - max) and q0 = the draft marginal of the depth,
-// the target distribution after k rejections at a node is  p_k[v] = max(alpha * e[v] - beta * q0[v], 0)  and the
-// draft distribution  q_k[v] = q0[v] / T  for the tokens not yet tried (a rejected token has q_k > p_k, so its
-// residual is zero from then on and the same formula covers it).  A rejection needs
-//     Z = sum_v max(p_k[v] - q_k[v], 0) = sum_v max(alpha * e[v] - b1 * q0[v], 0),   b1 = beta + 1/T,
-// then  alpha /= Z,  beta = b1 / Z,  T -= q0[x];  Z = 0 leaves p as it was.  Scalars are fp64; e is stored once
-// per node in fp32.
-// A rejection at a node with few children gets Z from a read-only pass over the vocabulary.  A node with a wide fan
-// of children still to try sorts its tokens once into SW_BINS bins of the ratio q0/e (counting sort on the float's
-// exponent and three mantissa bits, the (e, q0) pairs moved into bin order): token v contributes iff q0/e < alpha/b1,
-// so Z is a prefix sum over the sorted pairs below the threshold's bin plus an exact scan of that one bin.
-constexpr int SW_BINS = 2048;
-constexpr int SW_PBINS = 2048;      // bins of a row that is prepared ahead of the walk (sw_bin_at); 4096 measured slower:
-                                    // what the walk saves per rejection, the scatter kernel pays in histogram reads
-constexpr int SW_BUILD_MIN = 40;    // children still untried at a node for the sort to be worth its cost (about 30 passes)
-constexpr int SW_PRE_MIN = 6;       // children of the root from which its row is sorted ahead of the walk (a few passes' worth)
-constexpr int SW_WIN = 11264;       // sorted pairs kept in LDS around the threshold
-
-__device__ __forceinline__ int sw_bin(float ratio)
-{
-    const uint32_t b = (__float_as_uint(ratio) & 0x7FFFFFFFu) >> 20;      // NaN (0/0) and inf (e = 0) land on top: never active
-    return (int)(b < (uint32_t)SW_BINS ? b : (uint32_t)SW_BINS - 1u);
-}
-
-// The same order-preserving map with the bins spent where the ratios are: binades elo .. (biased exponents) get 2^m
-// bins each, what lies below shares bin 0 and what lies above (inf and NaN included) the last bin.  { 0, 3 } is sw_bin.
-struct SwBin { int elo, m; };
-
-__device__ __forceinline__ int sw_bin_at(float ratio, SwBin p)
-{
-    const uint32_t u = __float_as_uint(ratio) & 0x7FFFFFFFu;
-    const int d = (int)(u >> 23) - p.elo;
-    if (d < 0) return 0;
-    const uint32_t b = ((uint32_t)d << p.m) | ((u & 0x7FFFFFu) >> (23 - p.m));
-    return (int)(b < (uint32_t)SW_PBINS ? b : (uint32_t)SW_PBINS - 1u);
-}
-
-// Sorted pairs per prefix-sum chunk: 2^s with s the smallest value from 6 up that leaves at most SW_BINS chunks (a
-// power of two, so that the chunk of a sorted position is a shift: the walk asks once per rejection).
-__device__ __forceinline__ int sw_chunk_shift(int V)
-{
-    int s = 6;
-    while (((V + (1 << s) - 1) >> s) > SW_BINS) ++s;
-    return s;
-}
-
-// ---- the root's row sorted ahead of the walk, by many workgroups ---------------------------------------------------
-// Wide fans sit under the root (the best-first tree puts up to N children there when the first position's
-// marginal is flat), and a sort on the walk's single CU costs about 250 us.  When the root has at least SW_BUILD_MIN
-// children, SW_PRE_WGS workgroups prepare the root's row before the walk starts: row maximum, e = exp(logit - max)
-// with its sum, a bin histogram per workgroup, the (e, q0) pairs moved into bin order (bin offsets per workgroup),
-// and the sums of e and q0 per chunk of the sorted pairs.  Every step is its own launch (the grid-wide
-// dependencies are kernel boundaries); with fewer children every one of them returns at once.  The walk picks the
-// prepared row up if SwPre::ready says so.  Each workgroup owns a contiguous slice of the vocabulary; all sums
-// that cross workgroups are added in workgroup order, so they are the same in every run.
-constexpr int SW_PRE_WGS = 32;
-
-struct SwPre {                      // in the workspace, behind es and eq_sorted
-    int ready;                      // 1: the root's row is prepared (written by sw_pre_scatter)
-    float mx;
-    double z, tq;
-    float wg_max[SW_PRE_WGS];
-    float wg_tlo[SW_PRE_WGS], wg_thi[SW_PRE_WGS];         // range of log2(q0) - logit * log2(e) over the slice's tokens with q0 > 0
-    double wg_z[SW_PRE_WGS], wg_tq[SW_PRE_WGS];
-    int start[SW_PBINS + 1];
-    double chunk_e[SW_BINS], chunk_q[SW_BINS];            // sums over chunk c of the sorted pairs (not yet prefix sums)
-    int hist[SW_PRE_WGS][SW_PBINS];                       // pairs of workgroup w in bin b
-    // what the walk leaves for the bonus draw, and the draw's per-wavefront totals
-    double b_alpha, b_beta, b_u;
-    int b_has_q, b_depth;
-    int b_count;                                          // workgroups of the bonus kernel that have left their totals
-    double b_tot[SW_PRE_WGS * 16];
-    int b_last[SW_PRE_WGS * 16];
-};
-
-__device__ __forceinline__ bool sw_root_is_wide(const int32_t *parent, int M, int tid, double *shd)
-{
-    int mine = 0;
-    for (int c = tid; c < M; c += 1024) mine += parent[c] == -1 ? 1 : 0;
-    return (int)block_sum((double)mine, shd, tid) >= SW_PRE_MIN;
-}
-
-__device__ __forceinline__ void sw_slice(int V, int wg, int &v0, int &v1)
-{
-    const int per = ((V + SW_PRE_WGS - 1) / SW_PRE_WGS + 3) & ~3;      // a multiple of four: slices keep the row's alignment
-    v0 = min(wg * per, V);
-    v1 = min(v0 + per, V);
-}
-
-// Bins of the prepared row: log2(q0 / e) = log2(q0) - (logit - max) * log2(e) lies within the range that sw_pre_max
-// found (plus a binade of slack at either end for the roundings on the way); the binades of that range share the
-// bins, as many per binade as fit.  With the fixed map a row whose ratios span 30 binades used 240 of the 2048 bins
-// and the bin that the falling threshold sits in held 1500 pairs, all of which a rejection must look at.  Every
-// kernel works the parameters out from the same numbers, so they agree.
-__device__ __forceinline__ SwBin sw_bin_params(const SwPre *pre, float mx)
-{
-    float tlo = INFINITY, thi = -INFINITY;
-    for (int w = 0; w < SW_PRE_WGS; ++w) { tlo = fminf(tlo, pre->wg_tlo[w]); thi = fmaxf(thi, pre->wg_thi[w]); }
-    SwBin p = { 0, 3 };
-    const float shift = mx * 1.44269504f;
-    const float lo2 = tlo + shift, hi2 = thi + shift;
-    if (!(lo2 <= hi2) || !(lo2 > -200.f) || !(hi2 < 200.f)) return p;      // no token with q0 > 0, or a range beyond fp32's
-    const int elo = max((int)floorf(lo2) - 1 + 127, 0), ehi = min(max((int)ceilf(hi2) + 1 + 127, elo), 254);
-    const int span = ehi - elo + 1;
-    int m = 3;
-    while (m < 10 && (span << (m + 1)) <= SW_PBINS) ++m;
-    if ((span << m) > SW_PBINS) return p;
-    p.elo = elo; p.m = m;
-    return p;
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(1024) void sw_pre_max(const void *__restrict__ logits, const float *__restrict__ q0,
-                                                   const int32_t *__restrict__ parent, int M, int V, SwPre *pre)
-{
-    __shared__ double shd[16];
-    __shared__ float shf[16];
-    const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid == 0) pre->ready = 0;
-    if (!sw_root_is_wide(parent, M, tid, shd)) return;
-    int v0, v1;
-    sw_slice(V, blockIdx.x, v0, v1);
-    float mx = -INFINITY, tlo = INFINITY, thi = -INFINITY;
-    for (int v = v0 + tid; v < v1; v += 1024) {
-        const float x = load_logit<BF16>(logits, v), q = q0[v];
-        mx = fmaxf(mx, x);
-        const float t = __log2f(q) - x * 1.44269504f;
-        if (q > 0.f && fabsf(t) < 1e30f) { tlo = fminf(tlo, t); thi = fmaxf(thi, t); }
-    }
-    mx = block_max(mx, shf, tid);
-    __syncthreads();
-    tlo = -block_max(-tlo, shf, tid);
-    __syncthreads();
-    thi = block_max(thi, shf, tid);
-    if (tid == 0) { pre->wg_max[blockIdx.x] = mx; pre->wg_tlo[blockIdx.x] = tlo; pre->wg_thi[blockIdx.x] = thi; }
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(1024) void sw_pre_exp(const void *__restrict__ logits, const float *__restrict__ q0,
-                                                   const int32_t *__restrict__ parent, int M, int V, float *__restrict__ es,
-                                                   SwPre *pre)
-{
-    __shared__ double shd[16];
-    __shared__ int hist[SW_PBINS];
-    const int tid = threadIdx.x;
-    if (!sw_root_is_wide(parent, M, tid, shd)) return;
-    float mx = pre->wg_max[0];
-    for (int w = 1; w < SW_PRE_WGS; ++w) mx = fmaxf(mx, pre->wg_max[w]);
-    for (int b = tid; b < SW_PBINS; b += 1024) hist[b] = 0;
-    const SwBin bp = sw_bin_params(pre, mx);
-    __syncthreads();
-    int v0, v1;
-    sw_slice(V, blockIdx.x, v0, v1);
-    double z = 0.0, tq = 0.0;
-    for (int v = v0 + tid; v < v1; v += 1024) {
-        const float e = expf(load_logit<BF16>(logits, v) - mx), q = q0[v];
-        es[v] = e;
-        z += (double)e;
-        tq += (double)q;
-        atomicAdd(&hist[sw_bin_at(__fdiv_rn(q, e), bp)], 1);
-    }
-    z = block_sum(z, shd, tid);
-    tq = block_sum(tq, shd, tid);                            // (the barriers also complete the histogram)
-    if (tid == 0) { pre->wg_z[blockIdx.x] = z; pre->wg_tq[blockIdx.x] = tq; if (blockIdx.x == 0) pre->mx = mx; }
-    for (int b = tid; b < SW_PBINS; b += 1024) pre->hist[blockIdx.x][b] = hist[b];
-}
-
-// Bin offsets and scatter in one launch: every workgroup adds up the histograms of all of them (the same 256 KB for
-// each: cheaper than a launch of its own for one workgroup to do it), scans the bins, and moves its slice's pairs to
-// where its share of each bin starts.  Workgroup 0 also leaves the bin starts and the row's sums for the walk.
-__global__ __launch_bounds__(1024) void sw_pre_scatter(const float *__restrict__ q0, const int32_t *__restrict__ parent, int M, int V,
-                                                       const float *__restrict__ es, float2 *__restrict__ eq_sorted, SwPre *pre)
-{
-    __shared__ double shd[16];
-    __shared__ int wsum[16];
-    __shared__ double part[2][SW_PRE_WGS];
-    __shared__ int cursor[SW_PBINS];
-    constexpr int PB = SW_PBINS / 1024;                      // bins per thread: PB * tid .. PB * tid + PB - 1
-    static_assert(PB == 2 || PB == 4, "a thread's bins are fetched as one int2 or int4");
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, me = blockIdx.x;
-    if (!sw_root_is_wide(parent, M, tid, shd)) return;
-    if (me == 0 && tid < SW_PRE_WGS) { part[0][tid] = pre->wg_z[tid]; part[1][tid] = pre->wg_tq[tid]; }
-    int c[PB], mb[PB];                                       // all workgroups; those before this one
-#pragma unroll
-    for (int k = 0; k < PB; ++k) { c[k] = 0; mb[k] = 0; }
-#pragma unroll
-    for (int w = 0; w < SW_PRE_WGS; ++w) {
-        int h[PB];
-        if constexpr (PB == 4) {
-            const int4 x = *reinterpret_cast<const int4 *>(&pre->hist[w][PB * tid]);
-            h[0] = x.x; h[1] = x.y; h[2] = x.z; h[3] = x.w;
-        } else {
-            const int2 x = *reinterpret_cast<const int2 *>(&pre->hist[w][PB * tid]);
-            h[0] = x.x; h[1] = x.y;
-        }
-#pragma unroll
-        for (int k = 0; k < PB; ++k) { mb[k] = w == me ? c[k] : mb[k]; c[k] += h[k]; }
-    }
-    int own = 0;
-#pragma unroll
-    for (int k = 0; k < PB; ++k) own += c[k];
-    int ci = own;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int co = __shfl_up(ci, off);
-        if (lane >= off) ci += co;
-    }
-    if (lane == 63) wsum[wv] = ci;
-    __syncthreads();
-    int cb = 0;
-    for (int w = 0; w < wv; ++w) cb += wsum[w];
-    int st[PB + 1];                                          // where the thread's bins start
-    st[0] = cb + ci - own;
-#pragma unroll
-    for (int k = 0; k < PB; ++k) st[k + 1] = st[k] + c[k];
-#pragma unroll
-    for (int k = 0; k < PB; ++k) cursor[PB * tid + k] = st[k] + mb[k];
-    if (me == 0) {
-#pragma unroll
-        for (int k = 0; k < PB; ++k) pre->start[PB * tid + k] = st[k];
-        if (tid == 1023) pre->start[SW_PBINS] = st[PB];
-        if (tid == 0) {
-            double z = 0.0, tq = 0.0;
-            for (int w = 0; w < SW_PRE_WGS; ++w) { z += part[0][w]; tq += part[1][w]; }
-            pre->z = z; pre->tq = tq;
-            pre->ready = 1;
-        }
-    }
-    __syncthreads();
-    int v0, v1;
-    sw_slice(V, me, v0, v1);
-    const SwBin bp = sw_bin_params(pre, pre->mx);
-    for (int vb = v0; vb < v1; vb += 4 * 1024) {             // four tokens per thread at a time, their loads issued together
-        float e[4], q[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int v = vb + tid + 1024 * k;
-            e[k] = es[v < v1 ? v : v0];
-            q[k] = q0[v < v1 ? v : v0];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int v = vb + tid + 1024 * k;
-            if (v < v1) {
-                const int pos = atomicAdd(&cursor[sw_bin_at(__fdiv_rn(q[k], e[k]), bp)], 1);
-                eq_sorted[pos] = make_float2(e[k], q[k]);
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(1024) void sw_pre_chunks(const int32_t *__restrict__ parent, int M, int V,
-                                                      const float2 *__restrict__ eq_sorted, SwPre *pre)
-{
-    __shared__ double shd[16];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    if (!sw_root_is_wide(parent, M, tid, shd)) return;
-    const int CH = 1 << sw_chunk_shift(V);
-    constexpr int PER = SW_BINS / (SW_PRE_WGS * 16);          // chunks per wavefront
-    if (CH == 64) {                                          // one pair per lane and chunk: the wavefront's loads all at once
-        float2 x[PER];
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = (blockIdx.x * 16 + wv + k * SW_PRE_WGS * 16) * 64 + lane;
-            x[k] = eq_sorted[i < V ? i : 0];
-            if (i >= V) x[k] = make_float2(0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const double se = wave_sum_f64((double)x[k].x), sq = wave_sum_f64((double)x[k].y);
-            const int c = blockIdx.x * 16 + wv + k * SW_PRE_WGS * 16;
-            if (lane == 0) { pre->chunk_e[c] = se; pre->chunk_q[c] = sq; }
-        }
-        return;
-    }
-    for (int c = blockIdx.x * 16 + wv; c < SW_BINS; c += SW_PRE_WGS * 16) {
-        double se = 0.0, sq = 0.0;
-        for (int i = c * CH + lane; i < min(c * CH + CH, V); i += 64) {
-            const float2 x = eq_sorted[i];
-            se += (double)x.x; sq += (double)x.y;
-        }
-        se = wave_sum_f64(se); sq = wave_sum_f64(sq);
-        if (lane == 0) { pre->chunk_e[c] = se; pre->chunk_q[c] = sq; }
-    }
-}
-
-// The window of sorted pairs [lo, hi), hi - lo <= SW_WIN, by 1024 threads: every thread's loads are issued before the
-// first is stored (a load and its store per loop trip is a round trip to the L2 per trip).
-__device__ __forceinline__ void load_window(float2 *win, const float2 *eq_sorted, int lo, int hi, int tid)
-{
-    static_assert(SW_WIN % 1024 == 0, "whole trips of the workgroup");
-    float2 t[SW_WIN / 1024];
-#pragma unroll
-    for (int q = 0; q < SW_WIN / 1024; ++q) {
-        const int i = lo + tid + 1024 * q;
-        t[q] = eq_sorted[i < hi ? i : lo];
-    }
-#pragma unroll
-    for (int q = 0; q < SW_WIN / 1024; ++q) {
-        const int i = lo + tid + 1024 * q;
-        if (i < hi) win[i - lo] = t[q];
-    }
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(1024) void stochastic_walk(const void *__restrict__ logits, const float *__restrict__ marg, int B,
-                                                        const int32_t *__restrict__ parent, const int32_t *__restrict__ token,
-                                                        int M, int V, const float *__restrict__ uniforms,
-                                                        float *__restrict__ es, float2 *__restrict__ eq_sorted,
-                                                        SwPre *__restrict__ pre, int32_t *path, int32_t *n_acc,
-                                                        uint32_t *flag)
-{
-    __shared__ double shd[16];
-    __shared__ float shf[16];
-    __shared__ double seg[1024];
-    __shared__ double chunkE[SW_BINS], chunkQ[SW_BINS];  // sums of e and q0 over the sorted pairs before chunk c
-    __shared__ int start[SW_PBINS + 1], cursor[SW_BINS];
-    __shared__ float2 win[SW_WIN + 256];                  // sorted pairs win_lo .. win_hi - 1 (the threshold only falls,
-                                                          // so the window is refilled towards lower positions)
-    __shared__ float2 child_eq[BTV_MAX_NODES];            // (e, q0) of node c's token, fetched for all nodes at once
-    __shared__ int kid_node[BTV_MAX_NODES];               // the current node's children in node order (prepared row only)
-    __shared__ float kid_u[BTV_MAX_NODES];
-    __shared__ float2 kid_eq[BTV_MAX_NODES];              // (e, q0) of child j's token
-    __shared__ double kid_invT[BTV_MAX_NODES], kid_lhs[BTV_MAX_NODES];    // 1/T when child j is tried; u * q_k[x] of its test
-    __shared__ struct { double alpha, beta, T; int next, accepted, reload_hi, done, nkids, wcount[4]; } fast;
-    const int tid = threadIdx.x;
-    int cur = -1, n = 0, ui = 0, d = 0;
-    for (;;) {
-        const size_t base = (size_t)(cur + 1) * V;
-        const float *q0 = marg + (size_t)(d < B ? d : 0) * V;    // (unused when d == B: no children there)
-        const bool vec4 = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(q0) & 15) == 0;
-        const int CS = sw_chunk_shift(V), CH = 1 << CS;           // sorted pairs per prefix-sum chunk
-        // (the passes are unrolled so that several loads are in flight: one load per iteration leaves a pass bound
-        // by the round trip to the L2)
-        const bool prepared = cur == -1 && pre->ready == 1;      // the root's row was sorted ahead of this kernel
-        double z = 0.0, tq = 0.0;
-        const bool has_q = d < B;
-        if (prepared) {
-            z = pre->z; tq = pre->tq;
-        } else {
-            float mx = -INFINITY;
-#pragma unroll 8
-            for (int v = tid; v < V; v += 1024) mx = fmaxf(mx, load_logit<BF16>(logits, base + v));
-            mx = block_max(mx, shf, tid);
-#pragma unroll 8
-            for (int v = tid; v < V; v += 1024) {
-                const float e = expf(load_logit<BF16>(logits, base + v) - mx);
-                es[v] = e; z += (double)e;
-                tq += has_q ? (double)q0[v] : 0.0;
-            }
-            z = block_sum(z, shd, tid);                          // (its barriers also publish es)
-            tq = block_sum(tq, shd, tid);
-        }
-        double alpha = 1.0 / z, beta = 0.0, T = tq;
-        int accepted = -1, untried = 0;
-        bool binned = false;
-        int win_lo = 0, win_hi = 0;                              // (empty)
-        auto scan_chunks = [&]() {                                // chunkE / chunkQ: per-chunk sums -> sums before the chunk
-            const int lane = tid & 63, wv = tid >> 6;
-            const double e0 = chunkE[2 * tid], e1 = chunkE[2 * tid + 1], q0s = chunkQ[2 * tid], q1s = chunkQ[2 * tid + 1];
-            double ei = e0 + e1, qi = q0s + q1s;
-            for (int off = 1; off < 64; off <<= 1) {
-                const double eo = __shfl_up(ei, off), qo = __shfl_up(qi, off);
-                if (lane >= off) { ei += eo; qi += qo; }
-            }
-            if (lane == 63) { seg[wv] = ei; seg[16 + wv] = qi; }
-            __syncthreads();
-            double eb = 0.0, qb = 0.0;
-            for (int w = 0; w < wv; ++w) { eb += seg[w]; qb += seg[16 + w]; }
-            const double ex = eb + ei - (e0 + e1), qxs = qb + qi - (q0s + q1s);
-            chunkE[2 * tid] = ex; chunkE[2 * tid + 1] = ex + e0;
-            chunkQ[2 * tid] = qxs; chunkQ[2 * tid + 1] = qxs + q0s;
-            __syncthreads();
-        };
-        if (prepared) {                                          // (prepared implies d == 0 < B)
-            {   // every load before the first store: one round trip to the L2, not one per loop trip
-                int sb[SW_PBINS / 1024];
-                double ce[SW_BINS / 1024], cq[SW_BINS / 1024];
-#pragma unroll
-                for (int k = 0; k < SW_PBINS / 1024; ++k) sb[k] = pre->start[tid + 1024 * k];
-#pragma unroll
-                for (int k = 0; k < SW_BINS / 1024; ++k) { ce[k] = pre->chunk_e[tid + 1024 * k]; cq[k] = pre->chunk_q[tid + 1024 * k]; }
-                if (tid == 0) start[SW_PBINS] = pre->start[SW_PBINS];
-#pragma unroll
-                for (int k = 0; k < SW_PBINS / 1024; ++k) start[tid + 1024 * k] = sb[k];
-#pragma unroll
-                for (int k = 0; k < SW_BINS / 1024; ++k) { chunkE[tid + 1024 * k] = ce[k]; chunkQ[tid + 1024 * k] = cq[k]; }
-            }
-            __syncthreads();
-            scan_chunks();
-            binned = true;
-        }
-        if (prepared) {
-            // ---- the sorted row is at hand: the children are tried by the first wavefront alone, out of LDS, with no
-            // workgroup barrier per rejection; the others only help to move the window of sorted pairs --------------
-            const int lane = tid & 63, wv = tid >> 6;
-            const SwBin bp = sw_bin_params(pre, pre->mx);
-            {   // the children in node order: (node, uniform), their tokens' (e, q0)
-                const bool mine = tid < M && parent[tid] == cur;
-                const unsigned long long bal = __builtin_amdgcn_ballot_w64(mine);
-                if (wv < 4 && lane == 0) fast.wcount[wv] = __builtin_popcountll(bal);
-                __syncthreads();
-                if (mine) {
-                    int j = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-                    for (int w = 0; w < wv; ++w) j += fast.wcount[w];
-                    const int tk = token[tid];
-                    kid_node[j] = tk >= 0 && tk < V ? tid : -1 - tid;      // (negative: not a vocabulary id)
-                    kid_u[j] = uniforms[ui + j];
-                    if (tk >= 0 && tk < V) child_eq[tid] = make_float2(es[tk], q0[tk]);
-                }
-                if (tid == 0) {
-                    fast.alpha = alpha; fast.beta = beta; fast.T = T;
-                    fast.next = 0; fast.accepted = -1; fast.done = 0;
-                    fast.nkids = fast.wcount[0] + fast.wcount[1] + fast.wcount[2] + fast.wcount[3];
-                }
-                __syncthreads();
-            }
-            auto recip = [](double x) {                           // 1/x to within a few ulp: hardware estimate, two Newton steps
-                double r = __builtin_amdgcn_rcp(x);
-                r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-                r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-                return r;
-            };
-            // T falls by the tried token's q0 whatever the test decides, so every child's 1/T and the left side of its
-            // test are known before the loop: an exclusive prefix sum over the children, 64 at a time
-            if (wv == 0) {
-                double carry = 0.0;
-                for (int j0 = 0; j0 < fast.nkids; j0 += 64) {
-                    const int j = j0 + lane;
-                    const int c = j < fast.nkids ? kid_node[j] : -1;
-                    const double qx = c >= 0 ? (double)child_eq[c].y : 0.0;
-                    double incl = qx;
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const double o = __shfl_up(incl, off);
-                        if (lane >= off) incl += o;
-                    }
-                    const double Tj = T - (carry + (incl - qx));
-                    if (j < fast.nkids) {
-                        const double invT = Tj > 0.0 ? recip(Tj) : 0.0;
-                        kid_eq[j] = c >= 0 ? child_eq[c] : make_float2(0.f, 0.f);
-                        kid_invT[j] = invT;
-                        kid_lhs[j] = (double)kid_u[j] * (qx * invT);
-                    }
-                    carry += __shfl(incl, 63);
-                }
-            }
-            __syncthreads();
-            for (;;) {
-                if (wv == 0) {
-                    int j = fast.next;
-                    const int nk = fast.nkids;
-                    int acc = -1, want_hi = -1;
-                    alpha = fast.alpha; beta = fast.beta; T = fast.T;
-                    // child j + 1's entries are read while child j is tested: nothing in them depends on the tests
-                    const int jf = max(min(j, nk - 1), 0);
-                    int c_nx = kid_node[jf];
-                    float2 own_nx = kid_eq[jf];
-                    double invT_nx = kid_invT[jf], lhs_nx = kid_lhs[jf];
-                    for (; j < nk; ++j) {
-                        const int c = c_nx;
-                        const float2 own = own_nx;
-                        const double invT = invT_nx, lhs = lhs_nx;
-                        {
-                            const int j1 = min(j + 1, nk - 1);
-                            c_nx = kid_node[j1]; own_nx = kid_eq[j1]; invT_nx = kid_invT[j1]; lhs_nx = kid_lhs[j1];
-                        }
-                        if (__builtin_expect(c < 0, 0)) {        // spent uniform, raised flag, nothing indexed
-                            if (lane == 0) atomicOr(flag, 64u);
-                            continue;
-                        }
-                        const double px = alpha * (double)own.x - beta * (double)own.y;
-                        if (__builtin_expect(lhs < (px > 0.0 ? px : 0.0), 0)) { acc = c; ++j; break; }
-                        const double b1 = beta + invT;
-                        const int b = sw_bin_at((float)(b1 > 0.0 ? alpha * recip(b1) : INFINITY), bp);
-                        const int p0 = start[b], p1 = start[b + 1];
-                        const int ch = min(p0 >> CS, SW_BINS - 1), lo = ch << CS;
-                        const double ce = chunkE[ch], cq = chunkQ[ch];      // (asked for ahead of the scan's reads)
-                        double zr = 0.0;
-                        if (__builtin_expect(p1 - lo <= SW_WIN, 1)) {
-                            if (__builtin_expect(lo < win_lo || p1 > win_hi, 0)) { want_hi = p1; break; }      // the others help to move the window
-                            // four reads in flight per trip, none behind a branch (one read, its arithmetic and the loop
-                            // branch per trip made a trip cost an LDS round trip: the larger part of a rejection)
-                            // (the reads run up to 255 entries past p1, into the pad behind the window: what they bring is
-                            // not used)
-                            double z4[4] = { 0.0, 0.0, 0.0, 0.0 };
-                            const float2 *wp = win + (lo - win_lo + lane);
-                            const int trips = (p1 - lo + 255) >> 8;
-                            for (int t = 0, i = lo + lane; t < trips; ++t, i += 256, wp += 256) {
-                                float2 x[4];
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) x[q] = wp[64 * q];
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) {
-                                    const double r = alpha * (double)x[q].x - b1 * (double)x[q].y;
-                                    z4[q] += i + 64 * q < p1 && r > 0.0 ? r : 0.0;
-                                }
-                            }
-                            zr = (z4[0] + z4[1]) + (z4[2] + z4[3]);
-                        } else {                                 // a bin larger than the window (ratios that nearly all coincide)
-                            for (int i = lo + lane; i < p1; i += 64) {
-                                const float2 x = eq_sorted[i];
-                                const double r = alpha * (double)x.x - b1 * (double)x.y;
-                                zr += r > 0.0 ? r : 0.0;
-                            }
-                        }
-                        zr = wave_sum_f64(zr);
-                        const double below = alpha * ce - b1 * cq;
-                        zr += below > 0.0 ? below : 0.0;
-                        if (__builtin_expect(zr > 0.0, 1)) { const double iz = recip(zr); alpha *= iz; beta = b1 * iz; }
-                    }
-                    if (lane == 0) {
-                        fast.alpha = alpha; fast.beta = beta; fast.T = T;
-                        fast.next = j; fast.accepted = acc; fast.reload_hi = want_hi;
-                        fast.done = want_hi < 0;
-                    }
-                }
-                __syncthreads();
-                if (fast.done) break;
-                win_hi = fast.reload_hi;
-                win_lo = max(win_hi - SW_WIN, 0);
-                load_window(win, eq_sorted, win_lo, win_hi, tid);
-                __syncthreads();
-            }
-            alpha = fast.alpha; beta = fast.beta; T = fast.T;
-            accepted = fast.accepted;
-            ui += fast.next;                                     // one uniform per child tried
-            __syncthreads();                                     // (fast is rewritten at the next node only after everyone has read it)
-        } else if (d < B) {
-            // one round trip for every child's own e and q0, instead of one per child inside the loop
-            for (int c = tid; c < M; c += 1024) {
-                const bool mine = parent[c] == cur;
-                untried += mine ? 1 : 0;
-                const int tk = token[c];
-                if (mine && tk >= 0 && tk < V) child_eq[c] = make_float2(es[tk], q0[tk]);
-            }
-            untried = (int)block_sum((double)untried, shd, tid);          // children of this node still to be tried
-            for (int c = 0; c < M; ++c) {
-                if (parent[c] != cur) continue;                  // uniform across the workgroup
-                const int tk = token[c];
-                const double u = (double)uniforms[ui++];
-                if (tk < 0 || tk >= V) {                         // not a vocabulary id: the child is rejected (its uniform is
-                    if (tid == 0) atomicOr(flag, 64u);           // spent), nothing is indexed with it, the data flag is raised
-                    --untried;
-                    continue;
-                }
-                const float2 own = child_eq[c];
-                const double invT = T > 0.0 ? 1.0 / T : 0.0, qx = (double)own.y;
-                const double px = alpha * (double)own.x - beta * qx;     // p_k of the child's token
-                if (u * (qx * invT) < (px > 0.0 ? px : 0.0)) { accepted = c; break; }
-                const double b1 = beta + invT;
-                --untried;
-                if (!binned && untried >= SW_BUILD_MIN) {         // enough tests may follow for the sort to pay
-                    // ---- counting sort of the (e, q0) pairs by the bin of q0/e, then prefix sums over the sorted pairs ----
-                    for (int b = tid; b < SW_BINS; b += 1024) start[b] = 0;
-                    __syncthreads();
-                    for (int v = tid; v < V; v += 1024) atomicAdd(&start[sw_bin(__fdiv_rn(q0[v], es[v]))], 1);
-                    __syncthreads();
-                    {   // exclusive scan of the bin counts (two bins per thread)
-                        const int c0 = start[2 * tid], c1 = start[2 * tid + 1];
-                        int ci = c0 + c1;
-                        for (int off = 1; off < 64; off <<= 1) {
-                            const int co = __shfl_up(ci, off);
-                            if ((tid & 63) >= off) ci += co;
-                        }
-                        __syncthreads();
-                        if ((tid & 63) == 63) cursor[tid >> 6] = ci;
-                        __syncthreads();
-                        int cb = 0;
-                        for (int w = 0; w < (tid >> 6); ++w) cb += cursor[w];
-                        __syncthreads();
-                        const int cx = cb + ci - (c0 + c1);          // exclusive prefix of this thread's first bin
-                        start[2 * tid] = cx; start[2 * tid + 1] = cx + c0;
-                        cursor[2 * tid] = cx; cursor[2 * tid + 1] = cx + c0;
-                        if (tid == 1023) start[SW_BINS] = cx + c0 + c1;
-                    }
-                    __syncthreads();
-                    for (int v = tid; v < V; v += 1024) {
-                        const float e = es[v], q = q0[v];
-                        const int pos = atomicAdd(&cursor[sw_bin(__fdiv_rn(q, e))], 1);
-                        eq_sorted[pos] = make_float2(e, q);          // one 8-byte store: the scattered stores are what the sort costs
-                    }
-                    __syncthreads();
-                    {   // chunk c = sorted positions c*CH .. c*CH + CH - 1 (CH a power of two from 64 up, at most SW_BINS chunks): a
-                        // wave sums a chunk with coalesced loads; then an exclusive scan over the chunk sums
-                        const int lane = tid & 63, wv = tid >> 6;
-                        for (int c = wv; c < SW_BINS; c += 16) {
-                            double se = 0.0, sq = 0.0;
-                            for (int i = c * CH + lane; i < min(c * CH + CH, V); i += 64) {
-                                const float2 x = eq_sorted[i];
-                                se += (double)x.x; sq += (double)x.y;
-                            }
-                            for (int off = 32; off >= 1; off >>= 1) { se += __shfl_xor(se, off); sq += __shfl_xor(sq, off); }
-                            if (lane == 0) { chunkE[c] = se; chunkQ[c] = sq; }
-                        }
-                        __syncthreads();
-                    }
-                    scan_chunks();
-                    binned = true;
-                }
-                double zr = 0.0;                                 // residual max(p_k - q_k, 0): its sum
-                auto resid = [&](float ev, float qv) {
-                    const double r = alpha * (double)ev - b1 * (double)qv;
-                    zr += r > 0.0 ? r : 0.0;
-                };
-                if (binned) {
-                    // pairs before the threshold's bin all contribute: whole chunks through the prefix sums, the rest
-                    // of the chunk that holds the bin's start one by one; the threshold's own bin is scanned exactly
-                    const int b = sw_bin((float)(alpha / b1));   // b1 = 0: the threshold is +inf, every finite ratio is below it
-                    const int p0 = start[b], p1 = start[b + 1];
-                    const int ch = min(p0 >> CS, SW_BINS - 1), lo = ch << CS;
-                    if (p1 - lo <= SW_WIN) {
-                        if (lo < win_lo || p1 > win_hi) {        // (uniform) refill: the window ends at this bin's end
-                            __syncthreads();
-                            win_hi = p1;
-                            win_lo = max(p1 - SW_WIN, 0);
-                            load_window(win, eq_sorted, win_lo, win_hi, tid);
-                            __syncthreads();
-                        }
-                        for (int i = lo + tid; i < p1; i += 1024) { const float2 x = win[i - win_lo]; resid(x.x, x.y); }
-                    } else {                                     // a bin larger than the window (ratios that nearly all coincide)
-                        for (int i = lo + tid; i < p1; i += 1024) { const float2 x = eq_sorted[i]; resid(x.x, x.y); }
-                    }
-                    zr = block_sum(zr, shd, tid);
-                    const double below = alpha * chunkE[ch] - b1 * chunkQ[ch];
-                    zr += below > 0.0 ? below : 0.0;
-                } else {
-                    if (vec4) {
-#pragma unroll 4
-                        for (int v = tid * 4; v < V; v += 4096) {
-                            const float4 a = *reinterpret_cast<const float4 *>(es + v), q = *reinterpret_cast<const float4 *>(q0 + v);
-                            resid(a.x, q.x); resid(a.y, q.y); resid(a.z, q.z); resid(a.w, q.w);
-                        }
-                    } else {
-                        for (int v = tid; v < V; v += 1024) resid(es[v], q0[v]);
-                    }
-                    zr = block_sum(zr, shd, tid);
-                }
-                if (zr > 0.0) { const double iz = 1.0 / zr; alpha *= iz; beta = b1 * iz; }
-                T -= qx;                                         // drafted without replacement
-            }
-        }
-        if (accepted >= 0) {
-            if (tid == 0) path[n] = accepted;
-            cur = accepted; ++n; ++d;
-            __syncthreads();                                     // everyone is done with es before it is rewritten
-            continue;
-        }
-        // The bonus token is drawn by the kernel that follows (a pass over the vocabulary in fp64 is bound by the
-        // arithmetic of the one CU this kernel runs on: 16 us of its time): the residual's parameters, the uniform
-        // and the row go to the workspace.
-        if (tid == 0) {
-            pre->b_alpha = alpha; pre->b_beta = beta; pre->b_u = (double)uniforms[ui];
-            pre->b_has_q = has_q ? 1 : 0; pre->b_depth = has_q ? d : 0;
-            pre->b_count = 0;
-            *n_acc = n;
-        }
-        break;
-    }
-}
-
-// Bonus draw: smallest v with cumsum(p_k)[v] > u, p_k = max(alpha e - beta q0, 0).  Wavefront g of SW_PRE_WGS * 16 owns
-// a contiguous stretch of the vocabulary (whole wave instructions of 256 tokens, four per lane, when the rows allow
-// 16-byte loads) and leaves its total and its last positive token; the workgroup that counts itself in last picks
-// the token (sw_bonus_pick) on its first wavefront.  Totals, last tokens and the counter cross workgroups as relaxed
-// device-scope atomics, the counter only after the stores are acknowledged (the L2s of the XCDs are not coherent
-// with each other).
-__device__ __forceinline__ double sw_resid(double alpha, double beta, bool has_q, float ev, float qv)
-{
-    const double x = has_q ? alpha * (double)ev - beta * (double)qv : alpha * (double)ev;
-    return x > 0.0 ? x : 0.0;
-}
-
-__device__ __forceinline__ void sw_stretch(int V, bool wide, int g, int &w0, int &w1)
-{
-    const int waves = SW_PRE_WGS * 16;
-    const int stretch = wide ? ((V + waves - 1) / waves + 255) / 256 * 256 : ((V + waves - 1) / waves + 63) / 64 * 64;
-    w0 = (int)min((long long)g * stretch, (long long)V);
-    w1 = min(w0 + stretch, V);
-}
-
-__device__ void sw_bonus_pick(const float *__restrict__ marg, int V, const float *__restrict__ es, SwPre *pre, int32_t *bonus,
-                              int lane);
-
-__global__ __launch_bounds__(1024) void sw_bonus_draw(const float *__restrict__ marg, int V, const float *__restrict__ es, SwPre *pre,
-                                                      int32_t *bonus)
-{
-    __shared__ int is_last;
-    const int tid = threadIdx.x, lane = tid & 63, g = blockIdx.x * 16 + (tid >> 6);
-    const double alpha = pre->b_alpha, beta = pre->b_beta;
-    const bool has_q = pre->b_has_q != 0;
-    const float *q0 = marg + (size_t)pre->b_depth * V;
-    const bool wide = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(q0) & 15) == 0 && (reinterpret_cast<uintptr_t>(es) & 15) == 0;
-    int w0, w1;
-    sw_stretch(V, wide, g, w0, w1);
-    double loc = 0.0;
-    int lp = -1;
-    if (wide) {
-        const int trips = (w1 - w0 + 255) / 256;                  // (wave-uniform)
-        for (int t0 = 0; t0 < trips; t0 += 4) {                   // the loads of a trip issued together, none behind a branch
-            float4 a[4], q[4];
-            int vv[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int v = w0 + (t0 + k) * 256 + lane * 4;
-                vv[k] = t0 + k < trips && v < w1 ? v : -1;
-                a[k] = *reinterpret_cast<const float4 *>(es + (vv[k] < 0 ? 0 : v));
-                q[k] = has_q ? *reinterpret_cast<const float4 *>(q0 + (vv[k] < 0 ? 0 : v)) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool ok = vv[k] >= 0;
-                const double x0 = ok ? sw_resid(alpha, beta, has_q, a[k].x, q[k].x) : 0.0, x1 = ok ? sw_resid(alpha, beta, has_q, a[k].y, q[k].y) : 0.0,
-                             x2 = ok ? sw_resid(alpha, beta, has_q, a[k].z, q[k].z) : 0.0, x3 = ok ? sw_resid(alpha, beta, has_q, a[k].w, q[k].w) : 0.0;
-                loc += (x0 + x1) + (x2 + x3);
-                lp = x3 > 0.0 ? vv[k] + 3 : x2 > 0.0 ? vv[k] + 2 : x1 > 0.0 ? vv[k] + 1 : x0 > 0.0 ? vv[k] : lp;
-            }
-        }
-    } else {
-        for (int v = w0 + lane; v < w1; v += 64) {
-            const double x = sw_resid(alpha, beta, has_q, es[v], has_q ? q0[v] : 0.f);
-            loc += x;
-            lp = x > 0.0 ? v : lp;
-        }
-    }
-    loc = wave_sum_f64(loc);
-    for (int off = 32; off >= 1; off >>= 1) lp = max(lp, __shfl_xor(lp, off));
-    if (lane == 0) {
-        __hip_atomic_store(reinterpret_cast<unsigned long long *>(pre->b_tot) + g, (unsigned long long)__double_as_longlong(loc),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(pre->b_last + g, lp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) is_last = __hip_atomic_fetch_add(&pre->b_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == SW_PRE_WGS - 1;
-    __syncthreads();
-    if (is_last && tid < 64) sw_bonus_pick(marg, V, es, pre, bonus, tid);
-}
-
-// One wavefront: the totals in order tell which stretch holds the crossing; that stretch is looked at again, a wave
-// instruction's worth of tokens at a time: its total, then the lanes' prefix inside it, then the token inside the lane.
-__device__ void sw_bonus_pick(const float *__restrict__ marg, int V, const float *__restrict__ es, SwPre *pre, int32_t *bonus,
-                              int lane)
-{
-    constexpr int WAVES = SW_PRE_WGS * 16, PER = WAVES / 64;
-    const double alpha = pre->b_alpha, beta = pre->b_beta, u = pre->b_u;
-    const bool has_q = pre->b_has_q != 0;
-    const float *q0 = marg + (size_t)pre->b_depth * V;
-    const bool wide = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(q0) & 15) == 0 && (reinterpret_cast<uintptr_t>(es) & 15) == 0;
-    // lane l holds stretches PER * l .. PER * l + PER - 1: sums before each of them, added in stretch order
-    double t[PER];
-    int lastpos = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        t[k] = __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<unsigned long long *>(pre->b_tot) + PER * lane + k,
-                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        lastpos = max(lastpos, __hip_atomic_load(pre->b_last + PER * lane + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    }
-    for (int off = 32; off >= 1; off >>= 1) lastpos = max(lastpos, __shfl_xor(lastpos, off));
-    double own = 0.0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) own += t[k];
-    double incl = own;
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(incl, off);
-        if (lane >= off) incl += o;
-    }
-    double before = incl - own;
-    int gsel = INT_MAX;
-    double bsel = 0.0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        if (gsel == INT_MAX && u >= before && u < before + t[k]) { gsel = PER * lane + k; bsel = before; }
-        before += t[k];
-    }
-    const unsigned long long has = __builtin_amdgcn_ballot_w64(gsel != INT_MAX);
-    int found = INT_MAX;
-    if (has != 0ull) {                                           // (uniform) none if u is past the total
-        const int src = __builtin_ctzll(has);
-        const int g = __shfl(gsel, src);
-        double running = __shfl(bsel, src);
-        int w0, w1;
-        sw_stretch(V, wide, g, w0, w1);
-        int hit = INT_MAX;
-        if (wide) {
-            for (int g0 = w0; g0 < w1 && hit == INT_MAX; g0 += 256) {
-                const int v = g0 + lane * 4;
-                const bool ok = v < w1;
-                const float4 a = *reinterpret_cast<const float4 *>(es + (ok ? v : 0));
-                const float4 q = has_q ? *reinterpret_cast<const float4 *>(q0 + (ok ? v : 0)) : make_float4(0.f, 0.f, 0.f, 0.f);
-                const double x0 = ok ? sw_resid(alpha, beta, has_q, a.x, q.x) : 0.0, x1 = ok ? sw_resid(alpha, beta, has_q, a.y, q.y) : 0.0,
-                             x2 = ok ? sw_resid(alpha, beta, has_q, a.z, q.z) : 0.0, x3 = ok ? sw_resid(alpha, beta, has_q, a.w, q.w) : 0.0;
-                double inc = (x0 + x1) + (x2 + x3);
-                const double mine_sum = inc;
-                const double tot = wave_sum_f64(inc);
-                if (running + tot > u) {                         // (uniform) the crossing lies in these 256 tokens
-                    for (int off = 1; off < 64; off <<= 1) {     // inclusive prefix over the lanes
-                        const double o = __shfl_up(inc, off);
-                        if (lane >= off) inc += o;
-                    }
-                    const double excl = running + (inc - mine_sum);
-                    int mine = INT_MAX;                          // first of this lane's four tokens whose cumulative sum passes u
-                    if (ok) {
-                        if (excl + x0 > u) mine = v;
-                        else if (excl + (x0 + x1) > u) mine = v + 1;
-                        else if (excl + ((x0 + x1) + x2) > u) mine = v + 2;
-                        else if (excl + ((x0 + x1) + (x2 + x3)) > u) mine = v + 3;
-                    }
-                    for (int off = 32; off >= 1; off >>= 1) mine = min(mine, __shfl_xor(mine, off));
-                    if (mine != INT_MAX) hit = mine;             // (else rounding: the crossing is the next positive token)
-                }
-                running += tot;
-            }
-        } else {
-            for (int v0 = w0; v0 < w1 && hit == INT_MAX; v0 += 64) {
-                const int v = v0 + lane;
-                double x = v < w1 ? sw_resid(alpha, beta, has_q, es[v], has_q ? q0[v] : 0.f) : 0.0;
-                for (int off = 1; off < 64; off <<= 1) {         // inclusive prefix over the 64 tokens
-                    const double o = __shfl_up(x, off);
-                    if (lane >= off) x += o;
-                }
-                const unsigned long long over = __builtin_amdgcn_ballot_w64(v < w1 && running + x > u);
-                if (over) hit = v0 + __builtin_ctzll(over);
-                running += __shfl(x, 63);
-            }
-        }
-        // rounding left the crossing just past the stretch
-        found = hit != INT_MAX ? hit : max(__hip_atomic_load(pre->b_last + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0);
-    }
-    if (lane == 0) *bonus = found == INT_MAX ? lastpos : found;
-}
-
 // workgroups of the one-launch greedy kernel: OL_WAVES units each, every unit once
 int greedy_wgs(int M, int V)
 {
@@ -1705,7 +819,7 @@ extern "C" {
 size_t btv_tree_accept_workspace(int M, int V, int stochastic)
 {
     if (M < 1 || M > BTV_MAX_NODES || V < 1) return 0;
-    if (stochastic) return BTV_WS_HEADER + 3 * btv_align_up((size_t)V * 4, BTV_WS_ALIGN) + btv_align_up(sizeof(SwPre), BTV_WS_ALIGN);
+    if (stochastic) return btv_stochastic_workspace(V);
     const int chunks = (V + WCHUNK - 1) / WCHUNK;
     return BTV_WS_HEADER + btv_align_up((size_t)greedy_wgs(M, V) * ol_slots_per_wg(chunks) * sizeof(unsigned long long), BTV_WS_ALIGN);
 }
@@ -1802,45 +916,6 @@ int btv_tree_accept_greedy_batch(const void *logits, int dtype, const int32_t *p
     BTV_HIP(hipGetLastError());
     hipLaunchKernelGGL(greedy_walk, dim3(batch), dim3(256), 0, st, part, chunks, parent, token, M_max, path, n_acc, bonus,
                        argmax_out, q_offset, total_M, static_cast<uint32_t *>(ws));
-    BTV_HIP(hipGetLastError());
-    return BTV_OK;
-}
-
-int btv_tree_accept_stochastic(const void *logits, int dtype, const float *marginals, int B, const int32_t *parent,
-                               const int32_t *token, int M, int V, const float *uniforms, int32_t *path,
-                               int32_t *n_acc, int32_t *bonus, void *ws, size_t ws_bytes, void *stream)
-{
-    int rc = check_accept(logits, dtype, parent, token, M, V, path, n_acc, bonus);
-    if (rc) return rc;
-    BTV_REQUIRE(marginals && uniforms, "null pointer");
-    BTV_REQUIRE(B >= 1 && B <= BTV_MAX_DEPTH, "B=%d outside [1,%d]", B, BTV_MAX_DEPTH);
-    rc = btv_check_ws(ws, ws_bytes, btv_tree_accept_workspace(M, V, 1));
-    if (rc) return rc;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t vb = btv_align_up((size_t)V * 4, BTV_WS_ALIGN);
-    float *es = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
-    float2 *eq_sorted = reinterpret_cast<float2 *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER + vb);
-    SwPre *pre = reinterpret_cast<SwPre *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER + 3 * vb);
-    uint32_t *flag = static_cast<uint32_t *>(ws);
-    // the root's row, prepared by many workgroups when the root has a wide fan (each kernel finds that out itself)
-    if (dtype == BTV_BF16) {
-        hipLaunchKernelGGL(sw_pre_max<true>, dim3(SW_PRE_WGS), dim3(1024), 0, st, logits, marginals, parent, M, V, pre);
-        hipLaunchKernelGGL(sw_pre_exp<true>, dim3(SW_PRE_WGS), dim3(1024), 0, st, logits, marginals, parent, M, V, es, pre);
-    } else {
-        hipLaunchKernelGGL(sw_pre_max<false>, dim3(SW_PRE_WGS), dim3(1024), 0, st, logits, marginals, parent, M, V, pre);
-        hipLaunchKernelGGL(sw_pre_exp<false>, dim3(SW_PRE_WGS), dim3(1024), 0, st, logits, marginals, parent, M, V, es, pre);
-    }
-    hipLaunchKernelGGL(sw_pre_scatter, dim3(SW_PRE_WGS), dim3(1024), 0, st, marginals, parent, M, V, es, eq_sorted, pre);
-    hipLaunchKernelGGL(sw_pre_chunks, dim3(SW_PRE_WGS), dim3(1024), 0, st, parent, M, V, eq_sorted, pre);
-    BTV_HIP(hipGetLastError());
-    if (dtype == BTV_BF16)
-        hipLaunchKernelGGL(stochastic_walk<true>, dim3(1), dim3(1024), 0, st, logits, marginals, B, parent, token, M, V,
-                           uniforms, es, eq_sorted, pre, path, n_acc, flag);
-    else
-        hipLaunchKernelGGL(stochastic_walk<false>, dim3(1), dim3(1024), 0, st, logits, marginals, B, parent, token, M, V,
-                           uniforms, es, eq_sorted, pre, path, n_acc, flag);
-    // the bonus token: per-wavefront totals of the residual on 32 workgroups, the last of which finds the crossing
-    hipLaunchKernelGGL(sw_bonus_draw, dim3(SW_PRE_WGS), dim3(1024), 0, st, marginals, V, es, pre, bonus);
     BTV_HIP(hipGetLastError());
     return BTV_OK;
 }

@@ -1,0 +1,893 @@
+// Stochastic acceptance on the GPU (gfx950): token-level rejection walk at temperature 1 (App. C "Acceptance", Sec. 2.1).
+//
+// The scalar form of a node.  With e[v] = exp(logit[v] - max), q[v] = the draft marginal of the depth and T = the draft
+// mass not tried yet, the target distribution after some rejections is  p[v] = max(e[v] - s q[v], 0) / G(s)  with
+//     G(s) = sum_v max(e[v] - s q[v], 0)        (s = 0 at first: the softmax)
+// and the draft distribution of the untried tokens q[v] / T (a rejected token has p < q / T, so its residual is zero
+// from then on and the same formula covers it).  A child with token x and uniform u is accepted iff
+// u q[x] / T < p[x]; a rejection takes max(p - q / T, 0), which is  s <- s + G(s) / T,  T <- T - q[x]  (s stays where
+// the new residual would be all zero).  All of s, G, T and the sums behind them are fp64; e is one fp32 exponential per token.
+//
+// One launch of G workgroups walks the tree together: workgroup w owns a contiguous slice of the vocabulary, and a
+// thread keeps the (e, q) of its own tokens in registers for as long as the walk stays at a node.  What a node needs from
+// all of them (row maximum and sums, one G(s) per rejection) is exchanged in the workspace: every workgroup leaves
+// its part in words of its own, (tag << 32 | 32 bits of payload) so that a word says by itself whether it is this
+// exchange's, and every workgroup reads all parts and does the same arithmetic on them in the same order, so that they
+// all take the same decisions and nobody has to be told.  An exchange is one store and one load at the memory side
+// (relaxed device-scope atomics: the L2s of the 8 XCDs are not coherent with each other), about 2 us; two sets of words in turn are
+// enough, because a workgroup writes exchange i + 2 only after it has read all of exchange i + 1, which everybody
+// wrote after reading exchange i.  Tags count on from call to call (`base` in the workspace), so words are never cleared.
+// The slices are small enough for all workgroups to be on the chip at once (at most 64 of them on 256 CUs); a wait ends
+// after `wait_ticks` of the wall clock all the same, raises the data flag and ends the kernel.
+//
+// A wide fan is not walked one exchange per rejection.  s_{k+1} = s_k + G(s_k) / T_k is a recurrence in one scalar, T_k is known
+// beforehand, and G is convex and piecewise linear, G(s) = E - s Q with E, Q the sums of e and q over the tokens with
+// e / q > s.  So all of s_1 .. s_K are found at once by Newton's method on the whole sequence: E and Q are evaluated at
+// guesses for all s_k in one exchange, after which the recurrence is affine and is solved by a prefix scan; the guesses come from a table of
+// G at 256 points (one exchange).  The error squares with every exchange (measured on normal logits and marginals:
+// 5e-5 after the table, 1e-9 after one, rounding after two), and the sequence is taken when no s_k moved by more than
+// 1e-7 of itself, i.e. when what is left is below 1e-13; anything that does not converge is walked one by one.
+// For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
+//
+// What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
+// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 57 us against
+// one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
+// levels, bf16: 860 .. 1280 -> 35 .. 44 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
+// tokens instead of 2048 (half the workgroups): 54 and 47 us at the same two.
+#include "btv_common.h"
+
+#include <algorithm>
+#include <climits>
+
+namespace {
+
+typedef unsigned long long u64;
+
+constexpr int SA_T = 1024, SA_WAVES = SA_T / 64;
+constexpr int SA_MAX_WGS = 64;                          // slices: one lane of a wavefront per workgroup when parts are collected
+constexpr int SA_BINS = 1024;                           // bins of e / q, 32 per binade upwards from the current s
+constexpr int SA_GRID = 256;                            // points of the table that the first guesses come from
+constexpr int SA_PLANE = BTV_MAX_NODES;                 // points of an exchange: word i of point k at SA_PLANE * i + k
+constexpr int SA_WORDS = 4 * BTV_MAX_NODES;             // words of one workgroup's part: two doubles per point
+constexpr int SA_CHAIN = 4;                             // rows of a first-child chain that are read and exchanged together
+constexpr int SA_CHAIN_FAN = 8;                         // children up to which a node's first child is worth reading ahead (it is one of
+                                                        // several that the draft likes about as well, otherwise)
+constexpr int SA_DIRECT = 3;                            // rejections that are walked one by one in any case, one less per 32 children
+                                                        // (a node of many children has no likely one among its first)
+constexpr int SA_BATCH_MIN = 10;                        // children left from which the rest is solved at once (the price of ten exchanges)
+constexpr long long SA_WAIT_TICKS = 100000000ll;        // one second of the 100 MHz wall clock
+static_assert(SA_PLANE * 4 <= SA_WORDS && SA_GRID <= SA_PLANE, "all words of an exchange fit");
+
+struct SaParams {
+    const void *logits;
+    const float *marg, *uniforms;
+    const int32_t *parent, *token;
+    int32_t *path, *n_acc, *bonus;
+    uint32_t *flag, *base;
+    u64 *slots;                                         // [2][G][SA_WORDS]
+    int B, M, V, G, per;                                // per: tokens of a slice
+    long long wait_ticks;
+};
+
+// Sum of x over the wavefront, returned in every lane: quad swaps, row mirrors, then the row totals travel down the
+// rows (DPP moves of the two halves; lanes a step does not write add zero).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, true);
+    return x + __longlong_as_double(((long long)(uint32_t)hi << 32) | (long long)(uint32_t)lo);
+}
+__device__ __forceinline__ double wave_sum(double x)
+{
+    x = dpp_add<0xB1, 0xF>(x);      // quad_perm [1,0,3,2]
+    x = dpp_add<0x4E, 0xF>(x);      // quad_perm [2,3,0,1]
+    x = dpp_add<0x141, 0xF>(x);     // row_half_mirror
+    x = dpp_add<0x140, 0xF>(x);     // row_mirror: every lane holds its row's total
+    x = dpp_add<0x142, 0xA>(x);     // row_bcast15 into rows 1 and 3
+    x = dpp_add<0x143, 0xC>(x);     // row_bcast31 into rows 2 and 3: lane 63 holds the total
+    const long long b = __double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (long long)lo);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_max(float x)
+{
+    return fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp((int)0xFF800000u, __float_as_int(x), CTRL, ROW_MASK, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float x)
+{
+    x = dpp_max<0xB1, 0xF>(x);
+    x = dpp_max<0x4E, 0xF>(x);
+    x = dpp_max<0x141, 0xF>(x);
+    x = dpp_max<0x140, 0xF>(x);
+    x = dpp_max<0x142, 0xA>(x);
+    x = dpp_max<0x143, 0xC>(x);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+// Inclusive prefix sum over the lanes.
+__device__ __forceinline__ double wave_scan(double x, int lane)
+{
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(x, off);
+        if (lane >= off) x += o;
+    }
+    return x;
+}
+// Composition of the affine maps of lanes 0 .. lane - 1 (lane 0 first): x -> A x + B.
+template <typename F>
+__device__ __forceinline__ void wave_affine_before(F a, F b, int lane, F &A, F &B)
+{
+    for (int off = 1; off < 64; off <<= 1) {
+        const F ao = __shfl_up(a, off), bo = __shfl_up(b, off);
+        if (lane >= off) { b = a * bo + b; a = a * ao; }
+    }
+    A = __shfl_up(a, 1); B = __shfl_up(b, 1);
+    if (lane == 0) { A = (F)1; B = (F)0; }
+}
+
+template <bool BF16>
+__device__ __forceinline__ float load_logit(const void *logits, size_t idx)
+{
+    if (BF16) return __uint_as_float((uint32_t)static_cast<const uint16_t *>(logits)[idx] << 16);
+    return static_cast<const float *>(logits)[idx];
+}
+
+// N tokens of a row in pieces of four, v + step * i .. + 3 for i < N / 4; those from v1 on come as `pad`.  vec: the row allows
+// whole pieces (then v and v1 are multiples of four, and a piece is in or out).  All loads are issued before the first is
+// looked at.
+template <bool BF16, int N>
+__device__ __forceinline__ void load_tokens(const void *row, int v, int step, int v1, bool vec, float pad, float (&x)[N])
+{
+    if (vec) {
+        if constexpr (BF16) {
+            uint2 w[N / 4];
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) w[i] = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(row) + (v + step * i < v1 ? v + step * i : 0));
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) {
+                x[4 * i] = __uint_as_float(w[i].x << 16); x[4 * i + 1] = __uint_as_float(w[i].x & 0xFFFF0000u);
+                x[4 * i + 2] = __uint_as_float(w[i].y << 16); x[4 * i + 3] = __uint_as_float(w[i].y & 0xFFFF0000u);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) {
+                const float4 w = *reinterpret_cast<const float4 *>(static_cast<const float *>(row) + (v + step * i < v1 ? v + step * i : 0));
+                x[4 * i] = w.x; x[4 * i + 1] = w.y; x[4 * i + 2] = w.z; x[4 * i + 3] = w.w;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int t = v + step * (i / 4) + i % 4;
+            x[i] = load_logit<BF16>(row, t < v1 ? t : 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = v + step * (i / 4) + i % 4 < v1 ? x[i] : pad;
+}
+
+// e^x for x <= 0 to about one ulp: 2^(x log2(e)) with the rounding of the product, and of the constant, brought back in to
+// first order (expf spends two thirds of its instructions on arguments that do not occur here).  Below 2^-126: 0.
+__device__ __forceinline__ float exp_neg(float x)
+{
+    const float t = x * 1.44269502f;                    // log2(e) = 1.44269502 + 1.925963e-8
+    const float lo = fmaf(x, 1.44269502f, -t) + x * 1.92596299e-8f;
+    const float y = __builtin_amdgcn_exp2f(t);
+    return t > -1000.f ? fmaf(y, lo * 0.693147182f, y) : 0.f;
+}
+
+// Bin of a ratio e / q, descending: bin 0 holds the largest (NaN and inf too), 32 bins per binade upwards from b0; what lies
+// below b0 comes out from SA_BINS on.
+__device__ __forceinline__ int sa_bin(float r, int b0)
+{
+    return SA_BINS - 1 - min((int)((__float_as_uint(r) & 0x7FFFFFFFu) >> 18) - b0, SA_BINS - 1);
+}
+
+__device__ __forceinline__ void put_u32(u64 *p, uint32_t tag, uint32_t x)
+{
+    __hip_atomic_store(p, ((u64)tag << 32) | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_f64(u64 *lo, u64 *hi, uint32_t tag, double x)
+{
+    const u64 b = (u64)__double_as_longlong(x);
+    put_u32(lo, tag, (uint32_t)b);
+    put_u32(hi, tag, (uint32_t)(b >> 32));
+}
+__device__ __forceinline__ double get_f64(u64 lo, u64 hi)
+{
+    return __longlong_as_double((long long)(((hi & 0xFFFFFFFFull) << 32) | (lo & 0xFFFFFFFFull)));
+}
+// N words of each of R workgroups' parts, R * N loads in flight, once they all carry the tag: workgroup first + k * step,
+// k < R, at offset `at` of its part and every STEP words from there; workgroups from G on (and lanes with want = false) are left out.  False: the limit
+// has passed.  A wavefront sleeps between two looks, and where many words are exchanged only one wavefront of a
+// workgroup looks (at one word of each part) until everybody is there: sixteen wavefronts of every workgroup asking for the same
+// lines without a pause kept the stores to those lines from ever getting through.
+template <int R, int N, int STEP = 1>
+__device__ __forceinline__ bool take(const u64 *set, int first, int step, int G, int at, bool want, uint32_t tag, u64 (&w)[R][N],
+                                     long long wait_ticks)
+{
+    const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const u64 *p = set + (size_t)(first + k * step) * SA_WORDS + at;
+            const bool in = want && first + k * step < G;
+#pragma unroll
+            for (int i = 0; i < N; ++i) w[k][i] = in ? __hip_atomic_load(p + i * STEP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
+        }
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int i = 0; i < N; ++i) ok = ok && (uint32_t)(w[k][i] >> 32) == tag;
+        if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return true;
+        if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > wait_ticks) return false;
+        __builtin_amdgcn_s_sleep(2);
+    }
+}
+
+template <int PT>
+struct SaShared {
+    static constexpr int BT = PT < 4 ? 4 : PT;
+    int par[BTV_MAX_NODES], tok[BTV_MAX_NODES];
+    int first[BTV_MAX_NODES + 1], fan[BTV_MAX_NODES + 1];       // first child of node c (INT_MAX: none), and how many, at c + 1
+    float uni[BTV_MAX_NODES + 1];
+    int kcnt[SA_CHAIN][BTV_MAX_NODES / 64];             // children of chain row r among the nodes of wavefront w
+    int kid_node[BTV_MAX_NODES], kid_tok[BTV_MAX_NODES];
+    float kid_x[BTV_MAX_NODES];                         // the chain rows' children, row after row, in node order
+    double kid_q[BTV_MAX_NODES], kid_e[BTV_MAX_NODES];
+    float wm[SA_WAVES];
+    double wz[SA_WAVES], wq[SA_WAVES];
+    double z[SA_CHAIN], tq[SA_CHAIN], g, s_hi;
+    float Mx[SA_CHAIN][SA_MAX_WGS];                     // the slices' maxima, exp(slice maximum - maximum), parts of G
+    double F[SA_CHAIN][SA_MAX_WGS], GW[SA_CHAIN + 1][SA_MAX_WGS];
+    int acc0[SA_CHAIN];
+    int wsum[SA_WAVES];
+    int dead, status, acc, pick, last;
+    float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
+    double pt[BTV_MAX_NODES], ptG[BTV_MAX_NODES], invT[BTV_MAX_NODES];
+    double sE[SA_PLANE], sQ[SA_PLANE];
+    int bin_at[SA_BINS + 1];                            // where bin b (0 = largest ratios) starts
+    double cE[SA_T + 1], cQ[SA_T + 1];                  // sums over the sorted positions before PT * c
+    float2 sorted[SA_T * BT];                           // (e, q) of the slice, e / q descending by bin (last: what lies
+                                                        // below 64 KB is addressed with the instructions' own offsets)
+};
+
+// A walk that goes down mostly takes first children (they have the largest draft probability), so the rows of a node, its
+// first child, that one's first child and so on, SA_CHAIN of them, are read and exchanged together: wavefronts 4 r ..
+// 4 r + 3 hold row r of the chain, PT * 4 tokens per lane.  OVER: the slices are longer than those registers; what
+// is beyond a lane's first PT * 4 tokens is computed again from the row wherever it is needed (vocabularies above
+// 64 x 8192 tokens), and fans are walked one by one.
+template <bool BF16, int PT, bool OVER>
+__global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
+{
+    __shared__ SaShared<PT> L;
+    constexpr int TG = 4 * PT;                          // tokens of its chain row that a lane keeps
+    constexpr int BT = SaShared<PT>::BT;                // tokens of the slice that a thread sorts
+    constexpr int KW = BTV_MAX_NODES / 64;              // wavefronts that hold nodes
+    const int me = blockIdx.x, M = p.M, V = p.V, G = p.G;
+    int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // The compiler takes everything that depends on the thread alone out of the walk's loop, dozens of registers, and
+    // spills them; what tid is, it has to find out again at every node, and at every fan.
+    auto forget = [&]() {
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    };
+    const int v0 = min(me * p.per, V), v1 = min(v0 + p.per, V);
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(p.logits) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.marg) & 15) == 0;
+    for (int c = tid; c <= BTV_MAX_NODES; c += SA_T) {
+        L.first[c] = INT_MAX;
+        L.fan[c] = 0;
+        if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
+        if (c <= M) L.uni[c] = p.uniforms[c];
+    }
+    if (tid == 0) L.dead = 0;
+    const uint32_t base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    uint32_t seq = 0;
+    int cur = -1, n = 0, ui = 0, d = 0;
+    bool dead = false;
+    __syncthreads();
+    if (tid < M && L.par[tid] >= -1 && L.par[tid] < M) {
+        atomicMin(&L.first[L.par[tid] + 1], tid);
+        atomicAdd(&L.fan[L.par[tid] + 1], 1);
+    }
+    __syncthreads();
+    for (;;) {
+        forget();
+        // ---- the chain from cur, this wavefront group's row of it --------------------------------------------------
+        int node[SA_CHAIN], nch = 1;
+        node[0] = cur;
+#pragma unroll
+        for (int r = 1; r < SA_CHAIN; ++r) {
+            node[r] = nch == r && d + r - 1 < p.B && __builtin_amdgcn_readfirstlane(L.fan[node[r - 1] + 1]) <= SA_CHAIN_FAN ?
+                      __builtin_amdgcn_readfirstlane(L.first[node[r - 1] + 1]) : INT_MAX;
+            if (node[r] != INT_MAX) ++nch;
+            else node[r] = cur;
+        }
+        const int grp = wv / (SA_WAVES / SA_CHAIN), gt = tid & (SA_T / SA_CHAIN - 1);
+        const bool has_row = grp < nch;
+        const size_t row_at = (size_t)((grp == 0 ? node[0] : grp == 1 ? node[1] : grp == 2 ? node[2] : node[3]) + 1) * V;
+        const void *xrow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(p.logits) + row_at)
+                                : static_cast<const void *>(static_cast<const float *>(p.logits) + row_at);
+        const bool row_q = d + grp < p.B;
+        const float *q0 = p.marg + (size_t)(row_q ? d + grp : 0) * V;
+        // piece i of a lane: tokens tv + TS * i .. + 3, so that a wave instruction reads a stretch; up to vr from registers, from
+        // there to ve (OVER) from memory
+        constexpr int TS = SA_T / SA_CHAIN * 4;
+        int tv = v0 + gt * 4;
+        const int ve = has_row ? v1 : v0, vr = OVER ? min(v0 + TS * PT, ve) : ve;
+        float e[TG], q[TG];
+        auto load_row = [&]() {
+            load_tokens<BF16, TG>(xrow, tv, TS, vr, vec, -INFINITY, e);
+            load_tokens<false, TG>(q0, tv, TS, row_q ? vr : v0, vec, 0.f, q);
+        };
+        load_row();
+        u64 bal[SA_CHAIN];
+        if (wv < KW) {
+#pragma unroll
+            for (int r = 0; r < SA_CHAIN; ++r) {
+                bal[r] = __builtin_amdgcn_ballot_w64(r < nch && d + r < p.B && L.par[tid & (BTV_MAX_NODES - 1)] == node[r]);
+                if (lane == 0) L.kcnt[r][wv] = __builtin_popcountll(bal[r]);
+            }
+        }
+        float mx = e[0];
+#pragma unroll
+        for (int i = 1; i < TG; ++i) mx = fmaxf(mx, e[i]);
+        if (OVER)
+            for (int v = v0 + TS * PT + gt; v < ve; v += SA_T / SA_CHAIN) mx = fmaxf(mx, load_logit<BF16>(xrow, v));
+        mx = wave_max(mx);
+        if (lane == 0) L.wm[wv] = mx;
+        __syncthreads();
+        int koff[SA_CHAIN + 1];
+        koff[0] = 0;
+#pragma unroll
+        for (int r = 0; r < SA_CHAIN; ++r) {
+            const int4 c = *reinterpret_cast<const int4 *>(L.kcnt[r]);
+            static_assert(KW == 4, "four counts");
+            if (wv < KW && ((bal[r] >> lane) & 1)) {
+                const int j = koff[r] + (wv > 0 ? c.x : 0) + (wv > 1 ? c.y : 0) + (wv > 2 ? c.z : 0) + __builtin_popcountll(bal[r] & ((1ull << lane) - 1ull));
+                const int tk = L.tok[tid];
+                const bool ok = tk >= 0 && tk < V;      // not a vocabulary id: rejected, its uniform spent, nothing indexed
+                L.kid_node[j] = ok ? tid : -1 - tid;
+                L.kid_tok[j] = ok ? tk : 0;
+                L.kid_q[j] = ok ? (double)p.marg[(size_t)(d + r) * V + tk] : 0.0;
+                L.kid_x[j] = ok ? load_logit<BF16>(p.logits, (size_t)(node[r] + 1) * V + tk) : -INFINITY;
+            }
+            koff[r + 1] = __builtin_amdgcn_readfirstlane(koff[r] + c.x + c.y + c.z + c.w);
+        }
+        float m_own;
+        {
+            const float4 t = *reinterpret_cast<const float4 *>(L.wm + grp * 4);
+            m_own = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w));
+        }
+        const bool none = m_own == -INFINITY;           // nothing but -inf in this slice: it has no part in anything
+        double z = 0.0, tq = 0.0;
+#pragma unroll
+        for (int i = 0; i < TG; ++i) {
+            e[i] = none ? 0.f : exp_neg(e[i] - m_own);   // (past the end: -inf, which gives 0)
+            z += (double)e[i]; tq += (double)q[i];
+        }
+        auto e_at = [&](int v) { return none ? 0.f : exp_neg(load_logit<BF16>(xrow, v) - m_own); };
+        if (OVER)
+            for (int v = v0 + TS * PT + gt; v < ve; v += SA_T / SA_CHAIN) { z += (double)e_at(v); tq += row_q ? (double)q0[v] : 0.0; }
+        z = wave_sum(z); tq = wave_sum(tq);
+        if (lane == 0) { L.wz[wv] = z; L.wq[wv] = tq; }
+        __syncthreads();
+        ++seq;
+        if (wv < nch) {                                 // wavefront r exchanges row r
+            const int r = wv;
+            z = (L.wz[4 * r] + L.wz[4 * r + 1]) + (L.wz[4 * r + 2] + L.wz[4 * r + 3]);
+            tq = (L.wq[4 * r] + L.wq[4 * r + 1]) + (L.wq[4 * r + 2] + L.wq[4 * r + 3]);
+            const float m_row = fmaxf(fmaxf(L.wm[4 * r], L.wm[4 * r + 1]), fmaxf(L.wm[4 * r + 2], L.wm[4 * r + 3]));
+            float mw = lane == 0 ? m_row : -INFINITY;
+            double zw = lane == 0 ? z : 0.0, tw = lane == 0 ? tq : 0.0;
+            if (G > 1) {
+                u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS, *mine = set + (size_t)me * SA_WORDS + 8 * r;
+                const uint32_t tag = base + seq;
+                if (lane == 0) { put_u32(mine, tag, __float_as_uint(m_row)); put_f64(mine + 1, mine + 2, tag, z); put_f64(mine + 3, mine + 4, tag, tq); }
+                u64 w[1][5];
+                if (!take<1, 5>(set, lane, 0, G, 8 * r, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                mw = lane < G ? __uint_as_float((uint32_t)w[0][0]) : -INFINITY;
+                zw = lane < G ? get_f64(w[0][1], w[0][2]) : 0.0;
+                tw = lane < G ? get_f64(w[0][3], w[0][4]) : 0.0;
+            }
+            const float m = wave_max(mw);
+            const double F = mw == -INFINITY ? 0.0 : exp((double)mw - (double)m);
+            const double gw = zw * F;
+            L.Mx[r][lane] = mw; L.F[r][lane] = F; L.GW[r][lane] = gw;
+            z = wave_sum(gw); tq = wave_sum(tw);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int k0 = r == 0 ? koff[0] : r == 1 ? koff[1] : r == 2 ? koff[2] : koff[3];
+            const int k1 = r == 0 ? koff[1] : r == 1 ? koff[2] : r == 2 ? koff[3] : koff[4];
+            bool acc0 = false;                          // is the first child accepted, if the rows above took theirs?
+#pragma nounroll
+            for (int j = k0 + lane; j < k1; j += 64) {  // a child's e exactly as its slice's owner has it
+                const int w = L.kid_tok[j] / p.per;
+                const float x = L.kid_x[j];
+                const double ek = x == -INFINITY ? 0.0 : L.F[r][w] * (double)exp_neg(x - L.Mx[r][w]);
+                L.kid_e[j] = ek;
+                if (j == k0) acc0 = L.kid_node[j] >= 0 && (double)L.uni[min(ui + r, M)] * (L.kid_q[j] * (tq > 0.0 ? 1.0 / tq : 0.0)) * z < ek;
+            }
+            if (lane == 0) { L.z[r] = z; L.tq[r] = tq; L.acc0[r] = acc0 ? 1 : 0; }
+        }
+        __syncthreads();
+        if (L.dead) { dead = true; break; }
+        // ---- first children, as far as they are accepted -------------------------------------------------------------
+        int r = 0;
+        while (r < nch && n < M && __builtin_amdgcn_readfirstlane(L.acc0[r]) != 0) {
+            cur = __builtin_amdgcn_readfirstlane(L.first[cur + 1]);
+            if (me == 0 && tid == 0) p.path[n] = cur;
+            ++n; ++d; ++ui; ++r;
+        }
+        if (r == nch) continue;
+        // ---- row r: its first child is rejected, or it has none ---------------------------------------------------------
+        const int k0 = __builtin_amdgcn_readfirstlane(r == 0 ? koff[0] : r == 1 ? koff[1] : r == 2 ? koff[2] : koff[3]);
+        const int nk = __builtin_amdgcn_readfirstlane((r == 0 ? koff[1] : r == 1 ? koff[2] : r == 2 ? koff[3] : koff[4]) - k0);
+        const bool here = grp == r;                     // this wavefront holds the row's tokens
+        double s = 0.0, Gs = L.z[r], T = L.tq[r];
+        const double f = L.F[r][me], invf = f > 0.0 ? 1.0 / f : 0.0;
+        int gbuf = r, galt = SA_CHAIN;                  // GW[gbuf]: the parts of G(s)
+        bool batch_ok = !OVER;
+        int accepted = -1, j = 0;
+        for (; j < nk; ++j) {
+            const int c = L.kid_node[k0 + j];
+            if (c < 0) {
+                if (me == 0 && tid == 0) atomicOr(p.flag, 64u);
+                continue;
+            }
+            const double qx = L.kid_q[k0 + j], invT = T > 0.0 ? 1.0 / T : 0.0;
+            const double px = L.kid_e[k0 + j] - s * qx;      // G(s) times the target probability of the child's token
+            if ((double)L.uni[min(ui + j, M)] * (qx * invT) * Gs < (px > 0.0 ? px : 0.0)) { accepted = c; ++j; break; }
+            double s1 = s + Gs * invT;
+            bool all = false;
+            if (batch_ok && j + (nk >> 5) >= SA_DIRECT && nk - j >= SA_BATCH_MIN && s > 0.0) {
+                // ---- child j is rejected, K - 1 more follow: s_1 .. s_K at once (pt[i] is s_{i+1}, ptG[i] its G) ---------
+                forget();
+                const int K = nk - j, kj = k0 + j;
+                {
+                    const size_t at = (size_t)(cur + 1) * V;
+                    const void *brow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(p.logits) + at)
+                                            : static_cast<const void *>(static_cast<const float *>(p.logits) + at);
+                    const int bv = v0 + tid * BT;
+                    const float bm = L.Mx[r][me];
+                    float be[BT], bq[BT];
+                    load_tokens<BF16, BT>(brow, bv, 4, v1, vec, -INFINITY, be);
+                    load_tokens<false, BT>(p.marg + (size_t)d * V, bv, 4, v1, vec, 0.f, bq);
+                    const int b0 = (int)(__float_as_uint((float)(s * invf)) >> 18);
+                    L.bin_at[tid] = 0;
+                    if (wv == 0) {                      // 1 / T_k, and how far s can come
+                        double own[4], sum = 0.0, ht = 0.0;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) { const int k = 4 * lane + i; own[i] = k < K ? L.kid_q[kj + k] : 0.0; sum += own[i]; }
+                        double t = T - (wave_scan(sum, lane) - sum);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int k = 4 * lane + i;
+                            const double it = k < K && L.kid_node[kj + k] >= 0 && t > 0.0 ? 1.0 / t : 0.0;
+                            L.invT[k] = it; ht += it;
+                            t -= own[i];
+                        }
+                        ht = wave_sum(ht);
+                        if (lane == 0) L.s_hi = s + Gs * ht;
+                    }
+                    __syncthreads();
+                    int rank[BT], bin[BT];
+#pragma unroll
+                    for (int i = 0; i < BT; ++i) {      // (ratios below the current s never count again: left out)
+                        be[i] = exp_neg(be[i] - bm);
+                        bin[i] = bv + i < v1 && f > 0.0 ? sa_bin(__fdiv_rn(be[i], bq[i]), b0) : SA_BINS;
+                        rank[i] = bin[i] < SA_BINS ? atomicAdd(&L.bin_at[bin[i]], 1) : 0;
+                    }
+                    __syncthreads();
+                    {   // exclusive scan of the bin counts (one bin per thread)
+                        static_assert(SA_BINS == SA_T, "one bin per thread");
+                        const int c0 = L.bin_at[tid];
+                        int ci = c0;
+#pragma unroll
+                        for (int off = 1; off < 64; off <<= 1) {
+                            const int co = __shfl_up(ci, off);
+                            if (lane >= off) ci += co;
+                        }
+                        if (lane == 63) L.wsum[wv] = ci;
+                        __syncthreads();
+                        int cb = 0;
+#pragma nounroll
+                        for (int w = 0; w < wv; ++w) cb += L.wsum[w];
+                        L.bin_at[tid] = cb + ci - c0;
+                        if (tid == SA_T - 1) L.bin_at[SA_BINS] = cb + ci;
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int i = 0; i < BT; ++i)
+                        if (bin[i] < SA_BINS) L.sorted[L.bin_at[bin[i]] + rank[i]] = make_float2(be[i], bq[i]);
+                    __syncthreads();
+                    {   // prefix sums over the sorted positions, BT of them per thread
+                        const int cnt = L.bin_at[SA_BINS];
+                        double ce = 0.0, cq = 0.0;
+#pragma unroll
+                        for (int i = 0; i < BT; ++i)
+                            if (BT * tid + i < cnt) { const float2 x = L.sorted[BT * tid + i]; ce += (double)x.x; cq += (double)x.y; }
+                        const double ie = wave_scan(ce, lane), iq = wave_scan(cq, lane);
+                        if (lane == 63) { L.wz[wv] = ie; L.wq[wv] = iq; }
+                        __syncthreads();
+                        double se = 0.0, sq = 0.0;
+#pragma nounroll
+                        for (int w = 0; w < wv; ++w) { se += L.wz[w]; sq += L.wq[w]; }
+                        L.cE[tid] = se + (ie - ce); L.cQ[tid] = sq + (iq - cq);
+                        if (tid == SA_T - 1) { L.cE[SA_T] = se + ie; L.cQ[SA_T] = sq + iq; }
+                    }
+                    __syncthreads();
+                }
+                const int b0 = (int)(__float_as_uint((float)(s * invf)) >> 18);
+                const float span = __log2f((float)(L.s_hi / s)), step = span / (float)(SA_GRID - 1);
+                int status = 0;
+                // pass -1: the table at SA_GRID points and the guesses from it; then Newton on the true sums
+#pragma nounroll
+                for (int pass = -1; pass < 8; ++pass) {
+                    forget();
+                    const int np = pass < 0 ? SA_GRID : K;
+                    const int lkp = np > 128 ? 8 : np > 64 ? 7 : 6;      // points, a power of two
+                    const int LP = SA_T >> lkp, k = tid >> (10 - lkp), sub = tid & (LP - 1);      // LP neighbouring lanes per point
+                    {   // E and Q of this slice at point k, by LP neighbouring lanes
+                        const double sv = pass < 0 ? s * (double)exp2f(step * (float)k) : L.pt[k];
+                        double E = 0.0, Q = 0.0;
+                        if (f > 0.0) {
+                            const double sl = sv * invf;
+                            const int b = min(max(sa_bin((float)sl, b0), 0), SA_BINS - 1);
+                            const int p0 = L.bin_at[b] / BT, p1 = L.bin_at[b + 1];
+#pragma nounroll
+                            for (int i = p0 * BT + sub; i < p1; i += LP) {
+                                const float2 x = L.sorted[i];
+                                if ((double)x.x - sl * (double)x.y > 0.0) { E += (double)x.x; Q += (double)x.y; }
+                            }
+                            if (sub == 0) { E += L.cE[p0]; Q += L.cQ[p0]; }
+                        }
+#pragma nounroll
+                        for (int off = 1; off < LP; off <<= 1) { E += __shfl_xor(E, off); Q += __shfl_xor(Q, off); }
+                        E *= f;
+                        ++seq;
+                        if (G > 1) {
+                            if (sub == 0 && k < np) {
+                                u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + k;
+                                put_f64(o, o + SA_PLANE, base + seq, E); put_f64(o + 2 * SA_PLANE, o + 3 * SA_PLANE, base + seq, Q);
+                            }
+                        } else if (sub == 0) {
+                            L.sE[k] = E; L.sQ[k] = Q;
+                        }
+                    }
+                    if (G > 1) {
+                        // summed in two exchanges: workgroup w adds up the points w, w + G, ... of all workgroups, and everybody reads
+                        // the sums (with everybody reading every part instead, 4 MB for 32 workgroups, a pass took 3 us longer)
+                        const u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
+                        const int lg = 32 - __builtin_clz(G - 1), w = tid & ((1 << lg) - 1), pt = me + (tid >> lg) * G;
+                        u64 x[1][4];
+                        bool fine = true;
+                        if (me + (wv * 64 >> lg) * G < np) fine = take<1, 4, SA_PLANE>(set, w, 0, G, min(pt, SA_PLANE - 1), pt < np, base + seq, x, p.wait_ticks);
+                        ++seq;
+                        if (fine && me + (wv * 64 >> lg) * G < np) {
+                            double E = w < G && pt < np ? get_f64(x[0][0], x[0][1]) : 0.0, Q = w < G && pt < np ? get_f64(x[0][2], x[0][3]) : 0.0;
+#pragma nounroll
+                            for (int off = 1; off < 1 << lg; off <<= 1) { E += __shfl_xor(E, off); Q += __shfl_xor(Q, off); }
+                            if (w == 0 && pt < np) {
+                                u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + pt;
+                                put_f64(o, o + SA_PLANE, base + seq, E); put_f64(o + 2 * SA_PLANE, o + 3 * SA_PLANE, base + seq, Q);
+                            }
+                        }
+                        set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
+                        if (wv == 0 && fine) {          // (one wavefront waits for each workgroup's last sum)
+                            u64 y[1][1];
+                            fine = take<1, 1>(set, lane, 0, G, 3 * SA_PLANE + lane + (np - 1 - lane) / G * G, lane < np, base + seq, y, p.wait_ticks);
+                        }
+                        if (!fine && lane == 0) L.dead = 1;
+                        __syncthreads();
+                        if (L.dead) break;
+                        if (wv * 64 < np) {
+                            const int at = min(tid, SA_PLANE - 1);
+                            fine = take<1, 4, SA_PLANE>(set, at % G, 0, G, at, tid < np, base + seq, x, p.wait_ticks);
+                            if (tid < np) { L.sE[tid] = get_f64(x[0][0], x[0][1]); L.sQ[tid] = get_f64(x[0][2], x[0][3]); }
+                        }
+                        if (!fine && lane == 0) L.dead = 1;
+                    }
+                    __syncthreads();
+                    if (L.dead) break;
+                    if (pass < 0) {
+                        if (tid < SA_GRID) {
+                            const int kk = min(tid, SA_GRID - 2);
+                            const double ig = 1.0 / Gs;
+                            const float r0 = exp2f(step * (float)kk), r1 = exp2f(step * (float)(kk + 1));
+                            const float g0 = fmaxf((float)((L.sE[kk] - s * (double)r0 * L.sQ[kk]) * ig), 0.f);
+                            const float g1 = fmaxf((float)((L.sE[kk + 1] - s * (double)r1 * L.sQ[kk + 1]) * ig), 0.f);
+                            const float sl = r1 > r0 ? (g1 - g0) / (r1 - r0) : 0.f;
+                            L.tab[tid] = make_float2(sl, g0 - sl * r0);
+                        }
+                        __syncthreads();
+                        if (wv == 0) {                  // the recurrence solved on the table (fp32, s / s_cur and G / G_cur)
+                            float kap[4], nx[4];
+                            const double scale = Gs / s;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                kap[i] = (float)(scale * L.invT[4 * lane + i]);
+                                nx[i] = exp2f(0.5f * span * (float)(4 * lane + i + 1) / (float)K);
+                            }
+                            const float per_step = step > 0.f ? 1.f / step : 0.f;
+#pragma nounroll
+                            for (int it = 0; it < 16; ++it) {
+                                float at = __shfl_up(nx[3], 1), a = 1.f, b = 0.f, ai[4], bi[4];
+                                at = lane == 0 ? 1.f : at;
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const int kk = min(max((int)(__log2f(at) * per_step), 0), SA_GRID - 2);
+                                    const float2 t = L.tab[kk];
+                                    ai[i] = 1.f + t.x * kap[i]; bi[i] = t.y * kap[i];
+                                    b = ai[i] * b + bi[i]; a = ai[i] * a;
+                                    at = nx[i];
+                                }
+                                float A, Bv;
+                                wave_affine_before(a, b, lane, A, Bv);
+                                float x = A + Bv, moved = 0.f;
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    x = fmaxf(ai[i] * x + bi[i], 1.f);
+                                    if (4 * lane + i < K) moved = fmaxf(moved, fabsf(x - nx[i]) / x);
+                                    nx[i] = x;
+                                }
+                                if (__builtin_amdgcn_ballot_w64(!(moved < 3e-5f)) == 0ull) break;
+                            }
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) L.pt[4 * lane + i] = s * (double)nx[i];
+                        }
+                        __syncthreads();
+                        continue;
+                    }
+                    if (wv == 0) {
+                        double ai[4], bi[4], a = 1.0, b = 0.0;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int kk = 4 * lane + i;
+                            const double it = L.invT[kk];
+                            ai[i] = kk > 0 && kk < K ? 1.0 - L.sQ[kk - 1] * it : 1.0;
+                            bi[i] = kk < K ? (kk > 0 ? L.sE[kk - 1] : Gs) * it : 0.0;
+                            b = ai[i] * b + bi[i]; a = ai[i] * a;
+                        }
+                        double A, Bv;
+                        wave_affine_before(a, b, lane, A, Bv);
+                        double x = A * s + Bv;
+                        bool close = true, good = true;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int kk = 4 * lane + i;
+                            x = ai[i] * x + bi[i];
+                            if (kk < K) {
+                                const double g = L.sE[kk] - x * L.sQ[kk];
+                                close = close && fabs(x - L.pt[kk]) <= 1e-7 * x;
+                                good = good && g > 0.0;
+                                L.pt[kk] = x; L.ptG[kk] = g;
+                            }
+                        }
+                        const bool all_close = __builtin_amdgcn_ballot_w64(!close) == 0ull, all_good = __builtin_amdgcn_ballot_w64(!good) == 0ull;
+                        // (a residual that is all zero keeps s where it is, which the recurrence does not say: walked one by one)
+                        if (lane == 0) L.status = all_close ? (all_good ? 1 : 2) : 0;
+                        if (all_close && all_good) {    // child j + k is tried at s_k
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            int first = INT_MAX;
+#pragma nounroll
+                            for (int kk = 1 + lane; kk < K; kk += 64) {
+                                const double qk = L.kid_q[kj + kk], pk = L.kid_e[kj + kk] - L.pt[kk - 1] * qk;
+                                const bool acc = L.kid_node[kj + kk] >= 0 &&
+                                                 (double)L.uni[min(ui + j + kk, M)] * (qk * L.invT[kk]) * L.ptG[kk - 1] < (pk > 0.0 ? pk : 0.0);
+                                if (acc) first = min(first, kk);
+                            }
+                            for (int off = 32; off >= 1; off >>= 1) first = min(first, __shfl_xor(first, off));
+                            if (lane == 0) L.acc = first;
+#pragma nounroll
+                            for (int kk = 1 + lane; kk < min(K, first); kk += 64)
+                                if (L.kid_node[kj + kk] < 0 && me == 0) atomicOr(p.flag, 64u);
+                        }
+                    }
+                    __syncthreads();
+                    status = L.status;
+                    if (status != 0) break;
+                }
+                if (L.dead) { dead = true; break; }
+                if (status == 1 && L.acc < K) {
+                    accepted = L.kid_node[kj + L.acc];
+                    j += L.acc + 1;
+                    break;
+                }
+                forget();
+                asm volatile("" : "+v"(tv));
+                load_row();                             // (the row's registers were given up for the fan)
+#pragma unroll
+                for (int i = 0; i < TG; ++i) e[i] = none ? 0.f : exp_neg(e[i] - m_own);
+                if (status == 1) { s1 = L.pt[K - 1]; all = true; }      // all rejected: the parts of G(s_K) are still to be had
+                batch_ok = false;                       // not converged, or a residual that is all zero
+            }
+            // ---- one rejection: G at the next s --------------------------------------------------------------------
+            if (here) {
+                double a = 0.0;
+                if (f > 0.0) {
+                    const double sl = s1 * invf;
+#pragma unroll
+                    for (int i = 0; i < TG; ++i) {
+                        asm volatile("" : "+v"(e[i]), "+v"(q[i]));     // (or all of them are kept as doubles through the loop)
+                        const double x = (double)e[i] - sl * (double)q[i];
+                        a += x > 0.0 ? x : 0.0;
+                    }
+                    if (OVER)
+                        for (int v = v0 + TS * PT + gt; v < ve; v += SA_T / SA_CHAIN) {
+                            const double x = (double)e_at(v) - sl * (double)q0[v];
+                            a += x > 0.0 ? x : 0.0;
+                        }
+                }
+                a = wave_sum(a);
+                if (lane == 0) L.wz[wv & 3] = a;
+            }
+            __syncthreads();
+            ++seq;
+            if (wv == 0) {
+                const double a = ((L.wz[0] + L.wz[1]) + (L.wz[2] + L.wz[3])) * f;
+                double gw = lane == 0 ? a : 0.0;
+                if (G > 1) {
+                    u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
+                    const uint32_t tag = base + seq;
+                    if (lane == 0) put_f64(set + (size_t)me * SA_WORDS, set + (size_t)me * SA_WORDS + 1, tag, a);
+                    u64 w[1][2];
+                    if (!take<1, 2>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                    gw = lane < G ? get_f64(w[0][0], w[0][1]) : 0.0;
+                }
+                L.GW[galt][lane] = gw;
+                gw = wave_sum(gw);
+                if (lane == 0) L.g = gw;
+            }
+            __syncthreads();
+            if (L.dead) { dead = true; break; }
+            if (L.g > 0.0) { s = s1; Gs = L.g; const int t = gbuf; gbuf = galt; galt = t; }
+            T -= qx;                                    // drafted without replacement
+            if (all) { j = nk; break; }
+        }
+        if (dead) break;
+        ui += j;                                        // one uniform per child tried
+        if (accepted >= 0 && n < M) {
+            cur = __builtin_amdgcn_readfirstlane(accepted);
+            if (me == 0 && tid == 0) p.path[n] = cur;
+            ++n; ++d;
+            continue;
+        }
+        // ---- bonus: smallest v with cumsum(p)[v] > u ---------------------------------------------------------------
+        const double target = (double)L.uni[min(ui, M)] * Gs;
+        const double gw = L.GW[gbuf][lane], incl = wave_scan(gw, lane);
+        const u64 over = __builtin_amdgcn_ballot_w64(incl > target && gw > 0.0);
+        const int owner = over != 0ull ? __builtin_ctzll(over) : -1;
+        if (owner == me || owner < 0) {
+            // this slice holds the crossing (or rounding put it past the end: then every slice's last token with mass)
+            if (tid == 0) { L.pick = INT_MAX; L.last = -1; }
+            const double sl = s * invf;
+            auto mass = [&](float ev, float qv) { const double x = ((double)ev - sl * (double)qv) * f; return x > 0.0 ? x : 0.0; };
+            // tokens in order: piece after piece, in a piece lane after lane (OVER: the rest the same way, one token per lane)
+            double run = owner >= 0 ? __shfl(incl - gw, owner) : 0.0;
+            const int trips = (v1 - v0 + TS - 1) / TS, rest = OVER ? max(v1 - v0 - TS * PT + SA_T / SA_CHAIN - 1, 0) / (SA_T / SA_CHAIN) : 0;
+#pragma nounroll
+            for (int t = 0; t < (OVER ? PT + rest : min(trips, PT)); ++t) {
+                double x[4] = { 0.0, 0.0, 0.0, 0.0 };
+                int v = tv + TS * t;
+                if (here) {
+                    if (!OVER || t < PT) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            float ev = e[k], qv = q[k];
+#pragma unroll
+                            for (int i = 1; i < PT; ++i) { ev = t == i ? e[4 * i + k] : ev; qv = t == i ? q[4 * i + k] : qv; }
+                            x[k] = mass(ev, qv);
+                        }
+                    } else {
+                        v = v0 + TS * PT + (t - PT) * (SA_T / SA_CHAIN) + gt;
+                        if (v < ve) x[0] = mass(e_at(v), row_q ? q0[v] : 0.f);
+                    }
+                }
+                const double own = (x[0] + x[1]) + (x[2] + x[3]), iw = wave_scan(own, lane);
+                if (here && lane == 63) L.wz[wv & 3] = iw;
+                __syncthreads();
+                if (here) {
+                    double at = run + (iw - own);
+#pragma unroll
+                    for (int w = 0; w < 3; ++w) at += w < (wv & 3) ? L.wz[w] : 0.0;
+                    int hit = INT_MAX, last = -1;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        at += x[k];
+                        if (x[k] > 0.0) { last = v + k; hit = at > target ? min(hit, v + k) : hit; }
+                    }
+                    if (last >= 0) atomicMax(&L.last, last);
+                    if (owner >= 0 && hit != INT_MAX) atomicMin(&L.pick, hit);
+                }
+                run += (L.wz[0] + L.wz[1]) + (L.wz[2] + L.wz[3]);
+                __syncthreads();
+            }
+            __syncthreads();
+            if (owner >= 0 && tid == 0) *p.bonus = L.pick != INT_MAX ? L.pick : max(L.last, 0);
+        }
+        if (owner < 0) {
+            ++seq;
+            if (wv == 0) {
+                int last = lane == 0 ? L.last : -1;
+                if (G > 1) {
+                    u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
+                    const uint32_t tag = base + seq;
+                    if (lane == 0) put_u32(set + (size_t)me * SA_WORDS, tag, (uint32_t)L.last);
+                    u64 w[1][1];
+                    if (!take<1, 1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                    last = lane < G ? (int)(uint32_t)w[0][0] : -1;
+                }
+                for (int off = 32; off >= 1; off >>= 1) last = max(last, __shfl_xor(last, off));
+                if (me == 0 && lane == 0) *p.bonus = max(last, 0);
+            }
+            __syncthreads();
+            if (L.dead) dead = true;
+        }
+        break;
+    }
+    if (me == 0 && tid == 0) {
+        *p.n_acc = n;
+        if (dead) { *p.bonus = 0; atomicOr(p.flag, 128u); }
+        if (G > 1) __hip_atomic_store(p.base, base + seq + (dead ? 1u << 20 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Tokens per slice and slices for a vocabulary of V tokens: slices of 4096 tokens (four per thread) as long as 64 workgroups
+// cover the vocabulary, of 8192 up to twice that, longer ones above.
+struct SaPlan { int G, per, pt; bool over; };
+SaPlan sa_plan(int V)
+{
+    SaPlan a;
+    a.pt = V <= SA_MAX_WGS * SA_T * 2 ? 2 : V <= SA_MAX_WGS * SA_T * 4 ? 4 : 8;
+    a.over = V > SA_MAX_WGS * SA_T * 8;
+    const int most = SA_T * a.pt;
+    a.G = a.over ? SA_MAX_WGS : (V + most - 1) / most;
+    a.per = (int)((((long long)V + a.G - 1) / a.G + 3) / 4 * 4);
+    return a;
+}
+
+template <bool BF16>
+void sa_launch(const SaPlan &a, const SaParams &p, hipStream_t st)
+{
+    if (a.over) hipLaunchKernelGGL((stochastic_walk<BF16, 8, true>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else if (a.pt == 8) hipLaunchKernelGGL((stochastic_walk<BF16, 8, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else if (a.pt == 4) hipLaunchKernelGGL((stochastic_walk<BF16, 4, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else hipLaunchKernelGGL((stochastic_walk<BF16, 2, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+}
+
+}  // namespace
+
+size_t btv_stochastic_workspace(int V)
+{
+    return BTV_WS_HEADER + btv_align_up((size_t)2 * sa_plan(V).G * SA_WORDS * sizeof(u64), BTV_WS_ALIGN);
+}
+
+extern "C" int btv_tree_accept_stochastic(const void *logits, int dtype, const float *marginals, int B, const int32_t *parent,
+                                          const int32_t *token, int M, int V, const float *uniforms, int32_t *path,
+                                          int32_t *n_acc, int32_t *bonus, void *ws, size_t ws_bytes, void *stream)
+{
+    BTV_REQUIRE(logits && parent && token && path && n_acc && bonus, "null pointer");
+    BTV_REQUIRE(dtype == BTV_F32 || dtype == BTV_BF16, "dtype=%d unsupported", dtype);
+    BTV_REQUIRE(M >= 1 && M <= BTV_MAX_NODES, "M=%d outside [1,%d]", M, BTV_MAX_NODES);
+    BTV_REQUIRE(V >= 1, "V=%d", V);
+    BTV_REQUIRE(marginals && uniforms, "null pointer");
+    BTV_REQUIRE(B >= 1 && B <= BTV_MAX_DEPTH, "B=%d outside [1,%d]", B, BTV_MAX_DEPTH);
+    const int rc = btv_check_ws(ws, ws_bytes, btv_stochastic_workspace(V));
+    if (rc) return rc;
+    const SaPlan a = sa_plan(V);
+    SaParams p;
+    p.logits = logits; p.marg = marginals; p.uniforms = uniforms; p.parent = parent; p.token = token;
+    p.path = path; p.n_acc = n_acc; p.bonus = bonus;
+    p.flag = static_cast<uint32_t *>(ws); p.base = static_cast<uint32_t *>(ws) + 16;
+    p.slots = reinterpret_cast<u64 *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
+    p.B = B; p.M = M; p.V = V; p.G = a.G; p.per = a.per; p.wait_ticks = SA_WAIT_TICKS;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (dtype == BTV_BF16) sa_launch<true>(a, p, st);
+    else sa_launch<false>(a, p, st);
+    BTV_HIP(hipGetLastError());
+    return BTV_OK;
+}

@@ -289,6 +289,31 @@ def test_stochastic_wide_fan_long_vocabulary(G, oracle):
     assert checked >= 2
 
 
+@pytest.mark.parametrize("V", [1, 5, 2047, 2049, 30000, 131072, 131073, 262148, 524301])
+@pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
+def test_stochastic_slices(G, oracle, V, logit_dtype):
+    """Vocabularies around the limits of the slices that the workgroups take (2048, 4096 and 8192 tokens, 64 workgroups at
+    most, longer slices above), whole and ragged, over a deep tree whose first children are mostly accepted and over
+    one with a fan of 24 at the root."""
+    checked = 0
+    for seed, (B, N, sigma, noise) in enumerate([(6, 12, 4.0, 0.3), (2, 24, 0.5, 2.0), (6, 12, 4.0, 0.0)]):
+        marg = synth.marginals(40 + seed, B, V, sigma)
+        tree = oracle.tree_build(marg, N)
+        M = len(tree["parent"])
+        z = np.log(np.maximum(marg[np.minimum(np.concatenate([[0], tree["depth"]]), B - 1)].astype(np.float64), 1e-30))
+        z += synth.normal(50 + seed, "noise", z.shape, noise)
+        store, xf = synth.round_to_dtype(z, logit_dtype)
+        u = synth.uniform(60 + seed, "u", (M + 1,)).astype(np.float32)
+        ref = oracle.accept_stochastic(xf, marg, tree["parent"], tree["token"], tree["depth"], u)
+        if V > 1 and _ambiguous(ref):
+            continue
+        got = G.run_accept_stochastic(store, logit_dtype == "bf16", marg, tree["parent"], tree["token"], u)
+        assert got["n_acc"] == ref["n_acc"] and np.array_equal(got["path"], ref["path"]), (V, seed)
+        assert got["bonus"] == ref["bonus"], (V, seed)
+        checked += 1
+    assert checked >= 1
+
+
 def test_stochastic_token_outside_vocabulary_is_flagged_not_faulting():
     """A token id outside [0, V) is never used as an index: that child counts as rejected, the data flag is raised,
     and the walk goes on with the valid children."""
