@@ -3,8 +3,8 @@
 // Sec. 3.3 / Prop. 3.3 / Algorithm 1's frontier rule at a fixed budget N: repeatedly emit the
 // frontier prefix with the largest path score rho (Eq. 1), then push its best child and its next
 // sibling.  Two kernels:
-//   1. tb_thread_max   per slot of 32 marginals (one thread's share of a chunk): the largest, its place in the
-//                      slot, and the second largest (one pass over [B, V], all CUs);
+//   1. tb_thread_max   per slot of up to 32 marginals (one thread's share of a chunk): the largest, its place in
+//                      the slot, and the second largest (one pass over [B, V], all CUs; not for small vocabularies);
 //   2. tb_rank_expand  workgroup k derives from the maxima of position k a bound below which no token can be
 //                      among its K best (K = min(V, N): a rank-j token is preceded by its j earlier siblings, so
 //                      ranks >= N can never be emitted); a slot whose maximum reaches the bound and whose second
@@ -25,7 +25,14 @@ namespace {
 typedef unsigned long long u64;
 
 constexpr int MAXB = BTV_MAX_DEPTH;
-constexpr int SCAN = 8192;        // marginals scanned per workgroup (256 threads x 32)
+
+// A row is seen as slots of 2^lge marginals, one per thread and chunk of 256 << lge of them: the smallest lge that leaves at
+// most 16 chunks (the ranking workgroup keeps 16 slot records per thread in registers), 5 at most.  lge = 0, up to 4096
+// marginals, needs no pass ahead of the ranking: every slot is one marginal, read where it is needed.  Slots of 32 for
+// every vocabulary left too few of them where it is small: 5000 marginals were 256 slots, and the best 256 tokens of a
+// row, which the slots' maxima are to bound, were looked for in the whole row (110 .. 217 us instead of 30).
+constexpr int LGE_MAX = 5;
+__device__ __forceinline__ int slot_first(int lge, int chunk, int t) { return (chunk << (8 + lge)) + t * (lge ? 4 : 1); }      // + 1024 per piece of four
 
 __device__ __forceinline__ u64 make_key(float prob, uint32_t id)
 {
@@ -91,46 +98,41 @@ __device__ __forceinline__ void publish(float *q_row, uint32_t *tok_row, int r, 
 
 
 // ------------------------------------------------------------------------------------------------
-// Step 1: per-thread maxima.  Workgroup (chunk, row) scans elements chunk*SCAN .. chunk*SCAN + SCAN - 1 of the
-// row; thread t looks at elements 4t..4t+3 of every 1024 (its slot: 32 elements, numbered k = 4 * piece + element)
-// and keeps the largest probability it saw, where it saw it, and the second largest:
+// Step 1: per-thread maxima.  Workgroup (chunk, row) scans the chunk's 256 << LGE elements of the row; thread t looks
+// at elements 4t..4t+3 of every 1024 (its slot, elements numbered k = 4 * piece + element) and keeps the largest
+// probability it saw, where it saw it, and the second largest:
 // part[row][chunk][t] = { bits of the largest, bits of the second largest with k of the largest in the low 5 bits }.
 // The second largest is only ever compared with a bound whose low 19 bits are zero, so the 5 bits cost nothing.
 // Among equal probabilities the first one counts as the largest and the next as the second largest.
 // ------------------------------------------------------------------------------------------------
-struct TbCounters { int done; };
+struct TbCounters { int done; };            // zero between calls
 
-template <typename F>
-__device__ __forceinline__ void scan_chunk(const float *src, bool aligned, int V, int chunk, int tid, F f)
-{
-#pragma unroll
-    for (int j = 0; j < SCAN / 1024; ++j) {
-        const int v0 = chunk * SCAN + j * 1024 + tid * 4;        // coalesced: a wave reads 1 KiB per load
-        if (aligned && v0 + 4 <= V) {
-            const float4 a = *reinterpret_cast<const float4 *>(src + v0);
-            f(a.x, 4 * j); f(a.y, 4 * j + 1); f(a.z, 4 * j + 2); f(a.w, 4 * j + 3);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (v0 + i < V) f(src[v0 + i], 4 * j + i);
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, int B, int chunks, uint2 *part, TbCounters *ctr)
+template <int LGE>
+__global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, int chunks, uint2 *part)
 {
     const int tid = threadIdx.x, chunk = blockIdx.x, row = blockIdx.y;
     const float *src = marg + (size_t)row * V;
     const bool aligned = (((size_t)row * V) & 3) == 0 && (reinterpret_cast<uintptr_t>(marg) & 15) == 0;
     uint32_t m1 = 0u, m2 = 0u, k1 = 0u;
-    scan_chunk(src, aligned, V, chunk, tid, [&](float p, int k) {
+    auto see = [&](float p, int k) {
         const uint32_t b = prob_bits(p);
         m2 = umax(m2, b < m1 ? b : m1);                          // the smaller of the newcomer and the best so far
         k1 = b > m1 ? (uint32_t)k : k1;
         m1 = umax(m1, b);
-    });
+    };
+#pragma unroll
+    for (int j = 0; j < (1 << LGE) / 4; ++j) {
+        const int v0 = slot_first(LGE, chunk, tid) + j * 1024;   // coalesced: a wave reads 1 KiB per load
+        if (aligned && v0 + 4 <= V) {
+            const float4 a = *reinterpret_cast<const float4 *>(src + v0);
+            see(a.x, 4 * j); see(a.y, 4 * j + 1); see(a.z, 4 * j + 2); see(a.w, 4 * j + 3);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v0 + i < V) see(src[v0 + i], 4 * j + i);
+        }
+    }
     part[((size_t)row * chunks + chunk) * 256 + tid] = make_uint2(m1, (m2 & ~31u) | k1);
-    if (chunk == 0 && row % B == 0 && tid == 0) ctr[row / B].done = 0;   // the next kernel starts after this one has ended
 }
 
 constexpr int TBINS = 4096;
@@ -186,7 +188,7 @@ struct alignas(16) RankLds {                // bound and ranking of one position
     int last;
 };
 
-struct ExpandLds {                          // the expansion
+struct alignas(16) ExpandLds {              // the expansion
     float q[MAXB * BTV_MAX_NODES + 64];     // q[k*KP + r]: probability of rank r at position k (+ padding: q[..][r+1] is
                                             // fetched, not used, also for the last rank of the last position)
     double cost[BTV_MAX_NODES];             // adaptive budget: estimated cycle latency at budget n + 1
@@ -194,24 +196,25 @@ struct ExpandLds {                          // the expansion
                                             // node at the end of the expansion would be one more round trip)
 };
 
-// The level-synchronous expansion: pool = the best nodes found so far, in emission order; candidates of one level.
-constexpr int LV_CAND = 2048;
-constexpr int LV_PAD = 80;                  // zero keys behind a list that is counted over: the reads overrun by up to 66 keys
-struct alignas(16) LevelLds {
-    alignas(16) u64 ckey[LV_CAND + LV_PAD];
-    alignas(16) u64 pkey[2][BTV_MAX_NODES + LV_PAD];   // (+ zero keys behind the pool)
-    uint32_t pval[2][BTV_MAX_NODES];
-    uint16_t lex2id[BTV_MAX_NODES];         // node id by lexicographic place, for the level whose children are proposed
-    uint16_t mark[BTV_MAX_NODES];           // index + 1 of the pool entry whose proposals start at this candidate, else 0
-    uint16_t rcap[BTV_MAX_NODES];           // min(K, N / (i + 1))
-    int hist[BTV_MAX_NODES + 8];            // proposals that land right behind pool entry i - 1
-    int wmax[4];
-    uint16_t pos_of[MAXB * BTV_MAX_NODES];  // place in the pool by node id (level, index within the level)
-    int off[BTV_MAX_NODES];                 // exclusive scan of the candidates per pool entry
-    int cnt_lex[BTV_MAX_NODES];             // nodes of the new level per parent (by the parent's lexicographic place)
-    int wsum[4], wsum2[4];
-    uint32_t wtop[4];                       // per wavefront: score of its first node of the new level (0: none)
-    double dsum[4];
+// The level-by-level expansion (expand_sweep).
+constexpr int SW_CAP = 4096;                // candidates of all levels together
+constexpr int SW_COARSE = 512;              // bins of a score during the sweep: 4 per binade of fp32 (what is above 2 shares the last)
+constexpr int SW_BINS = 2048;               // bins when the tree is put in order: 16 per binade
+constexpr int SW_KEEP = 512;                // candidates that reach the last threshold (N and what shares its bin)
+constexpr int SW_THIN = 96;                 // nodes up to which a level is one wavefront's work
+struct alignas(16) SweepLds {
+    // score bits << 32 | depth, parent and rank of a candidate (sweep_meta); a level's candidates lie in lexicographic
+    // order of their rank paths.  At the end the upper half takes the candidate's place in the tree.
+    uint2 cand[SW_CAP];
+    alignas(16) int coarse[SW_COARSE];      // candidates per bin
+    alignas(16) int hist[SW_BINS];          // candidates that are left, per bin; then those in the bins above
+    int at[SW_BINS];                        // next place of the bin in `key`
+    u64 key[SW_KEEP];                       // score bits << 32 | ~candidate, bin after bin
+    uint16_t order[SW_KEEP];                // places in `key`, in the tree's order
+    alignas(16) int cnt[2][BTV_MAX_NODES];  // children per node of a block of 256
+    int wsum[4];
+    int d, a, b, th;                        // where the sweep stands
+    double wd[4];
     int n_stop;
 };
 
@@ -395,8 +398,6 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
     int n = 0;
     double run_a = 1.0, best_a = 0.0, best_c = 0.0;            // Ahat so far; Ahat and cost at the best budget so far
     bool stop = false;
-    // Slots are handed out in node order, so before node 64*RA - 1 is emitted only the first RA register rows can
-    // hold anything: the loop runs in phases over RA = 1..R, each compiled for its number of live rows.
     auto phase = [&](auto ra_c, int n_end) {
         constexpr int RA = decltype(ra_c)::value;
         while (n < n_end) {
@@ -542,11 +543,7 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
             ++n;
         }
     };
-    phase(std::integral_constant<int, 1>{}, min(N, 63));
-    if (R >= 2 && !stop) phase(std::integral_constant<int, (R >= 2 ? 2 : 1)>{}, min(N, 127));
-    if (R >= 3 && !stop) phase(std::integral_constant<int, (R >= 3 ? 3 : 1)>{}, min(N, 191));
-    if (R >= 4 && !stop) phase(std::integral_constant<int, (R >= 4 ? 4 : 1)>{}, N);
-    if (R < 4 && !stop) phase(std::integral_constant<int, R>{}, N);
+    phase(std::integral_constant<int, R>{}, N);
     double a = 0.0;                  // the surrogate: summed in fp64 and rounded once
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -572,400 +569,295 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
 // ------------------------------------------------------------------------------------------------
 // Step 3, part B'': the same tree, level by level, on the whole workgroup.
 // The emission order (rho desc, depth asc, rank path asc) is a total order of the lattice in which a node comes
-// after its parent and after its elder siblings, so the tree is the set of the N first prefixes of that order and
-// the emission order is that order: nothing about it needs the frontier.  Level d of the tree is among the
-// children of the level d-1 nodes kept so far.  The pool holds the best N nodes found up to the level before, in
-// order; every pool node of depth d-1 proposes its children of rank r < min(K, N / (i + 1)), i being its place
-// among the depth d-1 nodes (the child is preceded by the (i+1)(r+1) children of rank <= r of the parents up to its
-// own), cut further at the score of the pool's last node once the pool is full.  Up to 256 proposals (the rule
-// once the pool is full) are placed by counting: one per thread, its new place = the proposals above it + the pool
-// nodes above it; more are sorted (bitonic, 64-bit keys, in LDS) and merged into the pool by binary searches from
-// both sides.  The loop ends at depth B or when a level proposes nothing.
-// Key of a node = bits(rho) << 32 | (31 - depth) << 16 | (0xFFFF - lexkey); lexkey = place of the parent in the
-// lexicographic order of its level * KP + rank, which orders the nodes of one level by rank path; the place of a
-// new node in that order is the number of level nodes under parents before its parent, plus its rank (siblings
-// in the pool are always ranks 0 .. c-1).  Value = node id (level - 1) * 256 + place within the level | id of the
-// parent << 12 | lexicographic place << 24; places within a level never change once assigned, because the pool
-// only ever loses its last nodes.
-// A level costs a few microseconds whatever it holds, a node of the one-wavefront expansion a quarter to half a
-// microsecond whatever the tree looks like: the host of this function picks by the depth the tree can reach.
+// after its parent and after its elder siblings, so the tree is the set of the N first prefixes of that order, and nothing
+// about it needs the frontier, nor any order before the end.  The levels are swept once with a threshold that only
+// rises: level d's candidates are the children of level d-1's candidates that score above it (a node deeper than N nodes that
+// score at least as much cannot be among the first N), and after every level the threshold moves up to the lower
+// edge of the bin that holds the N-th best candidate so far (a histogram of the scores' bits, 16 bins per binade, to which every
+// candidate is added once; a suffix sum finds the bin).  A child of rank r is not needed either where the product of
+// (rank + 1) along its path exceeds N: that many prefixes of its own level come before it (kept per node as the most
+// children it can have: floor(N / product) = floor(floor(N / parent's product) / (r + 1))).
+// Children take their places in their parents' order, so that a candidate's index grows with the depth and, within a level, with
+// the rank path: score and index are the emission order's whole key.  At the end the candidates of the bins that
+// are left, N of them and the few that share the last bin, are put in order: bin after bin by the histogram, and
+// within a bin by counting.
+// A thin level is one wavefront's work, 64 nodes at a time: what it costs is the length of its chain of steps, of which workgroup
+// barriers and the LDS words around them would be a good part.  A wide one (the second level of a flat tree, all levels of
+// a small vocabulary's) is the whole workgroup's, 256 nodes at a time, which go to the wavefronts in turn (node 4 l + w to
+// lane l of wavefront w), since the wide fans come first.  A node writes its first four children from the registers that it
+// tested them in; the rest of a wide fan is tested and written by its wavefront together.  If the candidates outgrow
+// the LDS (marginals that are no probabilities can do that), nothing has been written yet and the frontier loop builds
+// the tree.
+// Measured (16 x 128256 marginals, whole call replayed from a HIP graph): see the rule in tb_rank_expand.
 // ------------------------------------------------------------------------------------------------
-// Bitonic sort of P2 (a power of two, at least 128) 64-bit keys in LDS, largest first, by 256 threads.  Every
-// compare-exchange at a distance below 128 happens in registers: a wavefront holds a block of 128 keys two per lane
-// (key e * 64 + lane of the block in register e), distance 64 pairs a lane's own two registers, shorter distances pair
-// lanes (the network is unrolled, every stage takes the cross-lane move that fits its distance).  Only the distances from 128 up go through LDS, one block barrier
-// each.  base = index of the block's first key in the whole array: it fixes each pair's direction.
-// x of lane (l ^ J) for J = 1 .. 32, on the vector ALU alone: quad permutes for 1 and 2, two row shifts (each written
-// to the banks of four lanes it is right for) for 4 and 8, the row / half-wave swaps for 16 and 32.  The same data
-// through ds_bpermute costs a trip through the LDS crossbar per 32 bits and stage.
-template <int J>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int lane)
+__device__ __forceinline__ int sweep_bin(uint32_t bits) { return (int)min(bits >> 19, (uint32_t)SW_BINS - 1u); }
+__device__ __forceinline__ int sweep_coarse(uint32_t bits) { return (int)min(bits >> 21, (uint32_t)SW_COARSE - 1u); }
+
+__device__ __forceinline__ double wave_incl_sum(double x, int lane)
 {
-    const int v = (int)x;
-    if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
-    else if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false); // quad_perm [2,3,0,1]
-    else if constexpr (J == 4) {
-        const int t = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false);                  // row_shl:4 -> lanes with bit 2 clear
-        return (uint32_t)__builtin_amdgcn_update_dpp(t, v, 0x114, 0xF, 0xA, false);               // row_shr:4 -> lanes with bit 2 set
-    } else if constexpr (J == 8) {
-        const int t = __builtin_amdgcn_update_dpp(v, v, 0x108, 0xF, 0x3, false);                  // row_shl:8 -> lanes 0-7 of a row
-        return (uint32_t)__builtin_amdgcn_update_dpp(t, v, 0x118, 0xF, 0xC, false);               // row_shr:8 -> lanes 8-15
-    } else if constexpr (J == 16) {
-        const auto sw = __builtin_amdgcn_permlane16_swap(x, x, false, false);                       // odd rows of [0] <-> even rows of [1]
-        return (lane & 16) ? sw[0] : sw[1];
-    } else {
-        const auto sw = __builtin_amdgcn_permlane32_swap(x, x, false, false);                       // upper half of [0] <-> lower half of [1]
-        return (lane & 32) ? sw[0] : sw[1];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(x, off);
+        if (lane >= off) x += o;
     }
+    return x;
 }
 
-// One compare-exchange stage at distance J of the bitonic network over a block of 128 keys (two per lane); kbit = the
-// merge size the stage belongs to (its bit of a key's index gives the direction).
-template <int J>
-__device__ __forceinline__ void wave_stage(u64 &k0, u64 &k1, int base, int kbit, int lane)
+// parent (0xFFFF: the root) | rank << 16 is what identifies a node; depth - 1 takes 4 bits and `cap` - 1, the most children, 8:
+// parent 12 bits, rank 8, depth 4, cap 8.
+__device__ __forceinline__ uint32_t sweep_meta(uint32_t par, uint32_t rank, int dep1, int cap) { return par | (rank << 12) | ((uint32_t)dep1 << 20) | ((uint32_t)(cap - 1) << 24); }
+constexpr uint32_t SW_ROOT = 0xFFFu;        // parent of the first level's nodes (no candidate that has children has this number)
+static_assert(SW_CAP <= 4096, "a parent's number takes 12 bits");
+
+// whole numbers: cap / (r + 1), cap <= 256
+__device__ __forceinline__ int sweep_share(int cap, int r) { return (int)(((float)cap + 0.5f) * __builtin_amdgcn_rcpf((float)(r + 1))); }
+
+__device__ __forceinline__ void sweep_put(SweepLds &L, int at, uint32_t score, uint32_t meta)
 {
-    if constexpr (J == 64) {
-        const bool desc = ((base + lane) & kbit) == 0;
-        const u64 hi = k0 > k1 ? k0 : k1, lo = k0 > k1 ? k1 : k0;
-        k0 = desc ? hi : lo;
-        k1 = desc ? lo : hi;
-    } else {
-        const bool lower = (lane & J) == 0;                       // this lane holds the pair's lower index
-        const u64 p0 = ((u64)lane_xor<J>((uint32_t)(k0 >> 32), lane) << 32) | lane_xor<J>((uint32_t)k0, lane);
-        const u64 p1 = ((u64)lane_xor<J>((uint32_t)(k1 >> 32), lane) << 32) | lane_xor<J>((uint32_t)k1, lane);
-        const bool max0 = lower == (((base + lane) & kbit) == 0), max1 = lower == (((base + 64 + lane) & kbit) == 0);
-        k0 = (max0 == (k0 > p0)) ? k0 : p0;
-        k1 = (max1 == (k1 > p1)) ? k1 : p1;
+    L.cand[at] = make_uint2(meta, score);
+    atomicAdd(&L.coarse[sweep_coarse(score)], 1);
+}
+
+// Children of one wavefront's nodes that score above the threshold: how many (first four in sc).
+__device__ __forceinline__ int sweep_count(float rp, int most, const float (&qr)[4], const float *qd, int K, int th, int lane, uint32_t (&sc)[4])
+{
+    int c = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        sc[r] = __float_as_uint(__fmul_rn(rp, qr[r]));
+        c += r < most && (int)sc[r] > th ? 1 : 0;              // (the scores fall with the rank)
     }
-}
-
-// the stages of one merge of size kbit, from distance J down to 1
-template <int J>
-__device__ __forceinline__ void wave_merge(u64 &k0, u64 &k1, int base, int kbit, int lane)
-{
-    wave_stage<J>(k0, k1, base, kbit, lane);
-    if constexpr (J > 1) wave_merge<J / 2>(k0, k1, base, kbit, lane);
-}
-
-// the whole network on one block of 128: merges of size 2, 4, ..., 128
-template <int K>
-__device__ __forceinline__ void wave_sort(u64 &k0, u64 &k1, int base, int lane)
-{
-    if constexpr (K > 2) wave_sort<K / 2>(k0, k1, base, lane);
-    wave_merge<K / 2>(k0, k1, base, K, lane);
-}
-
-__device__ __forceinline__ void bitonic_desc(u64 *key, int P2, int tid)
-{
-    const int lane = tid & 63, w = tid >> 6;
-    __syncthreads();
-    for (int blk = w; blk * 128 < P2; blk += 4) {                  // every block of 128 sorted on its own
-        u64 k0 = key[blk * 128 + lane], k1 = key[blk * 128 + 64 + lane];
-        wave_sort<128>(k0, k1, blk * 128, lane);
-        key[blk * 128 + lane] = k0;
-        key[blk * 128 + 64 + lane] = k1;
-    }
-    for (int k = 256; k <= P2; k <<= 1) {
-        for (int j = k >> 1; j >= 128; j >>= 1) {
-            __syncthreads();
-            for (int idx = tid; idx < P2 / 2; idx += 256) {
-                const int i1 = 2 * idx - (idx & (j - 1)), i2 = i1 + j;
-                const u64 a = key[i1], b = key[i2];
-                if ((a < b) == ((i1 & k) == 0)) { key[i1] = b; key[i2] = a; }
+    u64 wide = __builtin_amdgcn_ballot_w64(c == 4 && most > 4);
+    if (wide == 0ull) return c;
+    if (__builtin_popcountll(wide) <= 8) {                     // a few: the wavefront tests 64 ranks of each
+        while (wide != 0ull) {
+            const int src = __builtin_ctzll(wide);
+            wide &= wide - 1ull;
+            const float wr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rp), src));
+            const int wm = __builtin_amdgcn_readlane(most, src);
+            int cnt = 4;
+            for (int r0 = 4; r0 < wm; r0 += 64) {
+                const int r = r0 + lane;
+                const int got = __builtin_popcountll(__builtin_amdgcn_ballot_w64(r < wm && (int)__float_as_uint(__fmul_rn(wr, qd[min(r, K - 1)])) > th));
+                cnt += got;
+                if (got < 64) break;
             }
+            c = lane == src ? cnt : c;
+        }
+    } else {
+        int lo = 4, hi = c == 4 ? most : 4;
+        while (__builtin_amdgcn_ballot_w64(lo < hi) != 0ull) {
+            const int mid = (lo + hi) >> 1;
+            const bool ok = (int)__float_as_uint(__fmul_rn(rp, qd[min(mid, K - 1)])) > th, open = lo < hi;
+            lo = open && ok ? mid + 1 : lo;
+            hi = open && !ok ? mid : hi;
+        }
+        c = c == 4 ? lo : c;
+    }
+    return c;
+}
+
+// ... and their entries, from place `off` on.  i: the lane's node; lane src of the wavefront holds node i0 + src * step.
+__device__ __forceinline__ void sweep_write(SweepLds &L, int c, int off, int i, int i0, int step, uint32_t rb, int cap, int dep1, const float *qd, int lane,
+                                            const uint32_t (&sc)[4])
+{
+    const int part[4] = { cap, cap >> 1, (cap * 171) >> 9, cap >> 2 };      // cap / (r + 1)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if (__builtin_amdgcn_ballot_w64(r < c) == 0ull) return;
+        if (r < c) sweep_put(L, off + r, sc[r], sweep_meta((uint32_t)i, (uint32_t)r, dep1, part[r]));
+    }
+    u64 left = __builtin_amdgcn_ballot_w64(c > 4);
+    while (left != 0ull) {
+        const int src = __builtin_ctzll(left);
+        left &= left - 1ull;
+        const int wc = __builtin_amdgcn_readlane(c, src), wo = __builtin_amdgcn_readlane(off, src), wp = __builtin_amdgcn_readlane(cap, src);
+        const float wr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)rb, src));
+        for (int r = 4 + lane; r < wc; r += 64)
+            sweep_put(L, wo + r, __float_as_uint(__fmul_rn(wr, qd[r])), sweep_meta((uint32_t)(i0 + src * step), (uint32_t)r, dep1, sweep_share(wp, r)));
+    }
+}
+
+// The threshold, by one wavefront: lower edge of the coarse bin of the N-th best candidate (lane l: bins 8 l .. 8 l + 7).
+__device__ __forceinline__ int sweep_raise(const SweepLds &L, int N, int lane)
+{
+    const int4 x = reinterpret_cast<const int4 *>(L.coarse)[2 * lane], y = reinterpret_cast<const int4 *>(L.coarse)[2 * lane + 1];
+    const int s6 = y.w + y.z, s5 = s6 + y.y, s4 = s5 + y.x, s3 = s4 + x.w, s2 = s3 + x.z, s1 = s2 + x.y, own = s1 + x.x;
+    const int incl = wave_incl_scan(own), need = N - (__builtin_amdgcn_readlane(incl, 63) - incl);      // that many of this lane's best
+    const int sel = (y.w < need) + (s6 < need) + (s5 < need) + (s4 < need) + (s3 < need) + (s2 < need) + (s1 < need);
+    const u64 here = __builtin_amdgcn_ballot_w64(need > 0 && own >= need);
+    const int src = here != 0ull ? __builtin_ctzll(here) : 0;
+    return (8 * src + 7 - __builtin_amdgcn_readlane(sel, src)) << 21;
+}
+
+// Whole sweep.  Returns the number of candidates, -1 if they do not fit; th: the last threshold (score bits, as a signed number,
+// that a new candidate must exceed; -1 while there are fewer than N of them).
+__device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int &th)
+{
+    const int tid = w * 64 + lane, K1 = min(K, N);
+    if (tid < SW_COARSE / 4) reinterpret_cast<int4 *>(L.coarse)[tid] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    if (tid < K1)                                              // level 1: the K best tokens of position 0, already in order
+        sweep_put(L, tid, __float_as_uint(__fmul_rn(1.0f, S.q[tid])), sweep_meta(SW_ROOT, (uint32_t)tid, 0, sweep_share(N, tid)));
+    __syncthreads();
+    int d = 2, a = 0, b = K1, buf = 0;                         // the level before: candidates a .. b - 1
+    th = -1;
+    for (;;) {
+        if (w == 0) {
+            int seen = 0;                                      // candidates when the threshold was last moved
+            while (d <= B && a < b) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const float *qd = S.q + (d - 1) * KP;
+                const float qr[4] = { qd[0], qd[min(1, K - 1)], qd[min(2, K - 1)], qd[min(3, K - 1)] };
+                uint2 x = L.cand[min(a + lane, b - 1)];
+                // (a few more candidates since then hardly move it)
+                if (b >= N && (th < 0 || b - seen > (N >> 4))) { th = sweep_raise(L, N, lane); seen = b; }
+                if (b - a > SW_THIN) break;
+                int nb = b;
+                for (int a0 = a; a0 < b; a0 += 64) {
+                    const int i = a0 + lane;
+                    if (a0 != a) x = L.cand[min(i, b - 1)];
+                    const int cap = (int)(x.x >> 24) + 1;
+                    uint32_t sc[4];
+                    const int c = sweep_count(__uint_as_float(x.y), i < b ? min(cap, K) : 0, qr, qd, K, th, lane, sc);
+                    const int incl = wave_incl_scan(c), total = __builtin_amdgcn_readlane(incl, 63);
+                    if (nb + total > SW_CAP) { d = 0; break; }
+                    sweep_write(L, c, nb + incl - c, i, a0, 1, x.y, cap, d - 1, qd, lane, sc);
+                    nb += total;
+                }
+                if (d == 0) break;
+                a = b; b = nb;
+                ++d;
+            }
+            if (lane == 0) { L.d = d; L.a = a; L.b = b; L.th = th; }
         }
         __syncthreads();
-        for (int blk = w; blk * 128 < P2; blk += 4) {
-            u64 k0 = key[blk * 128 + lane], k1 = key[blk * 128 + 64 + lane];
-            wave_merge<64>(k0, k1, blk * 128, k, lane);
-            key[blk * 128 + lane] = k0;
-            key[blk * 128 + 64 + lane] = k1;
-        }
-    }
-    __syncthreads();
-}
-
-template <bool ADAPT>
-__device__ __forceinline__ void expand_levels(ExpandLds &S, LevelLds &L, int B, int K, int KP, int N, int tid, int32_t *parent,
-                                              int32_t *token, int32_t *depth, float *rho, int32_t *n_out, float *ahat,
-                                              const Adaptive &ad)
-{
-    const int lane = tid & 63, w = tid >> 6;
-    const int lg = 31 - __builtin_clz((unsigned)KP);
-    const u64 below = (1ull << lane) - 1ull;
-    int cur = 0, np = min(K, N);
-    L.rcap[tid] = (uint16_t)min(K, N / (tid + 1));
-    if (tid < np) {                                            // level 1: the K best tokens of position 0, already in order
-        L.pkey[0][tid] = ((u64)__float_as_uint(__fmul_rn(1.0f, S.q[tid])) << 32) | (30u << 16) | (0xFFFFu - (uint32_t)tid);
-        L.pval[0][tid] = (uint32_t)tid | (0xFFFu << 12) | ((uint32_t)tid << 24);
-        L.lex2id[tid] = (uint16_t)tid;
-    }
-    if (tid < LV_PAD) L.pkey[0][np + tid] = 0ull;         // the zero keys behind the pool
-    __syncthreads();
-    // No LDS read of the loop sits behind a lane-dependent branch (the compiler would wait for each on its own):
-    // lanes without work read place 0 and drop the result.  The searches run a fixed, wave-uniform number of steps.
-    const int search_steps = 32 - __builtin_clz((unsigned)min(K, N));
-    uint32_t top = __float_as_uint(__fmul_rn(1.0f, S.q[0]));   // the largest score among the nodes of the level before d
-    for (int d = 2; d <= B; ++d) {
-        // ---- how many children each pool node of depth d-1 proposes ------------------------------------------------
+        d = __builtin_amdgcn_readfirstlane(L.d); a = __builtin_amdgcn_readfirstlane(L.a); b = __builtin_amdgcn_readfirstlane(L.b);
+        th = __builtin_amdgcn_readfirstlane(L.th);
+        if (d == 0) return -1;
+        if (d > B || a == b) break;
+        // ---- a wide level, by the whole workgroup ----------------------------------------------------------------------
         const float *qd = S.q + (d - 1) * KP;
-        const u64 k = L.pkey[cur][tid < np ? tid : 0];
-        const uint32_t v = L.pval[cur][tid < np ? tid : 0];
-        const uint32_t g32 = (uint32_t)(L.pkey[cur][N - 1] >> 32);   // the pool's last score (read, not used, before the pool is full)
-        // The pool is full and not even the best child of the level's best node reaches its last score (the product
-        // rises with the parent's score): nobody proposes anything, as the counts below would find out at the cost
-        // of a search per parent.
-        if (np == N && __float_as_uint(__fmul_rn(__uint_as_float(top), qd[0])) < g32) break;      // (uniform)
-        const int rcap = L.rcap[v & 0xFFu];
-        const float rp = __uint_as_float((uint32_t)(k >> 32));
-        int c = tid < np && 31 - (int)((k >> 16) & 31u) == d - 1 ? rcap : 0;
-        if (np == N) {                                         // only scores that reach the pool's last node; they fall with the rank
-            int lo = 0, hi = c;
-            for (int st = 0; st < search_steps; ++st) {
-                const int mid = (lo + hi) >> 1;
-                const bool ge = __float_as_uint(__fmul_rn(rp, qd[mid])) >= g32;
-                const bool open = lo < hi;
-                lo = open && ge ? mid + 1 : lo;
-                hi = open && !ge ? mid : hi;
-            }
-            c = lo;
+        const float qr[4] = { qd[0], qd[min(1, K - 1)], qd[min(2, K - 1)], qd[min(3, K - 1)] };
+        int nb = b;
+        for (int a0 = a; a0 < b; a0 += 256, buf ^= 1) {
+            const int i = a0 + 4 * lane + w;
+            const uint2 x = L.cand[min(i, b - 1)];
+            const int cap = (int)(x.x >> 24) + 1;
+            uint32_t sc[4];
+            const int c = sweep_count(__uint_as_float(x.y), i < b ? min(cap, K) : 0, qr, qd, K, th, lane, sc);
+            L.cnt[buf][4 * lane + w] = c;
+            __syncthreads();
+            const int4 c4 = reinterpret_cast<const int4 *>(L.cnt[buf])[lane];
+            const int sum = c4.x + c4.y + c4.z + c4.w, incl = wave_incl_scan(sum), total = __builtin_amdgcn_readlane(incl, 63);
+            if (nb + total > SW_CAP) return -1;                // (uniform)
+            sweep_write(L, c, nb + incl - sum + (w > 0 ? c4.x : 0) + (w > 1 ? c4.y : 0) + (w > 2 ? c4.z : 0), i, a0 + w, 4, x.y, cap, d - 1, qd, lane, sc);
+            nb += total;
         }
-        const int incl = wave_incl_scan(c);
-        if (lane == 63) L.wsum[w] = incl;
-        L.mark[tid] = 0;
-        L.hist[tid] = 0;
-        if (tid == 0) L.hist[BTV_MAX_NODES] = 0;
         __syncthreads();
-        const int ws0 = L.wsum[0], ws1 = L.wsum[1], ws2 = L.wsum[2], ws3 = L.wsum[3];
-        const int base = (w > 0 ? ws0 : 0) + (w > 1 ? ws1 : 0) + (w > 2 ? ws2 : 0);
-        const int C = ws0 + ws1 + ws2 + ws3;
-        const int off = base + incl - c;
-        L.off[tid] = off;
-        if (C == 0) break;                                     // (uniform)
-        if (C > LV_CAND) {                                     // cannot happen (sum over i of N / (i+1) <= 1570 at N = 256)
-            if (tid == 0) atomicOr(ad.flag, 8u);
-            break;
-        }
-        const int nxt = cur ^ 1;
-        if (C <= 256) {
-            // ---- few proposals: one per thread, placed by counting ---------------------------------------------------
-            // Candidate j belongs to the last pool entry whose offset does not exceed j: the entries mark where their
-            // proposals start and a running maximum carries the marks along.
-            if (c > 0) L.mark[off] = (uint16_t)(tid + 1);
-            __syncthreads();
-            const int mk = wave_incl_max((int)L.mark[tid]);
-            if (lane == 63) L.wmax[w] = mk;
-            __syncthreads();
-            const int wm0 = L.wmax[0], wm1 = L.wmax[1], wm2 = L.wmax[2];
-            const int carry = max(max(w > 0 ? wm0 : 0, w > 1 ? wm1 : 0), w > 2 ? wm2 : 0);
-            const bool live = tid < C;
-            const int pe = live ? max(mk, carry) - 1 : 0;
-            const int r = live ? tid - L.off[pe] : 0;
-            const u64 pk = L.pkey[cur][pe];
-            const uint32_t plex = L.pval[cur][pe] >> 24;
-            const uint32_t sc = __float_as_uint(__fmul_rn(__uint_as_float((uint32_t)(pk >> 32)), qd[r]));
-            L.ckey[tid] = live ? ((u64)sc << 32) | ((uint32_t)(31 - d) << 16) | (0xFFFFu - ((plex << lg) + (uint32_t)r)) : 0ull;
-            if (tid < LV_PAD) L.ckey[256 + tid] = 0ull;        // with the zeros from C on: the zero keys behind the list
-            __syncthreads();
-            // A candidate's new place = the candidates above it + the pool nodes above it, both counted (T = 1, 2 or 4
-            // neighbouring lanes share a candidate, two keys per LDS read, eight reads in flight); a pool node moves
-            // down by the candidates above it = the candidates with at most its own place in pool nodes above them.
-            const int lgT = C <= 64 ? 2 : C <= 128 ? 1 : 0, T = 1 << lgT;
-            const int ci = tid >> lgT, part = tid & (T - 1);
-            const u64 mine = L.ckey[ci];                        // zero from C on: never placed
-            const uint32_t cval = (uint32_t)L.lex2id[(0xFFFFu - (uint32_t)(mine & 0xFFFFu)) >> lg] << 12;
-            const ulonglong2 *two = reinterpret_cast<const ulonglong2 *>(L.ckey);
-            const ulonglong2 *ptwo = reinterpret_cast<const ulonglong2 *>(L.pkey[cur]);
-            // The T lanes of a candidate take the pairs of a list in turn (lane `part` reads pairs part, part + T, ...),
-            // eight reads in flight, every address the trip's base plus a constant: with a compare, a select and an
-            // address sum per read the loop spent half its instructions on addresses.  The reads run past the list's
-            // end into LV_PAD zero keys, which are above nothing.
-            auto count_above = [&](auto t_c, const ulonglong2 *list, int n) {
-                constexpr int TT = decltype(t_c)::value;
-                const int pairs = (n + 1) >> 1, per = (pairs + TT - 1) / TT;
-                const ulonglong2 *at = list + part;
-                int cnt = 0;
-                for (int q = 0; q < per; q += 8, at += 8 * TT) {          // (uniform)
-                    ulonglong2 kk[8];
+        a = b; b = nb;
+        ++d;
+    }
+    th = b > N ? sweep_raise(L, N, lane) : -1;                 // (what lies below the threshold's bin is not looked at any more)
+    return b;
+}
+
+// more: nothing is written, and false returned, if the early stop has not come within N nodes.
+__device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, bool adapt, bool more, int tid, int32_t *parent,
+                                             int32_t *token, int32_t *depth, float *rho, int32_t *n_out, float *ahat,
+                                             const Adaptive &ad)
+{
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) kk[u] = at[u * TT];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        cnt += kk[u].x > mine ? 1 : 0;
-                        cnt += kk[u].y > mine ? 1 : 0;
-                    }
-                }
-                return cnt;
-            };
-            auto count_list = [&](const ulonglong2 *list, int n) {
-                if (lgT == 2) return count_above(std::integral_constant<int, 4>{}, list, n);
-                if (lgT == 1) return count_above(std::integral_constant<int, 2>{}, list, n);
-                return count_above(std::integral_constant<int, 1>{}, list, n);
-            };
-            int above_c = count_list(two, C), above_p = 0;
-            if (np <= 128) {
-                above_p = count_list(ptwo, np);
-            } else if (part == 0) {                            // a long pool: binary search, by the candidate's first lane
-                int lo = 0, hi = np;
-                for (int st = 0; st < 9; ++st) {
-                    const int mid = (lo + hi) >> 1;
-                    const bool gt = L.pkey[cur][mid] > mine;
-                    const bool open = lo < hi;
-                    lo = open && gt ? mid + 1 : lo;
-                    hi = open && !gt ? mid : hi;
-                }
-                above_p = lo;
-            }
-            if (T >= 2) {
-                above_c += __builtin_amdgcn_update_dpp(0, above_c, 0xB1, 0xF, 0xF, false);
-                above_p += __builtin_amdgcn_update_dpp(0, above_p, 0xB1, 0xF, 0xF, false);
-            }
-            if (T == 4) {
-                above_c += __builtin_amdgcn_update_dpp(0, above_c, 0x4E, 0xF, 0xF, false);
-                above_p += __builtin_amdgcn_update_dpp(0, above_p, 0x4E, 0xF, 0xF, false);
-            }
-            if (part == 0 && ci < C) {
-                atomicAdd(&L.hist[above_p], 1);
-                if (above_c + above_p < N) {
-                    L.pkey[nxt][above_c + above_p] = mine;
-                    L.pval[nxt][above_c + above_p] = cval;
-                }
-            }
-            __syncthreads();
-            const int hs = wave_incl_scan(L.hist[tid]);
-            if (lane == 63) L.wsum2[w] = hs;
-            __syncthreads();
-            const int h0 = L.wsum2[0], h1 = L.wsum2[1], h2 = L.wsum2[2];
-            const int moved = hs + (w > 0 ? h0 : 0) + (w > 1 ? h1 : 0) + (w > 2 ? h2 : 0);
-            if (tid < np && tid + moved < N) { L.pkey[nxt][tid + moved] = k; L.pval[nxt][tid + moved] = v; }
-        } else {
-            __syncthreads();
-            // ---- the proposals: candidate j belongs to the last pool entry whose offset does not exceed j -----------
-            int P2 = 512;
-            while (P2 < C) P2 <<= 1;
-            for (int j = tid; j < P2; j += 256) {
-                u64 key = 0ull;
-                if (j < C) {
-                    int lo = 0, hi = np;                       // first entry with off > j
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (L.off[mid] <= j) lo = mid + 1; else hi = mid;
-                    }
-                    const int pe = lo - 1, r = j - L.off[pe];
-                    const u64 pk = L.pkey[cur][pe];
-                    const uint32_t sc = __float_as_uint(__fmul_rn(__uint_as_float((uint32_t)(pk >> 32)), qd[r]));
-                    key = ((u64)sc << 32) | ((uint32_t)(31 - d) << 16) | (0xFFFFu - (((L.pval[cur][pe] >> 24) << lg) + (uint32_t)r));
-                }
-                L.ckey[j] = key;
-            }
-            bitonic_desc(L.ckey, P2, tid);
-            // ---- merge: a node's new place = its place in its own list + the nodes of the other list ahead of it ----
-            for (int j = tid; j < C; j += 256) {
-                const u64 ck = L.ckey[j];
-                int lo = 0, hi = np;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (L.pkey[cur][mid] > ck) lo = mid + 1; else hi = mid;
-                }
-                if (j + lo < N) {
-                    L.pkey[nxt][j + lo] = ck;
-                    L.pval[nxt][j + lo] = (uint32_t)L.lex2id[(0xFFFFu - (uint32_t)(ck & 0xFFFFu)) >> lg] << 12;
-                }
-            }
-            if (tid < np) {
-                int lo = 0, hi = C;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (L.ckey[mid] > k) lo = mid + 1; else hi = mid;
-                }
-                if (tid + lo < N) { L.pkey[nxt][tid + lo] = k; L.pval[nxt][tid + lo] = v; }
-            }
-        }
-        L.cnt_lex[tid] = 0;
-        np = min(np + C, N);
-        cur = nxt;
-        if (tid < LV_PAD) L.pkey[cur][np + tid] = 0ull;
-        __syncthreads();
-        // ---- the new level's nodes get their id and their lexicographic place --------------------------------------
-        const u64 k2 = L.pkey[cur][tid < np ? tid : 0];
-        const bool mine2 = tid < np && 31 - (int)((k2 >> 16) & 31u) == d;
-        const uint32_t lexkey = 0xFFFFu - (uint32_t)(k2 & 0xFFFFu);
-        const u64 bal = __builtin_amdgcn_ballot_w64(mine2);
-        {   // the pool is in falling order: a wavefront's first node of the new level is its best
-            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k2 >> 32), bal != 0ull ? __builtin_ctzll(bal) : 0);
-            if (lane == 0) { L.wsum2[w] = __builtin_popcountll(bal); L.wtop[w] = bal != 0ull ? first : 0u; }
-        }
-        if (mine2) atomicAdd(&L.cnt_lex[lexkey >> lg], 1);
-        __syncthreads();
-        top = umax(umax(L.wtop[0], L.wtop[1]), umax(L.wtop[2], L.wtop[3]));
-        const int p0 = L.wsum2[0], p1 = L.wsum2[1], p2 = L.wsum2[2];
-        const int place = __builtin_popcountll(bal & below) + (w > 0 ? p0 : 0) + (w > 1 ? p1 : 0) + (w > 2 ? p2 : 0);
-        const int cl = L.cnt_lex[tid];
-        const int il = wave_incl_scan(cl);
-        if (lane == 63) L.wsum[w] = il;
-        __syncthreads();
-        const int l0 = L.wsum[0], l1 = L.wsum[1], l2 = L.wsum[2];
-        L.cnt_lex[tid] = il - cl + (w > 0 ? l0 : 0) + (w > 1 ? l1 : 0) + (w > 2 ? l2 : 0);
-        __syncthreads();
-        const uint32_t lexpos = (uint32_t)L.cnt_lex[mine2 ? lexkey >> lg : 0] + (lexkey & (uint32_t)(KP - 1));
-        const uint32_t pv2 = L.pval[cur][tid < np ? tid : 0];
-        if (mine2) {
-            L.pval[cur][tid] = (uint32_t)((d - 1) * 256 + place) | (pv2 & 0x00FFF000u) | (lexpos << 24);
-            L.lex2id[lexpos] = (uint16_t)((d - 1) * 256 + place);
-        }
-        __syncthreads();
+    for (int i = 0; i < SW_BINS / 1024; ++i) reinterpret_cast<int4 *>(L.hist)[i * 256 + tid] = make_int4(0, 0, 0, 0);
+    // ---- the N first of the candidates, in order ---------------------------------------------------------------------
+    int th;
+    const int b = sweep_levels(S, L, B, K, KP, N, lane, w, th);
+    if (b < 0) return false;                                   // (uniform)
+    const int np = min(b, N);
+    for (int c = tid; c < b; c += 256) {
+        const uint32_t r = L.cand[c].y;
+        if ((int)r >= th) atomicAdd(&L.hist[sweep_bin(r)], 1);
     }
     __syncthreads();
-    // ---- the pool is the tree, in emission order ---------------------------------------------------------------------
+    int kept;                                                  // candidates that are left
+    {                                                          // thread t: bins 8 t .. 8 t + 7, and what lies above them
+        const int4 x = reinterpret_cast<const int4 *>(L.hist)[2 * tid], y = reinterpret_cast<const int4 *>(L.hist)[2 * tid + 1];
+        const int s7 = y.w, s6 = s7 + y.z, s5 = s6 + y.y, s4 = s5 + y.x, s3 = s4 + x.w, s2 = s3 + x.z, s1 = s2 + x.y, own = s1 + x.x;
+        const int incl = wave_incl_scan(own), total = __builtin_amdgcn_readlane(incl, 63);
+        if (lane == 0) L.wsum[w] = total;
+        __syncthreads();
+        const int t0 = L.wsum[0], t1 = L.wsum[1], t2 = L.wsum[2], t3 = L.wsum[3];
+        const int up = total - incl + (w < 1 ? t1 : 0) + (w < 2 ? t2 : 0) + (w < 3 ? t3 : 0);
+        kept = t0 + t1 + t2 + t3;
+        const int4 p = make_int4(up + s1, up + s2, up + s3, up + s4), q = make_int4(up + s5, up + s6, up + s7, up);
+        reinterpret_cast<int4 *>(L.hist)[2 * tid] = p;
+        reinterpret_cast<int4 *>(L.hist)[2 * tid + 1] = q;
+        reinterpret_cast<int4 *>(L.at)[2 * tid] = p;
+        reinterpret_cast<int4 *>(L.at)[2 * tid + 1] = q;
+    }
+    __syncthreads();
+    if (kept > SW_KEEP) return false;                          // (uniform) scores that are nearly all the same
+    for (int c = tid; c < b; c += 256) {
+        const uint32_t r = L.cand[c].y;
+        if ((int)r >= th) L.key[atomicAdd(&L.at[sweep_bin(r)], 1)] = ((u64)r << 32) | (u64)(0xFFFFFFFFu - (uint32_t)c);
+    }
+    __syncthreads();
+    for (int p = tid; p < kept; p += 256) {
+        const u64 k = L.key[p];
+        const int bin = sweep_bin((uint32_t)(k >> 32)), lo = L.hist[bin], hi = L.at[bin];
+        int place = lo;
+        for (int j = lo; j < hi; ++j) place += L.key[j] > k ? 1 : 0;
+        const uint32_t c = 0xFFFFFFFFu - (uint32_t)k;
+        L.cand[c].y = (uint32_t)place;
+        L.order[place] = (uint16_t)p;
+    }
+    __syncthreads();
+    const u64 k = L.key[tid < np ? L.order[tid] : 0];
+    const uint32_t mt = L.cand[0xFFFFFFFFu - (uint32_t)k].x;
+    const float r = tid < np ? __uint_as_float((uint32_t)(k >> 32)) : 0.f;
+    const int rank = (int)((mt >> 12) & 0xFFu), dep = (int)((mt >> 20) & 0xFu) + 1;
+    const uint32_t par = mt & 0xFFFu;
     int n = np;
-    if (ADAPT) {
-        // Sec. 3.4, Eq. 6: the budget stops at the first node that does not improve Ahat(n) * L_AR / C(n); Ahat is summed
-        // in emission order in fp64, by one thread
-        if (tid == 0) {
-            double run_a = 1.0, best_a = 0.0, best_c = 0.0;
-            int m = 0;
-            for (; m < np; ++m) {
-                const double c_n = S.cost[m];
-                const double a_new = run_a + (double)__uint_as_float((uint32_t)(L.pkey[cur][m] >> 32));
-                if (!(c_n > 0.0)) { atomicOr(ad.flag, 4u); break; }
-                if (m > 0 && !(a_new * best_c > best_a * c_n)) break;
-                run_a = a_new; best_a = a_new; best_c = c_n;
-            }
-            L.n_stop = m;
-            *n_out = m;
-            if (ahat) *ahat = (float)run_a;
-            if (ad.s_best) *ad.s_best = m > 0 ? best_a * ad.L_AR / best_c : -INFINITY;
-        }
+    if (adapt) {
+        // Sec. 3.4, Eq. 6: the budget stops at the first node that does not improve Ahat(n) * L_AR / C(n); all nodes before
+        // it improved, so a node is compared with the one before it (fp64 prefix sums in emission order)
+        double sum = wave_incl_sum((double)r, lane);
+        if (lane == 63) L.wd[w] = sum;
+        if (tid == 0) L.n_stop = np;
+        __syncthreads();
+        const double w0 = L.wd[0], w1 = L.wd[1], w2 = L.wd[2];
+        const double an = 1.0 + ((w > 0 ? w0 : 0.0) + (w > 1 ? w1 : 0.0) + (w > 2 ? w2 : 0.0) + sum), before = an - (double)r;
+        const double cn = tid < np ? S.cost[tid] : 1.0, cb = tid > 0 && tid < np ? S.cost[tid - 1] : 1.0;
+        if (tid < np && (!(cn > 0.0) || (tid > 0 && !(an * cb > before * cn)))) atomicMin(&L.n_stop, tid);
         __syncthreads();
         n = L.n_stop;
+        if (more && n == N) return false;                      // (uniform) still improving: the caller goes on to a larger budget
+        if (tid == n && n < np && !(cn > 0.0)) atomicOr(ad.flag, 4u);
+        if (tid == max(n - 1, 0)) {
+            *n_out = n;
+            if (ahat) *ahat = n > 0 ? (float)an : 1.0f;
+            if (ad.s_best) *ad.s_best = n > 0 ? an * ad.L_AR / cn : -INFINITY;
+        }
     }
-    if (tid < np) L.pos_of[L.pval[cur][tid] & 0xFFFu] = (uint16_t)tid;
-    __syncthreads();
-    double a = 0.0;
     if (tid < n) {
-        const u64 k = L.pkey[cur][tid];
-        const uint32_t v = L.pval[cur][tid];
-        const int dep = 31 - (int)((k >> 16) & 31u);
-        const uint32_t lexkey = 0xFFFFu - (uint32_t)(k & 0xFFFFu);
-        const int idx = (dep - 1) * KP + (int)(lexkey & (uint32_t)(KP - 1));
-        const uint32_t pu = (v >> 12) & 0xFFFu;
-        const float r = __uint_as_float((uint32_t)(k >> 32));
-        token[tid] = (int32_t)S.tok[idx];
-        parent[tid] = pu == 0xFFFu ? -1 : (int32_t)L.pos_of[pu];
+        token[tid] = (int32_t)S.tok[(dep - 1) * KP + rank];
+        parent[tid] = par == SW_ROOT ? -1 : (int32_t)L.cand[par].y;
         if (depth) depth[tid] = dep;
         if (rho) rho[tid] = r;
-        a = (double)r;
     }
-    if (!ADAPT) {
+    if (!adapt) {
+        double sum = (double)r;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off);
-        if (lane == 0) L.dsum[w] = a;
+        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+        if (lane == 0) L.wd[w] = sum;
         __syncthreads();
         if (tid == 0) {
             *n_out = n;
-            if (ahat) *ahat = (float)(1.0 + ((L.dsum[0] + L.dsum[1]) + (L.dsum[2] + L.dsum[3])));
+            if (ahat) *ahat = (float)(1.0 + ((L.wd[0] + L.wd[1]) + (L.wd[2] + L.wd[3])));
         }
     }
+    return true;
 }
 
 // Workgroup `row` ranks the candidates of its position into top_q / top_tok (global, [B][KP]); the workgroup that
@@ -1032,20 +924,20 @@ __device__ __forceinline__ void beam_block(const ExpandLds &S, BeamLds &Bm, int 
     }
 }
 
-__global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, int B, int K, int KP, int N, int chunks,
+__global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, int B, int K, int KP, int N, int chunks, int lge,
                                                       TbCounters *ctr, const uint2 *part, float *top_q, uint32_t *top_tok,
                                                       int32_t *parent,
                                                       int32_t *token, int32_t *depth, float *rho, int32_t *n_out, float *ahat,
                                                       Adaptive ad, int beam_width, Batch bt, int algo)
 {
-    __shared__ union RankOrLevels { RankLds rank; LevelLds lev; } U;     // the ranking is over when the expansion starts
+    __shared__ union RankOrLevels { RankLds rank; SweepLds lev; } U;     // the ranking is over when the expansion starts
     __shared__ ExpandLds S;
     __shared__ BeamLds BM;
     __shared__ int use_levels;
     RankLds &RL = U.rank;
     // Fetch every argument in one round trip: left to the compiler the scalar loads follow the code in four
     // dependent steps over an argument block of several cache lines that is cold in every launch.
-    asm volatile("" ::"s"(marg), "s"(V), "s"(B), "s"(K), "s"(KP), "s"(N), "s"(chunks), "s"(ctr), "s"(part), "s"(top_q),
+    asm volatile("" ::"s"(marg), "s"(V), "s"(B), "s"(K), "s"(KP), "s"(N), "s"(chunks), "s"(lge), "s"(ctr), "s"(part), "s"(top_q),
                  "s"(top_tok), "s"(parent), "s"(token), "s"(depth), "s"(rho), "s"(n_out), "s"(ahat), "s"(ad.cost), "s"(ad.L_AR),
                  "s"(ad.s_best), "s"(ad.flag), "s"(beam_width), "s"(bt.n_nodes), "s"(bt.q_offset), "s"(bt.flag));
     // Workgroup `row` = position row % B of request row / B; marginals, per-thread maxima and top lists are laid out
@@ -1059,17 +951,29 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     const uint2 *pr = part + (size_t)row * chunks * 256 + tid;
     // ---- the bound: K-th largest per-thread maximum of the row, down to the lower edge of its histogram bin ---
     uint32_t pv[16], pw[16];                                   // the loads are in flight while the histogram is cleared
+    uint32_t live = 0u;                                        // bit j: this thread has a slot in chunk j
+    if (lge == 0) {                                            // every marginal is a slot of its own (chunks <= 16)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const uint2 x = pr[(size_t)(j < chunks ? j : 0) * 256];      // no load behind a branch: all of them in flight at once
-        pv[j] = j < chunks ? x.x : 0u;
-        pw[j] = x.y;
+        for (int j = 0; j < 16; ++j) {
+            const int v = j * 256 + tid;
+            pv[j] = prob_bits(src[v < V ? v : 0]);
+            pw[j] = 0u;
+            live |= v < V ? 1u << j : 0u;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const uint2 x = pr[(size_t)(j < chunks ? j : 0) * 256];      // no load behind a branch: all of them in flight at once
+            pv[j] = x.x;
+            pw[j] = x.y;
+            live |= j < chunks ? 1u << j : 0u;
+        }
     }
     for (int b = tid; b < (TBINS + TBINS / 16) / 4; b += 256) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
     if (tid == 0) { RL.nsel = 0; RL.nslot = 0; }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 16; ++j) if (j < chunks) atomicAdd(&RL.bins[bin_at((int)(pv[j] >> 19))], 1);
+    for (int j = 0; j < 16; ++j) if ((live >> j) & 1u) atomicAdd(&RL.bins[bin_at((int)(pv[j] >> 19))], 1);
     for (int j = 16; j < chunks; ++j) atomicAdd(&RL.bins[bin_at((int)(pr[(size_t)j * 256].x >> 19))], 1);
     __syncthreads();
     {
@@ -1115,15 +1019,15 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         uint32_t one = 0u, more = 0u;                           // chunks whose slot holds one candidate / maybe several
 #pragma unroll
         for (int j = 0; j < 16; ++j)
-            if (j < chunks && pv[j] >= tau) {
-                if (pw[j] >= tau) more |= 1u << j; else one |= 1u << j;
+            if (((live >> j) & 1u) && pv[j] >= tau) {
+                if (pw[j] >= tau && lge != 0) more |= 1u << j; else one |= 1u << j;
             }
         int pos = wave_range(__builtin_popcount(one), &RL.nsel);
         while (__builtin_amdgcn_ballot_w64(one != 0u) != 0ull) {
             const bool has = one != 0u;
             const int j = has ? __builtin_ctz(one) : 0;
             const uint32_t k = BTV_PICK16(pw, j) & 31u;
-            const uint32_t v = (uint32_t)(j * SCAN + tid * 4) + (k >> 2) * 1024u + (k & 3u);
+            const uint32_t v = (uint32_t)slot_first(lge, j, tid) + (k >> 2) * 1024u + (k & 3u);
             RL.sel[has && pos < SELCAP ? pos : SELCAP + lane] = ((u64)BTV_PICK16(pv, j) << 32) | (u64)(0xFFFFFFFFu - v);
             pos += has ? 1 : 0;
             one &= one - 1u;
@@ -1149,8 +1053,8 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     if (nslot == 0 && chunks <= 256) {
         // nothing to read again
     } else if (nslot <= SLOTCAP && chunks <= 256) {
-        constexpr int PPS = SCAN / 1024;                       // 16-byte pieces per slot
-        const int total = nslot * PPS;
+        const int lgp = lge - 2, pmask = (1 << lgp) - 1;       // 16-byte pieces per slot (lge >= 2 here)
+        const int total = nslot << lgp;
         const bool whole = aligned && (V & 3) == 0;            // every piece that starts inside the row ends inside it
         for (int base = 0; base < total; base += 4 * 256) {
             float pe[16];
@@ -1161,12 +1065,12 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int i = base + u * 256 + tid;
-                    sl[u] = RL.slot[(i < total ? i : 0) / PPS];
+                    sl[u] = RL.slot[(i < total ? i : 0) >> lgp];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int i = base + u * 256 + tid;
-                    v0[u] = (sl[u] >> 8) * SCAN + (i % PPS) * 1024 + (sl[u] & 255) * 4;
+                    v0[u] = slot_first(lge, sl[u] >> 8, sl[u] & 255) + (i & pmask) * 1024;
                     if (i >= total || v0[u] >= V) v0[u] = -1;
                     const float4 a = *reinterpret_cast<const float4 *>(src + (v0[u] < 0 ? 0 : v0[u]));
                     pe[4 * u] = a.x; pe[4 * u + 1] = a.y; pe[4 * u + 2] = a.z; pe[4 * u + 3] = a.w;
@@ -1185,8 +1089,8 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) pe[4 * u + e] = 0.f;
                     if (i < total) {
-                        const int sl = RL.slot[i / PPS];
-                        v0[u] = (sl >> 8) * SCAN + (i % PPS) * 1024 + (sl & 255) * 4;
+                        const int sl = RL.slot[i >> lgp];
+                        v0[u] = slot_first(lge, sl >> 8, sl & 255) + (i & pmask) * 1024;
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             if (v0[u] + e < V) {
@@ -1228,7 +1132,10 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     // ---- the workgroup that finishes last expands -------------------------------------------------------------
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread's part of the lists has reached memory
     __syncthreads();
-    if (tid == 0) RL.last = __hip_atomic_fetch_add(&ctr[req].done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == B - 1;
+    if (tid == 0) {
+        RL.last = __hip_atomic_fetch_add(&ctr[req].done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == B - 1;
+        if (RL.last) __hip_atomic_store(&ctr[req].done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next call
+    }
     __syncthreads();
     if (!RL.last) return;
     {   // all of a thread's loads are issued before the first is stored (a load and its store per loop trip would
@@ -1278,62 +1185,67 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         beam_block(S, BM, B, K, KP, beam_width, tid, parent, token, depth, rho, n_out, ahat);
         return;
     }
-    // Which expansion: the level-synchronous one pays per level (measured: about 2.5 us up to 32 nodes, 3.0 to 64,
-    // 3.6 to 128, 4.2 beyond), the one-wavefront one per node (0.27 / 0.31 / 0.41 us up to 64 / 128 / 256 nodes), and
-    // with the early stop it ends at the chosen budget, typically a quarter of N_max.  The tree cannot be deeper than
-    // the greedy chain stays above the N-th best token of the first position (every node scores at least as much as
-    // the tree's last one, which scores at least that); a tree of depth 1 is the first level's list as it stands.
-    if (tid == 0) {
-        int reach = 0;
-        if (algo == 0) {
-            const float g_est = S.q[min(K, N) - 1];
-            float chain = 1.0f;
-            for (int k = 0; k < B; ++k) {
-                chain = __fmul_rn(chain, S.q[k * KP]);
-                if (!(chain >= g_est)) break;
-                reach = k + 1;
-            }
+    // Which expansion: the sweep pays per level (about 0.9 us, and 2 us at the end), the one-wavefront loop per node (0.27 us up to 64
+    // nodes, 0.41 us at 256), so the loop is left with the smallest trees that may be deep.  The tree cannot be deeper
+    // than the greedy chain stays above the N-th best token of the first position (every node scores at least as much as
+    // the tree's last one, which scores at least that).
+    // 16 positions x 128256 tokens, HIP-graph replays, sweep / loop: flat marginals (a star) N = 64: 14.8 / 27.9 us, N = 256: 22 / 114;
+    // depth 5 .. 6: N = 64: 20.3 / 27.9, N = 256: 32 / 114; a confident drafter (depth 8 .. 13) N = 8: 17.5 / 13.4, N = 16: 19.3 / 15.2,
+    // N = 64: 23.6 / 28, N = 256: 35 / 113 (65 with a pool kept in order from level to level, which this replaced).
+    if (w == 0) {
+        const int k = min(lane, B - 1);
+        float chain = lane < B ? __log2f(S.q[k * KP]) : -1e30f;            // (an estimate: the choice changes no result)
+#pragma unroll
+        for (int off = 1; off < MAXB; off <<= 1) {
+            const float o = __shfl_up(chain, off);
+            if (lane >= off) chain += o;
         }
-        const float per_level = N <= 32 ? 2.5f : N <= 64 ? 3.0f : N <= 128 ? 3.6f : 4.2f;
-        const float per_node = N <= 64 ? 0.27f : N <= 128 ? 0.31f : 0.41f;
-        const float nodes = ad.cost ? 0.25f * (float)N : (float)N;
-        use_levels = algo == 2 || (algo == 0 && (reach <= 1 || (float)reach * per_level < nodes * per_node));
+        const float g_est = __log2f(S.q[min(K, N) - 1]);
+        const int reach = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < B && chain >= g_est));
+        if (lane == 0) use_levels = algo == 2 || (algo == 0 && (N > 64 || 2.0f + 0.9f * (float)min(reach, N) < 0.27f * (float)N));
     }
     __syncthreads();
     if (use_levels) {
-        if (ad.cost) expand_levels<true>(S, U.lev, B, K, KP, N, tid, parent, token, depth, rho, n_out, ahat, ad);
-        else expand_levels<false>(S, U.lev, B, K, KP, N, tid, parent, token, depth, rho, n_out, ahat, ad);
-        return;
+        // with the early stop: it comes within the first 64 nodes as a rule, and their tree is a prefix of the larger one
+        const bool adapt = ad.cost != nullptr;
+        bool done = false;
+        for (int budget = adapt ? min(N, 64) : N;; budget = N) {
+            done = expand_sweep(S, U.lev, B, K, KP, budget, adapt, budget < N, tid, parent, token, depth, rho, n_out, ahat, ad);
+            if (done || budget == N) break;
+            __syncthreads();
+        }
+        if (done) return;
     }
     if (w != 0) return;
     if (ad.cost) {
         if (N <= 64) expand_wave<1, true>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
-        else if (N <= 128) expand_wave<2, true>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
         else expand_wave<4, true>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
     } else {
         if (N <= 64) expand_wave<1, false>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
-        else if (N <= 128) expand_wave<2, false>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
         else expand_wave<4, false>(S, B, K, KP, N, lane, parent, token, depth, rho, n_out, ahat, ad);
     }
 }
 
 int next_pow2(int x) { int p = 1; while (p < x) p <<= 1; return p; }
 
-struct TopkPlan { int K, KP, chunks; size_t ctr_bytes, part_bytes, top_bytes; };
+struct TopkPlan { int K, KP, lge, chunks; size_t ctr_bytes, part_bytes, top_bytes; };
+
+constexpr int MAX_BATCH = 1024;
 
 TopkPlan topk_plan(int batch, int B, int V, int N)
 {
     TopkPlan t;
     t.K = std::min(V, N);
     t.KP = std::max(next_pow2(t.K), 1);
-    t.chunks = (V + SCAN - 1) / SCAN;
-    t.ctr_bytes = btv_align_up((size_t)batch * sizeof(TbCounters), BTV_WS_ALIGN);
-    t.part_bytes = btv_align_up((size_t)batch * B * t.chunks * 256 * sizeof(uint2), BTV_WS_ALIGN);
+    t.lge = V <= 16 * 256 ? 0 : 2;
+    while (t.lge > 0 && t.lge < LGE_MAX && V > 16 * (256 << t.lge)) ++t.lge;
+    t.chunks = (V + (256 << t.lge) - 1) / (256 << t.lge);
+    // (the counters stay zero from call to call, so their place must not depend on the call's sizes)
+    t.ctr_bytes = btv_align_up((size_t)MAX_BATCH * sizeof(TbCounters), BTV_WS_ALIGN);
+    t.part_bytes = t.lge == 0 ? 0 : btv_align_up((size_t)batch * B * t.chunks * 256 * sizeof(uint2), BTV_WS_ALIGN);
     t.top_bytes = btv_align_up((size_t)batch * B * t.KP * 4, BTV_WS_ALIGN);
     return t;
 }
-
-constexpr int MAX_BATCH = 1024;
 
 size_t tree_build_ws(int batch, int B, int V, int N)
 {
@@ -1371,9 +1283,13 @@ static int tree_build_launch(const float *marginals, int batch, int B, int V, in
     Adaptive ad = ad_in;
     ad.flag = reinterpret_cast<uint32_t *>(base);
     bt.flag = reinterpret_cast<uint32_t *>(base);
-    hipLaunchKernelGGL(tb_thread_max, dim3(t.chunks, B * batch), dim3(256), 0, st, marginals, V, B, t.chunks, part, ctr);
+    const dim3 scan_grid(t.chunks, B * batch);
+    if (t.lge == 2) hipLaunchKernelGGL(tb_thread_max<2>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
+    else if (t.lge == 3) hipLaunchKernelGGL(tb_thread_max<3>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
+    else if (t.lge == 4) hipLaunchKernelGGL(tb_thread_max<4>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
+    else if (t.lge == 5) hipLaunchKernelGGL(tb_thread_max<5>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
     BTV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(tb_rank_expand, dim3(B * batch), dim3(256), 0, st, marginals, V, B, t.K, t.KP, N, t.chunks, ctr, part, top_q,
+    hipLaunchKernelGGL(tb_rank_expand, dim3(B * batch), dim3(256), 0, st, marginals, V, B, t.K, t.KP, N, t.chunks, t.lge, ctr, part, top_q,
                        top_tok, parent, token, depth, rho, n_out, ahat, ad, beam_width, bt, algo);
     BTV_HIP(hipGetLastError());
     return BTV_OK;

@@ -48,6 +48,22 @@ def test_small_and_ragged_vocabularies(G, oracle, B, V, N):
         _check(G, oracle, synth.marginals(50 + seed, B, V, 2.5), N)
 
 
+@pytest.mark.parametrize("V", [255, 256, 257, 4096, 4097, 16384, 16387, 65536, 65541, 131072, 131075])
+def test_vocabularies_around_the_slot_sizes(G, oracle, V):
+    """The ranking sees a row as slots whose size follows the vocabulary's: single marginals up to 4096, then 4 to 32 of them."""
+    for seed, (B, N, sigma) in enumerate([(3, 256, 2.5), (16, 64, 6.0), (2, 1, 1.0)]):
+        _check(G, oracle, synth.marginals(70 + seed, B, V, sigma), N)
+
+
+def test_more_candidates_than_the_sweep_holds(G, oracle):
+    """Marginals near 1 for many tokens (no probabilities, but finite and at most 1) make every level of the lattice larger than
+    the sweep's lists: the frontier loop takes over, whichever expansion was asked for."""
+    marg = np.sort(synth.uniform(5, "near_one", (16, 40)), axis=1)[:, ::-1]
+    marg = (1.0 - 1e-3 * (1.0 - marg)).astype(np.float32)
+    for N in (40, 256):
+        _check(G, oracle, marg, N)
+
+
 def test_ties_zeros_one_hot_and_budget_beyond_lattice(G, oracle):
     cases = [
         np.full((4, 8), 0.125, dtype=np.float32),                                   # everything ties
