@@ -53,6 +53,8 @@ struct AttnParams {
     int sps;                      // stages per split
     int nsplit;                   // key splits of the longest request
     int row_blocks, units;        // row blocks per (split, head, request) unit; number of units
+    long long *plan;              // batch only: [batch + 2], where the requests' work starts (see Stretch)
+    int batch, teams_log2, pairing, wmin, wr_log2;   // batch only: requests, teams of workgroups, whether a team is a pair, smallest share, rows per block
     float scale;                  // softmax scale
     float scale_log2;             // scale * log2(e) (times the key scale of an FP8 cache)
     float out_scale;              // 1, or the value scale of an FP8 cache
@@ -208,6 +210,8 @@ struct Fill {
     static_assert(LPW >= 1 && LPW * WAVES == Lds<D, EB>::INSTR, "fills must divide evenly over the waves");
     const unsigned char *base[LPW]; // K or V base of this KV head for fill jj (wave-uniform)
     const int32_t *block_table;     // row of this request (paged)
+    uint32_t pages;                 // paged, lane l: page 2 * page_tile + l of the request (a window of 32 tiles; PGV)
+    int page_tile;
     int num_blocks, S;
     uint32_t row_bytes;             // Hkv * D * EB: distance between consecutive keys
     uint32_t lane_off[LPW];         // contiguous: key_off*row_bytes + chunk*16;  paged: (key_off & 15)*row_bytes + chunk*16
@@ -254,7 +258,8 @@ __device__ __forceinline__ int fill_key_off(int w, int jj, int l)
 // Keys past the end of the sequence re-read the last valid row (finite data; their scores are masked).
 // JB .. JE - 1: which of the wave's LPW fills (all by default; the pipelined loop issues them one by one, each behind a
 // group of MFMAs, because an issue holds its wave for about a hundred cycles).
-template <int D, int WAVES, bool PAGED, int EB = 2, int JB = 0, int JE = Lds<D, EB>::INSTR / WAVES>
+// PGV: the page ids come from the window in f.pages (which must hold the tile's), else from scalar loads.
+template <int D, int WAVES, bool PAGED, int EB = 2, int JB = 0, int JE = Lds<D, EB>::INSTR / WAVES, bool PGV = false>
 __device__ __forceinline__ void issue_tile(const Fill<D, WAVES, PAGED, EB> &f, unsigned char *smem, int slot, int st, int w, int l)
 {
     using LD = Lds<D, EB>;
@@ -273,21 +278,25 @@ __device__ __forceinline__ void issue_tile(const Fill<D, WAVES, PAGED, EB> &f, u
             __builtin_amdgcn_global_load_lds(base + off, BTV_LDS_PTR(smem + slot * LD::STAGE + (w * f.LPW + jj) * 1024), 16, 0, 0);
         }
     } else {
-        // a 32-key tile spans two 16-token pages; their ids are wave-uniform (scalar loads, so the vector-memory
-        // counter only ever counts the LDS fills)
-        const int last_page = (f.S - 1) >> 4;
-        typedef const __attribute__((address_space(4))) int32_t *const_i32;   // constant space: scalar loads
-        const_i32 bt = reinterpret_cast<const_i32>(reinterpret_cast<uintptr_t>(f.block_table));
-        const int i0 = __builtin_amdgcn_readfirstlane(min(2 * st, last_page));
-        const int i1 = __builtin_amdgcn_readfirstlane(min(2 * st + 1, last_page));
-        const int id0 = bt[i0], id1 = bt[i1];
-        asm volatile("" ::"s"(id0), "s"(id1));                   // both loads are issued before either id is used: one wait, not two
+        // a 32-key tile spans two 16-token pages; their ids are wave-uniform (scalar loads, or lanes of the window, so the
+        // vector-memory counter only ever counts the LDS fills)
+        int id0, id1;
+        if constexpr (PGV) {
+            const int at = 2 * (st - f.page_tile);               // (uniform)
+            id0 = __builtin_amdgcn_readlane((int)f.pages, at);
+            id1 = __builtin_amdgcn_readlane((int)f.pages, at + 1);
+        } else {
+            const int last_page = (f.S - 1) >> 4;
+            typedef const __attribute__((address_space(4))) int32_t *const_i32;   // constant space: scalar loads
+            const_i32 bt = reinterpret_cast<const_i32>(reinterpret_cast<uintptr_t>(f.block_table));
+            const int i0 = __builtin_amdgcn_readfirstlane(min(2 * st, last_page));
+            const int i1 = __builtin_amdgcn_readfirstlane(min(2 * st + 1, last_page));
+            id0 = bt[i0]; id1 = bt[i1];
+            asm volatile("" ::"s"(id0), "s"(id1));               // both loads are issued before either id is used: one wait, not two
+        }
         const size_t page0 = (size_t)min(max(id0, 0), f.num_blocks - 1) * BTV_PAGE * f.row_bytes;
         const size_t page1 = (size_t)min(max(id1, 0), f.num_blocks - 1) * BTV_PAGE * f.row_bytes;
         if (whole) {
-            // The rows of one fill instruction all lie in the same half of the tile (an instruction covers 4 or 8
-            // consecutive LDS rows, and the K rows' permutation stays within 16), so the page is the instruction's,
-            // not the lane's: a scalar base plus the lane's fixed offset, as in the contiguous form.
             // The rows of one fill instruction all lie in the same half of the tile (an instruction covers 4 or 8
             // consecutive LDS rows, and the permutation of the K rows stays within 16), so the page is the
             // instruction's, not the lane's: a scalar base plus the lane's fixed offset, as in the contiguous form.
@@ -817,58 +826,48 @@ __device__ __forceinline__ LaneRow lane_row(int r, int rows_g, int G, int Hq, in
     return x;
 }
 
+// What one workgroup does in one go: rows of row block `by` of (request, KV head g) against the tiles st0 .. st1 - 1.
+struct Piece {
+    int rq, g, by, st0, st1;
+    int bx;                       // which partial of its rows this is
+    int direct;                   // the only one: O is written
+};
+
+// A page window (32 tiles' page ids) per 256 bytes, four of them in turn, behind everything else; not where two workgroups
+// fill the LDS of a CU to the last byte.
+template <int D, int RW, int KW, int NT, bool PAGED, int EB>
+struct PageLds {
+    static constexpr int BASE = WgLds<D, RW, KW, NT, EB>::BYTES;
+    static constexpr int PER_CU = RW * KW <= 4 ? 2 : 1;          // workgroups that are to share a CU
+    static constexpr bool USED = PAGED && (BASE + 1024) * PER_CU <= 160 * 1024;
+    static constexpr int BYTES = BASE + (USED ? 1024 : 0);
+};
+
 // Workgroup = RW row-waves x KW key-waves; wave (rw, kw) owns query rows [32 rw, 32 rw + 32) of the block and,
 // in every round of KW consecutive tiles, tile number kw.  LDS ring of NT tiles; one barrier per round.
-template <int D, int RW, int KW, int NT, bool PAGED, int EB = 2>
-__global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
+template <int D, int RW, int KW, int NT, bool PAGED, int EB>
+__device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *smem, int tid, const Req &rq_, const Piece &pc_)
 {
     static_assert(EB == 2 || (EB == 1 && KW >= 2), "FP8 K/V runs in the shapes whose waves alternate over the tiles");
     constexpr int WAVES = RW * KW;
     constexpr int WR = RW * 32;
     constexpr int DS = D / 16;
     constexpr int DT = D / 32;
-    // Waves that issue the ring fills.  With two waves per SIMD the hardware favours the older wave of each pair,
-    // which then idles at the round's barrier: those four waves issue every fill (an issue stalls its wave for
-    // about a hundred cycles), the younger four only compute.
+    // Waves that issue the ring fills.
     constexpr int IW = WAVES;
     constexpr int LPW = Lds<D, EB>::INSTR / IW;
     constexpr int AHEAD = NT - 2 * KW;            // tiles still in flight when a round's tiles have landed
     static_assert(AHEAD >= 0 && AHEAD * LPW < 64, "ring too small or too deep for the counter");
     using LD = Lds<D, EB>;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-
-    // Fetch every argument now, in one round trip.  Left to the compiler the scalar loads follow the early-exit tests
-    // below in five dependent steps, three of which miss the cache (the argument block spans three lines and is cold
-    // in every launch): about two microseconds before the first fill is issued.
-    asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.block_table), "s"(p.q_offset),
-                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G),
-                 "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.nsplit),
-                 "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale));
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, c = l & 31, h = l >> 5;
+    using PL = PageLds<D, RW, KW, NT, PAGED, EB>;
+    constexpr bool PGV = PL::USED;
+    const int w = tid >> 6, l = tid & 63, c = l & 31, h = l >> 5;
     const int kw = w % KW, rw = w / KW;
-    // Workgroups go to the 8 XCDs round-robin by their linear id.  A unit = (key split, KV head, request); the row
-    // blocks of one unit stream the same K/V bytes, so they get ids that are congruent mod 8 and share one L2.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
-    if (unit >= p.units) return;
-    // Ragged batches: the split index is rotated by the (request, head) number.  Without it a split count that is
-    // a multiple of 8 ties split i to XCD i % 8, and the requests with few splits load only the first XCDs.
-    const int bz = unit / p.nsplit;
-    const int bx = PAGED ? (unit % p.nsplit + 3 * bz) % p.nsplit : unit % p.nsplit;
-    const int rq = bz / p.Hkv, g = bz % p.Hkv;
-    const Req rq_ = load_req<PAGED>(p, rq);
-    if (!rq_.ok) {
-        if (tid == 0 && bx == 0 && by == 0) atomicOr(p.flag, 2u);
-        return;
-    }
+    const int rq = pc_.rq, g = pc_.g, by = pc_.by, bx = pc_.bx;
     const int Mr = rq_.M, Lr = rq_.L, S = Lr + Mr;
     const int rows_g = Mr * p.G;
-    if (by * WR >= rows_g) return;
-    const int tiles = (S + 31) / 32;
-    const int nsplit_r = (tiles + p.sps - 1) / p.sps;
-    if (bx >= nsplit_r) return;
-    const int st0 = bx * p.sps;
-    int st1 = min(st0 + p.sps, tiles);
+    const int st0 = pc_.st0;
+    int st1 = pc_.st1;
     {   // tree rows past the last node of this row block are invisible to all of its rows: their tiles are dropped
         const int node_hi = (min((by + 1) * WR, rows_g) - 1) / p.G;
         st1 = min(st1, max((Lr + node_hi + 1 + 31) / 32, st0 + 1));
@@ -876,8 +875,14 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
 
     using WL = WgLds<D, RW, KW, NT, EB>;
 
-    // ---- prologue loads, oldest first: parent[] (one entry per thread), this wave's share of its row-wave's query
-    // tile, the first ring tiles.  All are raw instructions counted by hand.
+    // ---- prologue loads, oldest first: the first two page windows, parent[] (one entry per thread), this wave's share of
+    // its row-wave's query tile, the first ring tiles.  All are raw instructions counted by hand.
+    const int32_t *bt_row = PAGED ? p.block_table + (long long)rq * p.max_blocks : nullptr;
+    auto load_window = [&](int g_) {                     // page ids of tiles st0 + 32 g_ .. + 31 (by the first wave)
+        const int32_t *src = bt_row + min(2 * (st0 + 32 * g_) + l, (S - 1) >> 4);
+        __builtin_amdgcn_global_load_lds(src, BTV_LDS_PTR(smem + PL::BASE + (g_ & 3) * 256), 4, 0, 0);
+    };
+    if (PGV && __builtin_amdgcn_readfirstlane(w) == 0) { load_window(0); load_window(1); }
     // parent[]: every wave moves 64 entries straight into LDS (index clamped to the request's nodes), whether or not
     // the workgroup reaches the tree rows; entries are checked where they are read.
 #pragma unroll
@@ -908,8 +913,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     // ---- start filling the ring ------------------------------------------------------------------------
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const bool issuer = wu < IW;
-    const Fill<D, IW, PAGED, EB> fill = make_fill<D, IW, PAGED, EB>(p.K, p.V, PAGED ? p.block_table + (long long)rq * p.max_blocks : nullptr,
-                                                                    p.num_blocks, p.Hkv, g, S, issuer ? wu : 0, l);
+    Fill<D, IW, PAGED, EB> fill = make_fill<D, IW, PAGED, EB>(p.K, p.V, bt_row, p.num_blocks, p.Hkv, g, S, issuer ? wu : 0, l);
     // KW == 1: three tiles up front (the first compute needs two), the rest of the ring fills during the first
     // rounds; an issue holds its wave for about a hundred cycles, so a full prefill would only delay the start.
     constexpr int PREFILL = WL::PREFILL;
@@ -926,7 +930,22 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     wait_vm_ops<PREFILL * LPW>(issuer ? (issued - st0) * LPW : 0);
     // A bare barrier, and raw LDS reads below: with the fence of a full synchronisation, or with ordinary reads of
     // memory that direct-to-LDS loads wrote, the compiler drains the ring fills first.
-    __builtin_amdgcn_s_barrier();                    // query tiles (filled by KW waves) and parent[] are visible
+    __builtin_amdgcn_s_barrier();                    // query tiles (filled by KW waves), parent[] and the page windows are visible
+    // The window that tile `issued` belongs to, once per 32 tiles; the first wave asks for the one after it, which is there long
+    // before it is read: the ring's waits cover every older load, and a barrier follows each of them.
+    auto turn_window = [&]() {
+        if constexpr (PGV) {
+            const int g_ = (issued - st0) >> 5;
+            uint32_t v;
+            asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                         : "=v"(v) : "v"((uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + PL::BASE + (uint32_t)((g_ & 3) * 256 + l * 4)) : "memory");
+            fill.pages = v;
+            fill.page_tile = st0 + 32 * g_;
+            if (g_ > 0 && wu == 0) load_window(g_ + 1);
+        }
+    };
+    auto next_window = [&]() { if (PGV && ((issued - st0) & 31) == 0) turn_window(); };
+    turn_window();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
     const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF;
     auto par_at = [&](int i) {
@@ -994,7 +1013,8 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     const uint32_t ring = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem);
     auto issue_one = [&]() {                             // the next tile of this split, if there is one
         if (issued < st1) {
-            if (issuer) issue_tile<D, IW, PAGED, EB>(fill, smem, islot, issued, wu, l);
+            next_window();
+            if (issuer) issue_tile<D, IW, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
             ++issued;
             if (++islot == NT) islot = 0;
         }
@@ -1004,7 +1024,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
         constexpr int P = decltype(part)::value;
         constexpr int MID = (LPW + 1) / 2, JB = P == 0 ? 0 : MID, JE = P == 0 ? MID : LPW;
         if constexpr (JB < JE)
-            if (issuer) issue_tile<D, IW, PAGED, EB, JB, JE>(fill, smem, islot, issued, wu, l);
+            if (issuer) issue_tile<D, IW, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l);
     };
     if constexpr (KW == 1) {
         // Every wave has its queries in registers and parent[] is consumed: the ring owns all stages from here on.
@@ -1046,6 +1066,28 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
         int Tf = min(st1, Lr / 32) - st0;                        // plain tiles at the start of this split
         if (Tf < 3) Tf = 0;
         int j0 = 0;                                              // first local tile the step-by-step loop below takes
+        // A wave whose 32 rows all lie past the request's last row has nothing to compute: it takes its share of the fills and
+        // its part in every barrier, and leaves its SIMD to the other wave there.
+        if (by * WR + __builtin_amdgcn_readfirstlane(rw) * 32 >= rows_g) {
+            if (Tf > 0) {
+                wait_tiles<LPW, NT - 4>(issued - st0 - 3);
+                __builtin_amdgcn_s_barrier();
+                for (int i = 1; i <= Tf - 2; ++i) {
+                    wait_tiles<LPW, 3>(issued - st0 - i - 3);
+                    __builtin_amdgcn_s_barrier();
+                    issue_one();
+                }
+            }
+            for (int j = Tf; j < st1 - st0; ++j) {
+                wait_tiles<LPW, NT - 1>(issued - st0 - j - 1);
+                __builtin_amdgcn_s_barrier();
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    if (issued - st0 - j < NT) issue_one();
+            }
+            wait_vmcnt<0>();
+            return;
+        }
         if (Tf > 0) {
             const uint32_t kbase = ring + lane_k_off<D>(l), vbase = ring + LD::TILEB + lane_v_off<D>(l);
             auto slot_off = [](int j) { return (uint32_t)((j & (NT - 1)) * LD::STAGE); };      // wave-uniform
@@ -1124,6 +1166,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
                 wait_tiles<LPW, 3>(issued - st0 - i - 3);
                 __builtin_amdgcn_s_barrier();
                 const bool fill_now = issued < st1;              // tile i+6 goes into the slot tile i-2 left
+                if (fill_now) next_window();
                 uint32_t k1 = 0, k2 = 0, v0 = 0, v1 = 0;
                 if constexpr (PH < 0) {
                     k1 = kbase + slot_off(i + 1); k2 = kbase + slot_off(i + 2);
@@ -1213,11 +1256,14 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
                 if (issued - st0 - j < NT) issue_one();
             do_tile<D>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb);
         }
+        if constexpr (PAGED) wait_vmcnt<0>();
     } else if constexpr (KW > 1) {
         // ---- main loop: one barrier per round of KW tiles, wave kw takes tile number kw of the round ------
         // At the top of the round starting at tile st, tiles st+KW .. issued-1 may still be in flight.  The
         // barrier also tells that every wave is done with the previous round, whose KW ring slots the next
         // issues overwrite.
+        // (a wave whose 32 rows all lie past the last one only fills)
+        const bool live = by * WR + __builtin_amdgcn_readfirstlane(rw) * 32 < rows_g;
         int cslot = kw;
         for (int st = st0; st < st1; st += KW) {
             if (issued - st - KW == AHEAD) wait_vmcnt<AHEAD * LPW>();
@@ -1226,11 +1272,12 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
 #pragma unroll
             for (int k = 0; k < KW; ++k)
                 if (issued < st1) {
-                    issue_tile<D, IW, PAGED, EB>(fill, smem, islot, issued, wu, l);
+                    next_window();
+                    issue_tile<D, IW, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
                     ++issued;
                     if (++islot == NT) islot = 0;
                 }
-            if (st + kw < st1) {
+            if (live && st + kw < st1) {
                 if constexpr (EB == 2)
                     do_tile<D>(ring + cslot * LD::STAGE, (st + kw) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb);
                 else
@@ -1338,7 +1385,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     }
 
     // ---- write: final bf16 rows when this request has a single split, scaled fp16 partials otherwise ---
-    if (nsplit_r == 1) {
+    if (pc_.direct) {
         const float inv = p.out_scale / l_run;
         uint16_t *Op = static_cast<uint16_t *>(p.O) + orow * D + dt0 * 32;
 #pragma unroll
@@ -1367,6 +1414,244 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
                     make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
             }
         if (h == 0 && kw == 0) *reinterpret_cast<float4 *>(p.ML + prow * 4) = make_float4(m_run, l_run, amax, 0.f);
+    }
+}
+
+// Fetch every argument now, in one round trip.  Left to the compiler the scalar loads follow the early-exit tests
+// in five dependent steps, three of which miss the cache (the argument block spans three lines and is cold in every
+// launch): about two microseconds before the first fill is issued.
+#define BTV_FETCH_ARGS(p)                                                                                                     \
+    asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.block_table), "s"(p.q_offset),              \
+                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), \
+                 "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.nsplit),          \
+                 "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale))
+
+// One request: a workgroup per (key split, KV head, row block).
+template <int D, int RW, int KW, int NT, int EB>
+__global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    BTV_FETCH_ARGS(p);
+    // Workgroups go to the 8 XCDs round-robin by their linear id.  A unit = (key split, KV head); the row
+    // blocks of one unit stream the same K/V bytes, so they get ids that are congruent mod 8 and share one L2.
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
+    if (unit >= p.units) return;
+    const Req rq = load_req<false>(p, 0);
+    Piece pc;
+    pc.rq = 0; pc.g = unit / p.nsplit; pc.by = by; pc.bx = unit % p.nsplit;
+    const int tiles = (rq.L + rq.M + 31) / 32, nsplit_r = (tiles + p.sps - 1) / p.sps;
+    if (by * RW * 32 >= rq.M * p.G || pc.bx >= nsplit_r) return;
+    pc.st0 = pc.bx * p.sps;
+    pc.st1 = min(pc.st0 + p.sps, tiles);
+    pc.direct = nsplit_r == 1;
+    attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc);
+}
+
+// A batch of short requests: a workgroup per (part of at most sps tiles, KV head, request, row block) of the largest request;
+// those that a request has no use for leave at once.
+template <int D, int RW, int KW, int NT, int EB>
+__global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    BTV_FETCH_ARGS(p);
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
+    if (unit >= p.units) return;
+    Piece pc;
+    // The part is rotated by the (request, head) number.  Without it a number of parts that is a multiple of 8 ties part i
+    // to XCD i % 8, and the requests with few parts load only the first XCDs.
+    const int bz = unit / p.nsplit;
+    pc.bx = (unit % p.nsplit + 3 * bz) % p.nsplit; pc.g = bz % p.Hkv; pc.rq = bz / p.Hkv; pc.by = by;
+    const Req rq = load_req<true>(p, pc.rq);
+    if (!rq.ok) {
+        if (threadIdx.x == 0 && by == 0 && pc.bx == 0 && pc.g == 0) atomicOr(p.flag, 2u);
+        return;
+    }
+    const int tiles = (rq.L + rq.M + 31) >> 5, parts = (tiles + p.sps - 1) / p.sps;
+    if (by * RW * 32 >= rq.M * p.G || pc.bx >= parts) return;
+    pc.st0 = pc.bx * p.sps;
+    pc.st1 = min(pc.st0 + p.sps, tiles);
+    pc.direct = parts == 1;
+    attn_piece<D, RW, KW, NT, true, EB>(p, smem, threadIdx.x, rq, pc);
+}
+
+// ---- ragged batches ---------------------------------------------------------------------------------------------------
+// The host knows bounds on the requests' sizes only, so the workgroups share the work out themselves: as many as the CUs
+// hold, all with about the same time to spend, whatever the lengths.  A request's work for one KV head is a row of
+// stretches, one per row block, START + weight * t long for t tiles (START: what starting on a row block and storing its
+// rows costs; the weight is WHOLE, or PART where no more than half of the block's rows exist, as a tile goes faster then).
+// The stretches lie one after the other, request after request, KV head after KV head (so an XCD keeps to one head or
+// two), and team k takes what lies between k w and (k + 1) w; where that cuts a stretch, tv_combine_batch
+// merges the parts.  A cut less than MARGIN tiles from where a stretch's tiles begin or end moves there.  A stretch of up to
+// SMALL tiles is not cut: the team that its beginning falls to does all of it.
+// Where trees may take several row blocks a team is a pair of workgroups (neighbours on one XCD, running side by side): a
+// stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
+// first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
+// (if it is small, one of them takes it alone).
+// Bound by the matrix cores' clock (about 2.1 GHz here) and their 57 % share of a tile's cycles; the figures beside the choice
+// of the form (make_batch_plan) are the whole call's, before and after.  A piece costs 8 us beyond its tiles (finding it 1,
+// page ids and first tiles 3, merging and storing 3, waiting for the other waves 1), START and MARGIN come from that.
+constexpr int WHOLE = 3, PART = 2, START = 8 * WHOLE, MARGIN = 8, SMALL = 16;
+struct Stretch { int t, du, wt, sl, len; };             // tiles; whole stretches; weight of the last; length of the halved one; all
+__device__ __forceinline__ Stretch stretch_of(const AttnParams &p, const Req &q)
+{
+    Stretch s;
+    s.t = q.ok ? (q.L + q.M + 31) >> 5 : 0;
+    const int rows = q.ok ? q.M * p.G : 0, rb = (rows + (1 << p.wr_log2) - 1) >> p.wr_log2;
+    s.du = rb >> p.pairing;
+    s.wt = rows - ((rb - 1) << p.wr_log2) <= 1 << p.wr_log2 >> 1 ? PART : WHOLE;
+    s.sl = p.pairing && (rb & 1) ? (s.t <= SMALL ? (s.t * s.wt + START + 1) >> 1 : ((s.t + 1) >> 1) * s.wt + START) : 0;
+    s.len = s.du * (s.t * (p.pairing ? WHOLE : s.wt) + START) + s.sl;
+    return s;
+}
+__device__ __forceinline__ int wave_incl_scan(int x)
+{
+    // (rows of 16 by shifts, then the last lane of each row into the rows behind it)
+#define BTV_SCAN_STEP(ctrl, rows) x += __builtin_amdgcn_update_dpp(0, x, ctrl, rows, 0xF, ctrl < 0x142)
+    BTV_SCAN_STEP(0x111, 0xF); BTV_SCAN_STEP(0x112, 0xF); BTV_SCAN_STEP(0x114, 0xF); BTV_SCAN_STEP(0x118, 0xF);
+    BTV_SCAN_STEP(0x142, 0xA); BTV_SCAN_STEP(0x143, 0xC);
+#undef BTV_SCAN_STEP
+    return x;
+}
+// 64 lengths: their low and high halves on their own, so that no sum leaves 32 bits
+__device__ __forceinline__ long long wave_incl_scan_len(int x)
+{
+    return ((long long)wave_incl_scan(x >> 16) << 16) + wave_incl_scan(x & 0xFFFF);
+}
+// Where a team stands.  Every wavefront of its workgroups works this out for itself.
+struct Walk {
+    long long first, end;                               // the team's share
+    long long pos, head;                                // what comes next; where its KV head's work begins
+    long long wh;                                       // one head's work
+    int h, w;                                           // that KV head; a share
+};
+
+// A chunk of 64 requests, one per lane: their stretches, and where they end in a head's work (cum: where the chunk begins).
+struct Chunk { Stretch s; long long incl; bool bad; };
+__device__ __forceinline__ Chunk load_chunk(const AttnParams &p, int c0, int lane, long long cum)
+{
+    Chunk c;
+    const bool in = c0 + lane < p.batch;
+    const Req q = load_req<true>(p, min(c0 + lane, p.batch - 1));
+    c.s = stretch_of(p, q);
+    c.bad = in && !q.ok;
+    c.incl = wave_incl_scan_len(in ? c.s.len : 0) + cum;
+    return c;
+}
+__device__ __forceinline__ long long last_lane(long long x)
+{
+    return (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), 63) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)x, 63));
+}
+
+// The share of a team (the `nth` on its XCD), and the first chunk of requests.  The very first workgroup leaves the plan for the merge.
+__device__ __forceinline__ Walk share_out(const AttnParams &p, int xcd, int nth, int lane, bool leader, Chunk &c)
+{
+    Walk k;
+    long long begin = 0;
+    bool bad = false;
+    for (int c0 = ((p.batch - 1) >> 6) << 6; c0 >= 0; c0 -= 64) {         // (the first chunk last; sums of the others do not matter yet)
+        c = load_chunk(p, c0, lane, 0);
+        bad = bad || c.bad;
+        begin += last_lane(c.incl);
+    }
+    k.wh = begin;
+    const long long all = k.wh * p.Hkv;
+    const long long w = max((all + (1 << p.teams_log2) - 1) >> p.teams_log2, (long long)p.wmin);
+    if (leader) {
+        long long cum = 0;
+        for (int c0 = 0; c0 < p.batch; c0 += 64) {
+            const Chunk d = c0 ? load_chunk(p, c0, lane, cum) : c;
+            if (c0 + lane < p.batch) p.plan[2 + c0 + lane] = d.incl - d.s.len;
+            cum = last_lane(d.incl);
+        }
+        if (lane == 0) { p.plan[0] = w; p.plan[1] = k.wh; }
+        if (bad) atomicOr(p.flag, 2u);
+    }
+    k.w = (int)min(w, (long long)INT_MAX);
+    // neighbouring shares on one XCD, as many on each: where the work is for a part of the teams, all XCDs have some
+    long long per_xcd = (1 << p.teams_log2) >> 3;
+    if (w == p.wmin) per_xcd = min(per_xcd, ((all + w - 1) / w + 7) >> 3);
+    k.first = k.pos = nth < per_xcd ? min((xcd * per_xcd + nth) * w, all) : all;
+    k.end = min(k.first + w, all);
+    k.head = 0; k.h = 0;
+    return k;
+}
+
+// The member's next piece; the walk moves behind it.  False: none left.  c holds the first chunk of requests.
+__device__ __forceinline__ bool next_piece(const AttnParams &p, Walk &k, int member, int lane, const Chunk &c, Piece &pc)
+{
+    while (k.pos < k.end) {
+        while (k.pos - k.head >= k.wh) { k.head += k.wh; ++k.h; }
+        const long long x = k.pos - k.head;
+        Chunk d = c;
+        int r0 = 0;
+        unsigned long long beyond;
+        while ((beyond = __builtin_amdgcn_ballot_w64(x < d.incl)) == 0ull) {
+            r0 += 64;
+            if (r0 >= p.batch) return false;            // (cannot be: x lies within the head's work)
+            d = load_chunk(p, r0, lane, last_lane(d.incl));
+        }
+        const int src = __builtin_ctzll(beyond);
+        Stretch s;
+        s.t = __builtin_amdgcn_readlane(d.s.t, src); s.du = __builtin_amdgcn_readlane(d.s.du, src);
+        s.wt = __builtin_amdgcn_readlane(d.s.wt, src); s.sl = __builtin_amdgcn_readlane(d.s.sl, src);
+        s.len = __builtin_amdgcn_readlane(d.s.len, src);
+        const int y = s.len + __builtin_amdgcn_readlane((int)(x - d.incl), src);       // place in the request's work
+        const int whole = s.t * (p.pairing ? WHOLE : s.wt) + START, u = min(y / whole, s.du);
+        const bool halved = u == s.du;
+        const int y0 = y - u * whole;                   // ... in the stretch
+        const long long us = k.pos - y0;                // where the stretch begins
+        pc.rq = r0 + src;
+        pc.g = k.h;
+        pc.by = p.pairing ? (halved ? 2 * u : 2 * u + member) : u;
+        pc.bx = 0; pc.direct = 1; pc.st0 = 0; pc.st1 = s.t;
+        if (s.t <= SMALL) {
+            k.pos = us + (halved ? s.sl : whole);
+            if (y0 == 0 && (!halved || ((pc.rq ^ k.h) & 1) == member)) return true;
+            continue;
+        }
+        const int wt = halved || !p.pairing ? s.wt : WHOLE;
+        const int tl = halved ? (s.t + 1) >> 1 : s.t, cl = tl * wt, cm = MARGIN * wt;  // tiles of the stretch; their length
+        const long long ts = us + START;                // they begin here
+        int c0 = y0 - START, c1 = (int)min(k.end - ts, (long long)cl);
+        if (c0 < cm) c0 = 0; else if (c0 > cl - cm) c0 = cl;
+        if (c1 < cm) c1 = 0; else if (c1 > cl - cm) c1 = cl;
+        k.pos = c1 < cl ? k.end : ts + cl;
+        if (c0 >= c1) continue;
+        const int cut = c0 == 0 ? 0 : (c0 - cm) / k.w + 1;
+        const int x0 = c0 / wt, x1 = c1 / wt;
+        if (!halved) {
+            pc.st0 = x0; pc.st1 = x1; pc.bx = cut; pc.direct = c0 == 0 && c1 == cl;
+            return true;
+        }
+        pc.bx = 2 * cut + member; pc.direct = 0;
+        pc.st0 = member ? x0 + x1 : 2 * x0;
+        pc.st1 = member ? min(2 * x1, s.t) : x0 + x1;
+        if (pc.st0 < pc.st1) return true;
+    }
+    return false;
+}
+
+template <int D, int RW, int KW, int NT, int EB>
+__global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_batch(AttnParams p)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    BTV_FETCH_ARGS(p);
+    asm volatile("" ::"s"(p.plan), "s"(p.batch), "s"(p.teams_log2), "s"(p.pairing), "s"(p.wmin), "s"(p.wr_log2));
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, member = slot & p.pairing;
+    Chunk c;
+    Walk k = share_out(p, xcd, slot >> p.pairing, threadIdx.x & 63, blockIdx.x == 0 && threadIdx.x < 64, c);
+    for (bool again = false;; again = true) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                   // keeps what derives from it (all addresses) from being carried across pieces
+        if (again) c = load_chunk(p, 0, tid & 63, 0);
+        Piece pc = {};
+        if (!next_piece(p, k, member, tid & 63, c, pc)) break;
+        attn_piece<D, RW, KW, NT, true, EB>(p, smem, tid, load_req<true>(p, pc.rq), pc);
+        // every wave is done with this piece's LDS, its own fills have landed; the stores may still be on their way
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
     }
 }
 
@@ -1399,24 +1684,26 @@ __device__ __forceinline__ float row32_sum(float x, int lane)
     return x + __uint_as_float((lane & 16) ? sw[0] : sw[1]);
 }
 
-template <int D, bool PAGED>
-__global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
+template <int D>
+__device__ __forceinline__ void store_row(const AttnParams &p, size_t row, int lane, const float (&acc)[D / 32], float inv)
+{
+    constexpr int E = D / 32;
+    uint16_t *dst = static_cast<uint16_t *>(p.O) + row * D + lane * E;
+    if (E == 4) {
+        uint32_t lo = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[1] * inv) << 16);
+        uint32_t hi = float_to_bf16_bits(acc[E - 2] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
+        *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
+    } else {
+        *reinterpret_cast<uint32_t *>(dst) = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void combine_row(const AttnParams &p, size_t row, int nsplit_r, float (&wsh)[8][32])
 {
     constexpr int E = D / 32;
     typedef _Float16 hvec __attribute__((ext_vector_type(E)));
-    __shared__ __attribute__((aligned(16))) float wsh[8][32];
-    // every argument in one round trip (the argument block is cold in every launch)
-    asm volatile("" ::"s"(p.O), "s"(p.q_offset), "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq),
-                 "s"(p.max_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.out_scale));
-    const int rq = blockIdx.y;
-    const Req rq_ = load_req<PAGED>(p, rq);
-    if (!rq_.ok) return;
-    const int stages = (rq_.L + rq_.M + TK - 1) / TK;
-    const int nsplit_r = (stages + p.sps - 1) / p.sps;
-    if (nsplit_r == 1) return;                      // the attention kernel wrote O directly
-    const int rin = threadIdx.x >> 5, lr = blockIdx.x * 8 + rin, lane = threadIdx.x & 31;
-    if (lr >= rq_.M * p.Hq) return;
-    const size_t row = (size_t)rq_.q0 * p.Hq + lr;
+    const int rin = threadIdx.x >> 5, lane = threadIdx.x & 31;
     const size_t sstride = (size_t)p.total_rows;
     // reference maximum over all splits: with more than 32 of them it takes a round trip of its own
     float mmax = NEG_BIG;
@@ -1462,14 +1749,105 @@ __global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
     }
     den = row32_sum(den, (int)threadIdx.x);
     const float inv = p.out_scale / den;
-    uint16_t *dst = static_cast<uint16_t *>(p.O) + row * D + lane * E;
-    if (E == 4) {
-        uint32_t lo = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[1] * inv) << 16);
-        uint32_t hi = float_to_bf16_bits(acc[E - 2] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
+    store_row<D>(p, row, lane, acc, inv);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
+{
+    __shared__ __attribute__((aligned(16))) float wsh[8][32];
+    // every argument in one round trip (the argument block is cold in every launch)
+    asm volatile("" ::"s"(p.O), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.total_rows), "s"(p.sps), "s"(p.out_scale));
+    const int nsplit_r = ((p.L + p.M + TK - 1) / TK + p.sps - 1) / p.sps;
+    const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
+    if (row >= p.M * p.Hq) return;
+    combine_row<D>(p, (size_t)row, nsplit_r, wsh);
+}
+
+// The same for a batch: how many parts a row has follows from where its request's work lies (the plan that the attention's first
+// workgroup left).
+template <int D>
+__global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
+{
+    __shared__ __attribute__((aligned(16))) float wsh[8][32];
+    asm volatile("" ::"s"(p.O), "s"(p.q_offset), "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.G),
+                 "s"(p.max_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.plan), "s"(p.Hkv), "s"(p.pairing), "s"(p.wr_log2), "s"(p.sps), "s"(p.out_scale));
+    const int r = blockIdx.y;
+    const Req q = load_req<true>(p, r);
+    long long w = 0, wh = 0, at = 0;
+    if (!p.sps) { w = p.plan[0]; wh = p.plan[1]; at = p.plan[2 + r]; }
+    if (!q.ok) return;
+    const int lr = blockIdx.x * 8 + (threadIdx.x >> 5);
+    if (lr >= q.M * p.Hq) return;
+    int n = 1;
+    if (p.sps) {                                        // short requests: equal parts
+        n = (((q.L + q.M + 31) >> 5) + p.sps - 1) / p.sps;
     } else {
-        *reinterpret_cast<uint32_t *>(dst) = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
+        const Stretch s = stretch_of(p, q);
+        const int node = lr / p.Hq, hq = lr - node * p.Hq, h = hq / p.G, by = (node * p.G + hq - h * p.G) >> p.wr_log2;
+        if (s.t <= SMALL) return;                           // written by the attention kernel
+        const int u = by >> p.pairing;
+        const bool halved = u == s.du;
+        const int wt = halved || !p.pairing ? s.wt : WHOLE;
+        const int cl = (halved ? (s.t + 1) >> 1 : s.t) * wt, cm = MARGIN * wt;
+        const long long ts = h * wh + at + (long long)u * (s.t * WHOLE + START) + START;   // (u = 0 where a team is one workgroup)
+        const long long lo = ts + cm, hi = ts + cl - cm;    // where a cut counts
+        if (hi >= lo) n += wh * p.Hkv < INT_MAX ? (int)hi / (int)w - ((int)lo - 1) / (int)w : (int)(hi / w - (lo - 1) / w);
+        if (halved) n *= 2;
     }
+    if (n == 1) return;
+    // As combine_row, in groups of eight parts (four loads where there are no more), the next group's loads ahead of this one's
+    // sums: most rows have two to four, and the fewer registers let twice the rows be under way.
+    constexpr int E = D / 32;
+    typedef _Float16 hvec __attribute__((ext_vector_type(E)));
+    const int rin = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    const size_t row = (size_t)q.q0 * p.Hq + lr, sstride = (size_t)p.total_rows;
+    auto magnitudes = [&](int s) {
+        const float4 x = *reinterpret_cast<const float4 *>(p.ML + (min(s, n - 1) * sstride + row) * 4);
+        return s < n ? x : make_float4(NEG_BIG, 0.f, 0.f, 0.f);
+    };
+    const _Float16 *Pp = p.Opart + row * D + lane * E;
+    hvec part[8], next[8];
+    auto load = [&](hvec (&x)[8], int s0) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) x[b] = *reinterpret_cast<const hvec *>(Pp + min(s0 + b, n - 1) * sstride * D);
+        if (s0 + 4 < n) {
+#pragma unroll
+            for (int b = 4; b < 8; ++b) x[b] = *reinterpret_cast<const hvec *>(Pp + min(s0 + b, n - 1) * sstride * D);
+        }
+    };
+    float4 ml = magnitudes(lane);
+    load(part, 0);
+    float mmax = ml.x, den = 0.f;
+    for (int s = lane + 32; s < n; s += 32) mmax = fmaxf(mmax, p.ML[(s * sstride + row) * 4]);     // (rare)
+    mmax = row32_max(mmax, (int)threadIdx.x);
+    float acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+    auto add = [&](const hvec (&x)[8], int at, auto first) {
+        constexpr int F = decltype(first)::value;
+        const float4 wg = *reinterpret_cast<const float4 *>(&wsh[rin][at + F]);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            acc[e] += wg.x * (float)x[F][e] + wg.y * (float)x[F + 1][e] + wg.z * (float)x[F + 2][e] + wg.w * (float)x[F + 3][e];
+    };
+    for (int s0 = 0; s0 < n; s0 += 8) {
+        const int at = s0 & 31;
+        if (at == 0) {                                      // the next 32 parts' weights, one per lane
+            if (s0) ml = magnitudes(s0 + lane);
+            const float w = s0 + lane < n ? __builtin_amdgcn_exp2f(ml.x - mmax) : 0.f;
+            den += w * ml.y;
+            wsh[rin][lane] = w * ml.z;                      // weight times the part's magnitude; 0 past the last part
+            // (the row's 32 lanes are one half of a wavefront: its LDS operations complete in order, no barrier needed)
+        }
+        if (s0 + 8 < n) load(next, s0 + 8);
+        add(part, at, std::integral_constant<int, 0>{});
+        if (s0 + 4 < n) add(part, at, std::integral_constant<int, 4>{});
+#pragma unroll
+        for (int b = 0; b < 8; ++b) part[b] = next[b];
+    }
+    const float inv = p.out_scale / row32_sum(den, (int)threadIdx.x);
+    store_row<D>(p, row, lane, acc, inv);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1590,13 +1968,11 @@ struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; };
 // with pairs of waves alternating over the tiles (KW = 2); very many rows over a very long prefix take the
 // 256-row software-pipelined shape (KW = 1), which measures the same there within run-to-run noise.
 // `force_split` > 0 and `force_shape` in 1..3 replace the heuristic's choices (the tuning entry point passes them).
-Plan make_plan(int M, int L, int Hq, int Hkv, int batch, int eb = 2, int force_split = 0, int force_shape = 0)
+Plan make_plan(int M, int L, int Hq, int Hkv, int eb = 2, int force_split = 0, int force_shape = 0)
 {
     Plan pl;
     int G = Hq / Hkv, rows_g = G * M;
-    // Ragged batches take the small workgroup whatever the largest tree: 64-row blocks pad the smaller trees less,
-    // and two such workgroups share a CU, so one's prologue and store overlap the other's main loop.
-    if (rows_g <= 128 || batch > 1) { pl.rw = 2; pl.kw = 2; pl.nt = 5; }
+    if (rows_g <= 128) { pl.rw = 2; pl.kw = 2; pl.nt = 5; }
     // 768 packed rows or more (192 nodes at 4 query heads per KV head, 96 at 8): the software-pipelined 256-row
     // shape, measured 12 % ahead at the 70B shape with a 32k prefix, 4 % at 256 nodes of the 8B shape, 2 % at 192;
     // below, pairs of waves alternating over the tiles are 3-8 % ahead.  The FP8 cache has only the latter.
@@ -1613,16 +1989,12 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int batch, int eb = 2, int force_s
     // that much shorter.
     const int tree_tiles = pl.stages - L / TK;
     const int extra = pl.kw == 1 ? (7 * tree_tiles + 9) / 10 : (tree_tiles + 3) / 4;
-    int base = Hkv * pl.row_blocks * batch;
-    // 64 rows or fewer: finer splits still pay.  Batches: the host only knows the largest request, so the longest
-    // request is cut into up to 8 units of at least 32 tiles and the dispatcher evens out the requests' lengths
-    // (measured on ragged and uniform batches of 4 to 16 requests: within 1.5x of the best shape and split count
-    // found for each; a uniform batch would do best with one unit per CU, which the host cannot tell from here).
+    int base = Hkv * pl.row_blocks;
+    // 64 rows or fewer: finer splits still pay.
     int target = rows_g <= 64 ? 512 : 256;
     // (rounded down: one split more than the CUs hold sends a second, nearly empty round of workgroups through the
     // chip, e.g. 6 splits x 48 = 288 workgroups at 192 nodes took 61 us against 43 us for 5 x 48 = 240)
     int want = force_split > 0 ? force_split : std::max(1, target / base);
-    if (batch > 1 && force_split <= 0) want = std::max(1, std::min(8, pl.stages / 32));
     // a split should stream at least 8 tiles (256 keys) unless the caller forces it
     if (force_split <= 0) want = std::min(want, std::max(1, pl.stages / 8));
     want = std::max(1, std::min(want, pl.stages));
@@ -1632,13 +2004,55 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int batch, int eb = 2, int force_s
     return pl;
 }
 
-struct WsLayout { size_t anc, ml, opart, total; };
+// A batch: shape of the workgroups by the largest tree's packed rows; in how many parts a row's partials may come; whether a
+// merge can be needed at all.  Then either (sps > 0) a workgroup per part of sps tiles, or the plan that the workgroups make
+// themselves: how many teams of them the chip holds and the smallest share (slots: a stretch of the longest request gets that
+// many parts where the average one is 2.5 times shorter; longer ones larger parts).
+struct PlanB { int rw, wr_log2, pairing, teams_log2, slots, wmin, sps, row_blocks; bool merge; };
+PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, int eb)
+{
+    PlanB b = {};
+    const int G = Hq / Hkv, rows_g = G * M_max, t = (L_max + M_max + TK - 1) / TK;
+    // The plan pays where the workgroups have much to do, or a few long requests leave a grid of parts ragged (64-row tiles per
+    // CU at most: 161 us against 217 for 8 requests of 5k to 15k with 35 to 115 nodes, 63 against 80 for 8 x 8k with 32);
+    // below, its larger row blocks and the longer way to the first tile cost more than an even load gives (14 requests
+    // of 256 to 4k with up to 46 nodes: 62 us against 53).
+    const long long rb64 = (rows_g + 63) >> 6, tiles_cu = Hkv * batch * rb64 * t / 256;
+    const bool is_short = tiles_cu * D < 220 * 128 && !(t >= 250 && tiles_cu >= (eb == 2 ? 60 : 100));
+    if (is_short) {
+        b.rw = 2; b.wr_log2 = 6;
+        b.row_blocks = (int)rb64;
+        const int base = Hkv * batch * b.row_blocks;
+        // One request: as in the contiguous form.  More: parts of 32 tiles even out the lengths; where that leaves the chip room
+        // (it takes 512 of these workgroups at once), parts of 8 tiles or more for one such round of the longest request, of
+        // 20 or more for two rounds (2 requests of up to 2.4k with 26 nodes took 31 us in 2 parts and take 15 in 9).
+        int want = batch == 1 ? std::min((rows_g <= 64 ? 512 : 256) / base, t / 8) : std::min(8, t / 32);
+        if (batch > 1 && base < 256) want = std::max(want, std::min(32, std::max(std::min(512 / base, t / 8), std::min(1024 / base, t / 20))));
+        b.sps = ((t + std::max(1, want) - 1) / std::max(1, want) + 1) & ~1;                // whole rounds of two tiles
+        b.slots = (t + b.sps - 1) / b.sps;
+        b.merge = b.slots > 1;
+        return b;
+    }
+    b.rw = rows_g <= 64 && eb == 1 ? 2 : rows_g <= 128 || eb == 1 ? 4 : 8;
+    b.wr_log2 = b.rw == 2 ? 6 : b.rw == 4 ? 7 : 8;
+    b.row_blocks = (rows_g + (1 << b.wr_log2) - 1) >> b.wr_log2;
+    b.pairing = b.row_blocks > 1;
+    b.teams_log2 = (b.rw == 2 ? 9 : 8) - b.pairing;     // (one workgroup per CU, or two of the small ones)
+    const long long stretches = (long long)Hkv * batch * ((b.row_blocks + b.pairing) >> b.pairing);
+    b.slots = std::min(32, std::max(8, 4 + (int)((5 << b.teams_log2) / (b.pairing ? stretches : 2 * stretches))));
+    b.wmin = std::max(2 * START, (t + b.slots - 5) / (b.slots - 4) * WHOLE);
+    b.merge = t > SMALL;
+    return b;
+}
 
-WsLayout ws_layout(int total_M, int Hq, int D, int nsplit)
+struct WsLayout { size_t anc, plan, ml, opart, total; };
+
+WsLayout ws_layout(int total_M, int Hq, int D, int nsplit, int batch = 0)
 {
     WsLayout w;
     size_t off = BTV_WS_HEADER;
     w.anc = off; off += btv_align_up((size_t)total_M * BTV_ANC_WORDS * 4, BTV_WS_ALIGN);
+    w.plan = off; off += batch ? btv_align_up((size_t)(batch + 2) * sizeof(long long), BTV_WS_ALIGN) : 0;
     size_t rows = (size_t)total_M * Hq;
     size_t ns = nsplit > 1 ? nsplit : 0;
     w.ml = off; off += btv_align_up(ns * rows * 4 * 4, BTV_WS_ALIGN);
@@ -1647,12 +2061,17 @@ WsLayout ws_layout(int total_M, int Hq, int D, int nsplit)
     return w;
 }
 
-template <int D, int RW, int KW, int NT, bool PAGED, int EB = 2>
+enum Form { ONE_REQUEST, SHORT_BATCH, LONG_BATCH };
+
+template <int D, int RW, int KW, int NT, Form FORM, int EB = 2>
 int launch_bf16(const AttnParams &p, dim3 grid, hipStream_t st)
 {
-    constexpr int LDS_BYTES = WgLds<D, RW, KW, NT, EB>::BYTES;
+    constexpr int LDS_BYTES = PageLds<D, RW, KW, NT, FORM != ONE_REQUEST, EB>::BYTES;
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
-    auto kern = tv_attn_bf16<D, RW, KW, NT, PAGED, EB>;
+    void (*kern)(AttnParams);
+    if constexpr (FORM == LONG_BATCH) kern = tv_attn_batch<D, RW, KW, NT, EB>;
+    else if constexpr (FORM == SHORT_BATCH) kern = tv_attn_short<D, RW, KW, NT, EB>;
+    else kern = tv_attn_bf16<D, RW, KW, NT, EB>;
     if (!configured.load(std::memory_order_acquire)) {
         BTV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     LDS_BYTES));
@@ -1663,22 +2082,21 @@ int launch_bf16(const AttnParams &p, dim3 grid, hipStream_t st)
     return BTV_OK;
 }
 
-template <bool PAGED>
-int dispatch_bf16(AttnParams &p, const Plan &pl, int D, int batch, int eb, hipStream_t st)
+template <Form FORM>
+int dispatch_bf16(const AttnParams &p, int rw, int D, int eb, dim3 grid, hipStream_t st)
 {
-    p.row_blocks = pl.row_blocks;
-    p.units = pl.nsplit * p.Hkv * batch;
-    const int units = pl.nsplit * p.Hkv * batch;
-    dim3 grid(((units + 7) / 8) * pl.row_blocks * 8);
     if (eb == 1) {      // FP8 K/V
-        if (D == 128 && pl.rw == 2 && pl.kw == 2 && pl.nt == 5) return launch_bf16<128, 2, 2, 5, PAGED, 1>(p, grid, st);
-        if (D == 128 && pl.rw == 4 && pl.kw == 2 && pl.nt == 8) return launch_bf16<128, 4, 2, 8, PAGED, 1>(p, grid, st);
+        if (D == 128 && rw == 2) return launch_bf16<128, 2, 2, 5, FORM, 1>(p, grid, st);
+        if constexpr (FORM != SHORT_BATCH)
+            if (D == 128 && rw == 4) return launch_bf16<128, 4, 2, 8, FORM, 1>(p, grid, st);
         return btv_fail(BTV_EINVAL, "no FP8-KV kernel for D=%d", D);
     }
 #define BTV_CASE(DD, RR, KK, NN) \
-    if (D == DD && pl.rw == RR && pl.kw == KK && pl.nt == NN) return launch_bf16<DD, RR, KK, NN, PAGED>(p, grid, st);
-    BTV_CASE(128, 2, 2, 5) BTV_CASE(128, 4, 2, 8) BTV_CASE(128, 8, 1, 8)
-    BTV_CASE(64, 2, 2, 5) BTV_CASE(64, 4, 2, 8) BTV_CASE(64, 8, 1, 8)
+    if (D == DD && rw == RR) return launch_bf16<DD, RR, KK, NN, FORM>(p, grid, st);
+    if constexpr (FORM != LONG_BATCH) { BTV_CASE(128, 2, 2, 5) BTV_CASE(64, 2, 2, 5) }
+    if constexpr (FORM != SHORT_BATCH) {
+        BTV_CASE(128, 4, 2, 8) BTV_CASE(128, 8, 1, 8) BTV_CASE(64, 4, 2, 8) BTV_CASE(64, 8, 1, 8)
+    }
 #undef BTV_CASE
     return btv_fail(BTV_EINVAL, "no kernel for D=%d", D);
 }
@@ -1720,7 +2138,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     int rc = check_shape(M, L, Hq, Hkv, D);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Plan pl = make_plan(M, L, Hq, Hkv, 1, eb, force_split, force_shape);
+    Plan pl = make_plan(M, L, Hq, Hkv, eb, force_split, force_shape);
     if (dtype == BTV_F32) pl.nsplit = 1;
     WsLayout wl = ws_layout(M, Hq, D, pl.nsplit);
     rc = btv_check_ws(ws, ws_bytes, wl.total);
@@ -1745,12 +2163,14 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
         BTV_HIP(hipGetLastError());
         return BTV_OK;
     }
-    rc = dispatch_bf16<false>(p, pl, D, 1, eb, st);
+    p.row_blocks = pl.row_blocks;
+    p.units = pl.nsplit * Hkv;
+    rc = dispatch_bf16<ONE_REQUEST>(p, pl.rw, D, eb, dim3(((p.units + 7) / 8) * pl.row_blocks * 8), st);
     if (rc) return rc;
     if (pl.nsplit > 1) {
         dim3 cg((M * Hq + 7) / 8, 1);
-        if (D == 64) hipLaunchKernelGGL((tv_combine_bf16<64, false>), cg, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((tv_combine_bf16<128, false>), cg, dim3(256), 0, st, p);
+        if (D == 64) hipLaunchKernelGGL(tv_combine_bf16<64>, cg, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL(tv_combine_bf16<128>, cg, dim3(256), 0, st, p);
         BTV_HIP(hipGetLastError());
     }
     return BTV_OK;
@@ -1771,8 +2191,8 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     BTV_REQUIRE(num_blocks >= 1 && max_blocks >= 1, "bad block counts");
     BTV_REQUIRE((long long)max_blocks * BTV_PAGE >= (long long)L_max + 1, "max_blocks too small for L_max");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Plan pl = make_plan(M_max, L_max, Hq, Hkv, batch, eb);
-    WsLayout wl = ws_layout(batch * M_max, Hq, D, pl.nsplit);
+    const PlanB pl = make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, eb);
+    WsLayout wl = ws_layout(batch * M_max, Hq, D, pl.slots, batch);
     rc = btv_check_ws(ws, ws_bytes, wl.total);
     if (rc) return rc;
     unsigned char *w8 = static_cast<unsigned char *>(ws);
@@ -1787,17 +2207,23 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     p.M = M_max; p.L = L_max; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv;
     p.total_rows = batch * M_max * Hq;    // partial buffers are sized for the bound; rows index by q_offset
     p.total_M = total_M;
-    p.sps = pl.sps; p.nsplit = pl.nsplit;
+    p.plan = reinterpret_cast<long long *>(w8 + wl.plan);
+    p.batch = batch; p.teams_log2 = pl.teams_log2; p.pairing = pl.pairing; p.wmin = pl.wmin; p.wr_log2 = pl.wr_log2;
     set_scales(p, D, scale, k_scale, v_scale);
     p.parent = parent;
-    rc = dispatch_bf16<true>(p, pl, D, batch, eb, st);
-    if (rc) return rc;
-    if (pl.nsplit > 1) {
-        dim3 cg((M_max * Hq + 7) / 8, batch);
-        if (D == 64) hipLaunchKernelGGL((tv_combine_bf16<64, true>), cg, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((tv_combine_bf16<128, true>), cg, dim3(256), 0, st, p);
-        BTV_HIP(hipGetLastError());
+    p.sps = pl.sps; p.row_blocks = pl.row_blocks;
+    if (pl.sps) {
+        p.nsplit = pl.slots;
+        p.units = pl.slots * Hkv * batch;
+        rc = dispatch_bf16<SHORT_BATCH>(p, pl.rw, D, eb, dim3(((p.units + 7) / 8) * pl.row_blocks * 8), st);
+    } else {
+        rc = dispatch_bf16<LONG_BATCH>(p, pl.rw, D, eb, dim3(1 << (pl.teams_log2 + pl.pairing)), st);
     }
+    if (rc || !pl.merge) return rc;
+    dim3 cg((M_max * Hq + 7) / 8, batch);
+    if (D == 64) hipLaunchKernelGGL(tv_combine_batch<64>, cg, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL(tv_combine_batch<128>, cg, dim3(256), 0, st, p);
+    BTV_HIP(hipGetLastError());
     return BTV_OK;
 }
 
@@ -1827,7 +2253,7 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK) return 0;
-    int nsplit = dtype == BTV_BF16 ? make_plan(M, L, Hq, Hkv, 1).nsplit : 1;
+    int nsplit = dtype == BTV_BF16 ? make_plan(M, L, Hq, Hkv).nsplit : 1;
     return ws_layout(M, Hq, D, nsplit).total;
 }
 
@@ -1862,7 +2288,7 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
 size_t btv_tree_verify_attn_fp8kv_workspace(int M, int L, int Hq, int Hkv, int D)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, 1, 1).nsplit).total;
+    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, 1).nsplit).total;
 }
 
 int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, float k_scale, float v_scale,
@@ -1878,7 +2304,7 @@ int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, fl
 size_t btv_tree_verify_attn_tuned_workspace(int M, int L, int Hq, int Hkv, int D, int kv_fp8, int nsplit, int shape)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || (kv_fp8 && D != 128) || nsplit < 0 || shape < 0 || shape > 3) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, 1, kv_fp8 ? 1 : 2, nsplit, shape).nsplit).total;
+    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, kv_fp8 ? 1 : 2, nsplit, shape).nsplit).total;
 }
 
 int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale, float v_scale,
@@ -1898,8 +2324,7 @@ int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int 
 size_t btv_tree_verify_attn_paged_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK) return 0;
-    Plan pl = make_plan(M_max, L_max, Hq, Hkv, batch);
-    return ws_layout(batch * M_max, Hq, D, pl.nsplit).total;
+    return ws_layout(batch * M_max, Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 2).slots, batch).total;
 }
 
 int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_blocks,
@@ -1915,8 +2340,7 @@ int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpo
 size_t btv_tree_verify_attn_paged_fp8kv_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    Plan pl = make_plan(M_max, L_max, Hq, Hkv, batch, 1);
-    return ws_layout(batch * M_max, Hq, D, pl.nsplit).total;
+    return ws_layout(batch * M_max, Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 1).slots, batch).total;
 }
 
 int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const void *V8pool, float k_scale,

@@ -254,6 +254,59 @@ def test_paged_ragged_several_splits(G, oracle):
     _paged_case(G, oracle, [2100, 2047, 2049], [33, 32, 31], 4, 4, 64, seed=64)
 
 
+def long_batch(batch, M_max, L_long, long_at):
+    """Request sizes around the edges of the plan of a batch with much to do: stretches of tiles that are not cut (up to 16 tiles),
+    just longer ones, no prefix at all, one very long request; trees around the ends of row blocks."""
+    Ls = [(0, 1, 31, 32, 495, 511, 513, 530, 700)[r % 9] for r in range(batch)]
+    Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
+    Ls[long_at] = L_long
+    return Ls, Ns
+
+
+@pytest.mark.parametrize("batch, M_max, L_long, long_at, Hq, Hkv, D", [
+    (66, 33, 2900, 64, 16, 2, 128),      # 256-row blocks, teams of two, two chunks of requests
+    (130, 33, 2900, 3, 16, 2, 64),
+    (66, 16, 8100, 65, 16, 2, 128),      # 128-row blocks, teams of one
+    (130, 9, 8100, 129, 16, 4, 64),
+])
+def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long, long_at, Hq, Hkv, D):
+    Ls, Ns = long_batch(batch, M_max, L_long, long_at)
+    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=65)
+
+
+@pytest.mark.parametrize("M, L", [(1, 24000), (9, 9000), (130, 24000)])     # many parts; more than 32; the work shared out
+def test_paged_batch_of_one(G, oracle, M, L):
+    _paged_case(G, oracle, [L], [M], 16, 2, 128, seed=66)
+
+
+def test_paged_bad_requests_are_skipped_where_the_work_is_shared_out(G):
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    Ls, Ns = long_batch(66, 33, 2900, 64)
+    bt, nb = synth.paged_layout(5, [l + n for l, n in zip(Ls, Ns)])
+    qoff = np.concatenate([[0], np.cumsum(Ns)]).astype(np.int32)
+    run = {}
+    for bad in (None, 7, 64):
+        torch.manual_seed(0)
+        Q = torch.randn(int(qoff[-1]), 16, 128, device="cuda", dtype=torch.bfloat16)
+        K, V = (torch.randn(nb, synth.PAGE, 2, 128, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        L = np.asarray(Ls, dtype=np.int32)
+        if bad is not None:
+            L[bad] = -1
+        par = G.dev(np.concatenate([np.arange(n) - 1 for n in Ns]).astype(np.int32))
+        O = torch.full_like(Q, 7.0)
+        ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_workspace(66, 33, 2900, 16, 2, 128))
+        btv.btv_tree_verify_attn_paged(Q, K, V, G.dev(bt), G.dev(qoff), G.dev(L), par, 33, 2900, O, ws)
+        torch.cuda.synchronize()
+        assert (btv.btv_workspace_status(ws) != 0) == (bad is not None)
+        run[bad] = O.float()
+    for bad in (7, 64):
+        rows = slice(int(qoff[bad]), int(qoff[bad + 1]))
+        assert (run[bad][rows] == 7.0).all()
+        run[bad][rows] = run[None][rows]
+        assert (run[bad] - run[None]).abs().max() <= TOL_BF16      # (the others' parts may be cut elsewhere)
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_bf16_random_shapes(G, oracle, seed):
     """Seeded random shapes inside the documented limits (ragged M and L, every GQA ratio up to 16, both head sizes,

@@ -203,6 +203,17 @@ def test_paged_ragged(G, oracle):
     _paged_case(G, oracle, [5000, 300, 2500, 4097, 64, 9000], [40, 64, 7, 100, 130, 16], 8, 2, seed=83)
 
 
+@pytest.mark.parametrize("batch, M_max, L_long", [
+    (130, 8, 8100),       # 64-row blocks, teams of one
+    (66, 33, 2900),       # 128-row blocks, teams of two, an odd row block in some requests
+])
+def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long):
+    Ls = [(63, 64, 200, 490, 511, 513, 530, 700, 900)[r % 9] for r in range(batch)]   # (a few keys alone give values that bf16 itself rounds by 0.016)
+    Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
+    Ls[64] = L_long
+    _paged_case(G, oracle, Ls, Ns, 16, 2, seed=84)
+
+
 def test_config4_ragged_paged_full_size(G, oracle):
     Ls, Ns = synth.c4_request_shapes()
     _paged_case(G, oracle, Ls, Ns, 32, 8, seed=synth.C4.seed)
