@@ -1962,46 +1962,71 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
 
 struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; };
 
-// Kernel shape by the number of packed rows per KV head (G*M).  Every wave owns 32 rows.  Measured on MI355X at
-// L = 8192 (8 KV heads): what counts is one workgroup per CU and as few key splits as that allows (the split
-// partials are written and read back), so few rows get small row blocks and many rows get 128-row blocks, both
-// with pairs of waves alternating over the tiles (KW = 2); very many rows over a very long prefix take the
-// 256-row software-pipelined shape (KW = 1), which measures the same there within run-to-run noise.
-// `force_split` > 0 and `force_shape` in 1..3 replace the heuristic's choices (the tuning entry point passes them).
-Plan make_plan(int M, int L, int Hq, int Hkv, int eb = 2, int force_split = 0, int force_shape = 0)
+// Splits of `want` parts for a shape.
+void split_plan(Plan &pl, int M, int L, int want)
 {
-    Plan pl;
-    int G = Hq / Hkv, rows_g = G * M;
-    if (rows_g <= 128) { pl.rw = 2; pl.kw = 2; pl.nt = 5; }
-    // 768 packed rows or more (192 nodes at 4 query heads per KV head, 96 at 8): the software-pipelined 256-row
-    // shape, measured 12 % ahead at the 70B shape with a 32k prefix, 4 % at 256 nodes of the 8B shape, 2 % at 192;
-    // below, pairs of waves alternating over the tiles are 3-8 % ahead.  The FP8 cache has only the latter.
-    else if (eb == 2 && rows_g >= 768) { pl.rw = 8; pl.kw = 1; pl.nt = 8; }
-    else { pl.rw = 4; pl.kw = 2; pl.nt = 8; }
-    if (force_shape == 1) { pl.rw = 2; pl.kw = 2; pl.nt = 5; }
-    if (force_shape == 2) { pl.rw = 4; pl.kw = 2; pl.nt = 8; }
-    if (force_shape == 3 && eb == 2) { pl.rw = 8; pl.kw = 1; pl.nt = 8; }
-    pl.wr = pl.rw * 32;
-    pl.row_blocks = (rows_g + pl.wr - 1) / pl.wr;
-    pl.stages = (L + M + TK - 1) / TK;
     // Tiles that hold tree rows cost more than plain tiles (mask; in the pipelined loop also a second row maximum)
     // and all sit in the last split: sizing the splits as if there were `extra` more tiles leaves the last one
     // that much shorter.
     const int tree_tiles = pl.stages - L / TK;
     const int extra = pl.kw == 1 ? (7 * tree_tiles + 9) / 10 : (tree_tiles + 3) / 4;
-    int base = Hkv * pl.row_blocks;
-    // 64 rows or fewer: finer splits still pay.
-    int target = rows_g <= 64 ? 512 : 256;
-    // (rounded down: one split more than the CUs hold sends a second, nearly empty round of workgroups through the
-    // chip, e.g. 6 splits x 48 = 288 workgroups at 192 nodes took 61 us against 43 us for 5 x 48 = 240)
-    int want = force_split > 0 ? force_split : std::max(1, target / base);
-    // a split should stream at least 8 tiles (256 keys) unless the caller forces it
-    if (force_split <= 0) want = std::min(want, std::max(1, pl.stages / 8));
     want = std::max(1, std::min(want, pl.stages));
     pl.sps = (pl.stages + (want > 1 ? extra : 0) + want - 1) / want;
     pl.sps = (pl.sps + pl.kw - 1) / pl.kw * pl.kw;         // whole rounds of KW tiles
     pl.nsplit = (pl.stages + pl.sps - 1) / pl.sps;
-    return pl;
+}
+
+// Shape of the workgroups (64, 128 or 256 packed rows of a KV head; 32 rows per wave, pairs of waves alternating over the
+// tiles in the first two, the software-pipelined loop in the third) and number of key splits of one request: those with
+// the least estimated time.  The estimate: what a workgroup's tiles take (two workgroups of the 64-row shape share a CU
+// at 1.2 times the time each), times the rounds in which the CUs of the fullest XCD take the workgroups, but no less than the
+// K/V bytes need, some of the smaller of the two on top; and for more than one split the merge.  Its constants are a fit to
+// 250 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
+// and 30 split counts: the choice is 1.3 % behind the best one found on average, the rule by row count alone that it
+// replaces (always 256 workgroups where the tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows
+// over 450 keys: 21 us in 256-row blocks and 2 splits, 12 us in 64-row blocks and 5).
+// `force_split` > 0 and `force_shape` in 1..3 replace the choice (the tuning entry point passes them).
+Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split = 0, int force_shape = 0)
+{
+    static constexpr struct { int rw, kw, nt; float start, tile[3]; } SHAPES[3] = {      // tile: us; bf16 D = 128, D = 64, FP8
+        { 2, 2, 5, 0.0f, { 0.456f, 0.239f, 0.443f } },
+        { 4, 2, 8, 0.5f, { 0.492f, 0.314f, 0.575f } },
+        { 8, 1, 8, 0.1f, { 0.695f, 0.421f, 0.0f } },
+    };
+    static constexpr float SHARED_TILE[3] = { 0.560f, 0.308f, 0.585f };                   // two 64-row workgroups on a CU
+    static constexpr int SPLITS[] = { 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64 };
+    const int rows_g = Hq / Hkv * M, kind = eb == 1 ? 2 : D == 64 ? 1 : 0;
+    const float bytes = 2.0f * ((float)L + M) * Hkv * D * eb, mem = bytes / 5.7e6f, part = 2.0f * M * Hq * D * 1e-6f;
+    Plan best = {};
+    float best_t = 0.f;
+    for (int k = 0; k < 3; ++k) {
+        if (force_shape ? force_shape != k + 1 && !(eb == 1 && force_shape == 3 && k == 1) : eb == 1 && k == 2) continue;
+        Plan pl;
+        pl.rw = SHAPES[k].rw; pl.kw = SHAPES[k].kw; pl.nt = SHAPES[k].nt;
+        pl.wr = pl.rw * 32;
+        pl.row_blocks = (rows_g + pl.wr - 1) / pl.wr;
+        pl.stages = (L + M + TK - 1) / TK;
+        auto consider = [&](int want) {
+            split_plan(pl, M, L, want);
+            const int n = pl.nsplit, wgs = (n * Hkv + 7) / 8 * 8 * pl.row_blocks;         // (as many as the fullest XCD has, times 8)
+            const float cap = k == 0 ? 512.f : 256.f, fill = wgs / cap;
+            const float rounds = 0.45f * std::ceil(fill) + 0.55f * std::max(1.f, fill);
+            const float comp = rounds * pl.sps * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]);
+            float t = SHAPES[k].start + std::max(comp, mem) + 0.2f * std::min(comp, mem);
+            if (n > 1) t += 2.0f + n * part + 0.09f * std::max(0, n - 32);
+            if (!best_t || t < best_t) { best = pl; best_t = t; }
+        };
+        if (force_split > 0) { consider(force_split); continue; }
+        // no more splits than tiles, nor partials than the built-in scratch array holds (32 MB are 6 us to write and read)
+        const int most = (int)std::min<long long>(std::min(64, pl.stages), std::max<long long>(1, (31ll << 20) / ((long long)M * Hq * (D * 2 + 16))));
+        for (int want : SPLITS)
+            if (want <= most) consider(want);
+        for (int cap = 256; cap <= (k == 0 ? 1024 : 512); cap *= 2) {                     // as many as whole rounds take
+            const int want = cap / (8 * pl.row_blocks) * 8 / Hkv;
+            if (want >= 1 && want <= most) consider(want);
+        }
+    }
+    return best;
 }
 
 // A batch: shape of the workgroups by the largest tree's packed rows; in how many parts a row's partials may come; whether a
@@ -2138,7 +2163,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     int rc = check_shape(M, L, Hq, Hkv, D);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    Plan pl = make_plan(M, L, Hq, Hkv, eb, force_split, force_shape);
+    Plan pl = make_plan(M, L, Hq, Hkv, D, eb, force_split, force_shape);
     if (dtype == BTV_F32) pl.nsplit = 1;
     WsLayout wl = ws_layout(M, Hq, D, pl.nsplit);
     rc = btv_check_ws(ws, ws_bytes, wl.total);
@@ -2253,7 +2278,7 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK) return 0;
-    int nsplit = dtype == BTV_BF16 ? make_plan(M, L, Hq, Hkv).nsplit : 1;
+    int nsplit = dtype == BTV_BF16 ? make_plan(M, L, Hq, Hkv, D).nsplit : 1;
     return ws_layout(M, Hq, D, nsplit).total;
 }
 
@@ -2288,7 +2313,7 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
 size_t btv_tree_verify_attn_fp8kv_workspace(int M, int L, int Hq, int Hkv, int D)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, 1).nsplit).total;
+    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, D, 1).nsplit).total;
 }
 
 int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, float k_scale, float v_scale,
@@ -2304,7 +2329,7 @@ int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, fl
 size_t btv_tree_verify_attn_tuned_workspace(int M, int L, int Hq, int Hkv, int D, int kv_fp8, int nsplit, int shape)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || (kv_fp8 && D != 128) || nsplit < 0 || shape < 0 || shape > 3) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, kv_fp8 ? 1 : 2, nsplit, shape).nsplit).total;
+    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, D, kv_fp8 ? 1 : 2, nsplit, shape).nsplit).total;
 }
 
 int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale, float v_scale,
