@@ -180,6 +180,9 @@ struct alignas(16) RankLds {                // bound and ranking of one position
             uint16_t slot[SLOTCAP + 64];        // slots (chunk * 256 + thread) whose maximum reaches the bound
         };
     };
+    alignas(16) int first[2048];            // rank_keys_binned: RANK_BINS bins; SELCAP keys
+    int at[2048];
+    u64 sorted[SELCAP];
     int hist[256];
     int wsum[4];
     int sel_bin;
@@ -254,7 +257,7 @@ __device__ __forceinline__ void rank_keys(const u64 *sel, int n, int K, int KP, 
     for (int i = K + tid; i < KP; i += nthreads) publish(q_row, tok_row, i, 0.f, 0u);
 }
 
-// The same for at most 256 keys on a workgroup of 256: a key belongs to T = 1, 2 or 4 neighbouring lanes, which take
+// The same for at most RANK_FEW keys on a workgroup of 256: a key belongs to T = 2 or 4 neighbouring lanes, which take
 // the list's pairs in turn (lane `part` reads pairs part, part + T, ...), two keys per LDS read and eight reads in
 // flight; the shares meet by quad swaps.  Every address is the trip's base plus a constant (a compare, a select and
 // an address sum per read had been half of the loop's instructions), none of the reads is conditional (the compiler
@@ -282,16 +285,66 @@ __device__ __forceinline__ int rank_count(const ulonglong2 *two, int n, int part
 
 __device__ __forceinline__ void rank_keys_split(u64 *sel, int n, int K, int KP, float *q_row, uint32_t *tok_row, int tid)
 {
-    const int lgT = n <= 64 ? 2 : n <= 128 ? 1 : 0, T = 1 << lgT;
+    const int lgT = n <= 64 ? 2 : 1, T = 1 << lgT;
     const int i = tid >> lgT, part = tid & (T - 1);
-    if (tid < RANK_PAD) sel[n + tid] = 0ull;                   // n <= 256 of the list's 512 places are taken
+    if (tid < RANK_PAD) sel[n + tid] = 0ull;                   // n <= RANK_FEW of the list's 512 places are taken
     __syncthreads();
     const u64 mine = sel[min(i, n)];
     const ulonglong2 *two = reinterpret_cast<const ulonglong2 *>(sel);
-    int cnt = lgT == 2 ? rank_count<4>(two, n, part, mine) : lgT == 1 ? rank_count<2>(two, n, part, mine) : rank_count<1>(two, n, part, mine);
-    if (T >= 2) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    int cnt = lgT == 2 ? rank_count<4>(two, n, part, mine) : rank_count<2>(two, n, part, mine);
+    cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
     if (T == 4) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
     if (part == 0 && i < n && cnt < K) publish(q_row, tok_row, cnt, __uint_as_float((uint32_t)(mine >> 32)), 0xFFFFFFFFu - (uint32_t)mine);
+    for (int e = K + tid; e < KP; e += 256) publish(q_row, tok_row, e, 0.f, 0u);
+}
+
+// How many of keys[lo .. hi - 1] are above `mine`: eight reads in flight.
+__device__ __forceinline__ int count_above(const u64 *keys, int lo, int hi, u64 mine)
+{
+    int n = 0;
+    for (int j = lo; j < hi; j += 8) {
+        u64 k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) k[u] = keys[min(j + u, hi - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) n += j + u < hi && k[u] > mine ? 1 : 0;
+    }
+    return n;
+}
+
+// More than RANK_FEW keys: into bins of a 64th of a binade above the bound (a key's bin falls as its probability does), an
+// exclusive sum of the bins from the top gives their first ranks, and a key is counted only against those of its bin.  What it takes
+// is six barriers: 256 keys of a confident drafter 1.6 us, comparing each with all of them 4.6.
+constexpr int RANK_FEW = 96, RANK_BINS = 2048, RANK_SHIFT = 17;
+__device__ __forceinline__ void rank_keys_binned(const u64 *sel, u64 *sorted, int *first, int *at, int *wsum, uint32_t tau, int n, int K, int KP, float *q_row,
+                                                 uint32_t *tok_row, int tid, int lane, int w)
+{
+    auto bin_of = [&](u64 k) { return min((int)(((uint32_t)(k >> 32) - tau) >> RANK_SHIFT), RANK_BINS - 1); };
+#pragma unroll
+    for (int i = 0; i < RANK_BINS / 1024; ++i) reinterpret_cast<int4 *>(first)[i * 256 + tid] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    for (int i = tid; i < n; i += 256) atomicAdd(&first[bin_of(sel[i])], 1);
+    __syncthreads();
+    {                                                          // thread t: bins 8 t .. 8 t + 7
+        const int4 x = reinterpret_cast<const int4 *>(first)[2 * tid], y = reinterpret_cast<const int4 *>(first)[2 * tid + 1];
+        const int s7 = y.w, s6 = s7 + y.z, s5 = s6 + y.y, s4 = s5 + y.x, s3 = s4 + x.w, s2 = s3 + x.z, s1 = s2 + x.y, own = s1 + x.x;
+        const int incl = wave_incl_scan(own), total = __builtin_amdgcn_readlane(incl, 63);
+        if (lane == 0) wsum[w] = total;
+        __syncthreads();
+        const int up = total - incl + (w < 1 ? wsum[1] : 0) + (w < 2 ? wsum[2] : 0) + (w < 3 ? wsum[3] : 0);
+        const int4 p = make_int4(up + s1, up + s2, up + s3, up + s4), q = make_int4(up + s5, up + s6, up + s7, up);
+        reinterpret_cast<int4 *>(first)[2 * tid] = p; reinterpret_cast<int4 *>(first)[2 * tid + 1] = q;
+        reinterpret_cast<int4 *>(at)[2 * tid] = p; reinterpret_cast<int4 *>(at)[2 * tid + 1] = q;
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += 256) sorted[atomicAdd(&at[bin_of(sel[i])], 1)] = sel[i];
+    __syncthreads();
+    for (int i = tid; i < n; i += 256) {
+        const u64 mine = sorted[i];
+        const int b = bin_of(mine), hi = at[b];
+        const int lo = first[b], rank = lo + count_above(sorted, lo, hi, mine);
+        if (rank < K) publish(q_row, tok_row, rank, __uint_as_float((uint32_t)(mine >> 32)), 0xFFFFFFFFu - (uint32_t)mine);
+    }
     for (int e = K + tid; e < KP; e += 256) publish(q_row, tok_row, e, 0.f, 0u);
 }
 
@@ -593,13 +646,29 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
 __device__ __forceinline__ int sweep_bin(uint32_t bits) { return (int)min(bits >> 19, (uint32_t)SW_BINS - 1u); }
 __device__ __forceinline__ int sweep_coarse(uint32_t bits) { return (int)min(bits >> 21, (uint32_t)SW_COARSE - 1u); }
 
-__device__ __forceinline__ double wave_incl_sum(double x, int lane)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double x)                // 0 where no lane is the source
 {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(x, off);
-        if (lane >= off) x += o;
-    }
+    const u64 b = __builtin_bit_cast(u64, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xF, CTRL < 0x142);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xF, CTRL < 0x142);
+    return __builtin_bit_cast(double, ((u64)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_incl_sum(double x)
+{
+    x += dpp_f64<0x111, 0xF>(x);
+    x += dpp_f64<0x112, 0xF>(x);
+    x += dpp_f64<0x114, 0xF>(x);
+    x += dpp_f64<0x118, 0xF>(x);
+    x += dpp_f64<0x142, 0xA>(x);
+    x += dpp_f64<0x143, 0xC>(x);
+    return x;
+}
+__device__ __forceinline__ float row_incl_sum(float x)             // within the rows of 16 lanes
+{
+    auto step = [&](auto ctrl) { x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true)); };
+    step(std::integral_constant<int, 0x111>{}); step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{}); step(std::integral_constant<int, 0x118>{});
     return x;
 }
 
@@ -692,7 +761,7 @@ __device__ __forceinline__ int sweep_raise(const SweepLds &L, int N, int lane)
 
 // Whole sweep.  Returns the number of candidates, -1 if they do not fit; th: the last threshold (score bits, as a signed number,
 // that a new candidate must exceed; -1 while there are fewer than N of them).
-__device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int &th)
+__device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int floor, int &th)
 {
     const int tid = w * 64 + lane, K1 = min(K, N);
     if (tid < SW_COARSE / 4) reinterpret_cast<int4 *>(L.coarse)[tid] = make_int4(0, 0, 0, 0);
@@ -701,7 +770,8 @@ __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int
         sweep_put(L, tid, __float_as_uint(__fmul_rn(1.0f, S.q[tid])), sweep_meta(SW_ROOT, (uint32_t)tid, 0, sweep_share(N, tid)));
     __syncthreads();
     int d = 2, a = 0, b = K1, buf = 0;                         // the level before: candidates a .. b - 1
-    th = -1;
+    th = floor;
+    bool raised = false;
     for (;;) {
         if (w == 0) {
             int seen = 0;                                      // candidates when the threshold was last moved
@@ -711,7 +781,7 @@ __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int
                 const float qr[4] = { qd[0], qd[min(1, K - 1)], qd[min(2, K - 1)], qd[min(3, K - 1)] };
                 uint2 x = L.cand[min(a + lane, b - 1)];
                 // (a few more candidates since then hardly move it)
-                if (b >= N && (th < 0 || b - seen > (N >> 4))) { th = sweep_raise(L, N, lane); seen = b; }
+                if (b >= N && (!raised || b - seen > (N >> 2))) { th = max(floor, sweep_raise(L, N, lane)); seen = b; raised = true; }
                 if (b - a > SW_THIN) break;
                 int nb = b;
                 for (int a0 = a; a0 < b; a0 += 64) {
@@ -762,19 +832,26 @@ __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int
     return b;
 }
 
+// star: the tree is the N best tokens of the first position.  floor: nodes that score no more (bits; -1: none) are not wanted.
 // more: nothing is written, and false returned, if the early stop has not come within N nodes.
-__device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, bool adapt, bool more, int tid, int32_t *parent,
+__device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, bool star, bool adapt, bool more, int floor, int tid, int32_t *parent,
                                              int32_t *token, int32_t *depth, float *rho, int32_t *n_out, float *ahat,
                                              const Adaptive &ad)
 {
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int np = min(K, N), rank = tid, dep = 1;
+    float r;
+    uint32_t par = SW_ROOT;
+    if (star) {
+        r = tid < np ? __fmul_rn(1.0f, S.q[tid]) : 0.f;
+    } else {
 #pragma unroll
     for (int i = 0; i < SW_BINS / 1024; ++i) reinterpret_cast<int4 *>(L.hist)[i * 256 + tid] = make_int4(0, 0, 0, 0);
     // ---- the N first of the candidates, in order ---------------------------------------------------------------------
     int th;
-    const int b = sweep_levels(S, L, B, K, KP, N, lane, w, th);
+    const int b = sweep_levels(S, L, B, K, KP, N, lane, w, floor, th);
     if (b < 0) return false;                                   // (uniform)
-    const int np = min(b, N);
+    np = min(b, N);
     for (int c = tid; c < b; c += 256) {
         const uint32_t r = L.cand[c].y;
         if ((int)r >= th) atomicAdd(&L.hist[sweep_bin(r)], 1);
@@ -806,8 +883,7 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
     for (int p = tid; p < kept; p += 256) {
         const u64 k = L.key[p];
         const int bin = sweep_bin((uint32_t)(k >> 32)), lo = L.hist[bin], hi = L.at[bin];
-        int place = lo;
-        for (int j = lo; j < hi; ++j) place += L.key[j] > k ? 1 : 0;
+        const int place = lo + count_above(L.key, lo, hi, k);
         const uint32_t c = 0xFFFFFFFFu - (uint32_t)k;
         L.cand[c].y = (uint32_t)place;
         L.order[place] = (uint16_t)p;
@@ -815,21 +891,24 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
     __syncthreads();
     const u64 k = L.key[tid < np ? L.order[tid] : 0];
     const uint32_t mt = L.cand[0xFFFFFFFFu - (uint32_t)k].x;
-    const float r = tid < np ? __uint_as_float((uint32_t)(k >> 32)) : 0.f;
-    const int rank = (int)((mt >> 12) & 0xFFu), dep = (int)((mt >> 20) & 0xFu) + 1;
-    const uint32_t par = mt & 0xFFFu;
+    r = tid < np ? __uint_as_float((uint32_t)(k >> 32)) : 0.f;
+    rank = (int)((mt >> 12) & 0xFFu); dep = (int)((mt >> 20) & 0xFu) + 1;
+    par = mt & 0xFFFu;
+    }
     int n = np;
     if (adapt) {
         // Sec. 3.4, Eq. 6: the budget stops at the first node that does not improve Ahat(n) * L_AR / C(n); all nodes before
         // it improved, so a node is compared with the one before it (fp64 prefix sums in emission order)
-        double sum = wave_incl_sum((double)r, lane);
+        double sum = wave_incl_sum((double)r);
         if (lane == 63) L.wd[w] = sum;
         if (tid == 0) L.n_stop = np;
         __syncthreads();
         const double w0 = L.wd[0], w1 = L.wd[1], w2 = L.wd[2];
         const double an = 1.0 + ((w > 0 ? w0 : 0.0) + (w > 1 ? w1 : 0.0) + (w > 2 ? w2 : 0.0) + sum), before = an - (double)r;
         const double cn = tid < np ? S.cost[tid] : 1.0, cb = tid > 0 && tid < np ? S.cost[tid - 1] : 1.0;
-        if (tid < np && (!(cn > 0.0) || (tid > 0 && !(an * cb > before * cn)))) atomicMin(&L.n_stop, tid);
+        // (one lane of each wavefront: the compiler takes the lanes of an atomic to one address one after the other, 5000 cycles)
+        const u64 stops = __builtin_amdgcn_ballot_w64(tid < np && (!(cn > 0.0) || (tid > 0 && !(an * cb > before * cn))));
+        if (lane == 0 && stops != 0ull) atomicMin(&L.n_stop, w * 64 + (int)__builtin_ctzll(stops));
         __syncthreads();
         n = L.n_stop;
         if (more && n == N) return false;                      // (uniform) still improving: the caller goes on to a larger budget
@@ -847,10 +926,8 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
         if (rho) rho[tid] = r;
     }
     if (!adapt) {
-        double sum = (double)r;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-        if (lane == 0) L.wd[w] = sum;
+        const double sum = wave_incl_sum((double)r);
+        if (lane == 63) L.wd[w] = sum;
         __syncthreads();
         if (tid == 0) {
             *n_out = n;
@@ -933,7 +1010,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     __shared__ union RankOrLevels { RankLds rank; SweepLds lev; } U;     // the ranking is over when the expansion starts
     __shared__ ExpandLds S;
     __shared__ BeamLds BM;
-    __shared__ int use_levels;
+    __shared__ int use_levels, L_floor[2];
     RankLds &RL = U.rank;
     // Fetch every argument in one round trip: left to the compiler the scalar loads follow the code in four
     // dependent steps over an argument block of several cache lines that is cold in every launch.
@@ -1121,10 +1198,10 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     }
     __syncthreads();
     const int nc = RL.nsel;
-    if (nc <= 256) {
+    if (nc <= RANK_FEW) {
         rank_keys_split(RL.sel, nc, K, KP, q_row, tok_row, tid);
     } else if (nc <= SELCAP) {
-        rank_keys(RL.sel, nc, K, KP, q_row, tok_row, tid, 256);
+        rank_keys_binned(RL.sel, RL.sorted, RL.first, RL.at, RL.wsum, tau, nc, K, KP, q_row, tok_row, tid, lane, w);
     } else if (w == 0) {                       // rare: one wavefront selects the K best of the row first
         wave_select_rank([&](auto f) { for (int v = lane; v < V; v += 64) f(make_key(src[v], (uint32_t)v)); },
                          K, KP, RL.hist, RL.sel, &RL.nsel, q_row, tok_row, lane);
@@ -1138,6 +1215,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     }
     __syncthreads();
     if (!RL.last) return;
+    const double cost_mine = ad.cost && tid < N ? ad.cost[tid] : 1.0;   // (on its way together with the lists)
     {   // all of a thread's loads are issued before the first is stored (a load and its store per loop trip would
         // make every trip a round trip to memory): 1, 4 or MAXB entries of each list per thread
         const size_t lists = (size_t)req * B * KP;
@@ -1178,8 +1256,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
             return;
         }
     }
-    if (ad.cost)
-        for (int e = tid; e < N; e += 256) S.cost[e] = ad.cost[e];
+    if (ad.cost && tid < N) S.cost[tid] = cost_mine;           // (N <= 256)
     __syncthreads();
     if (beam_width > 0) {                      // B rows = depths of the beam tree, K = min(V, width)
         beam_block(S, BM, B, K, KP, beam_width, tid, parent, token, depth, rho, n_out, ahat);
@@ -1194,23 +1271,48 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     // N = 64: 23.6 / 28, N = 256: 35 / 113 (65 with a pool kept in order from level to level, which this replaced).
     if (w == 0) {
         const int k = min(lane, B - 1);
-        float chain = lane < B ? __log2f(S.q[k * KP]) : -1e30f;            // (an estimate: the choice changes no result)
-#pragma unroll
-        for (int off = 1; off < MAXB; off <<= 1) {
-            const float o = __shfl_up(chain, off);
-            if (lane >= off) chain += o;
-        }
+        const float chain = row_incl_sum(lane < B ? __log2f(S.q[k * KP]) : -1e30f);      // (an estimate: the choice changes no result)
         const float g_est = __log2f(S.q[min(K, N) - 1]);
         const int reach = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < B && chain >= g_est));
-        if (lane == 0) use_levels = algo == 2 || (algo == 0 && (N > 64 || 2.0f + 0.9f * (float)min(reach, N) < 0.27f * (float)N));
+        // a star: no child of the best first token comes before the N-th best first token (a tie goes to the lesser depth)
+        const bool star = K >= N && (B == 1 || __fmul_rn(__fmul_rn(1.0f, S.q[0]), S.q[KP]) <= __fmul_rn(1.0f, S.q[N - 1]));
+        if (ad.cost && !star) {
+            // The early stop takes a node only if rho(n) C(n-1) > Ahat(n-1) (C(n) - C(n-1)); Ahat(n-1) is at least 1 and the
+            // sum of the greedy chain's n - 1 best scores, so no wanted node scores less than the least of these bounds over n
+            // (up to 64 nodes, the first budget; up to N).  Not with costs that are no costs
+            // or marginals that are no probabilities.
+            const float own = lane < B ? __builtin_amdgcn_exp2f(chain) : 0.f, sums = row_incl_sum(own);
+            const float first = 1.0f + __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(own), 0));
+            const float whole = 1.0f + __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(sums), 15));
+            bool good = lane >= B || S.q[k * KP] <= 1.0f;
+            uint32_t inv[2];                            // ~bits of the least: the greatest of them is wanted
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = u * 64 + lane, at = min(e, N - 1);
+                const double c = S.cost[at], cb = S.cost[max(at - 1, 0)];
+                good = good && c > 0.0 && c < 1e300;
+                const float l = (float)(c - cb) * __builtin_amdgcn_rcpf((float)cb) * (at > B ? whole : first);
+                const uint32_t x = e == 0 || e >= N ? 0u : l > 0.f ? ~__float_as_uint(l) : 0xFFFFFFFFu;
+                if (u < 2) inv[u] = x; else inv[1] = umax(inv[1], x);
+            }
+            const uint32_t a0 = wave_max_u32(inv[0]), a1 = umax(a0, wave_max_u32(inv[1]));
+            const bool ok = __builtin_amdgcn_ballot_w64(!good) == 0ull;
+            auto floor_of = [&](uint32_t a) {
+                const float l = __uint_as_float(~a);
+                return ok && l > 0.f && l < 1.0f ? (int)__float_as_uint(l * 0.999f) : -1;
+            };
+            if (lane == 0) { L_floor[0] = floor_of(a0); L_floor[1] = floor_of(a1); }
+        }
+        if (lane == 0)
+            use_levels = algo == 0 && star ? 2 : algo == 2 || (algo == 0 && (N > 64 || 2.0f + 0.9f * (float)min(reach, N) < 1.2f + 0.27f * (float)N)) ? 1 : 0;
     }
     __syncthreads();
     if (use_levels) {
         // with the early stop: it comes within the first 64 nodes as a rule, and their tree is a prefix of the larger one
-        const bool adapt = ad.cost != nullptr;
+        const bool adapt = ad.cost != nullptr, star = use_levels == 2;
         bool done = false;
-        for (int budget = adapt ? min(N, 64) : N;; budget = N) {
-            done = expand_sweep(S, U.lev, B, K, KP, budget, adapt, budget < N, tid, parent, token, depth, rho, n_out, ahat, ad);
+        for (int budget = adapt && !star ? min(N, 64) : N;; budget = N) {
+            done = expand_sweep(S, U.lev, B, K, KP, budget, star, adapt, budget < N, adapt && !star ? L_floor[budget < N ? 0 : 1] : -1, tid, parent, token, depth, rho, n_out, ahat, ad);
             if (done || budget == N) break;
             __syncthreads();
         }

@@ -55,6 +55,17 @@ def test_vocabularies_around_the_slot_sizes(G, oracle, V):
         _check(G, oracle, synth.marginals(70 + seed, B, V, sigma), N)
 
 
+@pytest.mark.parametrize("N", [1, 2, 40, 97, 256])
+@pytest.mark.parametrize("step", [-1, 0, 1])
+def test_star_and_its_first_deeper_node(G, oracle, N, step):
+    """The best second-level node just below the N-th best first token, level with it (the lesser depth comes first), just above."""
+    q0 = (0.5 * 0.97 ** np.arange(300)).astype(np.float32)
+    q1 = np.full(300, 1e-4, dtype=np.float32)
+    q1[7] = q0[N - 1] * np.float32(2)
+    q1[7] = np.nextafter(q1[7], np.float32(step)) if step else q1[7]
+    _check(G, oracle, np.stack([q0, q1, q1]), N)
+
+
 def test_more_candidates_than_the_sweep_holds(G, oracle):
     """Marginals near 1 for many tokens (no probabilities, but finite and at most 1) make every level of the lattice larger than
     the sweep's lists: the frontier loop takes over, whichever expansion was asked for."""
