@@ -1385,34 +1385,39 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     }
 
     // ---- write: final bf16 rows when this request has a single split, scaled fp16 partials otherwise ---
-    if (pc_.direct) {
-        const float inv = p.out_scale / l_run;
-        uint16_t *Op = static_cast<uint16_t *>(p.O) + orow * D + dt0 * 32;
+    // A lane holds channels 8 q + 4 h .. + 3 of its row, the other half of the wave the other four: they exchange every second
+    // group, so that each has 8 neighbouring channels and a store instruction touches half as many pieces of rows (there
+    // are 32 rows per instruction whatever its width; the stores of a 256-row workgroup took 3 us).
+    auto store_rows = [&](unsigned char *row, auto pack) {
 #pragma unroll
         for (int dt = 0; dt < DTK; ++dt)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                uint32_t lo = float_to_bf16_bits(fin[dt][q4 * 4 + 0] * inv) | (float_to_bf16_bits(fin[dt][q4 * 4 + 1] * inv) << 16);
-                uint32_t hi = float_to_bf16_bits(fin[dt][q4 * 4 + 2] * inv) | (float_to_bf16_bits(fin[dt][q4 * 4 + 3] * inv) << 16);
-                *reinterpret_cast<uint2 *>(Op + dt * 32 + q4 * 8 + h * 4) = make_uint2(lo, hi);
+            for (int q = 0; q < 4; q += 2) {
+                const uint2 a = pack(dt, q), b = pack(dt, q + 1);
+                const auto x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false), y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+                *reinterpret_cast<uint4 *>(row + (dt * 32 + (q + h) * 8) * 2) = make_uint4(x[0], y[0], x[1], y[1]);
             }
+    };
+    if (pc_.direct) {
+        const float inv = p.out_scale / l_run;
+        auto pack = [&](int dt, int q) {
+            return make_uint2(float_to_bf16_bits(fin[dt][q * 4 + 0] * inv) | (float_to_bf16_bits(fin[dt][q * 4 + 1] * inv) << 16),
+                              float_to_bf16_bits(fin[dt][q * 4 + 2] * inv) | (float_to_bf16_bits(fin[dt][q * 4 + 3] * inv) << 16));
+        };
+        store_rows(static_cast<unsigned char *>(p.O) + (orow * D + dt0 * 32) * 2, pack);
     } else {
         // Partials travel as fp16 relative to (a bound within a factor two of) the row's largest magnitude, kept
         // in fp32 beside m and l: half the bytes of fp32 to write, flush at the end of the kernel and read back, at
         // a relative error of at most 2^-10 of that magnitude, below the final bf16 rounding.
         const float sc = amax > 0.f ? 1.0f / amax : 0.f;
         const size_t prow = (size_t)bx * p.total_rows + orow;
-        _Float16 *Pp = p.Opart + prow * D + dt0 * 32;
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int dt = 0; dt < DTK; ++dt)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const h2 lo = { (_Float16)(fin[dt][q4 * 4 + 0] * sc), (_Float16)(fin[dt][q4 * 4 + 1] * sc) };
-                const h2 hi = { (_Float16)(fin[dt][q4 * 4 + 2] * sc), (_Float16)(fin[dt][q4 * 4 + 3] * sc) };
-                *reinterpret_cast<uint2 *>(Pp + dt * 32 + q4 * 8 + h * 4) =
-                    make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-            }
+        auto pack = [&](int dt, int q) {
+            const h2 lo = { (_Float16)(fin[dt][q * 4 + 0] * sc), (_Float16)(fin[dt][q * 4 + 1] * sc) };
+            const h2 hi = { (_Float16)(fin[dt][q * 4 + 2] * sc), (_Float16)(fin[dt][q * 4 + 3] * sc) };
+            return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+        };
+        store_rows(reinterpret_cast<unsigned char *>(p.Opart) + (prow * D + dt0 * 32) * 2, pack);
         if (h == 0 && kw == 0) *reinterpret_cast<float4 *>(p.ML + prow * 4) = make_float4(m_run, l_run, amax, 0.f);
     }
 }
