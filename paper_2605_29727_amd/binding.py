@@ -68,6 +68,23 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_face = None
+
+
+def _load_face():
+    """The native face of the calls below (csrc/face.cpp): the same checks, without ctypes' cost per argument."""
+    global _face
+    lib()
+    try:
+        from . import _face as face
+    except ImportError as e:
+        raise BtvError(BTV_EHIP, f"the native face is not built ({e}); run __graft_entry__.build() "
+                                 "(python -m paper_2605_29727_amd.build)") from None
+    face.set_error(BtvError)
+    _face = face
+    return face
+
+
 def _check(rc: int):
     if rc != BTV_OK:
         raise BtvError(rc, lib().btv_last_error().decode())
@@ -112,19 +129,11 @@ def btv_tree_build_workspace(B: int, V: int, N: int) -> int:
 
 
 def btv_tree_build(marginals, N: int, parent, token, depth, rho, n_out, ahat, ws) -> None:
-    B, V = marginals.shape
-    assert marginals.dtype == torch.float32
-    _check(lib().btv_tree_build(_ptr(marginals), B, V, N, _ptr(parent), _ptr(token), _ptr(depth), _ptr(rho),
-                                _ptr(n_out), _ptr(ahat), _ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0),
-                                _stream()))
+    (_face or _load_face()).tree_build(marginals, N, parent, token, depth, rho, n_out, ahat, ws)
 
 
 def btv_tree_build_adaptive(marginals, N_max: int, cost, L_AR: float, parent, token, depth, rho, n_out, ahat, s_best, ws) -> None:
-    B, V = marginals.shape
-    assert marginals.dtype == torch.float32 and cost.dtype == torch.float64 and cost.numel() >= N_max
-    _check(lib().btv_tree_build_adaptive(_ptr(marginals), B, V, N_max, _ptr(cost), C.c_double(L_AR), _ptr(parent),
-                                         _ptr(token), _ptr(depth), _ptr(rho), _ptr(n_out), _ptr(ahat), _ptr(s_best),
-                                         _ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_build_adaptive(marginals, N_max, cost, L_AR, parent, token, depth, rho, n_out, ahat, s_best, ws)
 
 
 def btv_tree_build_tuned(marginals, N: int, algo: int, parent, token, depth, rho, n_out, ahat, ws, cost=None, L_AR: float = 0.0,
@@ -158,10 +167,7 @@ def btv_tree_build_batch_workspace(batch: int, B: int, V: int, N_max: int) -> in
 
 
 def btv_tree_build_batch(marginals, n_nodes, q_offset, N_max: int, parent, token, depth, rho, n_out, ahat, ws) -> None:
-    batch, B, V = marginals.shape
-    _check(lib().btv_tree_build_batch(_ptr(marginals), batch, B, V, _ptr(n_nodes), _ptr(q_offset), int(N_max), _ptr(parent),
-                                      _ptr(token), _ptr(depth), _ptr(rho), _ptr(n_out), _ptr(ahat), _ptr(ws),
-                                      C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_build_batch(marginals, n_nodes, q_offset, N_max, parent, token, depth, rho, n_out, ahat, ws)
 
 
 def btv_tree_accept_batch_workspace(batch: int, total_M: int, V: int) -> int:
@@ -169,12 +175,7 @@ def btv_tree_accept_batch_workspace(batch: int, total_M: int, V: int) -> int:
 
 
 def btv_tree_accept_greedy_batch(logits, parent, token, q_offset, M_max: int, path, n_acc, bonus, argmax_out, ws) -> None:
-    rows, V = logits.shape
-    batch = q_offset.numel() - 1
-    _check(lib().btv_tree_accept_greedy_batch(_ptr(logits), _dtype_code(logits), _ptr(parent), _ptr(token), _ptr(q_offset),
-                                              batch, rows - batch, int(M_max), V, _ptr(path), _ptr(n_acc), _ptr(bonus),
-                                              _ptr(argmax_out), _ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0),
-                                              _stream()))
+    (_face or _load_face()).tree_accept_greedy_batch(logits, parent, token, q_offset, M_max, path, n_acc, bonus, argmax_out, ws)
 
 
 def btv_tree_build_beam(marginals, width: int, depth_max: int, parent, token, depth, rho, n_out, ahat, ws) -> None:
@@ -231,12 +232,7 @@ def btv_tree_verify_attn_workspace(M, L, Hq, Hkv, D, dtype_code) -> int:
 
 
 def btv_tree_verify_attn(Q, K, V, parent, L: int, O, ws, scale: float = 0.0) -> None:
-    M, Hq, D = Q.shape
-    Hkv = K.shape[1]
-    assert K.shape[0] >= L + M and V.shape == K.shape and O.shape == Q.shape
-    _check(lib().btv_tree_verify_attn(_ptr(Q), _ptr(K), _ptr(V), _ptr(parent), M, L, Hq, Hkv, D, _dtype_code(Q),
-                                      C.c_float(scale), _ptr(O), _ptr(ws),
-                                      C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_verify_attn(Q, K, V, parent, L, O, ws, scale)
 
 
 def btv_tree_verify_attn_noalloc(Q, K, V, parent, L: int, O, status=None, scale: float = 0.0) -> None:
@@ -271,14 +267,7 @@ def btv_tree_verify_attn_paged_workspace(batch, M_max, L_max, Hq, Hkv, D) -> int
 
 def btv_tree_verify_attn_paged(Q, Kpool, Vpool, block_table, q_offset, prefix_len, parent, M_max: int, L_max: int,
                                O, ws, scale: float = 0.0) -> None:
-    total_M, Hq, D = Q.shape
-    num_blocks, page, Hkv, _ = Kpool.shape
-    assert page == BTV_PAGE and Q.dtype == torch.bfloat16
-    batch, max_blocks = block_table.shape
-    _check(lib().btv_tree_verify_attn_paged(_ptr(Q), _ptr(Kpool), _ptr(Vpool), num_blocks, _ptr(block_table),
-                                            max_blocks, _ptr(q_offset), _ptr(prefix_len), _ptr(parent), batch,
-                                            total_M, M_max, L_max, Hq, Hkv, D, C.c_float(scale), _ptr(O), _ptr(ws),
-                                            C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_verify_attn_paged(Q, Kpool, Vpool, block_table, q_offset, prefix_len, parent, M_max, L_max, O, ws, scale)
 
 
 def btv_tree_verify_attn_fp8kv_workspace(M, L, Hq, Hkv, D) -> int:
@@ -287,13 +276,7 @@ def btv_tree_verify_attn_fp8kv_workspace(M, L, Hq, Hkv, D) -> int:
 
 def btv_tree_verify_attn_fp8kv(Q, K8, V8, k_scale: float, v_scale: float, parent, L: int, O, ws,
                                scale: float = 0.0) -> None:
-    M, Hq, D = Q.shape
-    Hkv = K8.shape[1]
-    assert K8.shape[0] >= L + M and V8.shape == K8.shape and O.shape == Q.shape
-    assert Q.dtype == torch.bfloat16 and K8.element_size() == 1 and V8.element_size() == 1
-    _check(lib().btv_tree_verify_attn_fp8kv(_ptr(Q), _ptr(K8), _ptr(V8), C.c_float(k_scale), C.c_float(v_scale),
-                                            _ptr(parent), M, L, Hq, Hkv, D, C.c_float(scale), _ptr(O), _ptr(ws),
-                                            C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_verify_attn_fp8kv(Q, K8, V8, k_scale, v_scale, parent, L, O, ws, scale)
 
 
 def btv_tree_verify_attn_paged_fp8kv_workspace(batch, M_max, L_max, Hq, Hkv, D) -> int:
@@ -302,15 +285,8 @@ def btv_tree_verify_attn_paged_fp8kv_workspace(batch, M_max, L_max, Hq, Hkv, D) 
 
 def btv_tree_verify_attn_paged_fp8kv(Q, K8pool, V8pool, k_scale: float, v_scale: float, block_table, q_offset,
                                      prefix_len, parent, M_max: int, L_max: int, O, ws, scale: float = 0.0) -> None:
-    total_M, Hq, D = Q.shape
-    num_blocks, page, Hkv, _ = K8pool.shape
-    assert page == BTV_PAGE and Q.dtype == torch.bfloat16 and K8pool.element_size() == 1 and V8pool.element_size() == 1
-    batch, max_blocks = block_table.shape
-    _check(lib().btv_tree_verify_attn_paged_fp8kv(_ptr(Q), _ptr(K8pool), _ptr(V8pool), C.c_float(k_scale),
-                                                  C.c_float(v_scale), num_blocks, _ptr(block_table), max_blocks,
-                                                  _ptr(q_offset), _ptr(prefix_len), _ptr(parent), batch, total_M, M_max,
-                                                  L_max, Hq, Hkv, D, C.c_float(scale), _ptr(O), _ptr(ws),
-                                                  C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_verify_attn_paged_fp8kv(Q, K8pool, V8pool, k_scale, v_scale, block_table, q_offset, prefix_len, parent,
+                                                          M_max, L_max, O, ws, scale)
 
 
 def btv_tree_accept_workspace(M: int, V: int, stochastic: bool) -> int:
@@ -326,10 +302,7 @@ def btv_tree_accept_greedy_tuned(logits, parent, token, path, n_acc, bonus, argm
 
 
 def btv_tree_accept_greedy(logits, parent, token, path, n_acc, bonus, argmax_out, ws) -> None:
-    rows, V = logits.shape
-    _check(lib().btv_tree_accept_greedy(_ptr(logits), _dtype_code(logits), _ptr(parent), _ptr(token), rows - 1, V,
-                                        _ptr(path), _ptr(n_acc), _ptr(bonus), _ptr(argmax_out), _ptr(ws),
-                                        C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_accept_greedy(logits, parent, token, path, n_acc, bonus, argmax_out, ws)
 
 
 def btv_tree_accept_lm_head_workspace(M: int, V: int) -> int:
@@ -337,47 +310,20 @@ def btv_tree_accept_lm_head_workspace(M: int, V: int) -> int:
 
 
 def btv_tree_accept_greedy_lm_head(hidden, W, parent, token, path, n_acc, bonus, argmax_out, ws) -> None:
-    rows, h = hidden.shape
-    V = W.shape[0]
-    assert W.shape[1] == h and _dtype_code(hidden) == BTV_BF16 and _dtype_code(W) == BTV_BF16
-    _check(lib().btv_tree_accept_greedy_lm_head(_ptr(hidden), _ptr(W), h, _ptr(parent), _ptr(token), rows - 1, V,
-                                                _ptr(path), _ptr(n_acc), _ptr(bonus), _ptr(argmax_out), _ptr(ws),
-                                                C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+    (_face or _load_face()).tree_accept_greedy_lm_head(hidden, W, parent, token, path, n_acc, bonus, argmax_out, ws)
 
 
 def btv_tree_accept_stochastic(logits, marginals, parent, token, uniforms, path, n_acc, bonus, ws) -> None:
-    rows, V = logits.shape
-    B = marginals.shape[0]
-    assert marginals.shape[1] == V and uniforms.numel() >= rows
-    _check(lib().btv_tree_accept_stochastic(_ptr(logits), _dtype_code(logits), _ptr(marginals), B, _ptr(parent),
-                                            _ptr(token), rows - 1, V, _ptr(uniforms), _ptr(path), _ptr(n_acc),
-                                            _ptr(bonus), _ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0),
-                                            _stream()))
+    (_face or _load_face()).tree_accept_stochastic(logits, marginals, parent, token, uniforms, path, n_acc, bonus, ws)
 
 
 def btv_kv_commit(K, V, L: int, M: int, path, n_acc, new_len=None) -> None:
     """K, V [layers, rows >= L+M, ...] contiguous tensors of one dtype; reordered in place."""
-    assert K.shape == V.shape and K.is_contiguous() and V.is_contiguous() and K.dim() >= 3
-    layers = K.shape[0]
-    row_bytes = K[0, 0].numel() * K.element_size()
-    _check(lib().btv_kv_commit(_ptr(K), _ptr(V), layers, C.c_longlong(K.stride(0) * K.element_size()), L, M, row_bytes,
-                               _ptr(path), _ptr(n_acc), _ptr(new_len), _stream()))
+    (_face or _load_face()).kv_commit(K, V, L, M, path, n_acc, new_len)
 
 
 def btv_kv_commit_paged(Kpool, Vpool, block_table, prefix_len, path, n_acc, new_len=None, ws=None, q_offset=None,
                         M_max: int = 0) -> None:
     """Kpool, Vpool [layers, num_blocks, PAGE, ...]; block_table [batch, max_blocks]; path [batch, M_max], or with
     q_offset [batch + 1] the ragged [total_M] layout of the batch acceptance (then M_max must be given)."""
-    assert Kpool.shape == Vpool.shape and Kpool.is_contiguous() and Vpool.is_contiguous() and Kpool.dim() >= 4
-    layers, num_blocks = Kpool.shape[0], Kpool.shape[1]
-    row_bytes = Kpool[0, 0, 0].numel() * Kpool.element_size()
-    batch, max_blocks = block_table.shape
-    if q_offset is None:
-        total_M, M_max = 0, path.shape[1]
-    else:
-        total_M = path.numel()
-        assert M_max >= 1
-    _check(lib().btv_kv_commit_paged(_ptr(Kpool), _ptr(Vpool), layers, C.c_longlong(Kpool.stride(0) * Kpool.element_size()),
-                                     num_blocks, _ptr(block_table), max_blocks, _ptr(prefix_len), _ptr(path), _ptr(q_offset),
-                                     int(total_M), _ptr(n_acc), batch, int(M_max), row_bytes, _ptr(new_len), _ptr(ws),
-                                     _stream()))
+    (_face or _load_face()).kv_commit_paged(Kpool, Vpool, block_table, prefix_len, path, n_acc, new_len, ws, q_offset, M_max)

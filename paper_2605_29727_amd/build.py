@@ -1,4 +1,4 @@
-"""Builds libbastion_tv.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds libbastion_tv.so for gfx950 with hipcc (cross-compiles without a GPU), and _face.so, its face for torch, with g++."""
 from __future__ import annotations
 
 import os
@@ -8,11 +8,24 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libbastion_tv.so")
+FACE = os.path.join(HERE, "_face.so")
 SOURCES = ["api.hip", "attn.hip", "tree_build.hip", "accept.hip", "stochastic.hip", "kv_commit.hip"]
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 VALU ops on this target.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", INCLUDE, "-I", CSRC]
+
+
+def _face_command() -> list:
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    libs = cpp_extension.library_paths()
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"]]
+            + [x for p in cpp_extension.include_paths() + ["/opt/rocm/include"] for x in ("-isystem", p)]
+            + [os.path.join(CSRC, "face.cpp"), "-o", FACE, "-L", HERE, "-l:libbastion_tv.so", "-Wl,-rpath,$ORIGIN"]
+            + [x for p in libs for x in ("-L", p)] + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
 
 
 def build(verbose: bool = False) -> str:
@@ -33,6 +46,9 @@ def build(verbose: bool = False) -> str:
         if verbose and out.strip():
             print(out)
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    p = subprocess.run(_face_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if p.returncode != 0:
+        raise RuntimeError(f"g++ failed on face.cpp:\n{p.stdout}")
     return LIB
 
 
