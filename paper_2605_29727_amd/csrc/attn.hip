@@ -38,7 +38,6 @@ struct AttnParams {
     const void *Q, *K, *V;
     void *O;
     const int32_t *parent;        // [total_M], indices local to each request
-    const uint32_t *anc;          // [total_M][BTV_ANC_WORDS], fp32 path only
     const int32_t *block_table;   // paged only
     const int32_t *q_offset;      // paged only, [batch+1]
     const int32_t *prefix_len;    // paged only, [batch]
@@ -83,15 +82,6 @@ __device__ __forceinline__ Req load_req(const AttnParams &p, int r)
     q.ok = q.M >= 1 && q.M <= p.M && q.L >= 0 && q.L <= p.L && q.q0 >= 0 &&
            q.q0 + q.M <= p.total_M && (long long)q.L + q.M <= (long long)p.max_blocks * BTV_PAGE;
     return q;
-}
-
-template <bool PAGED>
-__device__ __forceinline__ long long phys_row(const AttnParams &p, int r, int j)
-{
-    if (!PAGED) return j;
-    int b = p.block_table[(long long)r * p.max_blocks + (j >> 4)];
-    b = min(max(b, 0), p.num_blocks - 1);
-    return (long long)b * BTV_PAGE + (j & 15);
 }
 
 // Visibility of keys kb..kb+31 for a node: bit c set iff key kb+c is a prefix row, or a tree
@@ -1856,77 +1846,108 @@ __global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 kernel: one workgroup per (node, query head); threads stride over the visible keys with a
-// private online softmax, then the 256 partial states are merged.  Precision path, not the fast one.
+// fp32 kernel: one workgroup per (node, query head), over the keys in chunks of CH = 256 (D = 64) or 128 (D = 128; 512
+// threads for 256 keys measured the same).
+// Precision path, not the fast one; the shapes it sees are small, so what it costs is its chain of steps, a launch for
+// the ancestor masks among them once.  A key's score takes D / 64 neighbouring threads, 64 channels each; its
+// probability goes to LDS; then a thread owns one channel of 64 of the chunk's keys, whose values are on their way since
+// before the scores (one memory round trip per chunk).  The node's ancestors are walked by one thread over parent[] in
+// LDS while the keys arrive.  144 keys, 16 nodes, one head: 5.3 us; with a private softmax state of all channels per
+// thread, merged by D * 6 shuffles, and the masks' launch it was 12.3.
 // ------------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void tv_attn_f32(AttnParams p)
 {
-    __shared__ float qs[D];
-    __shared__ float red[4][D + 2];
+    constexpr int TPK = D / 64, CH = 256 / TPK, GROUPS = 256 / D, WAVES = 4;   // threads per key, keys per chunk, groups of 64 keys
+    static_assert(GROUPS * 64 == CH, "a thread of each group takes 64 of the chunk's keys");
+    __shared__ __attribute__((aligned(16))) float qs[D], prob[CH], red[GROUPS][D];
+    __shared__ float wmax[WAVES], wsum[WAVES];
+    __shared__ int par[BTV_MAX_NODES];
+    __shared__ unsigned char seen[BTV_MAX_NODES];
+    asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.flag), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.scale));
     const int i = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x, g = hq / p.G;
-    const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K),
-                *V = static_cast<const float *>(p.V);
-    const uint32_t *anc_i = p.anc + (size_t)i * BTV_ANC_WORDS;
-    for (int d = tid; d < D; d += 256) qs[d] = Q[((size_t)i * p.Hq + hq) * D + d];
-    __syncthreads();
-    float m = NEG_BIG, lsum = 0.f, o[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) o[d] = 0.f;
+    const float *Q = static_cast<const float *>(p.Q) + ((size_t)i * p.Hq + hq) * D;
+    const float *K = static_cast<const float *>(p.K) + (size_t)g * D, *V = static_cast<const float *>(p.V) + (size_t)g * D;
+    const size_t pitch = (size_t)p.Hkv * D;
     const int S = p.L + p.M;
-    for (int j = tid; j < S; j += 256) {
-        if (j >= p.L) {
-            int a = j - p.L;
-            if (!((anc_i[a >> 5] >> (a & 31)) & 1u)) continue;
+    const int kk = tid / TPK, part = (tid % TPK) * 64;                         // scores: this thread's key of the chunk, its channels
+    const int d = tid % D, kg = tid / D;                                       // values: its channel, its group of keys
+    if (tid < D) qs[tid] = Q[tid];
+    if (tid < p.M) par[tid] = p.parent[tid];
+    seen[tid] = 0;
+    float m = NEG_BIG, lsum = 0.f, o = 0.f;
+    for (int j0 = 0; j0 < S; j0 += CH) {
+        float4 kv[16];
+        float vv[64];
+        const float *kr = K + (size_t)min(j0 + kk, S - 1) * pitch + part;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) kv[u] = *reinterpret_cast<const float4 *>(kr + 4 * u);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (j0 + kg * 64 + b * 16 < S)                                     // (uniform in a wavefront)
+#pragma unroll
+                for (int u = 0; u < 16; ++u) vv[b * 16 + u] = V[(size_t)min(j0 + kg * 64 + b * 16 + u, S - 1) * pitch + d];
+        __syncthreads();                                                       // (also: the last chunk's probabilities have been read)
+        if (j0 == 0) {                                                         // the node's ancestors, and every parent's check
+            if (tid < p.M && (par[tid] < -1 || par[tid] >= tid)) atomicOr(p.flag, 1u);
+            if (tid == 255)
+                for (int a = i; a >= 0;) {
+                    seen[a] = 1;
+                    const int pa = par[a];
+                    a = pa < -1 || pa >= a ? -1 : pa;                          // an invalid entry ends the walk (flagged above)
+                }
         }
-        const float4 *kr = reinterpret_cast<const float4 *>(K + ((size_t)j * p.Hkv + g) * D);
         float s = 0.f;
 #pragma unroll
-        for (int d4 = 0; d4 < D / 4; ++d4) {
-            float4 kv = kr[d4];
-            s = fmaf(qs[4 * d4 + 0], kv.x, s); s = fmaf(qs[4 * d4 + 1], kv.y, s);
-            s = fmaf(qs[4 * d4 + 2], kv.z, s); s = fmaf(qs[4 * d4 + 3], kv.w, s);
+        for (int u = 0; u < 16; ++u) {
+            const float4 q4 = *reinterpret_cast<const float4 *>(&qs[part + 4 * u]);
+            s = fmaf(q4.x, kv[u].x, s); s = fmaf(q4.y, kv[u].y, s);
+            s = fmaf(q4.z, kv[u].z, s); s = fmaf(q4.w, kv[u].w, s);
         }
+        if (TPK == 2) s += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0xB1, 0xF, 0xF, false));   // the pair's other half
         s *= p.scale;
-        float mn = fmaxf(m, s);
-        float alpha = expf(m - mn), pj = expf(s - mn);
+        __syncthreads();                                                       // seen[]
+        const int j = j0 + kk;
+        const bool visible = j < p.L || (j < S && seen[j - p.L] != 0);
+        float mx = visible ? s : NEG_BIG;
+        mx = row32_max(mx, tid);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+        __syncthreads();
+        float mn = m;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) mn = fmaxf(mn, wmax[k]);
+        const float alpha = expf(m - mn), pj = visible ? expf(s - mn) : 0.f;
         m = mn;
         lsum = lsum * alpha + pj;
-        const float4 *vr = reinterpret_cast<const float4 *>(V + ((size_t)j * p.Hkv + g) * D);
+        if (part == 0) prob[kk] = pj;
+        __syncthreads();
+        o *= alpha;
 #pragma unroll
-        for (int d4 = 0; d4 < D / 4; ++d4) {
-            float4 vv = vr[d4];
-            o[4 * d4 + 0] = o[4 * d4 + 0] * alpha + pj * vv.x;
-            o[4 * d4 + 1] = o[4 * d4 + 1] * alpha + pj * vv.y;
-            o[4 * d4 + 2] = o[4 * d4 + 2] * alpha + pj * vv.z;
-            o[4 * d4 + 3] = o[4 * d4 + 3] * alpha + pj * vv.w;
-        }
-    }
-    // merge: global max, rescale, sum
-    float mw = m;
-    for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
-    if ((tid & 63) == 0) red[tid >> 6][0] = mw;
-    __syncthreads();
-    float mb = fmaxf(fmaxf(red[0][0], red[1][0]), fmaxf(red[2][0], red[3][0]));
-    __syncthreads();
-    float f = expf(m - mb);
-    lsum *= f;
-    for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
+        for (int b = 0; b < 4; ++b)
+            if (j0 + kg * 64 + b * 16 < S)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        float x = o[d] * f;
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-        o[d] = x;
+                for (int u = 0; u < 16; u += 4) {
+                    const float4 pr = *reinterpret_cast<const float4 *>(&prob[kg * 64 + b * 16 + u]);
+                    o = fmaf(pr.x, vv[b * 16 + u], o); o = fmaf(pr.y, vv[b * 16 + u + 1], o);
+                    o = fmaf(pr.z, vv[b * 16 + u + 2], o); o = fmaf(pr.w, vv[b * 16 + u + 3], o);
+                }
     }
-    if ((tid & 63) == 0) {
-        red[tid >> 6][D] = lsum;
-#pragma unroll
-        for (int d = 0; d < D; ++d) red[tid >> 6][d] = o[d];
-    }
+    lsum = row32_sum(lsum, tid);
+    lsum += __shfl_xor(lsum, 32);
+    if ((tid & 63) == 0) wsum[tid >> 6] = lsum;
+    red[kg][d] = o;
     __syncthreads();
-    float den = red[0][D] + red[1][D] + red[2][D] + red[3][D];
-    float *Op = static_cast<float *>(p.O) + ((size_t)i * p.Hq + hq) * D;
-    for (int d = tid; d < D; d += 256) Op[d] = (red[0][d] + red[1][d] + red[2][d] + red[3][d]) / den;
+    if (tid < D) {
+        float x = red[0][tid];
+#pragma unroll
+        for (int k = 1; k < GROUPS; ++k) x += red[k][tid];
+        float den = 0.f;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) den += wsum[k];
+        den *= 1.0f / TPK;                                                     // (every thread of a key counted it)
+        static_cast<float *>(p.O)[((size_t)i * p.Hq + hq) * D + tid] = x / den;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2075,13 +2096,12 @@ PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, i
     return b;
 }
 
-struct WsLayout { size_t anc, plan, ml, opart, total; };
+struct WsLayout { size_t plan, ml, opart, total; };
 
 WsLayout ws_layout(int total_M, int Hq, int D, int nsplit, int batch = 0)
 {
     WsLayout w;
     size_t off = BTV_WS_HEADER;
-    w.anc = off; off += btv_align_up((size_t)total_M * BTV_ANC_WORDS * 4, BTV_WS_ALIGN);
     w.plan = off; off += batch ? btv_align_up((size_t)(batch + 2) * sizeof(long long), BTV_WS_ALIGN) : 0;
     size_t rows = (size_t)total_M * Hq;
     size_t ns = nsplit > 1 ? nsplit : 0;
@@ -2176,7 +2196,6 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     unsigned char *w8 = static_cast<unsigned char *>(ws);
     AttnParams p = {};
     p.Q = Q; p.K = K; p.V = V; p.O = O;
-    p.anc = reinterpret_cast<uint32_t *>(w8 + wl.anc);
     p.ML = reinterpret_cast<float *>(w8 + wl.ml);
     p.Opart = reinterpret_cast<_Float16 *>(w8 + wl.opart);
     p.flag = flag_out ? flag_out : reinterpret_cast<uint32_t *>(w8);
@@ -2186,8 +2205,6 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     set_scales(p, D, scale, k_scale, v_scale);
     p.parent = parent;
     if (dtype == BTV_F32) {
-        rc = btv_launch_anc_mask(parent, nullptr, 1, M, M, const_cast<uint32_t *>(p.anc), p.flag, st);
-        if (rc) return rc;
         if (D == 64) hipLaunchKernelGGL(tv_attn_f32<64>, dim3(M, Hq), dim3(256), 0, st, p);
         else hipLaunchKernelGGL(tv_attn_f32<128>, dim3(M, Hq), dim3(256), 0, st, p);
         BTV_HIP(hipGetLastError());
@@ -2228,7 +2245,6 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     unsigned char *w8 = static_cast<unsigned char *>(ws);
     AttnParams p = {};
     p.Q = Q; p.K = Kpool; p.V = Vpool; p.O = O;
-    p.anc = reinterpret_cast<uint32_t *>(w8 + wl.anc);
     p.ML = reinterpret_cast<float *>(w8 + wl.ml);
     p.Opart = reinterpret_cast<_Float16 *>(w8 + wl.opart);
     p.flag = reinterpret_cast<uint32_t *>(w8);

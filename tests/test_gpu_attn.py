@@ -40,6 +40,16 @@ def test_fp32_shapes_and_trees(G, oracle, kind, M, L, Hq, Hkv, D):
     assert np.abs(out - ref).max() <= TOL_F32
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("M,L", [(1, 127), (1, 255), (2, 126), (3, 254), (17, 240), (256, 0), (200, 313)])
+def test_fp32_around_the_chunks_of_keys(G, oracle, M, L, D):
+    for kind in ("random", "star", "chain"):
+        parent = synth.tree_parents(8, M, kind)
+        t = synth.qkv(32, M, L, 4, 2, D, "fp32", tag=kind)
+        out = G.run_verify_attn(t, parent, L, "fp32")
+        assert np.abs(out - oracle.tree_attn(t["Qf"], t["Kf"], t["Vf"], parent, L)).max() <= TOL_F32
+
+
 # (M, L, Hq, Hkv, D): spans all three kernel configurations (G*M <= 64, <= 128, > 128 with several row blocks),
 # ragged tails (M, L not multiples of 32 / 64), L = 0, L smaller than a tile, and a prefix/tree boundary inside a tile.
 BF16_SHAPES = [
