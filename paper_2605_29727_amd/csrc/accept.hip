@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 
 namespace {
 
@@ -183,6 +184,32 @@ constexpr int OL_WAVES = 8;      // wavefronts per workgroup of the one-launch k
 static_assert(OL_WAVES * 64 > BTV_MAX_NODES, "the collector gives every logit row a thread");
 constexpr unsigned long long OL_NO_KEY = 1ull;
 constexpr long long OL_WAIT_TICKS = 100000000ll;    // collector's limit: one second of the 100 MHz wall clock
+
+// The walk, by one wavefront: t[r] = argmax of row r (in LDS), lane l holds nodes l, 64 + l, ... (par INT_MIN: none).
+__device__ __forceinline__ void walk_tree(const int *t, const int (&par)[WALK_ROWS], const int (&tok)[WALK_ROWS], int M, int lane, int32_t *path,
+                                          int32_t *n_acc, int32_t *bonus)
+{
+    bool ok[WALK_ROWS];
+#pragma unroll
+    for (int r = 0; r < WALK_ROWS; ++r) {
+        const int c = r * 64 + lane;
+        ok[r] = c < M && par[r] >= -1 && par[r] < M && tok[r] == t[par[r] + 1];
+    }
+    int cur = -1, n = 0;
+    while (n < M) {
+        int nx = -1;
+#pragma unroll
+        for (int r = WALK_ROWS - 1; r >= 0; --r) {
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(ok[r] && par[r] == cur);
+            if (m != 0ull) nx = r * 64 + __builtin_ctzll(m);
+        }
+        if (nx < 0) break;
+        if (lane == 0) path[n] = nx;
+        cur = nx;
+        ++n;
+    }
+    if (lane == 0) { *n_acc = n; *bonus = t[cur + 1]; }
+}
 
 // Rows that OL_WAVES consecutive units can touch: the slots a workgroup owns.
 __host__ __device__ inline int ol_slots_per_wg(int chunks)
@@ -389,40 +416,22 @@ __global__ __launch_bounds__(OL_WAVES * 64) void accept_greedy_one_launch(
     }
     __syncthreads();
     if (tid >= 64) return;
-    bool ok[WALK_ROWS];
-#pragma unroll
-    for (int r = 0; r < WALK_ROWS; ++r) {
-        const int c = r * 64 + tid;
-        ok[r] = c < M && par[r] >= -1 && par[r] < M && tok[r] == t[par[r] + 1];
-    }
-    int cur = -1, n = 0;
-    while (n < M) {
-        int nx = -1;
-#pragma unroll
-        for (int r = WALK_ROWS - 1; r >= 0; --r) {
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(ok[r] && par[r] == cur);
-            if (m != 0ull) nx = r * 64 + __builtin_ctzll(m);
-        }
-        if (nx < 0) break;
-        if (tid == 0) path[n] = nx;
-        cur = nx;
-        ++n;
-    }
-    if (tid == 0) { *n_acc = n; *bonus = t[cur + 1]; }
+    walk_tree(t, par, tok, M, lane, path, n_acc, bonus);
 }
 
 // One workgroup per request: finish the argmax of every row, then walk the tree.  With q_offset (a batch),
 // request r owns nodes q_offset[r] .. q_offset[r+1] - 1 and logit rows q_offset[r] + r .. q_offset[r+1] + r (its
 // root row first); without, there is one request of M nodes.
-__global__ __launch_bounds__(256) void greedy_walk(const Best *part, int chunks, const int32_t *parent,
+// A row's partials are read by as many lanes as there are of them (64 at most), eight or four reads in flight per lane; what
+// is left is latency (a wavefront per request that walked with workgroup barriers after a thread per row: 5.4 us, now 3.6 at 65 rows).
+constexpr int GW_WAVES = 16;
+__global__ __launch_bounds__(GW_WAVES * 64) void greedy_walk(const Best *part, int chunks, const int32_t *parent,
                                                    const int32_t *token, int M, int32_t *path, int32_t *n_acc,
                                                    int32_t *bonus, int32_t *argmax_out, const int32_t *q_offset,
                                                    int total_M, uint32_t *flag)
 {
     __shared__ int t[BTV_MAX_NODES + 1];
-    __shared__ int par[BTV_MAX_NODES], tok[BTV_MAX_NODES];
-    __shared__ int next;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (q_offset) {
         const int rq = blockIdx.x, o0 = q_offset[rq], m = q_offset[rq + 1] - o0;
         n_acc += rq; bonus += rq;
@@ -436,29 +445,57 @@ __global__ __launch_bounds__(256) void greedy_walk(const Best *part, int chunks,
         parent += o0; token += o0; path += o0;
         if (argmax_out) argmax_out += o0 + rq;
     }
-    for (int r = tid; r <= M; r += 256) {
-        Best b = part[(size_t)r * chunks];
-        for (int c = 1; c < chunks; ++c) best_take(b, part[(size_t)r * chunks + c].v, part[(size_t)r * chunks + c].i);
-        t[r] = b.i == INT_MAX ? 0 : b.i;
-        if (argmax_out) argmax_out[r] = t[r];
+    int par[WALK_ROWS], tok[WALK_ROWS];
+#pragma unroll
+    for (int r = 0; r < WALK_ROWS; ++r) {
+        const int c = r * 64 + lane;
+        const bool mine = wave == 0 && c < M;
+        par[r] = mine ? parent[c] : INT_MIN;
+        tok[r] = mine ? token[c] : -1;
     }
-    for (int c = tid; c < M; c += 256) { par[c] = parent[c]; tok[c] = token[c]; }
+    const int lg = chunks >= 64 ? 6 : chunks <= 1 ? 0 : 32 - __builtin_clz(chunks - 1);
+    const int per = 1 << lg, sub = lane & (per - 1), rsub = lane >> lg, step = GW_WAVES * (64 >> lg);    // lanes per row; rows per pass
+    auto finish = [&](Best b, int row) {
+        for (int off = 1; off < per; off <<= 1) {
+            const float ov = __shfl_xor(b.v, off);
+            const int oi = __shfl_xor(b.i, off);
+            best_take(b, ov, oi);
+        }
+        if (sub == 0 && row <= M) {
+            const int a = b.i == INT_MAX ? 0 : b.i;
+            t[row] = a;
+            if (argmax_out) argmax_out[row] = a;
+        }
+    };
+    const int first = wave * (64 >> lg);
+    if (chunks <= 64) {
+        for (int r0 = first; r0 <= M; r0 += 4 * step) {        // four passes' reads in flight
+            Best b[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[k] = part[(size_t)min(r0 + k * step + rsub, M) * chunks + min(sub, chunks - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                Best x = { -INFINITY, INT_MAX };
+                best_take(x, b[k].v, b[k].i);
+                if (r0 + k * step <= M) finish(x, r0 + k * step + rsub);
+            }
+        }
+    } else {
+        for (int r0 = first; r0 <= M; r0 += step) {            // (one row per wavefront)
+            const Best *row = part + (size_t)r0 * chunks;
+            Best x = { -INFINITY, INT_MAX };
+            for (int c0 = 0; c0 < chunks; c0 += 8 * 64) {
+                Best b[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) b[u] = row[min(c0 + u * 64 + lane, chunks - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) best_take(x, b[u].v, b[u].i);
+            }
+            finish(x, r0);
+        }
+    }
     __syncthreads();
-    int cur = -1, n = 0;
-    for (;;) {
-        if (tid == 0) next = INT_MAX;
-        __syncthreads();
-        const int want = t[cur + 1];
-        for (int c = tid; c < M; c += 256)
-            if (par[c] == cur && tok[c] == want) atomicMin(&next, c);
-        __syncthreads();
-        const int nx = next;
-        __syncthreads();
-        if (nx == INT_MAX || n >= M) break;
-        if (tid == 0) path[n] = nx;
-        cur = nx; ++n;
-    }
-    if (tid == 0) { *n_acc = n; *bonus = t[cur + 1]; }
+    if (wave == 0) walk_tree(t, par, tok, M, lane, path, n_acc, bonus);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -480,19 +517,23 @@ typedef __bf16 lm_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float lm_f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int lm_u32x4 __attribute__((ext_vector_type(4)));
 
-template <int RT, int WAVES, int KB, int TV>
+// VW waves side by side over the vocabulary times KW over the contraction (each takes every KW-th block of it, with a
+// slab of H of its own; the sums meet in LDS at the end).
+template <int RT, int VW, int KW, int KB, int TV>
 struct LmShape {
-    static constexpr int THREADS = WAVES * 64, ROWS = RT * 32;
+    static constexpr int WAVES = VW * KW, THREADS = WAVES * 64, ROWS = RT * 32;
+    static constexpr int GT = VW * 64;                    // threads that share a slab
     static constexpr int VROWS = TV * 32;                 // vocabulary rows of a wave
     static constexpr int RB = KB * 2;                     // bytes of a tile row
     static constexpr int CPR = RB / 16;                   // 16-byte chunks per row
     static constexpr int WTILE = VROWS * RB, SLAB = ROWS * RB;
-    static constexpr int LDS_BYTES = WAVES * WTILE + 2 * SLAB;
+    static constexpr int LDS_BYTES = WAVES * WTILE + KW * 2 * SLAB;
     static constexpr int WLD = VROWS * CPR / 64;          // load instructions per wave and block for W
-    static constexpr int HLD = (ROWS * CPR + THREADS - 1) / THREADS;   // chunks of the H slab per thread and block
-    static constexpr bool HEVEN = ROWS * CPR % THREADS == 0;
+    static constexpr int HLD = (ROWS * CPR + GT - 1) / GT;             // chunks of the H slab per thread and block
+    static constexpr bool HEVEN = ROWS * CPR % GT == 0;
+    static constexpr int SUMS = (KW - 1) * VW * TV * RT * 16 * 64 * 4; // accumulators handed over at the end
     static_assert(CPR == 8 || CPR == 16, "KB is 64 or 128");
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+    static_assert(LDS_BYTES <= 160 * 1024 && SUMS <= LDS_BYTES, "LDS of a CU");
     // byte offset of 16-byte chunk `col` of tile row `row`: 16 lanes reading one chunk index of 16 consecutive
     // rows must land in 16 different 16-byte bank groups of the 256-byte bank line
     __device__ static constexpr int at(int row, int col)
@@ -577,25 +618,31 @@ __device__ __forceinline__ void lm_multiply_plain(const unsigned char *wt, const
     }
 }
 
-template <int RT, int WAVES, int KB, int TV, bool RAW>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_argmax(
-    const uint16_t *__restrict__ H, const uint16_t *__restrict__ W, int R, int h, int V, Best *__restrict__ part)
+template <int RT, int VW, int KW, int KB, int TV, bool RAW>
+__global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_argmax(
+    const uint16_t *__restrict__ H, const uint16_t *__restrict__ W, int R, int h, int V, int chunks, int groups, Best *__restrict__ part)
 {
-    using S = LmShape<RT, WAVES, KB, TV>;
+    using S = LmShape<RT, VW, KW, KB, TV>;
     extern __shared__ __align__(16) unsigned char lm_lds[];
+    // Workgroup = a chunk of the vocabulary times a group of rows; the groups of one chunk stream the same weights and
+    // get ids that are congruent mod 8, i.e. one XCD's L2.
+    const int group = (int)(blockIdx.x >> 3) % groups, chunk = (int)(blockIdx.x >> 3) / groups * 8 + (int)(blockIdx.x & 7);
+    if (chunk >= chunks) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r32 = lane & 31, half = lane >> 5;
-    const int vwg = blockIdx.x * WAVES * S::VROWS, v0 = vwg + wave * S::VROWS;
+    const int vw = wave % VW, kw = __builtin_amdgcn_readfirstlane(wave / VW), gtid = tid - kw * S::GT, r0 = group * S::ROWS;
+    const int vwg = chunk * VW * S::VROWS, v0 = vwg + vw * S::VROWS;
     unsigned char *wtile = lm_lds + wave * S::WTILE;
-    unsigned char *slab = lm_lds + WAVES * S::WTILE;
-    const int nkb = h / KB;
+    unsigned char *slab = lm_lds + S::WAVES * S::WTILE + kw * 2 * S::SLAB;
+    const int nkb = h / KB, rounds = (nkb + KW - 1) / KW;
+    const int own = KW == 1 ? nkb : (nkb - kw + KW - 1) / KW;      // this wave's blocks of the contraction: kw, kw + KW, ... (may be none)
 
     // Addresses are a wave-uniform base (block of the contraction, first row of the workgroup) plus a 32-bit
     // per-lane offset that never changes.
     // W: instruction i moves rows i*(64/CPR) .. of the wave's tile, CPR lanes per row
     constexpr int RPI = 64 / S::CPR;                       // rows per load instruction
     const int wcol = lane % S::CPR, wrow0 = lane / S::CPR;
-    const unsigned char *wbase = reinterpret_cast<const unsigned char *>(W) + (size_t)vwg * h * 2;
-    const unsigned char *hbase = reinterpret_cast<const unsigned char *>(H);
+    const unsigned char *wbase = reinterpret_cast<const unsigned char *>(W) + (size_t)vwg * h * 2 + (own ? kw : 0) * (KB * 2);
+    const unsigned char *hbase = reinterpret_cast<const unsigned char *>(H) + (own ? kw : 0) * (KB * 2);
     uint32_t woff[S::WLD], hoff[S::HLD];
     // LDS destinations: rows 16 apart share the swizzle, so only the first 16 / RPI of a tile's store addresses
     // differ by more than a constant
@@ -610,13 +657,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     // H: chunk c of the slab -> row c / CPR, column c % CPR
 #pragma unroll
     for (int i = 0; i < S::HLD; ++i) {
-        const int c = tid + i * S::THREADS, row = c / S::CPR, col = c % S::CPR;
-        hoff[i] = (uint32_t)min(row, R - 1) * (uint32_t)(h * 2) + col * 16;
+        const int c = gtid + i * S::GT, row = c / S::CPR, col = c % S::CPR;
+        hoff[i] = (uint32_t)min(r0 + row, R - 1) * (uint32_t)(h * 2) + col * 16;
     }
-    // a thread's chunks are THREADS / CPR rows apart, a multiple of 16: same swizzle, constant distance
-    constexpr int HSTEP = S::THREADS / S::CPR;
-    static_assert(HSTEP % 16 == 0, "H chunks of a thread must share the swizzle");
-    const int hrow0 = tid / S::CPR, hdst0 = S::at(hrow0, tid % S::CPR);
+    // a thread's chunks are GT / CPR rows apart; where that is no multiple of 16 (whose swizzle is the same), each has its place
+    constexpr int HSTEP = S::GT / S::CPR;
+    constexpr bool HEVENLY = HSTEP % 16 == 0;
+    const int hrow0 = gtid / S::CPR, hcol0 = gtid % S::CPR, hdst0 = S::at(hrow0, hcol0);
     // operand reads: step j of a block uses chunk 2j + half of row r32 (same chunk on both sides), which sits at
     // at(r32, half) ^ (j << 5): the swizzle is an XOR and 2j + half = 2j ^ half
     const uint32_t ob = (uint32_t)S::at(r32, half);
@@ -631,18 +678,19 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 
     // Workgroups start at different blocks of the contraction and wrap round: rows of W are a multiple of 4 KB
     // apart, so workgroups marching in step would all hit the same few memory channels.
-    int curw = (blockIdx.x * 5) % nkb, curh = curw;
+    const int wrap = own ? own : 1;
+    int curw = (chunk * 5) % wrap, curh = curw;
     // (staging arrays are of a native vector type: arrays of the uint4 struct were left in scratch memory)
 #define LM_FETCH_W(w)                                                                                      \
     {                                                                                                      \
-        const unsigned char *b_ = wbase + (size_t)curw * (KB * 2);                                         \
-        curw = curw + 1 == nkb ? 0 : curw + 1;                                                             \
+        const unsigned char *b_ = wbase + (size_t)curw * (KW * KB * 2);                                         \
+        curw = curw + 1 == wrap ? 0 : curw + 1;                                                             \
         _Pragma("unroll") for (int i = 0; i < S::WLD; ++i) w[i] = *reinterpret_cast<const lm_u32x4 *>(b_ + woff[i]); \
     }
 #define LM_FETCH_H(x)                                                                                      \
     {                                                                                                      \
-        const unsigned char *b_ = hbase + (size_t)curh * (KB * 2);                                         \
-        curh = curh + 1 == nkb ? 0 : curh + 1;                                                             \
+        const unsigned char *b_ = hbase + (size_t)curh * (KW * KB * 2);                                         \
+        curh = curh + 1 == wrap ? 0 : curh + 1;                                                             \
         _Pragma("unroll") for (int i = 0; i < S::HLD; ++i) x[i] = *reinterpret_cast<const lm_u32x4 *>(b_ + hoff[i]); \
     }
 #define LM_STORE_W(w)                                                                                   \
@@ -654,10 +702,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     {                                                                                                   \
         _Pragma("unroll") for (int i = 0; i < S::HLD; ++i)                                              \
             if (S::HEVEN || hrow0 + i * HSTEP < S::ROWS)   /* past the slab: fetched, never stored */   \
-                *reinterpret_cast<lm_u32x4 *>((dst) + hdst0 + i * HSTEP * S::RB) = x[i];                \
+                *reinterpret_cast<lm_u32x4 *>((dst) + (HEVENLY ? hdst0 + i * HSTEP * S::RB : S::at(hrow0 + i * HSTEP, hcol0))) = x[i]; \
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) void *)lm_lds);
-    const uint32_t wt_addr = lds0 + wave * S::WTILE, slab_addr = lds0 + WAVES * S::WTILE;
+    const uint32_t wt_addr = lds0 + wave * S::WTILE, slab_addr = lds0 + S::WAVES * S::WTILE + kw * 2 * S::SLAB;
 #define LM_MULTIPLY(sl)                                                                                      \
     {                                                                                                        \
         if constexpr (RAW) lm_multiply<RT, TV, KB, S::RB>(wt_addr, slab_addr + (sl) * S::SLAB, ob, acc);     \
@@ -674,23 +722,23 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     LM_STORE_H(x, slab)
     LM_STORE_W(w0)
     __syncthreads();
-    for (int kb = 0; kb + 1 < nkb; kb += 2) {
+    for (int kb = 0; kb + 1 < rounds; kb += 2) {
         // even round: slab 0 and the W tile hold block kb, w1 block kb + 1
         LM_FETCH_H(x)                                   // block kb + 1
         LM_FETCH_W(w0)                                  // block kb + 2
-        LM_MULTIPLY(0)
+        if (KW == 1 || kb < own) LM_MULTIPLY(0)
         LM_STORE_H(x, slab + S::SLAB)                   // slab 1 is idle in this round
         LM_STORE_W(w1)                                  // own W tile: consumed by the multiply above
         __syncthreads();
         LM_FETCH_H(x)                                   // block kb + 2
         LM_FETCH_W(w1)                                  // block kb + 3
-        LM_MULTIPLY(1)
+        if (KW == 1 || kb + 1 < own) LM_MULTIPLY(1)
         LM_STORE_H(x, slab)
         LM_STORE_W(w0)
         __syncthreads();
     }
-    if (nkb & 1) {                                      // the last block of an odd count sits in slab 0
-        LM_MULTIPLY(0)
+    if (rounds & 1) {                                   // the last block of an odd count sits in slab 0
+        if (KW == 1 || rounds - 1 < own) LM_MULTIPLY(0)
         __syncthreads();
     }
 #undef LM_MULTIPLY
@@ -700,8 +748,33 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 #undef LM_STORE_H
 
     // per-lane scan over the 16 vocabulary rows of a tile that it holds (ascending), other half, then the waves
-    Best *wb = reinterpret_cast<Best *>(lm_lds);            // [WAVES][ROWS]
-    static_assert(S::LDS_BYTES >= WAVES * S::ROWS * (int)sizeof(Best), "exchange area must fit");
+    if constexpr (KW > 1) {                                 // the sums of the other parts of the contraction
+        float *ex = reinterpret_cast<float *>(lm_lds) + vw * (TV * RT * 16 * 64) + lane;
+        constexpr int PLANE = VW * TV * RT * 16 * 64;
+        if (kw > 0) {
+#pragma unroll
+            for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) ex[(kw - 1) * PLANE + ((tv * RT + rt) * 16 + e) * 64] = acc[tv][rt][e];
+        }
+        __syncthreads();
+        if (kw == 0) {
+#pragma unroll
+            for (int k = 0; k < KW - 1; ++k)
+#pragma unroll
+                for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[tv][rt][e] += ex[k * PLANE + ((tv * RT + rt) * 16 + e) * 64];
+        }
+        __syncthreads();
+    }
+    Best *wb = reinterpret_cast<Best *>(lm_lds);            // [VW][ROWS]
+    static_assert(S::LDS_BYTES >= VW * S::ROWS * (int)sizeof(Best), "exchange area must fit");
+    if (KW == 1 || kw == 0)
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         Best b = { -INFINITY, INT_MAX };
@@ -715,82 +788,130 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2
         const float ov = __shfl_xor(b.v, 32);
         const int oi = __shfl_xor(b.i, 32);
         best_take(b, ov, oi);
-        if (half == 0) wb[wave * S::ROWS + rt * 32 + r32] = b;
+        if (half == 0) wb[vw * S::ROWS + rt * 32 + r32] = b;
     }
     __syncthreads();
-    for (int row = tid; row < R; row += S::THREADS) {
+    for (int row = tid; row < min(R - r0, S::ROWS); row += S::THREADS) {
         Best b = wb[row];
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) best_take(b, wb[w * S::ROWS + row].v, wb[w * S::ROWS + row].i);
-        part[(size_t)row * gridDim.x + blockIdx.x] = b;
+        for (int w = 1; w < VW; ++w) best_take(b, wb[w * S::ROWS + row].v, wb[w * S::ROWS + row].i);
+        part[(size_t)(r0 + row) * chunks + chunk] = b;
     }
 }
 
-// grid = rows: best of a row's per-workgroup partials -> out[row]
-__global__ __launch_bounds__(256) void argmax_merge(const Best *part, int chunks, Best *out)
+// grid = rows: best of a row's per-workgroup partials -> out[row]; the workgroup that is done last walks the tree (a launch of
+// its own for that: 2 us more).  The rows' results cross the XCDs as relaxed device-scope atomics, which go through to
+// memory; a workgroup counts itself in when its own has arrived.  done: 0 between calls.
+__global__ __launch_bounds__(256) void argmax_merge_walk(const Best *part, int chunks, unsigned long long *out, uint32_t *done, const int32_t *parent,
+                                                         const int32_t *token, int M, int32_t *path, int32_t *n_acc, int32_t *bonus,
+                                                         int32_t *argmax_out)
 {
     __shared__ Best wb[4];
-    const int tid = threadIdx.x, row = blockIdx.x;
+    __shared__ int t[BTV_MAX_NODES + 1];
+    __shared__ int last;
+    const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
+    int par[WALK_ROWS], tok[WALK_ROWS];                        // (asked for now, by every workgroup; used by the last)
+#pragma unroll
+    for (int r = 0; r < WALK_ROWS; ++r) {
+        const int c = r * 64 + lane;
+        const bool mine = tid < 64 && c < M;
+        par[r] = mine ? parent[c] : INT_MIN;
+        tok[r] = mine ? token[c] : -1;
+    }
     Best b = { -INFINITY, INT_MAX };
     for (int c = tid; c < chunks; c += 256) best_take(b, part[(size_t)row * chunks + c].v, part[(size_t)row * chunks + c].i);
     b = best_wave(b);
-    if ((tid & 63) == 0) wb[tid >> 6] = b;
+    if (lane == 0) wb[tid >> 6] = b;
     __syncthreads();
     if (tid == 0) {
         Best r = wb[0];
         best_take(r, wb[1].v, wb[1].i); best_take(r, wb[2].v, wb[2].i); best_take(r, wb[3].v, wb[3].i);
-        out[row] = r;
+        const int a = r.i == INT_MAX ? 0 : r.i;
+        if (argmax_out) argmax_out[row] = a;
+        __hip_atomic_store(out + row, (unsigned long long)(uint32_t)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    __syncthreads();
+    if (!last) return;
+    for (int r = tid; r <= M; r += 256) t[r] = (int)(uint32_t)__hip_atomic_load(out + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (tid < 64) walk_tree(t, par, tok, M, lane, path, n_acc, bonus);
 }
 
-// Shape of the LM-head kernel for R rows of H: row tiles, waves per workgroup, contraction block, vocabulary
-// tiles per wave, raw or compiler-scheduled operand reads.
-struct LmPlan { int rt, waves, kb, tv, raw; };
+constexpr int LM_ONE_WG = 3000;
+constexpr int LM_DONE_WORD = 20;            // of the workspace's header: rows that are merged (0 between calls)
 
-inline LmPlan lm_plan(int R)
+// Shape of the LM-head kernel for R rows of H: row tiles per workgroup (R may take several groups of them), waves over the
+// vocabulary and over the contraction, contraction block, raw or compiler-scheduled operand reads (pipelined raw reads pay only
+// while a second set of operands fits beside the accumulators).
+struct LmPlan { int rt, vw, kw, kb, raw; };
+
+// The shape with the least estimated time: what a workgroup's blocks of the contraction take (alone on a CU, and where the
+// chip is full), times the rounds, no less than the stream of W, some of the smaller of the two on top, and the merge of
+// what the workgroups leave.  Fitted to 84 problems (h = 1024 to 4096, V = 8k to 128k, 2 to 256 rows) times all shapes: half a
+// percent behind the best shape on average.  The rule by the number of rows alone that it replaces (all rows in one workgroup, 4 or
+// 8 waves side by side) was 34 % behind: it left most CUs without a workgroup at small vocabularies (196 rows, h = 4096,
+// V = 8000: 32 workgroups, 138 us; 42 in four groups of rows) and streamed with few waves (h = 4096, V = 16k, one row: 40 us, 32
+// with two waves over the contraction).
+inline LmPlan lm_plan(int R, int h, int V)
 {
-    // Measured at h = 4096, V = 128256: every shape up to 160 rows runs within 10 % of the 1 or 2 row-tile case,
-    // which is bound by the stream of W; pipelined raw reads pay only while a second set of operands fits beside
-    // the accumulators, and two vocabulary tiles per wave bought nothing.
-    const int rt = (R + 31) / 32;
-    if (rt <= 2) return { rt, 4, 128, 1, 1 };
-    if (rt <= 6) return { rt, 8, 128, 1, 0 };
-    return { rt, 8, 64, 1, 0 };
+    static constexpr struct { LmPlan p; float alone, full; int per_cu; } SHAPES[] = {      // us per 128 of the contraction
+        { { 1, 4, 1, 128, 1 }, 0.622f, 1.045f, 2 }, { { 1, 2, 2, 128, 1 }, 0.670f, 1.237f, 2 },
+        { { 2, 4, 1, 128, 1 }, 0.836f, 1.338f, 2 }, { { 2, 2, 2, 128, 1 }, 1.053f, 1.186f, 1 },
+        { { 3, 4, 1, 128, 0 }, 0.993f, 1.850f, 2 }, { { 3, 8, 1, 128, 0 }, 1.628f, 1.802f, 1 },
+        { { 4, 4, 1, 128, 0 }, 1.274f, 1.361f, 1 }, { { 4, 8, 1, 128, 0 }, 1.946f, 2.107f, 1 },
+        { { 5, 8, 1, 128, 0 }, 2.185f, 2.354f, 1 }, { { 6, 8, 1, 128, 0 }, 2.579f, 2.787f, 1 },
+        { { 7, 8, 1, 64, 0 }, 3.420f, 3.716f, 1 }, { { 8, 8, 1, 64, 0 }, 3.500f, 3.792f, 1 },
+        { { 9, 8, 1, 64, 0 }, 3.900f, 4.250f, 1 },
+    };
+    const int tiles = (R + 31) / 32;
+    const float mem = 2.0f * V * h / 7.0e6f;
+    LmPlan best = SHAPES[0].p;
+    float best_t = 0.f;
+    for (const auto &s : SHAPES) {
+        if (s.p.rt > tiles) continue;
+        const int chunks = (V + s.p.vw * 32 - 1) / (s.p.vw * 32), groups = (tiles + s.p.rt - 1) / s.p.rt, wgs = (chunks + 7) / 8 * 8 * groups;
+        const float blocks = (float)((h / s.p.kb + s.p.kw - 1) / s.p.kw * s.p.kb) / 128.f, fill = wgs / (256.f * s.per_cu);
+        const float rounds = 0.45f * std::ceil(fill) + 0.55f * std::max(1.f, fill);
+        const float comp = rounds * blocks * (wgs <= 256 ? s.alone : s.full);
+        const float t = std::max(comp, mem) + 0.45f * std::min(comp, mem) + 1.1e-4f * chunks * R;
+        if (!best_t || t < best_t) { best = s.p; best_t = t; }
+    }
+    return best;
 }
 
-inline int lm_chunks(int R, int V)
-{
-    const LmPlan p = lm_plan(R);
-    return (V + p.waves * p.tv * 32 - 1) / (p.waves * p.tv * 32);
-}
+inline int lm_chunks(const LmPlan &p, int V) { return (V + p.vw * 32 - 1) / (p.vw * 32); }
 
-template <int RT, int WAVES, int KB, int TV, bool RAW>
+template <int RT, int VW, int KW, int KB, bool RAW>
 int lm_head_launch(const uint16_t *H, const uint16_t *W, int R, int h, int V, Best *part, hipStream_t st)
 {
-    using S = LmShape<RT, WAVES, KB, TV>;
+    using S = LmShape<RT, VW, KW, KB, 1>;
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
-    auto kern = lm_head_argmax<RT, WAVES, KB, TV, RAW>;
+    auto kern = lm_head_argmax<RT, VW, KW, KB, 1, RAW>;
     if (!configured.load(std::memory_order_acquire)) {
         BTV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     S::LDS_BYTES));
         configured.store(true, std::memory_order_release);
     }
-    const int chunks = (V + WAVES * S::VROWS - 1) / (WAVES * S::VROWS);
-    hipLaunchKernelGGL(kern, dim3(chunks), dim3(WAVES * 64), S::LDS_BYTES, st, H, W, R, h, V, part);
+    const int chunks = (V + VW * S::VROWS - 1) / (VW * S::VROWS), groups = (R + S::ROWS - 1) / S::ROWS;
+    hipLaunchKernelGGL(kern, dim3((chunks + 7) / 8 * 8 * groups), dim3(S::THREADS), S::LDS_BYTES, st, H, W, R, h, V, chunks, groups, part);
     BTV_HIP(hipGetLastError());
     return BTV_OK;
 }
 
-int lm_head_dispatch(const uint16_t *H, const uint16_t *W, int R, int h, int V, Best *part, hipStream_t st)
+int lm_head_dispatch(const LmPlan &p, const uint16_t *H, const uint16_t *W, int R, int h, int V, Best *part, hipStream_t st)
 {
-    const LmPlan p = lm_plan(R);
-#define LM_CASE(rt_, w_, kb_, tv_, raw_)                                                              \
-    if (p.rt == rt_ && p.waves == w_ && p.kb == kb_ && p.tv == tv_ && p.raw == raw_)                  \
-        return lm_head_launch<rt_, w_, kb_, tv_, raw_ != 0>(H, W, R, h, V, part, st);
-    LM_CASE(1, 4, 128, 1, 1) LM_CASE(2, 4, 128, 1, 1)
-    LM_CASE(3, 8, 128, 1, 0)
-    LM_CASE(4, 8, 128, 1, 0) LM_CASE(5, 8, 128, 1, 0) LM_CASE(6, 8, 128, 1, 0)
-    LM_CASE(7, 8, 64, 1, 0) LM_CASE(8, 8, 64, 1, 0) LM_CASE(9, 8, 64, 1, 0)
+#define LM_CASE(rt_, vw_, kw_, kb_, raw_)                                                             \
+    if (p.rt == rt_ && p.vw == vw_ && p.kw == kw_ && p.kb == kb_ && p.raw == raw_)                    \
+        return lm_head_launch<rt_, vw_, kw_, kb_, raw_ != 0>(H, W, R, h, V, part, st);
+    LM_CASE(1, 4, 1, 128, 1) LM_CASE(2, 4, 1, 128, 1)
+    LM_CASE(1, 2, 2, 128, 1) LM_CASE(2, 2, 2, 128, 1)
+    LM_CASE(3, 4, 1, 128, 0) LM_CASE(4, 4, 1, 128, 0)
+    LM_CASE(3, 8, 1, 128, 0)
+    LM_CASE(4, 8, 1, 128, 0) LM_CASE(5, 8, 1, 128, 0) LM_CASE(6, 8, 1, 128, 0)
+    LM_CASE(7, 8, 1, 64, 0) LM_CASE(8, 8, 1, 64, 0) LM_CASE(9, 8, 1, 64, 0)
 #undef LM_CASE
     return btv_fail(BTV_EINVAL, "no LM-head kernel for %d rows", R);
 }
@@ -858,7 +979,7 @@ size_t btv_tree_accept_lm_head_workspace(int M, int V)
 {
     if (M < 1 || M > BTV_MAX_NODES || V < 1) return 0;
     const size_t rows = (size_t)M + 1;
-    return BTV_WS_HEADER + btv_align_up(rows * lm_chunks(M + 1, V) * sizeof(Best), BTV_WS_ALIGN) +
+    return BTV_WS_HEADER + btv_align_up(rows * ((V + 31) / 32) * sizeof(Best), BTV_WS_ALIGN) +
            btv_align_up(rows * sizeof(Best), BTV_WS_ALIGN);
 }
 
@@ -875,17 +996,22 @@ int btv_tree_accept_greedy_lm_head(const void *hidden, const void *W, int h, con
     int rc = btv_check_ws(ws, ws_bytes, btv_tree_accept_lm_head_workspace(M, V));
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int R = M + 1, chunks = lm_chunks(R, V);
+    const int R = M + 1;
+    const LmPlan pl = lm_plan(R, h, V);
+    const int chunks = lm_chunks(pl, V);
     Best *part = reinterpret_cast<Best *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
-    Best *best = reinterpret_cast<Best *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER +
-                                          btv_align_up((size_t)R * chunks * sizeof(Best), BTV_WS_ALIGN));
+    unsigned long long *best = reinterpret_cast<unsigned long long *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER +
+                                          btv_align_up((size_t)R * ((V + 31) / 32) * sizeof(Best), BTV_WS_ALIGN));
     const uint16_t *Hp = static_cast<const uint16_t *>(hidden), *Wp = static_cast<const uint16_t *>(W);
-    rc = lm_head_dispatch(Hp, Wp, R, h, V, part, st);
+    rc = lm_head_dispatch(pl, Hp, Wp, R, h, V, part, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(argmax_merge, dim3(R), dim3(256), 0, st, part, chunks, best);
-    BTV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(greedy_walk, dim3(1), dim3(256), 0, st, best, 1, parent, token, M, path, n_acc, bonus, argmax_out,
-                       static_cast<const int32_t *>(nullptr), 0, static_cast<uint32_t *>(nullptr));
+    // one workgroup reads few partials itself; many take one per row (65000 took one workgroup 16 us)
+    if ((long long)R * chunks > LM_ONE_WG)
+        hipLaunchKernelGGL(argmax_merge_walk, dim3(R), dim3(256), 0, st, part, chunks, best, static_cast<uint32_t *>(ws) + LM_DONE_WORD, parent, token, M,
+                           path, n_acc, bonus, argmax_out);
+    else
+        hipLaunchKernelGGL(greedy_walk, dim3(1), dim3(GW_WAVES * 64), 0, st, part, chunks, parent, token, M, path, n_acc, bonus, argmax_out,
+                           static_cast<const int32_t *>(nullptr), 0, static_cast<uint32_t *>(nullptr));
     BTV_HIP(hipGetLastError());
     return BTV_OK;
 }
@@ -914,7 +1040,7 @@ int btv_tree_accept_greedy_batch(const void *logits, int dtype, const int32_t *p
     if (dtype == BTV_BF16) hipLaunchKernelGGL(argmax_chunks<true>, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
     else hipLaunchKernelGGL(argmax_chunks<false>, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
     BTV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(greedy_walk, dim3(batch), dim3(256), 0, st, part, chunks, parent, token, M_max, path, n_acc, bonus,
+    hipLaunchKernelGGL(greedy_walk, dim3(batch), dim3(GW_WAVES * 64), 0, st, part, chunks, parent, token, M_max, path, n_acc, bonus,
                        argmax_out, q_offset, total_M, static_cast<uint32_t *>(ws));
     BTV_HIP(hipGetLastError());
     return BTV_OK;

@@ -53,6 +53,18 @@ def test_matches_oracle(oracle, gpu, M, h, V):
         assert _check(oracle, xf, wf, parent, token, got) >= (M + 1) // 2
 
 
+@pytest.mark.parametrize("M,h,V", [(3, 128, 2500), (31, 384, 12321), (32, 640, 9000), (63, 896, 4097), (64, 256, 8191), (95, 384, 9000),
+                                   (127, 640, 6007), (128, 128, 9001), (255, 384, 16100)])
+def test_shapes_chosen_by_size(oracle, gpu, M, h, V):
+    """Waves over the contraction (even and odd numbers of blocks, a single one), groups of rows (whole and ragged), the merge by
+    one workgroup and by one per row; each twice on one workspace."""
+    parent = synth.tree_parents(4, M, "random")
+    token = synth.sibling_distinct_tokens(4, parent, V)
+    xs, xf, ws, wf = synth.lm_head(4, M + 1, h, V, "bf16")
+    for _ in range(2):
+        assert _check(oracle, xf, wf, parent, token, gpu.run_accept_greedy_lm_head(xs, ws, parent, token)) >= (M + 1) // 2
+
+
 def test_planted_path_is_accepted(oracle, gpu):
     M, h, V = 64, 512, 5000
     parent = synth.tree_parents(3, M, "deep")
