@@ -409,47 +409,6 @@ __device__ __forceinline__ float tile_max(const f32x16 &s)
 // Scores arrive in log2 units: the queries were multiplied by scale * log2(e) once, in the prologue, so a
 // probability is exp2(score - reference) with no multiply per element.
 //
-// Lazy reference maximum: m_run only moves when the tile maximum exceeds it by more than LAZY, so probabilities
-// stay below 2^LAZY and the O^T / row-sum rescale is skipped on most tiles.  The result is unchanged: numerator
-// and denominator refer to the same m_run.
-template <int DT>
-__device__ __forceinline__ void lazy_rescale(float tmax, float &m_run, float &l_run, f32x16 (&oacc)[DT])
-{
-    constexpr float LAZY = 8.0f;
-    const bool grow = tmax - m_run > LAZY;
-    if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
-        const float mnew = grow ? tmax : m_run;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);
-        m_run = mnew;
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
-    }
-}
-
-// P^T = exp2(S^T - m_run) as bf16 B-operands; the row sum adds the rounded values PV uses
-// (v_dot2c_f32_bf16 against (1, 1): two probabilities per instruction).
-__device__ __forceinline__ void softmax_tile(const f32x16 &s, float m_run, float &l_run, bf16x8 (&pb)[2])
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 ones = { (__bf16)1.0f, (__bf16)1.0f };
-    float ls[2] = { l_run, 0.f };
-#pragma unroll
-    for (int mm = 0; mm < 2; ++mm)
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(s[mm * 8 + e] - m_run);
-            const float p1 = __builtin_amdgcn_exp2f(s[mm * 8 + e + 1] - m_run);
-            const bf16x2 pp = { (__bf16)p0, (__bf16)p1 };
-            pb[mm][e] = pp[0];
-            pb[mm][e + 1] = pp[1];
-            ls[mm] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, ls[mm], false);
-        }
-    l_run = ls[0] + ls[1];
-}
-
 // One half (keys 8 mm .. 8 mm + 7 of the lane's 16) of a tile whose scores already are relative to the reference:
 // P = exp2(x) as a B operand, its rounded values added to `sum`.
 __device__ __forceinline__ void exp_half(const f32x16 &x, int mm, bf16x8 &pbm, float &sum)
@@ -469,8 +428,9 @@ __device__ __forceinline__ void exp_half(const f32x16 &x, int mm, bf16x8 &pbm, f
 
 // The reference of the step-by-step tiles enters through the matrix cores as well: the score accumulator starts from
 // -base (negb: the same value in all 16 registers), base being the running maximum once there is one (0 before), so
-// the scores arrive relative to it and a probability is exp2 of the accumulator as it stands.  Only when the maximum
-// moves (the lazy rule of lazy_rescale, on the scores' true values) are the tile's scores shifted by hand.
+// the scores arrive relative to it and a probability is exp2 of the accumulator as it stands.  The reference only moves where
+// the tile's maximum exceeds it by more than LAZY, so that probabilities stay below 2^LAZY and most tiles rescale nothing; the
+// result is the same, numerator and denominator refer to the same m_run.  Where it moves the tile's scores are shifted by hand.
 template <int DT>
 __device__ __forceinline__ void rebase_tile(f32x16 &srel, float &base, f32x16 &negb, float &m_run, float &l_run, f32x16 (&oacc)[DT])
 {
@@ -494,13 +454,28 @@ __device__ __forceinline__ void rebase_tile(f32x16 &srel, float &base, f32x16 &n
     }
 }
 
-// P^T = exp2(x) for scores x already relative to the reference; the row sum adds the rounded values PV uses.
-__device__ __forceinline__ void softmax_rel(const f32x16 &x, float &l_run, bf16x8 (&pb)[2])
+// Probabilities of a tile whose scores are relative to the reference.  The reference has to follow the scores up (rebase_tile)
+// where there is none yet or the tile is masked (`exact`); otherwise nothing stands between the scores and their
+// exponentials, and the tile's sum tells afterwards whether one of them exceeded 16: then it is done again, against a new one.  (The
+// maximum, its exchange between the halves of the wave and the branch on it are 150 cycles of a tile's 1300 to 1800.)
+constexpr float GROW = 1048576.0f;       // 2^20: a sum of 16 terms above it means some score > 16
+template <int DT>
+__device__ __forceinline__ void probabilities(f32x16 &x, bool exact, float &base, f32x16 &negb, float &m_run, float &l_run, f32x16 (&oacc)[DT],
+                                              bf16x8 (&pb)[2])
 {
-    float ls[2] = { l_run, 0.f };
-    exp_half(x, 0, pb[0], ls[0]);
-    exp_half(x, 1, pb[1], ls[1]);
-    l_run = ls[0] + ls[1];
+    if (exact) rebase_tile<DT>(x, base, negb, m_run, l_run, oacc);
+    float ts[2] = { 0.f, 0.f };
+    exp_half(x, 0, pb[0], ts[0]);
+    exp_half(x, 1, pb[1], ts[1]);
+    float sum = ts[0] + ts[1];
+    if (!exact && __builtin_amdgcn_ballot_w64(!(sum <= GROW)) != 0ull) {
+        rebase_tile<DT>(x, base, negb, m_run, l_run, oacc);
+        ts[0] = ts[1] = 0.f;
+        exp_half(x, 0, pb[0], ts[0]);
+        exp_half(x, 1, pb[1], ts[1]);
+        sum = ts[0] + ts[1];
+    }
+    l_run += sum;
 }
 
 // O^T += V^T . P^T
@@ -532,7 +507,7 @@ template <int D>
 __device__ __forceinline__ void do_tile(uint32_t stage, int kb, int Lr, int l,
                                         const uint32_t (&anc_i)[BTV_ANC_WORDS],
                                         const bf16x8 (&qreg)[D / 16], float &m_run, float &l_run, f32x16 (&oacc)[D / 32],
-                                        float &base, f32x16 &negb)
+                                        float &base, f32x16 &negb, bool first)
 {
     constexpr int DS = D / 16, DT = D / 32;
     u32x4 ka[DS];
@@ -543,10 +518,10 @@ __device__ __forceinline__ void do_tile(uint32_t stage, int kb, int Lr, int l,
     lds_wait_k<DS, DT * 2>(ka);          // the counter completes in order: K has landed when 2*DT reads remain
     lds_read_vt<D, 1>(va_addr, va);
     f32x16 s = qk_tile<DS>(ka, qreg, negb);
-    if (kb + 32 > Lr) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
-    rebase_tile<DT>(s, base, negb, m_run, l_run, oacc);
+    const bool masked = kb + 32 > Lr;
+    if (masked) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
     bf16x8 pb[2];
-    softmax_rel(s, l_run, pb);
+    probabilities<DT>(s, first || masked, base, negb, m_run, l_run, oacc, pb);
     lds_wait_vt<DT>(va);
     pv_tile<DT>(va, pb, oacc);
 }
@@ -628,7 +603,8 @@ __device__ __forceinline__ void lds_wait_vt8(u32x2 (&v8)[4][2])
 template <int D>
 __device__ __forceinline__ void do_tile8(uint32_t stage, int kb, int Lr, int l,
                                          const uint32_t (&anc_i)[BTV_ANC_WORDS],
-                                         const bf16x8 (&qreg)[D / 16], float &m_run, float &l_run, f32x16 (&oacc)[D / 32])
+                                         const bf16x8 (&qreg)[D / 16], float &m_run, float &l_run, f32x16 (&oacc)[D / 32],
+                                         float &base, f32x16 &negb, bool first)
 {
     static_assert(D == 128, "FP8 K/V: head dimension 128 only");
     constexpr int DS = D / 16, DT = D / 32;
@@ -639,18 +615,16 @@ __device__ __forceinline__ void do_tile8(uint32_t stage, int kb, int Lr, int l,
     lds_read_vt8<D, 0>(va_addr, v8);
     lds_wait_k8<DT>(k8);                 // the counter completes in order: K has landed when DT reads remain
     lds_read_vt8<D, 1>(va_addr, v8);
-    f32x16 s;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+    f32x16 s = negb;
 #pragma unroll
     for (int k = 0; k < DS / 2; ++k) {
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp8x8_to_bf16x8(k8[k][0], k8[k][1]), qreg[2 * k], s, 0, 0, 0);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp8x8_to_bf16x8(k8[k][2], k8[k][3]), qreg[2 * k + 1], s, 0, 0, 0);
     }
-    if (kb + 32 > Lr) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
-    lazy_rescale<DT>(tile_max(s), m_run, l_run, oacc);
+    const bool masked = kb + 32 > Lr;
+    if (masked) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
     bf16x8 pb[2];
-    softmax_tile(s, m_run, l_run, pb);
+    probabilities<DT>(s, first || masked, base, negb, m_run, l_run, oacc, pb);
     lds_wait_vt8(v8);
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm)
@@ -1052,7 +1026,6 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         // K and V^T operands live in two half-tile buffers, each refilled right after the MFMAs that read it.
         static_assert(NT == 8, "the pipelined loop is written for a ring of 8 stages");
         constexpr int KH = DS / 2;                               // LDS reads per K half (a V^T half takes 2 * DT)
-        constexpr float GROW = 1048576.0f;                       // 2^20: a half-row sum of 16 terms above it means some x > 16
         int Tf = min(st1, Lr / 32) - st0;                        // plain tiles at the start of this split
         if (Tf < 3) Tf = 0;
         int j0 = 0;                                              // first local tile the step-by-step loop below takes
@@ -1244,7 +1217,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
             for (int k = 0; k < 2; ++k)
                 if (issued - st0 - j < NT) issue_one();
-            do_tile<D>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb);
+            do_tile<D>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, true);
         }
         if constexpr (PAGED) wait_vmcnt<0>();
     } else if constexpr (KW > 1) {
@@ -1254,7 +1227,8 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         // issues overwrite.
         // (a wave whose 32 rows all lie past the last one only fills)
         const bool live = by * WR + __builtin_amdgcn_readfirstlane(rw) * 32 < rows_g;
-        int cslot = kw;
+        const int kwu = wu % KW;                                 // (kw, as a scalar)
+        int cslot = kwu;
         for (int st = st0; st < st1; st += KW) {
             if (issued - st - KW == AHEAD) wait_vmcnt<AHEAD * LPW>();
             else wait_vmcnt<0>();
@@ -1267,11 +1241,11 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                     ++issued;
                     if (++islot == NT) islot = 0;
                 }
-            if (live && st + kw < st1) {
+            if (live && st + kwu < st1) {
                 if constexpr (EB == 2)
-                    do_tile<D>(ring + cslot * LD::STAGE, (st + kw) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb);
+                    do_tile<D>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, st == st0);
                 else
-                    do_tile8<D>(ring + cslot * LD::STAGE, (st + kw) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc);
+                    do_tile8<D>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, st == st0);
             }
             cslot += KW;
             if (cslot >= NT) cslot -= NT;

@@ -192,6 +192,21 @@ def test_bf16_every_kernel_shape_elementwise(G, oracle, shape_id, dims):
         assert np.abs(out - ref).max() <= TOL_BF16, (kind, dims, shape_id, np.abs(out - ref).max())
 
 
+@pytest.mark.parametrize("steep", [2, 8])
+@pytest.mark.parametrize("shape_id", [1, 2, 3])
+@pytest.mark.parametrize("dims", [(16, 700, 32, 8, 128), (70, 1029, 16, 4, 64), (250, 650, 8, 2, 128)])
+def test_bf16_maxima_that_grow_along_the_prefix(G, oracle, shape_id, dims, steep):
+    """Scores of a standard deviation of 16 to 90 in log2 units: a row's maximum passes the reference taken from its first tile
+    by more than 16 in most rows, by more than exp2 can hold in some."""
+    M, L, Hq, Hkv, D = dims
+    parent = synth.tree_parents(M + L, M, "random")
+    t = synth.qkv(48, M, L, Hq, Hkv, D, "bf16", tag=f"grow{dims}")
+    scale = steep * np.log(2)            # (a power of two times log2(e): the queries are not rounded again)
+    ref = oracle.tree_attn(t["Qf"], t["Kf"], t["Vf"], parent, L, scale=scale)
+    out = G.run_verify_attn(t, parent, L, "bf16", nsplit=1, shape=shape_id, scale=scale)
+    assert np.abs(out - ref).max() <= TOL_BF16
+
+
 @pytest.mark.parametrize("dims,kind", [((256, 16384, 32, 8, 128), "random"), ((131, 16397, 16, 2, 128), "deep"),
                                        ((250, 16415, 64, 8, 128), "chain")])
 def test_bf16_long_prefix_many_rows_elementwise(G, oracle, dims, kind):

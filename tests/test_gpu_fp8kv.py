@@ -61,6 +61,20 @@ def test_every_kernel_shape_elementwise(G, oracle, shape_id, dims):
     assert np.abs(out - ref).max() <= TOL, (dims, shape_id, np.abs(out - ref).max())
 
 
+@pytest.mark.parametrize("steep", [2, 8])
+@pytest.mark.parametrize("shape_id", [1, 2])
+@pytest.mark.parametrize("dims", [(16, 700, 32, 8), (70, 1029, 16, 4)])
+def test_maxima_that_grow_along_the_prefix(G, oracle, shape_id, dims, steep):
+    M, L, Hq, Hkv = dims
+    parent = synth.tree_parents(M + L, M, "random")
+    q, kv = _inputs(75, M, L, Hq, Hkv, tag=f"grow{dims}")
+    kv = dict(kv, k_scale=2.0 ** -6)
+    scale = steep * np.log(2)
+    ref = _oracle(oracle, q, kv, parent, L, scale=scale)
+    out = G.run_verify_attn_fp8kv(q["Q"], kv, parent, L, nsplit=1, shape=shape_id, scale=scale)
+    assert np.abs(out - ref).max() <= TOL
+
+
 @pytest.mark.parametrize("kind", ["chain", "star", "binary", "caterpillar", "random", "deep"])
 def test_tree_kinds_with_split(G, oracle, kind):
     M, L, Hq, Hkv = 48, 1500, 16, 4
