@@ -308,10 +308,12 @@ int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const vo
  * (unchanged if that is all zero) and q[x] <- 0, q renormalised; when no child is accepted the
  * bonus token is the inverse-CDF sample of p with the next uniform.  uniforms [M+1] fp32 in
  * [0,1), consumed in order.  marginals [B,V] fp32 as given to tree_build.
- *   One launch of up to 64 workgroups, each with a slice of the vocabulary, that exchange their parts of
- *   every vocabulary-wide sum in the workspace and walk the tree in step.  A workgroup that waits for another's
- *   part longer than a second of wall clock gives up: the data flag is raised and the kernel ends
- *   (the workspace is then to be zero-filled before its next use).
+ *   One launch of up to 64 workgroups (no more than CUs that the stream may use), each with a slice of
+ *   the vocabulary, that exchange their parts of every vocabulary-wide sum in the workspace and walk
+ *   the tree in step.  Where they do not all run at once, because other work holds the CUs, a workgroup
+ *   that has waited 10 ms for another's part leaves, and one of those that left walks the tree alone:
+ *   the results are there all the same, some milliseconds later, and the workspace is fit for the
+ *   next call.
  * ------------------------------------------------------------------------------------------- */
 size_t btv_tree_accept_workspace(int M, int V, int stochastic);
 int btv_tree_accept_greedy(const void *logits, int dtype, const int32_t *parent, const int32_t *token,
@@ -330,6 +332,15 @@ int btv_tree_accept_stochastic(const void *logits, int dtype, const float *margi
                                const int32_t *parent, const int32_t *token, int M, int V,
                                const float *uniforms, int32_t *path, int32_t *n_acc, int32_t *bonus,
                                void *ws, size_t ws_bytes, void *stream);
+/* btv_tree_accept_stochastic with what the library otherwise chooses given by the caller (tests of
+ * those paths): max_workgroups in [1, 64], 0 = the library's choice; wait_ticks = how long a
+ * workgroup waits for another's part, in ticks of the 100 MHz wall clock; negative = give up where
+ * the first look does not find it.  Results as there. */
+int btv_tree_accept_stochastic_tuned(const void *logits, int dtype, const float *marginals, int B,
+                                     const int32_t *parent, const int32_t *token, int M, int V,
+                                     const float *uniforms, int32_t *path, int32_t *n_acc,
+                                     int32_t *bonus, void *ws, size_t ws_bytes, void *stream,
+                                     int max_workgroups, long long wait_ticks);
 
 /* ---------------------------------------------------------------------------------------------
  * Greedy acceptance straight from the final hidden states: the LM head of App. E (2*s*h*V FLOPs,

@@ -32,6 +32,7 @@ EXPORTS = [
     "btv_tree_accept_greedy", "btv_tree_accept_stochastic", "btv_tree_accept_lm_head_workspace",
     "btv_tree_accept_greedy_lm_head", "btv_tree_verify_attn_tuned_workspace", "btv_tree_verify_attn_tuned",
     "btv_tree_verify_attn_noalloc", "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned",
+    "btv_tree_accept_stochastic_tuned",
 ]
 
 
@@ -62,7 +63,7 @@ def lib() -> C.CDLL:
                   "btv_tree_verify_attn", "btv_tree_verify_attn_paged", "btv_tree_verify_attn_fp8kv",
                   "btv_tree_verify_attn_paged_fp8kv", "btv_tree_accept_greedy",
                   "btv_tree_accept_stochastic", "btv_tree_verify_attn_tuned", "btv_tree_verify_attn_noalloc",
-                  "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned"):
+                  "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned", "btv_tree_accept_stochastic_tuned"):
             getattr(L, n).restype = C.c_int
         _lib = L
     return _lib
@@ -315,6 +316,16 @@ def btv_tree_accept_greedy_lm_head(hidden, W, parent, token, path, n_acc, bonus,
 
 def btv_tree_accept_stochastic(logits, marginals, parent, token, uniforms, path, n_acc, bonus, ws) -> None:
     (_face or _load_face()).tree_accept_stochastic(logits, marginals, parent, token, uniforms, path, n_acc, bonus, ws)
+
+
+def btv_tree_accept_stochastic_tuned(logits, marginals, parent, token, uniforms, path, n_acc, bonus, ws, max_workgroups: int = 0,
+                                     wait_ticks: int = 1000000) -> None:
+    rows, V = logits.shape
+    assert marginals.shape[1] == V and uniforms.numel() >= rows
+    _check(lib().btv_tree_accept_stochastic_tuned(_ptr(logits), _dtype_code(logits), _ptr(marginals), marginals.shape[0], _ptr(parent),
+                                                  _ptr(token), rows - 1, V, _ptr(uniforms), _ptr(path), _ptr(n_acc), _ptr(bonus),
+                                                  _ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0), _stream(),
+                                                  int(max_workgroups), C.c_longlong(int(wait_ticks))))
 
 
 def btv_kv_commit(K, V, L: int, M: int, path, n_acc, new_len=None) -> None:

@@ -17,8 +17,15 @@
 // (relaxed device-scope atomics: the L2s of the 8 XCDs are not coherent with each other), about 2 us; two sets of words in turn are
 // enough, because a workgroup writes exchange i + 2 only after it has read all of exchange i + 1, which everybody
 // wrote after reading exchange i.  Tags count on from call to call (`base` in the workspace), so words are never cleared.
-// The slices are small enough for all workgroups to be on the chip at once (at most 64 of them on 256 CUs); a wait ends
-// after `wait_ticks` of the wall clock all the same, raises the data flag and ends the kernel.
+//
+// The exchanges need all workgroups on the chip at once.  There are no more of them than CUs that the stream may use (the LDS
+// holds one on a CU), and longer slices where those are few; but other work may hold the CUs, so nothing depends on it: a
+// wait ends after `wait_ticks` of the wall clock, its workgroup leaves the exchanges, and the first to do so (it finds no claim
+// of these tags in the workspace) walks the tree once more alone, over the whole vocabulary, and writes every result (workgroups
+// that do get through write the same).  Then it moves `base` past all tags that a call can use.  A workgroup that only starts
+// after that takes the new tags, finds nobody and does the same again, so whoever has written words under some tags, `base` is
+// past them when the kernel ends, and the next call takes none of them for its own.  Alone the walk takes 4 to 12 ms at
+// V = 128256, which is where the limit lies: 10 ms, so that waiting costs no more than it can save.
 //
 // A wide fan is not walked one exchange per rejection.  s_{k+1} = s_k + G(s_k) / T_k is a recurrence in one scalar, T_k is known
 // beforehand, and G is convex and piecewise linear, G(s) = E - s Q with E, Q the sums of e and q over the tokens with
@@ -55,7 +62,8 @@ constexpr int SA_CHAIN_FAN = 8;                         // children up to which 
 constexpr int SA_DIRECT = 3;                            // rejections that are walked one by one in any case, one less per 32 children
                                                         // (a node of many children has no likely one among its first)
 constexpr int SA_BATCH_MIN = 10;                        // children left from which the rest is solved at once (the price of ten exchanges)
-constexpr long long SA_WAIT_TICKS = 100000000ll;        // one second of the 100 MHz wall clock
+constexpr long long SA_WAIT_TICKS = 1000000ll;          // 10 ms of the 100 MHz wall clock
+constexpr uint32_t SA_SPAN = 1u << 20;                  // more tags than a call can use (256 nodes of at most 18 + 256 exchanges)
 static_assert(SA_PLANE * 4 <= SA_WORDS && SA_GRID <= SA_PLANE, "all words of an exchange fit");
 
 struct SaParams {
@@ -64,6 +72,7 @@ struct SaParams {
     const int32_t *parent, *token;
     int32_t *path, *n_acc, *bonus;
     uint32_t *flag, *base;
+    u64 *claim;                                         // 1 << 32 | the tags' base of the last walk that was done alone
     u64 *slots;                                         // [2][G][SA_WORDS]
     int B, M, V, G, per;                                // per: tokens of a slice
     long long wait_ticks;
@@ -245,7 +254,7 @@ struct SaShared {
     double F[SA_CHAIN][SA_MAX_WGS], GW[SA_CHAIN + 1][SA_MAX_WGS];
     int acc0[SA_CHAIN];
     int wsum[SA_WAVES];
-    int dead, status, acc, pick, last;
+    int dead, status, acc, pick, last, late;
     float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
     double pt[BTV_MAX_NODES], ptG[BTV_MAX_NODES], invT[BTV_MAX_NODES];
     double sE[SA_PLANE], sQ[SA_PLANE];
@@ -260,14 +269,22 @@ struct SaShared {
 // 4 r + 3 hold row r of the chain, PT * 4 tokens per lane.  OVER: the slices are longer than those registers; what
 // is beyond a lane's first PT * 4 tokens is computed again from the row wherever it is needed (vocabularies above
 // 64 x 8192 tokens), and fans are walked one by one.
-template <bool BF16, int PT, bool OVER>
-__global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
+// The next call's tags begin `used` further on, unless another workgroup has moved them already.
+__device__ __forceinline__ void sa_move_on(uint32_t *word, uint32_t base, uint32_t used)
 {
-    __shared__ SaShared<PT> L;
+    __hip_atomic_compare_exchange_strong(word, &base, base + used, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ALONE: one workgroup (me = 0) with the whole vocabulary for a slice.  Returns whether a wait has passed its limit
+// (the same in all threads; results may then be missing).
+template <bool BF16, int PT, bool OVER, bool ALONE>
+__device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int me, uint32_t &base)
+{
+    static_assert(OVER || !ALONE, "a slice of any length");
     constexpr int TG = 4 * PT;                          // tokens of its chain row that a lane keeps
     constexpr int BT = SaShared<PT>::BT;                // tokens of the slice that a thread sorts
     constexpr int KW = BTV_MAX_NODES / 64;              // wavefronts that hold nodes
-    const int me = blockIdx.x, M = p.M, V = p.V, G = p.G;
+    const int M = p.M, V = p.V, G = ALONE ? 1 : p.G, per = ALONE ? V : p.per;
     int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     // The compiler takes everything that depends on the thread alone out of the walk's loop, dozens of registers, and
     // spills them; what tid is, it has to find out again at every node, and at every fan.
@@ -276,7 +293,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
         lane = tid & 63;
         wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     };
-    const int v0 = min(me * p.per, V), v1 = min(v0 + p.per, V);
+    const int v0 = min(me * per, V), v1 = min(v0 + per, V);
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(p.logits) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.marg) & 15) == 0;
     for (int c = tid; c <= BTV_MAX_NODES; c += SA_T) {
         L.first[c] = INT_MAX;
@@ -284,8 +301,8 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
         if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
         if (c <= M) L.uni[c] = p.uniforms[c];
     }
-    if (tid == 0) L.dead = 0;
-    const uint32_t base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (tid == 0) { L.dead = 0; L.late = 0; }
+    base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     uint32_t seq = 0;
     int cur = -1, n = 0, ui = 0, d = 0;
     bool dead = false;
@@ -405,7 +422,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
             bool acc0 = false;                          // is the first child accepted, if the rows above took theirs?
 #pragma nounroll
             for (int j = k0 + lane; j < k1; j += 64) {  // a child's e exactly as its slice's owner has it
-                const int w = L.kid_tok[j] / p.per;
+                const int w = L.kid_tok[j] / per;
                 const float x = L.kid_x[j];
                 const double ek = x == -INFINITY ? 0.0 : L.F[r][w] * (double)exp_neg(x - L.Mx[r][w]);
                 L.kid_e[j] = ek;
@@ -589,10 +606,11 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
                             fine = take<1, 4, SA_PLANE>(set, at % G, 0, G, at, tid < np, base + seq, x, p.wait_ticks);
                             if (tid < np) { L.sE[tid] = get_f64(x[0][0], x[0][1]); L.sQ[tid] = get_f64(x[0][2], x[0][3]); }
                         }
-                        if (!fine && lane == 0) L.dead = 1;
+                        // (not L.dead: another wavefront may not have looked at that yet)
+                        if (!fine && lane == 0) L.late = 1;
                     }
                     __syncthreads();
-                    if (L.dead) break;
+                    if (L.late) break;
                     if (pass < 0) {
                         if (tid < SA_GRID) {
                             const int kk = min(tid, SA_GRID - 2);
@@ -691,7 +709,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
                     status = L.status;
                     if (status != 0) break;
                 }
-                if (L.dead) { dead = true; break; }
+                if (L.dead | L.late) { dead = true; break; }
                 if (status == 1 && L.acc < K) {
                     accepted = L.kid_node[kj + L.acc];
                     j += L.acc + 1;
@@ -829,25 +847,61 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
         }
         break;
     }
-    if (me == 0 && tid == 0) {
+    if (!dead && me == 0 && tid == 0) {
         *p.n_acc = n;
-        if (dead) { *p.bonus = 0; atomicOr(p.flag, 128u); }
-        if (G > 1) __hip_atomic_store(p.base, base + seq + (dead ? 1u << 20 : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (G > 1) sa_move_on(p.base, base, seq);
     }
+    return dead;
 }
 
-// Tokens per slice and slices for a vocabulary of V tokens: slices of 4096 tokens (four per thread) as long as 64 workgroups
-// cover the vocabulary, of 8192 up to twice that, longer ones above.
+template <bool BF16, int PT, bool OVER>
+__global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
+{
+    __shared__ SaShared<PT> L;
+    uint32_t base, none;
+    if (!sa_walk<BF16, PT, OVER, false>(p, L, blockIdx.x, base)) return;
+    // (the arguments are read again: held through the walk above for what is next to never needed, they cost it registers, 1 us
+    // of 40 where a drafter is mostly followed)
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const SaParams &p2 = *(const SaParams *)args;
+    const u64 call = 1ull << 32 | base;
+    if (threadIdx.x == 0) L.status = __hip_atomic_exchange(p2.claim, call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call;
+    __syncthreads();
+    if (!L.status) return;
+    sa_walk<BF16, PT, true, true>(p2, L, 0, none);
+    if (threadIdx.x == 0) sa_move_on(p2.base, base, SA_SPAN);
+}
+
+// Slices for a vocabulary of V tokens on at most `most` workgroups: of 2048 tokens (two per thread) as long as those cover the
+// vocabulary, of 4096, of 8192, longer ones above.
 struct SaPlan { int G, per, pt; bool over; };
-SaPlan sa_plan(int V)
+SaPlan sa_plan(int V, int most)
 {
     SaPlan a;
-    a.pt = V <= SA_MAX_WGS * SA_T * 2 ? 2 : V <= SA_MAX_WGS * SA_T * 4 ? 4 : 8;
-    a.over = V > SA_MAX_WGS * SA_T * 8;
-    const int most = SA_T * a.pt;
-    a.G = a.over ? SA_MAX_WGS : (V + most - 1) / most;
+    a.pt = V <= most * SA_T * 2 ? 2 : V <= most * SA_T * 4 ? 4 : 8;
+    a.over = V > most * SA_T * 8;
+    const int slice = SA_T * a.pt;
+    a.G = a.over ? most : (V + slice - 1) / slice;
     a.per = (int)((((long long)V + a.G - 1) / a.G + 3) / 4 * 4);
     return a;
+}
+
+// CUs that work on the stream may use: those of the device, or of the mask that the stream was made with (0.3 us a call).  With
+// 32 of them the two walks named at the top take 71 and 60 us, with 16 125 and 115.
+int usable_cus(hipStream_t st)
+{
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
+        int n = 0;
+        for (uint32_t w : mask) n += __builtin_popcount(w);
+        if (n > 0) return n;
+    } else {
+        (void)hipGetLastError();                        // (the launch's own error is what is reported)
+    }
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) return n;
+    return 1;
 }
 
 template <bool BF16>
@@ -863,12 +917,13 @@ void sa_launch(const SaPlan &a, const SaParams &p, hipStream_t st)
 
 size_t btv_stochastic_workspace(int V)
 {
-    return BTV_WS_HEADER + btv_align_up((size_t)2 * sa_plan(V).G * SA_WORDS * sizeof(u64), BTV_WS_ALIGN);
+    return BTV_WS_HEADER + btv_align_up((size_t)2 * sa_plan(V, SA_MAX_WGS).G * SA_WORDS * sizeof(u64), BTV_WS_ALIGN);   // (fewer workgroups: fewer slices)
 }
 
-extern "C" int btv_tree_accept_stochastic(const void *logits, int dtype, const float *marginals, int B, const int32_t *parent,
-                                          const int32_t *token, int M, int V, const float *uniforms, int32_t *path,
-                                          int32_t *n_acc, int32_t *bonus, void *ws, size_t ws_bytes, void *stream)
+extern "C" int btv_tree_accept_stochastic_tuned(const void *logits, int dtype, const float *marginals, int B, const int32_t *parent,
+                                                const int32_t *token, int M, int V, const float *uniforms, int32_t *path,
+                                                int32_t *n_acc, int32_t *bonus, void *ws, size_t ws_bytes, void *stream,
+                                                int max_workgroups, long long wait_ticks)
 {
     BTV_REQUIRE(logits && parent && token && path && n_acc && bonus, "null pointer");
     BTV_REQUIRE(dtype == BTV_F32 || dtype == BTV_BF16, "dtype=%d unsupported", dtype);
@@ -876,18 +931,29 @@ extern "C" int btv_tree_accept_stochastic(const void *logits, int dtype, const f
     BTV_REQUIRE(V >= 1, "V=%d", V);
     BTV_REQUIRE(marginals && uniforms, "null pointer");
     BTV_REQUIRE(B >= 1 && B <= BTV_MAX_DEPTH, "B=%d outside [1,%d]", B, BTV_MAX_DEPTH);
+    BTV_REQUIRE(max_workgroups >= 0 && max_workgroups <= SA_MAX_WGS, "max_workgroups=%d outside [0,%d]", max_workgroups, SA_MAX_WGS);
     const int rc = btv_check_ws(ws, ws_bytes, btv_stochastic_workspace(V));
     if (rc) return rc;
-    const SaPlan a = sa_plan(V);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    SaPlan a = sa_plan(V, max_workgroups ? max_workgroups : SA_MAX_WGS);
+    if (!max_workgroups && a.G > 1) a = sa_plan(V, std::min(SA_MAX_WGS, usable_cus(st)));
     SaParams p;
     p.logits = logits; p.marg = marginals; p.uniforms = uniforms; p.parent = parent; p.token = token;
     p.path = path; p.n_acc = n_acc; p.bonus = bonus;
-    p.flag = static_cast<uint32_t *>(ws); p.base = static_cast<uint32_t *>(ws) + 16;
+    p.flag = static_cast<uint32_t *>(ws);
+    p.base = static_cast<uint32_t *>(ws) + 16; p.claim = static_cast<u64 *>(ws) + 9;
     p.slots = reinterpret_cast<u64 *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
-    p.B = B; p.M = M; p.V = V; p.G = a.G; p.per = a.per; p.wait_ticks = SA_WAIT_TICKS;
-    hipStream_t st = static_cast<hipStream_t>(stream);
+    p.B = B; p.M = M; p.V = V; p.G = a.G; p.per = a.per; p.wait_ticks = wait_ticks;
     if (dtype == BTV_BF16) sa_launch<true>(a, p, st);
     else sa_launch<false>(a, p, st);
     BTV_HIP(hipGetLastError());
     return BTV_OK;
+}
+
+extern "C" int btv_tree_accept_stochastic(const void *logits, int dtype, const float *marginals, int B, const int32_t *parent,
+                                          const int32_t *token, int M, int V, const float *uniforms, int32_t *path,
+                                          int32_t *n_acc, int32_t *bonus, void *ws, size_t ws_bytes, void *stream)
+{
+    return btv_tree_accept_stochastic_tuned(logits, dtype, marginals, B, parent, token, M, V, uniforms, path, n_acc, bonus, ws,
+                                            ws_bytes, stream, 0, SA_WAIT_TICKS);
 }

@@ -116,7 +116,8 @@ def run_accept_greedy(logits_store: np.ndarray, bf16_bits: bool, parent, token) 
     return {"n_acc": n, "path": path.cpu().numpy()[:n], "bonus": int(bonus.item()), "argmax": am.cpu().numpy()}
 
 
-def run_accept_stochastic(logits_store: np.ndarray, bf16_bits: bool, marg, parent, token, uniforms) -> dict:
+def run_accept_stochastic(logits_store: np.ndarray, bf16_bits: bool, marg, parent, token, uniforms, tuned=None, ws=None) -> dict:
+    """tuned: (max_workgroups, wait_ticks) of the tuned entry point.  ws: a workspace of an earlier call."""
     x = dev(logits_store, bf16_bits)
     M = len(parent)
     par, tok = dev(np.asarray(parent, dtype=np.int32)), dev(np.asarray(token, dtype=np.int32))
@@ -124,11 +125,15 @@ def run_accept_stochastic(logits_store: np.ndarray, bf16_bits: bool, marg, paren
     path = torch.full((M,), -7, dtype=torch.int32, device="cuda")
     n_acc = torch.full((1,), -7, dtype=torch.int32, device="cuda")
     bonus = torch.full((1,), -7, dtype=torch.int32, device="cuda")
-    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(M, x.shape[1], True))
-    btv.btv_tree_accept_stochastic(x, m, par, tok, u, path, n_acc, bonus, ws)
+    if ws is None:
+        ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(M, x.shape[1], True))
+    if tuned:
+        btv.btv_tree_accept_stochastic_tuned(x, m, par, tok, u, path, n_acc, bonus, ws, *tuned)
+    else:
+        btv.btv_tree_accept_stochastic(x, m, par, tok, u, path, n_acc, bonus, ws)
     torch.cuda.synchronize()
     n = int(n_acc.item())
-    return {"n_acc": n, "path": path.cpu().numpy()[:n], "bonus": int(bonus.item())}
+    return {"n_acc": n, "path": path.cpu().numpy()[:n], "bonus": int(bonus.item()), "status": int(btv.btv_workspace_status(ws))}
 
 
 def run_accept_greedy_lm_head(hidden_bits: np.ndarray, W_bits, parent, token) -> dict:

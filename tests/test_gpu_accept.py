@@ -336,3 +336,59 @@ def test_stochastic_token_outside_vocabulary_is_flagged_not_faulting():
     n = int(n_acc.item())
     assert 0 <= n <= M and 0 <= int(bonus.item()) < V
     assert 0 not in path.cpu().numpy()[:n].tolist()          # node 0 carries the invalid id: never accepted
+
+
+def _walk_cases(oracle, V, logit_dtype):
+    """A deep tree whose first children are mostly accepted, one whose first children are mostly not, and a fan of 24 all of
+    which is rejected; without the ambiguous ones."""
+    for seed, (B, N, sigma, noise) in enumerate([(6, 12, 4.0, 0.3), (6, 24, 3.0, 2.0), (2, 24, 0.5, 2.0)]):
+        marg = synth.marginals(40 + seed, B, V, sigma)
+        tree = oracle.tree_build(marg, N)
+        M = len(tree["parent"])
+        z = np.log(np.maximum(marg[np.minimum(np.concatenate([[0], tree["depth"]]), B - 1)].astype(np.float64), 1e-30))
+        z += synth.normal(50 + seed, "noise", z.shape, noise)
+        store, xf = synth.round_to_dtype(z, logit_dtype)
+        u = synth.uniform(60 + seed, "u", (M + 1,)).astype(np.float32)
+        if seed == 2:
+            u[:24] = 0.999999
+        ref = oracle.accept_stochastic(xf, marg, tree["parent"], tree["token"], tree["depth"], u)
+        if not _ambiguous(ref):
+            yield (store, logit_dtype == "bf16", marg, tree["parent"], tree["token"], u), ref
+
+
+def _same(got, ref):
+    return got["n_acc"] == ref["n_acc"] and np.array_equal(got["path"], ref["path"]) and got["bonus"] == ref["bonus"]
+
+
+@pytest.mark.parametrize("V,workgroups", [(5000, 2), (5003, 1), (30000, 8), (30000, 4), (30001, 3), (128256, 32), (128256, 1)])
+@pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
+def test_stochastic_on_few_compute_units(G, oracle, V, workgroups, logit_dtype):
+    """Where fewer workgroups than the vocabulary has slices can run at once, the slices get longer (the register
+    shapes at 4096 and 8192 tokens, slices read again from memory above), down to one workgroup."""
+    checked = 0
+    for args, ref in _walk_cases(oracle, V, logit_dtype):
+        got = G.run_accept_stochastic(*args, tuned=(workgroups, 1000000))
+        assert _same(got, ref) and got["status"] == 0, (V, workgroups)
+        checked += 1
+    assert checked >= 1
+
+
+@pytest.mark.parametrize("V,workgroups", [(5000, 0), (30001, 0), (128256, 0), (128256, 32), (128256, 16), (131072, 5)])
+@pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
+def test_stochastic_when_the_workgroups_do_not_run_at_once(G, oracle, V, workgroups, logit_dtype):
+    """A wait limit below zero makes a workgroup leave the exchange at the first part it does not find: one of those that
+    left walks the tree alone.  The results are the oracle's all the same, no flag is raised, and the next calls on the
+    workspace, with and without the limit, are right too."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(24, V, True))
+    checked = 0
+    for args, ref in _walk_cases(oracle, V, logit_dtype):
+        for wait in (-1, -1, 1000000, -1, 1000000):
+            got = G.run_accept_stochastic(*args, tuned=(workgroups, wait), ws=ws)
+            assert _same(got, ref) and got["status"] == 0, (V, workgroups, wait)
+        checked += 1
+    torch.cuda.synchronize()
+    words = ws[64:80].view(torch.int32).cpu().tolist()
+    assert words[0] >= 1 << 20 and words[3] == 1                 # a walk was done alone, and its tags are left behind
+    assert checked >= 1

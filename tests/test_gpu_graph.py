@@ -84,3 +84,55 @@ def test_graph_replays_equal_eager(oracle, fp8):
         want = snapshot()
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("V", [1500, 30000])
+def test_stochastic_graph_replays_equal_eager(oracle, V):
+    """The rejection walk keeps its tags from call to call in the workspace, and asks the stream for its CUs when it is
+    launched: recorded, replayed with other inputs and with eager calls on the same workspace in between, every call
+    gives the oracle's results."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    import gpu_util as G
+    B, N = 6, 24
+    cases = []
+    for seed in range(6):
+        m = synth.marginals(20 + seed, B, V, 3.0)
+        tree = oracle.tree_build(m, N)
+        z = np.log(np.maximum(m[np.minimum(np.concatenate([[0], tree["depth"]]), B - 1)].astype(np.float64), 1e-30))
+        z += synth.normal(30 + seed, "noise", z.shape, 0.7)
+        store, xf = synth.round_to_dtype(z, "fp32")
+        u = synth.uniform(40 + seed, "u", (N + 1,)).astype(np.float32)
+        ref = oracle.accept_stochastic(xf, m, tree["parent"], tree["token"], tree["depth"], u)
+        if ref["margin"] >= 1e-4 and ref["bonus_gap"] >= 1e-6:
+            cases.append(([G.dev(np.ascontiguousarray(a)) for a in (store, m, tree["parent"].astype(np.int32), tree["token"].astype(np.int32), u)], ref))
+    assert len(cases) >= 2
+    args = [x.clone() for x in cases[0][0]]
+    path = torch.zeros(N, dtype=torch.int32, device="cuda")
+    n_acc, bonus = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(N, V, True))
+
+    def step():
+        btv.btv_tree_accept_stochastic(*args, path, n_acc, bonus, ws)
+
+    def check(ref):
+        torch.cuda.synchronize()
+        n = int(n_acc.item())
+        assert n == ref["n_acc"] and path.cpu().numpy()[:n].tolist() == ref["path"].tolist() and int(bonus.item()) == ref["bonus"]
+
+    step()
+    check(cases[0][1])
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            step()
+    torch.cuda.synchronize()
+    for a, ref in cases + cases[:2]:
+        for dst, src in zip(args, a):
+            dst.copy_(src)
+        for call in (g.replay, g.replay, step, g.replay):
+            path.fill_(-7); n_acc.fill_(-7); bonus.fill_(-7)
+            call()
+            check(ref)
