@@ -6,8 +6,15 @@
  *   - Unless a parameter says HOST, every pointer is a DEVICE pointer owned by the caller.
  *     The library allocates no caller-visible memory; scratch space is the caller's `ws`
  *     (size from the matching *_workspace() query, 256-byte aligned).  A workspace must be
- *     zero-filled once, before its first use; every call leaves it ready for the next one (the
- *     data flag aside, see btv_workspace_status).  A workspace serves one call at a time.
+ *     zero-filled once, before its first use, and then belongs to ONE KIND of call: kernels keep
+ *     state in it from call to call (places that are zero between calls, tags that count on), and a
+ *     call of another kind would write over that or take its own data for it.  The kinds:
+ *       tree build in all its forms | attention in all its forms and the ancestor mask |
+ *       greedy acceptance of one request | stochastic acceptance | acceptance from hidden states |
+ *       greedy acceptance of a batch | KV commit
+ *     Every call leaves its workspace ready for the next one of its kind, of any size that the
+ *     workspace holds (the data flag aside, see btv_workspace_status).  To give a workspace to
+ *     another kind, zero-fill it again.  A workspace serves one call at a time.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls only
  *     enqueue work; outputs are valid once the caller has synchronised the stream.
  *   - Return value: BTV_OK, or a negative btv_status.  All argument checks run on the host

@@ -111,7 +111,9 @@ def _dtype_code(t) -> int:
 
 
 def alloc_workspace(nbytes: int, device="cuda") -> torch.Tensor:
-    """A zero-initialised device buffer of at least nbytes (torch allocations are 256-byte aligned)."""
+    """A zero-initialised device buffer of at least nbytes (torch allocations are 256-byte aligned).  One for each kind of
+    call: tree builds, attention, greedy acceptance, stochastic acceptance, acceptance from hidden states, batch
+    acceptance (include/bastion_tv.h: what kernels keep in it from call to call does not survive a call of another kind)."""
     return torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 

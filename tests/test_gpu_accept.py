@@ -392,3 +392,16 @@ def test_stochastic_when_the_workgroups_do_not_run_at_once(G, oracle, V, workgro
     words = ws[64:80].view(torch.int32).cpu().tolist()
     assert words[0] >= 1 << 20 and words[3] == 1                 # a walk was done alone, and its tags are left behind
     assert checked >= 1
+
+
+def test_stochastic_workspace_serves_changing_sizes(G, oracle):
+    """One workspace over calls of other vocabularies, other numbers of workgroups and walks that had to be done alone: the
+    words of earlier calls, at other places, are taken for nothing."""
+    from paper_2605_29727_amd import binding as btv
+    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(24, 131072, True))
+    cases = [(V, args, ref) for V in (1500, 5000, 30001, 131072) for args, ref in _walk_cases(oracle, V, "fp32")]
+    assert len(cases) >= 6
+    for turn in range(3):
+        for k, (V, args, ref) in enumerate(cases[turn:] + cases[:turn]):
+            got = G.run_accept_stochastic(*args, tuned=((0, 3, 17)[(turn + k) % 3], -1 if k % 4 == 3 else 1000000), ws=ws)
+            assert _same(got, ref) and got["status"] == 0, (turn, V)
