@@ -61,9 +61,18 @@ struct Args {
         if (v == -1 && PyErr_Occurred()) throw Raised();
         return v;
     }
-    int int32()
+    int int32() { return narrow(integer()); }
+    int converted_int32()                               // what int(x) makes of the argument
     {
-        const long long v = integer();
+        PyObject *o = PyNumber_Long(next());
+        if (!o) throw Raised();
+        const long long v = PyLong_AsLongLong(o);
+        Py_DECREF(o);
+        if (v == -1 && PyErr_Occurred()) throw Raised();
+        return narrow(v);
+    }
+    static int narrow(long long v)
+    {
         if (v != (int)v) raise(PyExc_OverflowError, "integer argument out of range");
         return (int)v;
     }
@@ -184,7 +193,7 @@ FACE(tree_build_batch)
         const float *marg = pointer<float>(m);
         const int batch = size(m, 0), B = size(m, 1), V = size(m, 2);
         const int32_t *n_nodes = next_pointer<int32_t>(a), *q_offset = next_pointer<int32_t>(a);
-        const int N = a.int32();
+        const int N = a.converted_int32();
         auto *parent = next_pointer<int32_t>(a), *token = next_pointer<int32_t>(a), *depth = next_pointer<int32_t>(a);
         auto *rho = next_pointer<float>(a);
         auto *n_out = next_pointer<int32_t>(a);
@@ -292,7 +301,7 @@ FACE(tree_accept_greedy_batch)
         const int32_t *parent = next_pointer<int32_t>(a), *token = next_pointer<int32_t>(a);
         const at::Tensor &qo = a.tensor();
         const int32_t *q_offset = pointer<int32_t>(qo);
-        const int batch = (int)qo.numel() - 1, total_M = size(l, 0) - batch, M_max = a.int32();
+        const int batch = (int)qo.numel() - 1, total_M = size(l, 0) - batch, M_max = a.converted_int32();
         auto *path = next_pointer<int32_t>(a), *n_acc = next_pointer<int32_t>(a), *bonus = next_pointer<int32_t>(a);
         auto *argmax_out = next_pointer<int32_t>(a);
         const Workspace ws = next_workspace(a);
@@ -376,11 +385,13 @@ FACE(kv_commit_paged)
         auto *new_len = next_pointer<int32_t>(a);
         void *ws = next_pointer(a);
         const int32_t *q_offset = next_pointer<int32_t>(a);
-        int M_max = a.int32(), total_M = 0;
+        int M_max = 0, total_M = 0;
         if (q_offset) {
+            M_max = a.converted_int32();
             total_M = (int)p.numel();
             require(M_max >= 1, "M_max must be given with q_offset");
         } else {
+            a.next();
             M_max = size(p, 1);
         }
         const int layers = size(k, 0), blocks = size(k, 1), bytes = row_bytes(k, 3), batch = size(bt, 0), max_blocks = size(bt, 1);

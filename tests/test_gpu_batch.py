@@ -200,3 +200,31 @@ def test_accept_batch_flags_request_reaching_past_the_arrays():
     torch.cuda.synchronize()
     assert btv.btv_workspace_status(ws) == btv.BTV_EDATA
     assert int(n_acc[1].item()) == 0 and int(n_acc[0].item()) >= 0
+
+
+@pytest.mark.parametrize("number", [float, np.int64, np.float32, str, lambda n: __import__("torch").tensor(n)])
+def test_bounds_are_taken_as_int_takes_them(number):
+    """N_max and M_max of the batch calls are whatever int() makes a number of; kv_commit_paged does not look at M_max without
+    q_offset."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    B, V, N = 2, 40, 5
+    i32 = lambda *v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    zeros = lambda n, dtype=torch.int32: torch.zeros(n, dtype=dtype, device="cuda")
+    marg = torch.softmax(torch.randn((1, B, V), device="cuda"), -1).contiguous()
+    qo, parent, token, n_out = i32(0, N), zeros(N), zeros(N), zeros(1)
+    btv.btv_tree_build_batch(marg, i32(N), qo, number(N), parent, token, None, None, n_out, None,
+                             btv.alloc_workspace(btv.btv_tree_build_batch_workspace(1, B, V, N)))
+    path, n_acc, bonus, argmax = zeros(N), zeros(1), zeros(1), zeros(N + 1)
+    logits = torch.randn((N + 1, V), device="cuda")
+    btv.btv_tree_accept_greedy_batch(logits, parent, token, qo, number(N), path, n_acc, bonus, argmax,
+                                     btv.alloc_workspace(btv.btv_tree_accept_batch_workspace(1, N, V)))
+    assert int(n_out) == N and torch.equal(argmax.long(), logits.argmax(-1))
+    K, L = torch.randn((1, 2, 16, 1, 64), device="cuda"), 3
+    want = K.clone()
+    want[0, 0, L] = K[0, 0, L + 2]
+    for q_offset, M_max in ((qo, number(N)), (None, None)):
+        k, v, new_len = K.clone(), K.clone(), zeros(1)
+        btv.btv_kv_commit_paged(k, v, i32(0, 1).view(1, 2), i32(L), i32(2, 0, 0, 0, 0) if q_offset is not None else i32(2, 0, 0, 0, 0).view(1, N),
+                                i32(1), new_len, None, q_offset, M_max)
+        assert torch.equal(k[0, 0, :L + 1], want[0, 0, :L + 1]) and torch.equal(v, k) and int(new_len) == L + 1
