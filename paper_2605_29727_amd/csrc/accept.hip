@@ -504,7 +504,7 @@ __global__ __launch_bounds__(GW_WAVES * 64) void greedy_walk(const Best *part, i
 // matrix cores and reduced to one (value, token) pair per row and workgroup: the logits never reach
 // memory, the 2*V*h bytes of W are streamed once.
 //
-// Transposed product, C^T = W_tile * H^T (v_mfma_f32_32x32x16_bf16): a wave owns TV tiles of 32
+// Transposed product, C^T = W_tile * H^T (v_mfma_f32_32x32x16_bf16): a wave owns 32
 // vocabulary rows and every row of H, so a lane's accumulator registers run over vocabulary rows of
 // one H row and the argmax is a per-lane scan.  The operand layout wants lane l to hold row l % 32,
 // which as a direct load would touch 64 cache lines per instruction and use 16 bytes of each;
@@ -519,11 +519,11 @@ typedef unsigned int lm_u32x4 __attribute__((ext_vector_type(4)));
 
 // VW waves side by side over the vocabulary times KW over the contraction (each takes every KW-th block of it, with a
 // slab of H of its own; the sums meet in LDS at the end).
-template <int RT, int VW, int KW, int KB, int TV>
+template <int RT, int VW, int KW, int KB>
 struct LmShape {
     static constexpr int WAVES = VW * KW, THREADS = WAVES * 64, ROWS = RT * 32;
     static constexpr int GT = VW * 64;                    // threads that share a slab
-    static constexpr int VROWS = TV * 32;                 // vocabulary rows of a wave
+    static constexpr int VROWS = 32;                      // vocabulary rows of a wave
     static constexpr int RB = KB * 2;                     // bytes of a tile row
     static constexpr int CPR = RB / 16;                   // 16-byte chunks per row
     static constexpr int WTILE = VROWS * RB, SLAB = ROWS * RB;
@@ -531,7 +531,7 @@ struct LmShape {
     static constexpr int WLD = VROWS * CPR / 64;          // load instructions per wave and block for W
     static constexpr int HLD = (ROWS * CPR + GT - 1) / GT;             // chunks of the H slab per thread and block
     static constexpr bool HEVEN = ROWS * CPR % GT == 0;
-    static constexpr int SUMS = (KW - 1) * VW * TV * RT * 16 * 64 * 4; // accumulators handed over at the end
+    static constexpr int SUMS = (KW - 1) * VW * RT * 16 * 64 * 4; // accumulators handed over at the end
     static_assert(CPR == 8 || CPR == 16, "KB is 64 or 128");
     static_assert(LDS_BYTES <= 160 * 1024 && SUMS <= LDS_BYTES, "LDS of a CU");
     // byte offset of 16-byte chunk `col` of tile row `row`: 16 lanes reading one chunk index of 16 consecutive
@@ -542,87 +542,76 @@ struct LmShape {
     }
 };
 
-// One block of the contraction for a wave: KB / 16 steps of TV + RT operand reads and TV * RT MFMAs.  Here the
+// One block of the contraction for a wave: KB / 16 steps of 1 + RT operand reads and RT MFMAs.  Here the
 // reads are raw instructions with hand-placed waits (as ordinary loads each is waited for right before its MFMA,
 // which leaves the matrix core idle for an LDS round trip): the reads of step j + 1 are issued before the MFMAs
 // of step j, and the in-order counter tells when step j's have landed.
-template <int RT, int TV>
-__device__ __forceinline__ void lm_read_step(uint32_t wt, uint32_t hb, int tile_bytes, lm_u32x4 (&a)[TV], lm_u32x4 (&b)[RT])
+template <int RT>
+__device__ __forceinline__ void lm_read_step(uint32_t wt, uint32_t hb, int tile_bytes, lm_u32x4 &a, lm_u32x4 (&b)[RT])
 {
-#pragma unroll
-    for (int tv = 0; tv < TV; ++tv)
-        asm volatile("ds_read_b128 %0, %1" : "=v"(a[tv]) : "v"(wt + (uint32_t)(tv * tile_bytes)) : "memory");
+    asm volatile("ds_read_b128 %0, %1" : "=v"(a) : "v"(wt) : "memory");
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
         asm volatile("ds_read_b128 %0, %1" : "=v"(b[rt]) : "v"(hb + (uint32_t)(rt * tile_bytes)) : "memory");
 }
 
-template <int RT, int TV, int YOUNGER>
-__device__ __forceinline__ void lm_wait_step(lm_u32x4 (&a)[TV], lm_u32x4 (&b)[RT])
+template <int RT, int YOUNGER>
+__device__ __forceinline__ void lm_wait_step(lm_u32x4 &a, lm_u32x4 (&b)[RT])
 {
     static_assert(YOUNGER >= 0 && YOUNGER <= 15, "lgkmcnt range");
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(YOUNGER) : "memory");
-#pragma unroll
-    for (int tv = 0; tv < TV; ++tv) asm volatile("" : "+v"(a[tv]));     // uses below may not move above the wait
+    asm volatile("" : "+v"(a));                                         // uses below may not move above the wait
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(b[rt]));
 }
 
 // ob = offset of this lane's operand chunk at step 0 within a 32-row tile; step j sits at ob ^ (j << 5)
-template <int RT, int TV, int KB, int RB>
-__device__ __forceinline__ void lm_multiply(uint32_t wt, uint32_t hb, uint32_t ob, lm_f32x16 (&acc)[TV][RT])
+template <int RT, int KB, int RB>
+__device__ __forceinline__ void lm_multiply(uint32_t wt, uint32_t hb, uint32_t ob, lm_f32x16 (&acc)[RT])
 {
-    constexpr int STEPS = KB / 16, N = TV + RT;
+    constexpr int STEPS = KB / 16, N = 1 + RT;
     static_assert(N <= 15, "lgkmcnt range");
-    lm_u32x4 a[2][TV], b[2][RT];
-    lm_read_step<RT, TV>(wt + ob, hb + ob, 32 * RB, a[0], b[0]);
+    lm_u32x4 a[2], b[2][RT];
+    lm_read_step<RT>(wt + ob, hb + ob, 32 * RB, a[0], b[0]);
 #pragma unroll
     for (int j = 0; j < STEPS; ++j) {
         if (j + 1 < STEPS) {
             const uint32_t o = ob ^ (uint32_t)((j + 1) << 5);
-            lm_read_step<RT, TV>(wt + o, hb + o, 32 * RB, a[(j + 1) & 1], b[(j + 1) & 1]);
-            lm_wait_step<RT, TV, N>(a[j & 1], b[j & 1]);
+            lm_read_step<RT>(wt + o, hb + o, 32 * RB, a[(j + 1) & 1], b[(j + 1) & 1]);
+            lm_wait_step<RT, N>(a[j & 1], b[j & 1]);
         } else {
-            lm_wait_step<RT, TV, 0>(a[j & 1], b[j & 1]);
+            lm_wait_step<RT, 0>(a[j & 1], b[j & 1]);
         }
 #pragma unroll
-        for (int tv = 0; tv < TV; ++tv)
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                acc[tv][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a[j & 1][tv]),
-                                                                      __builtin_bit_cast(lm_bf16x8, b[j & 1][rt]),
-                                                                      acc[tv][rt], 0, 0, 0);
+        for (int rt = 0; rt < RT; ++rt)
+            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a[j & 1]),
+                                                              __builtin_bit_cast(lm_bf16x8, b[j & 1][rt]), acc[rt], 0, 0, 0);
     }
 }
 
 // The same block with ordinary loads, scheduled by the compiler: leaner in registers, used when the accumulators
 // of many row tiles leave no room for a second set of operands.
-template <int RT, int TV, int KB, int RB>
+template <int RT, int KB, int RB>
 __device__ __forceinline__ void lm_multiply_plain(const unsigned char *wt, const unsigned char *hb, uint32_t ob,
-                                                  lm_f32x16 (&acc)[TV][RT])
+                                                  lm_f32x16 (&acc)[RT])
 {
 #pragma unroll
     for (int j = 0; j < KB / 16; ++j) {
         const uint32_t o = ob ^ (uint32_t)(j << 5);
-        lm_u32x4 a[TV];
-#pragma unroll
-        for (int tv = 0; tv < TV; ++tv) a[tv] = *reinterpret_cast<const lm_u32x4 *>(wt + tv * 32 * RB + o);
+        const lm_u32x4 a = *reinterpret_cast<const lm_u32x4 *>(wt + o);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const lm_u32x4 b = *reinterpret_cast<const lm_u32x4 *>(hb + rt * 32 * RB + o);
-#pragma unroll
-            for (int tv = 0; tv < TV; ++tv)
-                acc[tv][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a[tv]),
-                                                                      __builtin_bit_cast(lm_bf16x8, b), acc[tv][rt], 0, 0, 0);
+            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(lm_bf16x8, a), __builtin_bit_cast(lm_bf16x8, b), acc[rt], 0, 0, 0);
         }
     }
 }
 
-template <int RT, int VW, int KW, int KB, int TV, bool RAW>
+template <int RT, int VW, int KW, int KB, bool RAW>
 __global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_argmax(
     const uint16_t *__restrict__ H, const uint16_t *__restrict__ W, int R, int h, int V, int chunks, int groups, Best *__restrict__ part)
 {
-    using S = LmShape<RT, VW, KW, KB, TV>;
+    using S = LmShape<RT, VW, KW, KB>;
     extern __shared__ __align__(16) unsigned char lm_lds[];
     // Workgroup = a chunk of the vocabulary times a group of rows; the groups of one chunk stream the same weights and
     // get ids that are congruent mod 8, i.e. one XCD's L2.
@@ -668,13 +657,11 @@ __global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     // at(r32, half) ^ (j << 5): the swizzle is an XOR and 2j + half = 2j ^ half
     const uint32_t ob = (uint32_t)S::at(r32, half);
 
-    lm_f32x16 acc[TV][RT];
+    lm_f32x16 acc[RT];
 #pragma unroll
-    for (int tv = 0; tv < TV; ++tv)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[tv][rt][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
 
     // Workgroups start at different blocks of the contraction and wrap round: rows of W are a multiple of 4 KB
     // apart, so workgroups marching in step would all hit the same few memory channels.
@@ -708,8 +695,8 @@ __global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t wt_addr = lds0 + wave * S::WTILE, slab_addr = lds0 + S::WAVES * S::WTILE + kw * 2 * S::SLAB;
 #define LM_MULTIPLY(sl)                                                                                      \
     {                                                                                                        \
-        if constexpr (RAW) lm_multiply<RT, TV, KB, S::RB>(wt_addr, slab_addr + (sl) * S::SLAB, ob, acc);     \
-        else lm_multiply_plain<RT, TV, KB, S::RB>(wtile, slab + (sl) * S::SLAB, ob, acc);                    \
+        if constexpr (RAW) lm_multiply<RT, KB, S::RB>(wt_addr, slab_addr + (sl) * S::SLAB, ob, acc);         \
+        else lm_multiply_plain<RT, KB, S::RB>(wtile, slab + (sl) * S::SLAB, ob, acc);                        \
     }
 
     // While block t is multiplied from LDS, the weights of blocks t + 1 and t + 2 are in registers or on their way
@@ -749,26 +736,22 @@ __global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
 
     // per-lane scan over the 16 vocabulary rows of a tile that it holds (ascending), other half, then the waves
     if constexpr (KW > 1) {                                 // the sums of the other parts of the contraction
-        float *ex = reinterpret_cast<float *>(lm_lds) + vw * (TV * RT * 16 * 64) + lane;
-        constexpr int PLANE = VW * TV * RT * 16 * 64;
+        float *ex = reinterpret_cast<float *>(lm_lds) + vw * (RT * 16 * 64) + lane;
+        constexpr int PLANE = VW * RT * 16 * 64;
         if (kw > 0) {
 #pragma unroll
-            for (int tv = 0; tv < TV; ++tv)
+            for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ex[(kw - 1) * PLANE + ((tv * RT + rt) * 16 + e) * 64] = acc[tv][rt][e];
+                for (int e = 0; e < 16; ++e) ex[(kw - 1) * PLANE + (rt * 16 + e) * 64] = acc[rt][e];
         }
         __syncthreads();
         if (kw == 0) {
 #pragma unroll
             for (int k = 0; k < KW - 1; ++k)
 #pragma unroll
-                for (int tv = 0; tv < TV; ++tv)
+                for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[tv][rt][e] += ex[k * PLANE + ((tv * RT + rt) * 16 + e) * 64];
+                    for (int e = 0; e < 16; ++e) acc[rt][e] += ex[k * PLANE + (rt * 16 + e) * 64];
         }
         __syncthreads();
     }
@@ -779,12 +762,10 @@ __global__ __launch_bounds__(VW * KW * 64) __attribute__((amdgpu_waves_per_eu(2,
     for (int rt = 0; rt < RT; ++rt) {
         Best b = { -INFINITY, INT_MAX };
 #pragma unroll
-        for (int tv = 0; tv < TV; ++tv)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int v = v0 + tv * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-                if (v < V) best_take(b, acc[tv][rt][e], v);
-            }
+        for (int e = 0; e < 16; ++e) {
+            const int v = v0 + (e >> 2) * 8 + half * 4 + (e & 3);
+            if (v < V) best_take(b, acc[rt][e], v);
+        }
         const float ov = __shfl_xor(b.v, 32);
         const int oi = __shfl_xor(b.i, 32);
         best_take(b, ov, oi);
@@ -887,9 +868,9 @@ inline int lm_chunks(const LmPlan &p, int V) { return (V + p.vw * 32 - 1) / (p.v
 template <int RT, int VW, int KW, int KB, bool RAW>
 int lm_head_launch(const uint16_t *H, const uint16_t *W, int R, int h, int V, Best *part, hipStream_t st)
 {
-    using S = LmShape<RT, VW, KW, KB, 1>;
+    using S = LmShape<RT, VW, KW, KB>;
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
-    auto kern = lm_head_argmax<RT, VW, KW, KB, 1, RAW>;
+    auto kern = lm_head_argmax<RT, VW, KW, KB, RAW>;
     if (!configured.load(std::memory_order_acquire)) {
         BTV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     S::LDS_BYTES));

@@ -59,8 +59,6 @@ struct AttnParams {
     float out_scale;              // 1, or the value scale of an FP8 cache
 };
 
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
-
 __device__ __forceinline__ uint32_t float_to_bf16_bits(float f)
 {   // round to nearest even; inputs here are finite
     uint32_t u = __float_as_uint(f);
@@ -111,21 +109,17 @@ __device__ __forceinline__ uint32_t vis_word(const AncT &anc, int kb, int L)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Ancestor bitmask: anc[i] = {i} u anc[parent[i]].  One workgroup per request, one thread per node,
+// Ancestor bitmask: anc[i] = {i} u anc[parent[i]].  One workgroup, one thread per node,
 // each walking its own chain (parents are strictly decreasing, so the walk ends; an out-of-range
 // parent is treated as -1 and flagged).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void anc_mask_kernel(const int32_t *parent, const int32_t *q_offset, int M_max,
-                                                       int total_M, uint32_t *anc, uint32_t *flag)
+__global__ __launch_bounds__(256) void anc_mask_kernel(const int32_t *parent, int M, uint32_t *anc, uint32_t *flag)
 {
     __shared__ int32_t par[BTV_MAX_NODES];
-    int r = blockIdx.x, i = threadIdx.x;
-    int q0 = q_offset ? q_offset[r] : 0;
-    int M = q_offset ? q_offset[r + 1] - q0 : M_max;
-    if (M < 1 || M > M_max || q0 < 0 || q0 + M > total_M) return;   // flagged by the attention kernel's own check
+    int i = threadIdx.x;
     bool bad = false;
     if (i < M) {
-        int pa = parent[q0 + i];
+        int pa = parent[i];
         if (pa < -1 || pa >= i) { bad = true; pa = -1; }
         par[i] = pa;
     }
@@ -139,7 +133,7 @@ __global__ __launch_bounds__(256) void anc_mask_kernel(const int32_t *parent, co
             for (int k = 0; k < BTV_ANC_WORDS; ++k)
                 if ((a >> 5) == k) w[k] |= 1u << (a & 31);
         }
-        uint4 *dst = reinterpret_cast<uint4 *>(anc + (size_t)(q0 + i) * BTV_ANC_WORDS);
+        uint4 *dst = reinterpret_cast<uint4 *>(anc + (size_t)i * BTV_ANC_WORDS);
         dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
         dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
     }
@@ -758,8 +752,8 @@ struct WgLds {
     static constexpr int PAROFF = KW == 1 ? (RING > QOFF + QBYTES ? RING : QOFF + QBYTES) : (QOFF - PRE_B >= 1024 ? PRE_B : QOFF + QBYTES);
     static constexpr int USED = (PAROFF + 1024 > QOFF + QBYTES ? PAROFF + 1024 : QOFF + QBYTES) > RING
                                     ? (PAROFF + 1024 > QOFF + QBYTES ? PAROFF + 1024 : QOFF + QBYTES) : RING;
-    // two key-waves exchange half a row each (+ m, l, bound); more key-waves: donors to wave 0
-    static constexpr int MERGE = KW == 2 ? RW * 2 * ((D / 64) * 16 + 3) * 64 * 4 : RW * (KW - 1) * ((D / 32) * 16 + 2) * 64 * 4;
+    static_assert(KW == 1 || KW == 2, "the merge is between two key-waves");
+    static constexpr int MERGE = KW == 2 ? RW * 2 * ((D / 64) * 16 + 3) * 64 * 4 : 0;    // they exchange half a row each (+ m, l, bound)
     static constexpr int BYTES = USED > MERGE ? USED : MERGE;
     static_assert(QOFF % 1024 == 0 && PAROFF % 1024 == 0 && BYTES <= 160 * 1024, "LDS budget");
     static_assert(BTV_MAX_NODES * 4 <= 1024, "parent[] staging");
@@ -817,9 +811,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     constexpr int WR = RW * 32;
     constexpr int DS = D / 16;
     constexpr int DT = D / 32;
-    // Waves that issue the ring fills.
-    constexpr int IW = WAVES;
-    constexpr int LPW = Lds<D, EB>::INSTR / IW;
+    constexpr int LPW = Lds<D, EB>::INSTR / WAVES;       // fill instructions per wave and tile
     constexpr int AHEAD = NT - 2 * KW;            // tiles still in flight when a round's tiles have landed
     static_assert(AHEAD >= 0 && AHEAD * LPW < 64, "ring too small or too deep for the counter");
     using LD = Lds<D, EB>;
@@ -876,8 +868,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 
     // ---- start filling the ring ------------------------------------------------------------------------
     const int wu = __builtin_amdgcn_readfirstlane(w);
-    const bool issuer = wu < IW;
-    Fill<D, IW, PAGED, EB> fill = make_fill<D, IW, PAGED, EB>(p.K, p.V, bt_row, p.num_blocks, p.Hkv, g, S, issuer ? wu : 0, l);
+    Fill<D, WAVES, PAGED, EB> fill = make_fill<D, WAVES, PAGED, EB>(p.K, p.V, bt_row, p.num_blocks, p.Hkv, g, S, wu, l);
     // KW == 1: three tiles up front (the first compute needs two), the rest of the ring fills during the first
     // rounds; an issue holds its wave for about a hundred cycles, so a full prefill would only delay the start.
     constexpr int PREFILL = WL::PREFILL;
@@ -885,13 +876,13 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
     for (int k = 0; k < PREFILL; ++k)
         if (issued < st1) {
-            if (issuer) issue_tile<D, IW, PAGED, EB>(fill, smem, islot, issued, wu, l);
+            issue_tile<D, WAVES, PAGED, EB>(fill, smem, islot, issued, wu, l);
             ++issued; ++islot;
         }
     if (islot >= NT) islot -= NT;
 
     // ---- parent[] and the query tile have landed when only the ring fills are in flight ------------------------
-    wait_vm_ops<PREFILL * LPW>(issuer ? (issued - st0) * LPW : 0);
+    wait_vm_ops<PREFILL * LPW>((issued - st0) * LPW);
     // A bare barrier, and raw LDS reads below: with the fence of a full synchronisation, or with ordinary reads of
     // memory that direct-to-LDS loads wrote, the compiler drains the ring fills first.
     __builtin_amdgcn_s_barrier();                    // query tiles (filled by KW waves), parent[] and the page windows are visible
@@ -978,7 +969,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     auto issue_one = [&]() {                             // the next tile of this split, if there is one
         if (issued < st1) {
             next_window();
-            if (issuer) issue_tile<D, IW, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
+            issue_tile<D, WAVES, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
             ++issued;
             if (++islot == NT) islot = 0;
         }
@@ -988,7 +979,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         constexpr int P = decltype(part)::value;
         constexpr int MID = (LPW + 1) / 2, JB = P == 0 ? 0 : MID, JE = P == 0 ? MID : LPW;
         if constexpr (JB < JE)
-            if (issuer) issue_tile<D, IW, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l);
+            issue_tile<D, WAVES, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l);
     };
     if constexpr (KW == 1) {
         // Every wave has its queries in registers and parent[] is consumed: the ring owns all stages from here on.
@@ -1220,7 +1211,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             do_tile<D>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, true);
         }
         if constexpr (PAGED) wait_vmcnt<0>();
-    } else if constexpr (KW > 1) {
+    } else {
         // ---- main loop: one barrier per round of KW tiles, wave kw takes tile number kw of the round ------
         // At the top of the round starting at tile st, tiles st+KW .. issued-1 may still be in flight.  The
         // barrier also tells that every wave is done with the previous round, whose KW ring slots the next
@@ -1237,7 +1228,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             for (int k = 0; k < KW; ++k)
                 if (issued < st1) {
                     next_window();
-                    issue_tile<D, IW, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
+                    issue_tile<D, WAVES, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
                     ++issued;
                     if (++islot == NT) islot = 0;
                 }
@@ -1307,40 +1298,9 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         };
         if (kw == 0) take(std::integral_constant<int, 0>{}); else take(std::integral_constant<int, DTK>{});
         dt0 = kw * DTK;                             // the kept blocks now sit in oacc[0 .. DTK)
-    } else if (KW > 1) {                            // donors write side by side, wave kw = 0 reduces
-        constexpr int SLOT = (DT * 16 + 2) * 64;    // floats per donor
-        float *mg = reinterpret_cast<float *>(smem) + (rw * (KW - 1)) * SLOT;
-        wait_vmcnt<0>();
-        __syncthreads();                            // every wave is done with the ring
-        if (kw > 0) {
-            float *d = mg + (kw - 1) * SLOT;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) d[(dt * 16 + v) * 64 + l] = oacc[dt][v];
-            d[(DT * 16) * 64 + l] = m_run;
-            d[(DT * 16 + 1) * 64 + l] = l_run;
-        }
-        __syncthreads();
-        if (kw == 0) {
-#pragma unroll
-            for (int donor = 0; donor < KW - 1; ++donor) {
-                const float *d = mg + donor * SLOT;
-                const float m1 = d[(DT * 16) * 64 + l], l1 = d[(DT * 16 + 1) * 64 + l];
-                const float mn = fmaxf(m_run, m1);
-                const float a0 = __builtin_amdgcn_exp2f(m_run - mn);
-                const float a1 = __builtin_amdgcn_exp2f(m1 - mn);
-                m_run = mn;
-                l_run = l_run * a0 + l1 * a1;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) oacc[dt][v] = oacc[dt][v] * a0 + d[(dt * 16 + v) * 64 + l] * a1;
-            }
-        }
     }
-    if ((KW != 2 && kw != 0) || !rvalid) return;
-    if constexpr (KW != 2) {
+    if (!rvalid) return;
+    if constexpr (KW == 1) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1963,7 +1923,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
 struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; };
 
 // Splits of `want` parts for a shape.
-void split_plan(Plan &pl, int M, int L, int want)
+void split_plan(Plan &pl, int L, int want)
 {
     // Tiles that hold tree rows cost more than plain tiles (mask; in the pipelined loop also a second row maximum)
     // and all sit in the last split: sizing the splits as if there were `extra` more tiles leaves the last one
@@ -2007,7 +1967,7 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
         pl.row_blocks = (rows_g + pl.wr - 1) / pl.wr;
         pl.stages = (L + M + TK - 1) / TK;
         auto consider = [&](int want) {
-            split_plan(pl, M, L, want);
+            split_plan(pl, L, want);
             const int n = pl.nsplit, wgs = (n * Hkv + 7) / 8 * 8 * pl.row_blocks;         // (as many as the fullest XCD has, times 8)
             const float cap = k == 0 ? 512.f : 256.f, fill = wgs / cap;
             const float rounds = 0.45f * std::ceil(fill) + 0.55f * std::max(1.f, fill);
@@ -2249,16 +2209,7 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
 
 }  // namespace
 
-int btv_launch_anc_mask(const int32_t *parent, const int32_t *q_offset, int batch, int M_max, int total_M,
-                        uint32_t *anc, uint32_t *flag, hipStream_t st)
-{
-    hipLaunchKernelGGL(anc_mask_kernel, dim3(batch), dim3(256), 0, st, parent, q_offset, M_max, total_M, anc, flag);
-    BTV_HIP(hipGetLastError());
-    return BTV_OK;
-}
-
 extern "C" {
-
 
 int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws, size_t ws_bytes, void *stream)
 {
@@ -2266,8 +2217,9 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
     BTV_REQUIRE(M >= 1 && M <= BTV_MAX_NODES, "M=%d outside [1,%d]", M, BTV_MAX_NODES);
     int rc = btv_check_ws(ws, ws_bytes, BTV_WS_HEADER);
     if (rc) return rc;
-    return btv_launch_anc_mask(parent, nullptr, 1, M, M, anc, static_cast<uint32_t *>(ws),
-                               static_cast<hipStream_t>(stream));
+    hipLaunchKernelGGL(anc_mask_kernel, dim3(1), dim3(256), 0, static_cast<hipStream_t>(stream), parent, M, anc, static_cast<uint32_t *>(ws));
+    BTV_HIP(hipGetLastError());
+    return BTV_OK;
 }
 
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype)

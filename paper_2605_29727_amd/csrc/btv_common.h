@@ -36,8 +36,4 @@ static inline int btv_check_ws(const void *ws, size_t have, size_t need)
     return BTV_OK;
 }
 
-// ---- internal launchers (defined in the .hip files) --------------------------------------------
-int btv_launch_anc_mask(const int32_t *parent, const int32_t *q_offset, int batch, int M_max, int total_M,
-                        uint32_t *anc, uint32_t *flag, hipStream_t st);
-
 size_t btv_stochastic_workspace(int V);         // bytes btv_tree_accept_stochastic needs

@@ -76,17 +76,6 @@ __device__ __forceinline__ int wave_incl_scan(int x)
     return x;
 }
 
-__device__ __forceinline__ int wave_incl_max(int x)               // the same with max, for values >= 0
-{
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));
-    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));
-    return x;
-}
-
 // The ranked lists travel from the workgroups that rank to the one that expands through memory, within one launch and
 // between compute dies whose L2 caches do not see each other: they are written and read as relaxed device-scope
 // atomics, which go through to memory, and the writer waits for its stores before it counts itself as done.
@@ -450,7 +439,6 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
     }
     int n = 0;
     double run_a = 1.0, best_a = 0.0, best_c = 0.0;            // Ahat so far; Ahat and cost at the best budget so far
-    bool stop = false;
     auto phase = [&](auto ra_c, int n_end) {
         constexpr int RA = decltype(ra_c)::value;
         while (n < n_end) {
@@ -460,15 +448,14 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
     #pragma unroll
             for (int r = 1; r < RA; ++r) lm = umax(lm, e_key[r]);
             const uint32_t m = wave_max_u32(lm);
-            if (__builtin_expect(m == 0u, 0)) { stop = true; break; }     // frontier empty: the lattice is exhausted
+            if (__builtin_expect(m == 0u, 0)) break;     // frontier empty: the lattice is exhausted
             if (ADAPT) {
                 const double a_new = run_a + (double)__uint_as_float(m - 1u);
                 if (__builtin_expect(!(c_n > 0.0), 0)) {           // invalid cost: stop here and tell
                     if (lane == 0) atomicOr(ad.flag, 4u);
-                    stop = true;
                     break;
                 }
-                if (n > 0 && !(a_new * best_c > best_a * c_n)) { stop = true; break; }   // the estimated speedup did not improve
+                if (n > 0 && !(a_new * best_c > best_a * c_n)) break;   // the estimated speedup did not improve
                 run_a = a_new; best_a = a_new; best_c = c_n;
             }
             u64 al[RA];
