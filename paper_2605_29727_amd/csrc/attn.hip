@@ -20,6 +20,7 @@
 #include <atomic>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -784,6 +785,25 @@ __device__ __forceinline__ LaneRow lane_row(int r, int rows_g, int G, int Hq, in
     return x;
 }
 
+// Largest finite magnitude of a lane's values: what its row's partials are divided by.  (An infinite one, from a value in the
+// cache or a sum past the end of fp32, would leave nothing of the row's other channels.)
+template <int B> __device__ __forceinline__ float finite_max(const f32x16 (&x)[B])
+{
+    float a = 0.f;
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) a = fmaxf(a, fabsf(x[b][v]));
+    if (__builtin_amdgcn_ballot_w64(a > FLT_MAX) != 0ull) {        // (rare)
+        a = 0.f;
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) a = fabsf(x[b][v]) <= FLT_MAX ? fmaxf(a, fabsf(x[b][v])) : a;
+    }
+    return fmaxf(a, __shfl_xor(a, 32));             // the other half of the wave holds the row's other channels
+}
+
 // What one workgroup does in one go: rows of row block `by` of (request, KV head g) against the tiles st0 .. st1 - 1.
 struct Piece {
     int rq, g, by, st0, st1;
@@ -1258,11 +1278,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     if constexpr (KW == 2) {
         constexpr int SLOT = (DTK * 16 + 3) * 64;   // floats a wave hands over
         float *mg = reinterpret_cast<float *>(smem) + rw * 2 * SLOT;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) amax = fmaxf(amax, fabsf(oacc[dt][v]));
-        amax = fmaxf(amax, __shfl_xor(amax, 32));   // the other half of the wave holds the row's other channels
+        amax = finite_max<DT>(oacc);
         wait_vmcnt<0>();
         __syncthreads();                            // every wave is done with the ring
         float *out = mg + kw * SLOT;
@@ -1288,7 +1304,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         const float xa = kw == 0 ? amax * a0 : x1 * a1, xb = kw == 0 ? x1 * a1 : amax * a0;
         m_run = mn;
         l_run = la + lb;
-        amax = xa + xb;                             // >= the merged row's largest magnitude, at most twice it
+        amax = fminf(xa + xb, FLT_MAX);             // >= the merged row's largest (finite) magnitude, at most twice it
         auto take = [&](auto first) {
             constexpr int F = decltype(first)::value;
 #pragma unroll
@@ -1304,8 +1320,8 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { fin[dt][v] = oacc[dt][v]; amax = fmaxf(amax, fabsf(oacc[dt][v])); }
-        amax = fmaxf(amax, __shfl_xor(amax, 32));
+            for (int v = 0; v < 16; ++v) fin[dt][v] = oacc[dt][v];
+        amax = finite_max<DT>(oacc);
     }
 
     // ---- write: final bf16 rows when this request has a single split, scaled fp16 partials otherwise ---

@@ -351,3 +351,48 @@ def test_bf16_random_shapes(G, oracle, seed):
     out = G.run_verify_attn(t, parent, L, "bf16")
     assert np.isfinite(out).all()
     assert np.abs(out - ref).max() <= TOL_BF16, (M, L, Hkv * Gq, Hkv, D, kind, np.abs(out - ref).max())
+
+
+@pytest.mark.parametrize("value", ["inf", "-inf", "nan"])
+@pytest.mark.parametrize("dims", [(64, 700, 8, 2, 128), (70, 1029, 16, 4, 64)])
+def test_bf16_non_finite_values_stay_in_their_channel(G, oracle, dims, value):
+    """An infinite or NaN value in the cache costs a row that channel alone, into however many parts the keys are cut: the
+    partials' scale is the row's largest finite magnitude."""
+    M, L, Hq, Hkv, D = dims
+    parent = synth.tree_parents(5, M, "random")
+    t = synth.qkv(91, M, L, Hq, Hkv, D, "bf16")
+    ref = oracle.tree_attn(t["Qf"], t["Kf"], t["Vf"], parent, L)
+    t["V"][5, 0, 7] = synth.round_to_dtype(np.array([float(value)]), "bf16")[0][0]
+    hit = np.zeros(ref.shape, dtype=bool)
+    hit[:, :Hq // Hkv, 7] = True
+    for shape in (1, 2, 3):
+        for nsplit in (1, 2, 6, 40):
+            out = G.run_verify_attn(t, parent, L, "bf16", nsplit=nsplit, shape=shape)
+            assert not np.isfinite(out[hit]).any(), (shape, nsplit)
+            assert np.abs(out - ref)[~hit].max() <= TOL_BF16, (shape, nsplit)
+
+
+def test_paged_non_finite_values_stay_in_their_channel(G):
+    """The same where a batch's rows come in parts: equal parts of short requests, and parts of an equal share of the work."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    for Ls, Ns in (([5000, 300, 2500], [40, 64, 7]), long_batch(66, 33, 2900, 64)):
+        bt, nb = synth.paged_layout(5, [l + n for l, n in zip(Ls, Ns)])
+        qoff = np.concatenate([[0], np.cumsum(Ns)]).astype(np.int32)
+        torch.manual_seed(0)
+        Q = torch.randn(int(qoff[-1]), 16, 128, device="cuda", dtype=torch.bfloat16)
+        K, V = (torch.randn(nb, synth.PAGE, 2, 128, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        par = G.dev(np.concatenate([np.arange(n) - 1 for n in Ns]).astype(np.int32))
+        ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_workspace(len(Ls), max(Ns), max(Ls), 16, 2, 128))
+        run = []
+        for value in (0.0, float("inf")):
+            V[:, 3, 0, 7] = value                         # a token of every page
+            O = torch.zeros_like(Q)
+            btv.btv_tree_verify_attn_paged(Q, K, V, G.dev(bt), G.dev(qoff), G.dev(np.asarray(Ls, dtype=np.int32)), par, max(Ns), max(Ls), O, ws)
+            run.append(O.float())
+        long_rows = torch.from_numpy(np.repeat(np.asarray(Ls) >= 32, Ns)).cuda()
+        assert not run[1][long_rows, :8, 7].isfinite().any()
+        for x in run:
+            x[:, :8, 7] = 0
+        assert (run[0] - run[1]).abs().max() <= 2.0 ** -8       # (two bf16 roundings of values below 2, partials scaled otherwise)
+        assert run[0].abs().max() > 0.1
