@@ -33,7 +33,9 @@
 // guesses for all s_k in one exchange, after which the recurrence is affine and is solved by a prefix scan; the guesses come from a table of
 // G at 256 points (one exchange).  The error squares with every exchange (measured on normal logits and marginals:
 // 5e-5 after the table, 1e-9 after one, rounding after two), and the sequence is taken when no s_k moved by more than
-// 1e-7 of itself, i.e. when what is left is below 1e-13; anything that does not converge is walked one by one.
+// 1e-7 of itself: what is left is second order then, below 1e-13, except for tokens whose kink (e = s q) lies within that
+// last move, which E and Q count on the wrong side; such a token leaves at most 1e-7 of s times q / T, of the size of the
+// rounding of e.  Anything that does not converge is walked one by one.
 // For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
 //
 // What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
@@ -854,23 +856,32 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
     return dead;
 }
 
+// The walk alone, in a function of its own that reads the arguments again: what is next to never needed is not to cost the walk above
+// registers, nor to lie in the way of its code (inlined, with the arguments held: 0.5 to 1 us of 25 to 45).
+typedef const __attribute__((address_space(4))) SaParams *SaArgs;
+template <int PT> using SaLds = __attribute__((address_space(3))) SaShared<PT> *;
+template <bool BF16, int PT>
+__device__ __attribute__((noinline, cold)) void sa_walk_alone(SaArgs args, SaLds<PT> L)
+{
+    uint32_t none;
+    sa_walk<BF16, PT, true, true>(*(const SaParams *)args, *(SaShared<PT> *)L, 0, none);
+}
+
 template <bool BF16, int PT, bool OVER>
 __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 {
     __shared__ SaShared<PT> L;
-    uint32_t base, none;
+    uint32_t base;
     if (!sa_walk<BF16, PT, OVER, false>(p, L, blockIdx.x, base)) return;
-    // (the arguments are read again: held through the walk above for what is next to never needed, they cost it registers, 1 us
-    // of 40 where a drafter is mostly followed)
-    auto args = __builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
-    const SaParams &p2 = *(const SaParams *)args;
+    auto again = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(again));
+    const SaArgs args = (SaArgs)again;
     const u64 call = 1ull << 32 | base;
-    if (threadIdx.x == 0) L.status = __hip_atomic_exchange(p2.claim, call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call;
+    if (threadIdx.x == 0) L.status = __hip_atomic_exchange(args->claim, call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call;
     __syncthreads();
     if (!L.status) return;
-    sa_walk<BF16, PT, true, true>(p2, L, 0, none);
-    if (threadIdx.x == 0) sa_move_on(p2.base, base, SA_SPAN);
+    sa_walk_alone<BF16, PT>(args, (SaLds<PT>)&L);
+    if (threadIdx.x == 0) sa_move_on(args->base, base, SA_SPAN);
 }
 
 // Slices for a vocabulary of V tokens on at most `most` workgroups: of 2048 tokens (two per thread) as long as those cover the
