@@ -1,12 +1,13 @@
-// Tree-masked attention for gfx950 (MI355X): ancestor bitmask, bf16 MFMA split-K kernel,
-// fp32 reference-precision kernel, split-K combine, and the two C-ABI entry points.
+// Tree-masked attention for gfx950 (MI355X): ancestor bitmask, bf16 MFMA split-K kernels (one request, batches of short
+// requests, batches whose workgroups share the work out; bf16 or FP8 K/V), fp32 reference-precision kernel, split-K
+// combine, and their C-ABI entry points.
 //
 // What is computed (App. C, "Linearization and verification mask"): node i attends to the L
 // prefix rows of the KV cache and to the tree rows of its ancestors and itself.
 //
 // bf16 kernel layout.  For one KV head the G = Hq/Hkv query heads of every node are packed
 // into rows r = i*G + j, so the whole GQA group shares each K/V byte that is streamed.
-// A workgroup (4 wavefronts of 64 lanes) owns WR rows and a range of 32-key tiles; K and V
+// A workgroup (4 or 8 wavefronts of 64 lanes) owns WR rows and a range of 32-key tiles; K and V
 // tiles are staged through LDS once per workgroup (ring of stages filled by direct-to-LDS loads).
 // Scores are computed transposed, S^T = K . Q^T with 32x32x16 bf16 MFMA: in the accumulator
 // layout a lane then holds ONE query column and 16 keys, so the running max / sum of the
@@ -144,10 +145,10 @@ __global__ __launch_bounds__(256) void anc_mask_kernel(const int32_t *parent, in
 // ------------------------------------------------------------------------------------------------
 // bf16 MFMA kernel
 //
-// LDS holds a ring of NS stages; a stage is one 32-key tile: the K rows and the V rows exactly as
+// LDS holds a ring of NT stages; a stage is one 32-key tile: the K rows and the V rows exactly as
 // they lie in memory ([key][channel], 2*D bytes per row).  Stages are filled by direct-to-LDS
 // global loads (each lane moves 16 bytes, a wave instruction fills 1 KiB of LDS), so no staging
-// registers and no VALU work are spent on data movement and NS-1 stages stay in flight.
+// registers and no VALU work are spent on data movement and up to NT-1 stages stay in flight.
 // Bank conflicts are avoided by choosing which 16-byte chunk of a row each lane fetches: the chunk
 // stored at physical position pc of LDS row r is chunk pc ^ f(r) of the source row.
 //   K: LDS row i holds key kb + swap_bits_2_3(i) (the MFMA A-row order that makes a lane's 16 score

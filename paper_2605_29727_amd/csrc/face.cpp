@@ -1,7 +1,7 @@
 // The calls of the C interface that a decoding loop makes, for Python: torch tensors in, status checked, on the current
 // stream.  Through ctypes a call spent 6 to 9 us here (a Stream object, a pointer object and three attribute look-ups per
-// tensor), about what its kernels take at small sizes; here it is under one.  What is checked, and what is
-// raised, is what binding.py does for the other calls.
+// tensor), about what its kernels take at small sizes; here it is under one, of the 3 to 4 us that a call of one or two
+// launches takes on the host.  What is checked, and what is raised, is what binding.py does for the other calls.
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 

@@ -613,14 +613,14 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
 // about it needs the frontier, nor any order before the end.  The levels are swept once with a threshold that only
 // rises: level d's candidates are the children of level d-1's candidates that score above it (a node deeper than N nodes that
 // score at least as much cannot be among the first N), and after every level the threshold moves up to the lower
-// edge of the bin that holds the N-th best candidate so far (a histogram of the scores' bits, 16 bins per binade, to which every
+// edge of the bin that holds the N-th best candidate so far (a histogram of the scores' bits, 4 bins per binade, to which every
 // candidate is added once; a suffix sum finds the bin).  A child of rank r is not needed either where the product of
 // (rank + 1) along its path exceeds N: that many prefixes of its own level come before it (kept per node as the most
 // children it can have: floor(N / product) = floor(floor(N / parent's product) / (r + 1))).
 // Children take their places in their parents' order, so that a candidate's index grows with the depth and, within a level, with
 // the rank path: score and index are the emission order's whole key.  At the end the candidates of the bins that
-// are left, N of them and the few that share the last bin, are put in order: bin after bin by the histogram, and
-// within a bin by counting.
+// are left, N of them and the few that share the last bin, are put in order: bin after bin by a finer histogram (16 per
+// binade), and within a bin by counting.
 // A thin level is one wavefront's work, 64 nodes at a time: what it costs is the length of its chain of steps, of which workgroup
 // barriers and the LDS words around them would be a good part.  A wide one (the second level of a flat tree, all levels of
 // a small vocabulary's) is the whole workgroup's, 256 nodes at a time, which go to the wavefronts in turn (node 4 l + w to

@@ -239,9 +239,9 @@ def test_config5_stochastic_full_vocab(G, oracle):
 
 @pytest.mark.parametrize("V,fan", [(300, 120), (5000, 200), (40000, 64), (2048 * 64 + 200, 48)])
 def test_stochastic_wide_fans(G, oracle, V, fan):
-    """Nodes with many children take the sorted-ratio path of the walk (prefix sums over the (e, q0) pairs in bins of
-    q0/e): flat marginals give a wide fan under the root, a target close to the draft makes acceptances late in the
-    fan likely, and vocabularies below and above the chunk limits are covered."""
+    """Nodes with many children have their rejections solved together (Newton's method on sums over each slice's tokens, sorted
+    into bins of e/q): flat marginals give a wide fan under the root, a target close to the draft makes acceptances late in the
+    fan likely, and one workgroup, few, and slices of 2048 and of 4096 tokens are covered."""
     B = 3
     checked = 0
     for seed in range(8):
@@ -265,9 +265,8 @@ def test_stochastic_wide_fans(G, oracle, V, fan):
 
 
 def test_stochastic_wide_fan_long_vocabulary(G, oracle):
-    """A vocabulary of 300000: the sorted pairs' prefix sums take chunks of 256 pairs (a power of two, so that the
-    chunk of a position is a shift) and the last chunk is ragged.  With probabilities this small most seeds fall
-    under the ambiguity margins; those that do not must agree."""
+    """A vocabulary of 300000: slices of 8192 tokens, eight per thread where a fan is sorted, and a ragged last one.  With
+    probabilities this small most seeds fall under the ambiguity margins; those that do not must agree."""
     B, V, fan = 3, 300000, 40
     checked = 0
     for seed in range(8):
