@@ -903,6 +903,7 @@ SaPlan sa_plan(int V, int most)
 int usable_cus(hipStream_t st)
 {
     uint32_t mask[32] = {};
+    if (st == hipStreamLegacy) st = nullptr;            // (the other name of the same stream, which the query may not know)
     if (hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
         int n = 0;
         for (uint32_t w : mask) n += __builtin_popcount(w);
