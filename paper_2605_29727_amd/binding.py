@@ -31,7 +31,7 @@ EXPORTS = [
     "btv_tree_accept_workspace",
     "btv_tree_accept_greedy", "btv_tree_accept_stochastic", "btv_tree_accept_lm_head_workspace",
     "btv_tree_accept_greedy_lm_head", "btv_tree_verify_attn_tuned_workspace", "btv_tree_verify_attn_tuned",
-    "btv_tree_verify_attn_noalloc", "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned",
+    "btv_tree_verify_attn_noalloc", "btv_tree_verify_attn_merge_tuned", "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned",
     "btv_tree_accept_stochastic_tuned",
 ]
 
@@ -63,7 +63,7 @@ def lib() -> C.CDLL:
                   "btv_tree_verify_attn", "btv_tree_verify_attn_paged", "btv_tree_verify_attn_fp8kv",
                   "btv_tree_verify_attn_paged_fp8kv", "btv_tree_accept_greedy",
                   "btv_tree_accept_stochastic", "btv_tree_verify_attn_tuned", "btv_tree_verify_attn_noalloc",
-                  "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned", "btv_tree_accept_stochastic_tuned"):
+                  "btv_tree_verify_attn_merge_tuned", "btv_tree_build_tuned", "btv_tree_accept_greedy_tuned", "btv_tree_accept_stochastic_tuned"):
             getattr(L, n).restype = C.c_int
         _lib = L
     return _lib
@@ -262,6 +262,19 @@ def btv_tree_verify_attn_tuned(Q, K, V, parent, L: int, O, ws, scale: float = 0.
                                             C.c_float(v_scale), _ptr(parent), M, L, Hq, Hkv, D, C.c_float(scale),
                                             int(nsplit), int(shape), _ptr(O), _ptr(ws),
                                             C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
+
+
+def btv_tree_verify_attn_merge_tuned(Q, K, V, parent, L: int, O, ws, scale: float = 0.0, nsplit: int = 0, shape: int = 0,
+                                     k_scale: float = 1.0, v_scale: float = 1.0, merge: int = 0, wait_ticks: int = 2000) -> None:
+    """btv_tree_verify_attn_tuned with the merge of the pieces passed as well (include/bastion_tv.h)."""
+    M, Hq, D = Q.shape
+    Hkv = K.shape[1]
+    kv_fp8 = K.element_size() == 1
+    assert K.shape[0] >= L + M and V.shape == K.shape and O.shape == Q.shape and Q.dtype == torch.bfloat16
+    _check(lib().btv_tree_verify_attn_merge_tuned(_ptr(Q), _ptr(K), _ptr(V), 1 if kv_fp8 else 0, C.c_float(k_scale),
+                                                  C.c_float(v_scale), _ptr(parent), M, L, Hq, Hkv, D, C.c_float(scale),
+                                                  int(nsplit), int(shape), int(merge), int(wait_ticks), _ptr(O), _ptr(ws),
+                                                  C.c_size_t(ws.numel() if ws is not None else 0), _stream()))
 
 
 def btv_tree_verify_attn_paged_workspace(batch, M_max, L_max, Hq, Hkv, D) -> int:

@@ -46,6 +46,9 @@ struct AttnParams {
     _Float16 *Opart;              // [nsplit][total_rows][D]: split partial of O^T's row, divided by its largest magnitude
     float *ML;                    // [nsplit][total_rows][4]: reference max, row sum, that magnitude, unused
     uint32_t *flag;
+    unsigned long long *sync;     // one request: words of the merge inside the attention kernel (null: tv_combine_bf16 merges)
+    int wait_ticks;               // ... how long a workgroup waits for the others of its group
+    int apart;                    // ... tests: as if the group were not on one XCD
     int M, L;                     // contiguous: actual sizes; paged: host upper bounds
     int Hq, Hkv, G;
     int max_blocks, num_blocks;
@@ -810,6 +813,8 @@ struct Piece {
     int rq, g, by, st0, st1;
     int bx;                       // which partial of its rows this is
     int direct;                   // the only one: O is written
+    int grouped;                  // its partial is `pitch` rows on end in the place of the group (merge_group)
+    int group, pitch;
 };
 
 // A page window (32 tiles' page ids) per 256 bytes, four of them in turn, behind everything else; not where two workgroups
@@ -824,8 +829,9 @@ struct PageLds {
 
 // Workgroup = RW row-waves x KW key-waves; wave (rw, kw) owns query rows [32 rw, 32 rw + 32) of the block and,
 // in every round of KW consecutive tiles, tile number kw.  LDS ring of NT tiles; one barrier per round.
-template <int D, int RW, int KW, int NT, bool PAGED, int EB>
-__device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *smem, int tid, const Req &rq_, const Piece &pc_)
+// begun(): called once the first loads are on their way (by all threads).
+template <int D, int RW, int KW, int NT, bool PAGED, int EB, typename Begun>
+__device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *smem, int tid, const Req &rq_, const Piece &pc_, Begun begun)
 {
     static_assert(EB == 2 || (EB == 1 && KW >= 2), "FP8 K/V runs in the shapes whose waves alternate over the tiles");
     constexpr int WAVES = RW * KW;
@@ -922,6 +928,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     };
     auto next_window = [&]() { if (PGV && ((issued - st0) & 31) == 0) turn_window(); };
     turn_window();
+    begun();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
     const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF;
     auto par_at = [&](int i) {
@@ -1351,7 +1358,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         // in fp32 beside m and l: half the bytes of fp32 to write, flush at the end of the kernel and read back, at
         // a relative error of at most 2^-10 of that magnitude, below the final bf16 rounding.
         const float sc = amax > 0.f ? 1.0f / amax : 0.f;
-        const size_t prow = (size_t)bx * p.total_rows + orow;
+        const size_t prow = pc_.grouped ? (size_t)((pc_.group * p.nsplit + bx) * pc_.pitch + rw * 32 + c) : (size_t)bx * p.total_rows + orow;
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
         auto pack = [&](int dt, int q) {
             const h2 lo = { (_Float16)(fin[dt][q * 4 + 0] * sc), (_Float16)(fin[dt][q * 4 + 1] * sc) };
@@ -1368,9 +1375,165 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 // launch): about two microseconds before the first fill is issued.
 #define BTV_FETCH_ARGS(p)                                                                                                     \
     asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.block_table), "s"(p.q_offset),              \
-                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), \
+                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.sync), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), \
                  "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.nsplit),          \
                  "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale))
+
+// ---- the merge inside the attention kernel --------------------------------------------------------------------------------
+// A group = the workgroups whose partials belong to the same rows: the key splits of one (KV head, row block).  Where the
+// launch gives every group workgroup ids that are congruent mod 8 they run on one XCD, their partials meet in that XCD's L2, and each of
+// them, once all have stored theirs, merges its share of the rows (every nsplit-th) and writes O.  That takes the place of a second
+// launch: the write-back of the partials between the kernels, a launch and tv_combine_bf16's own round trips.
+//
+// Nothing depends on where workgroups run or on whether they run at once:
+// * A workgroup writes the XCD it runs on (the hardware's register) beside the call's tag when it starts, and reads its peers' words
+//   at its end.  Only if all have started, and on its own XCD, it relies on the L2 ("together"); otherwise its partials are
+//   released to the whole device first, and the others' acquired.  A workgroup that is together knows that all its peers are
+//   on this XCD, whatever they know themselves.
+// * A workgroup says that its partials are stored in a word in the L2 (near; a store of workgroup scope, which stays there), and if it is
+//   not together in a word at the memory side as well (far).  It waits until all have, for `wait_ticks` at most.  If that passes it says
+//   so in the same words, looks once more, at near and far words alike, and leaves if somebody still is missing.  Whoever stores
+//   last sees all words, and who has left among them (each writes its own word, and has it acknowledged, before it looks at the others'), and
+//   merges their shares too.  Two that do the same share write the same values.
+// * Words carry the call's tag (one more than `epoch`, which every workgroup reads at its start and whoever has seen all of the group
+//   moves on), so they are never cleared and a workspace may change its sizes from call to call.
+// An exchange between 32 workgroups takes 930 cycles through the L2 and 2300 at the memory side (MI355X, store to all have read).
+constexpr int MERGE_GROUPS = 128, MERGE_SPLITS = 32;
+typedef unsigned long long u64;
+struct MergeWords {                                     // of one group
+    u64 started[MERGE_SPLITS];                          // tag << 8 | XCD
+    u64 near[MERGE_SPLITS], far[MERGE_SPLITS];          // tag << 8 | 1 if it has left
+    u64 epoch, pad[31];
+};
+static_assert(sizeof(MergeWords) == 1024, "whole cache lines per group");
+constexpr int MERGE_WAIT_TICKS = 2000;                  // 20 us of the 100 MHz wall clock
+
+__device__ __forceinline__ uint32_t this_xcd() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)); }     // HW_REG_XCC_ID, bits 3:0
+
+// Loads past the L1 (to which the group's other workgroups do not write): a scalar base and a lane's offset.
+template <typename T> __device__ __forceinline__ T load_shared(const void *base, uint32_t off)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one word");
+    typedef typename std::conditional<sizeof(T) == 8, u64, uint32_t>::type W;
+    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const W *>(static_cast<const char *>(base) + off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// One row of the group's partials: the arithmetic of combine_row, up to 32 splits in one pass.  row: of O; at: of the partials of the
+// first split, `pitch` rows ahead of the next one's.  (Split behind split in a place of the group's own: rows of the layout that
+// tv_combine_bf16 reads, where the heads lie between each other, would leave an XCD with one head only every eighth channel of its L2.)
+template <int D> __device__ __forceinline__ void store_row(const AttnParams &p, size_t row, int lane, const float (&acc)[D / 32], float inv);
+__device__ __forceinline__ float row32_max(float x, int lane);
+__device__ __forceinline__ float row32_sum(float x, int lane);
+template <int D>
+__device__ __forceinline__ void merge_row(const AttnParams &p, uint32_t row, uint32_t at, uint32_t pitch, int n, float *wsh, int tid)
+{
+    constexpr int E = D / 32;
+    typedef _Float16 hvec __attribute__((ext_vector_type(E)));
+    const int lane = tid & 31;
+    const uint32_t ml_at = ((uint32_t)min(lane, n - 1) * pitch + at) * 16;
+    const float2 ml = load_shared<float2>(p.ML, ml_at);
+    const float mz = load_shared<float>(p.ML, ml_at + 8);
+    at = (at * D + lane * E) * 2;
+    pitch *= D * 2;
+    asm volatile("" : "+s"(pitch));                     // (or what follows from it is worked out ahead of the loop, in registers that are short)
+    hvec part[MERGE_SPLITS];
+#pragma unroll
+    for (int g = 0; g < MERGE_SPLITS / 8; ++g)
+        if (8 * g < n) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                part[8 * g + b] = load_shared<hvec>(p.Opart, at);
+                at += 8 * g + b + 1 < n ? pitch : 0u;   // (past the last split: it again, with weight 0)
+            }
+        }
+    const float mmax = row32_max(lane < n ? ml.x : NEG_BIG, tid);
+    const float w = __builtin_amdgcn_exp2f(ml.x - mmax);
+    wsh[lane] = lane < n ? w * mz : 0.f;                // weight times the partial's magnitude
+    const float den = row32_sum(lane < n ? w * ml.y : 0.f, tid);
+    // (the row's 32 lanes are one half of a wavefront: its LDS operations complete in order, no barrier needed)
+    float acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < MERGE_SPLITS / 8; ++g)
+        if (8 * g < n) {
+            const float4 w0 = *reinterpret_cast<const float4 *>(wsh + 8 * g), w1 = *reinterpret_cast<const float4 *>(wsh + 8 * g + 4);
+            const float wg[8] = { w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w };
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] += wg[b] * (float)part[8 * g + b][e];
+        }
+    store_row<D>(p, row, lane, acc, p.out_scale / den);
+}
+
+// The rest of a workgroup whose partials have been stored (by its threads; not necessarily acknowledged yet).
+template <int D, int WAVES, int WR>
+__device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, unsigned char *smem, int tid, const Piece &pc, int n, u64 tag)
+{
+    const int split = pc.bx;
+    float *wsh = reinterpret_cast<float *>(smem);                       // [2 * WAVES][32]: weights of a row per half wavefront
+    uint32_t *said = reinterpret_cast<uint32_t *>(smem) + WAVES * 2 * 32;       // what the first wavefront has seen
+    const int lane = tid & 63, peer = min(lane, n - 1);
+    u64 begun = 0;
+    if (tid < 64) begun = __hip_atomic_load(&m.started[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the thread's first row, ahead of the wait (rr < 4096 and G <= 16: the product with ceil(2^16 / G) gives the quotient)
+    const int rows = min(WR, p.M * p.G - pc.by * WR), inv_g = (65536 + p.G - 1) / p.G;
+    auto row_at = [&](int r) {
+        const int rr = pc.by * WR + r, node = (rr * inv_g) >> 16;
+        return (uint32_t)(node * p.Hq + pc.g * p.G + (rr - node * p.G));
+    };
+    int r = split + n * (tid >> 5);
+    uint32_t row = row_at(r);
+    asm volatile("" : "+v"(row));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's partials are in the L2 ...
+    __syncthreads();                                    // ... and all the workgroup's
+    if (tid < 64) {
+        const bool together = __builtin_amdgcn_ballot_w64(begun != (tag << 8 | this_xcd())) == 0ull && !p.apart;
+        if (!together) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        auto say = [&](u64 word) {
+            if (lane == 0) __hip_atomic_store(&m.near[split], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (!together) {
+                if (lane == 0) __hip_atomic_store(&m.far[split], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+        };
+        u64 left = 0;
+        auto look = [&](bool both) {                    // are all there?  Which have left?
+            const u64 a = __hip_atomic_load(&m.near[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const u64 b = both ? __hip_atomic_load(&m.far[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a;
+            const bool in_a = a >> 8 == tag, in_b = b >> 8 == tag;
+            left = __builtin_amdgcn_ballot_w64(lane < n && ((in_a && (a & 1)) || (in_b && (b & 1))));
+            return __builtin_amdgcn_ballot_w64(!in_a && !in_b) == 0ull;
+        };
+        say(tag << 8);
+        const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+        bool all = look(!together);
+        while (!all) {
+            if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > p.wait_ticks) {
+                say(tag << 8 | 1);
+                all = look(true);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            all = look(!together);
+        }
+        if (all && !together) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (lane == 0) { said[0] = all; said[1] = (uint32_t)left; }
+    }
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(said[0])) return;
+    uint32_t left = __builtin_amdgcn_readfirstlane(said[1]) & ~(1u << split);
+    for (;;) {
+        for (; r < rows; r += n * WAVES * 2, row = row_at(r)) merge_row<D>(p, row, (uint32_t)(pc.group * n * pc.pitch + r), pc.pitch, n, wsh + (tid >> 5) * 32, tid);
+        if (!left) break;
+        r = __builtin_ctz(left) + n * (tid >> 5);       // (rare) the share of one that has left
+        row = row_at(r);
+        left &= left - 1;
+    }
+    if (tid == 0) __hip_atomic_store(&m.epoch, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // One request: a workgroup per (key split, KV head, row block).
 template <int D, int RW, int KW, int NT, int EB>
@@ -1378,20 +1541,42 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     BTV_FETCH_ARGS(p);
-    // Workgroups go to the 8 XCDs round-robin by their linear id.  A unit = (key split, KV head); the row
-    // blocks of one unit stream the same K/V bytes, so they get ids that are congruent mod 8 and share one L2.
+    // Workgroups go to the 8 XCDs round-robin by their linear id.  The row blocks of one (key split, KV head) stream the same K/V
+    // bytes, so they get ids that are congruent mod 8 and share one L2; where the merge is done here, so do all splits of a group
+    // (p.units counts the (split, head) pairs, or the heads, or the groups that are dealt out to the XCDs).
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
-    if (unit >= p.units) return;
+    Piece pc = {};
+    if (!p.sync) {
+        const int unit = (slot / p.row_blocks) * 8 + xcd;
+        if (unit >= p.units) return;
+        pc.by = slot % p.row_blocks; pc.g = unit / p.nsplit; pc.bx = unit % p.nsplit;
+    } else if (p.units == p.Hkv) {
+        const int q = slot / p.row_blocks;
+        pc.by = slot % p.row_blocks; pc.g = (q / p.nsplit) * 8 + xcd; pc.bx = q % p.nsplit;
+        if (pc.g >= p.Hkv) return;
+    } else {
+        const int q = (slot / p.nsplit) * 8 + xcd;
+        pc.by = q % p.row_blocks; pc.g = q / p.row_blocks; pc.bx = slot % p.nsplit;
+        if (pc.g >= p.Hkv) return;
+    }
     const Req rq = load_req<false>(p, 0);
-    Piece pc;
-    pc.rq = 0; pc.g = unit / p.nsplit; pc.by = by; pc.bx = unit % p.nsplit;
     const int tiles = (rq.L + rq.M + 31) / 32, nsplit_r = (tiles + p.sps - 1) / p.sps;
-    if (by * RW * 32 >= rq.M * p.G || pc.bx >= nsplit_r) return;
+    if (pc.by * RW * 32 >= rq.M * p.G || pc.bx >= nsplit_r) return;
     pc.st0 = pc.bx * p.sps;
     pc.st1 = min(pc.st0 + p.sps, tiles);
     pc.direct = nsplit_r == 1;
-    attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc);
+    pc.grouped = p.sync != nullptr;
+    pc.group = pc.g * p.row_blocks + pc.by;
+    pc.pitch = min(RW * 32, rq.M * p.G) + 1;            // (rows of the same number lie in different channels)
+    MergeWords *m = reinterpret_cast<MergeWords *>(p.sync) + pc.group;
+    u64 tag = 0;
+    if (p.sync)      // (a scalar load: nothing writes it before every workgroup of the group has read it)
+        tag = *reinterpret_cast<const __attribute__((address_space(4))) u64 *>(reinterpret_cast<uintptr_t>(&m->epoch)) + 1;
+    attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc, [&] {
+        if (p.sync && threadIdx.x == 0)
+            __hip_atomic_store(&m->started[pc.bx], tag << 8 | this_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
+    if (p.sync) merge_group<D, RW * KW, RW * 32>(p, *m, smem, threadIdx.x, pc, nsplit_r, tag);
 }
 
 // A batch of short requests: a workgroup per (part of at most sps tiles, KV head, request, row block) of the largest request;
@@ -1404,7 +1589,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
     if (unit >= p.units) return;
-    Piece pc;
+    Piece pc = {};
     // The part is rotated by the (request, head) number.  Without it a number of parts that is a multiple of 8 ties part i
     // to XCD i % 8, and the requests with few parts load only the first XCDs.
     const int bz = unit / p.nsplit;
@@ -1419,7 +1604,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
     pc.st0 = pc.bx * p.sps;
     pc.st1 = min(pc.st0 + p.sps, tiles);
     pc.direct = parts == 1;
-    attn_piece<D, RW, KW, NT, true, EB>(p, smem, threadIdx.x, rq, pc);
+    attn_piece<D, RW, KW, NT, true, EB>(p, smem, threadIdx.x, rq, pc, [] {});
 }
 
 // ---- ragged batches ---------------------------------------------------------------------------------------------------
@@ -1594,7 +1779,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_batch(AttnParams p)
         if (again) c = load_chunk(p, 0, tid & 63, 0);
         Piece pc = {};
         if (!next_piece(p, k, member, tid & 63, c, pc)) break;
-        attn_piece<D, RW, KW, NT, true, EB>(p, smem, tid, load_req<true>(p, pc.rq), pc);
+        attn_piece<D, RW, KW, NT, true, EB>(p, smem, tid, load_req<true>(p, pc.rq), pc, [] {});
         // every wave is done with this piece's LDS, its own fills have landed; the stores may still be on their way
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -1939,6 +2124,21 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
 
 struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; };
 
+// Whether the workgroups of a plan merge their partials themselves (merge_group): few enough splits and groups for its words; all
+// groups' workgroups congruent mod 8, and as many on each XCD; and the chip takes all at once.
+bool merges_inside(const Plan &pl, int Hkv)
+{
+    const int groups = Hkv * pl.row_blocks;
+    return pl.nsplit > 1 && pl.nsplit <= MERGE_SPLITS && groups <= MERGE_GROUPS && (Hkv % 8 == 0 || groups % 8 == 0) &&
+           pl.nsplit * groups <= (pl.rw == 2 ? 512 : 256);
+}
+
+// Rows of one split's partials, by either merge.
+size_t partial_rows(const Plan &pl, int M, int Hq, int Hkv)
+{
+    return std::max<size_t>((size_t)M * Hq, (size_t)Hkv * pl.row_blocks * (std::min(pl.wr, M * (Hq / Hkv)) + 1));
+}
+
 // Splits of `want` parts for a shape.
 void split_plan(Plan &pl, int L, int want)
 {
@@ -1995,7 +2195,8 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
         };
         if (force_split > 0) { consider(force_split); continue; }
         // no more splits than tiles, nor partials than the built-in scratch array holds (32 MB are 6 us to write and read)
-        const int most = (int)std::min<long long>(std::min(64, pl.stages), std::max<long long>(1, (31ll << 20) / ((long long)M * Hq * (D * 2 + 16))));
+        const int most = (int)std::min<long long>(std::min(64, pl.stages),
+                                                  std::max<long long>(1, (31ll << 20) / (long long)(partial_rows(pl, M, Hq, Hkv) * (D * 2 + 16))));
         for (int want : SPLITS)
             if (want <= most) consider(want);
         for (int cap = 256; cap <= (k == 0 ? 1024 : 512); cap *= 2) {                     // as many as whole rounds take
@@ -2047,14 +2248,15 @@ PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, i
     return b;
 }
 
-struct WsLayout { size_t plan, ml, opart, total; };
+// The merge's words lie at the same place in every workspace of attention calls that hold partials: other calls leave them alone.
+struct WsLayout { size_t sync, plan, ml, opart, total; };
 
-WsLayout ws_layout(int total_M, int Hq, int D, int nsplit, int batch = 0)
+WsLayout ws_layout(size_t rows, int D, int nsplit, int batch = 0)
 {
     WsLayout w;
     size_t off = BTV_WS_HEADER;
+    w.sync = off; off += batch || nsplit > 1 ? MERGE_GROUPS * sizeof(MergeWords) : 0;
     w.plan = off; off += batch ? btv_align_up((size_t)(batch + 2) * sizeof(long long), BTV_WS_ALIGN) : 0;
-    size_t rows = (size_t)total_M * Hq;
     size_t ns = nsplit > 1 ? nsplit : 0;
     w.ml = off; off += btv_align_up(ns * rows * 4 * 4, BTV_WS_ALIGN);
     w.opart = off; off += btv_align_up(ns * rows * D * 2, BTV_WS_ALIGN);
@@ -2132,7 +2334,8 @@ void set_scales(AttnParams &p, int D, float scale, float k_scale, float v_scale)
 
 int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *parent, int M, int L, int Hq, int Hkv,
                     int D, int dtype, int eb, float scale, float k_scale, float v_scale, void *O, void *ws,
-                    size_t ws_bytes, void *stream, int force_split = 0, int force_shape = 0, uint32_t *flag_out = nullptr)
+                    size_t ws_bytes, void *stream, int force_split = 0, int force_shape = 0, uint32_t *flag_out = nullptr,
+                    int merge = 0, int wait_ticks = MERGE_WAIT_TICKS)
 {
     BTV_REQUIRE(Q && K && V && parent && O, "null pointer");
     BTV_REQUIRE(aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(O), "Q, K, V and O must be 16-byte aligned");
@@ -2141,7 +2344,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     hipStream_t st = static_cast<hipStream_t>(stream);
     Plan pl = make_plan(M, L, Hq, Hkv, D, eb, force_split, force_shape);
     if (dtype == BTV_F32) pl.nsplit = 1;
-    WsLayout wl = ws_layout(M, Hq, D, pl.nsplit);
+    WsLayout wl = ws_layout(partial_rows(pl, M, Hq, Hkv), D, pl.nsplit);
     rc = btv_check_ws(ws, ws_bytes, wl.total);
     if (rc) return rc;
     unsigned char *w8 = static_cast<unsigned char *>(ws);
@@ -2162,10 +2365,20 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
         return BTV_OK;
     }
     p.row_blocks = pl.row_blocks;
-    p.units = pl.nsplit * Hkv;
-    rc = dispatch_bf16<ONE_REQUEST>(p, pl.rw, D, eb, dim3(((p.units + 7) / 8) * pl.row_blocks * 8), st);
+    const bool inside = merge != 1 && merges_inside(pl, Hkv) && (merge || btv_usable_cus(st) >= 256);
+    int wgs;
+    if (inside) {
+        p.sync = reinterpret_cast<unsigned long long *>(w8 + wl.sync);
+        p.wait_ticks = wait_ticks; p.apart = merge == 3;
+        p.units = Hkv % 8 == 0 ? Hkv : Hkv * pl.row_blocks;
+        wgs = pl.nsplit * Hkv * pl.row_blocks;
+    } else {
+        p.units = pl.nsplit * Hkv;
+        wgs = ((p.units + 7) / 8) * pl.row_blocks * 8;
+    }
+    rc = dispatch_bf16<ONE_REQUEST>(p, pl.rw, D, eb, dim3(wgs), st);
     if (rc) return rc;
-    if (pl.nsplit > 1) {
+    if (pl.nsplit > 1 && !inside) {
         dim3 cg((M * Hq + 7) / 8, 1);
         if (D == 64) hipLaunchKernelGGL(tv_combine_bf16<64>, cg, dim3(256), 0, st, p);
         else hipLaunchKernelGGL(tv_combine_bf16<128>, cg, dim3(256), 0, st, p);
@@ -2190,7 +2403,7 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     BTV_REQUIRE((long long)max_blocks * BTV_PAGE >= (long long)L_max + 1, "max_blocks too small for L_max");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const PlanB pl = make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, eb);
-    WsLayout wl = ws_layout(batch * M_max, Hq, D, pl.slots, batch);
+    WsLayout wl = ws_layout((size_t)batch * M_max * Hq, D, pl.slots, batch);
     rc = btv_check_ws(ws, ws_bytes, wl.total);
     if (rc) return rc;
     unsigned char *w8 = static_cast<unsigned char *>(ws);
@@ -2242,8 +2455,8 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK) return 0;
-    int nsplit = dtype == BTV_BF16 ? make_plan(M, L, Hq, Hkv, D).nsplit : 1;
-    return ws_layout(M, Hq, D, nsplit).total;
+    const Plan pl = make_plan(M, L, Hq, Hkv, D);
+    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, dtype == BTV_BF16 ? pl.nsplit : 1).total;
 }
 
 int btv_tree_verify_attn(const void *Q, const void *K, const void *V, const int32_t *parent, int M, int L, int Hq,
@@ -2277,7 +2490,8 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
 size_t btv_tree_verify_attn_fp8kv_workspace(int M, int L, int Hq, int Hkv, int D)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, D, 1).nsplit).total;
+    const Plan pl = make_plan(M, L, Hq, Hkv, D, 1);
+    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, pl.nsplit).total;
 }
 
 int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, float k_scale, float v_scale,
@@ -2293,13 +2507,23 @@ int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, fl
 size_t btv_tree_verify_attn_tuned_workspace(int M, int L, int Hq, int Hkv, int D, int kv_fp8, int nsplit, int shape)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || (kv_fp8 && D != 128) || nsplit < 0 || shape < 0 || shape > 3) return 0;
-    return ws_layout(M, Hq, D, make_plan(M, L, Hq, Hkv, D, kv_fp8 ? 1 : 2, nsplit, shape).nsplit).total;
+    const Plan pl = make_plan(M, L, Hq, Hkv, D, kv_fp8 ? 1 : 2, nsplit, shape);
+    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, pl.nsplit).total;
 }
 
 int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale, float v_scale,
                                const int32_t *parent, int M, int L, int Hq, int Hkv, int D, float scale, int nsplit,
                                int shape, void *O, void *ws, size_t ws_bytes, void *stream)
 {
+    return btv_tree_verify_attn_merge_tuned(Q, K, V, kv_fp8, k_scale, v_scale, parent, M, L, Hq, Hkv, D, scale, nsplit, shape, 0,
+                                            MERGE_WAIT_TICKS, O, ws, ws_bytes, stream);
+}
+
+int btv_tree_verify_attn_merge_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale, float v_scale,
+                                     const int32_t *parent, int M, int L, int Hq, int Hkv, int D, float scale, int nsplit,
+                                     int shape, int merge, int wait_ticks, void *O, void *ws, size_t ws_bytes, void *stream)
+{
+    BTV_REQUIRE(merge >= 0 && merge <= 3, "merge=%d outside [0,3]", merge);
     BTV_REQUIRE(nsplit >= 0 && shape >= 0 && shape <= 3, "nsplit=%d or shape=%d out of range", nsplit, shape);
     if (kv_fp8) {
         int rc = check_fp8(D, k_scale, v_scale);
@@ -2307,13 +2531,13 @@ int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int 
         BTV_REQUIRE(shape != 3, "shape 3 is not built for an FP8 cache");
     }
     return attn_contiguous(Q, K, V, parent, M, L, Hq, Hkv, D, BTV_BF16, kv_fp8 ? 1 : 2, scale, kv_fp8 ? k_scale : 1.0f,
-                           kv_fp8 ? v_scale : 1.0f, O, ws, ws_bytes, stream, nsplit, shape);
+                           kv_fp8 ? v_scale : 1.0f, O, ws, ws_bytes, stream, nsplit, shape, nullptr, merge, wait_ticks);
 }
 
 size_t btv_tree_verify_attn_paged_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK) return 0;
-    return ws_layout(batch * M_max, Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 2).slots, batch).total;
+    return ws_layout((size_t)batch * M_max * Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 2).slots, batch).total;
 }
 
 int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_blocks,
@@ -2329,7 +2553,7 @@ int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpo
 size_t btv_tree_verify_attn_paged_fp8kv_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    return ws_layout(batch * M_max, Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 1).slots, batch).total;
+    return ws_layout((size_t)batch * M_max * Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 1).slots, batch).total;
 }
 
 int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const void *V8pool, float k_scale,

@@ -37,3 +37,4 @@ static inline int btv_check_ws(const void *ws, size_t have, size_t need)
 }
 
 size_t btv_stochastic_workspace(int V);         // bytes btv_tree_accept_stochastic needs
+int btv_usable_cus(hipStream_t st);            // CUs that work on the stream may use

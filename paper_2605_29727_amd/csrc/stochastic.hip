@@ -884,7 +884,8 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
     if (threadIdx.x == 0) sa_move_on(args->base, base, SA_SPAN);
 }
 
-// Slices for a vocabulary of V tokens on at most `most` workgroups: of 2048 tokens (two per thread) as long as those cover the
+// Slices for a vocabulary of V tokens on at most `most` workgroups (no more than CUs that the stream may use: with 32 of them the two
+// walks named at the top take 71 and 60 us, with 16 125 and 115): of 2048 tokens (two per thread) as long as those cover the
 // vocabulary, of 4096, of 8192, longer ones above.
 struct SaPlan { int G, per, pt; bool over; };
 SaPlan sa_plan(int V, int most)
@@ -896,24 +897,6 @@ SaPlan sa_plan(int V, int most)
     a.G = a.over ? most : (V + slice - 1) / slice;
     a.per = (int)((((long long)V + a.G - 1) / a.G + 3) / 4 * 4);
     return a;
-}
-
-// CUs that work on the stream may use: those of the device, or of the mask that the stream was made with (0.3 us a call).  With
-// 32 of them the two walks named at the top take 71 and 60 us, with 16 125 and 115.
-int usable_cus(hipStream_t st)
-{
-    uint32_t mask[32] = {};
-    if (st == hipStreamLegacy) st = nullptr;            // (the other name of the same stream, which the query may not know)
-    if (hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
-        int n = 0;
-        for (uint32_t w : mask) n += __builtin_popcount(w);
-        if (n > 0) return n;
-    } else {
-        (void)hipGetLastError();                        // (the launch's own error is what is reported)
-    }
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) return n;
-    return 1;
 }
 
 template <bool BF16>
@@ -948,7 +931,7 @@ extern "C" int btv_tree_accept_stochastic_tuned(const void *logits, int dtype, c
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     SaPlan a = sa_plan(V, max_workgroups ? max_workgroups : SA_MAX_WGS);
-    if (!max_workgroups && a.G > 1) a = sa_plan(V, std::min(SA_MAX_WGS, usable_cus(st)));
+    if (!max_workgroups && a.G > 1) a = sa_plan(V, std::min(SA_MAX_WGS, btv_usable_cus(st)));
     SaParams p;
     p.logits = logits; p.marg = marginals; p.uniforms = uniforms; p.parent = parent; p.token = token;
     p.path = path; p.n_acc = n_acc; p.bonus = bonus;
