@@ -1281,10 +1281,15 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     // scale and store half a row.  dt0 .. dt0 + DTK - 1 are the channel blocks this wave ends up with.
     int dt0 = 0;
     constexpr int DTK = KW == 2 ? DT / 2 : DT;
-    float fin[DTK][16];                             // what this wave stores
-    float amax = 0.f;                               // bound on the row's largest magnitude (for the fp16 partials)
+    float fin[DTK][16];                             // what this wave stores: its rows times `factor`
+    float amax;                                     // bound on the row's largest magnitude (for the fp16 partials)
+    // Partials travel as fp16 relative to (a bound within a factor two of) the row's largest magnitude, kept in fp32 beside m and l:
+    // half the bytes of fp32 to write, flush at the end of the kernel and read back, at a relative error of at most 2^-10 of that
+    // magnitude, below the final bf16 rounding.  (The bound stays above LEAST, so that its reciprocal is finite.)
+    constexpr float LEAST = 1.0e-36f;
+    auto factor = [&]() { return pc_.direct ? p.out_scale / l_run : 1.0f / amax; };
     if constexpr (KW == 2) {
-        constexpr int SLOT = (DTK * 16 + 3) * 64;   // floats a wave hands over
+        constexpr int QUADS = DTK * 4, SLOT = (DTK * 16 + 3) * 64;      // floats a wave hands over: groups of four, then m, l, bound
         float *mg = reinterpret_cast<float *>(smem) + rw * 2 * SLOT;
         amax = finite_max<DT>(oacc);
         wait_vmcnt<0>();
@@ -1293,9 +1298,11 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         auto give = [&](auto first) {               // the channel blocks first .. first + DTK - 1 go to the partner
             constexpr int F = decltype(first)::value;
 #pragma unroll
-            for (int dt = 0; dt < DTK; ++dt)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) out[(dt * 16 + v) * 64 + l] = oacc[F + dt][v];
+            for (int q = 0; q < QUADS; ++q) {
+                const f32x16 &o = oacc[F + q / 4];
+                const f32x4 x = { o[4 * (q & 3)], o[4 * (q & 3) + 1], o[4 * (q & 3) + 2], o[4 * (q & 3) + 3] };
+                reinterpret_cast<f32x4 *>(out)[q * 64 + l] = x;
+            }
         };
         if (kw == 0) give(std::integral_constant<int, DTK>{}); else give(std::integral_constant<int, 0>{});
         out[(DTK * 16) * 64 + l] = m_run;
@@ -1304,32 +1311,38 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         __syncthreads();
         const float *in = mg + (kw ^ 1) * SLOT;
         const float m1 = in[(DTK * 16) * 64 + l], l1 = in[(DTK * 16 + 1) * 64 + l], x1 = in[(DTK * 16 + 2) * 64 + l];
+        f32x4 other[QUADS];
+#pragma unroll
+        for (int q = 0; q < QUADS; ++q) other[q] = reinterpret_cast<const f32x4 *>(in)[q * 64 + l];
         const float mn = fmaxf(m_run, m1);
-        const float a0 = __builtin_amdgcn_exp2f(m_run - mn);
-        const float a1 = __builtin_amdgcn_exp2f(m1 - mn);
+        float a0 = __builtin_amdgcn_exp2f(m_run - mn);
+        float a1 = __builtin_amdgcn_exp2f(m1 - mn);
         // both waves must arrive at the same l and bound: sums of the same two products, order fixed by kw
         const float la = kw == 0 ? l_run * a0 : l1 * a1, lb = kw == 0 ? l1 * a1 : l_run * a0;
         const float xa = kw == 0 ? amax * a0 : x1 * a1, xb = kw == 0 ? x1 * a1 : amax * a0;
         m_run = mn;
         l_run = la + lb;
-        amax = fminf(xa + xb, FLT_MAX);             // >= the merged row's largest (finite) magnitude, at most twice it
+        amax = fminf(fmaxf(xa + xb, LEAST), FLT_MAX);     // >= the merged row's largest (finite) magnitude, at most twice it
+        const float f = factor();
+        a0 *= f; a1 *= f;
         auto take = [&](auto first) {
             constexpr int F = decltype(first)::value;
 #pragma unroll
             for (int dt = 0; dt < DTK; ++dt)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) fin[dt][v] = oacc[F + dt][v] * a0 + in[(dt * 16 + v) * 64 + l] * a1;
+                for (int v = 0; v < 16; ++v) fin[dt][v] = fmaf(oacc[F + dt][v], a0, other[dt * 4 + v / 4][v & 3] * a1);
         };
         if (kw == 0) take(std::integral_constant<int, 0>{}); else take(std::integral_constant<int, DTK>{});
         dt0 = kw * DTK;                             // the kept blocks now sit in oacc[0 .. DTK)
     }
     if (!rvalid) return;
     if constexpr (KW == 1) {
+        amax = fmaxf(finite_max<DT>(oacc), LEAST);
+        const float f = factor();
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) fin[dt][v] = oacc[dt][v];
-        amax = finite_max<DT>(oacc);
+            for (int v = 0; v < 16; ++v) fin[dt][v] = oacc[dt][v] * f;
     }
 
     // ---- write: final bf16 rows when this request has a single split, scaled fp16 partials otherwise ---
@@ -1347,22 +1360,17 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             }
     };
     if (pc_.direct) {
-        const float inv = p.out_scale / l_run;
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
         auto pack = [&](int dt, int q) {
-            return make_uint2(float_to_bf16_bits(fin[dt][q * 4 + 0] * inv) | (float_to_bf16_bits(fin[dt][q * 4 + 1] * inv) << 16),
-                              float_to_bf16_bits(fin[dt][q * 4 + 2] * inv) | (float_to_bf16_bits(fin[dt][q * 4 + 3] * inv) << 16));
+            const b2 lo = { (__bf16)fin[dt][q * 4 + 0], (__bf16)fin[dt][q * 4 + 1] }, hi = { (__bf16)fin[dt][q * 4 + 2], (__bf16)fin[dt][q * 4 + 3] };
+            return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
         };
         store_rows(static_cast<unsigned char *>(p.O) + (orow * D + dt0 * 32) * 2, pack);
     } else {
-        // Partials travel as fp16 relative to (a bound within a factor two of) the row's largest magnitude, kept
-        // in fp32 beside m and l: half the bytes of fp32 to write, flush at the end of the kernel and read back, at
-        // a relative error of at most 2^-10 of that magnitude, below the final bf16 rounding.
-        const float sc = amax > 0.f ? 1.0f / amax : 0.f;
         const size_t prow = pc_.grouped ? (size_t)((pc_.group * p.nsplit + bx) * pc_.pitch + rw * 32 + c) : (size_t)bx * p.total_rows + orow;
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
         auto pack = [&](int dt, int q) {
-            const h2 lo = { (_Float16)(fin[dt][q * 4 + 0] * sc), (_Float16)(fin[dt][q * 4 + 1] * sc) };
-            const h2 hi = { (_Float16)(fin[dt][q * 4 + 2] * sc), (_Float16)(fin[dt][q * 4 + 3] * sc) };
+            const h2 lo = { (_Float16)fin[dt][q * 4 + 0], (_Float16)fin[dt][q * 4 + 1] }, hi = { (_Float16)fin[dt][q * 4 + 2], (_Float16)fin[dt][q * 4 + 3] };
             return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
         };
         store_rows(reinterpret_cast<unsigned char *>(p.Opart) + (prow * D + dt0 * 32) * 2, pack);
@@ -1410,61 +1418,124 @@ constexpr int MERGE_WAIT_TICKS = 2000;                  // 20 us of the 100 MHz 
 
 __device__ __forceinline__ uint32_t this_xcd() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)); }     // HW_REG_XCC_ID, bits 3:0
 
-// Loads past the L1 (to which the group's other workgroups do not write): a scalar base and a lane's offset.
-template <typename T> __device__ __forceinline__ T load_shared(const void *base, uint32_t off)
-{
-    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one word");
-    typedef typename std::conditional<sizeof(T) == 8, u64, uint32_t>::type W;
-    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const W *>(static_cast<const char *>(base) + off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-
-// One row of the group's partials: the arithmetic of combine_row, up to 32 splits in one pass.  row: of O; at: of the partials of the
-// first split, `pitch` rows ahead of the next one's.  (Split behind split in a place of the group's own: rows of the layout that
-// tv_combine_bf16 reads, where the heads lie between each other, would leave an XCD with one head only every eighth channel of its L2.)
-template <int D> __device__ __forceinline__ void store_row(const AttnParams &p, size_t row, int lane, const float (&acc)[D / 32], float inv);
-__device__ __forceinline__ float row32_max(float x, int lane);
-__device__ __forceinline__ float row32_sum(float x, int lane);
-template <int D>
-__device__ __forceinline__ void merge_row(const AttnParams &p, uint32_t row, uint32_t at, uint32_t pitch, int n, float *wsh, int tid)
-{
-    constexpr int E = D / 32;
-    typedef _Float16 hvec __attribute__((ext_vector_type(E)));
-    const int lane = tid & 31;
-    const uint32_t ml_at = ((uint32_t)min(lane, n - 1) * pitch + at) * 16;
-    const float2 ml = load_shared<float2>(p.ML, ml_at);
-    const float mz = load_shared<float>(p.ML, ml_at + 8);
-    at = (at * D + lane * E) * 2;
-    pitch *= D * 2;
-    asm volatile("" : "+s"(pitch));                     // (or what follows from it is worked out ahead of the loop, in registers that are short)
-    hvec part[MERGE_SPLITS];
+// One of the group's shares: rows of, of + n, .. of the block's `rows`.  16 lanes take a row's partial of one split with one load each
+// (a load holds its wave for some 80 cycles whatever its width), 4, 2 or 1 such sets of lanes of a wavefront share a row's splits out,
+// by how many rows there are.  Loads go past the L1, to which the group's other workgroups do not write.  The arithmetic is combine_row's, the
+// sums over the splits in another order.  What a wavefront spends its time on is one instruction after the other (two wavefronts
+// on a SIMD, some 7 cycles each): offsets are worked out before the wait for the others, sums are multiply-adds on the fp16 values as they are.
+template <int D, int WAVES> struct Share {
+    static constexpr int E = D / 16, SETS = WAVES * 4;  // values per lane; sets of 16 lanes
+    int of, count, lp;                                  // first row, number of rows, log2 of the sets per row
+    int k, row, ml, part[8];                            // a set's row: which of the share's, of O; byte offsets of what it loads
+    __device__ __forceinline__ void begin(int of_, int n, int rows, int tid)
+    {
+        of = of_;
+        count = (rows - of + n - 1) / n;
+        lp = 4 * count <= SETS ? 2 : 2 * count <= SETS ? 1 : 0;
+        k = (tid >> 4) >> lp;
+    }
+    __device__ __forceinline__ void find(const AttnParams &p, const Piece &pc, int n, int wr, int tid)
+    {
+        // (rr < 4096 and G <= 16: the product with ceil(2^16 / G) gives the quotient)
+        const int r = of + n * k, rr = pc.by * wr + r, node = (rr * ((65536 + p.G - 1) / p.G)) >> 16;
+        row = node * p.Hq + pc.g * p.G + (rr - node * p.G);
+        ml = (min(tid & ((16 << lp) - 1), n - 1) * pc.pitch + r) * 16;
 #pragma unroll
-    for (int g = 0; g < MERGE_SPLITS / 8; ++g)
-        if (8 * g < n) {
+        for (int b = 0; b < 8; ++b) part[b] = part_at(pc, b, 0, n, tid);
+    }
+    __device__ __forceinline__ int part_at(const Piece &pc, int b, int at, int n, int tid) const
+    {
+        const int s = at + ((tid >> 4) & ((1 << lp) - 1)) + (b << lp);
+        return (min(s, n - 1) * pc.pitch + of + n * k) * (D * 2) + (tid & 15) * (E * 2);
+    }
+};
+
+template <int D, int WAVES>
+__device__ __forceinline__ void merge_share(const AttnParams &p, const Piece &pc, Share<D, WAVES> sh, int n, int wr, float *weights, int tid)
+{
+    constexpr int E = Share<D, WAVES>::E, PAST_L1 = 16;                 // SC1
+    typedef _Float16 hvec __attribute__((ext_vector_type(E)));
+    typedef __bf16 bvec __attribute__((ext_vector_type(E)));
+    const int lp = sh.lp, set = tid >> 4, sub = set & ((1 << lp) - 1);
+    float *wsh = weights + (set >> lp << lp) * MERGE_SPLITS;           // (by the row's first set: no other wavefront's, whatever lp is)
+    const uint32_t pitch = (uint32_t)pc.pitch, first = (uint32_t)(pc.group * n) * pitch;
+    const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ML + (size_t)first * 4, 0, (int)(n * pitch * 16), 0x00027000);
+    const auto part_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Opart + (size_t)first * D, 0, (int)(n * pitch * D * 2), 0x00027000);
+    const int s0 = tid & ((16 << lp) - 1), s1 = s0 + 16;                // splits whose weights this lane works out (s1: one set per row)
+    while (sh.k < sh.count) {
+        auto load_ml = [&](int off) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(ml_rsrc, off, 0, PAST_L1)); };
+        const float4 m0 = load_ml(sh.ml);
+        float4 m1 = make_float4(NEG_BIG, 0.f, 0.f, 0.f);
+        if (lp == 0 && n > 16) m1 = load_ml((min(s1, n - 1) * pc.pitch + sh.of + n * sh.k) * 16);
+        hvec part[8];
+        auto load_parts = [&]() {
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                part[8 * g + b] = load_shared<hvec>(p.Opart, at);
-                at += 8 * g + b + 1 < n ? pitch : 0u;   // (past the last split: it again, with weight 0)
+                if constexpr (E == 8) part[b] = __builtin_bit_cast(hvec, __builtin_amdgcn_raw_buffer_load_b128(part_rsrc, sh.part[b], 0, PAST_L1));
+                else part[b] = __builtin_bit_cast(hvec, __builtin_amdgcn_raw_buffer_load_b64(part_rsrc, sh.part[b], 0, PAST_L1));
             }
-        }
-    const float mmax = row32_max(lane < n ? ml.x : NEG_BIG, tid);
-    const float w = __builtin_amdgcn_exp2f(ml.x - mmax);
-    wsh[lane] = lane < n ? w * mz : 0.f;                // weight times the partial's magnitude
-    const float den = row32_sum(lane < n ? w * ml.y : 0.f, tid);
-    // (the row's 32 lanes are one half of a wavefront: its LDS operations complete in order, no barrier needed)
-    float acc[E];
+        };
+        load_parts();
+        auto over_row = [&](float x, auto op) {                         // over the row's 16, 32 or 64 lanes
+            x = op(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0xB1, 0xF, 0xF, false)));      // quad_perm [1,0,3,2]
+            x = op(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x4E, 0xF, 0xF, false)));      // quad_perm [2,3,0,1]
+            x = op(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x141, 0xF, 0xF, false)));     // row_half_mirror
+            x = op(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x140, 0xF, 0xF, false)));     // row_mirror
+            if (lp >= 1) {
+                const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                x = op(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+            }
+            if (lp == 2) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                x = op(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+            }
+            return x;
+        };
+        const float x0 = s0 < n ? m0.x : NEG_BIG, x1 = s1 < n ? m1.x : NEG_BIG;
+        const float mmax = over_row(lp == 0 ? fmaxf(x0, x1) : x0, [](float u, float v) { return fmaxf(u, v); });
+        const float w0 = s0 < n ? __builtin_amdgcn_exp2f(x0 - mmax) : 0.f, w1 = lp == 0 && s1 < n ? __builtin_amdgcn_exp2f(x1 - mmax) : 0.f;
+        // weight times the partial's magnitude; 0 past the last split.  (The row's lanes are of one wavefront: no barrier needed.)
+        if (s0 < MERGE_SPLITS) wsh[s0] = s0 < n ? w0 * m0.z : 0.f;
+        if (lp == 0) wsh[s1] = s1 < n ? w1 * m1.z : 0.f;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const float den = over_row((s0 < n ? w0 * m0.y : 0.f) + (lp == 0 && s1 < n ? w1 * m1.y : 0.f), [](float u, float v) { return u + v; });
+        float inv = p.out_scale / den;
+        float acc[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0.f;
+        for (int e = 0; e < E; ++e) acc[e] = 0.f;
+        for (int at = 0;;) {
+            float wg[8];
 #pragma unroll
-    for (int g = 0; g < MERGE_SPLITS / 8; ++g)
-        if (8 * g < n) {
-            const float4 w0 = *reinterpret_cast<const float4 *>(wsh + 8 * g), w1 = *reinterpret_cast<const float4 *>(wsh + 8 * g + 4);
-            const float wg[8] = { w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w };
+            for (int b = 0; b < 8; ++b) wg[b] = wsh[(at + sub + (b << lp)) & (MERGE_SPLITS - 1)];
 #pragma unroll
             for (int b = 0; b < 8; ++b)
+                if (at + (b << lp) < n) {                               // (a set past the last split: weight 0)
 #pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] += wg[b] * (float)part[8 * g + b][e];
+                    for (int e = 0; e < E; ++e) acc[e] = fmaf(wg[b], (float)part[b][e], acc[e]);
+                }
+            at += 8 << lp;
+            if (at >= n) break;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) sh.part[b] = sh.part_at(pc, b, at, n, tid);
+            load_parts();
         }
-    store_row<D>(p, row, lane, acc, p.out_scale / den);
+        bvec o;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {                                   // the row's sets
+            if (lp >= 1) {
+                const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+                acc[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            }
+            if (lp == 2) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+                acc[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            }
+            o[e] = (__bf16)(acc[e] * inv);
+        }
+        if (sub == 0) *reinterpret_cast<bvec *>(static_cast<__bf16 *>(p.O) + (size_t)sh.row * D + (tid & 15) * E) = o;
+        sh.k += sh.SETS >> lp;
+        if (sh.k < sh.count) sh.find(p, pc, n, wr, tid);
+    }
 }
 
 // The rest of a workgroup whose partials have been stored (by its threads; not necessarily acknowledged yet).
@@ -1472,20 +1543,15 @@ template <int D, int WAVES, int WR>
 __device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, unsigned char *smem, int tid, const Piece &pc, int n, u64 tag)
 {
     const int split = pc.bx;
-    float *wsh = reinterpret_cast<float *>(smem);                       // [2 * WAVES][32]: weights of a row per half wavefront
-    uint32_t *said = reinterpret_cast<uint32_t *>(smem) + WAVES * 2 * 32;       // what the first wavefront has seen
-    const int lane = tid & 63, peer = min(lane, n - 1);
+    uint32_t *said = reinterpret_cast<uint32_t *>(smem) + WAVES * 4 * MERGE_SPLITS;      // what the first wavefront has seen (behind merge_share's weights)
+    const int lane = tid & 63, peer = min(lane, n - 1), rows = min(WR, p.M * p.G - pc.by * WR);
     u64 begun = 0;
     if (tid < 64) begun = __hip_atomic_load(&m.started[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the thread's first row, ahead of the wait (rr < 4096 and G <= 16: the product with ceil(2^16 / G) gives the quotient)
-    const int rows = min(WR, p.M * p.G - pc.by * WR), inv_g = (65536 + p.G - 1) / p.G;
-    auto row_at = [&](int r) {
-        const int rr = pc.by * WR + r, node = (rr * inv_g) >> 16;
-        return (uint32_t)(node * p.Hq + pc.g * p.G + (rr - node * p.G));
-    };
-    int r = split + n * (tid >> 5);
-    uint32_t row = row_at(r);
-    asm volatile("" : "+v"(row));
+    Share<D, WAVES> own;                                // found ahead of the wait
+    own.begin(split, n, rows, tid);
+    own.find(p, pc, n, WR, tid);
+    asm volatile("" : "+v"(own.k), "+v"(own.row), "+v"(own.ml), "+v"(own.part[0]), "+v"(own.part[1]), "+v"(own.part[2]), "+v"(own.part[3]),
+                 "+v"(own.part[4]), "+v"(own.part[5]), "+v"(own.part[6]), "+v"(own.part[7]));
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's partials are in the L2 ...
     __syncthreads();                                    // ... and all the workgroup's
     if (tid < 64) {
@@ -1508,28 +1574,31 @@ __device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, 
             return __builtin_amdgcn_ballot_w64(!in_a && !in_b) == 0ull;
         };
         say(tag << 8);
-        const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
         bool all = look(!together);
-        while (!all) {
-            if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > p.wait_ticks) {
-                say(tag << 8 | 1);
-                all = look(true);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            all = look(!together);
+        if (!all) {
+            const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+            do {
+                if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > p.wait_ticks) {
+                    say(tag << 8 | 1);
+                    all = look(true);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                all = look(!together);
+            } while (!all);
         }
         if (all && !together) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (lane == 0) { said[0] = all; said[1] = (uint32_t)left; }
+        if (lane == 0) *reinterpret_cast<uint2 *>(said) = make_uint2(all, (uint32_t)left);
     }
     __syncthreads();
-    if (!__builtin_amdgcn_readfirstlane(said[0])) return;
-    uint32_t left = __builtin_amdgcn_readfirstlane(said[1]) & ~(1u << split);
-    for (;;) {
-        for (; r < rows; r += n * WAVES * 2, row = row_at(r)) merge_row<D>(p, row, (uint32_t)(pc.group * n * pc.pitch + r), pc.pitch, n, wsh + (tid >> 5) * 32, tid);
-        if (!left) break;
-        r = __builtin_ctz(left) + n * (tid >> 5);       // (rare) the share of one that has left
-        row = row_at(r);
+    const uint2 seen = *reinterpret_cast<const uint2 *>(said);
+    if (!__builtin_amdgcn_readfirstlane(seen.x)) return;
+    merge_share<D, WAVES>(p, pc, own, n, WR, reinterpret_cast<float *>(smem), tid);
+    uint32_t left = __builtin_amdgcn_readfirstlane(seen.y) & ~(1u << split);
+    while (left) {                                      // (rare) the shares of those that have left
+        own.begin(__builtin_ctz(left), n, rows, tid);
+        own.find(p, pc, n, WR, tid);
+        merge_share<D, WAVES>(p, pc, own, n, WR, reinterpret_cast<float *>(smem), tid);
         left &= left - 1;
     }
     if (tid == 0) __hip_atomic_store(&m.epoch, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

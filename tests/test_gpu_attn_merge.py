@@ -1,7 +1,8 @@
 """The merge of split partials by the workgroups that stored them, against the merge by a second launch (needs an MI355X).
 
-Both do the same arithmetic on the same partials in the same order, so the outputs are compared bit for bit; the second launch's
-parity with the oracle is test_gpu_attn.py's and test_gpu_fp8kv.py's.  Every way a workgroup can take is forced: it waits for the
+Both do the same arithmetic on the same partials; the sums over the splits differ in their order, that is by some 1e-6 of the terms
+before the final rounding to bf16, which may then fall to the neighbouring number (spacing: at most 2^-7 of it).  The second launch's
+parity with the oracle is test_gpu_attn.py's and test_gpu_fp8kv.py's.  All ways of the merge by workgroups give the same bits.  Every way a workgroup can take is forced: it waits for the
 others, it leaves at once (the last one then merges for all), and it does not rely on a common L2.
 """
 import pytest
@@ -30,25 +31,32 @@ def _call(x, L, ws, nsplit, shape, **how):
     return O
 
 
+def _close(O, ref):
+    o, r = O.float(), ref.float()
+    return bool(((o - r).abs() <= r.abs() * 2.0 ** -7 + 1e-6).all())
+
+
 # (L, M, Hq, Hkv, D, fp8, shape, splits): one row block and several, a ragged last one, a single row in it, heads that fill the
 # XCDs and heads that only do so with their row blocks, the most splits, two workgroups on a CU, no room for all at once, few heads
 CASES = [(8192, 64, 32, 8, 128, False, 2, 16), (3001, 33, 32, 8, 128, False, 1, 9), (2000, 65, 16, 8, 128, False, 2, 5),
          (4000, 256, 32, 8, 128, False, 3, 8), (1531, 23, 32, 8, 64, False, 1, 13), (900, 128, 8, 2, 128, False, 1, 7),
          (700, 97, 16, 4, 64, False, 2, 4), (5000, 7, 64, 8, 128, False, 1, 32), (12003, 33, 32, 8, 128, True, 1, 20),
          (500, 100, 32, 8, 128, True, 2, 3), (333, 5, 16, 16, 64, False, 1, 2), (4000, 200, 32, 8, 128, False, 1, 8),
-         (1000, 40, 8, 2, 128, False, 1, 6), (20000, 3, 8, 8, 64, False, 3, 32)]
+         (1000, 40, 8, 2, 128, False, 1, 6), (20000, 3, 8, 8, 64, False, 3, 32), (8192, 64, 32, 8, 128, False, 3, 29)]
 
 
 @pytest.mark.parametrize("case", CASES)
-def test_same_bits_as_the_second_launch(case):
+def test_same_as_the_second_launch(case):
     L, M, Hq, Hkv, D, fp8, shape, nsplit = case
     x = _inputs(L, L, M, Hq, Hkv, D, fp8)
     ws = btv.alloc_workspace(btv.btv_tree_verify_attn_tuned_workspace(M, L, Hq, Hkv, D, fp8, nsplit, shape))
     ref = _call(x, L, ws, nsplit, shape, merge=1)
     assert torch.isfinite(ref).all()
+    first = _call(x, L, ws, nsplit, shape, merge=2)
+    assert _close(first, ref)
     for how in WAYS + WAYS[:2]:
         O = _call(x, L, ws, nsplit, shape, **how)
-        assert torch.equal(O, ref), how
+        assert torch.equal(O, first), how
     assert btv.btv_workspace_status(ws) == 0
 
 
@@ -66,7 +74,7 @@ def test_a_workspace_over_changing_sizes_and_ways():
     for k in range(3):
         for i, (x, c) in enumerate(zip(ins, cases)):
             O = _call(x, c[0], ws, c[7], c[6], **WAYS[(i + k) % len(WAYS)])
-            assert torch.equal(O, refs[i]), (k, c)
+            assert _close(O, refs[i]), (k, c)
         O = torch.full_like(Q, float("nan"))
         btv.btv_tree_verify_attn_paged(Q, pages(K), pages(V), torch.arange(36, dtype=torch.int32, device="cuda").reshape(1, 36), i32(0, 64),
                                        i32(512), par, 64, 512, O, ws)
@@ -79,7 +87,7 @@ def test_replays_of_a_graph():
     L, M, Hq, Hkv, D, fp8, shape, nsplit = CASES[0]
     x, y = _inputs(1, L, M, Hq, Hkv, D, fp8), _inputs(2, L, M, Hq, Hkv, D, fp8)
     ws = btv.alloc_workspace(btv.btv_tree_verify_attn_tuned_workspace(M, L, Hq, Hkv, D, fp8, nsplit, shape))
-    ref = [_call(z, L, ws, nsplit, shape, merge=1) for z in (x, y)]
+    ref = [_call(z, L, ws, nsplit, shape, merge=2) for z in (x, y)]
     st = [t.clone() for t in x]
     O = torch.empty_like(x[0])
     run = lambda: btv.btv_tree_verify_attn_merge_tuned(st[0], st[1], st[2], st[3], L, O, ws, 0.0, nsplit, shape, merge=0)
