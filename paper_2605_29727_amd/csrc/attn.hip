@@ -1160,14 +1160,18 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                 if (fill_now) issue_part(std::integral_constant<int, 0>{});      // behind four MFMAs: its issue stall is covered
                 if constexpr (PH < 0) read_v_half_at<D, 1>(v0, vh);                     // V(i-1) second half  queue: K(i+1)lo, V(i-1)b
                 else rv(std::integral_constant<int, PH + 7>{}, C1{});
+                __builtin_amdgcn_sched_barrier(0);
                 exp_half(x, 0, pcur[0], ts);
-                __builtin_amdgcn_sched_barrier(0);                // (the exponentials stay in front of the wait: they cover the reads)
+                asm volatile("" : "+v"(pcur[0]), "+v"(ts));       // (the exponentials stay between the reads and their wait)
+                __builtin_amdgcn_sched_barrier(0);
                 wait_v_half<DT, 0>(vh);                           // V(i-1) second half (and K(i+1) low)
                 pv_half<DT>(vh, pprev[1], oacc);
                 if (fill_now) issue_part(std::integral_constant<int, 1>{});
                 if constexpr (PH < 0) read_v_half_at<D, 0>(v1, vh);                     // V(i) first half     queue: V(i)a
                 else rv(std::integral_constant<int, PH>{}, C0{});
+                __builtin_amdgcn_sched_barrier(0);
                 exp_half(x, 1, pcur[1], ts);
+                asm volatile("" : "+v"(pcur[1]), "+v"(ts));
                 __builtin_amdgcn_sched_barrier(0);
                 if (__builtin_amdgcn_ballot_w64(!(ts <= GROW)) != 0ull) regrow(pcur, ts);     // rare
                 l_run += ts;
