@@ -197,7 +197,7 @@ constexpr int SW_THIN = 96;                 // nodes up to which a level is one 
 struct alignas(16) SweepLds {
     // score bits << 32 | depth, parent and rank of a candidate (sweep_meta); a level's candidates lie in lexicographic
     // order of their rank paths.  At the end the upper half takes the candidate's place in the tree.
-    uint2 cand[SW_CAP];
+    uint2 cand[SW_CAP + 4];                 // (and four places for what sweep_thin writes past the last)
     alignas(16) int coarse[SW_COARSE];      // candidates per bin
     alignas(16) int hist[SW_BINS];          // candidates that are left, per bin; then those in the bins above
     int at[SW_BINS];                        // next place of the bin in `key`
@@ -206,6 +206,7 @@ struct alignas(16) SweepLds {
     alignas(16) int cnt[2][BTV_MAX_NODES];  // children per node of a block of 256
     int wsum[4];
     int d, a, b, th;                        // where the sweep stands
+    int kept;
     double wd[4];
     int n_stop;
 };
@@ -612,7 +613,10 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
 // after its parent and after its elder siblings, so the tree is the set of the N first prefixes of that order, and nothing
 // about it needs the frontier, nor any order before the end.  The levels are swept once with a threshold that only
 // rises: level d's candidates are the children of level d-1's candidates that score above it (a node deeper than N nodes that
-// score at least as much cannot be among the first N), and after every level the threshold moves up to the lower
+// score at least as much cannot be among the first N).  It begins at the N-th best of a set of prefixes that need no sweep
+// (sweep_bound), which as a rule leaves so few candidates, in thin levels, that one wavefront goes through them all with the threshold
+// as it is (sweep_thin): N = 256 of a confident drafter, 13 levels: 600 candidates instead of 1480 without it, the sweep 14.8 ->
+// 10.1 us.  Where they are many all the same, the rest is swept with a threshold that moves up, after a level, to the lower
 // edge of the bin that holds the N-th best candidate so far (a histogram of the scores' bits, 4 bins per binade, to which every
 // candidate is added once; a suffix sum finds the bin).  A child of rank r is not needed either where the product of
 // (rank + 1) along its path exceeds N: that many prefixes of its own level come before it (kept per node as the most
@@ -742,22 +746,169 @@ __device__ __forceinline__ int sweep_raise(const SweepLds &L, int N, int lane)
     const int incl = wave_incl_scan(own), need = N - (__builtin_amdgcn_readlane(incl, 63) - incl);      // that many of this lane's best
     const int sel = (y.w < need) + (s6 < need) + (s5 < need) + (s4 < need) + (s3 < need) + (s2 < need) + (s1 < need);
     const u64 here = __builtin_amdgcn_ballot_w64(need > 0 && own >= need);
-    const int src = here != 0ull ? __builtin_ctzll(here) : 0;
+    if (here == 0ull) return -1;                               // fewer than N of them
+    const int src = __builtin_ctzll(here);
     return (8 * src + 7 - __builtin_amdgcn_readlane(sel, src)) << 21;
 }
 
-// Whole sweep.  Returns the number of candidates, -1 if they do not fit; th: the last threshold (score bits, as a signed number,
-// that a new candidate must exceed; -1 while there are fewer than N of them).
-__device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int floor, int &th)
+// A threshold to start from, by the whole workgroup: the greedy chain's nodes and the 64 best siblings of each are prefixes, and so
+// are all first tokens; the N-th best of them is no better than the N-th best of all.  Lower edge of its bin less one (a
+// score on the edge counts: it may be that of a lesser depth), -1 if there are fewer.  Not where the marginals are no
+// probabilities: a child may then be better than its parent.  (The chain's scores by a scan, a little less than they are: a score's exact
+// rounding does not matter here.  Scores fall from lane to lane, so one lane counts for all of a bin's: atomics of many lanes on
+// few bins took 2.4 us in all.)
+__device__ __forceinline__ int sweep_bound(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w)
 {
-    const int tid = w * 64 + lane, K1 = min(K, N);
+    const int tid = w * 64 + lane, K1 = min(K, N), most = min(K1, 64);
+    if (tid < SW_COARSE / 4) reinterpret_cast<int4 *>(L.coarse)[tid] = make_int4(0, 0, 0, 0);
+    const float first = S.q[min(tid, K - 1)], best = lane < B ? S.q[lane * KP] : 1.0f;
+    float own[MAXB / 4];                                       // wavefront w: positions w + 1, w + 5, ..
+#pragma unroll
+    for (int u = 0; u < MAXB / 4; ++u) own[u] = S.q[min(4 * u + w + 1, B - 1) * KP + min(lane, K - 1)];
+    const int least = K >= N ? (int)__float_as_uint(__fmul_rn(1.0f, S.q[N - 1])) - 1 : -1;      // (N first tokens are that good)
+    const bool sound = __builtin_amdgcn_ballot_w64(!(best <= 1.0f)) == 0ull;
+    float chain = best;                                        // lane k: of the chain's node at depth k + 1
+    auto step = [&](auto ctrl) {
+        const float o = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0x3F800000, (int)__float_as_uint(chain), decltype(ctrl)::value, 0xF, 0xF, false));
+        chain *= o;
+    };
+    step(std::integral_constant<int, 0x111>{}); step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{}); step(std::integral_constant<int, 0x118>{});
+    chain *= 0.99999f;
+    __syncthreads();
+    auto count = [&](uint32_t score, int n) {
+        const int more = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && (int)score > least));
+        const int bin = sweep_coarse(score), bin1 = __builtin_amdgcn_update_dpp(0, bin, 0x101, 0xF, 0xF, false);      // row_shl:1
+        const int at = (lane & 15) + 1;                        // (rows of 16 lanes, each for itself)
+        const bool last = lane == more - 1 || at == 16;
+        if (lane < more && (last || bin != bin1)) {
+            atomicAdd(&L.coarse[bin], at);
+            if (!last) atomicAdd(&L.coarse[bin1], -at);
+        }
+    };
+    count(__float_as_uint(__fmul_rn(1.0f, first)), K1 - w * 64);
+#pragma unroll
+    for (int u = 0; u < MAXB / 4; ++u)
+        if (4 * u + w + 1 < B)
+            count(__float_as_uint(__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(chain), min(4 * u + w, 15))) * own[u]), most);
+    __syncthreads();
+    return sound ? max(sweep_raise(L, N, lane) - 1, -1) : -1;
+}
+
+// Levels 1, 2, .. by one wavefront, with the threshold as it is.  What a level costs is one instruction after the other, some 7 cycles
+// each: the next level's probabilities are asked for a level ahead; a node that has children writes four, the last first, so that those that
+// it does not have are overwritten by the nodes behind it; the rest of a wide fan is tested and written with one probability per
+// lane; no histogram is kept.  Stops (d, a, b as in sweep_levels) at a level that is wide, or where the candidates become many.
+__device__ __forceinline__ void sweep_thin(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int bound, int th, int &d, int &a, int &b)
+{
+    const int K1 = min(K, N);
+    d = 2; a = 0; b = 0;
+    for (int t0 = 0; t0 < K1; t0 += 64) {                      // level 1: the best tokens of position 0, already in order
+        const int t = t0 + lane;
+        const uint32_t score = __float_as_uint(__fmul_rn(1.0f, S.q[min(t, K - 1)]));
+        const bool in = t < K1 && (int)score > bound;          // (the first is kept whatever the floor)
+        if (in) L.cand[t] = make_uint2(sweep_meta(SW_ROOT, (uint32_t)t, 0, sweep_share(N, t)), score);
+        const int got = __builtin_popcountll(__builtin_amdgcn_ballot_w64(in));
+        b += got;
+        if (got < 64) break;
+    }
+    const float inv_rank = __builtin_amdgcn_rcpf((float)(lane + 5));     // (sweep_share of rank 4 + lane)
+    const int r1 = min(1, K - 1), r2 = min(2, K - 1), r3 = min(3, K - 1), rv = min(4 + lane, K - 1);
+    float q[5], nq[5];                                         // ranks 0 .. 3, and 4 + lane, of position d - 1
+    auto fetch = [&](int dd, float (&x)[5]) {
+        const float *qd = S.q + (min(dd, B) - 1) * KP;
+        x[0] = qd[0]; x[1] = qd[r1]; x[2] = qd[r2]; x[3] = qd[r3]; x[4] = qd[rv];
+    };
+    fetch(2, q);
+    const uint32_t cand = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)L.cand;
+    uint32_t level = 1u << 20;                                 // what sweep_meta adds for depth - 1
+    while (d <= B && a < b && b - a <= 2 * SW_THIN && b <= SW_CAP / 4) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint2 x = L.cand[min(a + lane, b - 1)];
+        fetch(d + 1, nq);
+        int nb = b;
+        for (int a0 = a; a0 < b; a0 += 64) {
+            const int i = a0 + lane;
+            const float rp = __uint_as_float(x.y);
+            const int cap = (int)(x.x >> 24) + 1, most = i < b ? min(cap, K) : 0;
+            if (a0 + 64 < b) x = L.cand[min(i + 64, b - 1)];
+            uint32_t sc[4];
+            int c = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                sc[r] = __float_as_uint(__fmul_rn(rp, q[r]));
+                c += (int)sc[r] > th ? 1 : 0;                  // (the scores fall with the rank)
+            }
+            c = min(c, most);
+            const u64 wide = __builtin_amdgcn_ballot_w64(min(c, most - 1) >= 4);
+            for (u64 left = wide; left != 0ull; left &= left - 1ull) {
+                const int src = __builtin_ctzll(left), wm = __builtin_amdgcn_readlane(most, src);
+                const float wr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rp), src));
+                int cnt = 4 + __builtin_popcountll(__builtin_amdgcn_ballot_w64(4 + lane < wm && (int)__float_as_uint(__fmul_rn(wr, q[4])) > th));
+                for (int r0 = 68; __builtin_expect(cnt == r0 && r0 < wm, 0); r0 += 64) {
+                    const int r = r0 + lane;
+                    cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(r < wm && (int)__float_as_uint(__fmul_rn(wr, S.q[(d - 1) * KP + min(r, K - 1)])) > th));
+                }
+                c = lane == src ? cnt : c;
+            }
+            const int incl = wave_incl_scan(c), total = __builtin_amdgcn_readlane(incl, 63), off = nb + incl - c;
+            if (__builtin_expect(nb + total > SW_CAP, 0)) { b = SW_CAP + 1; return; }        // (marginals that are no probabilities)
+            const uint32_t meta = (uint32_t)i + level - (1u << 24);
+            const uint32_t part[4] = { (uint32_t)cap, (uint32_t)cap >> 1, ((uint32_t)cap * 171u) >> 9, (uint32_t)cap >> 2 };     // cap / (r + 1)
+            if (c > 0) {                                       // (these nodes' first places are all different; raw writes, which stay in this order)
+                const uint32_t at = cand + 8u * (uint32_t)off;
+#define BTV_PUT(R)                                                                                                                \
+    {                                                                                                                             \
+        const u64 e_ = ((u64)sc[R] << 32) | (meta + ((uint32_t)R << 12) + (part[R] << 24));                                       \
+        asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(at), "v"(e_), "n"(8 * R) : "memory");                                  \
+    }
+                BTV_PUT(3) BTV_PUT(2) BTV_PUT(1) BTV_PUT(0)
+#undef BTV_PUT
+            }
+            for (u64 left = wide; left != 0ull; left &= left - 1ull) {
+                const int src = __builtin_ctzll(left);
+                const int wc = __builtin_amdgcn_readlane(c, src), wo = __builtin_amdgcn_readlane(off, src), wp = __builtin_amdgcn_readlane(cap, src);
+                const float wr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rp), src));
+                const uint32_t wm = (uint32_t)(a0 + src) + level - (1u << 24);
+                if (4 + lane < wc)
+                    L.cand[wo + 4 + lane] = make_uint2(wm + ((uint32_t)(4 + lane) << 12) + ((uint32_t)(((float)wp + 0.5f) * inv_rank) << 24), __float_as_uint(__fmul_rn(wr, q[4])));
+                if (__builtin_expect(wc > 68, 0))
+                    for (int r = 68 + lane; r < wc; r += 64)
+                        L.cand[wo + r] = make_uint2(sweep_meta((uint32_t)(a0 + src), (uint32_t)r, d - 1, sweep_share(wp, r)),
+                                                    __float_as_uint(__fmul_rn(wr, S.q[(d - 1) * KP + r])));
+            }
+            nb += total;
+        }
+        a = b; b = nb;
+        ++d;
+        level += 1u << 20;
+#pragma unroll
+        for (int r = 0; r < 5; ++r) q[r] = nq[r];
+    }
+}
+
+// Whole sweep.  Returns the number of candidates, -1 if they do not fit.
+__device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int floor)
+{
+    const int tid = w * 64 + lane;
+    int d, a, b, buf = 0;                                      // a .. b - 1: the candidates of the level before
+    const int bound = sweep_bound(S, L, B, K, KP, N, lane, w);
+    int th = max(floor, bound);
+    if (w == 0) {
+        sweep_thin(S, L, B, K, KP, N, lane, bound, th, d, a, b);
+        if (lane == 0) { L.d = d; L.a = a; L.b = b; }
+    }
+    __syncthreads();
+    d = __builtin_amdgcn_readfirstlane(L.d); a = __builtin_amdgcn_readfirstlane(L.a); b = __builtin_amdgcn_readfirstlane(L.b);
+    if (b > SW_CAP) return -1;
+    if (d > B || a == b) return b;
+    // ---- wide levels, or many candidates: with a threshold that rises ------------------------------------------------------
+    __syncthreads();
     if (tid < SW_COARSE / 4) reinterpret_cast<int4 *>(L.coarse)[tid] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    if (tid < K1)                                              // level 1: the K best tokens of position 0, already in order
-        sweep_put(L, tid, __float_as_uint(__fmul_rn(1.0f, S.q[tid])), sweep_meta(SW_ROOT, (uint32_t)tid, 0, sweep_share(N, tid)));
+    for (int c = tid; c < b; c += 256) atomicAdd(&L.coarse[sweep_coarse(L.cand[c].y)], 1);
     __syncthreads();
-    int d = 2, a = 0, b = K1, buf = 0;                         // the level before: candidates a .. b - 1
-    th = floor;
+    floor = th;
     bool raised = false;
     for (;;) {
         if (w == 0) {
@@ -792,7 +943,7 @@ __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int
         d = __builtin_amdgcn_readfirstlane(L.d); a = __builtin_amdgcn_readfirstlane(L.a); b = __builtin_amdgcn_readfirstlane(L.b);
         th = __builtin_amdgcn_readfirstlane(L.th);
         if (d == 0) return -1;
-        if (d > B || a == b) break;
+        if (d > B || a == b) return b;
         // ---- a wide level, by the whole workgroup ----------------------------------------------------------------------
         const float *qd = S.q + (d - 1) * KP;
         const float qr[4] = { qd[0], qd[min(1, K - 1)], qd[min(2, K - 1)], qd[min(3, K - 1)] };
@@ -815,8 +966,6 @@ __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int
         a = b; b = nb;
         ++d;
     }
-    th = b > N ? sweep_raise(L, N, lane) : -1;                 // (what lies below the threshold's bin is not looked at any more)
-    return b;
 }
 
 // star: the tree is the N best tokens of the first position.  floor: nodes that score no more (bits; -1: none) are not wanted.
@@ -835,16 +984,13 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
 #pragma unroll
     for (int i = 0; i < SW_BINS / 1024; ++i) reinterpret_cast<int4 *>(L.hist)[i * 256 + tid] = make_int4(0, 0, 0, 0);
     // ---- the N first of the candidates, in order ---------------------------------------------------------------------
-    int th;
-    const int b = sweep_levels(S, L, B, K, KP, N, lane, w, floor, th);
+    const int b = sweep_levels(S, L, B, K, KP, N, lane, w, floor);
     if (b < 0) return false;                                   // (uniform)
     np = min(b, N);
-    for (int c = tid; c < b; c += 256) {
-        const uint32_t r = L.cand[c].y;
-        if ((int)r >= th) atomicAdd(&L.hist[sweep_bin(r)], 1);
-    }
+    for (int c = tid; c < b; c += 256) atomicAdd(&L.hist[sweep_bin(L.cand[c].y)], 1);
+    if (tid == 0) L.kept = b;
     __syncthreads();
-    int kept;                                                  // candidates that are left
+    int kept;                                                  // candidates in the bins of the first N
     {                                                          // thread t: bins 8 t .. 8 t + 7, and what lies above them
         const int4 x = reinterpret_cast<const int4 *>(L.hist)[2 * tid], y = reinterpret_cast<const int4 *>(L.hist)[2 * tid + 1];
         const int s7 = y.w, s6 = s7 + y.z, s5 = s6 + y.y, s4 = s5 + y.x, s3 = s4 + x.w, s2 = s3 + x.z, s1 = s2 + x.y, own = s1 + x.x;
@@ -853,18 +999,22 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
         __syncthreads();
         const int t0 = L.wsum[0], t1 = L.wsum[1], t2 = L.wsum[2], t3 = L.wsum[3];
         const int up = total - incl + (w < 1 ? t1 : 0) + (w < 2 ? t2 : 0) + (w < 3 ? t3 : 0);
-        kept = t0 + t1 + t2 + t3;
         const int4 p = make_int4(up + s1, up + s2, up + s3, up + s4), q = make_int4(up + s5, up + s6, up + s7, up);
         reinterpret_cast<int4 *>(L.hist)[2 * tid] = p;
         reinterpret_cast<int4 *>(L.hist)[2 * tid + 1] = q;
         reinterpret_cast<int4 *>(L.at)[2 * tid] = p;
         reinterpret_cast<int4 *>(L.at)[2 * tid + 1] = q;
+        if (up < N && up + own >= N)                           // the bin of the N-th is one of these: what is above it, and it
+            L.kept = q.z + y.z >= N ? (q.w + y.w >= N ? q.w + y.w : q.z + y.z) : q.y + y.y >= N ? q.y + y.y : q.x + y.x >= N ? q.x + y.x :
+                     p.w + x.w >= N ? p.w + x.w : p.z + x.z >= N ? p.z + x.z : p.y + x.y >= N ? p.y + x.y : p.x + x.x;
     }
     __syncthreads();
+    kept = L.kept;
     if (kept > SW_KEEP) return false;                          // (uniform) scores that are nearly all the same
     for (int c = tid; c < b; c += 256) {
         const uint32_t r = L.cand[c].y;
-        if ((int)r >= th) L.key[atomicAdd(&L.at[sweep_bin(r)], 1)] = ((u64)r << 32) | (u64)(0xFFFFFFFFu - (uint32_t)c);
+        const int bin = sweep_bin(r);
+        if (L.hist[bin] < N) L.key[atomicAdd(&L.at[bin], 1)] = ((u64)r << 32) | (u64)(0xFFFFFFFFu - (uint32_t)c);
     }
     __syncthreads();
     for (int p = tid; p < kept; p += 256) {
@@ -1249,13 +1399,13 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         beam_block(S, BM, B, K, KP, beam_width, tid, parent, token, depth, rho, n_out, ahat);
         return;
     }
-    // Which expansion: the sweep pays per level (about 0.9 us, and 2 us at the end), the one-wavefront loop per node (0.27 us up to 64
-    // nodes, 0.41 us at 256), so the loop is left with the smallest trees that may be deep.  The tree cannot be deeper
+    // Which expansion: the sweep pays per level (about 0.4 us, 1.4 us for its threshold and 2 us at the end), the one-wavefront loop per
+    // node (0.24 us up to 64 nodes, 0.5 us at 256), so the loop is left with the smallest trees that may be deep.  The tree cannot be deeper
     // than the greedy chain stays above the N-th best token of the first position (every node scores at least as much as
     // the tree's last one, which scores at least that).
-    // 16 positions x 128256 tokens, HIP-graph replays, sweep / loop: flat marginals (a star) N = 64: 14.8 / 27.9 us, N = 256: 22 / 114;
-    // depth 5 .. 6: N = 64: 20.3 / 27.9, N = 256: 32 / 114; a confident drafter (depth 8 .. 13) N = 8: 17.5 / 13.4, N = 16: 19.3 / 15.2,
-    // N = 64: 23.6 / 28, N = 256: 35 / 113 (65 with a pool kept in order from level to level, which this replaced).
+    // 16 positions x 128256 tokens, HIP-graph replays, sweep / loop: a confident drafter (depth 8 .. 13) N = 16: 17.7 / 15.0 us, N = 32: 19.9 /
+    // 19.3, N = 48: 20.7 / 23.1, N = 64: 21.4 / 27.1, N = 256: 26.8 / 137; depth 4 .. 5: N = 16: 14.8 / 15.0, N = 24: 15.6 / 16.9, N = 64:
+    // 18.1 / 27.1; 4 positions x 64 tokens, N = 16: 10.0 / 11.2.
     if (w == 0) {
         const int k = min(lane, B - 1);
         const float chain = row_incl_sum(lane < B ? __log2f(S.q[k * KP]) : -1e30f);      // (an estimate: the choice changes no result)
@@ -1291,7 +1441,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
             if (lane == 0) { L_floor[0] = floor_of(a0); L_floor[1] = floor_of(a1); }
         }
         if (lane == 0)
-            use_levels = algo == 0 && star ? 2 : algo == 2 || (algo == 0 && (N > 64 || 2.0f + 0.9f * (float)min(reach, N) < 1.2f + 0.27f * (float)N)) ? 1 : 0;
+            use_levels = algo == 0 && star ? 2 : algo == 2 || (algo == 0 && (N > 64 || 1.8f + 0.4f * (float)min(reach, N) < 0.19f * (float)N)) ? 1 : 0;
     }
     __syncthreads();
     if (use_levels) {

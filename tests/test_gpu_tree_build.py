@@ -112,3 +112,18 @@ def test_more_candidates_than_the_selection_keeps(G, oracle):
     for marg in (uniform, ramp, steps, mixed):
         for N in (7, 64, 256):
             _check(G, oracle, marg, N)
+
+
+@pytest.mark.parametrize("N", [5, 64, 97, 256])
+def test_wide_fans_along_the_chain(G, oracle, N):
+    """What the thin levels of the sweep do with fans: one and several nodes of a level with more than 4 and more than 68 children above the
+    threshold, with and without ties, down to a threshold that scores lie on exactly (powers of two are edges of its bins)."""
+    B, V = 16, 400
+    flat = np.tile(1e-3 * 0.9995 ** np.arange(V), (B, 1))
+    one = flat.copy(); one[:, 17] = 0.6                                       # a chain with many near-equal siblings at every depth
+    two = flat.copy(); two[:, 17] = 0.5; two[:, 18] = 0.4999                  # 2^depth chains
+    tied = np.full((B, V), 2.0 ** -9); tied[:, 3] = 0.5                       # all siblings tie, on an edge
+    halves = np.tile(2.0 ** -np.arange(1.0, 11.0), (B, 1))                    # every score a power of two
+    first = one.copy(); first[0] = 0.002 * 0.998 ** np.arange(V)             # a wide first level, confident from there on
+    for marg in (one, two, tied, halves, first):
+        _check(G, oracle, marg.astype(np.float32), N)
