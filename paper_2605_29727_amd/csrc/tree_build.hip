@@ -1183,34 +1183,38 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
             live |= j < chunks ? 1u << j : 0u;
         }
     }
-    for (int b = tid; b < (TBINS + TBINS / 16) / 4; b += 256) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
     if (tid == 0) { RL.nsel = 0; RL.nslot = 0; }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 16; ++j) if ((live >> j) & 1u) atomicAdd(&RL.bins[bin_at((int)(pv[j] >> 19))], 1);
-    for (int j = 16; j < chunks; ++j) atomicAdd(&RL.bins[bin_at((int)(pr[(size_t)j * 256].x >> 19))], 1);
-    __syncthreads();
-    {
-        int hb[16], own = 0;                                   // thread t owns bins 16t .. 16t+15
-#pragma unroll
-        for (int b = 0; b < 16; ++b) { hb[b] = RL.bins[tid * 17 + b]; own += hb[b]; }
-        const int incl = wave_incl_scan(own), wtot = __builtin_amdgcn_readlane(incl, 63);
-        if (lane == 0) RL.wsum[w] = wtot;
+    // A row of so few marginals that all of them can be ranked needs no bound (4 x 64 of them, N = 16: 10.0 -> 8.0 us).
+    const bool few = lge == 0 && V <= RANK_FEW;                // (uniform)
+    if (!few) {
+        for (int b = tid; b < (TBINS + TBINS / 16) / 4; b += 256) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        int above = wtot - incl;                               // in the bins of the higher threads
-        for (int ww = w + 1; ww < 4; ++ww) above += RL.wsum[ww];
-        if (above < K && above + own >= K) {
-            int cum = above, sel = tid * 16;
 #pragma unroll
-            for (int b = 15; b >= 0; --b) {
-                if (cum < K && cum + hb[b] >= K) sel = tid * 16 + b;
-                cum += hb[b];
+        for (int j = 0; j < 16; ++j) if ((live >> j) & 1u) atomicAdd(&RL.bins[bin_at((int)(pv[j] >> 19))], 1);
+        for (int j = 16; j < chunks; ++j) atomicAdd(&RL.bins[bin_at((int)(pr[(size_t)j * 256].x >> 19))], 1);
+        __syncthreads();
+        {
+            int hb[16], own = 0;                                   // thread t owns bins 16t .. 16t+15
+#pragma unroll
+            for (int b = 0; b < 16; ++b) { hb[b] = RL.bins[tid * 17 + b]; own += hb[b]; }
+            const int incl = wave_incl_scan(own), wtot = __builtin_amdgcn_readlane(incl, 63);
+            if (lane == 0) RL.wsum[w] = wtot;
+            __syncthreads();
+            int above = wtot - incl;                               // in the bins of the higher threads
+            for (int ww = w + 1; ww < 4; ++ww) above += RL.wsum[ww];
+            if (above < K && above + own >= K) {
+                int cum = above, sel = tid * 16;
+#pragma unroll
+                for (int b = 15; b >= 0; --b) {
+                    if (cum < K && cum + hb[b] >= K) sel = tid * 16 + b;
+                    cum += hb[b];
+                }
+                RL.sel_bin = sel;
             }
-            RL.sel_bin = sel;
+            __syncthreads();                                       // the histogram is dead from here on: sel[] takes its place
         }
-        __syncthreads();                                       // the histogram is dead from here on: sel[] takes its place
     }
-    const uint32_t tau = (uint32_t)RL.sel_bin << 19;
+    const uint32_t tau = few ? 0u : (uint32_t)RL.sel_bin << 19;
     // ---- the candidates.  A slot whose maximum reaches the bound holds a candidate; when its second largest stays
     // below the bound, which is the rule (K of thousands of slots are taken), that maximum is the slot's only one
     // and goes to the list as it stands, with the token id that its place in the slot gives.  The other slots
@@ -1229,7 +1233,10 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         }
         return first + incl - mine;
     };
-    {
+    if (few) {
+        if (tid < V) RL.sel[tid] = ((u64)pv[0] << 32) | (u64)(0xFFFFFFFFu - (uint32_t)tid);
+        if (tid == 0) RL.nsel = V;
+    } else {
         uint32_t one = 0u, more = 0u;                           // chunks whose slot holds one candidate / maybe several
 #pragma unroll
         for (int j = 0; j < 16; ++j)

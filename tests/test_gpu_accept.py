@@ -404,3 +404,19 @@ def test_stochastic_workspace_serves_changing_sizes(G, oracle):
         for k, (V, args, ref) in enumerate(cases[turn:] + cases[:turn]):
             got = G.run_accept_stochastic(*args, tuned=((0, 3, 17)[(turn + k) % 3], -1 if k % 4 == 3 else 1000000), ws=ws)
             assert _same(got, ref) and got["status"] == 0, (turn, V)
+
+
+@pytest.mark.parametrize("bits", [False, True])
+@pytest.mark.parametrize("V,M", [(1, 3), (15, 127), (16, 128), (64, 127), (64, 128), (65, 63), (128, 63), (128, 64), (129, 31), (256, 31), (256, 32), (257, 31)])
+def test_greedy_small_vocabularies(G, oracle, V, M, bits):
+    """Around the sizes up to which one workgroup takes all rows: last rows and last tokens, ties (the lowest id), rows of -inf and of
+    signed zeros."""
+    parent = synth.tree_parents(V + M, M, "random")
+    token = (np.arange(M) % V).astype(np.int32)
+    x = np.round(synth.target_logits(V + M, M + 1, V, 2.0, "fp32")[1] * 2) / 2
+    x[0] = -np.inf
+    x[min(2, M), :] = -0.0
+    x[min(2, M), V // 2] = 0.0
+    x[M, V - 1] = 50.0                                                        # the very last element
+    store, xf = synth.round_to_dtype(x.astype(np.float64), "bf16" if bits else "fp32")
+    _greedy_case(G, oracle, store, xf, bits, parent, token)
