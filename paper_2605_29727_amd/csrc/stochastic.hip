@@ -39,7 +39,7 @@
 // For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
 //
 // What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
-// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 57 us against
+// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 45 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
 // levels, bf16: 860 .. 1280 -> 35 .. 44 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
 // tokens instead of 2048 (half the workgroups): 54 and 47 us at the same two.
@@ -56,8 +56,8 @@ constexpr int SA_T = 1024, SA_WAVES = SA_T / 64;
 constexpr int SA_MAX_WGS = 64;                          // slices: one lane of a wavefront per workgroup when parts are collected
 constexpr int SA_BINS = 1024;                           // bins of e / q, 32 per binade upwards from the current s
 constexpr int SA_GRID = 256;                            // points of the table that the first guesses come from
-constexpr int SA_PLANE = BTV_MAX_NODES;                 // points of an exchange: word i of point k at SA_PLANE * i + k
-constexpr int SA_WORDS = 4 * BTV_MAX_NODES;             // words of one workgroup's part: two doubles per point
+constexpr int SA_POINTS = BTV_MAX_NODES;                // points of an exchange
+constexpr int SA_WORDS = 4 * SA_POINTS;                 // words of one workgroup's part: point k's two doubles at 4 k
 constexpr int SA_CHAIN = 4;                             // rows of a first-child chain that are read and exchanged together
 constexpr int SA_CHAIN_FAN = 8;                         // children up to which a node's first child is worth reading ahead (it is one of
                                                         // several that the draft likes about as well, otherwise)
@@ -66,7 +66,7 @@ constexpr int SA_DIRECT = 3;                            // rejections that are w
 constexpr int SA_BATCH_MIN = 10;                        // children left from which the rest is solved at once (the price of ten exchanges)
 constexpr long long SA_WAIT_TICKS = 1000000ll;          // 10 ms of the 100 MHz wall clock
 constexpr uint32_t SA_SPAN = 1u << 20;                  // more tags than a call can use (256 nodes of at most 18 + 256 exchanges)
-static_assert(SA_PLANE * 4 <= SA_WORDS && SA_GRID <= SA_PLANE, "all words of an exchange fit");
+static_assert(SA_GRID <= SA_POINTS, "all points of an exchange fit");
 
 struct SaParams {
     const void *logits;
@@ -211,11 +211,11 @@ __device__ __forceinline__ double get_f64(u64 lo, u64 hi)
     return __longlong_as_double((long long)(((hi & 0xFFFFFFFFull) << 32) | (lo & 0xFFFFFFFFull)));
 }
 // N words of each of R workgroups' parts, R * N loads in flight, once they all carry the tag: workgroup first + k * step,
-// k < R, at offset `at` of its part and every STEP words from there; workgroups from G on (and lanes with want = false) are left out.  False: the limit
+// k < R, from offset `at` of its part on; workgroups from G on (and lanes with want = false) are left out.  False: the limit
 // has passed.  A wavefront sleeps between two looks, and where many words are exchanged only one wavefront of a
 // workgroup looks (at one word of each part) until everybody is there: sixteen wavefronts of every workgroup asking for the same
 // lines without a pause kept the stores to those lines from ever getting through.
-template <int R, int N, int STEP = 1>
+template <int R, int N>
 __device__ __forceinline__ bool take(const u64 *set, int first, int step, int G, int at, bool want, uint32_t tag, u64 (&w)[R][N],
                                      long long wait_ticks)
 {
@@ -226,7 +226,7 @@ __device__ __forceinline__ bool take(const u64 *set, int first, int step, int G,
             const u64 *p = set + (size_t)(first + k * step) * SA_WORDS + at;
             const bool in = want && first + k * step < G;
 #pragma unroll
-            for (int i = 0; i < N; ++i) w[k][i] = in ? __hip_atomic_load(p + i * STEP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
+            for (int i = 0; i < N; ++i) w[k][i] = in ? __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
         }
         bool ok = true;
 #pragma unroll
@@ -259,7 +259,7 @@ struct SaShared {
     int dead, status, acc, pick, last, late;
     float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
     double pt[BTV_MAX_NODES], ptG[BTV_MAX_NODES], invT[BTV_MAX_NODES];
-    double sE[SA_PLANE], sQ[SA_PLANE];
+    double sE[SA_POINTS], sQ[SA_POINTS], part[SA_T];
     int bin_at[SA_BINS + 1];                            // where bin b (0 = largest ratios) starts
     double cE[SA_T + 1], cQ[SA_T + 1];                  // sums over the sorted positions before PT * c
     float2 sorted[SA_T * BT];                           // (e, q) of the slice, e / q descending by bin (last: what lies
@@ -467,14 +467,16 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 forget();
                 const int K = nk - j, kj = k0 + j;
                 {
-                    const size_t at = (size_t)(cur + 1) * V;
-                    const void *brow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(p.logits) + at)
-                                            : static_cast<const void *>(static_cast<const float *>(p.logits) + at);
+                    // the row's tokens, from its four wavefronts to all of them
+                    if (here) {
+#pragma unroll
+                        for (int i = 0; i < TG; ++i) L.sorted[(tv - v0) + TS * (i / 4) + i % 4] = make_float2(e[i], q[i]);
+                    }
+                    __syncthreads();
                     const int bv = v0 + tid * BT;
-                    const float bm = L.Mx[r][me];
                     float be[BT], bq[BT];
-                    load_tokens<BF16, BT>(brow, bv, 4, v1, vec, -INFINITY, be);
-                    load_tokens<false, BT>(p.marg + (size_t)d * V, bv, 4, v1, vec, 0.f, bq);
+#pragma unroll
+                    for (int i = 0; i < BT; ++i) { const float2 x = L.sorted[tid * BT + i]; be[i] = x.x; bq[i] = x.y; }
                     const int b0 = (int)(__float_as_uint((float)(s * invf)) >> 18);
                     L.bin_at[tid] = 0;
                     if (wv == 0) {                      // 1 / T_k, and how far s can come
@@ -496,7 +498,6 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                     int rank[BT], bin[BT];
 #pragma unroll
                     for (int i = 0; i < BT; ++i) {      // (ratios below the current s never count again: left out)
-                        be[i] = exp_neg(be[i] - bm);
                         bin[i] = bv + i < v1 && f > 0.0 ? sa_bin(__fdiv_rn(be[i], bq[i]), b0) : SA_BINS;
                         rank[i] = bin[i] < SA_BINS ? atomicAdd(&L.bin_at[bin[i]], 1) : 0;
                     }
@@ -569,44 +570,54 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         E *= f;
                         ++seq;
                         if (G > 1) {
-                            if (sub == 0 && k < np) {
-                                u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + k;
-                                put_f64(o, o + SA_PLANE, base + seq, E); put_f64(o + 2 * SA_PLANE, o + 3 * SA_PLANE, base + seq, Q);
+                            if (sub < 4 && k < np) {    // four lanes a point: consecutive words by consecutive lanes
+                                const u64 b = (u64)__double_as_longlong(sub & 2 ? Q : E);
+                                put_u32(p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + 4 * k + sub, base + seq, (uint32_t)(sub & 1 ? b >> 32 : b));
                             }
                         } else if (sub == 0) {
                             L.sE[k] = E; L.sQ[k] = Q;
                         }
                     }
                     if (G > 1) {
-                        // summed in two exchanges: workgroup w adds up the points w, w + G, ... of all workgroups, and everybody reads
-                        // the sums (with everybody reading every part instead, 4 MB for 32 workgroups, a pass took 3 us longer)
+                        // summed in two exchanges: each workgroup adds up 2^lgp neighbouring points of all workgroups, and everybody
+                        // reads the sums (with everybody reading every part instead, 4 MB for 32 workgroups, a pass took 3 us
+                        // longer).  What an exchange of this size costs is the number of its requests, loads and stores alike: a
+                        // thread has one double of one part and neighbouring threads neighbouring doubles, so that 16 lanes share
+                        // a request where they read 8 points of a part (256 points, 32 workgroups: 9.3 -> 4.0 us both exchanges, 128
+                        // points 4.1 .. 5.8 -> 2.6 .. 3.2, against a lane that read all four words of its point, every lane in
+                        // another part; the same words written 256 bytes apart instead: 17 us).
+                        const int lgp = G >= np ? 0 : 32 - __builtin_clz((np - 1) / G), lgd = lgp + 1, lgw = min(lgd, 6);
                         const u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
-                        const int lg = 32 - __builtin_clz(G - 1), w = tid & ((1 << lg) - 1), pt = me + (tid >> lg) * G;
-                        u64 x[1][4];
+                        u64 x[1][2];
                         bool fine = true;
-                        if (me + (wv * 64 >> lg) * G < np) fine = take<1, 4, SA_PLANE>(set, w, 0, G, min(pt, SA_PLANE - 1), pt < np, base + seq, x, p.wait_ticks);
+                        const int mine = min(np - (me << lgp), 1 << lgp) * 2;      // doubles that this workgroup adds up
                         ++seq;
-                        if (fine && me + (wv * 64 >> lg) * G < np) {
-                            double E = w < G && pt < np ? get_f64(x[0][0], x[0][1]) : 0.0, Q = w < G && pt < np ? get_f64(x[0][2], x[0][3]) : 0.0;
+                        if (mine > 0) {
+                            const int w = tid >> lgd, dd = tid & ((1 << lgd) - 1);
+                            if ((wv * 64 >> lgd) < G) {
+                                const bool in = w < G && dd < mine;
+                                fine = take<1, 2>(set, w, 0, G, ((me << lgp) * 2 + (in ? dd : 0)) * 2, in, base + seq - 1, x, p.wait_ticks);
+                                double y = in ? get_f64(x[0][0], x[0][1]) : 0.0;
 #pragma nounroll
-                            for (int off = 1; off < 1 << lg; off <<= 1) { E += __shfl_xor(E, off); Q += __shfl_xor(Q, off); }
-                            if (w == 0 && pt < np) {
-                                u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + pt;
-                                put_f64(o, o + SA_PLANE, base + seq, E); put_f64(o + 2 * SA_PLANE, o + 3 * SA_PLANE, base + seq, Q);
+                                for (int off = 1 << lgw; off < 64; off <<= 1) y += __shfl_xor(y, off);
+                                if (lane < 1 << lgw) L.part[(wv << lgw) + lane] = y;
+                                if (!fine && lane == 0) L.dead = 1;
+                            }
+                            __syncthreads();
+                            if (L.dead) break;
+                            if (tid < mine) {
+                                double y = 0.0;
+#pragma nounroll
+                                for (int i = tid; i < ((((G << lgd) + 63) >> 6) << lgw); i += 1 << lgd) y += L.part[i];
+                                u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + 2 * tid;
+                                put_f64(o, o + 1, base + seq, y);
                             }
                         }
                         set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
-                        if (wv == 0 && fine) {          // (one wavefront waits for each workgroup's last sum)
-                            u64 y[1][1];
-                            fine = take<1, 1>(set, lane, 0, G, 3 * SA_PLANE + lane + (np - 1 - lane) / G * G, lane < np, base + seq, y, p.wait_ticks);
-                        }
-                        if (!fine && lane == 0) L.dead = 1;
-                        __syncthreads();
-                        if (L.dead) break;
-                        if (wv * 64 < np) {
-                            const int at = min(tid, SA_PLANE - 1);
-                            fine = take<1, 4, SA_PLANE>(set, at % G, 0, G, at, tid < np, base + seq, x, p.wait_ticks);
-                            if (tid < np) { L.sE[tid] = get_f64(x[0][0], x[0][1]); L.sQ[tid] = get_f64(x[0][2], x[0][3]); }
+                        if (wv * 64 < 2 * np) {
+                            const int k = min(tid >> 1, np - 1);
+                            fine = take<1, 2>(set, k >> lgp, 0, G, 4 * (k & ((1 << lgp) - 1)) + 2 * (tid & 1), tid < 2 * np, base + seq, x, p.wait_ticks);
+                            if (tid < 2 * np) (tid & 1 ? L.sQ : L.sE)[k] = get_f64(x[0][0], x[0][1]);
                         }
                         // (not L.dead: another wavefront may not have looked at that yet)
                         if (!fine && lane == 0) L.late = 1;

@@ -264,6 +264,32 @@ def test_stochastic_wide_fans(G, oracle, V, fan):
     assert checked >= 4
 
 
+@pytest.mark.parametrize("V,fan", [(4000, 12), (4096, 255), (6000, 255), (10000, 130), (2048 * 15, 255), (2048 * 31, 66), (2048 * 33, 33),
+                                   (2048 * 33, 34), (2048 * 63, 255), (2048 * 64, 20), (2048 * 64, 65)])
+def test_stochastic_fans_over_the_workgroups(G, oracle, V, fan):
+    """The sums at a fan's points are shared out among the workgroups in runs of a power of two: numbers of workgroups and of
+    children that leave some with a shorter run or with none, one part per wavefront of the adding and many."""
+    B = 2
+    checked = 0
+    for seed in range(5):
+        marg = synth.marginals(730 + seed, B, V, 0.7)
+        tree = oracle.tree_build(marg, fan)
+        z = np.log(np.maximum(marg[np.minimum(np.concatenate([[0], tree["depth"]]), B - 1)].astype(np.float64), 1e-30))
+        z += synth.normal(830 + seed, "noise", z.shape, [0.3, 1.0, 2.0][seed % 3])
+        store, xf = synth.round_to_dtype(z, "fp32")
+        u = synth.uniform(930 + seed, "u", (fan + 1,)).astype(np.float32)
+        if seed % 2 == 1:
+            u[:] = 0.999999
+        ref = oracle.accept_stochastic(xf, marg, tree["parent"], tree["token"], tree["depth"], u)
+        if _ambiguous(ref):
+            continue
+        got = G.run_accept_stochastic(store, False, marg, tree["parent"], tree["token"], u)
+        assert got["n_acc"] == ref["n_acc"] and np.array_equal(got["path"], ref["path"]), (V, fan, seed)
+        assert got["bonus"] == ref["bonus"], (V, fan, seed)
+        checked += 1
+    assert checked >= 2
+
+
 def test_stochastic_wide_fan_long_vocabulary(G, oracle):
     """A vocabulary of 300000: slices of 8192 tokens, eight per thread where a fan is sorted, and a ragged last one.  With
     probabilities this small most seeds fall under the ambiguity margins; those that do not must agree."""
