@@ -193,6 +193,11 @@ constexpr int SW_CAP = 4096;                // candidates of all levels together
 constexpr int SW_COARSE = 512;              // bins of a score during the sweep: 4 per binade of fp32 (what is above 2 shares the last)
 constexpr int SW_BINS = 2048;               // bins when the tree is put in order: 16 per binade
 constexpr int SW_KEEP = 512;                // candidates that reach the last threshold (N and what shares its bin)
+constexpr int SW_FANS = 12;                 // fans wider than four that one wavefront walks alone
+// Probability of the greedy chain's second node from which the sweep starts from the chain.  With / without, 16 positions x 30000 tokens: one
+// token of probability 0.9 x 0.93^k at position k: N = 64 1.8, N = 256 5.1 us less; 0.7: 0.9 and 2.1 less; 0.6 x 0.9^k (a second node of
+// 0.32): 0.6 and 1.3 less; 0.5: 0.1 less and 0.1 more; softmax of 3 N(0, 1): 0.5 and 0.8 more.
+constexpr float SW_CHAIN = 0.3f;
 constexpr int SW_THIN = 96;                 // nodes up to which a level is one wavefront's work
 struct alignas(16) SweepLds {
     // score bits << 32 | depth, parent and rank of a candidate (sweep_meta); a level's candidates lie in lexicographic
@@ -613,12 +618,12 @@ __device__ __forceinline__ void expand_wave(ExpandLds &S, int B, int K, int KP, 
 // after its parent and after its elder siblings, so the tree is the set of the N first prefixes of that order, and nothing
 // about it needs the frontier, nor any order before the end.  The levels are swept once with a threshold that only
 // rises: level d's candidates are the children of level d-1's candidates that score above it (a node deeper than N nodes that
-// score at least as much cannot be among the first N).  It begins at the N-th best of a set of prefixes that need no sweep
-// (sweep_bound), which as a rule leaves so few candidates, in thin levels, that one wavefront goes through them all with the threshold
-// as it is (sweep_thin): N = 256 of a confident drafter, 13 levels: 600 candidates instead of 1480 without it, the sweep 14.8 ->
-// 10.1 us.  Where they are many all the same, the rest is swept with a threshold that moves up, after a level, to the lower
-// edge of the bin that holds the N-th best candidate so far (a histogram of the scores' bits, 4 bins per binade, to which every
-// candidate is added once; a suffix sum finds the bin).  A child of rank r is not needed either where the product of
+// score at least as much cannot be among the first N).  Where the draft is confident (SW_CHAIN) it begins at the N-th best of a set of
+// prefixes that need no sweep (sweep_bound), which as a rule leaves so few candidates, in thin levels, that one wavefront goes through them all with the threshold as it is (sweep_thin): N = 256 of a
+// confident drafter, 13 levels: 600 candidates instead of 1480 without it, the sweep 14.8 -> 10.1 us.  Elsewhere, and where they are many all
+// the same, the levels are swept with a threshold that moves up, after a level, to the lower edge of the bin that holds the N-th best
+// candidate so far (a histogram of the scores' bits, 4 bins per binade, to which every candidate is added once; a suffix sum
+// finds the bin).  A child of rank r is not needed either where the product of
 // (rank + 1) along its path exceeds N: that many prefixes of its own level come before it (kept per node as the most
 // children it can have: floor(N / product) = floor(floor(N / parent's product) / (r + 1))).
 // Children take their places in their parents' order, so that a candidate's index grows with the depth and, within a level, with
@@ -798,7 +803,8 @@ __device__ __forceinline__ int sweep_bound(const ExpandLds &S, SweepLds &L, int 
 // Levels 1, 2, .. by one wavefront, with the threshold as it is.  What a level costs is one instruction after the other, some 7 cycles
 // each: the next level's probabilities are asked for a level ahead; a node that has children writes four, the last first, so that those that
 // it does not have are overwritten by the nodes behind it; the rest of a wide fan is tested and written with one probability per
-// lane; no histogram is kept.  Stops (d, a, b as in sweep_levels) at a level that is wide, or where the candidates become many.
+// lane; no histogram is kept.  Stops (d, a, b as in sweep_levels) at a level that is wide, or where the candidates become many, or the
+// wide fans (about 0.25 us each here, one after the other; a limit of 8 or of 16 is slower on peaked marginals of 1000 to 128256 tokens).
 __device__ __forceinline__ void sweep_thin(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int bound, int th, int &d, int &a, int &b)
 {
     const int K1 = min(K, N);
@@ -821,6 +827,7 @@ __device__ __forceinline__ void sweep_thin(const ExpandLds &S, SweepLds &L, int 
     };
     fetch(2, q);
     const uint32_t cand = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)L.cand;
+    int fans = 0;
     uint32_t level = 1u << 20;                                 // what sweep_meta adds for depth - 1
     while (d <= B && a < b && b - a <= 2 * SW_THIN && b <= SW_CAP / 4) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -841,6 +848,8 @@ __device__ __forceinline__ void sweep_thin(const ExpandLds &S, SweepLds &L, int 
             }
             c = min(c, most);
             const u64 wide = __builtin_amdgcn_ballot_w64(min(c, most - 1) >= 4);
+            fans += __builtin_popcountll(wide);
+            if (fans > SW_FANS) return;
             for (u64 left = wide; left != 0ull; left &= left - 1ull) {
                 const int src = __builtin_ctzll(left), wm = __builtin_amdgcn_readlane(most, src);
                 const float wr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rp), src));
@@ -891,22 +900,28 @@ __device__ __forceinline__ void sweep_thin(const ExpandLds &S, SweepLds &L, int 
 __device__ __forceinline__ int sweep_levels(const ExpandLds &S, SweepLds &L, int B, int K, int KP, int N, int lane, int w, int floor)
 {
     const int tid = w * 64 + lane;
-    int d, a, b, buf = 0;                                      // a .. b - 1: the candidates of the level before
-    const int bound = sweep_bound(S, L, B, K, KP, N, lane, w);
-    int th = max(floor, bound);
-    if (w == 0) {
-        sweep_thin(S, L, B, K, KP, N, lane, bound, th, d, a, b);
-        if (lane == 0) { L.d = d; L.a = a; L.b = b; }
+    const bool chain = B > 1 && __builtin_amdgcn_ballot_w64(__fmul_rn(S.q[0], S.q[KP]) >= SW_CHAIN) != 0ull;
+    int d = 2, a = 0, b = min(K, N), th = floor, buf = 0;      // a .. b - 1: the candidates of the level before
+    if (chain) {
+        const int bound = sweep_bound(S, L, B, K, KP, N, lane, w);
+        th = max(floor, bound);
+        if (w == 0) {
+            sweep_thin(S, L, B, K, KP, N, lane, bound, th, d, a, b);
+            if (lane == 0) { L.d = d; L.a = a; L.b = b; }
+        }
+        __syncthreads();
+        d = __builtin_amdgcn_readfirstlane(L.d); a = __builtin_amdgcn_readfirstlane(L.a); b = __builtin_amdgcn_readfirstlane(L.b);
+        if (b > SW_CAP) return -1;
+        if (d > B || a == b) return b;
+        __syncthreads();
     }
-    __syncthreads();
-    d = __builtin_amdgcn_readfirstlane(L.d); a = __builtin_amdgcn_readfirstlane(L.a); b = __builtin_amdgcn_readfirstlane(L.b);
-    if (b > SW_CAP) return -1;
-    if (d > B || a == b) return b;
     // ---- wide levels, or many candidates: with a threshold that rises ------------------------------------------------------
-    __syncthreads();
     if (tid < SW_COARSE / 4) reinterpret_cast<int4 *>(L.coarse)[tid] = make_int4(0, 0, 0, 0);
     __syncthreads();
-    for (int c = tid; c < b; c += 256) atomicAdd(&L.coarse[sweep_coarse(L.cand[c].y)], 1);
+    if (chain)
+        for (int c = tid; c < b; c += 256) atomicAdd(&L.coarse[sweep_coarse(L.cand[c].y)], 1);
+    else if (tid < b)                                          // level 1: the best tokens of position 0, already in order
+        sweep_put(L, tid, __float_as_uint(__fmul_rn(1.0f, S.q[tid])), sweep_meta(SW_ROOT, (uint32_t)tid, 0, sweep_share(N, tid)));
     __syncthreads();
     floor = th;
     bool raised = false;
@@ -978,7 +993,7 @@ __device__ __forceinline__ bool expand_sweep(ExpandLds &S, SweepLds &L, int B, i
     int np = min(K, N), rank = tid, dep = 1;
     float r;
     uint32_t par = SW_ROOT;
-    if (star) {
+    if (__builtin_expect(star, 1)) {                           // (0.1 us of 7: what follows is 50 KB of code)
         r = tid < np ? __fmul_rn(1.0f, S.q[tid]) : 0.f;
     } else {
 #pragma unroll
@@ -1406,8 +1421,9 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         beam_block(S, BM, B, K, KP, beam_width, tid, parent, token, depth, rho, n_out, ahat);
         return;
     }
-    // Which expansion: the sweep pays per level (about 0.4 us, 1.4 us for its threshold and 2 us at the end), the one-wavefront loop per
-    // node (0.24 us up to 64 nodes, 0.5 us at 256), so the loop is left with the smallest trees that may be deep.  The tree cannot be deeper
+    // Which expansion: the sweep pays per level (0.4 us and 1.4 us for its threshold where it starts from the chain, 0.9 us elsewhere, and 2 us at
+    // the end), the one-wavefront loop per node (0.24 us up to 64 nodes, 0.5 us at 256), so the loop is left with the smallest
+    // trees that may be deep.  The tree cannot be deeper
     // than the greedy chain stays above the N-th best token of the first position (every node scores at least as much as
     // the tree's last one, which scores at least that).
     // 16 positions x 128256 tokens, HIP-graph replays, sweep / loop: a confident drafter (depth 8 .. 13) N = 16: 17.7 / 15.0 us, N = 32: 19.9 /
@@ -1448,7 +1464,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
             if (lane == 0) { L_floor[0] = floor_of(a0); L_floor[1] = floor_of(a1); }
         }
         if (lane == 0)
-            use_levels = algo == 0 && star ? 2 : algo == 2 || (algo == 0 && (N > 64 || 1.8f + 0.4f * (float)min(reach, N) < 0.19f * (float)N)) ? 1 : 0;
+            use_levels = algo == 0 && star ? 2 : algo == 2 || (algo == 0 && (N > 64 || 0.7f + 0.5f * (float)min(reach, N) < 0.22f * (float)N)) ? 1 : 0;
     }
     __syncthreads();
     if (use_levels) {

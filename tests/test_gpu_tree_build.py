@@ -127,3 +127,18 @@ def test_wide_fans_along_the_chain(G, oracle, N):
     first = one.copy(); first[0] = 0.002 * 0.998 ** np.arange(V)             # a wide first level, confident from there on
     for marg in (one, two, tied, halves, first):
         _check(G, oracle, marg.astype(np.float32), N)
+
+
+@pytest.mark.parametrize("N", [5, 64, 97, 256])
+def test_sweep_from_a_confident_chain(G, oracle, N):
+    """The same on either side of the confidence from which the sweep starts from the chain, and with more wide fans than one
+    wavefront goes through."""
+    B, V = 16, 400
+    flat = np.tile(1e-3 * 0.9995 ** np.arange(V), (B, 1))
+    two = flat.copy(); two[:, 17] = 0.55; two[:, 18] = 0.4399                 # 2^depth chains, each node with a wide fan
+    tied = np.full((B, V), 2.0 ** -9); tied[:, 3] = 0.75                      # all siblings tie, on an edge
+    halves = np.tile(2.0 ** -np.arange(10.0), (B, 1))                         # every score a power of two, the chain's all one
+    below, above = flat.copy(), flat.copy()
+    below[:, 5] = 0.547; above[:, 5] = 0.548                                  # a second node of probability a little less, and more, than 0.3
+    for marg in (two, tied, halves, below, above):
+        _check(G, oracle, marg.astype(np.float32), N)
