@@ -39,7 +39,7 @@
 // For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
 //
 // What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
-// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 45 us against
+// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 44 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
 // levels, bf16: 860 .. 1280 -> 35 .. 44 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
 // tokens instead of 2048 (half the workgroups): 54 and 47 us at the same two.
@@ -210,29 +210,37 @@ __device__ __forceinline__ double get_f64(u64 lo, u64 hi)
 {
     return __longlong_as_double((long long)(((hi & 0xFFFFFFFFull) << 32) | (lo & 0xFFFFFFFFull)));
 }
-// N words of each of R workgroups' parts, R * N loads in flight, once they all carry the tag: workgroup first + k * step,
-// k < R, from offset `at` of its part on; workgroups from G on (and lanes with want = false) are left out.  False: the limit
-// has passed.  A wavefront sleeps between two looks, and where many words are exchanged only one wavefront of a
-// workgroup looks (at one word of each part) until everybody is there: sixteen wavefronts of every workgroup asking for the same
-// lines without a pause kept the stores to those lines from ever getting through.
-template <int R, int N>
-__device__ __forceinline__ bool take(const u64 *set, int first, int step, int G, int at, bool want, uint32_t tag, u64 (&w)[R][N],
-                                     long long wait_ticks)
+// Two words of each of R workgroups' parts, R loads in flight, once they all carry the tag: workgroup first + k * step,
+// k < R, from offset `at` (even) of its part on; workgroups from G on (and lanes with want = false) are left out.  False: the limit
+// has passed.  What this costs is the number of requests, whatever their size: both words come with one load (each has its own tag, so
+// nothing depends on their coming together), and lanes that want neighbouring words share a request (a chain's exchange, five words
+// of each of 32 workgroups by four wavefronts: 3.1 -> 2.4 us against a load per word with one lane per workgroup; the words of all
+// workgroups side by side instead, which reads still fewer lines, has them all write to the same ones: 2.7 us for one double
+// instead of 1.7).  A wavefront sleeps between two looks.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <int R>
+__device__ __forceinline__ bool take(const u64 *set, int first, int step, int G, int at, bool want, uint32_t tag, ulong2 (&w)[R], long long wait_ticks)
 {
     const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
     for (;;) {
+        u32x4 x[R];
+        const u64 *p[R];
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const u64 *p = set + (size_t)(first + k * step) * SA_WORDS + at;
-            const bool in = want && first + k * step < G;
-#pragma unroll
-            for (int i = 0; i < N; ++i) w[k][i] = in ? __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)tag << 32;
-        }
+        for (int k = 0; k < R; ++k) p[k] = set + (want && first + k * step < G ? (size_t)(first + k * step) * SA_WORDS + at : 0);
+        static_assert(R == 1 || R == 4, "what is written out here");
+        if constexpr (R == 1)
+            asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(x[0]) : "v"(p[0]) : "memory");
+        else
+            asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                         "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                         : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]) : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]) : "memory");
         bool ok = true;
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-#pragma unroll
-            for (int i = 0; i < N; ++i) ok = ok && (uint32_t)(w[k][i] >> 32) == tag;
+        for (int k = 0; k < R; ++k) {
+            const bool in = want && first + k * step < G;
+            ok = ok && (!in || (x[k][1] == tag && x[k][3] == tag));
+            w[k] = make_ulong2(((u64)x[k][1] << 32) | x[k][0], ((u64)x[k][3] << 32) | x[k][2]);
+        }
         if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return true;
         if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > wait_ticks) return false;
         __builtin_amdgcn_s_sleep(2);
@@ -404,14 +412,27 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             float mw = lane == 0 ? m_row : -INFINITY;
             double zw = lane == 0 ? z : 0.0, tw = lane == 0 ? tq : 0.0;
             if (G > 1) {
-                u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS, *mine = set + (size_t)me * SA_WORDS + 8 * r;
+                u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                 const uint32_t tag = base + seq;
-                if (lane == 0) { put_u32(mine, tag, __float_as_uint(m_row)); put_f64(mine + 1, mine + 2, tag, z); put_f64(mine + 3, mine + 4, tag, tq); }
-                u64 w[1][5];
-                if (!take<1, 5>(set, lane, 0, G, 8 * r, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
-                mw = lane < G ? __uint_as_float((uint32_t)w[0][0]) : -INFINITY;
-                zw = lane < G ? get_f64(w[0][1], w[0][2]) : 0.0;
-                tw = lane < G ? get_f64(w[0][3], w[0][4]) : 0.0;
+                if (lane < 6) {                         // z, the draft mass, the maximum (twice, for whole pairs of words)
+                    const u64 b = (u64)__double_as_longlong(lane < 2 ? z : tq);
+                    put_u32(set + (size_t)me * SA_WORDS + 8 * r + lane, tag, lane >= 4 ? __float_as_uint(m_row) : (uint32_t)(lane & 1 ? b >> 32 : b));
+                }
+                // four lanes read a part's row, which lies in one line, and hand it to the lane that has the part
+                ulong2 w[4];
+                if (!take<4>(set, lane >> 2, 16, G, 8 * r + 2 * (lane & 3), (lane & 3) < 3, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                uint32_t *x = reinterpret_cast<uint32_t *>(L.sorted) + r * (SA_MAX_WGS * 9);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uint32_t *o = x + ((lane >> 2) + 16 * k) * 9 + 2 * (lane & 3);
+                    o[0] = (uint32_t)w[k].x;
+                    o[1] = (uint32_t)w[k].y;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                x += lane * 9;
+                mw = lane < G ? __uint_as_float(x[4]) : -INFINITY;
+                zw = lane < G ? get_f64(x[0], x[1]) : 0.0;
+                tw = lane < G ? get_f64(x[2], x[3]) : 0.0;
             }
             const float m = wave_max(mw);
             const double F = mw == -INFINITY ? 0.0 : exp((double)mw - (double)m);
@@ -588,7 +609,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         // another part; the same words written 256 bytes apart instead: 17 us).
                         const int lgp = G >= np ? 0 : 32 - __builtin_clz((np - 1) / G), lgd = lgp + 1, lgw = min(lgd, 6);
                         const u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
-                        u64 x[1][2];
+                        ulong2 x[1];
                         bool fine = true;
                         const int mine = min(np - (me << lgp), 1 << lgp) * 2;      // doubles that this workgroup adds up
                         ++seq;
@@ -596,8 +617,8 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                             const int w = tid >> lgd, dd = tid & ((1 << lgd) - 1);
                             if ((wv * 64 >> lgd) < G) {
                                 const bool in = w < G && dd < mine;
-                                fine = take<1, 2>(set, w, 0, G, ((me << lgp) * 2 + (in ? dd : 0)) * 2, in, base + seq - 1, x, p.wait_ticks);
-                                double y = in ? get_f64(x[0][0], x[0][1]) : 0.0;
+                                fine = take<1>(set, w, 0, G, ((me << lgp) * 2 + dd) * 2, in, base + seq - 1, x, p.wait_ticks);
+                                double y = in ? get_f64(x[0].x, x[0].y) : 0.0;
 #pragma nounroll
                                 for (int off = 1 << lgw; off < 64; off <<= 1) y += __shfl_xor(y, off);
                                 if (lane < 1 << lgw) L.part[(wv << lgw) + lane] = y;
@@ -616,8 +637,8 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                         if (wv * 64 < 2 * np) {
                             const int k = min(tid >> 1, np - 1);
-                            fine = take<1, 2>(set, k >> lgp, 0, G, 4 * (k & ((1 << lgp) - 1)) + 2 * (tid & 1), tid < 2 * np, base + seq, x, p.wait_ticks);
-                            if (tid < 2 * np) (tid & 1 ? L.sQ : L.sE)[k] = get_f64(x[0][0], x[0][1]);
+                            fine = take<1>(set, k >> lgp, 0, G, 4 * (k & ((1 << lgp) - 1)) + 2 * (tid & 1), tid < 2 * np, base + seq, x, p.wait_ticks);
+                            if (tid < 2 * np) (tid & 1 ? L.sQ : L.sE)[k] = get_f64(x[0].x, x[0].y);
                         }
                         // (not L.dead: another wavefront may not have looked at that yet)
                         if (!fine && lane == 0) L.late = 1;
@@ -764,10 +785,11 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 if (G > 1) {
                     u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                     const uint32_t tag = base + seq;
-                    if (lane == 0) put_f64(set + (size_t)me * SA_WORDS, set + (size_t)me * SA_WORDS + 1, tag, a);
-                    u64 w[1][2];
-                    if (!take<1, 2>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
-                    gw = lane < G ? get_f64(w[0][0], w[0][1]) : 0.0;
+                    const u64 b = (u64)__double_as_longlong(a);
+                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)(lane ? b >> 32 : b));
+                    ulong2 w[1];
+                    if (!take<1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                    gw = lane < G ? get_f64(w[0].x, w[0].y) : 0.0;
                 }
                 L.GW[galt][lane] = gw;
                 gw = wave_sum(gw);
@@ -847,10 +869,10 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 if (G > 1) {
                     u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                     const uint32_t tag = base + seq;
-                    if (lane == 0) put_u32(set + (size_t)me * SA_WORDS, tag, (uint32_t)L.last);
-                    u64 w[1][1];
-                    if (!take<1, 1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
-                    last = lane < G ? (int)(uint32_t)w[0][0] : -1;
+                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)L.last);
+                    ulong2 w[1];
+                    if (!take<1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
+                    last = lane < G ? (int)(uint32_t)w[0].x : -1;
                 }
                 for (int off = 32; off >= 1; off >>= 1) last = max(last, __shfl_xor(last, off));
                 if (me == 0 && lane == 0) *p.bonus = max(last, 0);
