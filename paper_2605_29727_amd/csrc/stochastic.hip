@@ -39,7 +39,7 @@
 // For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
 //
 // What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
-// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 44 us against
+// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 40 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
 // levels, bf16: 860 .. 1280 -> 35 .. 44 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
 // tokens instead of 2048 (half the workgroups): 54 and 47 us at the same two.
@@ -117,25 +117,67 @@ __device__ __forceinline__ float wave_max(float x)
     x = dpp_max<0x143, 0xC>(x);
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
-// Inclusive prefix sum over the lanes.
-__device__ __forceinline__ double wave_scan(double x, int lane)
+// Inclusive prefix sums over the lanes: of a row of 16 lanes by its shifts, then the rows before.
+__device__ __forceinline__ double wave_scan(double x)
 {
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(x, off);
-        if (lane >= off) x += o;
-    }
-    return x;
+    x = dpp_add<0x111, 0xF>(x);     // row_shr:1, 2, 4, 8
+    x = dpp_add<0x112, 0xF>(x);
+    x = dpp_add<0x114, 0xF>(x);
+    x = dpp_add<0x118, 0xF>(x);
+    x = dpp_add<0x142, 0xA>(x);     // row_bcast15 into rows 1 and 3
+    return dpp_add<0x143, 0xC>(x);  // row_bcast31 into rows 2 and 3
 }
-// Composition of the affine maps of lanes 0 .. lane - 1 (lane 0 first): x -> A x + B.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_add(int x) { return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xF, true); }
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x = dpp_add<0x111, 0xF>(x); x = dpp_add<0x112, 0xF>(x); x = dpp_add<0x114, 0xF>(x); x = dpp_add<0x118, 0xF>(x);
+    x = dpp_add<0x142, 0xA>(x);
+    return dpp_add<0x143, 0xC>(x);
+}
+// x of another lane of the row, or of a row before; `none` where there is no such lane.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_of(float x, float none)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(none), (int)__float_as_uint(x), CTRL, ROW_MASK, 0xF, false));
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_of(double x, double none)
+{
+    const u64 b = (u64)__double_as_longlong(x), n = (u64)__double_as_longlong(none);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)n, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(n >> 32), (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
+// Composition of the affine maps of lanes 0 .. lane - 1 (lane 0 first): x -> A x + B.  (By moves between the lanes: through
+// LDS, six round trips one after the other, the table's solution took 3.1 us instead of 2.6, a Newton step 1.4 instead of 1.2.)
 template <typename F>
 __device__ __forceinline__ void wave_affine_before(F a, F b, int lane, F &A, F &B)
 {
-    for (int off = 1; off < 64; off <<= 1) {
-        const F ao = __shfl_up(a, off), bo = __shfl_up(b, off);
-        if (lane >= off) { b = a * bo + b; a = a * ao; }
-    }
+#define BTV_STEP(CTRL, ROWS) { const F ao = dpp_of<CTRL, ROWS>(a, (F)1), bo = dpp_of<CTRL, ROWS>(b, (F)0); b = a * bo + b; a = a * ao; }
+    BTV_STEP(0x111, 0xF) BTV_STEP(0x112, 0xF) BTV_STEP(0x114, 0xF) BTV_STEP(0x118, 0xF) BTV_STEP(0x142, 0xA) BTV_STEP(0x143, 0xC)
+#undef BTV_STEP
     A = __shfl_up(a, 1); B = __shfl_up(b, 1);
     if (lane == 0) { A = (F)1; B = (F)0; }
+}
+// Sum over the 2^lg (up to 16) neighbouring lanes of a group.
+__device__ __forceinline__ double group_sum(double x, int lg)
+{
+    x = dpp_add<0xB1, 0xF>(x);
+    x = dpp_add<0x4E, 0xF>(x);
+    if (lg > 2) x = dpp_add<0x141, 0xF>(x);
+    if (lg > 3) x = dpp_add<0x140, 0xF>(x);
+    return x;
+}
+// Sum of the first n (uniform) of one value per wavefront, in their order; all are read at once (one after the other they made the
+// sort of a fan 5.3 us, with the scans through LDS; 3.9 now).
+template <typename F>
+__device__ __forceinline__ F sum_before(const F *x, int n)
+{
+    F t = (F)0;
+#pragma unroll
+    for (int i = 0; i < SA_WAVES; ++i) t += i < n ? x[i] : (F)0;
+    return t;
 }
 
 template <bool BF16>
@@ -504,7 +546,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         double own[4], sum = 0.0, ht = 0.0;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) { const int k = 4 * lane + i; own[i] = k < K ? L.kid_q[kj + k] : 0.0; sum += own[i]; }
-                        double t = T - (wave_scan(sum, lane) - sum);
+                        double t = T - (wave_scan(sum) - sum);
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int k = 4 * lane + i;
@@ -526,17 +568,10 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                     {   // exclusive scan of the bin counts (one bin per thread)
                         static_assert(SA_BINS == SA_T, "one bin per thread");
                         const int c0 = L.bin_at[tid];
-                        int ci = c0;
-#pragma unroll
-                        for (int off = 1; off < 64; off <<= 1) {
-                            const int co = __shfl_up(ci, off);
-                            if (lane >= off) ci += co;
-                        }
+                        const int ci = wave_scan(c0);
                         if (lane == 63) L.wsum[wv] = ci;
                         __syncthreads();
-                        int cb = 0;
-#pragma nounroll
-                        for (int w = 0; w < wv; ++w) cb += L.wsum[w];
+                        const int cb = sum_before(L.wsum, wv);
                         L.bin_at[tid] = cb + ci - c0;
                         if (tid == SA_T - 1) L.bin_at[SA_BINS] = cb + ci;
                     }
@@ -551,12 +586,10 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
 #pragma unroll
                         for (int i = 0; i < BT; ++i)
                             if (BT * tid + i < cnt) { const float2 x = L.sorted[BT * tid + i]; ce += (double)x.x; cq += (double)x.y; }
-                        const double ie = wave_scan(ce, lane), iq = wave_scan(cq, lane);
+                        const double ie = wave_scan(ce), iq = wave_scan(cq);
                         if (lane == 63) { L.wz[wv] = ie; L.wq[wv] = iq; }
                         __syncthreads();
-                        double se = 0.0, sq = 0.0;
-#pragma nounroll
-                        for (int w = 0; w < wv; ++w) { se += L.wz[w]; sq += L.wq[w]; }
+                        const double se = sum_before(L.wz, wv), sq = sum_before(L.wq, wv);
                         L.cE[tid] = se + (ie - ce); L.cQ[tid] = sq + (iq - cq);
                         if (tid == SA_T - 1) { L.cE[SA_T] = se + ie; L.cQ[SA_T] = sq + iq; }
                     }
@@ -586,8 +619,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                             }
                             if (sub == 0) { E += L.cE[p0]; Q += L.cQ[p0]; }
                         }
-#pragma nounroll
-                        for (int off = 1; off < LP; off <<= 1) { E += __shfl_xor(E, off); Q += __shfl_xor(Q, off); }
+                        E = group_sum(E, 10 - lkp); Q = group_sum(Q, 10 - lkp);
                         E *= f;
                         ++seq;
                         if (G > 1) {
@@ -811,7 +843,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         }
         // ---- bonus: smallest v with cumsum(p)[v] > u ---------------------------------------------------------------
         const double target = (double)L.uni[min(ui, M)] * Gs;
-        const double gw = L.GW[gbuf][lane], incl = wave_scan(gw, lane);
+        const double gw = L.GW[gbuf][lane], incl = wave_scan(gw);
         const u64 over = __builtin_amdgcn_ballot_w64(incl > target && gw > 0.0);
         const int owner = over != 0ull ? __builtin_ctzll(over) : -1;
         if (owner == me || owner < 0) {
@@ -840,7 +872,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         if (v < ve) x[0] = mass(e_at(v), row_q ? q0[v] : 0.f);
                     }
                 }
-                const double own = (x[0] + x[1]) + (x[2] + x[3]), iw = wave_scan(own, lane);
+                const double own = (x[0] + x[1]) + (x[2] + x[3]), iw = wave_scan(own);
                 if (here && lane == 63) L.wz[wv & 3] = iw;
                 __syncthreads();
                 if (here) {
