@@ -304,7 +304,7 @@ struct SaShared {
     double z[SA_CHAIN], tq[SA_CHAIN], g, s_hi;
     float Mx[SA_CHAIN][SA_MAX_WGS];                     // the slices' maxima, exp(slice maximum - maximum), parts of G
     double F[SA_CHAIN][SA_MAX_WGS], GW[SA_CHAIN + 1][SA_MAX_WGS];
-    int acc0[SA_CHAIN];
+    alignas(16) int acc0[SA_CHAIN];
     int wsum[SA_WAVES];
     int dead, status, acc, pick, last, late;
     float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
@@ -394,12 +394,23 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             load_tokens<false, TG>(q0, tv, TS, row_q ? vr : v0, vec, 0.f, q);
         };
         load_row();
+        // this lane's node, if it is a child of a chain row's: what it needs of the rows is asked for behind them
         u64 bal[SA_CHAIN];
+        float kid_q = 0.f, kid_x = -INFINITY;
+        int kid_tok = -1;
         if (wv < KW) {
+            int at = -1, above = cur;
 #pragma unroll
             for (int r = 0; r < SA_CHAIN; ++r) {
-                bal[r] = __builtin_amdgcn_ballot_w64(r < nch && d + r < p.B && L.par[tid & (BTV_MAX_NODES - 1)] == node[r]);
+                const bool child = r < nch && d + r < p.B && L.par[tid & (BTV_MAX_NODES - 1)] == node[r];
+                bal[r] = __builtin_amdgcn_ballot_w64(child);
+                if (child) { at = d + r; above = node[r]; }
                 if (lane == 0) L.kcnt[r][wv] = __builtin_popcountll(bal[r]);
+            }
+            kid_tok = L.tok[tid & (BTV_MAX_NODES - 1)];
+            if (at >= 0 && kid_tok >= 0 && kid_tok < V) {
+                kid_q = p.marg[(size_t)at * V + kid_tok];
+                kid_x = load_logit<BF16>(p.logits, (size_t)(above + 1) * V + kid_tok);
             }
         }
         float mx = e[0];
@@ -418,12 +429,11 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             static_assert(KW == 4, "four counts");
             if (wv < KW && ((bal[r] >> lane) & 1)) {
                 const int j = koff[r] + (wv > 0 ? c.x : 0) + (wv > 1 ? c.y : 0) + (wv > 2 ? c.z : 0) + __builtin_popcountll(bal[r] & ((1ull << lane) - 1ull));
-                const int tk = L.tok[tid];
-                const bool ok = tk >= 0 && tk < V;      // not a vocabulary id: rejected, its uniform spent, nothing indexed
+                const bool ok = kid_tok >= 0 && kid_tok < V;      // not a vocabulary id: rejected, its uniform spent, nothing indexed
                 L.kid_node[j] = ok ? tid : -1 - tid;
-                L.kid_tok[j] = ok ? tk : 0;
-                L.kid_q[j] = ok ? (double)p.marg[(size_t)(d + r) * V + tk] : 0.0;
-                L.kid_x[j] = ok ? load_logit<BF16>(p.logits, (size_t)(node[r] + 1) * V + tk) : -INFINITY;
+                L.kid_tok[j] = ok ? kid_tok : 0;
+                L.kid_q[j] = (double)kid_q;
+                L.kid_x[j] = kid_x;
             }
             koff[r + 1] = __builtin_amdgcn_readfirstlane(koff[r] + c.x + c.y + c.z + c.w);
         }
@@ -499,10 +509,17 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         if (L.dead) { dead = true; break; }
         // ---- first children, as far as they are accepted -------------------------------------------------------------
         int r = 0;
-        while (r < nch && n < M && __builtin_amdgcn_readfirstlane(L.acc0[r]) != 0) {
-            cur = __builtin_amdgcn_readfirstlane(L.first[cur + 1]);
-            if (me == 0 && tid == 0) p.path[n] = cur;
-            ++n; ++d; ++ui; ++r;
+        {
+            const int4 a = *reinterpret_cast<const int4 *>(L.acc0);
+            const int acc0[SA_CHAIN] = { a.x, a.y, a.z, a.w };
+            const int next = __builtin_amdgcn_readfirstlane(L.first[(nch > 3 ? node[3] : nch > 2 ? node[2] : nch > 1 ? node[1] : node[0]) + 1]);
+#pragma unroll
+            for (int k = 0; k < SA_CHAIN; ++k) {
+                if (r != k || k >= nch || n >= M || __builtin_amdgcn_readfirstlane(acc0[k]) == 0) break;
+                cur = k + 1 < SA_CHAIN && k + 1 < nch ? node[(k + 1) % SA_CHAIN] : next;
+                if (me == 0 && tid == 0) p.path[n] = cur;
+                ++n; ++d; ++ui; ++r;
+            }
         }
         if (r == nch) continue;
         // ---- row r: its first child is rejected, or it has none ---------------------------------------------------------
