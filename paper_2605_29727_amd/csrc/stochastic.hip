@@ -256,7 +256,7 @@ __device__ __forceinline__ double get_f64(u64 lo, u64 hi)
 // k < R, from offset `at` (even) of its part on; workgroups from G on (and lanes with want = false) are left out.  False: the limit
 // has passed.  What this costs is the number of requests, whatever their size: both words come with one load (each has its own tag, so
 // nothing depends on their coming together), and lanes that want neighbouring words share a request (a chain's exchange, five words
-// of each of 32 workgroups by four wavefronts: 3.1 -> 2.4 us against a load per word with one lane per workgroup; the words of all
+// of each of 63 workgroups by four wavefronts: 3.1 -> 2.4 us against a load per word with one lane per workgroup; the words of all
 // workgroups side by side instead, which reads still fewer lines, has them all write to the same ones: 2.7 us for one double
 // instead of 1.7).  A wavefront sleeps between two looks.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -653,7 +653,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         // reads the sums (with everybody reading every part instead, 4 MB for 32 workgroups, a pass took 3 us
                         // longer).  What an exchange of this size costs is the number of its requests, loads and stores alike: a
                         // thread has one double of one part and neighbouring threads neighbouring doubles, so that 16 lanes share
-                        // a request where they read 8 points of a part (256 points, 32 workgroups: 9.3 -> 4.0 us both exchanges, 128
+                        // a request where they read 8 points of a part (256 points, 63 workgroups: 9.3 -> 4.0 us both exchanges, 128
                         // points 4.1 .. 5.8 -> 2.6 .. 3.2, against a lane that read all four words of its point, every lane in
                         // another part; the same words written 256 bytes apart instead: 17 us).
                         const int lgp = G >= np ? 0 : 32 - __builtin_clz((np - 1) / G), lgd = lgp + 1, lgw = min(lgd, 6);
