@@ -1608,8 +1608,9 @@ __device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, 
     if (tid == 0) __hip_atomic_store(&m.epoch, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One request: a workgroup per (key split, KV head, row block).
-template <int D, int RW, int KW, int NT, int EB>
+// One request: a workgroup per (key split, KV head, row block).  MERGE: the workgroups merge the splits (a kernel of its own: with
+// both in one, those that do not merge took 0.2 us longer).
+template <int D, int RW, int KW, int NT, int EB, bool MERGE>
 __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -1619,7 +1620,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     // (p.units counts the (split, head) pairs, or the heads, or the groups that are dealt out to the XCDs).
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     Piece pc = {};
-    if (!p.sync) {
+    if constexpr (!MERGE) {
         const int unit = (slot / p.row_blocks) * 8 + xcd;
         if (unit >= p.units) return;
         pc.by = slot % p.row_blocks; pc.g = unit / p.nsplit; pc.bx = unit % p.nsplit;
@@ -1638,18 +1639,21 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     pc.st0 = pc.bx * p.sps;
     pc.st1 = min(pc.st0 + p.sps, tiles);
     pc.direct = nsplit_r == 1;
-    pc.grouped = p.sync != nullptr;
+    pc.grouped = MERGE;
     pc.group = pc.g * p.row_blocks + pc.by;
     pc.pitch = min(RW * 32, rq.M * p.G) + 1;            // (rows of the same number lie in different channels)
-    MergeWords *m = reinterpret_cast<MergeWords *>(p.sync) + pc.group;
-    u64 tag = 0;
-    if (p.sync)      // (a scalar load: nothing writes it before every workgroup of the group has read it)
-        tag = *reinterpret_cast<const __attribute__((address_space(4))) u64 *>(reinterpret_cast<uintptr_t>(&m->epoch)) + 1;
-    attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc, [&] {
-        if (p.sync && threadIdx.x == 0)
-            __hip_atomic_store(&m->started[pc.bx], tag << 8 | this_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    });
-    if (p.sync) merge_group<D, RW * KW, RW * 32>(p, *m, smem, threadIdx.x, pc, nsplit_r, tag);
+    if constexpr (MERGE) {
+        MergeWords *m = reinterpret_cast<MergeWords *>(p.sync) + pc.group;
+        // (a scalar load: nothing writes it before every workgroup of the group has read it)
+        const u64 tag = *reinterpret_cast<const __attribute__((address_space(4))) u64 *>(reinterpret_cast<uintptr_t>(&m->epoch)) + 1;
+        attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc, [&] {
+            if (threadIdx.x == 0)
+                __hip_atomic_store(&m->started[pc.bx], tag << 8 | this_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+        merge_group<D, RW * KW, RW * 32>(p, *m, smem, threadIdx.x, pc, nsplit_r, tag);
+    } else {
+        attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc, [] {});
+    }
 }
 
 // A batch of short requests: a workgroup per (part of at most sps tiles, KV head, request, row block) of the largest request;
@@ -2195,14 +2199,17 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
     if (i < words) p[i] = 0u;
 }
 
-struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; };
+struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; float bytes; };      // (bytes of K and V)
 
 // Whether the workgroups of a plan merge their partials themselves (merge_group): few enough splits and groups for its words; all
-// groups' workgroups congruent mod 8, and as many on each XCD; and the chip takes all at once.
+// groups' workgroups congruent mod 8, and as many on each XCD; and the chip takes all at once.  Where the KV heads do not share out
+// evenly over the XCDs the groups do, and a head's row blocks, on up to 8 XCDs, each read its K/V: 2 .. 4 % faster than the two
+// launches for up to 64 MB of such reading (330 plans of 1 to 6 KV heads), 1 .. 3 % slower on average above, 25 % at 140 .. 200 MB.
 bool merges_inside(const Plan &pl, int Hkv)
 {
     const int groups = Hkv * pl.row_blocks;
-    return pl.nsplit > 1 && pl.nsplit <= MERGE_SPLITS && groups <= MERGE_GROUPS && (Hkv % 8 == 0 || groups % 8 == 0) &&
+    return pl.nsplit > 1 && pl.nsplit <= MERGE_SPLITS && groups <= MERGE_GROUPS &&
+           (Hkv % 8 == 0 || (groups % 8 == 0 && pl.bytes * (float)(std::min(8, pl.row_blocks) - 1) <= 64e6f)) &&
            pl.nsplit * groups <= (pl.rw == 2 ? 512 : 256);
 }
 
@@ -2253,7 +2260,7 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
         if (force_shape ? force_shape != k + 1 && !(eb == 1 && force_shape == 3 && k == 1) : eb == 1 && k == 2) continue;
         Plan pl;
         pl.rw = SHAPES[k].rw; pl.kw = SHAPES[k].kw; pl.nt = SHAPES[k].nt;
-        pl.wr = pl.rw * 32;
+        pl.wr = pl.rw * 32; pl.bytes = bytes;
         pl.row_blocks = (rows_g + pl.wr - 1) / pl.wr;
         pl.stages = (L + M + TK - 1) / TK;
         auto consider = [&](int want) {
@@ -2337,17 +2344,17 @@ WsLayout ws_layout(size_t rows, int D, int nsplit, int batch = 0)
     return w;
 }
 
-enum Form { ONE_REQUEST, SHORT_BATCH, LONG_BATCH };
+enum Form { ONE_REQUEST, ONE_MERGED, SHORT_BATCH, LONG_BATCH };
 
 template <int D, int RW, int KW, int NT, Form FORM, int EB = 2>
 int launch_bf16(const AttnParams &p, dim3 grid, hipStream_t st)
 {
-    constexpr int LDS_BYTES = PageLds<D, RW, KW, NT, FORM != ONE_REQUEST, EB>::BYTES;
+    constexpr int LDS_BYTES = PageLds<D, RW, KW, NT, (FORM > ONE_MERGED), EB>::BYTES;
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
     void (*kern)(AttnParams);
     if constexpr (FORM == LONG_BATCH) kern = tv_attn_batch<D, RW, KW, NT, EB>;
     else if constexpr (FORM == SHORT_BATCH) kern = tv_attn_short<D, RW, KW, NT, EB>;
-    else kern = tv_attn_bf16<D, RW, KW, NT, EB>;
+    else kern = tv_attn_bf16<D, RW, KW, NT, EB, FORM == ONE_MERGED>;
     if (!configured.load(std::memory_order_acquire)) {
         BTV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     LDS_BYTES));
@@ -2449,7 +2456,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
         p.units = pl.nsplit * Hkv;
         wgs = ((p.units + 7) / 8) * pl.row_blocks * 8;
     }
-    rc = dispatch_bf16<ONE_REQUEST>(p, pl.rw, D, eb, dim3(wgs), st);
+    rc = inside ? dispatch_bf16<ONE_MERGED>(p, pl.rw, D, eb, dim3(wgs), st) : dispatch_bf16<ONE_REQUEST>(p, pl.rw, D, eb, dim3(wgs), st);
     if (rc) return rc;
     if (pl.nsplit > 1 && !inside) {
         dim3 cg((M * Hq + 7) / 8, 1);
