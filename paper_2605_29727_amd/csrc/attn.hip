@@ -2238,22 +2238,23 @@ void split_plan(Plan &pl, int L, int want)
 // the least estimated time.  The estimate: what a workgroup's tiles take (two workgroups of the 64-row shape share a CU
 // at 1.2 times the time each), times the rounds in which the CUs of the fullest XCD take the workgroups, but no less than the
 // K/V bytes need, some of the smaller of the two on top; and for more than one split the merge.  Its constants are a fit to
-// 250 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
-// and 30 split counts: the choice is 1.3 % behind the best one found on average, the rule by row count alone that it
-// replaces (always 256 workgroups where the tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows
-// over 450 keys: 21 us in 256-row blocks and 2 splits, 12 us in 64-row blocks and 5).
+// 700 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
+// and 28 split counts: the choice is 1.2 % behind the best one found on average (with half of them left out of the fit, 1.5 % on
+// those; with the constants of the merge by a second launch 2.1 %), a rule by row count alone (always 256 workgroups where the
+// tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows over 450 keys: 21 us in 256-row blocks
+// and 2 splits, 12 us in 64-row blocks and 5).
 // `force_split` > 0 and `force_shape` in 1..3 replace the choice (the tuning entry point passes them).
 Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split = 0, int force_shape = 0)
 {
     static constexpr struct { int rw, kw, nt; float start, tile[3]; } SHAPES[3] = {      // tile: us; bf16 D = 128, D = 64, FP8
-        { 2, 2, 5, 0.0f, { 0.456f, 0.239f, 0.443f } },
-        { 4, 2, 8, 0.5f, { 0.492f, 0.314f, 0.575f } },
-        { 8, 1, 8, 0.1f, { 0.695f, 0.421f, 0.0f } },
+        { 2, 2, 5, 0.0f, { 0.414f, 0.239f, 0.412f } },
+        { 4, 2, 8, 0.54f, { 0.532f, 0.290f, 0.574f } },
+        { 8, 1, 8, 0.08f, { 0.768f, 0.429f, 0.0f } },
     };
-    static constexpr float SHARED_TILE[3] = { 0.560f, 0.308f, 0.585f };                   // two 64-row workgroups on a CU
+    static constexpr float SHARED_TILE[3] = { 0.733f, 0.342f, 0.597f };                   // two 64-row workgroups on a CU
     static constexpr int SPLITS[] = { 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64 };
     const int rows_g = Hq / Hkv * M, kind = eb == 1 ? 2 : D == 64 ? 1 : 0;
-    const float bytes = 2.0f * ((float)L + M) * Hkv * D * eb, mem = bytes / 5.7e6f, part = 2.0f * M * Hq * D * 1e-6f;
+    const float bytes = 2.0f * ((float)L + M) * Hkv * D * eb, mem = bytes / 8.3e6f, part = 2.0f * M * Hq * D * 1e-6f;
     Plan best = {};
     float best_t = 0.f;
     for (int k = 0; k < 3; ++k) {
@@ -2267,10 +2268,10 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
             split_plan(pl, L, want);
             const int n = pl.nsplit, wgs = (n * Hkv + 7) / 8 * 8 * pl.row_blocks;         // (as many as the fullest XCD has, times 8)
             const float cap = k == 0 ? 512.f : 256.f, fill = wgs / cap;
-            const float rounds = 0.45f * std::ceil(fill) + 0.55f * std::max(1.f, fill);
+            const float rounds = 0.56f * std::ceil(fill) + 0.44f * std::max(1.f, fill);
             const float comp = rounds * pl.sps * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]);
-            float t = SHAPES[k].start + std::max(comp, mem) + 0.2f * std::min(comp, mem);
-            if (n > 1) t += 2.0f + n * part + 0.09f * std::max(0, n - 32);
+            float t = SHAPES[k].start + std::max(comp, mem) + 0.184f * std::min(comp, mem);
+            if (n > 1) t += merges_inside(pl, Hkv) ? 1.67f + 0.70f * n * part : 1.73f + 1.09f * n * part + 0.116f * std::max(0, n - 32);
             if (!best_t || t < best_t) { best = pl; best_t = t; }
         };
         if (force_split > 0) { consider(force_split); continue; }
