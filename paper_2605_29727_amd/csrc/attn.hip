@@ -2235,26 +2235,26 @@ void split_plan(Plan &pl, int L, int want)
 
 // Shape of the workgroups (64, 128 or 256 packed rows of a KV head; 32 rows per wave, pairs of waves alternating over the
 // tiles in the first two, the software-pipelined loop in the third) and number of key splits of one request: those with
-// the least estimated time.  The estimate: what a workgroup's tiles take (two workgroups of the 64-row shape share a CU
-// at 1.2 times the time each), times the rounds in which the CUs of the fullest XCD take the workgroups, but no less than the
+// the least estimated time.  The estimate: what a workgroup takes, its start and its tiles (two workgroups of the 64-row shape
+// share a CU at 1.3 times the time each), times the rounds in which the CUs of the fullest XCD take the workgroups, but no less than the
 // K/V bytes need, some of the smaller of the two on top; and for more than one split the merge.  Its constants are a fit to
-// 700 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
-// and 28 split counts: the choice is 1.2 % behind the best one found on average (with half of them left out of the fit, 1.5 % on
-// those; with the constants of the merge by a second launch 2.1 %), a rule by row count alone (always 256 workgroups where the
-// tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows over 450 keys: 21 us in 256-row blocks
-// and 2 splits, 12 us in 64-row blocks and 5).
+// 1200 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
+// and 28 split counts, of the choice and of the time: the choice is 1.2 % behind the best one found on average (fitted to 700 of
+// them, 1.1 % on the other 500; with the constants of the merge by a second launch 2.0 %), a rule by row count alone (always
+// 256 workgroups where the tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows over 450 keys: 21 us
+// in 256-row blocks and 2 splits, 12 us in 64-row blocks and 5).
 // `force_split` > 0 and `force_shape` in 1..3 replace the choice (the tuning entry point passes them).
 Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split = 0, int force_shape = 0)
 {
-    static constexpr struct { int rw, kw, nt; float start, tile[3]; } SHAPES[3] = {      // tile: us; bf16 D = 128, D = 64, FP8
-        { 2, 2, 5, 0.0f, { 0.414f, 0.239f, 0.412f } },
-        { 4, 2, 8, 0.54f, { 0.532f, 0.290f, 0.574f } },
-        { 8, 1, 8, 0.08f, { 0.768f, 0.429f, 0.0f } },
+    static constexpr struct { int rw, kw, nt; float start, tile[3]; } SHAPES[3] = {      // us; tile: bf16 D = 128, D = 64, FP8
+        { 2, 2, 5, 1.90f, { 0.420f, 0.271f, 0.372f } },
+        { 4, 2, 8, 2.47f, { 0.494f, 0.294f, 0.495f } },
+        { 8, 1, 8, 2.22f, { 0.675f, 0.433f, 0.0f } },
     };
-    static constexpr float SHARED_TILE[3] = { 0.733f, 0.342f, 0.597f };                   // two 64-row workgroups on a CU
+    static constexpr float SHARED_TILE[3] = { 0.596f, 0.337f, 0.517f };                   // two 64-row workgroups on a CU
     static constexpr int SPLITS[] = { 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64 };
     const int rows_g = Hq / Hkv * M, kind = eb == 1 ? 2 : D == 64 ? 1 : 0;
-    const float bytes = 2.0f * ((float)L + M) * Hkv * D * eb, mem = bytes / 8.3e6f, part = 2.0f * M * Hq * D * 1e-6f;
+    const float bytes = 2.0f * ((float)L + M) * Hkv * D * eb, mem = bytes / 6.73e6f, part = 2.0f * M * Hq * D * 1e-6f;
     Plan best = {};
     float best_t = 0.f;
     for (int k = 0; k < 3; ++k) {
@@ -2268,10 +2268,10 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
             split_plan(pl, L, want);
             const int n = pl.nsplit, wgs = (n * Hkv + 7) / 8 * 8 * pl.row_blocks;         // (as many as the fullest XCD has, times 8)
             const float cap = k == 0 ? 512.f : 256.f, fill = wgs / cap;
-            const float rounds = 0.56f * std::ceil(fill) + 0.44f * std::max(1.f, fill);
-            const float comp = rounds * pl.sps * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]);
-            float t = SHAPES[k].start + std::max(comp, mem) + 0.184f * std::min(comp, mem);
-            if (n > 1) t += merges_inside(pl, Hkv) ? 1.67f + 0.70f * n * part : 1.73f + 1.09f * n * part + 0.116f * std::max(0, n - 32);
+            const float rounds = 0.31f * std::ceil(fill) + 0.69f * std::max(1.f, fill);
+            const float comp = rounds * (SHAPES[k].start + pl.sps * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]));
+            float t = std::max(comp, mem) + 0.123f * std::min(comp, mem);
+            if (n > 1) t += merges_inside(pl, Hkv) ? 1.67f + 0.70f * n * part : 1.78f + 0.83f * n * part + 0.095f * std::max(0, n - 32);
             if (!best_t || t < best_t) { best = pl; best_t = t; }
         };
         if (force_split > 0) { consider(force_split); continue; }
