@@ -658,7 +658,7 @@ def main():
     traffic, traffic_src = measured_traffic(L, N)
     roofline = {"bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(gbps / HBM_PEAK_GBPS, 4), "traffic": traffic, "traffic_source": traffic_src,
-                "kernel": "tree_verify_attn (tv_attn_bf16, which also forms the ancestor mask, + tv_combine_bf16)",
+                "kernel": "tree_verify_attn (tv_attn_bf16, which also forms the ancestor mask and merges its key splits; + tv_combine_bf16 where it does not)",
                 "algorithmic_bytes": ab, "us_per_launch": round(attn_ms * 1e3, 3),
                 "us_in_step": round(attn_ms_in_step * 1e3, 3), "us_warm_cache": round(attn_warm_ms * 1e3, 3),
                 "us_bracketed_one_by_one": attn_each,

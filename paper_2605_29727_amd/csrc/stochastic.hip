@@ -14,7 +14,7 @@
 // its part in words of its own, (tag << 32 | 32 bits of payload) so that a word says by itself whether it is this
 // exchange's, and every workgroup reads all parts and does the same arithmetic on them in the same order, so that they
 // all take the same decisions and nobody has to be told.  An exchange is one store and one load at the memory side
-// (relaxed device-scope atomics: the L2s of the 8 XCDs are not coherent with each other), about 2 us; two sets of words in turn are
+// (relaxed device-scope atomics: the L2s of the 8 XCDs are not coherent with each other), 1.5 us; two sets of words in turn are
 // enough, because a workgroup writes exchange i + 2 only after it has read all of exchange i + 1, which everybody
 // wrote after reading exchange i.  Tags count on from call to call (`base` in the workspace), so words are never cleared.
 //
@@ -38,11 +38,12 @@
 // rounding of e.  Anything that does not converge is walked one by one.
 // For the evaluations a workgroup sorts its slice once by e / q into bins with prefix sums.
 //
-// What bounds it is latency: an exchange (2 us), the row loads in front of it (2 us), code that runs once per call.  Measured
+// What bounds it is latency: an exchange (1.5 us for one double, 2.5 for a chain's rows or for the sums at
+// 128 points), the row loads in front of it (2 us), code that runs once per call.  Measured
 // at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 40 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
-// levels, bf16: 860 .. 1280 -> 35 .. 44 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
-// tokens instead of 2048 (half the workgroups): 54 and 47 us at the same two.
+// levels, bf16: 860 .. 1280 -> 32 .. 37 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
+// tokens instead of 2048 (half the workgroups): 53 and 52 .. 56 us at the same two.
 #include "btv_common.h"
 
 #include <algorithm>
@@ -967,7 +968,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 }
 
 // Slices for a vocabulary of V tokens on at most `most` workgroups (no more than CUs that the stream may use: with 32 of them the two
-// walks named at the top take 71 and 60 us, with 16 125 and 115): of 2048 tokens (two per thread) as long as those cover the
+// walks named at the top take 53 and 52 .. 56 us, with 16 110 and 101 .. 118): of 2048 tokens (two per thread) as long as those cover the
 // vocabulary, of 4096, of 8192, longer ones above.
 struct SaPlan { int G, per, pt; bool over; };
 SaPlan sa_plan(int V, int most)
