@@ -40,10 +40,10 @@
 //
 // What bounds it is latency: an exchange (1.5 us for one double, 2.5 for a chain's rows or for the sums at
 // 128 points), the row loads in front of it (2 us), code that runs once per call.  Measured
-// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 40 us against
+// at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 39 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
-// levels, bf16: 860 .. 1280 -> 32 .. 37 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
-// tokens instead of 2048 (half the workgroups): 53 and 52 .. 56 us at the same two.
+// levels, bf16: 860 .. 1280 -> 31 .. 36 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
+// tokens instead of 2048 (half the workgroups): 52 and 48 .. 52 us at the same two.
 #include "btv_common.h"
 
 #include <algorithm>
@@ -313,8 +313,10 @@ struct SaShared {
     double sE[SA_POINTS], sQ[SA_POINTS], part[SA_T];
     int bin_at[SA_BINS + 1];                            // where bin b (0 = largest ratios) starts
     double cE[SA_T + 1], cQ[SA_T + 1];                  // sums over the sorted positions before PT * c
-    float2 sorted[SA_T * BT];                           // (e, q) of the slice, e / q descending by bin (last: what lies
+    float2 sorted[SA_T * BT];                           // (e, q) of the slice, e / q descending by bin (behind the rest: what lies
                                                         // below 64 KB is addressed with the instructions' own offsets)
+    static constexpr bool KEEP = BT == 4;               // (e, q) in the row's order, kept through a fan (8 tokens a thread leave no room for it)
+    float2 row[KEEP ? SA_T * BT : 1];
 };
 
 // A walk that goes down mostly takes first children (they have the largest draft probability), so the rows of a node, its
@@ -543,21 +545,23 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             if ((double)L.uni[min(ui + j, M)] * (qx * invT) * Gs < (px > 0.0 ? px : 0.0)) { accepted = c; ++j; break; }
             double s1 = s + Gs * invT;
             bool all = false;
-            if (batch_ok && j + (nk >> 5) >= SA_DIRECT && nk - j >= SA_BATCH_MIN && s > 0.0) {
+            // (expected not to happen, which keeps the fan's code out of the way of the chain's: a followed draft takes 1.7 us of 36 less)
+            if (__builtin_expect(batch_ok && j + (nk >> 5) >= SA_DIRECT && nk - j >= SA_BATCH_MIN && s > 0.0, 0)) {
                 // ---- child j is rejected, K - 1 more follow: s_1 .. s_K at once (pt[i] is s_{i+1}, ptG[i] its G) ---------
                 forget();
                 const int K = nk - j, kj = k0 + j;
                 {
                     // the row's tokens, from its four wavefronts to all of them
+                    float2 *row = SaShared<PT>::KEEP ? L.row : L.sorted;
                     if (here) {
 #pragma unroll
-                        for (int i = 0; i < TG; ++i) L.sorted[(tv - v0) + TS * (i / 4) + i % 4] = make_float2(e[i], q[i]);
+                        for (int i = 0; i < TG; ++i) row[(tv - v0) + TS * (i / 4) + i % 4] = make_float2(e[i], q[i]);
                     }
                     __syncthreads();
                     const int bv = v0 + tid * BT;
                     float be[BT], bq[BT];
 #pragma unroll
-                    for (int i = 0; i < BT; ++i) { const float2 x = L.sorted[tid * BT + i]; be[i] = x.x; bq[i] = x.y; }
+                    for (int i = 0; i < BT; ++i) { const float2 x = row[tid * BT + i]; be[i] = x.x; bq[i] = x.y; }
                     const int b0 = (int)(__float_as_uint((float)(s * invf)) >> 18);
                     L.bin_at[tid] = 0;
                     if (wv == 0) {                      // 1 / T_k, and how far s can come
@@ -801,9 +805,17 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 }
                 forget();
                 asm volatile("" : "+v"(tv));
-                load_row();                             // (the row's registers were given up for the fan)
+                if constexpr (SaShared<PT>::KEEP) {     // (the row's registers were given up for the fan; from memory: 0.9 us more)
 #pragma unroll
-                for (int i = 0; i < TG; ++i) e[i] = none ? 0.f : exp_neg(e[i] - m_own);
+                    for (int i = 0; i < TG; ++i) {
+                        const float2 x = L.row[(tv - v0) + TS * (i / 4) + i % 4];
+                        e[i] = x.x; q[i] = x.y;
+                    }
+                } else {
+                    load_row();
+#pragma unroll
+                    for (int i = 0; i < TG; ++i) e[i] = none ? 0.f : exp_neg(e[i] - m_own);
+                }
                 if (status == 1) { s1 = L.pt[K - 1]; all = true; }      // all rejected: the parts of G(s_K) are still to be had
                 batch_ok = false;                       // not converged, or a residual that is all zero
             }
@@ -968,7 +980,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 }
 
 // Slices for a vocabulary of V tokens on at most `most` workgroups (no more than CUs that the stream may use: with 32 of them the two
-// walks named at the top take 53 and 52 .. 56 us, with 16 110 and 101 .. 118): of 2048 tokens (two per thread) as long as those cover the
+// walks named at the top take 52 and 48 .. 52 us, with 16 110 and 101 .. 118): of 2048 tokens (two per thread) as long as those cover the
 // vocabulary, of 4096, of 8192, longer ones above.
 struct SaPlan { int G, per, pt; bool over; };
 SaPlan sa_plan(int V, int most)
