@@ -49,6 +49,20 @@ def test_full_vocabulary(G, oracle, sigma, seed, N_max, kind):
     _check(G, oracle, marg, N_max, _cost(kind, N_max), 1.0)
 
 
+@pytest.mark.parametrize("N_max", [5, 64, 65, 158, 256])
+@pytest.mark.parametrize("kind,scale", [("affine", 1.0), ("affine", 1e-3), ("quadratic", 3.0), ("flat", 1.0), ("steep", 1.0)])
+def test_confident_chain(G, oracle, N_max, kind, scale):
+    """A draft that the sweep follows from its greedy chain: under the floor of the early stop where the costs give one, from the
+    chain's own bound where they do not, in 64 nodes and past them; with a few wide fans, and with all first tokens alike."""
+    B, V = 12, 700
+    base = synth.marginals(21, B, V, 3.0).astype(np.float64)
+    hot = 0.9 * 0.93 ** np.arange(B)
+    sharp = base * (1.0 - hot[:, None]); sharp[np.arange(B), 31 * np.arange(1, B + 1)] += hot
+    even = np.full((B, V), 2.0 ** -10); even[:, 11] = 0.75
+    for marg in (sharp, even):
+        _check(G, oracle, marg.astype(np.float32), N_max, _cost(kind, N_max, scale), 1.5)
+
+
 def test_stops_span_the_range(G, oracle):
     """Flat cost: runs to N_max; cost proportional to N: stops after the first node; in between for the others."""
     marg = synth.marginals(3, 16, 128256, 5.0)
