@@ -222,7 +222,10 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
  *   j over 0..L-1 and L+a for a in anc(i).
  * Q, O [M,Hq,D]; K, V [L+M,Hkv,D] (tree node a at row L+a); all row-major, contiguous, of
  * `dtype`, 16-byte aligned; softmax and accumulation in fp32.  scale <= 0 selects 1/sqrt(D).
- * Workspace: ancestor bitmasks and split-K partial results.
+ * Workspace: split-K partial results, and words by which the workgroups that merge them find each
+ * other.  The query answers what every call of up to M nodes over up to L keys needs (heads, D and
+ * dtype being the same), so one workspace for the largest sizes serves all smaller ones: a shorter
+ * context or a smaller tree may be cut into more parts and need more than a longer one.
  * ------------------------------------------------------------------------------------------- */
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype);
 int btv_tree_verify_attn(const void *Q, const void *K, const void *V, const int32_t *parent,
@@ -236,8 +239,7 @@ int btv_tree_verify_attn(const void *Q, const void *K, const void *V, const int3
  * call allocates and frees nothing and synchronises nothing.
  *   status   [1] uint32 DEVICE, optional: kernels OR their data-error bits into it (non-zero =
  *            what btv_workspace_status would report as BTV_EDATA); the caller clears it.
- *   Shapes whose scratch need (btv_tree_verify_attn_workspace) exceeds the array are refused with
- *   BTV_EWORKSPACE and nothing is launched; every shape with M * Hq <= 4096 rows fits.
+ *   Every shape's need fits the array.
  *   All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  *   streams, two threads) race and give wrong results; calls on one stream are safe.
  * All other arguments and errors as for btv_tree_verify_attn. */
@@ -402,7 +404,7 @@ int btv_kv_commit_paged(void *Kpool, void *Vpool, int layers, long long layer_st
  *            rounds pieces to whole tiles, so fewer may result)
  *   shape    0 = the library's choice; 1, 2, 3 = workgroups of 64, 128, 256 packed query rows
  *            (3 is not built for an FP8 cache: BTV_EINVAL)
- * The workspace query takes the same nsplit and shape as the call it sizes.
+ * The workspace query takes the same nsplit and shape as the call it sizes (M and L may be larger).
  * ------------------------------------------------------------------------------------------- */
 size_t btv_tree_verify_attn_tuned_workspace(int M, int L, int Hq, int Hkv, int D, int kv_fp8,
                                             int nsplit, int shape);

@@ -2170,6 +2170,7 @@ __global__ __launch_bounds__(256) void tv_attn_f32(AttnParams p)
 // One array per GPU, part of the loaded code object (zero until first used), held until the process ends.  Host code
 // never uses the array's name as an address: the device address is asked for once per device and kept.
 constexpr size_t SCRATCH_BYTES = (size_t)32 << 20;
+constexpr size_t MOST_PARTIALS = (size_t)31 << 20;      // bytes of partials that a plan of one request may take: they and the words fit the array
 constexpr int SCRATCH_MAX_DEVICES = 64;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 void *g_scratch_ptr[SCRATCH_MAX_DEVICES];
@@ -2199,6 +2200,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
     if (i < words) p[i] = 0u;
 }
 
+constexpr int MOST_SPLITS = 64;                         // that the library chooses by itself
 struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; float bytes; };      // (bytes of K and V)
 
 // Whether the workgroups of a plan merge their partials themselves (merge_group): few enough splits and groups for its words; all
@@ -2276,8 +2278,8 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
         };
         if (force_split > 0) { consider(force_split); continue; }
         // no more splits than tiles, nor partials than the built-in scratch array holds (32 MB are 6 us to write and read)
-        const int most = (int)std::min<long long>(std::min(64, pl.stages),
-                                                  std::max<long long>(1, (31ll << 20) / (long long)(partial_rows(pl, M, Hq, Hkv) * (D * 2 + 16))));
+        const int most = (int)std::min<long long>(std::min(MOST_SPLITS, pl.stages),
+                                                  std::max<long long>(1, (long long)(MOST_PARTIALS / (partial_rows(pl, M, Hq, Hkv) * (D * 2 + 16)))));
         for (int want : SPLITS)
             if (want <= most) consider(want);
         for (int cap = 256; cap <= (k == 0 ? 1024 : 512); cap *= 2) {                     // as many as whole rounds take
@@ -2343,6 +2345,27 @@ WsLayout ws_layout(size_t rows, int D, int nsplit, int batch = 0)
     w.opart = off; off += btv_align_up(ns * rows * D * 2, BTV_WS_ALIGN);
     w.total = off;
     return w;
+}
+
+// What the workspace queries of one request answer: enough for every call of up to M nodes over up to L keys.  The plan's own need
+// is no answer to that: a shorter context or a smaller tree may be cut into more parts, or rows padded to larger blocks (32 nodes of an
+// 8B shape: 8.8 MB at 32768 keys, 9.1 at 10208).  No plan of these sizes has more splits than there are tiles, nor than MOST_SPLITS, nor more than
+// MOST_PARTIALS bytes in more than one split; partial_rows grows with M.  64 nodes over 8192 keys: 32.6 MB where that call's plan takes 8.6.
+size_t enough_for(int M, int L, int Hq, int Hkv, int D, int eb, int force_split = 0, int force_shape = 0)
+{
+    size_t most = 0;
+    const int n = std::min(force_split > 0 ? force_split : MOST_SPLITS, (L + M + TK - 1) / TK);
+    for (int k = 1; k <= 3 && n > 1; ++k) {
+        if (force_shape ? std::min(force_shape, eb == 1 ? 2 : 3) != k : eb == 1 && k == 3) continue;
+        Plan pl = {};
+        pl.wr = 32 << k;
+        pl.row_blocks = (Hq / Hkv * M + pl.wr - 1) / pl.wr;
+        const size_t part = partial_rows(pl, M, Hq, Hkv) * (D * 2 + 16);
+        most = std::max(most, force_split > 0 ? n * part : std::min(n * part, MOST_PARTIALS));
+    }
+    // (the two arrays are aligned one by one)
+    static_assert(MOST_PARTIALS + BTV_WS_HEADER + MERGE_GROUPS * sizeof(MergeWords) + 2 * BTV_WS_ALIGN <= SCRATCH_BYTES, "a plan's need fits the built-in array");
+    return ws_layout(0, D, n).total + btv_align_up(most, BTV_WS_ALIGN) + (n > 1 ? BTV_WS_ALIGN : 0);
 }
 
 enum Form { ONE_REQUEST, ONE_MERGED, SHORT_BATCH, LONG_BATCH };
@@ -2536,8 +2559,7 @@ int btv_tree_ancestor_mask(const int32_t *parent, int M, uint32_t *anc, void *ws
 size_t btv_tree_verify_attn_workspace(int M, int L, int Hq, int Hkv, int D, int dtype)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK) return 0;
-    const Plan pl = make_plan(M, L, Hq, Hkv, D);
-    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, dtype == BTV_BF16 ? pl.nsplit : 1).total;
+    return dtype == BTV_BF16 ? enough_for(M, L, Hq, Hkv, D, 2) : ws_layout(0, D, 1).total;
 }
 
 int btv_tree_verify_attn(const void *Q, const void *K, const void *V, const int32_t *parent, int M, int L, int Hq,
@@ -2553,10 +2575,6 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
     BTV_REQUIRE(dtype == BTV_F32 || dtype == BTV_BF16, "dtype=%d unsupported", dtype);
     int rc = check_shape(M, L, Hq, Hkv, D);
     if (rc) return rc;
-    const size_t need = btv_tree_verify_attn_workspace(M, L, Hq, Hkv, D, dtype);
-    if (need > SCRATCH_BYTES)
-        return btv_fail(BTV_EWORKSPACE, "this shape needs %zu bytes of scratch, the built-in array holds %zu: use "
-                        "btv_tree_verify_attn with a workspace", need, SCRATCH_BYTES);
     void *ws = nullptr;
     rc = scratch_address(&ws);
     if (rc) return rc;
@@ -2571,8 +2589,7 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
 size_t btv_tree_verify_attn_fp8kv_workspace(int M, int L, int Hq, int Hkv, int D)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    const Plan pl = make_plan(M, L, Hq, Hkv, D, 1);
-    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, pl.nsplit).total;
+    return enough_for(M, L, Hq, Hkv, D, 1);
 }
 
 int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, float k_scale, float v_scale,
@@ -2588,8 +2605,7 @@ int btv_tree_verify_attn_fp8kv(const void *Q, const void *K8, const void *V8, fl
 size_t btv_tree_verify_attn_tuned_workspace(int M, int L, int Hq, int Hkv, int D, int kv_fp8, int nsplit, int shape)
 {
     if (check_shape(M, L, Hq, Hkv, D) != BTV_OK || (kv_fp8 && D != 128) || nsplit < 0 || shape < 0 || shape > 3) return 0;
-    const Plan pl = make_plan(M, L, Hq, Hkv, D, kv_fp8 ? 1 : 2, nsplit, shape);
-    return ws_layout(partial_rows(pl, M, Hq, Hkv), D, pl.nsplit).total;
+    return enough_for(M, L, Hq, Hkv, D, kv_fp8 ? 1 : 2, nsplit, shape);
 }
 
 int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale, float v_scale,

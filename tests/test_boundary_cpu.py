@@ -158,3 +158,57 @@ def test_host_calibration_matches_the_oracle(oracle):
     assert btv.btv_verify_cost_curve(0, *args) == []
     with pytest.raises(btv.BtvError):
         btv.btv_verify_cost_curve(257, *args)
+
+
+def _need(lib, fn, *args):
+    """What a call needs by its own plan, from the refusal of a workspace of no bytes (nothing is launched)."""
+    fake = C.c_void_p(4096)
+    a = [fake if x is None else x for x in args]
+    assert getattr(lib, fn)(*a, fake, fake, C.c_size_t(0), None) == -2       # BTV_EWORKSPACE
+    return int(re.search(rb"too small: 0 < (\d+) bytes", lib.btv_last_error()).group(1))
+
+
+def _attn_need(lib, M, L, Hq, Hkv, D, dtype):
+    return _need(lib, "btv_tree_verify_attn", None, None, None, None, M, L, Hq, Hkv, D, dtype, C.c_float(0.0))
+
+
+def _attn_fp8_need(lib, M, L, Hq, Hkv):
+    one = C.c_float(1.0)
+    return _need(lib, "btv_tree_verify_attn_fp8kv", None, None, None, one, one, None, M, L, Hq, Hkv, 128, C.c_float(0.0))
+
+
+def _attn_tuned_need(lib, M, L, Hq, Hkv, nsplit, shape):
+    one = C.c_float(1.0)
+    return _need(lib, "btv_tree_verify_attn_tuned", None, None, None, 0, one, one, None, M, L, Hq, Hkv, 128, C.c_float(0.0), nsplit, shape)
+
+
+# (most nodes, longest context, Hq, Hkv, D): the 8B shape with trees of all sizes (32 nodes at 10208 keys need more than at
+# 32768), wide and narrow groups, one head, more heads than workgroups that the chip holds at once
+@pytest.mark.parametrize("shape", [(32, 32768, 32, 8, 128), (24, 16384, 32, 8, 128), (16, 16384, 32, 8, 128), (256, 9000, 32, 8, 128), (65, 8192, 64, 8, 128),
+                                   (23, 1531, 32, 8, 64), (64, 6000, 16, 1, 128), (33, 4000, 64, 64, 128), (16, 128, 1, 1, 64), (1, 31, 4, 4, 64),
+                                   (128, 32768, 28, 4, 128)])
+def test_a_workspace_for_the_largest_sizes_serves_all_smaller_ones(lib, shape):
+    M, L, Hq, Hkv, D = shape
+    for n in ("btv_tree_verify_attn_fp8kv_workspace", "btv_tree_verify_attn_tuned_workspace"):
+        getattr(lib, n).restype = C.c_size_t
+    trees = sorted({M, 1, max(1, M // 2), max(1, M - 1)} | {m for m in (4, 16, 17, 32, 33, 64, 65, 129) if m < M})
+    contexts = [L, 0, max(0, L - 1)] + list(range(16, L, max(1, L // 512)))
+    have = lib.btv_tree_verify_attn_workspace(M, L, Hq, Hkv, D, 1)
+    assert max(_attn_need(lib, m, l, Hq, Hkv, D, 1) for m in trees for l in contexts) <= have
+    assert max(_attn_need(lib, m, l, Hq, Hkv, D, 0) for m in trees for l in contexts[:9]) <= lib.btv_tree_verify_attn_workspace(M, L, Hq, Hkv, D, 0)
+    assert have < (1 << 25)                       # (what the built-in array of the allocation-free form holds)
+    if D != 128:
+        return
+    have = lib.btv_tree_verify_attn_fp8kv_workspace(M, L, Hq, Hkv, D)
+    assert max(_attn_fp8_need(lib, m, l, Hq, Hkv) for m in trees for l in contexts) <= have
+    for nsplit, form in ((0, 1), (0, 3), (7, 0), (32, 2), (100, 1)):
+        have = lib.btv_tree_verify_attn_tuned_workspace(M, L, Hq, Hkv, D, 0, nsplit, form)
+        assert max(_attn_tuned_need(lib, m, l, Hq, Hkv, nsplit, form) for m in trees for l in contexts[::4]) <= have
+
+
+def test_a_workspace_smaller_than_a_call_needs_is_refused(lib):
+    fake, f0 = C.c_void_p(4096), C.c_float(0.0)
+    for M, L in ((64, 8192), (32, 10208), (3, 100)):
+        need = _attn_need(lib, M, L, 32, 8, 128, 1)
+        rc = lib.btv_tree_verify_attn(fake, fake, fake, fake, M, L, 32, 8, 128, 1, f0, fake, fake, C.c_size_t(need - 1), None)
+        assert rc == -2 and b"too small" in lib.btv_last_error()
