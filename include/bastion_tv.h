@@ -258,7 +258,8 @@ int btv_tree_verify_attn_noalloc(const void *Q, const void *K, const void *V, co
  *   M_max, L_max  HOST upper bounds on any request's node count / prefix length (they size the
  *               grid and the workspace); a request exceeding them, or whose L+M exceeds
  *               max_blocks*BTV_PAGE, is skipped and flagged (see btv_workspace_status).
- * Block ids outside [0, num_blocks) are clamped, so no access leaves the pools. */
+ * Block ids outside [0, num_blocks) are clamped, so no access leaves the pools.
+ * The workspace query answers what every call with no larger batch, M_max and L_max needs. */
 size_t btv_tree_verify_attn_paged_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D);
 int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_blocks,
                                const int32_t *block_table, int max_blocks, const int32_t *q_offset,

@@ -2295,19 +2295,23 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
 // themselves: how many teams of them the chip holds and the smallest share (slots: a stretch of the longest request gets that
 // many parts where the average one is 2.5 times shorter; longer ones larger parts).
 struct PlanB { int rw, wr_log2, pairing, teams_log2, slots, wmin, sps, row_blocks; bool merge; };
+// The plan that the workgroups make themselves pays where they have much to do, or a few long requests leave a grid of parts
+// ragged (64-row tiles per CU at most: 161 us against 217 for 8 requests of 5k to 15k with 35 to 115 nodes, 63 against 80 for 8 x 8k with 32);
+// below, its larger row blocks and the longer way to the first tile cost more than an even load gives (14 requests
+// of 256 to 4k with up to 46 nodes: 62 us against 53).
+bool short_batch(int rows_g, int t, int Hkv, int D, int batch, int eb)
+{
+    const long long tiles_cu = (long long)Hkv * batch * ((rows_g + 63) >> 6) * t / 256;
+    return tiles_cu * D < 220 * 128 && !(t >= 250 && tiles_cu >= (eb == 2 ? 60 : 100));
+}
+
 PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, int eb)
 {
     PlanB b = {};
     const int G = Hq / Hkv, rows_g = G * M_max, t = (L_max + M_max + TK - 1) / TK;
-    // The plan pays where the workgroups have much to do, or a few long requests leave a grid of parts ragged (64-row tiles per
-    // CU at most: 161 us against 217 for 8 requests of 5k to 15k with 35 to 115 nodes, 63 against 80 for 8 x 8k with 32);
-    // below, its larger row blocks and the longer way to the first tile cost more than an even load gives (14 requests
-    // of 256 to 4k with up to 46 nodes: 62 us against 53).
-    const long long rb64 = (rows_g + 63) >> 6, tiles_cu = Hkv * batch * rb64 * t / 256;
-    const bool is_short = tiles_cu * D < 220 * 128 && !(t >= 250 && tiles_cu >= (eb == 2 ? 60 : 100));
-    if (is_short) {
+    if (short_batch(rows_g, t, Hkv, D, batch, eb)) {
         b.rw = 2; b.wr_log2 = 6;
-        b.row_blocks = (int)rb64;
+        b.row_blocks = (rows_g + 63) >> 6;
         const int base = Hkv * batch * b.row_blocks;
         // One request: as in the contiguous form.  More: parts of 32 tiles even out the lengths; where that leaves the chip room
         // (it takes 512 of these workgroups at once), parts of 8 tiles or more for one such round of the longest request, of
@@ -2366,6 +2370,25 @@ size_t enough_for(int M, int L, int Hq, int Hkv, int D, int eb, int force_split 
     // (the two arrays are aligned one by one)
     static_assert(MOST_PARTIALS + BTV_WS_HEADER + MERGE_GROUPS * sizeof(MergeWords) + 2 * BTV_WS_ALIGN <= SCRATCH_BYTES, "a plan's need fits the built-in array");
     return ws_layout(0, D, n).total + btv_align_up(most, BTV_WS_ALIGN) + (n > 1 ? BTV_WS_ALIGN : 0);
+}
+
+// The same for a batch: up to `batch` requests, M_max nodes, L_max keys.  Fewer or smaller requests are cut into more parts, so their
+// partials may be the more.  Of make_batch_plan's forms: a short batch takes up to 8 parts of 32 tiles or more; where its grid is
+// small, up to 32 parts (512 of one request) of 8 tiles or more, in no more than 1024 (512) workgroups of 64 rows; the others 8
+// parts, or 4 and their share of (5 << teams_log2) pieces, which is 640 row blocks, 1280 where they go in pairs.  All of it grows with
+// the sizes, and so does what makes a batch one of the others.  8 x 128 nodes over 16k keys 124.9 MB, which is that plan's own need.
+size_t enough_for_batch(int batch, int M_max, int L_max, int Hq, int Hkv, int D, int eb)
+{
+    const int rows_g = Hq / Hkv * M_max, t = (L_max + M_max + TK - 1) / TK;
+    const long long rows = (long long)batch * M_max * Hq, one = (long long)M_max * Hq;
+    long long most = 0;
+    if (t >= 64) most = rows * std::min(8, t / 32);
+    if (t >= 16) most = std::max({ most, std::min<long long>(rows * std::min(32, t / 8), 1024 * 64), std::min<long long>(one * std::min(512, t / 8), 512 * 64) });
+    if (!short_batch(rows_g, t, Hkv, D, batch, eb)) {
+        const long long spread = 640 * 128 * (rows_g <= 128 ? 1 : eb == 1 || rows_g <= 256 ? 2 : 4);
+        most = std::max(most, std::min(rows * 32, std::max(rows * 8, rows * 4 + spread)));
+    }
+    return ws_layout(0, D, 1, batch).total + (most ? btv_align_up((size_t)most * (D * 2 + 16), BTV_WS_ALIGN) + BTV_WS_ALIGN : 0);
 }
 
 enum Form { ONE_REQUEST, ONE_MERGED, SHORT_BATCH, LONG_BATCH };
@@ -2634,7 +2657,7 @@ int btv_tree_verify_attn_merge_tuned(const void *Q, const void *K, const void *V
 size_t btv_tree_verify_attn_paged_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK) return 0;
-    return ws_layout((size_t)batch * M_max * Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 2).slots, batch).total;
+    return enough_for_batch(batch, M_max, L_max, Hq, Hkv, D, 2);
 }
 
 int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_blocks,
@@ -2650,7 +2673,7 @@ int btv_tree_verify_attn_paged(const void *Q, const void *Kpool, const void *Vpo
 size_t btv_tree_verify_attn_paged_fp8kv_workspace(int batch, int M_max, int L_max, int Hq, int Hkv, int D)
 {
     if (batch < 1 || batch > 4096 || check_shape(M_max, L_max, Hq, Hkv, D) != BTV_OK || D != 128) return 0;
-    return ws_layout((size_t)batch * M_max * Hq, D, make_batch_plan(M_max, L_max, Hq, Hkv, D, batch, 1).slots, batch).total;
+    return enough_for_batch(batch, M_max, L_max, Hq, Hkv, D, 1);
 }
 
 int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const void *V8pool, float k_scale,

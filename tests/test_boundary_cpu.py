@@ -206,6 +206,30 @@ def test_a_workspace_for_the_largest_sizes_serves_all_smaller_ones(lib, shape):
         assert max(_attn_tuned_need(lib, m, l, Hq, Hkv, nsplit, form) for m in trees for l in contexts[::4]) <= have
 
 
+@pytest.mark.parametrize("heads", [(32, 8), (16, 2), (4, 1), (64, 16), (28, 4)])
+def test_a_workspace_for_the_largest_batch_serves_all_smaller_ones(lib, heads):
+    import random
+    Hq, Hkv = heads
+    rng = random.Random(Hq)
+    lib.btv_tree_verify_attn_paged_fp8kv_workspace.restype = C.c_size_t
+    one, f0, fake = C.c_float(1.0), C.c_float(0.0), [None] * 3
+
+    def need(fp8, batch, M_max, L_max, D):
+        sizes = (1, None, 1 << 20, None, None, None, batch, batch, M_max, L_max, Hq, Hkv, D, f0)
+        if fp8:
+            return _need(lib, "btv_tree_verify_attn_paged_fp8kv", *fake, one, one, *sizes)
+        return _need(lib, "btv_tree_verify_attn_paged", *fake, *sizes)
+
+    for _ in range(300):
+        fp8, batch, M_max, L_max = rng.randrange(2), int(2 ** rng.uniform(0, 8)), int(2 ** rng.uniform(0, 8)), int(2 ** rng.uniform(2, 15.3))
+        D = 128 if fp8 else rng.choice([64, 128])
+        have = (lib.btv_tree_verify_attn_paged_fp8kv_workspace(batch, M_max, L_max, Hq, Hkv, D) if fp8
+                else lib.btv_tree_verify_attn_paged_workspace(batch, M_max, L_max, Hq, Hkv, D))
+        for k in range(40):
+            b, m, l = [x if rng.random() < 0.4 else rng.randint(1, x) for x in (batch, M_max, L_max)]
+            assert need(fp8, b, m, l, D) <= have, (fp8, batch, M_max, L_max, D, b, m, l)
+
+
 def test_a_workspace_smaller_than_a_call_needs_is_refused(lib):
     fake, f0 = C.c_void_p(4096), C.c_float(0.0)
     for M, L in ((64, 8192), (32, 10208), (3, 100)):
