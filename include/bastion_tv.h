@@ -415,7 +415,8 @@ int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int 
                                size_t ws_bytes, void *stream);
 /* The same with the merge of the pieces passed as well (the two forms above: 0 and 2000).
  *   merge       0 = the library's choice; 1 = by a second launch; 2 = by the workgroups that stored
- *               the pieces, where the plan allows it; 3 = as 2, as if they did not share an L2
+ *               the pieces, where the plan allows it; 3 = as 2, with the pieces of the same rows dealt
+ *               out over the XCDs, so that their workgroups share no L2
  *   wait_ticks  how long one of those waits for the others (10 ns each; negative: not at all), after
  *               which the last to store its piece merges for it */
 int btv_tree_verify_attn_merge_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale,

@@ -48,7 +48,6 @@ struct AttnParams {
     uint32_t *flag;
     unsigned long long *sync;     // one request: words of the merge inside the attention kernel (null: tv_combine_bf16 merges)
     int wait_ticks;               // ... how long a workgroup waits for the others of its group
-    int apart;                    // ... tests: as if the group were not on one XCD
     int M, L;                     // contiguous: actual sizes; paged: host upper bounds
     int Hq, Hkv, G;
     int max_blocks, num_blocks;
@@ -1559,7 +1558,7 @@ __device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's partials are in the L2 ...
     __syncthreads();                                    // ... and all the workgroup's
     if (tid < 64) {
-        const bool together = __builtin_amdgcn_ballot_w64(begun != (tag << 8 | this_xcd())) == 0ull && !p.apart;
+        const bool together = __builtin_amdgcn_ballot_w64(begun != (tag << 8 | this_xcd())) == 0ull;
         if (!together) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         auto say = [&](u64 word) {
             if (lane == 0) __hip_atomic_store(&m.near[split], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1617,7 +1616,8 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     BTV_FETCH_ARGS(p);
     // Workgroups go to the 8 XCDs round-robin by their linear id.  The row blocks of one (key split, KV head) stream the same K/V
     // bytes, so they get ids that are congruent mod 8 and share one L2; where the merge is done here, so do all splits of a group
-    // (p.units counts the (split, head) pairs, or the heads, or the groups that are dealt out to the XCDs).
+    // (p.units counts the (split, head) pairs, or the heads, or the groups that are dealt out to the XCDs; 0: the pairs are dealt
+    // out although the merge is done here, so that tests meet a group on several XCDs).
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     Piece pc = {};
     if constexpr (!MERGE) {
@@ -1628,9 +1628,13 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
         const int q = slot / p.row_blocks;
         pc.by = slot % p.row_blocks; pc.g = (q / p.nsplit) * 8 + xcd; pc.bx = q % p.nsplit;
         if (pc.g >= p.Hkv) return;
-    } else {
+    } else if (p.units) {
         const int q = (slot / p.nsplit) * 8 + xcd;
         pc.by = q % p.row_blocks; pc.g = q / p.row_blocks; pc.bx = slot % p.nsplit;
+        if (pc.g >= p.Hkv) return;
+    } else {
+        const int unit = (slot / p.row_blocks) * 8 + xcd;
+        pc.by = slot % p.row_blocks; pc.g = unit / p.nsplit; pc.bx = unit % p.nsplit;
         if (pc.g >= p.Hkv) return;
     }
     const Req rq = load_req<false>(p, 0);
@@ -2496,9 +2500,9 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     int wgs;
     if (inside) {
         p.sync = reinterpret_cast<unsigned long long *>(w8 + wl.sync);
-        p.wait_ticks = wait_ticks; p.apart = merge == 3;
-        p.units = Hkv % 8 == 0 ? Hkv : Hkv * pl.row_blocks;
-        wgs = pl.nsplit * Hkv * pl.row_blocks;
+        p.wait_ticks = wait_ticks;
+        p.units = merge == 3 ? 0 : Hkv % 8 == 0 ? Hkv : Hkv * pl.row_blocks;
+        wgs = merge == 3 ? (pl.nsplit * Hkv + 7) / 8 * 8 * pl.row_blocks : pl.nsplit * Hkv * pl.row_blocks;
     } else {
         p.units = pl.nsplit * Hkv;
         wgs = ((p.units + 7) / 8) * pl.row_blocks * 8;

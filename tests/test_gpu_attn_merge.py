@@ -3,7 +3,8 @@
 Both do the same arithmetic on the same partials; the sums over the splits differ in their order, that is by some 1e-6 of the terms
 before the final rounding to bf16, which may then fall to the neighbouring number (spacing: at most 2^-7 of it).  The second launch's
 parity with the oracle is test_gpu_attn.py's and test_gpu_fp8kv.py's.  All ways of the merge by workgroups give the same bits.  Every way a workgroup can take is forced: it waits for the
-others, it leaves at once (the last one then merges for all), and it does not rely on a common L2.
+others, it leaves at once (the last one then merges for all), and (merge = 3) it shares its rows with workgroups on other XCDs, whose
+L2s do not see what it stores unless it is written back and theirs are invalidated.
 """
 import pytest
 import torch
@@ -29,6 +30,14 @@ def _call(x, L, ws, nsplit, shape, **how):
     O = torch.full_like(x[0], float("nan"))
     btv.btv_tree_verify_attn_merge_tuned(x[0], x[1], x[2], x[3], L, O, ws, 0.0, nsplit, shape, **how)
     return O
+
+
+def _xcds(ws, n):
+    """The XCDs that the first group's workgroups of the last call ran on: the first n words behind the workspace's header (256 bytes)
+    hold tag << 8 | XCD.  None where no call has merged inside."""
+    words = ws[256:256 + 8 * n].view(torch.int64).tolist()
+    assert len({w >> 8 for w in words}) == 1
+    return {w & 255 for w in words} if words[0] >> 8 else None
 
 
 def _close(O, ref):
@@ -57,6 +66,9 @@ def test_same_as_the_second_launch(case):
     for how in WAYS + WAYS[:2]:
         O = _call(x, L, ws, nsplit, shape, **how)
         assert torch.equal(O, first), how
+        on = _xcds(ws, 2)
+        if on and how["merge"] and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            assert len(on) == (2 if how["merge"] == 3 else 1), how
     assert btv.btv_workspace_status(ws) == 0
 
 
