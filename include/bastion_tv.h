@@ -417,8 +417,9 @@ int btv_tree_verify_attn_tuned(const void *Q, const void *K, const void *V, int 
  *   merge       0 = the library's choice; 1 = by a second launch; 2 = by the workgroups that stored
  *               the pieces, where the plan allows it; 3 = as 2, with the pieces of the same rows dealt
  *               out over the XCDs, so that their workgroups share no L2
- *   wait_ticks  how long one of those waits for the others (10 ns each; negative: not at all), after
- *               which the last to store its piece merges for it */
+ *   wait_ticks  how long one of those waits for the others (10 ns each; negative: not at all; 500 at
+ *               most for one that has not started), after which the last to store its piece merges
+ *               for it */
 int btv_tree_verify_attn_merge_tuned(const void *Q, const void *K, const void *V, int kv_fp8, float k_scale,
                                      float v_scale, const int32_t *parent, int M, int L, int Hq, int Hkv,
                                      int D, float scale, int nsplit, int shape, int merge, int wait_ticks,

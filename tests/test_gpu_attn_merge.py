@@ -119,3 +119,24 @@ def test_replays_of_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(O, ref[k % 2]), k
         assert torch.equal(_call(y, L, ws, nsplit, shape, merge=2), ref[1]), k
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[4], CASES[11][:6] + (3, 8), CASES[12]])
+def test_beside_a_kernel_that_holds_compute_units(case):
+    """Workgroups whose peers cannot start leave, and the last one merges for them: the same bits, and the calls on the other stream end
+    while that kernel runs or after it, whichever way the two are scheduled."""
+    L, M, Hq, Hkv, D, fp8, shape, nsplit = case
+    x = _inputs(3, L, M, Hq, Hkv, D, fp8)
+    ws = btv.alloc_workspace(btv.btv_tree_verify_attn_tuned_workspace(M, L, Hq, Hkv, D, fp8, nsplit, shape))
+    ref = _call(x, L, ws, nsplit, shape, merge=2)
+    sink = torch.zeros(4096, dtype=torch.int32, device="cuda")
+    here, there = torch.cuda.Stream(), torch.cuda.Stream()
+    for held in (64, 192):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(there):
+            btv.btv_mfma_peak(held, 20000, sink)                # (2 ms)
+        with torch.cuda.stream(here):
+            outs = [_call(x, L, ws, nsplit, shape, merge=2) for _ in range(10)]
+        torch.cuda.synchronize()
+        assert all(torch.equal(O, ref) for O in outs)
+    assert btv.btv_workspace_status(ws) == 0
