@@ -421,8 +421,11 @@ __global__ __launch_bounds__(OL_WAVES * 64) void accept_greedy_one_launch(
 
 // The same where one workgroup takes all rows at once: vocabularies of up to 4 LPR tokens, LPR neighbouring lanes per row and up to
 // SMALL_PASSES rows per lane, all loads in flight before the first is looked at.  The maxima meet in LDS, so nothing goes through the
-// workspace and nobody waits: what remains is a launch, a memory round trip and the walk (17 x 64 fp32: 5.2 -> 2.9 us).
-constexpr int SMALL_PASSES = 4, SMALL_THREADS = 512;
+// workspace and nobody waits: what remains is a launch, a memory round trip and the walk (17 x 64 fp32: 4.8 us by accept_greedy_one_launch,
+// 2.6 by this).  A pass is 0.9 us, so that three passes are the most that gain (us by one launch / by this, at one, two, three and
+// four passes: 64 tokens 4.7 / 2.6, 4.9 / 3.5, 4.6 / 4.3, 5.1 / 5.2; 128 tokens 4.5 / 2.7, 4.6 / 3.6, 4.6 / 4.5, 4.8 / 5.6; 256 tokens 4.5 / 2.8 at
+// one, 4.8 / 4.8 at three, 4.6 / 5.9 at four).  More than 4 tokens per lane gain for a handful of rows only: 512 tokens, 17 rows 5.0 / 7.3.
+constexpr int SMALL_PASSES = 3, SMALL_THREADS = 512;
 template <bool BF16, int LPR>
 __global__ __launch_bounds__(SMALL_THREADS) void accept_greedy_small(const void *logits, int V, const int32_t *parent, const int32_t *token, int M,
                                                                      int32_t *path, int32_t *n_acc, int32_t *bonus, int32_t *argmax_out)

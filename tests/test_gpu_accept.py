@@ -433,7 +433,8 @@ def test_stochastic_workspace_serves_changing_sizes(G, oracle):
 
 
 @pytest.mark.parametrize("bits", [False, True])
-@pytest.mark.parametrize("V,M", [(1, 3), (15, 127), (16, 128), (64, 127), (64, 128), (65, 63), (128, 63), (128, 64), (129, 31), (256, 31), (256, 32), (257, 31)])
+@pytest.mark.parametrize("V,M", [(1, 3), (15, 127), (16, 128), (64, 127), (64, 128), (65, 63), (128, 63), (128, 64), (129, 31), (256, 31), (256, 32), (257, 31),
+                                 (64, 95), (64, 96), (128, 47), (128, 48), (200, 23), (256, 23), (256, 24)])
 def test_greedy_small_vocabularies(G, oracle, V, M, bits):
     """Around the sizes up to which one workgroup takes all rows: last rows and last tokens, ties (the lowest id), rows of -inf and of
     signed zeros."""
