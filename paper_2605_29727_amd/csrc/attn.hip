@@ -1714,9 +1714,11 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
 // first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
 // (if it is small, one of them takes it alone).
-// Bound by the matrix cores' clock (about 2.1 GHz here) and their 57 % share of a tile's cycles; the figures beside the choice
-// of the form (make_batch_plan) are the whole call's, before and after.  A piece costs 8 us beyond its tiles (finding it 1,
-// page ids and first tiles 3, merging and storing 3, waiting for the other waves 1), START and MARGIN come from that.
+// Bound by the tiles (1.08 us each in bf16 pieces of more than 128 rows, 0.79 below; FP8 0.61 in pieces of more than 64 rows, 0.44 below), by
+// the shares' unevenness (14 of 160 us for 8 requests of 1k to 16k with 32 to 128 nodes, 15 of 55 for 32 small ones over FP8, whose
+// time follows these weights within 5 %) and by the pieces: 7 to 8.6 us each beyond its tiles (finding it 1, page ids and first tiles 3, merging
+// and storing 3, waiting for the other waves 1), START and MARGIN come from that.  The figures beside the choice of the form
+// (short_batch) are the whole call's, before and after.
 constexpr int WHOLE = 3, PART = 2, START = 8 * WHOLE, MARGIN = 8, SMALL = 16;
 struct Stretch { int t, du, wt, sl, len; };             // tiles; whole stretches; weight of the last; length of the halved one; all
 __device__ __forceinline__ Stretch stretch_of(const AttnParams &p, const Req &q)

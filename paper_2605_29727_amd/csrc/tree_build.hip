@@ -1200,7 +1200,9 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         }
     }
     if (tid == 0) { RL.nsel = 0; RL.nslot = 0; }
-    // A row of so few marginals that all of them can be ranked needs no bound (4 x 64 of them, N = 16: 10.0 -> 8.0 us).
+    // A row of so few marginals that all of them can be ranked needs no bound (4 x 64 of them, N = 16: 10.4 us with one, 8.2 without; 4 x 96, N = 64:
+    // 13.1 and 11.1).  The line is where the ranking by counting ends here; it has lanes for 128 keys, and without the bound up to there 4 x 128 would take
+    // 7.9 for 9.4 us (N = 16).  Above, the ranking by bins needs the bound.
     const bool few = lge == 0 && V <= RANK_FEW;                // (uniform)
     if (!few) {
         for (int b = tid; b < (TBINS + TBINS / 16) / 4; b += 256) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
