@@ -1587,13 +1587,13 @@ __device__ __forceinline__ void merge_group(const AttnParams &p, MergeWords &m, 
         bool all = look(!together);
         if (!all) {
             const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
-            int limit = __builtin_amdgcn_ballot_w64(begun >> 8 != tag) ? min(p.wait_ticks, MERGE_START_TICKS) : p.wait_ticks;
+            int limit = min(p.wait_ticks, MERGE_START_TICKS);
             do {
                 if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > limit) {
-                    if (limit < p.wait_ticks) {         // have the others started by now?
-                        begun = __hip_atomic_load(&m.started[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (limit < p.wait_ticks) {         // have all started by now?
                         limit = p.wait_ticks;
-                        if (__builtin_amdgcn_ballot_w64(begun >> 8 != tag) == 0ull) continue;
+                        const u64 now = __hip_atomic_load(&m.started[peer], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (__builtin_amdgcn_ballot_w64(now >> 8 != tag) == 0ull) continue;
                     }
                     say(tag << 8 | 1);
                     all = look(true);
