@@ -50,6 +50,7 @@ struct AttnParams {
     int wait_ticks;               // ... how long a workgroup waits for the others of its group
     int M, L;                     // contiguous: actual sizes; paged: host upper bounds
     int Hq, Hkv, G;
+    int ginv;                     // ceil(2^16 / G): (x * ginv) >> 16 = x / G for every packed row x < 4096 (G <= 16)
     int max_blocks, num_blocks;
     int total_rows;               // rows of the partial buffers (>= total_M * Hq)
     int total_M;
@@ -751,16 +752,16 @@ struct WgLds {
     static constexpr int QBYTES = RW * QTILE;
     static constexpr int PRE_B = PREFILL * STAGE;
     static constexpr int QOFF = RING - QBYTES > PRE_B ? RING - QBYTES : PRE_B;
-    // parent[]: in a stage the prologue leaves free, else behind the query tiles; behind the ring for the pipelined
-    // shape, which reads it after the plain prefix tiles
-    static constexpr int PAROFF = KW == 1 ? (RING > QOFF + QBYTES ? RING : QOFF + QBYTES) : (QOFF - PRE_B >= 1024 ? PRE_B : QOFF + QBYTES);
-    static constexpr int USED = (PAROFF + 1024 > QOFF + QBYTES ? PAROFF + 1024 : QOFF + QBYTES) > RING
-                                    ? (PAROFF + 1024 > QOFF + QBYTES ? PAROFF + 1024 : QOFF + QBYTES) : RING;
+    // parent[] and the ancestor sets: in stages the prologue leaves free, else behind the query tiles; behind the ring for the
+    // pipelined shape, which reads the sets after the plain prefix tiles
+    static constexpr int PARENTS = BTV_MAX_NODES * 4, TREEB = PARENTS + BTV_MAX_NODES * BTV_ANC_WORDS * 4;
+    static constexpr int PAROFF = KW == 1 ? (RING > QOFF + QBYTES ? RING : QOFF + QBYTES) : (QOFF - PRE_B >= TREEB ? PRE_B : QOFF + QBYTES);
+    static constexpr int USED = (PAROFF + TREEB > QOFF + QBYTES ? PAROFF + TREEB : QOFF + QBYTES) > RING
+                                    ? (PAROFF + TREEB > QOFF + QBYTES ? PAROFF + TREEB : QOFF + QBYTES) : RING;
     static_assert(KW == 1 || KW == 2, "the merge is between two key-waves");
     static constexpr int MERGE = KW == 2 ? RW * 2 * ((D / 64) * 16 + 3) * 64 * 4 : 0;    // they exchange half a row each (+ m, l, bound)
     static constexpr int BYTES = USED > MERGE ? USED : MERGE;
     static_assert(QOFF % 1024 == 0 && PAROFF % 1024 == 0 && BYTES <= 160 * 1024, "LDS budget");
-    static_assert(BTV_MAX_NODES * 4 <= 1024, "parent[] staging");
 };
 
 // Wait until at most n (wave-uniform, clamped to [0, MAXN]) vector-memory operations are in flight.
@@ -778,14 +779,56 @@ template <int MAXN> __device__ __forceinline__ void wait_vm_ops(int n)
 // it is needed (mask construction, final store) rather than held in registers through the main loop.  Padding rows
 // (r >= rows_g) recompute row 0 and are never written.
 struct LaneRow { bool valid; int node; long long orow; };
-__device__ __forceinline__ LaneRow lane_row(int r, int rows_g, int G, int Hq, int g, int q0)
+__device__ __forceinline__ LaneRow lane_row(const AttnParams &p, int r, int rows_g, int g, int q0)
 {
     LaneRow x;
     x.valid = r < rows_g;
     const int rr = x.valid ? r : 0;
-    x.node = rr / G;
-    x.orow = (long long)(q0 + x.node) * Hq + g * G + (rr % G);       // row of Q/O as [total_M*Hq, D]
+    x.node = (rr * p.ginv) >> 16;
+    x.orow = (long long)(q0 + x.node) * p.Hq + g * p.G + (rr - x.node * p.G);       // row of Q/O as [total_M*Hq, D]
     return x;
+}
+
+// Ancestor sets of the request's nodes, set[i] = {i} u set[parent[i]], by the threads of the workgroup, one per node: a thread
+// takes over what its node's ancestor has found so far and goes on from where that one has got to, so that what it knows doubles from
+// turn to turn: log2 of the depth turns of some 200 cycles, where a walk along parent[] takes as many as the tree is deep (270 each; 2.8 us for a
+// random tree of 33 nodes in a workgroup that all others of its group wait for, 7 for one of 60 levels).  The wavefronts do not wait for
+// each other: a thread writes its set before the place to go on from, and reads the place before the set (the LDS operations of a wavefront are in
+// order), so what it takes is never less than the ancestors down to that place, whoever is ahead.  Every turn moves down: places strictly decrease.
+// par: parent[] as staged (entries are checked here), then the places; sets: BTV_ANC_WORDS words per node, the upper half only where
+// there are more than 128 nodes.  The sets may be read behind the next barrier.
+__device__ __forceinline__ void find_ancestors(const AttnParams &p, uint32_t par, uint32_t sets, int M, int tid)
+{
+    static_assert(BTV_ANC_WORDS == 8 && BTV_MAX_NODES <= 256, "two 16-byte pieces per set, a thread per node");
+    const bool mine = tid < M, big = M > 128;                    // (big: uniform)
+    const uint32_t pa = par + 4u * (uint32_t)tid, sa = sets + 32u * (uint32_t)tid;
+    int at = -1;
+    u32x4 lo, hi;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { lo[k] = tid >> 5 == k ? 1u << (tid & 31) : 0u; hi[k] = tid >> 5 == k + 4 ? 1u << (tid & 31) : 0u; }
+    if (mine) {
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(at) : "v"(pa) : "memory");
+        if (at < -1 || at >= tid) { atomicOr(p.flag, 1u); at = -1; }
+    }
+    auto put = [&]() {                                           // the set, then the place
+        if (big) asm volatile("ds_write_b128 %0, %1 offset:16" ::"v"(sa), "v"(hi) : "memory");
+        asm volatile("ds_write_b128 %0, %1\n\tds_write_b32 %2, %3" ::"v"(sa), "v"(lo), "v"(pa), "v"(at) : "memory");
+    };
+    if (mine) put();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                                // all entries are checked, all sets hold their node
+    while (at >= 0) {                                            // (a wavefront: while any of its lanes goes on)
+        const uint32_t pb = par + 4u * (uint32_t)at, sb = sets + 32u * (uint32_t)at;
+        int next;
+        u32x4 l2, h2 = { 0u, 0u, 0u, 0u };
+        if (big) asm volatile("ds_read_b32 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %4 offset:16\n\ts_waitcnt lgkmcnt(0)"
+                              : "=&v"(next), "=&v"(l2), "=&v"(h2) : "v"(pb), "v"(sb) : "memory");
+        else asm volatile("ds_read_b32 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(next), "=&v"(l2) : "v"(pb), "v"(sb) : "memory");
+        lo |= l2; hi |= h2;
+        at = next;
+        put();
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
 // Largest finite magnitude of a lane's values: what its row's partials are divided by.  (An infinite one, from a value in the
@@ -851,7 +894,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     const int st0 = pc_.st0;
     int st1 = pc_.st1;
     {   // tree rows past the last node of this row block are invisible to all of its rows: their tiles are dropped
-        const int node_hi = (min((by + 1) * WR, rows_g) - 1) / p.G;
+        const int node_hi = ((min((by + 1) * WR, rows_g) - 1) * p.ginv) >> 16;
         st1 = min(st1, max((Lr + node_hi + 1 + 31) / 32, st0 + 1));
     }
 
@@ -884,8 +927,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         const int j = kw * QPW + jj;
         const int qrow = j * QRPI + l / QCH, pc = l % QCH;
         const int rf = by * WR + rw * 32 + qrow;
-        const int rrf = rf < rows_g ? rf : 0;
-        const long long of = (long long)(rq_.q0 + rrf / p.G) * p.Hq + g * p.G + (rrf % p.G);
+        const long long of = lane_row(p, rf, rows_g, g, rq_.q0).orow;
         const unsigned char *src = static_cast<const unsigned char *>(p.Q) + of * (D * 2) + ((pc ^ swz_k<D, 2>(qrow)) << 4);
         // the destination must be wave-uniform: rw and kw are, but the compiler cannot know
         const int dst = __builtin_amdgcn_readfirstlane(WL::QOFF + rw * WL::QTILE + j * 1024);
@@ -929,12 +971,8 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     turn_window();
     begun();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
-    const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF;
-    auto par_at = [&](int i) {
-        int v;
-        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(par_lds + 4u * (uint32_t)i) : "memory");
-        return v;
-    };
+    const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF, sets_lds = par_lds + WL::PARENTS;
+    if (tree_wg) find_ancestors(p, par_lds, sets_lds, Mr, tid);
     // Operand s holds the 8 channels that contraction step s takes from this lane's half: 16 s + 8 h .. + 7 for
     // bf16 K, 32 (s/2) + 16 h + 8 (s%2) .. + 7 for FP8 K (the order of its 16-byte operand reads).
     u32x4 qv[DS];
@@ -950,30 +988,24 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     }
 
     // ---- ancestor bitmask of this lane's node, only in workgroups whose keys reach the tree rows ----------
-    // parent[] is checked (every entry, once per workgroup) and walked from its copy in LDS.
+    // Shapes whose waves alternate over the tiles keep the sets inside the ring and read theirs before the main loop; the pipelined
+    // shape keeps them behind the ring and reads them after the plain prefix tiles, so that they are not live through that loop.
     uint32_t anc_i[BTV_ANC_WORDS];
 #pragma unroll
     for (int k = 0; k < BTV_ANC_WORDS; ++k) anc_i[k] = 0u;
-    // Built where a shape needs it: shapes whose waves alternate over the tiles stage parent[] inside the ring and
-    // must read it before the main loop; the pipelined shape keeps it behind the ring and builds the masks after
-    // the plain prefix tiles, so that they are not live through that loop.
-#define BTV_BUILD_MASK()                                                                                              \
-    if (tree_wg) {                                                                                                    \
-        bool bad_ = false;                                                                                            \
-        for (int i_ = tid; i_ < Mr; i_ += WAVES * 64) {                                                               \
-            const int pa_ = par_at(i_);                                                                               \
-            bad_ = bad_ || pa_ < -1 || pa_ >= i_;                                                                     \
-        }                                                                                                             \
-        if (bad_) atomicOr(p.flag, 1u);                                                                               \
-        const LaneRow lr_ = lane_row(by * WR + rw * 32 + c, rows_g, p.G, p.Hq, g, rq_.q0);                            \
-        for (int a_ = lr_.node; a_ >= 0;) {                                                                           \
-            _Pragma("unroll") for (int k_ = 0; k_ < BTV_ANC_WORDS; ++k_)                                              \
-                if ((a_ >> 5) == k_) anc_i[k_] |= 1u << (a_ & 31);                                                    \
-            const int pa_ = par_at(a_);                                                                               \
-            a_ = (pa_ < -1 || pa_ >= a_) ? -1 : pa_; /* an invalid entry ends the walk (flagged above) */             \
-        }                                                                                                             \
+    auto read_mask = [&]() {
+        if (!tree_wg) return;
+        const uint32_t a = sets_lds + (uint32_t)lane_row(p, by * WR + rw * 32 + c, rows_g, g, rq_.q0).node * (BTV_ANC_WORDS * 4);
+        u32x4 lo, hi = { 0u, 0u, 0u, 0u };
+        if (Mr > 128) asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(a) : "memory");
+        else asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(lo) : "v"(a) : "memory");
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { anc_i[k] = lo[k]; anc_i[k + 4] = hi[k]; }
+    };
+    if constexpr (KW > 1) {
+        if (tree_wg) __builtin_amdgcn_s_barrier();               // every wave's sets are there
+        read_mask();
     }
-    if constexpr (KW > 1) { BTV_BUILD_MASK() }
 
     float m_run = NEG_BIG, l_run = 0.f;
     float base = 0.f;                 // what the step-by-step tiles' scores are relative to (rebase_tile)
@@ -1232,7 +1264,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
             for (int v = 0; v < 16; ++v) negb[v] = -m_run;
         }
-        BTV_BUILD_MASK()
+        read_mask();                                             // (barriers since the sets were written: those of the prologue)
         for (int j = j0; j < st1 - st0; ++j) {
             wait_tiles<LPW, NT - 1>(issued - st0 - j - 1);       // tile j has landed
             __builtin_amdgcn_s_barrier();                        // ... for every wave, and all are done with tile j-1
@@ -1273,7 +1305,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             if (cslot >= NT) cslot -= NT;
         }
     }
-    const LaneRow lrow = lane_row(by * WR + rw * 32 + c, rows_g, p.G, p.Hq, g, rq_.q0);
+    const LaneRow lrow = lane_row(p, by * WR + rw * 32 + c, rows_g, g, rq_.q0);
     const bool rvalid = lrow.valid;
     const long long orow = lrow.orow;
     // both halves of a wave hold partial row sums of the same queries
@@ -1386,7 +1418,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 // launch): about two microseconds before the first fill is issued.
 #define BTV_FETCH_ARGS(p)                                                                                                     \
     asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.block_table), "s"(p.q_offset),              \
-                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.sync), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), \
+                 "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.sync), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.ginv), \
                  "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.nsplit),          \
                  "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale))
 
@@ -1446,8 +1478,7 @@ template <int D, int WAVES> struct Share {
     }
     __device__ __forceinline__ void find(const AttnParams &p, const Piece &pc, int n, int wr, int tid)
     {
-        // (rr < 4096 and G <= 16: the product with ceil(2^16 / G) gives the quotient)
-        const int r = of + n * k, rr = pc.by * wr + r, node = (rr * ((65536 + p.G - 1) / p.G)) >> 16;
+        const int r = of + n * k, rr = pc.by * wr + r, node = (rr * p.ginv) >> 16;
         row = node * p.Hq + pc.g * p.G + (rr - node * p.G);
         ml = (min(tid & ((16 << lp) - 1), n - 1) * pc.pitch + r) * 16;
 #pragma unroll
@@ -2499,7 +2530,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     p.ML = reinterpret_cast<float *>(w8 + wl.ml);
     p.Opart = reinterpret_cast<_Float16 *>(w8 + wl.opart);
     p.flag = flag_out ? flag_out : reinterpret_cast<uint32_t *>(w8);
-    p.M = M; p.L = L; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv;
+    p.M = M; p.L = L; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv; p.ginv = (65536 + p.G - 1) / p.G;
     p.total_rows = M * Hq; p.total_M = M;
     p.sps = pl.sps; p.nsplit = pl.nsplit;
     set_scales(p, D, scale, k_scale, v_scale);
@@ -2560,7 +2591,7 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     p.flag = reinterpret_cast<uint32_t *>(w8);
     p.block_table = block_table; p.q_offset = q_offset; p.prefix_len = prefix_len;
     p.max_blocks = max_blocks; p.num_blocks = num_blocks;
-    p.M = M_max; p.L = L_max; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv;
+    p.M = M_max; p.L = L_max; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv; p.ginv = (65536 + p.G - 1) / p.G;
     p.total_rows = batch * M_max * Hq;    // partial buffers are sized for the bound; rows index by q_offset
     p.total_M = total_M;
     p.plan = reinterpret_cast<long long *>(w8 + wl.plan);

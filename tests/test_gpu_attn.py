@@ -128,6 +128,26 @@ def test_ancestor_mask_bit_exact(G, oracle):
             assert np.array_equal(anc.cpu().numpy().view(np.uint32), oracle.ancestor_mask(parent))
 
 
+@pytest.mark.parametrize("shape_id", [1, 2, 3])
+@pytest.mark.parametrize("M", [1, 31, 33, 64, 65, 128, 129, 255, 256])
+def test_bf16_every_node_sees_its_ancestors_alone(G, oracle, M, shape_id):
+    """Keys of zero give every visible row the same weight, and channel d of tree row a is 64 where a % 128 == d, 0 elsewhere:
+    O[i, d] is 64 times the number of ancestors a of i with a % 128 == d (0, 1 or 2), over L + the number of all of them.  The output is rounded
+    by 2^-9 of itself, a partial by 2^-10 of the row's largest value, which is at most twice as large."""
+    L, D = 5, 128
+    for kind in KINDS:
+        parent = synth.tree_parents(M + 1, M, kind)
+        rows = np.zeros((L + M, 1, D), dtype=np.float32)
+        rows[L + np.arange(M), 0, np.arange(M) % D] = 64.0
+        t = {"Q": np.full((M, 2, D), 0x3F80, dtype=np.uint16), "K": np.zeros((L + M, 1, D), dtype=np.uint16),
+             "V": (rows.view(np.uint32) >> 16).astype(np.uint16)}
+        anc = np.unpackbits(oracle.ancestor_mask(parent).view(np.uint8), axis=1, bitorder="little")[:, :M].astype(np.float64)
+        ref = anc @ rows[L:, 0] / (L + anc.sum(1, keepdims=True))
+        for ns in (1, 3):
+            out = G.run_verify_attn(t, parent, L, "bf16", nsplit=ns, shape=shape_id)
+            assert np.all(np.abs(out - ref[:, None]) <= 2 ** -7 * ref[:, None]), (kind, ns)
+
+
 def test_invalid_parent_is_flagged_not_faulting(G):
     import torch
     from paper_2605_29727_amd import binding as btv
