@@ -54,15 +54,26 @@ struct AttnParams {
     int max_blocks, num_blocks;
     int total_rows;               // rows of the partial buffers (>= total_M * Hq)
     int total_M;
-    int sps;                      // stages per split
-    int nsplit;                   // key splits of the longest request
+    int sps;                      // one request: whole tiles per split (`longer` of them take a round more); batch: tiles per part
+    int longer;
+    int nsplit;                   // key splits (batch: of the longest request)
     int row_blocks, units;        // row blocks per (split, head, request) unit; number of units
+    uint32_t inv_row_blocks, inv_nsplit, inv_sps, inv_Hkv;    // for quotient()
     long long *plan;              // batch only: [batch + 2], where the requests' work starts (see Stretch)
     int batch, teams_log2, pairing, wmin, wr_log2;   // batch only: requests, teams of workgroups, whether a team is a pair, smallest share, rows per block
     float scale;                  // softmax scale
     float scale_log2;             // scale * log2(e) (times the key scale of an FP8 cache)
     float out_scale;              // 1, or the value scale of an FP8 cache
 };
+
+// n / d for n >= 0, with inv = reciprocal(d).  (A division by a number that the compiler does not know takes some 30 instructions, and a workgroup
+// has three to five of them ahead of its first load.)
+__host__ constexpr uint32_t reciprocal(int d) { return d <= 1 ? 0u : (uint32_t)((0x100000000ull + (unsigned)d - 1) / (unsigned)d); }
+__device__ __forceinline__ int quotient(int n, int d, uint32_t inv)
+{
+    const int q = (int)__umulhi((uint32_t)n, inv);      // at most one too many
+    return d == 1 ? n : q - (q * d > n);
+}
 
 __device__ __forceinline__ uint32_t float_to_bf16_bits(float f)
 {   // round to nearest even; inputs here are finite
@@ -839,7 +850,8 @@ template <int B> __device__ __forceinline__ float finite_max(const f32x16 (&x)[B
 #pragma unroll
     for (int b = 0; b < B; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) a = fmaxf(a, fabsf(x[b][v]));
+        for (int v = 0; v < 16; v += 2)              // (fmaxf of fabsf's takes three instructions a value: each is made canonical first)
+            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(a) : "v"(x[b][v]), "v"(x[b][v + 1]));
     if (__builtin_amdgcn_ballot_w64(a > FLT_MAX) != 0ull) {        // (rare)
         a = 0.f;
 #pragma unroll
@@ -1419,8 +1431,8 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #define BTV_FETCH_ARGS(p)                                                                                                     \
     asm volatile("" ::"s"(p.Q), "s"(p.K), "s"(p.V), "s"(p.O), "s"(p.parent), "s"(p.block_table), "s"(p.q_offset),              \
                  "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.flag), "s"(p.sync), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.ginv), \
-                 "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.nsplit),          \
-                 "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale))
+                 "s"(p.max_blocks), "s"(p.num_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.sps), "s"(p.longer), "s"(p.nsplit), \
+                 "s"(p.inv_row_blocks), "s"(p.inv_nsplit), "s"(p.row_blocks), "s"(p.units), "s"(p.scale_log2), "s"(p.out_scale))
 
 // ---- the merge inside the attention kernel --------------------------------------------------------------------------------
 // A group = the workgroups whose partials belong to the same rows: the key splits of one (KV head, row block).  Where the
@@ -1665,28 +1677,27 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     Piece pc = {};
     if constexpr (!MERGE) {
-        const int unit = (slot / p.row_blocks) * 8 + xcd;
+        const int q = quotient(slot, p.row_blocks, p.inv_row_blocks), unit = q * 8 + xcd;
         if (unit >= p.units) return;
-        pc.by = slot % p.row_blocks; pc.g = unit / p.nsplit; pc.bx = unit % p.nsplit;
+        pc.by = slot - q * p.row_blocks; pc.g = quotient(unit, p.nsplit, p.inv_nsplit); pc.bx = unit - pc.g * p.nsplit;
     } else if (p.units == p.Hkv) {
-        const int q = slot / p.row_blocks;
-        pc.by = slot % p.row_blocks; pc.g = (q / p.nsplit) * 8 + xcd; pc.bx = q % p.nsplit;
+        const int q = quotient(slot, p.row_blocks, p.inv_row_blocks), u = quotient(q, p.nsplit, p.inv_nsplit);
+        pc.by = slot - q * p.row_blocks; pc.g = u * 8 + xcd; pc.bx = q - u * p.nsplit;
         if (pc.g >= p.Hkv) return;
     } else if (p.units) {
-        const int q = (slot / p.nsplit) * 8 + xcd;
-        pc.by = q % p.row_blocks; pc.g = q / p.row_blocks; pc.bx = slot % p.nsplit;
+        const int u = quotient(slot, p.nsplit, p.inv_nsplit), q = u * 8 + xcd;
+        pc.g = quotient(q, p.row_blocks, p.inv_row_blocks); pc.by = q - pc.g * p.row_blocks; pc.bx = slot - u * p.nsplit;
         if (pc.g >= p.Hkv) return;
     } else {
-        const int unit = (slot / p.row_blocks) * 8 + xcd;
-        pc.by = slot % p.row_blocks; pc.g = unit / p.nsplit; pc.bx = unit % p.nsplit;
+        const int q = quotient(slot, p.row_blocks, p.inv_row_blocks), unit = q * 8 + xcd;
+        pc.by = slot - q * p.row_blocks; pc.g = quotient(unit, p.nsplit, p.inv_nsplit); pc.bx = unit - pc.g * p.nsplit;
         if (pc.g >= p.Hkv) return;
     }
     const Req rq = load_req<false>(p, 0);
-    const int tiles = (rq.L + rq.M + 31) / 32, nsplit_r = (tiles + p.sps - 1) / p.sps;
-    if (pc.by * RW * 32 >= rq.M * p.G || pc.bx >= nsplit_r) return;
-    pc.st0 = pc.bx * p.sps;
-    pc.st1 = min(pc.st0 + p.sps, tiles);
-    pc.direct = nsplit_r == 1;
+    const int tiles = (rq.L + rq.M + 31) / 32;
+    pc.st0 = pc.bx * p.sps + KW * min(pc.bx, p.longer);
+    pc.st1 = min(pc.st0 + p.sps + (pc.bx < p.longer ? KW : 0), tiles);
+    pc.direct = p.nsplit == 1;
     pc.grouped = MERGE;
     pc.group = pc.g * p.row_blocks + pc.by;
     pc.pitch = min(RW * 32, rq.M * p.G) + 1;            // (rows of the same number lie in different channels)
@@ -1698,7 +1709,7 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_bf16(AttnParams p)
             if (threadIdx.x == 0)
                 __hip_atomic_store(&m->started[pc.bx], tag << 8 | this_xcd(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         });
-        merge_group<D, RW * KW, RW * 32>(p, *m, smem, threadIdx.x, pc, nsplit_r, tag);
+        merge_group<D, RW * KW, RW * 32>(p, *m, smem, threadIdx.x, pc, p.nsplit, tag);
     } else {
         attn_piece<D, RW, KW, NT, false, EB>(p, smem, threadIdx.x, rq, pc, [] {});
     }
@@ -1711,20 +1722,22 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     BTV_FETCH_ARGS(p);
+    asm volatile("" ::"s"(p.inv_sps), "s"(p.inv_Hkv));
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int by = slot % p.row_blocks, unit = (slot / p.row_blocks) * 8 + xcd;
+    const int uq = quotient(slot, p.row_blocks, p.inv_row_blocks), by = slot - uq * p.row_blocks, unit = uq * 8 + xcd;
     if (unit >= p.units) return;
     Piece pc = {};
     // The part is rotated by the (request, head) number.  Without it a number of parts that is a multiple of 8 ties part i
     // to XCD i % 8, and the requests with few parts load only the first XCDs.
-    const int bz = unit / p.nsplit;
-    pc.bx = (unit % p.nsplit + 3 * bz) % p.nsplit; pc.g = bz % p.Hkv; pc.rq = bz / p.Hkv; pc.by = by;
+    const int bz = quotient(unit, p.nsplit, p.inv_nsplit), turned = unit - bz * p.nsplit + 3 * bz;
+    pc.bx = turned - quotient(turned, p.nsplit, p.inv_nsplit) * p.nsplit;
+    pc.rq = quotient(bz, p.Hkv, p.inv_Hkv); pc.g = bz - pc.rq * p.Hkv; pc.by = by;
     const Req rq = load_req<true>(p, pc.rq);
     if (!rq.ok) {
         if (threadIdx.x == 0 && by == 0 && pc.bx == 0 && pc.g == 0) atomicOr(p.flag, 2u);
         return;
     }
-    const int tiles = (rq.L + rq.M + 31) >> 5, parts = (tiles + p.sps - 1) / p.sps;
+    const int tiles = (rq.L + rq.M + 31) >> 5, parts = quotient(tiles + p.sps - 1, p.sps, p.inv_sps);
     if (by * RW * 32 >= rq.M * p.G || pc.bx >= parts) return;
     pc.st0 = pc.bx * p.sps;
     pc.st1 = min(pc.st0 + p.sps, tiles);
@@ -2015,11 +2028,10 @@ __global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
 {
     __shared__ __attribute__((aligned(16))) float wsh[8][32];
     // every argument in one round trip (the argument block is cold in every launch)
-    asm volatile("" ::"s"(p.O), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.total_rows), "s"(p.sps), "s"(p.out_scale));
-    const int nsplit_r = ((p.L + p.M + TK - 1) / TK + p.sps - 1) / p.sps;
+    asm volatile("" ::"s"(p.O), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.total_rows), "s"(p.nsplit), "s"(p.out_scale));
     const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
     if (row >= p.M * p.Hq) return;
-    combine_row<D>(p, (size_t)row, nsplit_r, wsh);
+    combine_row<D>(p, (size_t)row, p.nsplit, wsh);
 }
 
 // The same for a batch: how many parts a row has follows from where its request's work lies (the plan that the attention's first
@@ -2251,7 +2263,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *p, int words)
 }
 
 constexpr int MOST_SPLITS = 64;                         // that the library chooses by itself
-struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, nsplit; float bytes; };      // (bytes of K and V)
+struct Plan { int rw, kw, nt, wr, row_blocks, stages, sps, longer, nsplit; float bytes; };      // (bytes of K and V)
 
 // Whether the workgroups of a plan merge their partials themselves (merge_group): few enough splits and groups for its words; all
 // groups' workgroups congruent mod 8, and as many on each XCD; and the chip takes all at once.  Where the KV heads do not share out
@@ -2271,18 +2283,17 @@ size_t partial_rows(const Plan &pl, int M, int Hq, int Hkv)
     return std::max<size_t>((size_t)M * Hq, (size_t)Hkv * pl.row_blocks * (std::min(pl.wr, M * (Hq / Hkv)) + 1));
 }
 
-// Splits of `want` parts for a shape.
+// Splits of `want` parts for a shape: whole rounds of KW tiles, as evenly as they go.
 void split_plan(Plan &pl, int L, int want)
 {
-    // Tiles that hold tree rows cost more than plain tiles (mask; in the pipelined loop also a second row maximum)
-    // and all sit in the last split: sizing the splits as if there were `extra` more tiles leaves the last one
-    // that much shorter.
-    const int tree_tiles = pl.stages - L / TK;
-    const int extra = pl.kw == 1 ? (7 * tree_tiles + 9) / 10 : (tree_tiles + 3) / 4;
-    want = std::max(1, std::min(want, pl.stages));
-    pl.sps = (pl.stages + (want > 1 ? extra : 0) + want - 1) / want;
-    pl.sps = (pl.sps + pl.kw - 1) / pl.kw * pl.kw;         // whole rounds of KW tiles
-    pl.nsplit = (pl.stages + pl.sps - 1) / pl.sps;
+    // The last split has the tree rows: its workgroups find the ancestor sets and mask tiles (in the pipelined loop those also lose
+    // the overlap).  Shared out as if there were `extra` more rounds at the end, it is that much shorter.
+    const int tree_tiles = pl.stages - L / TK, rounds = (pl.stages + pl.kw - 1) / pl.kw;
+    pl.nsplit = std::max(1, std::min(want, rounds));
+    const int extra = std::min(pl.kw == 1 ? 1 + (7 * tree_tiles + 9) / 10 : 2 + tree_tiles / 8, rounds / pl.nsplit - 1);
+    const int all = rounds + (pl.nsplit > 1 ? extra : 0);
+    pl.sps = all / pl.nsplit * pl.kw;
+    pl.longer = all % pl.nsplit;
 }
 
 // Shape of the workgroups (64, 128 or 256 packed rows of a KV head; 32 rows per wave, pairs of waves alternating over the
@@ -2321,7 +2332,7 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
             const int n = pl.nsplit, wgs = (n * Hkv + 7) / 8 * 8 * pl.row_blocks;         // (as many as the fullest XCD has, times 8)
             const float cap = k == 0 ? 512.f : 256.f, fill = wgs / cap;
             const float rounds = 0.31f * std::ceil(fill) + 0.69f * std::max(1.f, fill);
-            const float comp = rounds * (SHAPES[k].start + pl.sps * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]));
+            const float comp = rounds * (SHAPES[k].start + (pl.sps + (pl.longer ? pl.kw : 0)) * (k == 0 && wgs > 256 ? SHARED_TILE[kind] : SHAPES[k].tile[kind]));
             float t = std::max(comp, mem) + 0.123f * std::min(comp, mem);
             if (n > 1) t += merges_inside(pl, Hkv) ? 1.67f + 0.70f * n * part : 1.78f + 0.83f * n * part + 0.095f * std::max(0, n - 32);
             if (!best_t || t < best_t) { best = pl; best_t = t; }
@@ -2532,7 +2543,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
     p.flag = flag_out ? flag_out : reinterpret_cast<uint32_t *>(w8);
     p.M = M; p.L = L; p.Hq = Hq; p.Hkv = Hkv; p.G = Hq / Hkv; p.ginv = (65536 + p.G - 1) / p.G;
     p.total_rows = M * Hq; p.total_M = M;
-    p.sps = pl.sps; p.nsplit = pl.nsplit;
+    p.sps = pl.sps; p.longer = pl.longer; p.nsplit = pl.nsplit; p.inv_nsplit = reciprocal(pl.nsplit);
     set_scales(p, D, scale, k_scale, v_scale);
     p.parent = parent;
     if (dtype == BTV_F32) {
@@ -2541,7 +2552,7 @@ int attn_contiguous(const void *Q, const void *K, const void *V, const int32_t *
         BTV_HIP(hipGetLastError());
         return BTV_OK;
     }
-    p.row_blocks = pl.row_blocks;
+    p.row_blocks = pl.row_blocks; p.inv_row_blocks = reciprocal(pl.row_blocks);
     const bool inside = merge != 1 && merges_inside(pl, Hkv) && (merge || btv_usable_cus(st) >= 256);
     int wgs;
     if (inside) {
@@ -2598,9 +2609,9 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
     p.batch = batch; p.teams_log2 = pl.teams_log2; p.pairing = pl.pairing; p.wmin = pl.wmin; p.wr_log2 = pl.wr_log2;
     set_scales(p, D, scale, k_scale, v_scale);
     p.parent = parent;
-    p.sps = pl.sps; p.row_blocks = pl.row_blocks;
+    p.sps = pl.sps; p.row_blocks = pl.row_blocks; p.inv_row_blocks = reciprocal(pl.row_blocks);
     if (pl.sps) {
-        p.nsplit = pl.slots;
+        p.nsplit = pl.slots; p.inv_nsplit = reciprocal(pl.slots); p.inv_sps = reciprocal(pl.sps); p.inv_Hkv = reciprocal(Hkv);
         p.units = pl.slots * Hkv * batch;
         rc = dispatch_bf16<SHORT_BATCH>(p, pl.rw, D, eb, dim3(((p.units + 7) / 8) * pl.row_blocks * 8), st);
     } else {
