@@ -2290,7 +2290,7 @@ void split_plan(Plan &pl, int L, int want)
     // the overlap).  Shared out as if there were `extra` more rounds at the end, it is that much shorter.
     const int tree_tiles = pl.stages - L / TK, rounds = (pl.stages + pl.kw - 1) / pl.kw;
     pl.nsplit = std::max(1, std::min(want, rounds));
-    const int extra = std::min(pl.kw == 1 ? 1 + (7 * tree_tiles + 9) / 10 : 2 + tree_tiles / 8, rounds / pl.nsplit - 1);
+    const int extra = std::min(pl.kw == 1 ? (7 * tree_tiles + 9) / 10 : 1, rounds / pl.nsplit - 1);
     const int all = rounds + (pl.nsplit > 1 ? extra : 0);
     pl.sps = all / pl.nsplit * pl.kw;
     pl.longer = all % pl.nsplit;

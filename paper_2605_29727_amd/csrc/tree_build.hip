@@ -27,7 +27,7 @@ typedef unsigned long long u64;
 constexpr int MAXB = BTV_MAX_DEPTH;
 
 // A row is seen as slots of 2^lge marginals, one per thread and chunk of 256 << lge of them: the smallest lge that leaves at
-// most 16 chunks (the ranking workgroup keeps 16 slot records per thread in registers), 5 at most.  lge = 0, up to 4096
+// most 16 chunks (the ranking workgroup keeps 4 slot records per thread in registers), 5 at most.  lge = 0, up to 4096
 // marginals, needs no pass ahead of the ranking: every slot is one marginal, read where it is needed.  Slots of 32 for
 // every vocabulary left too few of them where it is small: 5000 marginals were 256 slots, and the best 256 tokens of a
 // row, which the slots' maxima are to bound, were looked for in the whole row (110 .. 217 us instead of 30).
@@ -79,12 +79,11 @@ __device__ __forceinline__ int wave_incl_scan(int x)
 // The ranked lists travel from the workgroups that rank to the one that expands through memory, within one launch and
 // between compute dies whose L2 caches do not see each other: they are written and read as relaxed device-scope
 // atomics, which go through to memory, and the writer waits for its stores before it counts itself as done.
-__device__ __forceinline__ void publish(float *q_row, uint32_t *tok_row, int r, float q, uint32_t tok)
+__device__ __forceinline__ void publish(u64 *top_row, int r, u64 key)        // probability bits << 32 | token
 {
-    __hip_atomic_store(q_row + r, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(tok_row + r, tok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(top_row + r, (key & 0xFFFFFFFF00000000ull) | (0xFFFFFFFFu - (uint32_t)key), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
+constexpr u64 NO_TOKEN = 0xFFFFFFFFull;      // the key of probability 0, token 0: what stands behind the K best of a list
 
 // ------------------------------------------------------------------------------------------------
 // Step 1: per-thread maxima.  Workgroup (chunk, row) scans the chunk's 256 << LGE elements of the row; thread t looks
@@ -124,6 +123,10 @@ __global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, i
     part[((size_t)row * chunks + chunk) * 256 + tid] = make_uint2(m1, (m2 & ~31u) | k1);
 }
 
+// The ranking workgroup: its chain of short steps is bound by the issue of instructions, so the 4096 slots of a position are 4 to a thread.  With 256
+// threads and 16 to a thread the whole call (16 positions x 128256 tokens, sigma 5) took 20.8 us for 64 nodes and 28.7 for 256, with 1024 19.0 and 27.1.
+constexpr int RANK_T = 1024, RANK_W = RANK_T / 64, PER = 4096 / RANK_T;
+
 constexpr int TBINS = 4096;
 
 // ------------------------------------------------------------------------------------------------
@@ -144,36 +147,28 @@ constexpr int TBINS = 4096;
 constexpr int SELCAP = 512;
 constexpr int SLOTCAP = 1024;
 
-__device__ __forceinline__ int bin_at(int b) { return b + (b >> 4); }
-
-// Element i of sixteen registers for a lane-dependent i, by halving.  The values arrive one by one and pass through an
-// empty asm, which hides from the compiler that they are the elements of one array: it would turn the selects into
-// an indexed load and move the array into scratch memory.
-__device__ __forceinline__ uint32_t pick16v(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4, uint32_t x5, uint32_t x6, uint32_t x7, uint32_t x8, uint32_t x9, uint32_t x10, uint32_t x11, uint32_t x12, uint32_t x13, uint32_t x14, uint32_t x15, int i)
+// One of four registers for a lane-dependent i.  The values pass through an empty asm one by one, which hides from the compiler that they are the
+// elements of one array: it would turn the selects into an indexed load and move the array into scratch memory.
+__device__ __forceinline__ uint32_t pick4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, int i)
 {
-    asm volatile("" : "+v"(x0)); asm volatile("" : "+v"(x1)); asm volatile("" : "+v"(x2)); asm volatile("" : "+v"(x3)); asm volatile("" : "+v"(x4)); asm volatile("" : "+v"(x5)); asm volatile("" : "+v"(x6)); asm volatile("" : "+v"(x7)); asm volatile("" : "+v"(x8)); asm volatile("" : "+v"(x9)); asm volatile("" : "+v"(x10)); asm volatile("" : "+v"(x11)); asm volatile("" : "+v"(x12)); asm volatile("" : "+v"(x13)); asm volatile("" : "+v"(x14)); asm volatile("" : "+v"(x15));
-    const uint32_t a0 = (i & 8) ? x8 : x0, a1 = (i & 8) ? x9 : x1, a2 = (i & 8) ? x10 : x2, a3 = (i & 8) ? x11 : x3;
-    const uint32_t a4 = (i & 8) ? x12 : x4, a5 = (i & 8) ? x13 : x5, a6 = (i & 8) ? x14 : x6, a7 = (i & 8) ? x15 : x7;
-    const uint32_t b0 = (i & 4) ? a4 : a0, b1 = (i & 4) ? a5 : a1, b2 = (i & 4) ? a6 : a2, b3 = (i & 4) ? a7 : a3;
-    const uint32_t c0 = (i & 2) ? b2 : b0, c1 = (i & 2) ? b3 : b1;
-    return (i & 1) ? c1 : c0;
+    asm volatile("" : "+v"(x0)); asm volatile("" : "+v"(x1)); asm volatile("" : "+v"(x2)); asm volatile("" : "+v"(x3));
+    const uint32_t a = (i & 2) ? x2 : x0, b = (i & 2) ? x3 : x1;
+    return (i & 1) ? b : a;
 }
-#define BTV_PICK16(x, i) pick16v(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7], x[8], x[9], x[10], x[11], x[12], x[13], x[14], x[15], i)
 
 struct alignas(16) RankLds {                // bound and ranking of one position
     union {
-        int bins[TBINS + TBINS / 16];       // histogram of the per-thread maxima (before the candidates exist); bin b at
-                                            // b + b / 16, so that a thread's 16 bins and its neighbours' fall into different banks
+        alignas(16) int bins[TBINS];        // histogram of the per-thread maxima (before the candidates exist)
         struct {
             alignas(16) u64 sel[SELCAP + 64];   // the candidates (+ a place per lane for the stores that store nothing)
             uint16_t slot[SLOTCAP + 64];        // slots (chunk * 256 + thread) whose maximum reaches the bound
         };
     };
     alignas(16) int first[2048];            // rank_keys_binned: RANK_BINS bins; SELCAP keys
-    int at[2048];
+    alignas(16) int at[2048];
     u64 sorted[SELCAP];
     int hist[256];
-    int wsum[4];
+    int wsum[RANK_W];
     int sel_bin;
     int nslot;
     int nsel;
@@ -229,68 +224,36 @@ struct Adaptive {                           // Algorithm 1's early stop (cost ==
     uint32_t *flag;
 };
 
-// sel[0..n): distinct keys; those of rank < K (rank = number of keys above) go to q_row / tok_row (global).
-// Threads tid, tid + nthreads, ... take one key each.
-__device__ __forceinline__ void rank_keys(const u64 *sel, int n, int K, int KP, float *q_row, uint32_t *tok_row, int tid, int nthreads)
-{
-    for (int i0 = 0; i0 < n; i0 += 2 * nthreads) {            // two keys per thread at a time
-        u64 mine[2];
-        int rank[2] = { 0, 0 };
-#pragma unroll
-        for (int c = 0; c < 2; ++c) mine[c] = i0 + c * nthreads + tid < n ? sel[i0 + c * nthreads + tid] : ~0ull;
-        for (int j = 0; j < n; ++j) {
-            const u64 kj = sel[j];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) rank[c] += kj > mine[c] ? 1 : 0;
-        }
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-            if (i0 + c * nthreads + tid < n && rank[c] < K) {
-                publish(q_row, tok_row, rank[c], __uint_as_float((uint32_t)(mine[c] >> 32)), 0xFFFFFFFFu - (uint32_t)mine[c]);
-            }
-    }
-    for (int i = K + tid; i < KP; i += nthreads) publish(q_row, tok_row, i, 0.f, 0u);
-}
-
-// The same for at most RANK_FEW keys on a workgroup of 256: a key belongs to T = 2 or 4 neighbouring lanes, which take
-// the list's pairs in turn (lane `part` reads pairs part, part + T, ...), two keys per LDS read and eight reads in
-// flight; the shares meet by quad swaps.  Every address is the trip's base plus a constant (a compare, a select and
+// sel[0 .. n): distinct keys; those of rank < K (rank = number of keys above) go to the position's list.  A key belongs to T
+// neighbouring lanes, which take the list's pairs in turn (lane `part` reads pairs part, part + T, ...), two keys per LDS read and U reads in
+// flight; the shares meet by moves within the row of 16 lanes.  Every address is the trip's base plus a constant (a compare, a select and
 // an address sum per read had been half of the loop's instructions), none of the reads is conditional (the compiler
-// would wait for each conditional read on its own), and they run past the end of the list into RANK_PAD zero keys,
-// which are above nothing.
-constexpr int RANK_PAD = 80;
-template <int T>
-__device__ __forceinline__ int rank_count(const ulonglong2 *two, int n, int part, u64 mine)
+// would wait for each conditional read on its own), and they run past the end of the list into zero keys, which are above nothing.
+template <int T, int U>
+__device__ __forceinline__ void rank_keys(u64 *sel, int n, int K, u64 *top_row, int tid)
 {
-    const int pairs = (n + 1) >> 1, per = (pairs + T - 1) / T;
-    const ulonglong2 *at = two + part;
+    static_assert(T <= 16, "a key's lanes are of one row");
+    const int i = tid / T, part = tid % T, trips = (n + 2 * T * U - 1) / (2 * T * U);      // (uniform)
+    if (n + tid < trips * 2 * T * U) sel[n + tid] = 0ull;
+    __syncthreads();
+    const u64 mine = sel[min(i, n - 1)];
+    const ulonglong2 *at = reinterpret_cast<const ulonglong2 *>(sel) + part;
     int cnt = 0;
-    for (int r = 0; r < per; r += 8, at += 8 * T) {            // (uniform)
-        ulonglong2 kk[8];
+    for (int r = 0; r < trips; ++r, at += U * T) {
+        ulonglong2 kk[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) kk[u] = at[u * T];
+        for (int u = 0; u < U; ++u) kk[u] = at[u * T];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             cnt += kk[u].x > mine ? 1 : 0;
             cnt += kk[u].y > mine ? 1 : 0;
         }
     }
-    return cnt;
-}
-
-__device__ __forceinline__ void rank_keys_split(u64 *sel, int n, int K, int KP, float *q_row, uint32_t *tok_row, int tid)
-{
-    const int lgT = n <= 64 ? 2 : 1, T = 1 << lgT;
-    const int i = tid >> lgT, part = tid & (T - 1);
-    if (tid < RANK_PAD) sel[n + tid] = 0ull;                   // n <= RANK_FEW of the list's 512 places are taken
-    __syncthreads();
-    const u64 mine = sel[min(i, n)];
-    const ulonglong2 *two = reinterpret_cast<const ulonglong2 *>(sel);
-    int cnt = lgT == 2 ? rank_count<4>(two, n, part, mine) : rank_count<2>(two, n, part, mine);
-    cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
-    if (T == 4) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
-    if (part == 0 && i < n && cnt < K) publish(q_row, tok_row, cnt, __uint_as_float((uint32_t)(mine >> 32)), 0xFFFFFFFFu - (uint32_t)mine);
-    for (int e = K + tid; e < KP; e += 256) publish(q_row, tok_row, e, 0.f, 0u);
+    if (T >= 2) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);     // quad_perm [1,0,3,2]
+    if (T >= 4) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);     // quad_perm [2,3,0,1]
+    if (T >= 8) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x141, 0xF, 0xF, false);    // row_half_mirror
+    if (T >= 16) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x140, 0xF, 0xF, false);   // row_mirror
+    if (part == 0 && i < n && cnt < K) publish(top_row, cnt, mine);
 }
 
 // How many of keys[lo .. hi - 1] are above `mine`: eight reads in flight.
@@ -307,40 +270,37 @@ __device__ __forceinline__ int count_above(const u64 *keys, int lo, int hi, u64 
     return n;
 }
 
-// More than RANK_FEW keys: into bins of a 64th of a binade above the bound (a key's bin falls as its probability does), an
-// exclusive sum of the bins from the top gives their first ranks, and a key is counted only against those of its bin.  What it takes
-// is six barriers: 256 keys of a confident drafter 1.6 us, comparing each with all of them 4.6.
-constexpr int RANK_FEW = 96, RANK_BINS = 2048, RANK_SHIFT = 17;
-__device__ __forceinline__ void rank_keys_binned(const u64 *sel, u64 *sorted, int *first, int *at, int *wsum, uint32_t tau, int n, int K, int KP, float *q_row,
-                                                 uint32_t *tok_row, int tid, int lane, int w)
+// More keys: into bins of a 64th of a binade above the bound (a key's bin falls as its probability does), an
+// exclusive sum of the bins from the top gives their first ranks, and a key is counted only against those of its bin: six barriers
+// instead of n^2 comparisons (the whole call with 256 nodes, a confident drafter: 27.8 us by counting, 26.3 by bins).
+constexpr int RANK_FEW = 256;               // vocabularies up to this size are ranked whole
+constexpr int RANK_BINS = 2048, RANK_SHIFT = 17;
+__device__ __forceinline__ void rank_keys_binned(const u64 *sel, u64 *sorted, int *first, int *at, int *wsum, uint32_t tau, int n, int K, u64 *top_row, int tid,
+                                                 int lane, int w)
 {
-    auto bin_of = [&](u64 k) { return min((int)(((uint32_t)(k >> 32) - tau) >> RANK_SHIFT), RANK_BINS - 1); };
-#pragma unroll
-    for (int i = 0; i < RANK_BINS / 1024; ++i) reinterpret_cast<int4 *>(first)[i * 256 + tid] = make_int4(0, 0, 0, 0);
+    static_assert(RANK_BINS == 2 * RANK_T && SELCAP <= RANK_T, "two bins and at most one key per thread");
+    const u64 key = sel[min(tid, n - 1)];
+    const int bin = min((int)(((uint32_t)(key >> 32) - tau) >> RANK_SHIFT), RANK_BINS - 1);
+    reinterpret_cast<int2 *>(first)[tid] = make_int2(0, 0);
     __syncthreads();
-    for (int i = tid; i < n; i += 256) atomicAdd(&first[bin_of(sel[i])], 1);
+    if (tid < n) atomicAdd(&first[bin], 1);
     __syncthreads();
-    {                                                          // thread t: bins 8 t .. 8 t + 7
-        const int4 x = reinterpret_cast<const int4 *>(first)[2 * tid], y = reinterpret_cast<const int4 *>(first)[2 * tid + 1];
-        const int s7 = y.w, s6 = s7 + y.z, s5 = s6 + y.y, s4 = s5 + y.x, s3 = s4 + x.w, s2 = s3 + x.z, s1 = s2 + x.y, own = s1 + x.x;
-        const int incl = wave_incl_scan(own), total = __builtin_amdgcn_readlane(incl, 63);
+    {                                                          // thread t: bins 2 t and 2 t + 1
+        const int2 x = reinterpret_cast<const int2 *>(first)[tid];
+        const int own = x.x + x.y, incl = wave_incl_scan(own), total = __builtin_amdgcn_readlane(incl, 63);
         if (lane == 0) wsum[w] = total;
         __syncthreads();
-        const int up = total - incl + (w < 1 ? wsum[1] : 0) + (w < 2 ? wsum[2] : 0) + (w < 3 ? wsum[3] : 0);
-        const int4 p = make_int4(up + s1, up + s2, up + s3, up + s4), q = make_int4(up + s5, up + s6, up + s7, up);
-        reinterpret_cast<int4 *>(first)[2 * tid] = p; reinterpret_cast<int4 *>(first)[2 * tid + 1] = q;
-        reinterpret_cast<int4 *>(at)[2 * tid] = p; reinterpret_cast<int4 *>(at)[2 * tid + 1] = q;
+        const int others = wave_incl_scan(lane < RANK_W && lane > w ? wsum[lane & (RANK_W - 1)] : 0);
+        const int up = total - incl + __builtin_amdgcn_readlane(others, RANK_W - 1);
+        reinterpret_cast<int2 *>(first)[tid] = reinterpret_cast<int2 *>(at)[tid] = make_int2(up + x.y, up);
     }
     __syncthreads();
-    for (int i = tid; i < n; i += 256) sorted[atomicAdd(&at[bin_of(sel[i])], 1)] = sel[i];
+    if (tid < n) sorted[atomicAdd(&at[bin], 1)] = key;
     __syncthreads();
-    for (int i = tid; i < n; i += 256) {
-        const u64 mine = sorted[i];
-        const int b = bin_of(mine), hi = at[b];
-        const int lo = first[b], rank = lo + count_above(sorted, lo, hi, mine);
-        if (rank < K) publish(q_row, tok_row, rank, __uint_as_float((uint32_t)(mine >> 32)), 0xFFFFFFFFu - (uint32_t)mine);
+    if (tid < n) {
+        const int lo = first[bin], rank = lo + count_above(sorted, lo, at[bin], key);
+        if (rank < K) publish(top_row, rank, key);
     }
-    for (int e = K + tid; e < KP; e += 256) publish(q_row, tok_row, e, 0.f, 0u);
 }
 
 template <typename ForEach>
@@ -386,8 +346,7 @@ __device__ __forceinline__ u64 wave_kth_largest(ForEach for_each, int K, int *hi
 }
 
 template <typename ForEach>
-__device__ __forceinline__ void wave_select_rank(ForEach for_each, int K, int KP, int *hist, u64 *sel, int *nsel, float *q_row,
-                                                 uint32_t *tok_row, int lane)
+__device__ __forceinline__ void wave_select(ForEach for_each, int K, int *hist, u64 *sel, int *nsel, int lane)
 {
     const u64 kth = wave_kth_largest(for_each, K, hist, lane);
     if (lane == 0) *nsel = 0;
@@ -398,8 +357,6 @@ __device__ __forceinline__ void wave_select_rank(ForEach for_each, int K, int KP
             if (pos < SELCAP) sel[pos] = key;                  // exactly K keys: they are distinct
         }
     });
-    __builtin_amdgcn_wave_barrier();
-    rank_keys(sel, K, K, KP, q_row, tok_row, lane, 64);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1154,11 +1111,50 @@ __device__ __forceinline__ void beam_block(const ExpandLds &S, BeamLds &Bm, int 
     }
 }
 
-__global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, int B, int K, int KP, int N, int chunks, int lge,
-                                                      TbCounters *ctr, const uint2 *part, float *top_q, uint32_t *top_tok,
-                                                      int32_t *parent,
+// All positions of a request with few marginals, by one workgroup: no list goes through memory, and nobody counts workgroups in.
+// solo: log2 of the keys that a position has room for, and log2 of the lanes that share a key << 8.
+__device__ __forceinline__ void rank_alone(ExpandLds &S, u64 *keys, const float *marg, int V, int B, int K, int KP, int solo, int tid)
+{
+    const int lgv = solo & 255, lgt = (solo >> 8) & 255, Vp = 1 << lgv, T = 1 << lgt;
+    {
+        const int pos = tid >> lgv, v = tid & (Vp - 1);
+        const bool in = pos < B && v < V;
+        const u64 key = make_key(marg[in ? (size_t)pos * V + v : 0], (uint32_t)v);
+        keys[tid] = in ? key : 0ull;                           // (a key of zero is above nothing)
+    }
+    for (int e = tid; e < B * KP; e += RANK_T)
+        if ((e & (KP - 1)) >= K) { S.q[e] = 0.f; S.tok[e] = 0u; }
+    __syncthreads();
+    const int pos = tid >> (lgv + lgt), v = (tid >> lgt) & (Vp - 1), part = tid & (T - 1);
+    const u64 mine = keys[(pos << lgv) + v];
+    const ulonglong2 *at = reinterpret_cast<const ulonglong2 *>(keys + (pos << lgv)) + part;
+    int cnt = 0;
+    for (int r = 0; r < 1 << (lgv - lgt - 1); r += 8, at += 8 * T) {         // (uniform; a lane has 8 pairs or more)
+        ulonglong2 kk[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) kk[u] = at[u * T];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            cnt += kk[u].x > mine ? 1 : 0;
+            cnt += kk[u].y > mine ? 1 : 0;
+        }
+    }
+    if (T >= 2) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);     // quad_perm [1,0,3,2]
+    if (T >= 4) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);     // quad_perm [2,3,0,1]
+    if (T >= 8) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x141, 0xF, 0xF, false);    // row_half_mirror
+    if (T >= 16) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x140, 0xF, 0xF, false);   // row_mirror
+    if (part == 0 && pos < B && v < V && cnt < K) {
+        S.q[pos * KP + cnt] = __uint_as_float((uint32_t)(mine >> 32));
+        S.tok[pos * KP + cnt] = 0xFFFFFFFFu - (uint32_t)mine;
+    }
+}
+
+// SOLO: a workgroup takes all positions of a request (solo_plan; a kernel of its own: in one with the other the others took 0.2 us longer).
+template <bool SOLO>
+__global__ __launch_bounds__(RANK_T) void tb_rank_expand(const float *marg, int V, int B, int K, int KP, int N, int chunks, int lge,
+                                                      TbCounters *ctr, const uint2 *part, u64 *top, int32_t *parent,
                                                       int32_t *token, int32_t *depth, float *rho, int32_t *n_out, float *ahat,
-                                                      Adaptive ad, int beam_width, Batch bt, int algo)
+                                                      Adaptive ad, int beam_width, Batch bt, int algo, int solo)
 {
     __shared__ union RankOrLevels { RankLds rank; SweepLds lev; } U;     // the ranking is over when the expansion starts
     __shared__ ExpandLds S;
@@ -1167,67 +1163,51 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     RankLds &RL = U.rank;
     // Fetch every argument in one round trip: left to the compiler the scalar loads follow the code in four
     // dependent steps over an argument block of several cache lines that is cold in every launch.
-    asm volatile("" ::"s"(marg), "s"(V), "s"(B), "s"(K), "s"(KP), "s"(N), "s"(chunks), "s"(lge), "s"(ctr), "s"(part), "s"(top_q),
-                 "s"(top_tok), "s"(parent), "s"(token), "s"(depth), "s"(rho), "s"(n_out), "s"(ahat), "s"(ad.cost), "s"(ad.L_AR),
-                 "s"(ad.s_best), "s"(ad.flag), "s"(beam_width), "s"(bt.n_nodes), "s"(bt.q_offset), "s"(bt.flag));
+    asm volatile("" ::"s"(marg), "s"(V), "s"(B), "s"(K), "s"(KP), "s"(N), "s"(chunks), "s"(lge), "s"(ctr), "s"(part), "s"(top),
+                 "s"(parent), "s"(token), "s"(depth), "s"(rho), "s"(n_out), "s"(ahat), "s"(ad.cost), "s"(ad.L_AR),
+                 "s"(ad.s_best), "s"(ad.flag), "s"(beam_width), "s"(bt.n_nodes), "s"(bt.q_offset), "s"(bt.flag), "s"(solo));
     // Workgroup `row` = position row % B of request row / B; marginals, per-thread maxima and top lists are laid out
     // request after request, outputs start at the request's q_offset.
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), row = blockIdx.x;
-    const int req = row / B;
-    float *q_row = top_q + (size_t)row * KP;
-    uint32_t *tok_row = top_tok + (size_t)row * KP;
+    const int req = SOLO ? row : row / B;
+    double cost_mine = 1.0;
+    if constexpr (SOLO) {                      // the whole request by this workgroup (see solo_plan)
+        rank_alone(S, reinterpret_cast<u64 *>(RL.bins), marg + (size_t)req * B * V, V, B, K, KP, solo, tid);
+        if (ad.cost && tid < N) cost_mine = ad.cost[tid];
+    } else {
+    u64 *top_row = top + (size_t)row * KP;
     const float *src = marg + (size_t)row * V;
     const bool aligned = (((size_t)row * V) & 3) == 0 && (reinterpret_cast<uintptr_t>(marg) & 15) == 0;
-    const uint2 *pr = part + (size_t)row * chunks * 256 + tid;
+    const int slots = lge == 0 ? V : chunks * 256;             // slot e: chunk e / 256, thread e % 256 of the scan (or marginal e)
+    const uint2 *pr = part + (size_t)row * chunks * 256;
     // ---- the bound: K-th largest per-thread maximum of the row, down to the lower edge of its histogram bin ---
-    uint32_t pv[16], pw[16];                                   // the loads are in flight while the histogram is cleared
-    uint32_t live = 0u;                                        // bit j: this thread has a slot in chunk j
-    if (lge == 0) {                                            // every marginal is a slot of its own (chunks <= 16)
+    uint32_t pv[PER], pw[PER];                                 // the loads are in flight while the histogram is cleared
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int v = j * 256 + tid;
-            pv[j] = prob_bits(src[v < V ? v : 0]);
-            pw[j] = 0u;
-            live |= v < V ? 1u << j : 0u;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint2 x = pr[(size_t)(j < chunks ? j : 0) * 256];      // no load behind a branch: all of them in flight at once
-            pv[j] = x.x;
-            pw[j] = x.y;
-            live |= j < chunks ? 1u << j : 0u;
-        }
+    for (int j = 0; j < PER; ++j) {                            // no load behind a branch: all of them in flight at once
+        const int e = j * RANK_T + tid, at = e < slots ? e : 0;
+        if (lge == 0) { pv[j] = prob_bits(src[at]); pw[j] = 0u; }
+        else { const uint2 x = pr[at]; pv[j] = x.x; pw[j] = x.y; }
     }
     if (tid == 0) { RL.nsel = 0; RL.nslot = 0; }
-    // A row of so few marginals that all of them can be ranked needs no bound (4 x 64 of them, N = 16: 10.4 us with one, 8.2 without; 4 x 96, N = 64:
-    // 13.1 and 11.1).  The line is where the ranking by counting ends here; it has lanes for 128 keys, and without the bound up to there 4 x 128 would take
-    // 7.9 for 9.4 us (N = 16).  Above, the ranking by bins needs the bound.
-    const bool few = lge == 0 && V <= RANK_FEW;                // (uniform)
+    // A row of so few marginals that all of them can be ranked needs no bound.
+    const bool few = V <= RANK_FEW;                            // (uniform)
     if (!few) {
-        for (int b = tid; b < (TBINS + TBINS / 16) / 4; b += 256) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
+        for (int b = tid; b < TBINS / 4; b += RANK_T) reinterpret_cast<int4 *>(RL.bins)[b] = make_int4(0, 0, 0, 0);
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 16; ++j) if ((live >> j) & 1u) atomicAdd(&RL.bins[bin_at((int)(pv[j] >> 19))], 1);
-        for (int j = 16; j < chunks; ++j) atomicAdd(&RL.bins[bin_at((int)(pr[(size_t)j * 256].x >> 19))], 1);
+        for (int j = 0; j < PER; ++j) if (j * RANK_T + tid < slots) atomicAdd(&RL.bins[(int)(pv[j] >> 19)], 1);
+        for (int e = PER * RANK_T + tid; e < slots; e += RANK_T) atomicAdd(&RL.bins[(int)(pr[e].x >> 19)], 1);
         __syncthreads();
         {
-            int hb[16], own = 0;                                   // thread t owns bins 16t .. 16t+15
-#pragma unroll
-            for (int b = 0; b < 16; ++b) { hb[b] = RL.bins[tid * 17 + b]; own += hb[b]; }
-            const int incl = wave_incl_scan(own), wtot = __builtin_amdgcn_readlane(incl, 63);
+            const int4 hb = reinterpret_cast<const int4 *>(RL.bins)[tid];                  // thread t owns bins 4 t .. 4 t + 3
+            const int own = hb.x + hb.y + hb.z + hb.w, incl = wave_incl_scan(own), wtot = __builtin_amdgcn_readlane(incl, 63);
             if (lane == 0) RL.wsum[w] = wtot;
             __syncthreads();
-            int above = wtot - incl;                               // in the bins of the higher threads
-            for (int ww = w + 1; ww < 4; ++ww) above += RL.wsum[ww];
+            const int others = wave_incl_scan(lane < RANK_W && lane > w ? RL.wsum[lane & (RANK_W - 1)] : 0);
+            const int above = wtot - incl + __builtin_amdgcn_readlane(others, RANK_W - 1);  // in the bins of the higher threads
             if (above < K && above + own >= K) {
-                int cum = above, sel = tid * 16;
-#pragma unroll
-                for (int b = 15; b >= 0; --b) {
-                    if (cum < K && cum + hb[b] >= K) sel = tid * 16 + b;
-                    cum += hb[b];
-                }
-                RL.sel_bin = sel;
+                const int s3 = above + hb.w, s2 = s3 + hb.z, s1 = s2 + hb.y;
+                RL.sel_bin = tid * 4 + (s3 >= K ? 3 : s2 >= K ? 2 : s1 >= K ? 1 : 0);
             }
             __syncthreads();                                       // the histogram is dead from here on: sel[] takes its place
         }
@@ -1236,7 +1216,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     // ---- the candidates.  A slot whose maximum reaches the bound holds a candidate; when its second largest stays
     // below the bound, which is the rule (K of thousands of slots are taken), that maximum is the slot's only one
     // and goes to the list as it stands, with the token id that its place in the slot gives.  The other slots
-    // are listed and read again, one 16-byte piece of a slot per thread and four pieces in flight per thread.
+    // are listed and read again, one 16-byte piece of a slot per thread.
     // Places in the lists are handed out per wavefront: every lane counts what it has, a scan places the lanes,
     // one lane takes the wavefront's range from the shared counter (one LDS round trip, not one per entry).
     // A lane rarely holds more than one entry: it keeps its entries as a bit mask and the wavefront loops until
@@ -1255,37 +1235,43 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         if (tid < V) RL.sel[tid] = ((u64)pv[0] << 32) | (u64)(0xFFFFFFFFu - (uint32_t)tid);
         if (tid == 0) RL.nsel = V;
     } else {
-        uint32_t one = 0u, more = 0u;                           // chunks whose slot holds one candidate / maybe several
+        uint32_t one = 0u, more = 0u;                           // records whose slot holds one candidate / maybe several
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (((live >> j) & 1u) && pv[j] >= tau) {
+        for (int j = 0; j < PER; ++j)
+            if (j * RANK_T + tid < slots && pv[j] >= tau) {
                 if (pw[j] >= tau && lge != 0) more |= 1u << j; else one |= 1u << j;
             }
-        int pos = wave_range(__builtin_popcount(one), &RL.nsel);
-        while (__builtin_amdgcn_ballot_w64(one != 0u) != 0ull) {
-            const bool has = one != 0u;
-            const int j = has ? __builtin_ctz(one) : 0;
-            const uint32_t k = BTV_PICK16(pw, j) & 31u;
-            const uint32_t v = (uint32_t)slot_first(lge, j, tid) + (k >> 2) * 1024u + (k & 3u);
-            RL.sel[has && pos < SELCAP ? pos : SELCAP + lane] = ((u64)BTV_PICK16(pv, j) << 32) | (u64)(0xFFFFFFFFu - v);
-            pos += has ? 1 : 0;
-            one &= one - 1u;
+        if (__builtin_amdgcn_ballot_w64(one != 0u) != 0ull) {
+            int pos = wave_range(__builtin_popcount(one), &RL.nsel);
+            do {
+                const bool has = one != 0u;
+                const int j = has ? __builtin_ctz(one) : 0, e = j * RANK_T + tid;
+                const uint32_t k = pick4(pw[0], pw[1], pw[2], pw[3], j) & 31u;
+                const uint32_t v = (uint32_t)slot_first(lge, e >> 8, e & 255) + (k >> 2) * 1024u + (k & 3u);
+                RL.sel[has && pos < SELCAP ? pos : SELCAP + lane] = ((u64)pick4(pv[0], pv[1], pv[2], pv[3], j) << 32) | (u64)(0xFFFFFFFFu - v);
+                pos += has ? 1 : 0;
+                one &= one - 1u;
+            } while (__builtin_amdgcn_ballot_w64(one != 0u) != 0ull);
         }
         int mine = __builtin_popcount(more);
-        for (int j = 16; j < chunks && j < 256; ++j) mine += pr[(size_t)j * 256].x >= tau ? 1 : 0;
-        pos = wave_range(mine, &RL.nslot);
-        while (__builtin_amdgcn_ballot_w64(more != 0u) != 0ull) {
-            const bool has = more != 0u;
-            const int j = has ? __builtin_ctz(more) : 0;
-            RL.slot[has && pos < SLOTCAP ? pos : SLOTCAP + lane] = (uint16_t)(j * 256 + tid);
-            pos += has ? 1 : 0;
-            more &= more - 1u;
-        }
-        for (int j = 16; j < chunks && j < 256; ++j)
-            if (pr[(size_t)j * 256].x >= tau) {
-                if (pos < SLOTCAP) RL.slot[pos] = (uint16_t)(j * 256 + tid);
-                ++pos;
+        if (chunks <= 256)                                      // (a place of the list takes 16 bits)
+            for (int e = PER * RANK_T + tid; e < slots; e += RANK_T) mine += pr[e].x >= tau ? 1 : 0;
+        if (__builtin_amdgcn_ballot_w64(mine != 0) != 0ull) {
+            int pos = wave_range(mine, &RL.nslot);
+            while (__builtin_amdgcn_ballot_w64(more != 0u) != 0ull) {
+                const bool has = more != 0u;
+                const int j = has ? __builtin_ctz(more) : 0;
+                RL.slot[has && pos < SLOTCAP ? pos : SLOTCAP + lane] = (uint16_t)(j * RANK_T + tid);
+                pos += has ? 1 : 0;
+                more &= more - 1u;
             }
+            if (chunks <= 256)
+                for (int e = PER * RANK_T + tid; e < slots; e += RANK_T)
+                    if (pr[e].x >= tau) {
+                        if (pos < SLOTCAP) RL.slot[pos] = (uint16_t)e;
+                        ++pos;
+                    }
+        }
     }
     __syncthreads();
     const int nslot = RL.nslot;
@@ -1295,62 +1281,28 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         const int lgp = lge - 2, pmask = (1 << lgp) - 1;       // 16-byte pieces per slot (lge >= 2 here)
         const int total = nslot << lgp;
         const bool whole = aligned && (V & 3) == 0;            // every piece that starts inside the row ends inside it
-        for (int base = 0; base < total; base += 4 * 256) {
-            float pe[16];
-            int v0[4];
-            uint32_t ok = 0u;                                   // bit 4u + e: element e of piece u is a candidate
-            if (whole) {                                        // no load depends on a branch: four in flight at once
-                int sl[4];
+        for (int base = 0; base < total; base += RANK_T) {
+            const int i = base + tid, sl = RL.slot[(i < total ? i : 0) >> lgp];
+            const int v = slot_first(lge, sl >> 8, sl & 255) + (i & pmask) * 1024, v0 = i < total && v < V ? v : -1;
+            float pe[4] = { 0.f, 0.f, 0.f, 0.f };
+            uint32_t ok = 0u;                                   // bit e: element e of the piece is a candidate
+            if (whole) {
+                const float4 a = *reinterpret_cast<const float4 *>(src + (v0 < 0 ? 0 : v0));
+                pe[0] = a.x; pe[1] = a.y; pe[2] = a.z; pe[3] = a.w;
+            } else if (v0 >= 0) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = base + u * 256 + tid;
-                    sl[u] = RL.slot[(i < total ? i : 0) >> lgp];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = base + u * 256 + tid;
-                    v0[u] = slot_first(lge, sl[u] >> 8, sl[u] & 255) + (i & pmask) * 1024;
-                    if (i >= total || v0[u] >= V) v0[u] = -1;
-                    const float4 a = *reinterpret_cast<const float4 *>(src + (v0[u] < 0 ? 0 : v0[u]));
-                    pe[4 * u] = a.x; pe[4 * u + 1] = a.y; pe[4 * u + 2] = a.z; pe[4 * u + 3] = a.w;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (v0[u] >= 0 && prob_bits(pe[4 * u + e]) >= tau) ok |= 1u << (4 * u + e);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = base + u * 256 + tid;
-                    v0[u] = -1;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) pe[4 * u + e] = 0.f;
-                    if (i < total) {
-                        const int sl = RL.slot[i >> lgp];
-                        v0[u] = slot_first(lge, sl >> 8, sl & 255) + (i & pmask) * 1024;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (v0[u] + e < V) {
-                                pe[4 * u + e] = src[v0[u] + e];
-                                if (prob_bits(pe[4 * u + e]) >= tau) ok |= 1u << (4 * u + e);
-                            }
-                    }
-                }
+                for (int e = 0; e < 4; ++e) pe[e] = src[min(v0 + e, V - 1)];
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (v0 >= 0 && v0 + e < V && prob_bits(pe[e]) >= tau) ok |= 1u << e;
+            if (__builtin_amdgcn_ballot_w64(ok != 0u) == 0ull) continue;
             int pos = wave_range(__builtin_popcount(ok), &RL.nsel);
             while (__builtin_amdgcn_ballot_w64(ok != 0u) != 0ull) {
                 const bool has = ok != 0u;
-                const int bit = has ? __builtin_ctz(ok) : 0;
-                const float pq = __uint_as_float(pick16v(__float_as_uint(pe[0]), __float_as_uint(pe[1]), __float_as_uint(pe[2]),
-                    __float_as_uint(pe[3]), __float_as_uint(pe[4]), __float_as_uint(pe[5]), __float_as_uint(pe[6]), __float_as_uint(pe[7]),
-                    __float_as_uint(pe[8]), __float_as_uint(pe[9]), __float_as_uint(pe[10]), __float_as_uint(pe[11]), __float_as_uint(pe[12]),
-                    __float_as_uint(pe[13]), __float_as_uint(pe[14]), __float_as_uint(pe[15]), bit));
-                int va = (bit & 8) ? v0[2] : v0[0], vb = (bit & 8) ? v0[3] : v0[1];
-                asm volatile("" : "+v"(va), "+v"(vb));
-                const int v = ((bit & 4) ? vb : va) + (bit & 3);
-                RL.sel[has && pos < SELCAP ? pos : SELCAP + lane] = make_key(pq, (uint32_t)v);
+                const int e = has ? __builtin_ctz(ok) : 0;
+                const float pq = __uint_as_float(pick4(__float_as_uint(pe[0]), __float_as_uint(pe[1]), __float_as_uint(pe[2]), __float_as_uint(pe[3]), e));
+                RL.sel[has && pos < SELCAP ? pos : SELCAP + lane] = make_key(pq, (uint32_t)(v0 + e));
                 pos += has ? 1 : 0;
                 ok &= ok - 1u;
             }
@@ -1359,15 +1311,18 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
         RL.nsel = SELCAP + 1;                                  // too many slots tie at the bound: select from the row
     }
     __syncthreads();
-    const int nc = RL.nsel;
-    if (nc <= RANK_FEW) {
-        rank_keys_split(RL.sel, nc, K, KP, q_row, tok_row, tid);
-    } else if (nc <= SELCAP) {
-        rank_keys_binned(RL.sel, RL.sorted, RL.first, RL.at, RL.wsum, tau, nc, K, KP, q_row, tok_row, tid, lane, w);
-    } else if (w == 0) {                       // rare: one wavefront selects the K best of the row first
-        wave_select_rank([&](auto f) { for (int v = lane; v < V; v += 64) f(make_key(src[v], (uint32_t)v)); },
-                         K, KP, RL.hist, RL.sel, &RL.nsel, q_row, tok_row, lane);
+    int nc = RL.nsel;
+    if (nc > SELCAP) {                         // rare: one wavefront selects the K best of the row first
+        __syncthreads();
+        if (w == 0) wave_select([&](auto f) { for (int v = lane; v < V; v += 64) f(make_key(src[v], (uint32_t)v)); }, K, RL.hist, RL.sel, &RL.nsel, lane);
+        nc = K;
+        __syncthreads();
     }
+    if (nc <= 64) rank_keys<16, 2>(RL.sel, nc, K, top_row, tid);
+    else if (nc <= 128) rank_keys<8, 8>(RL.sel, nc, K, top_row, tid);
+    else if (few) rank_keys<4, 8>(RL.sel, nc, K, top_row, tid);
+    else rank_keys_binned(RL.sel, RL.sorted, RL.first, RL.at, RL.wsum, tau, nc, K, top_row, tid, lane, w);
+    if (K + tid < KP) publish(top_row, K + tid, NO_TOKEN);     // (KP <= 256)
     // ---- the workgroup that finishes last expands -------------------------------------------------------------
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread's part of the lists has reached memory
     __syncthreads();
@@ -1377,30 +1332,21 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     }
     __syncthreads();
     if (!RL.last) return;
-    const double cost_mine = ad.cost && tid < N ? ad.cost[tid] : 1.0;   // (on its way together with the lists)
+    if (ad.cost && tid < N) cost_mine = ad.cost[tid];         // (on its way together with the lists)
     {   // all of a thread's loads are issued before the first is stored (a load and its store per loop trip would
-        // make every trip a round trip to memory): 1, 4 or MAXB entries of each list per thread
-        const size_t lists = (size_t)req * B * KP;
-        const int n = B * KP;
-        auto fetch = [&](auto per_thread) {
-            constexpr int PT = decltype(per_thread)::value;
-            float qv[PT];
-            uint32_t tv[PT];
+        // make every trip a round trip to memory)
+        const u64 *lists = top + (size_t)req * B * KP;
+        const int n = B * KP;                                  // (4096 at most)
+        u64 x[MAXB * BTV_MAX_NODES / RANK_T];
 #pragma unroll
-            for (int i = 0; i < PT; ++i) {
-                const int e = tid + 256 * i, ee = e < n ? e : 0;
-                qv[i] = __hip_atomic_load(top_q + lists + ee, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                tv[i] = __hip_atomic_load(top_tok + lists + ee, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int i = 0; i < MAXB * BTV_MAX_NODES / RANK_T; ++i)
+            if (i * RANK_T < n) x[i] = __hip_atomic_load(lists + min(tid + i * RANK_T, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-            for (int i = 0; i < PT; ++i) {
-                const int e = tid + 256 * i;
-                if (e < n) { S.q[e] = qv[i]; S.tok[e] = tv[i]; }
-            }
-        };
-        if (n <= 256) fetch(std::integral_constant<int, 1>{});
-        else if (n <= 1024) fetch(std::integral_constant<int, 4>{});
-        else fetch(std::integral_constant<int, MAXB>{});
+        for (int i = 0; i < MAXB * BTV_MAX_NODES / RANK_T; ++i) {
+            const int e = tid + i * RANK_T;
+            if (e < n) { S.q[e] = __uint_as_float((uint32_t)(x[i] >> 32)); S.tok[e] = (uint32_t)x[i]; }
+        }
+    }
     }
 
     if (bt.n_nodes) {                          // this request's budget and output rows
@@ -1420,6 +1366,7 @@ __global__ __launch_bounds__(256) void tb_rank_expand(const float *marg, int V, 
     }
     if (ad.cost && tid < N) S.cost[tid] = cost_mine;           // (N <= 256)
     __syncthreads();
+    if (w >= 4) return;                        // the expansions are written for four wavefronts (those that have ended count at no barrier)
     if (beam_width > 0) {                      // B rows = depths of the beam tree, K = min(V, width)
         beam_block(S, BM, B, K, KP, beam_width, tid, parent, token, depth, rho, n_out, ahat);
         return;
@@ -1508,15 +1455,26 @@ TopkPlan topk_plan(int batch, int B, int V, int N)
     // (the counters stay zero from call to call, so their place must not depend on the call's sizes)
     t.ctr_bytes = btv_align_up((size_t)MAX_BATCH * sizeof(TbCounters), BTV_WS_ALIGN);
     t.part_bytes = t.lge == 0 ? 0 : btv_align_up((size_t)batch * B * t.chunks * 256 * sizeof(uint2), BTV_WS_ALIGN);
-    t.top_bytes = btv_align_up((size_t)batch * B * t.KP * 4, BTV_WS_ALIGN);
+    t.top_bytes = btv_align_up((size_t)batch * B * t.KP * sizeof(u64), BTV_WS_ALIGN);
     return t;
+}
+
+// One workgroup for all positions of a request where its threads hold all marginals twice, positions and vocabulary rounded up to powers of two
+// (16 marginals at least, so that a lane of those that share a key has eight pairs of keys to look at).  4 x 64 marginals, 16 nodes: 8.2 us with a workgroup
+// per position, whose lists the last one to finish fetches from memory, 6.5 alone; 4 x 128, 64 nodes: 12.4 and 11.3; 4 x 200, a thread per marginal: 12.7 and 15.2.
+int solo_plan(int B, int V)
+{
+    const int Vp = std::max(16, next_pow2(V)), Bp = next_pow2(B);
+    if (2 * Vp * Bp > RANK_T) return 0;
+    const int T = std::min(std::min(RANK_T / (Vp * Bp), Vp / 16), 16);
+    return __builtin_ctz(Vp) | __builtin_ctz(T) << 8;
 }
 
 size_t tree_build_ws(int batch, int B, int V, int N)
 {
     if (batch < 1 || batch > MAX_BATCH || B < 1 || B > MAXB || V < 1 || N < 1 || N > BTV_MAX_NODES) return 0;
     TopkPlan t = topk_plan(batch, B, V, N);
-    return BTV_WS_HEADER + t.ctr_bytes + t.part_bytes + 2 * t.top_bytes;
+    return BTV_WS_HEADER + t.ctr_bytes + t.part_bytes + t.top_bytes;
 }
 
 }  // namespace
@@ -1543,8 +1501,7 @@ static int tree_build_launch(const float *marginals, int batch, int B, int V, in
     unsigned char *base = static_cast<unsigned char *>(ws);
     TbCounters *ctr = reinterpret_cast<TbCounters *>(base + BTV_WS_HEADER);
     uint2 *part = reinterpret_cast<uint2 *>(base + BTV_WS_HEADER + t.ctr_bytes);
-    float *top_q = reinterpret_cast<float *>(base + BTV_WS_HEADER + t.ctr_bytes + t.part_bytes);
-    uint32_t *top_tok = reinterpret_cast<uint32_t *>(base + BTV_WS_HEADER + t.ctr_bytes + t.part_bytes + t.top_bytes);
+    u64 *top = reinterpret_cast<u64 *>(base + BTV_WS_HEADER + t.ctr_bytes + t.part_bytes);
     Adaptive ad = ad_in;
     ad.flag = reinterpret_cast<uint32_t *>(base);
     bt.flag = reinterpret_cast<uint32_t *>(base);
@@ -1554,8 +1511,10 @@ static int tree_build_launch(const float *marginals, int batch, int B, int V, in
     else if (t.lge == 4) hipLaunchKernelGGL(tb_thread_max<4>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
     else if (t.lge == 5) hipLaunchKernelGGL(tb_thread_max<5>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
     BTV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(tb_rank_expand, dim3(B * batch), dim3(256), 0, st, marginals, V, B, t.K, t.KP, N, t.chunks, t.lge, ctr, part, top_q,
-                       top_tok, parent, token, depth, rho, n_out, ahat, ad, beam_width, bt, algo);
+    const int solo = solo_plan(B, V);
+    const auto rank_expand = solo ? tb_rank_expand<true> : tb_rank_expand<false>;
+    hipLaunchKernelGGL(rank_expand, dim3(solo ? batch : B * batch), dim3(RANK_T), 0, st, marginals, V, B, t.K, t.KP, N, t.chunks, t.lge, ctr, part, top,
+                       parent, token, depth, rho, n_out, ahat, ad, beam_width, bt, algo, solo);
     BTV_HIP(hipGetLastError());
     return BTV_OK;
 }

@@ -48,6 +48,28 @@ def test_small_and_ragged_vocabularies(G, oracle, B, V, N):
         _check(G, oracle, synth.marginals(50 + seed, B, V, 2.5), N)
 
 
+@pytest.mark.parametrize("V", [1, 2, 15, 16, 17, 32, 33, 64, 65, 127, 128, 129, 256, 257, 512, 513])
+@pytest.mark.parametrize("B", [1, 3, 4, 5, 16])
+def test_small_vocabularies_whole_and_by_position(G, oracle, B, V):
+    """Where one workgroup takes all positions (up to 512 marginals, both sizes rounded up to powers of two), where a position's marginals are
+    ranked whole (up to 256) and where they have a bound; probabilities of few distinct values too, so that most of them tie."""
+    for N in (1, 20, 256):
+        marg = synth.marginals(90, B, V, 2.0)
+        _check(G, oracle, marg, N)
+        _check(G, oracle, np.round(marg * 24).astype(np.float32) / 32, N)
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1, 2])
+@pytest.mark.parametrize("N", [63, 127, 255, 256])
+def test_number_of_candidates_around_the_ways_of_ranking_them(G, oracle, N, extra):
+    """N + extra tokens of one probability's bin above all others: they are what the ranking orders, by 16 or 8 lanes a key or by bins."""
+    marg = np.full((4, 6000), 1e-6, dtype=np.float32)
+    rng = np.random.default_rng(N + extra)
+    for row in marg:
+        row[rng.permutation(6000)[:N + extra]] = (1.0 + rng.integers(0, 3, N + extra) / 64.0).astype(np.float32) / 512
+    _check(G, oracle, marg, N)
+
+
 @pytest.mark.parametrize("V", [255, 256, 257, 4096, 4097, 16384, 16387, 65536, 65541, 131072, 131075])
 def test_vocabularies_around_the_slot_sizes(G, oracle, V):
     """The ranking sees a row as slots whose size follows the vocabulary's: single marginals up to 4096, then 4 to 32 of them."""
