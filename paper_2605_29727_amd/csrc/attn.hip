@@ -842,6 +842,26 @@ __device__ __forceinline__ void find_ancestors(const AttnParams &p, uint32_t par
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
+// The same for up to 64 nodes, by each wavefront for itself: lane i has node i, sets and places stay in registers and move between the lanes
+// (log2 of the depth turns of some 100 cycles, no barrier).  lo, hi: the set of `node`.
+__device__ __forceinline__ void wave_ancestors(const AttnParams &p, uint32_t par, int M, int l, int node, uint32_t &lo, uint32_t &hi)
+{
+    int at;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(at) : "v"(par + 4u * (uint32_t)l) : "memory");
+    if (l < M && (at < -1 || at >= l)) atomicOr(p.flag, 1u);
+    if (l >= M || at >= l) at = -1;
+    uint32_t a = l < 32 ? 1u << l : 0u, b = l < 32 ? 0u : 1u << (l & 31);
+    while (__builtin_amdgcn_ballot_w64(at >= 0) != 0ull) {
+        uint32_t a2, b2;
+        int next;
+        asm volatile("ds_bpermute_b32 %0, %3, %4\n\tds_bpermute_b32 %1, %3, %5\n\tds_bpermute_b32 %2, %3, %6\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(a2), "=&v"(b2), "=&v"(next) : "v"(at < 0 ? 4 * l : 4 * at), "v"(a), "v"(b), "v"(at));
+        a |= a2; b |= b2;                                        // (a lane that is done takes its own)
+        at = next;
+    }
+    asm volatile("ds_bpermute_b32 %0, %2, %3\n\tds_bpermute_b32 %1, %2, %4\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(4 * node), "v"(a), "v"(b));
+}
+
 // Largest finite magnitude of a lane's values: what its row's partials are divided by.  (An infinite one, from a value in the
 // cache or a sum past the end of fp32, would leave nothing of the row's other channels.)
 template <int B> __device__ __forceinline__ float finite_max(const f32x16 (&x)[B])
@@ -984,7 +1004,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     begun();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
     const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF, sets_lds = par_lds + WL::PARENTS;
-    if (tree_wg) find_ancestors(p, par_lds, sets_lds, Mr, tid);
+    if (tree_wg && Mr > 64) find_ancestors(p, par_lds, sets_lds, Mr, tid);
     // Operand s holds the 8 channels that contraction step s takes from this lane's half: 16 s + 8 h .. + 7 for
     // bf16 K, 32 (s/2) + 16 h + 8 (s%2) .. + 7 for FP8 K (the order of its 16-byte operand reads).
     u32x4 qv[DS];
@@ -1007,7 +1027,12 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     for (int k = 0; k < BTV_ANC_WORDS; ++k) anc_i[k] = 0u;
     auto read_mask = [&]() {
         if (!tree_wg) return;
-        const uint32_t a = sets_lds + (uint32_t)lane_row(p, by * WR + rw * 32 + c, rows_g, g, rq_.q0).node * (BTV_ANC_WORDS * 4);
+        const int node = lane_row(p, by * WR + rw * 32 + c, rows_g, g, rq_.q0).node;
+        if (Mr <= 64) {
+            wave_ancestors(p, par_lds, Mr, l, node, anc_i[0], anc_i[1]);
+            return;
+        }
+        const uint32_t a = sets_lds + (uint32_t)node * (BTV_ANC_WORDS * 4);
         u32x4 lo, hi = { 0u, 0u, 0u, 0u };
         if (Mr > 128) asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(a) : "memory");
         else asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(lo) : "v"(a) : "memory");
@@ -1015,7 +1040,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         for (int k = 0; k < 4; ++k) { anc_i[k] = lo[k]; anc_i[k + 4] = hi[k]; }
     };
     if constexpr (KW > 1) {
-        if (tree_wg) __builtin_amdgcn_s_barrier();               // every wave's sets are there
+        if (tree_wg && Mr > 64) __builtin_amdgcn_s_barrier();    // every wave's sets are there
         read_mask();
     }
 
