@@ -59,6 +59,26 @@ def test_small_vocabularies_whole_and_by_position(G, oracle, B, V):
         _check(G, oracle, np.round(marg * 24).astype(np.float32) / 32, N)
 
 
+@pytest.mark.parametrize("V", [4097, 8192, 16390, 40001, 131072])
+def test_marginals_at_any_float(G, oracle, V):
+    """Rows, and the first of them, that begin 4, 8 or 12 bytes past a multiple of 16."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    B, N = 5, 40
+    marg = synth.marginals(91, B, V, 3.0)
+    ref = oracle.tree_build(marg, N)
+    for shift in (0, 1, 2, 3):
+        room = torch.zeros(B * V + shift, device="cuda")
+        room[shift:] = torch.from_numpy(marg.reshape(-1)).cuda()
+        out = {k: torch.zeros(N, dtype=torch.int32, device="cuda") for k in ("parent", "token", "depth")}
+        rho, n_out, ahat = torch.zeros(N, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, device="cuda")
+        btv.btv_tree_build(room[shift:].view(B, V), N, out["parent"], out["token"], out["depth"], rho, n_out, ahat,
+                           btv.alloc_workspace(btv.btv_tree_build_workspace(B, V, N)))
+        for k in out:
+            assert np.array_equal(out[k].cpu().numpy(), ref[k]), (k, shift)
+        assert np.array_equal(rho.cpu().numpy().view(np.uint32), ref["rho"].view(np.uint32)), shift
+
+
 @pytest.mark.parametrize("extra", [-1, 0, 1, 2])
 @pytest.mark.parametrize("N", [63, 127, 255, 256])
 def test_number_of_candidates_around_the_ways_of_ranking_them(G, oracle, N, extra):
