@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -33,113 +34,65 @@ __device__ __forceinline__ Best best_wave(Best b)
     return b;
 }
 
-// Best element of vocabulary chunk `chunk` of row `row` as seen by this thread (256 threads per workgroup).  Whole,
-// 16-byte aligned chunks take four (bf16) or eight (fp32) 16-byte loads per thread, all in flight before the first
-// is looked at.
 template <bool BF16>
-__device__ __forceinline__ Best chunk_scan(const void *logits, int V, int row, int chunk, int tid)
+__device__ __forceinline__ float load_one(const void *logits, size_t idx)
 {
-    const int v0 = chunk * ACHUNK, v1 = min(v0 + ACHUNK, V);
+    if (BF16) return __uint_as_float((uint32_t)static_cast<const uint16_t *>(logits)[idx] << 16);
+    return static_cast<const float *>(logits)[idx];
+}
+
+// Best of elements v0 .. v1 - 1 of a row (its first at element `base` of the logits), as seen by thread tid of T.  What lies in whole 16-byte pieces
+// of memory is read by 16-byte loads, U per thread in flight before the first is looked at, wherever the row begins (a vocabulary that is no multiple of
+// eight leaves most rows unaligned); the few elements before and behind those pieces one per thread, by a load that is under way with the others.
+// Loads past the last piece are redirected to it, so that none lies behind a branch that the threads may take apart: the compiler would wait for each.
+// A thread meets its elements in rising index order, so "larger than the best so far" alone keeps the first of equal values, and the place is kept as
+// the number of the element within the trip (a constant in the instruction): three instructions per element against eight for best_take, by which the scan was
+// bound.  Elements equal to the start value, -inf, are not taken that way: where a thread ends without a place its wavefront goes through them again.
+// us, before (rows of unaligned vocabularies by one element per load) -> now: 65 rows of 128255 bf16 12.8 -> 8.4, 21 of 30001 10.4 -> 5.9; batches of 8 requests: 520 rows
+// of 128255 89.8 -> 27.6, 168 of 20001 14.2 -> 6.6 (and aligned: 65 of 128256 8.9 -> 8.2, 520 of them 29.8 -> 27.6).
+template <bool BF16, int T, int U>
+__device__ __forceinline__ Best span_scan(const void *logits, size_t base, int v0, int v1, int tid)
+{
+    constexpr int ES = BF16 ? 2 : 4, PER = 16 / ES;              // element size, elements per piece
+    const unsigned char *first = static_cast<const unsigned char *>(logits) + (base + v0) * ES;
+    const int n = v1 - v0, head = min((PER - (int)((reinterpret_cast<uintptr_t>(first) & 15) / ES)) & (PER - 1), n);
+    const int P = (n - head) / PER, tail = n - head - P * PER;
+    const uint4 *x = reinterpret_cast<const uint4 *>(first + head * ES);
+    const int ve = tid < head ? v0 + tid : tid < head + tail ? v1 - tail + tid - head : v0;
+    const float edge = load_one<BF16>(logits, base + ve);
     Best b = { -INFINITY, INT_MAX };
-    if (BF16) {
-        const uint16_t *x = static_cast<const uint16_t *>(logits) + (size_t)row * V;
-        if ((((size_t)row * V * 2) & 15) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {
-            if (v1 - v0 == ACHUNK) {
-                uint4 q[4];
+    auto pass = [&](auto exact) {
+        for (int h = 0; h < P; h += U * T) {                     // (uniform)
+            uint4 q[U];
+            if (h + U * T <= P) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const uint4 *>(x + v0 + tid * 8 + j * 2048);
-                // the thread meets its elements in rising index order: "larger than the best so far" keeps the first of
-                // equal values, the place is the element's number (a constant of the instruction); elements equal to
-                // the start value, -inf, are not taken, and a wavefront in which a thread ends without a place takes
-                // the exact pass below
-                float bv = -INFINITY;
-                int bk = -1;
+                for (int j = 0; j < U; ++j) q[j] = x[h + j * T + tid];
+            } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float lo = __uint_as_float(wds[e] << 16), hi = __uint_as_float(wds[e] & 0xFFFF0000u);
-                        if (lo > bv) { bv = lo; bk = j * 8 + 2 * e; }
-                        if (hi > bv) { bv = hi; bk = j * 8 + 2 * e + 1; }
-                    }
-                }
-                if (__builtin_amdgcn_ballot_w64(bk < 0) == 0ull) {
-                    b.v = bv;
-                    b.i = v0 + tid * 8 + (bk >> 3) * 2048 + (bk & 7);
-                    return b;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
-                    const int v = v0 + tid * 8 + j * 2048;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        best_take(b, __uint_as_float(wds[e] << 16), v + 2 * e);
-                        best_take(b, __uint_as_float(wds[e] & 0xFFFF0000u), v + 2 * e + 1);
-                    }
-                }
-                return b;
+                for (int j = 0; j < U; ++j) q[j] = x[min(h + j * T + tid, P - 1)];
             }
-            for (int v = v0 + tid * 8; v < v1; v += 256 * 8) {
-                if (v + 8 <= v1) {
-                    uint4 q = *reinterpret_cast<const uint4 *>(x + v);
-                    uint32_t wds[4] = { q.x, q.y, q.z, q.w };
+            auto place = [&](int k) { return v0 + head + min(h + k / PER * T + tid, P - 1) * PER + k % PER; };
+            float bv = b.v;
+            int bk = -1;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        best_take(b, __uint_as_float(wds[e] << 16), v + 2 * e);
-                        best_take(b, __uint_as_float(wds[e] & 0xFFFF0000u), v + 2 * e + 1);
-                    }
-                } else {
-                    for (int e = v; e < v1; ++e) best_take(b, __uint_as_float((uint32_t)x[e] << 16), e);
+            for (int j = 0; j < U; ++j) {
+                const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    const float f = !BF16 ? __uint_as_float(wds[e & 3]) : e & 1 ? __uint_as_float(wds[e / 2] & 0xFFFF0000u) : __uint_as_float(wds[e / 2] << 16);
+                    if constexpr (decltype(exact)::value) best_take(b, f, place(j * PER + e));
+                    else if (f > bv) { bv = f; bk = j * PER + e; }
                 }
             }
-        } else {
-            for (int v = v0 + tid; v < v1; v += 256) best_take(b, __uint_as_float((uint32_t)x[v] << 16), v);
+            if (bk >= 0) { b.v = bv; b.i = place(bk); }
         }
-    } else {
-        const float *x = static_cast<const float *>(logits) + (size_t)row * V;
-        if ((((size_t)row * V * 4) & 15) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {
-            if (v1 - v0 == ACHUNK) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float4 q[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const float4 *>(x + v0 + tid * 4 + (h * 4 + j) * 1024);
-                    float bv = b.v;                              // (as for bf16: rising order, exact pass on demand)
-                    int bk = -1;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float f[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (f[e] > bv) { bv = f[e]; bk = j * 4 + e; }
-                    }
-                    const bool none = bk < 0 && b.i == INT_MAX;
-                    if (__builtin_amdgcn_ballot_w64(none) == 0ull) {
-                        if (bk >= 0) { b.v = bv; b.i = v0 + tid * 4 + (h * 4 + (bk >> 2)) * 1024 + (bk & 3); }
-                        continue;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int v = v0 + tid * 4 + (h * 4 + j) * 1024;
-                        best_take(b, q[j].x, v); best_take(b, q[j].y, v + 1); best_take(b, q[j].z, v + 2); best_take(b, q[j].w, v + 3);
-                    }
-                }
-                return b;
-            }
-            for (int v = v0 + tid * 4; v < v1; v += 256 * 4) {
-                if (v + 4 <= v1) {
-                    float4 q = *reinterpret_cast<const float4 *>(x + v);
-                    best_take(b, q.x, v); best_take(b, q.y, v + 1); best_take(b, q.z, v + 2); best_take(b, q.w, v + 3);
-                } else {
-                    for (int e = v; e < v1; ++e) best_take(b, x[e], e);
-                }
-            }
-        } else {
-            for (int v = v0 + tid; v < v1; v += 256) best_take(b, x[v], v);
-        }
+    };
+    pass(std::false_type{});
+    if (P > 0 && __builtin_amdgcn_ballot_w64(b.i == INT_MAX) != 0ull) {
+        b = Best{ -INFINITY, INT_MAX };
+        pass(std::true_type{});
     }
+    if (tid < head + tail) best_take(b, edge, ve);
     return b;
 }
 
@@ -149,7 +102,7 @@ __global__ __launch_bounds__(256) void argmax_chunks(const void *logits, int V, 
 {
     __shared__ Best wb[4];
     const int tid = threadIdx.x, chunk = blockIdx.x, row = blockIdx.y;
-    Best b = best_wave(chunk_scan<BF16>(logits, V, row, chunk, tid));
+    Best b = best_wave(span_scan<BF16, 256, BF16 ? 4 : 8>(logits, (size_t)row * V, chunk * ACHUNK, min(chunk * ACHUNK + ACHUNK, V), tid));
     if ((tid & 63) == 0) wb[tid >> 6] = b;
     __syncthreads();
     if (tid == 0) {
@@ -226,124 +179,6 @@ __device__ __forceinline__ unsigned long long best_key(Best b)
     return ((unsigned long long)mono << 32) | (uint32_t)~(uint32_t)b.i;
 }
 
-// Best element of elements v0 .. v1-1 of a row as seen by this lane.  Where the row is 16-byte aligned the unit is
-// fetched with eight 16-byte loads per lane at a time, all in flight before the first is looked at; a ragged unit (the
-// last of a row) takes the same loads with the pieces past its end redirected to its first piece and left out, and
-// the elements behind the last whole piece one per lane.  Nothing here loads inside a loop whose next trip needs
-// the value: twenty such trips for the last 1280 elements of a row were two thirds of the kernel's time.
-template <bool BF16, bool WHOLE>
-__device__ __forceinline__ void wave_scan_pieces(Best &b, const uint4 *x, int v0, int npiece, int lane)
-{
-    constexpr int PER = BF16 ? 8 : 4;                            // elements per 16-byte piece
-    for (int h = 0; h * 512 < npiece; ++h) {
-        uint4 q[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int p = (h * 8 + j) * 64 + lane;
-            q[j] = x[WHOLE || p < npiece ? p : 0];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int p = (h * 8 + j) * 64 + lane;
-            if (!WHOLE && p >= npiece) continue;
-            const int v = v0 + p * PER;
-            const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (BF16) {
-                    best_take(b, __uint_as_float(wds[e] << 16), v + 2 * e);
-                    best_take(b, __uint_as_float(wds[e] & 0xFFFF0000u), v + 2 * e + 1);
-                } else {
-                    best_take(b, __uint_as_float(wds[e]), v + e);
-                }
-            }
-        }
-    }
-}
-
-// A whole unit, the cheap way: the lane meets its elements in rising index order, so "larger than the best so far"
-// alone keeps the first of equal values, and the place is kept as the number of the element within the trip (a
-// constant in the instruction).  Three instructions per element against eight for best_take: with four wavefronts per
-// SIMD the scan was bound by this arithmetic, not by memory.  Elements equal to the start value, -inf, are not
-// taken here: a lane that ends without a place sends the wavefront through wave_scan_pieces after all.
-template <bool BF16>
-__device__ __forceinline__ void wave_scan_whole(Best &b, const uint4 *x, int v0, int lane)
-{
-    constexpr int PER = BF16 ? 8 : 4;
-    for (int h = 0; h < WCHUNK / (512 * PER); ++h) {
-        uint4 q[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) q[j] = x[(h * 8 + j) * 64 + lane];
-        float bv = b.v;
-        int bk = -1;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (BF16) {
-                    const float lo = __uint_as_float(wds[e] << 16), hi = __uint_as_float(wds[e] & 0xFFFF0000u);
-                    if (lo > bv) { bv = lo; bk = j * PER + 2 * e; }
-                    if (hi > bv) { bv = hi; bk = j * PER + 2 * e + 1; }
-                } else {
-                    const float f = __uint_as_float(wds[e]);
-                    if (f > bv) { bv = f; bk = j * PER + e; }
-                }
-            }
-        }
-        if (bk >= 0) {
-            b.v = bv;
-            b.i = v0 + ((h * 8 + bk / PER) * 64 + lane) * PER + bk % PER;
-        }
-    }
-}
-
-template <bool BF16>
-__device__ __forceinline__ float wave_scan_one(const void *logits, size_t idx)
-{
-    if (BF16) return __uint_as_float((uint32_t)static_cast<const uint16_t *>(logits)[idx] << 16);
-    return static_cast<const float *>(logits)[idx];
-}
-
-template <bool BF16>
-__device__ __forceinline__ Best wave_scan(const void *logits, int V, int row, int v0, int v1, int lane)
-{
-    Best b = { -INFINITY, INT_MAX };
-    constexpr int ES = BF16 ? 2 : 4, PER = 16 / ES;              // element size, elements per 16-byte load
-    const bool aligned = (((size_t)row * V * ES) & 15) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
-    const size_t base = (size_t)row * V;
-    if (aligned) {                                               // (v0 is a multiple of WCHUNK)
-        const uint4 *x = reinterpret_cast<const uint4 *>(static_cast<const unsigned char *>(logits) + (base + v0) * ES);
-        const int npiece = (v1 - v0) / PER;
-        if (v1 - v0 == WCHUNK) {
-            wave_scan_whole<BF16>(b, x, v0, lane);
-            if (__builtin_amdgcn_ballot_w64(b.i == INT_MAX) == 0ull) return b;
-            b = Best{ -INFINITY, INT_MAX };                      // (a lane saw nothing above -inf)
-            wave_scan_pieces<BF16, true>(b, x, v0, npiece, lane);
-            return b;
-        }
-        wave_scan_pieces<BF16, false>(b, x, v0, npiece, lane);
-        const int v = v0 + npiece * PER + lane;                  // fewer than PER elements are left
-        const float last = wave_scan_one<BF16>(logits, base + (v < v1 ? v : v0));
-        if (v < v1) best_take(b, last, v);
-        return b;
-    }
-    for (int vb = v0; vb < v1; vb += 64 * 8) {                   // eight loads in flight
-        float xv[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int v = vb + j * 64 + lane;
-            xv[j] = wave_scan_one<BF16>(logits, base + (v < v1 ? v : v0));
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int v = vb + j * 64 + lane;
-            if (v < v1) best_take(b, xv[j], v);
-        }
-    }
-    return b;
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(OL_WAVES * 64) void accept_greedy_one_launch(
     const void *logits, int V, int chunks, unsigned long long *slot, uint32_t *flag, const int32_t *parent,
@@ -372,7 +207,7 @@ __global__ __launch_bounds__(OL_WAVES * 64) void accept_greedy_one_launch(
         if (u < units) {
             row = u / chunks;
             const int chunk = u - row * chunks;
-            b = best_wave(wave_scan<BF16>(logits, V, row, chunk * WCHUNK, min(chunk * WCHUNK + WCHUNK, V), lane));
+            b = best_wave(span_scan<BF16, 64, 8>(logits, (size_t)row * V, chunk * WCHUNK, min(chunk * WCHUNK + WCHUNK, V), lane));
         }
         if (lane == 0) { wbest[wave] = b; wrow[wave] = row; }
         if (collector)
@@ -448,7 +283,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void accept_greedy_small(const void 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = p * RPP + r0, v = l + LPR * i;
-                x[p][i] = wave_scan_one<BF16>(logits, row <= M && v < V ? (size_t)row * V + v : 0);
+                x[p][i] = load_one<BF16>(logits, row <= M && v < V ? (size_t)row * V + v : 0);
             }
 #pragma unroll
     for (int p = 0; p < SMALL_PASSES; ++p)

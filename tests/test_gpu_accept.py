@@ -56,6 +56,45 @@ def test_greedy_config2_full_vocab_with_planted_paths(G, oracle, dtype):
     _greedy_case(G, oracle, store, xf, dtype == "bf16", tree["parent"], tree["token"])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [257, 300, 511, 1021, 4089, 4095, 4096, 4103, 8190, 8193, 8201, 12287])
+def test_greedy_rows_at_any_element(G, oracle, V, dtype):
+    """The first row, and with it all others, begins 0 .. 7 elements behind a multiple of 16 bytes.  The largest value is among a row's or a unit's first and
+    last few elements (which are no whole 16 bytes) as often as inside; it occurs more than once; rows of -inf and NaN have their rule."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    M, nb = 17, 3
+    rows = M + nb
+    rng = np.random.default_rng(V)
+    x = np.round(rng.standard_normal((rows, V)) * 2).astype(np.float32) / 2          # few values: ties everywhere
+    ends = [0, 1, 6, 7, 8, V - 9, V - 8, V - 2, V - 1] + [v for v in (4088, 4095, 4096, 8184, 8191, 8192) if v < V]
+    for r in range(rows - 4):
+        for v in rng.choice(ends, 2, replace=False):
+            x[r, v] = 9.0
+    x[rows - 4] = -np.inf
+    x[rows - 3] = np.nan
+    x[rows - 2] = -np.inf; x[rows - 2, V - 1] = -3.0
+    x[rows - 1] = -np.inf; x[rows - 1, 0] = np.nan
+    want = [int(np.argmax(np.where(np.isnan(r), -np.inf, r))) if (r > -np.inf).any() or not np.isnan(r).any() else
+            int(np.argmax(~np.isnan(r))) for r in x]
+    parent, token = synth.tree_parents(V, M, "random"), np.arange(M, dtype=np.int32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    z = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda")
+    for shift in range(8 if dtype == "bf16" else 4):
+        room = torch.zeros(rows * V + shift, dtype=dt, device="cuda")
+        room[shift:] = torch.from_numpy(x.reshape(-1)).to(dt).cuda()
+        rows_at = room[shift:].view(rows, V)
+        am = z(rows)
+        btv.btv_tree_accept_greedy(rows_at[nb - 1:], G.dev(parent), G.dev(token), z(M), z(1), z(1), am[:M + 1],
+                                   btv.alloc_workspace(btv.btv_tree_accept_workspace(M, V, False)))
+        assert am[:M + 1].tolist() == want[nb - 1:], shift
+        offsets = np.array([0, 2, 3, M], dtype=np.int32)
+        forest = np.concatenate([synth.tree_parents(r, int(n), "random") for r, n in enumerate(np.diff(offsets))]).astype(np.int32)
+        btv.btv_tree_accept_greedy_batch(rows_at, G.dev(forest), G.dev(token), G.dev(offsets), M, z(M), z(nb), z(nb), am,
+                                         btv.alloc_workspace(btv.btv_tree_accept_batch_workspace(nb, M, V)))
+        assert am.tolist() == want, shift
+
+
 @pytest.mark.parametrize("kind", ["chain", "star", "binary", "random", "deep"])
 @pytest.mark.parametrize("M,V", [(1, 1), (7, 13), (256, 1000), (100, 8193), (33, 128256)])
 def test_greedy_tree_kinds_and_odd_vocabularies(G, oracle, kind, M, V):
