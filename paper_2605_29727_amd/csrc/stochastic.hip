@@ -62,6 +62,11 @@ constexpr int SA_WORDS = 4 * SA_POINTS;                 // words of one workgrou
 constexpr int SA_CHAIN = 4;                             // rows of a first-child chain that are read and exchanged together
 constexpr int SA_CHAIN_FAN = 8;                         // children up to which a node's first child is worth reading ahead (it is one of
                                                         // several that the draft likes about as well, otherwise)
+// Up to so many workgroups run on one XCD (every eighth of a grid eight times as large; the others leave at once), and their exchanges stay in
+// its L2.  us, over memory / in the L2: 11 workgroups 39 children rejected 38.7 / 34.5, 16 of them 100 rejected 38.9 / 34.9, a followed draft 28.4 / 28.4 and
+// 34.1 / 33.6 (what the exchanges gain its rows lose, which come through one XCD's share of the memory); 32 workgroups 37.8 / 34.0.  A quarter of the XCD's
+// CUs is left for other streams' work: where fewer are free the walk waits for them, or ends alone.
+constexpr int SA_NEAR = 24;
 constexpr int SA_DIRECT = 3;                            // rejections that are walked one by one in any case, one less per 32 children
                                                         // (a node of many children has no likely one among its first)
 constexpr int SA_BATCH_MIN = 10;                        // children left from which the rest is solved at once (the price of ten exchanges)
@@ -239,15 +244,19 @@ __device__ __forceinline__ int sa_bin(float r, int b0)
     return SA_BINS - 1 - min((int)((__float_as_uint(r) & 0x7FFFFFFFu) >> 18) - b0, SA_BINS - 1);
 }
 
-__device__ __forceinline__ void put_u32(u64 *p, uint32_t tag, uint32_t x)
+__device__ __forceinline__ uint32_t this_xcd() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)); }     // HW_REG_XCC_ID, bits 3:0
+
+// near: all workgroups run on one XCD, and the word need not go further than its L2.
+__device__ __forceinline__ void put_u32(u64 *p, uint32_t tag, uint32_t x, bool near)
 {
-    __hip_atomic_store(p, ((u64)tag << 32) | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (near) __hip_atomic_store(p, ((u64)tag << 32) | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(p, ((u64)tag << 32) | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void put_f64(u64 *lo, u64 *hi, uint32_t tag, double x)
+__device__ __forceinline__ void put_f64(u64 *lo, u64 *hi, uint32_t tag, double x, bool near)
 {
     const u64 b = (u64)__double_as_longlong(x);
-    put_u32(lo, tag, (uint32_t)b);
-    put_u32(hi, tag, (uint32_t)(b >> 32));
+    put_u32(lo, tag, (uint32_t)b, near);
+    put_u32(hi, tag, (uint32_t)(b >> 32), near);
 }
 __device__ __forceinline__ double get_f64(u64 lo, u64 hi)
 {
@@ -307,7 +316,7 @@ struct SaShared {
     double F[SA_CHAIN][SA_MAX_WGS], GW[SA_CHAIN + 1][SA_MAX_WGS];
     alignas(16) int acc0[SA_CHAIN];
     int wsum[SA_WAVES];
-    int dead, status, acc, pick, last, late;
+    int dead, status, acc, pick, last, late, near;
     float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
     double pt[BTV_MAX_NODES], ptG[BTV_MAX_NODES], invT[BTV_MAX_NODES];
     double sE[SA_POINTS], sQ[SA_POINTS], part[SA_T];
@@ -330,9 +339,10 @@ __device__ __forceinline__ void sa_move_on(uint32_t *word, uint32_t base, uint32
     __hip_atomic_compare_exchange_strong(word, &base, base + used, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// ALONE: one workgroup (me = 0) with the whole vocabulary for a slice.  Returns whether a wait has passed its limit
+// ALONE: one workgroup (me = 0) with the whole vocabulary for a slice.  NEAR: the workgroups are dealt out so that they run on one XCD; if the first
+// exchange, which goes through memory, says so of all of them, the others stay in its L2.  Returns whether a wait has passed its limit
 // (the same in all threads; results may then be missing).
-template <bool BF16, int PT, bool OVER, bool ALONE>
+template <bool BF16, int PT, bool OVER, bool ALONE, bool NEAR>
 __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int me, uint32_t &base)
 {
     static_assert(OVER || !ALONE, "a slice of any length");
@@ -356,11 +366,11 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
         if (c <= M) L.uni[c] = p.uniforms[c];
     }
-    if (tid == 0) { L.dead = 0; L.late = 0; }
+    if (tid == 0) { L.dead = 0; L.late = 0; L.near = 0; }
     base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     uint32_t seq = 0;
     int cur = -1, n = 0, ui = 0, d = 0;
-    bool dead = false;
+    bool dead = false, near = false;
     __syncthreads();
     if (tid < M && L.par[tid] >= -1 && L.par[tid] < M) {
         atomicMin(&L.first[L.par[tid] + 1], tid);
@@ -469,9 +479,9 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             if (G > 1) {
                 u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                 const uint32_t tag = base + seq;
-                if (lane < 6) {                         // z, the draft mass, the maximum (twice, for whole pairs of words)
+                if (lane < 6) {                         // z, the draft mass, the maximum (NEAR: where this workgroup runs; else the maximum again, for whole pairs of words)
                     const u64 b = (u64)__double_as_longlong(lane < 2 ? z : tq);
-                    put_u32(set + (size_t)me * SA_WORDS + 8 * r + lane, tag, lane >= 4 ? __float_as_uint(m_row) : (uint32_t)(lane & 1 ? b >> 32 : b));
+                    put_u32(set + (size_t)me * SA_WORDS + 8 * r + lane, tag, NEAR && lane == 5 ? this_xcd() : lane >= 4 ? __float_as_uint(m_row) : (uint32_t)(lane & 1 ? b >> 32 : b), near);
                 }
                 // four lanes read a part's row, which lies in one line, and hand it to the lane that has the part
                 ulong2 w[4];
@@ -488,6 +498,8 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 mw = lane < G ? __uint_as_float(x[4]) : -INFINITY;
                 zw = lane < G ? get_f64(x[0], x[1]) : 0.0;
                 tw = lane < G ? get_f64(x[2], x[3]) : 0.0;
+                // (all workgroups read the same words: they all find the same)
+                if (NEAR && r == 0 && seq == 1 && __builtin_amdgcn_ballot_w64(lane < G && x[5] != this_xcd()) == 0ull) L.near = 1;
             }
             const float m = wave_max(mw);
             const double F = mw == -INFINITY ? 0.0 : exp((double)mw - (double)m);
@@ -510,6 +522,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         }
         __syncthreads();
         if (L.dead) { dead = true; break; }
+        if (NEAR) near = __builtin_amdgcn_readfirstlane(L.near) != 0;
         // ---- first children, as far as they are accepted -------------------------------------------------------------
         int r = 0;
         {
@@ -647,7 +660,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                         if (G > 1) {
                             if (sub < 4 && k < np) {    // four lanes a point: consecutive words by consecutive lanes
                                 const u64 b = (u64)__double_as_longlong(sub & 2 ? Q : E);
-                                put_u32(p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + 4 * k + sub, base + seq, (uint32_t)(sub & 1 ? b >> 32 : b));
+                                put_u32(p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + 4 * k + sub, base + seq, (uint32_t)(sub & 1 ? b >> 32 : b), near);
                             }
                         } else if (sub == 0) {
                             L.sE[k] = E; L.sQ[k] = Q;
@@ -685,7 +698,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
 #pragma nounroll
                                 for (int i = tid; i < ((((G << lgd) + 63) >> 6) << lgw); i += 1 << lgd) y += L.part[i];
                                 u64 *o = p.slots + ((size_t)(seq & 1) * G + me) * SA_WORDS + 2 * tid;
-                                put_f64(o, o + 1, base + seq, y);
+                                put_f64(o, o + 1, base + seq, y, near);
                             }
                         }
                         set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
@@ -848,7 +861,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                     u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                     const uint32_t tag = base + seq;
                     const u64 b = (u64)__double_as_longlong(a);
-                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)(lane ? b >> 32 : b));
+                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)(lane ? b >> 32 : b), near);
                     ulong2 w[1];
                     if (!take<1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
                     gw = lane < G ? get_f64(w[0].x, w[0].y) : 0.0;
@@ -931,7 +944,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 if (G > 1) {
                     u64 *set = p.slots + (size_t)(seq & 1) * G * SA_WORDS;
                     const uint32_t tag = base + seq;
-                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)L.last);
+                    if (lane < 2) put_u32(set + (size_t)me * SA_WORDS + lane, tag, (uint32_t)L.last, near);
                     ulong2 w[1];
                     if (!take<1>(set, lane, 0, G, 0, true, tag, w, p.wait_ticks) && lane == 0) L.dead = 1;
                     last = lane < G ? (int)(uint32_t)w[0].x : -1;
@@ -959,15 +972,16 @@ template <bool BF16, int PT>
 __device__ __attribute__((noinline, cold)) void sa_walk_alone(SaArgs args, SaLds<PT> L)
 {
     uint32_t none;
-    sa_walk<BF16, PT, true, true>(*(const SaParams *)args, *(SaShared<PT> *)L, 0, none);
+    sa_walk<BF16, PT, true, true, false>(*(const SaParams *)args, *(SaShared<PT> *)L, 0, none);
 }
 
-template <bool BF16, int PT, bool OVER>
+template <bool BF16, int PT, bool OVER, bool NEAR>
 __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 {
     __shared__ SaShared<PT> L;
     uint32_t base;
-    if (!sa_walk<BF16, PT, OVER, false>(p, L, blockIdx.x, base)) return;
+    if (NEAR && (blockIdx.x & 7)) return;               // (ids that are congruent mod 8 run on one XCD)
+    if (!sa_walk<BF16, PT, OVER, false, NEAR>(p, L, NEAR ? blockIdx.x >> 3 : blockIdx.x, base)) return;
     auto again = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(again));
     const SaArgs args = (SaArgs)again;
@@ -982,7 +996,7 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 // Slices for a vocabulary of V tokens on at most `most` workgroups (no more than CUs that the stream may use: with 32 of them the two
 // walks named at the top take 52 and 48 .. 52 us, with 16 110 and 101 .. 118): of 2048 tokens (two per thread) as long as those cover the
 // vocabulary, of 4096, of 8192, longer ones above.
-struct SaPlan { int G, per, pt; bool over; };
+struct SaPlan { int G, per, pt; bool over, near; };
 SaPlan sa_plan(int V, int most)
 {
     SaPlan a;
@@ -991,16 +1005,18 @@ SaPlan sa_plan(int V, int most)
     const int slice = SA_T * a.pt;
     a.G = a.over ? most : (V + slice - 1) / slice;
     a.per = (int)((((long long)V + a.G - 1) / a.G + 3) / 4 * 4);
+    a.near = false;
     return a;
 }
 
 template <bool BF16>
 void sa_launch(const SaPlan &a, const SaParams &p, hipStream_t st)
 {
-    if (a.over) hipLaunchKernelGGL((stochastic_walk<BF16, 8, true>), dim3(a.G), dim3(SA_T), 0, st, p);
-    else if (a.pt == 8) hipLaunchKernelGGL((stochastic_walk<BF16, 8, false>), dim3(a.G), dim3(SA_T), 0, st, p);
-    else if (a.pt == 4) hipLaunchKernelGGL((stochastic_walk<BF16, 4, false>), dim3(a.G), dim3(SA_T), 0, st, p);
-    else hipLaunchKernelGGL((stochastic_walk<BF16, 2, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    if (a.over) hipLaunchKernelGGL((stochastic_walk<BF16, 8, true, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else if (a.pt == 8) hipLaunchKernelGGL((stochastic_walk<BF16, 8, false, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else if (a.pt == 4) hipLaunchKernelGGL((stochastic_walk<BF16, 4, false, false>), dim3(a.G), dim3(SA_T), 0, st, p);
+    else if (a.near) hipLaunchKernelGGL((stochastic_walk<BF16, 2, false, true>), dim3(8 * a.G), dim3(SA_T), 0, st, p);
+    else hipLaunchKernelGGL((stochastic_walk<BF16, 2, false, false>), dim3(a.G), dim3(SA_T), 0, st, p);
 }
 
 }  // namespace
@@ -1026,7 +1042,11 @@ extern "C" int btv_tree_accept_stochastic_tuned(const void *logits, int dtype, c
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     SaPlan a = sa_plan(V, max_workgroups ? max_workgroups : SA_MAX_WGS);
-    if (!max_workgroups && a.G > 1) a = sa_plan(V, std::min(SA_MAX_WGS, btv_usable_cus(st)));
+    if (!max_workgroups && a.G > 1) {
+        const int cus = btv_usable_cus(st);
+        a = sa_plan(V, std::min(SA_MAX_WGS, cus));
+        a.near = a.pt == 2 && !a.over && a.G > 1 && a.G <= SA_NEAR && cus >= 256;
+    }
     SaParams p;
     p.logits = logits; p.marg = marginals; p.uniforms = uniforms; p.parent = parent; p.token = token;
     p.path = path; p.n_acc = n_acc; p.bonus = bonus;

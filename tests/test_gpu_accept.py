@@ -57,6 +57,45 @@ def test_greedy_config2_full_vocab_with_planted_paths(G, oracle, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [2049, 4099, 20001, 32768, 49152, 49153])
+def test_stochastic_exchanges_in_one_l2_and_through_memory(G, V, dtype):
+    """The library's own choice (up to 24 workgroups on one XCD) and the same number of them dealt out over the chip do the same arithmetic: the same
+    path and bonus for wide fans that are rejected, followed drafts and what lies between, call after call on one workspace."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    N, B = 90, 10
+    g = torch.Generator(device="cuda"); g.manual_seed(V)
+    wgs = -(-V // 2048)
+    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(N, V, True))
+    z = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda")
+    for k, (kind, noise) in enumerate([("star", 3.0), ("random", 2.0), ("chain", 0.3), ("deep", 0.5), ("star", 0.5)]):
+        marg = torch.softmax(3 * torch.randn((B, V), generator=g, device="cuda"), 1)
+        parent = synth.tree_parents(V + k, N, kind)
+        depth = _depths(parent)
+        keep = depth <= B
+        parent = torch.from_numpy(np.where(keep, parent, -1).astype(np.int32)).cuda()
+        order = marg.argsort(1, descending=True)
+        rank = {}
+        token = []
+        for i, pa in enumerate(parent.tolist()):
+            rank[pa] = rank.get(pa, -1) + 1
+            token.append(int(order[min(int(depth[i]), B) - 1, rank[pa]]))
+        x = torch.randn((N + 1, V), generator=g, device="cuda") * noise
+        if kind in ("chain", "deep"):
+            x += marg.clamp(min=1e-30).log()[torch.from_numpy(np.concatenate([[0], depth])).clamp(max=B - 1).long().cuda()]
+        x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        u = torch.rand(N + 1, generator=g, device="cuda")
+        tok = torch.tensor(token, dtype=torch.int32, device="cuda")
+        res = []
+        for most in (0, wgs, 0):
+            path, n, b = z(N), z(1), z(1)
+            btv.btv_tree_accept_stochastic_tuned(x, marg, parent, tok, u, path, n, b, ws, most)
+            res.append((int(n), path[:int(n)].tolist(), int(b)))
+        assert res[0] == res[1] == res[2], (kind, res)
+    assert btv.btv_workspace_status(ws) == 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("V", [257, 300, 511, 1021, 4089, 4095, 4096, 4103, 8190, 8193, 8201, 12287])
 def test_greedy_rows_at_any_element(G, oracle, V, dtype):
     """The first row, and with it all others, begins 0 .. 7 elements behind a multiple of 16 bytes.  The largest value is among a row's or a unit's first and
