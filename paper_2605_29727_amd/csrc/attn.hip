@@ -1778,17 +1778,19 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // The stretches lie one after the other, request after request, KV head after KV head (so an XCD keeps to one head or
 // two), and team k takes what lies between k w and (k + 1) w; where that cuts a stretch, tv_combine_batch
 // merges the parts.  A cut less than MARGIN tiles from where a stretch's tiles begin or end moves there.  A stretch of up to
-// SMALL tiles is not cut: the team that its beginning falls to does all of it.
+// SMALL tiles is not cut: the team that its beginning falls to does all of it.  Both make shares uneven by as much as they are long, and that costs
+// more than the pieces they save (8 and 16 tiles: the fullest share of 32 requests of 100 to 4000 tokens was 242 of 174 on average, now 195).
 // Where trees may take several row blocks a team is a pair of workgroups (neighbours on one XCD, running side by side): a
 // stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
 // first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
 // (if it is small, one of them takes it alone).
 // Bound by the tiles (1.08 us each in bf16 pieces of more than 128 rows, 0.79 below; FP8 0.61 in pieces of more than 64 rows, 0.44 below), by
-// the shares' unevenness (14 of 160 us for 8 requests of 1k to 16k with 32 to 128 nodes, 15 of 55 for 32 small ones over FP8, whose
-// time follows these weights within 5 %) and by the pieces: 7 to 8.6 us each beyond its tiles (finding it 1, page ids and first tiles 3, merging
-// and storing 3, waiting for the other waves 1), START and MARGIN come from that.  The figures beside the choice of the form
+// by the pieces: 7 to 8.6 us each beyond its tiles (finding it 1, page ids and first tiles 3, merging
+// and storing 3, waiting for the other waves 1), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
+// 8 requests of 1k to 16k, bf16 156 / 155 / 152; 32 of 100 to 4000, FP8 59.7 / 52.8 / 50.9; 5 of up to 8k with 83 nodes 58.5 / 51.8 / 53.8; 9 of up to 9k with
+// 12 42.0 / 39.7 / 39.9; 14 of up to 6k, FP8 67.4 / 65.4 / 65.0.  The figures beside the choice of the form
 // (short_batch) are the whole call's, before and after.
-constexpr int WHOLE = 3, PART = 2, START = 8 * WHOLE, MARGIN = 8, SMALL = 16;
+constexpr int WHOLE = 3, PART = 2, START = 10 * WHOLE, MARGIN = 2, SMALL = 8;
 struct Stretch { int t, du, wt, sl, len; };             // tiles; whole stretches; weight of the last; length of the halved one; all
 __device__ __forceinline__ Stretch stretch_of(const AttnParams &p, const Req &q)
 {
@@ -2381,21 +2383,22 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
 // themselves: how many teams of them the chip holds and the smallest share (slots: a stretch of the longest request gets that
 // many parts where the average one is 2.5 times shorter; longer ones larger parts).
 struct PlanB { int rw, wr_log2, pairing, teams_log2, slots, wmin, sps, row_blocks; bool merge; };
-// The plan that the workgroups make themselves pays where they have much to do, or a few long requests leave a grid of parts
-// ragged (64-row tiles per CU at most: 161 us against 217 for 8 requests of 5k to 15k with 35 to 115 nodes, 63 against 80 for 8 x 8k with 32);
-// below, its larger row blocks and the longer way to the first tile cost more than an even load gives (14 requests
-// of 256 to 4k with up to 46 nodes: 62 us against 53).
-bool short_batch(int rows_g, int t, int Hkv, int D, int batch, int eb)
+// The plan that the workgroups make themselves pays where they have much to do (64-row tiles per CU at most, of 128 channels; t: tiles of the longest
+// request); below, its larger row blocks and the longer way to the first tile cost more than an even load gives.  us, a grid of parts / the plan, of 70
+// batches: 72 tiles per CU, t = 208 51.5 / 45.4; 92, t = 147 42.1 / 37.1; 118, t = 135 35.1 / 37.6; 119, t = 42 31.3 / 46.9; 165, t = 96 48.0 / 46.6; D = 64, 31 (of
+// 128 channels), t = 331 20.0 / 24.3, 49, t = 251 26.6 / 27.0, 68, t = 435 32.0 / 26.8, 72, t = 221 32.0 / 27.6; 52, t = 72 22.4 / 23.1; 233, FP8, t = 248
+// 69.1 / 61.0.
+bool short_batch(int rows_g, int t, int Hkv, int D, int batch)
 {
     const long long tiles_cu = (long long)Hkv * batch * ((rows_g + 63) >> 6) * t / 256;
-    return tiles_cu * D < 220 * 128 && !(t >= 250 && tiles_cu >= (eb == 2 ? 60 : 100));
+    return tiles_cu * D < 220 * 128 && !(t >= 90 && tiles_cu * D * t >= 13000ll * 128);
 }
 
 PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, int eb)
 {
     PlanB b = {};
     const int G = Hq / Hkv, rows_g = G * M_max, t = (L_max + M_max + TK - 1) / TK;
-    if (short_batch(rows_g, t, Hkv, D, batch, eb)) {
+    if (short_batch(rows_g, t, Hkv, D, batch)) {
         b.rw = 2; b.wr_log2 = 6;
         b.row_blocks = (rows_g + 63) >> 6;
         const int base = Hkv * batch * b.row_blocks;
@@ -2470,7 +2473,7 @@ size_t enough_for_batch(int batch, int M_max, int L_max, int Hq, int Hkv, int D,
     long long most = 0;
     if (t >= 64) most = rows * std::min(8, t / 32);
     if (t >= 16) most = std::max({ most, std::min<long long>(rows * std::min(32, t / 8), 1024 * 64), std::min<long long>(one * std::min(512, t / 8), 512 * 64) });
-    if (!short_batch(rows_g, t, Hkv, D, batch, eb)) {
+    if (!short_batch(rows_g, t, Hkv, D, batch)) {
         const long long spread = 640 * 128 * (rows_g <= 128 ? 1 : eb == 1 || rows_g <= 256 ? 2 : 4);
         most = std::max(most, std::min(rows * 32, std::max(rows * 8, rows * 4 + spread)));
     }

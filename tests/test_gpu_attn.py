@@ -300,8 +300,7 @@ def test_paged_ragged_several_splits(G, oracle):
 
 
 def long_batch(batch, M_max, L_long, long_at):
-    """Request sizes around the edges of the plan of a batch with much to do: stretches of tiles that are not cut (up to 16 tiles),
-    just longer ones, no prefix at all, one very long request; trees around the ends of row blocks."""
+    """Request sizes around the edges of the plan of a batch with much to do: stretches of 16 tiles, just longer ones, no prefix at all, one very long request; trees around the ends of row blocks."""
     Ls = [(0, 1, 31, 32, 495, 511, 513, 530, 700)[r % 9] for r in range(batch)]
     Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
     Ls[long_at] = L_long
@@ -317,6 +316,14 @@ def long_batch(batch, M_max, L_long, long_at):
 def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long, long_at, Hq, Hkv, D):
     Ls, Ns = long_batch(batch, M_max, L_long, long_at)
     _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=65)
+
+
+@pytest.mark.parametrize("batch, M_max, L_long, long_at, Hq, Hkv, D", [(66, 33, 3200, 60, 16, 2, 128), (70, 16, 8100, 0, 16, 2, 128), (130, 9, 8100, 64, 16, 4, 64)])
+def test_paged_batches_around_stretches_that_are_cut(G, oracle, batch, M_max, L_long, long_at, Hq, Hkv, D):
+    """Stretches of 6 to 13 tiles: up to 8 are not cut, a cut within two of an end moves there, beside one that many workgroups share."""
+    Ls, Ns = long_batch(batch, M_max, L_long, long_at)
+    Ls = [(180, 222, 230, 255, 256, 270, 289, 320, 350, 383, 400)[r % 11] if r != long_at else l for r, l in enumerate(Ls)]
+    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=67)
 
 
 @pytest.mark.parametrize("M, L", [(1, 24000), (9, 9000), (130, 24000)])     # many parts; more than 32; the work shared out
