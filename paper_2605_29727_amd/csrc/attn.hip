@@ -1752,11 +1752,14 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
     const int uq = quotient(slot, p.row_blocks, p.inv_row_blocks), by = slot - uq * p.row_blocks, unit = uq * 8 + xcd;
     if (unit >= p.units) return;
     Piece pc = {};
-    // The part is rotated by the (request, head) number.  Without it a number of parts that is a multiple of 8 ties part i
-    // to XCD i % 8, and the requests with few parts load only the first XCDs.
-    const int bz = quotient(unit, p.nsplit, p.inv_nsplit), turned = unit - bz * p.nsplit + 3 * bz;
-    pc.bx = turned - quotient(turned, p.nsplit, p.inv_nsplit) * p.nsplit;
+    // The part is rotated by the request (and the head).  Without it part i of a head is on the same XCD in every request, or on the
+    // same few, and as all requests have a first part and only the longest a last one, some XCDs have most of the work: rotated by the
+    // (request, head) number, which comes to the same for an even number of parts, 29 requests of up to 2347 keys with 30 nodes took
+    // 69 us, now 61; 31 of up to 3181 with 10 65.5 and 58.
+    const int bz = quotient(unit, p.nsplit, p.inv_nsplit);
     pc.rq = quotient(bz, p.Hkv, p.inv_Hkv); pc.g = bz - pc.rq * p.Hkv; pc.by = by;
+    const int turned = unit - bz * p.nsplit + 3 * pc.g + pc.rq;
+    pc.bx = turned - quotient(turned, p.nsplit, p.inv_nsplit) * p.nsplit;
     const Req rq = load_req<true>(p, pc.rq);
     if (!rq.ok) {
         if (threadIdx.x == 0 && by == 0 && pc.bx == 0 && pc.g == 0) atomicOr(p.flag, 2u);
@@ -2402,11 +2405,20 @@ PlanB make_batch_plan(int M_max, int L_max, int Hq, int Hkv, int D, int batch, i
         b.rw = 2; b.wr_log2 = 6;
         b.row_blocks = (rows_g + 63) >> 6;
         const int base = Hkv * batch * b.row_blocks;
-        // One request: as in the contiguous form.  More: parts of 32 tiles even out the lengths; where that leaves the chip room
-        // (it takes 512 of these workgroups at once), parts of 8 tiles or more for one such round of the longest request, of
-        // 20 or more for two rounds (2 requests of up to 2.4k with 26 nodes took 31 us in 2 parts and take 15 in 9).
-        int want = batch == 1 ? std::min((rows_g <= 64 ? 512 : 256) / base, t / 8) : std::min(8, t / 32);
-        if (batch > 1 && base < 256) want = std::max(want, std::min(32, std::max(std::min(512 / base, t / 8), std::min(1024 / base, t / 20))));
+        // One request: as in the contiguous form.  More: parts of 32 tiles even out the lengths, or of 24 where the workgroups of the
+        // whole requests are few (17 requests of up to 1.8k keys with 22 nodes 35.5 us in one part and 26.8 in two, 31 of up to 2.6k
+        // with 49, D = 64, 32.6 in two and 27.7 in three; but 30 of up to 2k with 40 49 and 61).  Where that leaves the chip room (it
+        // takes 512 of these workgroups at once, but two that share a CU take longer), parts of 4 tiles or more for a workgroup per
+        // CU, of 8 or more for two of the longest request, of 16 or more for two rounds of those (2 requests of up to 2.4k with 26
+        // nodes took 31 us in 2 parts and take 15 in 9; 7 of up to 1k with 8 13.8 in 3 and 12.0 in 4; 2 of up to 5.7k with 66 26.5
+        // in 6 and 23.1 in 8), if a part is more than 10 tiles shorter than the whole: the partials and their merge cost as much
+        // (6 of up to 463, D = 64, 9.4 in one and 8.4 in 4; 10 of up to 270 8.7 in one and 10.0 in 3).
+        int want = batch == 1 ? std::min((rows_g <= 64 ? 512 : 256) / base, t / 8) : std::min(8, t / (base < 512 ? 24 : 32));
+        if (batch > 1 && base < 256) {
+            const int one = std::min(256 / base, (t + 3) / 4), two = std::min(512 / base, t / 8);
+            const int by = std::min(32, std::max(2 * two >= 3 * one ? two : one, std::min(1024 / base, t / 16)));
+            if (by > 1 && t - (t + by - 1) / by > 10) want = std::max(want, by);
+        }
         b.sps = ((t + std::max(1, want) - 1) / std::max(1, want) + 1) & ~1;                // whole rounds of two tiles
         b.slots = (t + b.sps - 1) / b.sps;
         b.merge = b.slots > 1;
@@ -2462,16 +2474,18 @@ size_t enough_for(int M, int L, int Hq, int Hkv, int D, int eb, int force_split 
 }
 
 // The same for a batch: up to `batch` requests, M_max nodes, L_max keys.  Fewer or smaller requests are cut into more parts, so their
-// partials may be the more.  Of make_batch_plan's forms: a short batch takes up to 8 parts of 32 tiles or more; where its grid is
-// small, up to 32 parts (512 of one request) of 8 tiles or more, in no more than 1024 (512) workgroups of 64 rows; the others 8
-// parts, or 4 and their share of (5 << teams_log2) pieces, which is 640 row blocks, 1280 where they go in pairs.  All of it grows with
-// the sizes, and so does what makes a batch one of the others.  8 x 128 nodes over 16k keys 124.9 MB, which is that plan's own need.
+// partials may be the more.  Of make_batch_plan's forms: a short batch takes up to 8 parts of 24 tiles or more; where its grid is
+// small, up to 32 parts of 4 tiles or more in no more than 256 workgroups of 64 rows, or of 8 tiles or more in no more than 1024
+// (one request: 512 parts in 512); the others 8 parts, or 4 and their share of (5 << teams_log2) pieces, which is 640 row blocks, 1280
+// where they go in pairs.  All of it grows with the sizes, and so does what makes a batch one of the others.  8 x 128 nodes over 16k
+// keys 124.9 MB, which is that plan's own need.
 size_t enough_for_batch(int batch, int M_max, int L_max, int Hq, int Hkv, int D, int eb)
 {
     const int rows_g = Hq / Hkv * M_max, t = (L_max + M_max + TK - 1) / TK;
     const long long rows = (long long)batch * M_max * Hq, one = (long long)M_max * Hq;
     long long most = 0;
-    if (t >= 64) most = rows * std::min(8, t / 32);
+    if (t >= 48) most = rows * std::min(8, t / 24);
+    if (t >= 12) most = std::max(most, std::min<long long>(rows * std::min(32, (t + 3) / 4), 256 * 64));
     if (t >= 16) most = std::max({ most, std::min<long long>(rows * std::min(32, t / 8), 1024 * 64), std::min<long long>(one * std::min(512, t / 8), 512 * 64) });
     if (!short_batch(rows_g, t, Hkv, D, batch)) {
         const long long spread = 640 * 128 * (rows_g <= 128 ? 1 : eb == 1 || rows_g <= 256 ? 2 : 4);
