@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libbastion_tv.so")
 FACE = os.path.join(HERE, "_face.so")
-SOURCES = ["api.hip", "attn.hip", "tree_build.hip", "accept.hip", "stochastic.hip", "kv_commit.hip"]
+SOURCES = ["api.hip", "attn.hip", "tree_build.hip", "accept.hip", "lm_head.hip", "stochastic.hip", "kv_commit.hip"]
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 VALU ops on this target.
 # Kernel arguments that are scalars or pointers come in registers with a wavefront's start (the first 14 words of them) instead of by loads

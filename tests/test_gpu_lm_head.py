@@ -65,6 +65,16 @@ def test_shapes_chosen_by_size(oracle, gpu, M, h, V):
         assert _check(oracle, xf, wf, parent, token, gpu.run_accept_greedy_lm_head(xs, ws, parent, token)) >= (M + 1) // 2
 
 
+@pytest.mark.parametrize("M,h,V", [(1, 128, 40001), (16, 384, 33000), (33, 128, 24577), (47, 256, 30001), (95, 384, 24600), (127, 128, 33000),
+                                   (150, 128, 32769), (191, 256, 33333), (223, 128, 82001), (255, 128, 41000), (256, 128, 50001), (100, 256, 90000)])
+def test_shares_of_large_vocabularies(oracle, gpu, M, h, V):
+    """Shares of one and of several rounds, the last one ragged, and every arrangement of the waves (by rows and tokens of a CU)."""
+    parent = synth.tree_parents(5, M, "random")
+    token = synth.sibling_distinct_tokens(5, parent, V)
+    xs, xf, ws, wf = synth.lm_head(5, M + 1, h, V, "bf16")
+    assert _check(oracle, xf, wf, parent, token, gpu.run_accept_greedy_lm_head(xs, ws, parent, token)) >= (M + 1) // 2
+
+
 def test_planted_path_is_accepted(oracle, gpu):
     M, h, V = 64, 512, 5000
     parent = synth.tree_parents(3, M, "deep")
