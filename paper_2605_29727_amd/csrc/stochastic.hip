@@ -316,7 +316,7 @@ struct SaShared {
     double F[SA_CHAIN][SA_MAX_WGS], GW[SA_CHAIN + 1][SA_MAX_WGS];
     alignas(16) int acc0[SA_CHAIN];
     int wsum[SA_WAVES];
-    int dead, status, acc, pick, last, late, near;
+    int dead, status, acc, pick, last, late;
     float2 tab[SA_GRID];                                // slope and intercept of G / G_cur over s / s_cur between two points
     double pt[BTV_MAX_NODES], ptG[BTV_MAX_NODES], invT[BTV_MAX_NODES];
     double sE[SA_POINTS], sQ[SA_POINTS], part[SA_T];
@@ -326,6 +326,7 @@ struct SaShared {
                                                         // below 64 KB is addressed with the instructions' own offsets)
     static constexpr bool KEEP = BT == 4;               // (e, q) in the row's order, kept through a fan (8 tokens a thread leave no room for it)
     float2 row[KEEP ? SA_T * BT : 1];
+    int near;                                           // (last: the places of the others matter, 8 bytes further on they cost 0.4 us of 37)
 };
 
 // A walk that goes down mostly takes first children (they have the largest draft probability), so the rows of a node, its
@@ -366,7 +367,10 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
         if (c <= M) L.uni[c] = p.uniforms[c];
     }
-    if (tid == 0) { L.dead = 0; L.late = 0; L.near = 0; }
+    if (tid == 0) {
+        L.dead = 0; L.late = 0;
+        if constexpr (NEAR) L.near = 0;
+    }
     base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     uint32_t seq = 0;
     int cur = -1, n = 0, ui = 0, d = 0;
