@@ -1985,18 +1985,37 @@ __device__ __forceinline__ float row32_sum(float x, int lane)
     return x + __uint_as_float((lane & 16) ? sw[0] : sw[1]);
 }
 
-template <int D>
-__device__ __forceinline__ void store_row(const AttnParams &p, size_t row, int lane, const float (&acc)[D / 32], float inv)
+// Over the N = 8, 16 or 32 lanes of a row.
+template <int N>
+__device__ __forceinline__ float lanes_max(float x)
 {
-    constexpr int E = D / 32;
+    if (N == 32) return row32_max(x, (int)threadIdx.x);
+    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0xB1, 0xF, 0xF, false)));
+    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x4E, 0xF, 0xF, false)));
+    x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x141, 0xF, 0xF, false)));
+    return N == 8 ? x : fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x140, 0xF, 0xF, false)));
+}
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x)
+{
+    if (N == 32) return row32_sum(x, (int)threadIdx.x);
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0xB1, 0xF, 0xF, false));
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x4E, 0xF, 0xF, false));
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x141, 0xF, 0xF, false));
+    return N == 8 ? x : x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x140, 0xF, 0xF, false));
+}
+
+// E = 2, 4 or 8 channels per lane
+template <int D, int E>
+__device__ __forceinline__ void store_row(const AttnParams &p, size_t row, int lane, const float (&acc)[E], float inv)
+{
     uint16_t *dst = static_cast<uint16_t *>(p.O) + row * D + lane * E;
-    if (E == 4) {
-        uint32_t lo = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[1] * inv) << 16);
-        uint32_t hi = float_to_bf16_bits(acc[E - 2] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
-    } else {
-        *reinterpret_cast<uint32_t *>(dst) = float_to_bf16_bits(acc[0] * inv) | (float_to_bf16_bits(acc[E - 1] * inv) << 16);
-    }
+    uint32_t x[E / 2];
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) x[e] = float_to_bf16_bits(acc[2 * e] * inv) | (float_to_bf16_bits(acc[2 * e + 1] * inv) << 16);
+    if constexpr (E == 8) *reinterpret_cast<uint4 *>(dst) = make_uint4(x[0], x[1], x[2], x[3]);
+    else if constexpr (E == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(x[0], x[1]);
+    else *reinterpret_cast<uint32_t *>(dst) = x[0];
 }
 
 template <int D>
@@ -2050,7 +2069,7 @@ __device__ __forceinline__ void combine_row(const AttnParams &p, size_t row, int
     }
     den = row32_sum(den, (int)threadIdx.x);
     const float inv = p.out_scale / den;
-    store_row<D>(p, row, lane, acc, inv);
+    store_row<D, E>(p, row, lane, acc, inv);
 }
 
 template <int D>
@@ -2065,11 +2084,15 @@ __global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
 }
 
 // The same for a batch: how many parts a row has follows from where its request's work lies (the plan that the attention's first
-// workgroup left).
-template <int D>
+// workgroup left).  What bounds it is the chain of the request's place, the parts and the sums: lanes of E channels, the first PARTS
+// parts all asked for at once.  With 8 channels a lane has 16-byte loads and half of the wavefronts do, so those of many rows are under way
+// together (8 requests of up to 128 nodes, 32 heads: attention and merge 155.9 -> 149.8 us; 32 of up to 24, FP8, 51.1 -> 49.1); few rows leave the
+// chip room, and D / 32 channels with 16 parts at once are faster (7 requests of 33 nodes, 16 heads, in up to 20 parts: 23.8 and 25.6).
+template <int D, int E, int PARTS>
 __global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
 {
-    __shared__ __attribute__((aligned(16))) float wsh[8][32];
+    constexpr int LPR = D / E, ROWS = 256 / LPR;             // lanes of a row, rows of a workgroup
+    __shared__ __attribute__((aligned(16))) float wsh[ROWS][LPR];
     asm volatile("" ::"s"(p.O), "s"(p.q_offset), "s"(p.prefix_len), "s"(p.Opart), "s"(p.ML), "s"(p.M), "s"(p.L), "s"(p.Hq), "s"(p.G),
                  "s"(p.max_blocks), "s"(p.total_rows), "s"(p.total_M), "s"(p.plan), "s"(p.Hkv), "s"(p.pairing), "s"(p.wr_log2), "s"(p.sps), "s"(p.out_scale));
     const int r = blockIdx.y;
@@ -2077,7 +2100,7 @@ __global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
     long long w = 0, wh = 0, at = 0;
     if (!p.sps) { w = p.plan[0]; wh = p.plan[1]; at = p.plan[2 + r]; }
     if (!q.ok) return;
-    const int lr = blockIdx.x * 8 + (threadIdx.x >> 5);
+    const int lr = blockIdx.x * ROWS + threadIdx.x / LPR;
     if (lr >= q.M * p.Hq) return;
     int n = 1;
     if (p.sps) {                                        // short requests: equal parts
@@ -2096,58 +2119,60 @@ __global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
         if (halved) n *= 2;
     }
     if (n == 1) return;
-    // As combine_row, in groups of eight parts (four loads where there are no more), the next group's loads ahead of this one's
-    // sums: most rows have two to four, and the fewer registers let twice the rows be under way.
-    constexpr int E = D / 32;
+    // The first PARTS parts, in groups of four, are all asked for before the first is looked at.
     typedef _Float16 hvec __attribute__((ext_vector_type(E)));
-    const int rin = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    constexpr int GROUPS = PARTS / 4, TURNS = PARTS > LPR ? PARTS / LPR : 1;
+    const int rin = threadIdx.x / LPR, lane = threadIdx.x % LPR;
     const size_t row = (size_t)q.q0 * p.Hq + lr, sstride = (size_t)p.total_rows;
     auto magnitudes = [&](int s) {
         const float4 x = *reinterpret_cast<const float4 *>(p.ML + (min(s, n - 1) * sstride + row) * 4);
         return s < n ? x : make_float4(NEG_BIG, 0.f, 0.f, 0.f);
     };
     const _Float16 *Pp = p.Opart + row * D + lane * E;
-    hvec part[8], next[8];
-    auto load = [&](hvec (&x)[8], int s0) {
+    hvec part[GROUPS][4];
+    auto load = [&](hvec (&x)[4], int s0) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) x[b] = *reinterpret_cast<const hvec *>(Pp + min(s0 + b, n - 1) * sstride * D);
-        if (s0 + 4 < n) {
-#pragma unroll
-            for (int b = 4; b < 8; ++b) x[b] = *reinterpret_cast<const hvec *>(Pp + min(s0 + b, n - 1) * sstride * D);
-        }
     };
-    float4 ml = magnitudes(lane);
-    load(part, 0);
-    float mmax = ml.x, den = 0.f;
-    for (int s = lane + 32; s < n; s += 32) mmax = fmaxf(mmax, p.ML[(s * sstride + row) * 4]);     // (rare)
-    mmax = row32_max(mmax, (int)threadIdx.x);
+    float4 ml[TURNS];
+#pragma unroll
+    for (int k = 0; k < TURNS; ++k) ml[k] = magnitudes(k * LPR + lane);
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        if (g == 0 || n > 4 * g) load(part[g], 4 * g);
+    float mmax = ml[0].x, den = 0.f;
+#pragma unroll
+    for (int k = 1; k < TURNS; ++k) mmax = fmaxf(mmax, ml[k].x);
+    for (int s = lane + TURNS * LPR; s < n; s += LPR) mmax = fmaxf(mmax, p.ML[(s * sstride + row) * 4]);     // (rare)
+    mmax = lanes_max<LPR>(mmax);
     float acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = 0.f;
-    auto add = [&](const hvec (&x)[8], int at, auto first) {
-        constexpr int F = decltype(first)::value;
-        const float4 wg = *reinterpret_cast<const float4 *>(&wsh[rin][at + F]);
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            acc[e] += wg.x * (float)x[F][e] + wg.y * (float)x[F + 1][e] + wg.z * (float)x[F + 2][e] + wg.w * (float)x[F + 3][e];
+    auto weights = [&](const float4 &m, int s0) {           // of the LPR parts from s0 on, one per lane
+        const float w = s0 + lane < n ? __builtin_amdgcn_exp2f(m.x - mmax) : 0.f;
+        den += w * m.y;
+        wsh[rin][lane] = w * m.z;                           // weight times the part's magnitude; 0 past the last part
+        // (the row's lanes are in one wavefront: its LDS operations complete in order, no barrier needed)
     };
-    for (int s0 = 0; s0 < n; s0 += 8) {
-        const int at = s0 & 31;
-        if (at == 0) {                                      // the next 32 parts' weights, one per lane
-            if (s0) ml = magnitudes(s0 + lane);
-            const float w = s0 + lane < n ? __builtin_amdgcn_exp2f(ml.x - mmax) : 0.f;
-            den += w * ml.y;
-            wsh[rin][lane] = w * ml.z;                      // weight times the part's magnitude; 0 past the last part
-            // (the row's 32 lanes are one half of a wavefront: its LDS operations complete in order, no barrier needed)
-        }
-        if (s0 + 8 < n) load(next, s0 + 8);
-        add(part, at, std::integral_constant<int, 0>{});
-        if (s0 + 4 < n) add(part, at, std::integral_constant<int, 4>{});
+    auto add = [&](const hvec (&x)[4], int at) {
+        const float4 wg = *reinterpret_cast<const float4 *>(&wsh[rin][at]);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) part[b] = next[b];
+        for (int e = 0; e < E; ++e) acc[e] += wg.x * (float)x[0][e] + wg.y * (float)x[1][e] + wg.z * (float)x[2][e] + wg.w * (float)x[3][e];
+    };
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        if (g == 0 || n > 4 * g) {
+            if (4 * g % LPR == 0) weights(ml[4 * g / LPR], 4 * g);
+            add(part[g], 4 * g % LPR);
+        }
+#pragma unroll 1
+    for (int s0 = PARTS; s0 < n; s0 += 4) {
+        if ((s0 & (LPR - 1)) == 0) weights(magnitudes(s0 + lane), s0);
+        load(part[0], s0);
+        add(part[0], s0 & (LPR - 1));
     }
-    const float inv = p.out_scale / row32_sum(den, (int)threadIdx.x);
-    store_row<D>(p, row, lane, acc, inv);
+    const float inv = p.out_scale / lanes_sum<LPR>(den);
+    store_row<D, E>(p, row, lane, acc, inv);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2660,9 +2685,11 @@ int attn_paged(const void *Q, const void *Kpool, const void *Vpool, int num_bloc
         rc = dispatch_bf16<LONG_BATCH>(p, pl.rw, D, eb, dim3(1 << (pl.teams_log2 + pl.pairing)), st);
     }
     if (rc || !pl.merge) return rc;
-    dim3 cg((M_max * Hq + 7) / 8, batch);
-    if (D == 64) hipLaunchKernelGGL(tv_combine_batch<64>, cg, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL(tv_combine_batch<128>, cg, dim3(256), 0, st, p);
+    const int rows = M_max * Hq;
+    auto combine = [&](auto kern, int per) { hipLaunchKernelGGL(kern, dim3((rows + per - 1) / per, batch), dim3(256), 0, st, p); };
+    const bool many = (long long)rows * batch > 12288;
+    if (D == 64) many ? combine(tv_combine_batch<64, 8, 8>, 32) : combine(tv_combine_batch<64, 2, 16>, 8);
+    else many ? combine(tv_combine_batch<128, 8, 8>, 16) : combine(tv_combine_batch<128, 4, 16>, 8);
     BTV_HIP(hipGetLastError());
     return BTV_OK;
 }

@@ -326,6 +326,14 @@ def test_paged_batches_around_stretches_that_are_cut(G, oracle, batch, M_max, L_
     _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=67)
 
 
+@pytest.mark.parametrize("batch, M_max, L, Hq, Hkv, D", [(6, 128, 700, 16, 2, 64), (7, 110, 710, 16, 2, 64), (6, 128, 700, 16, 2, 128), (7, 110, 710, 16, 2, 128),
+                                                         (2, 8, 5000, 8, 1, 128), (2, 9, 5100, 8, 1, 64)])
+def test_paged_batches_of_parts(G, oracle, batch, M_max, L, Hq, Hkv, D):
+    """The merge of a short batch's parts: on either side of the number of rows that changes its lanes, and of more parts than it asks for at once."""
+    Ls, Ns = [L - 13 * r for r in range(batch)], [M_max - r % 3 for r in range(batch)]
+    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=68)
+
+
 @pytest.mark.parametrize("M, L", [(1, 24000), (9, 9000), (130, 24000)])     # many parts; more than 32; the work shared out
 def test_paged_batch_of_one(G, oracle, M, L):
     _paged_case(G, oracle, [L], [M], 16, 2, 128, seed=66)
