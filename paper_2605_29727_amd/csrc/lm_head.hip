@@ -14,10 +14,10 @@
 // the argmax is a scan in registers.  Tiles store the 16-byte chunks of a row XOR-permuted by the row number, so operand
 // reads (16 lanes = 16 different rows) are conflict-free.
 //
-// What bounds it: with up to some 60 rows the rate of memory (64 rows, h = 4096, V = 128256: 1.05 GB in 181 us, 5.8 TB/s,
-// 191 before; 2 rows, h = 4096, V = 128256: 177 us), in short calls the chain of one stage, the merge and the walk (7 rows,
+// What bounds it: with up to some 60 rows the rate of memory (64 rows, h = 4096, V = 128256: 1.05 GB in 162 us, 6.5 TB/s,
+// 191 before; 2 rows, h = 4096, V = 128256: 155 us), in short calls the chain of one stage, the merge and the walk (7 rows,
 // h = 1024, V = 8000 11.5 -> 8.8). With more rows what a CU can get into LDS, some 33 KB per us: all of H (from the L2) for
-// each of its chunks besides W, and the operand reads from LDS (256 rows, h = 4096, V = 128256 329 -> 268).  Tried without
+// each of its chunks besides W, and the operand reads from LDS (256 rows, h = 4096, V = 128256 329 -> 261).  Tried without
 // gain: rings of their own for H (short) and W (long), loaded by waves of their own, 64 rows 183 -> 220; stages of 32
 // (64-byte pieces of W), 247 rows at V = 26424 61 -> 72; leaving out the loads of rows that are not there (their branches
 // cost more), 163 rows at V = 10203 31 -> 36.
@@ -77,10 +77,11 @@ __device__ __forceinline__ LmBest unpacked(unsigned long long x)
     return x ? LmBest{ __uint_as_float(key & 0x80000000u ? key & 0x7FFFFFFFu : ~key), (int)~(uint32_t)x } : LmBest{ -INFINITY, INT_MAX };
 }
 
-// 16 bytes per lane to LDS, lane after lane from `to`
+// 16 bytes per lane to LDS, lane after lane from `to`.  STREAM: marked as read once (2: non-temporal).
+template <bool STREAM>
 __device__ __forceinline__ void load_1k(const unsigned char *from, unsigned char *to)
 {
-    __builtin_amdgcn_global_load_lds(from, LM_LDS_PTR(to), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(from, LM_LDS_PTR(to), 16, 0, STREAM ? 2 : 0);
 }
 __device__ __forceinline__ const unsigned char *uniform(const unsigned char *p)
 {
@@ -135,7 +136,7 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-template <int VT, int RT, int VW, int RW, int KW, int KB>
+template <int VT, int RT, int VW, int RW, int KW, int KB, bool STREAM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_shares(
     const unsigned char *__restrict__ H, const unsigned char *__restrict__ W, int R, int h, int V, int share, int chunks, int stride, LmBest *__restrict__ part)
 {
@@ -175,7 +176,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     auto load = [&](int i) {
         const bool ofW = (i + 1) * S::WAVES <= S::WI || (i * S::WAVES < S::WI && i * S::WAVES + wave < S::WI);    // (mostly a constant)
-        if (i < S::LPW - 1 || S::REM == S::WAVES || wave < S::REM) load_1k((ofW ? fromW : fromH) + off[i], to + i * S::WAVES * 1024);
+        if (i < S::LPW - 1 || S::REM == S::WAVES || wave < S::REM) {
+            if (ofW) load_1k<STREAM>(fromW + off[i], to + i * S::WAVES * 1024);
+            else load_1k<false>(fromH + off[i], to + i * S::WAVES * 1024);
+        }
     };
     auto end = [&]() {
         ++issued;
@@ -369,12 +373,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-template <int VT, int RT, int VW, int RW, int KW, int KB>
+template <int VT, int RT, int VW, int RW, int KW, int KB, bool STREAM>
 int launch(const void *H, const void *W, int R, int h, int V, int share, int chunks, LmBest *part, hipStream_t st)
 {
     using S = Share<VT, RT, VW, RW, KW, KB>;
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
-    auto kern = lm_head_shares<VT, RT, VW, RW, KW, KB>;
+    auto kern = lm_head_shares<VT, RT, VW, RW, KW, KB, STREAM>;
     if (!configured.load(std::memory_order_acquire)) {
         BTV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES));
         configured.store(true, std::memory_order_release);
@@ -393,7 +397,11 @@ int pick(int vt, const void *H, const void *W, int R, int h, int V, int share, i
 {
     if constexpr (VT > 1)
         if (vt < VT) return pick<RT, VW, RW, KW, KB, VT - 1>(vt, H, W, R, h, V, share, chunks, part, st);
-    return launch<VT, RT, VW, RW, KW, KB>(H, W, R, h, V, share, chunks, part, st);
+    // Weights that the last-level cache (256 MB) holds no useful part of from one step to the next are read past it.  us, without / with, the same matrix
+    // again and again: 1050 MB, 64 nodes 182 / 162, 410 MB 58.2 / 58.5, 303 MB 49.7 / 49.1, 270 MB 48.4 / 49.7, 164 MB 30.1 / 32.6; with another one of its
+    // size in between the line lies at 130 MB (390 MB 82 / 72).
+    if ((size_t)V * h * 2 > ((size_t)384 << 20)) return launch<VT, RT, VW, RW, KW, KB, true>(H, W, R, h, V, share, chunks, part, st);
+    return launch<VT, RT, VW, RW, KW, KB, false>(H, W, R, h, V, share, chunks, part, st);
 }
 
 }  // namespace
