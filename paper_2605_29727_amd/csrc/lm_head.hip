@@ -15,7 +15,7 @@
 // reads (16 lanes = 16 different rows) are conflict-free.
 //
 // What bounds it: with up to some 60 rows the rate of memory (64 rows, h = 4096, V = 128256: 1.05 GB in 162 us, 6.5 TB/s,
-// 191 before; 2 rows, h = 4096, V = 128256: 155 us), in short calls the chain of one stage, the merge and the walk (7 rows,
+// 191 before; 4 rows, V = 50000: 72 -> 64 us), in short calls the chain of one stage, the merge and the walk (7 rows,
 // h = 1024, V = 8000 11.5 -> 8.8). With more rows what a CU can get into LDS, some 33 KB per us: all of H (from the L2) for
 // each of its chunks besides W, and the operand reads from LDS (256 rows, h = 4096, V = 128256 329 -> 261).  Tried without
 // gain: rings of their own for H (short) and W (long), loaded by waves of their own, 64 rows 183 -> 220; stages of 32
