@@ -864,9 +864,14 @@ __device__ __forceinline__ void wave_ancestors(const AttnParams &p, uint32_t par
 
 // Largest finite magnitude of a lane's values: what its row's partials are divided by.  (An infinite one, from a value in the
 // cache or a sum past the end of fp32, would leave nothing of the row's other channels.)
-template <int B> __device__ __forceinline__ float finite_max(const f32x16 (&x)[B])
+template <int B> __device__ __forceinline__ float finite_max(f32x16 (&x)[B])
 {
     float a = 0.f;
+    // x may be the result of matrix instructions that are still under way, and the compiler puts no wait states ahead of inline assembly
+    // (ahead of a vector instruction of its own 12 for a 32x32x16).  The maxima follow these by way of a, the x by being passed through.
+#pragma unroll
+    for (int b = 1; b < B; ++b) asm volatile("" : "+v"(x[b]));
+    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(x[0]), "+v"(a));
 #pragma unroll
     for (int b = 0; b < B; ++b)
 #pragma unroll

@@ -249,7 +249,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int j = 0; j < RT; ++j) {
 #pragma unroll
-                for (int i = 0; i < VT; ++i) asm volatile("ds_write_b128 %0, %1" ::"v"(sums + (uint32_t)(kw * PLANE + i * 1024)), "v"(acc[i][j]) : "memory");
+                for (int i = 0; i < VT; ++i)                     // (ordinary stores: ahead of one in inline assembly the compiler would not wait for acc)
+                    *(__attribute__((address_space(3))) f32x4 *)(uintptr_t)(sums + (uint32_t)(kw * PLANE + i * 1024)) = acc[i][j];
                 lgkm_wait<0>();
                 __builtin_amdgcn_s_barrier();
                 for (int i = kw; i < VT; i += KW) {
