@@ -320,7 +320,8 @@ int btv_tree_verify_attn_paged_fp8kv(const void *Q, const void *K8pool, const vo
  * [0,1), consumed in order.  marginals [B,V] fp32 as given to tree_build.
  *   One launch of up to 64 workgroups (no more than CUs that the stream may use), each with a slice of
  *   the vocabulary, that exchange their parts of every vocabulary-wide sum in the workspace and walk
- *   the tree in step.  Where they do not all run at once, because other work holds the CUs, a workgroup
+ *   the tree in step.  (Up to 24 run on one XCD; where one of them does not get a CU there, because other
+ *   work holds them, a workgroup on another XCD stands in for it.)  Where they do not all run at once, a workgroup
  *   that has waited 10 ms for another's part leaves, and one of those that left walks the tree alone:
  *   the results are there all the same, some milliseconds later, and the workspace is fit for the
  *   next call.

@@ -62,11 +62,20 @@ constexpr int SA_WORDS = 4 * SA_POINTS;                 // words of one workgrou
 constexpr int SA_CHAIN = 4;                             // rows of a first-child chain that are read and exchanged together
 constexpr int SA_CHAIN_FAN = 8;                         // children up to which a node's first child is worth reading ahead (it is one of
                                                         // several that the draft likes about as well, otherwise)
-// Up to so many workgroups run on one XCD (every eighth of a grid eight times as large; the others leave at once), and their exchanges stay in
-// its L2.  us, over memory / in the L2: 11 workgroups 39 children rejected 38.7 / 34.5, 16 of them 100 rejected 38.9 / 34.9, a followed draft 28.4 / 28.4 and
-// 34.1 / 33.6 (what the exchanges gain its rows lose, which come through one XCD's share of the memory); 32 workgroups 37.8 / 34.0.  A quarter of the XCD's
-// CUs is left for other streams' work: where fewer are free the walk waits for them, or ends alone.
+// Up to so many workgroups run on one XCD (a grid eight times as large, of which all others but the stand-ins below leave at once), and their exchanges
+// stay in its L2.  us, over memory / in the L2: 11 workgroups 39 children rejected 38.7 / 34.5, 16 of them 100 rejected 38.9 / 34.9, a followed draft 28.4 / 28.4 and
+// 34.1 / 33.6 (what the exchanges gain its rows lose, which come through one XCD's share of the memory); 32 workgroups 37.8 / 34.0.
+// A workgroup takes a CU for itself, of which an XCD has 32, and other work may hold them, another stream's walk for one.  So each slice has a
+// stand-in as well, a workgroup on one of the seven other XCDs: it leaves when it sees that its slice has been taken, and takes it if that has not
+// happened SA_START after its own start.  The first of the two that counts itself in (a word per slice; both of them do in every call, so that an even
+// number is there at its start) has the slice, and the other one leaves whenever it starts.  A walk with a stand-in in it exchanges through memory.  The
+// counting costs 0.5 us of 18 to 28 where the draft is followed and up to 0.3 of 35 in a fan; four streams of walks of 24 workgroups that meet on one XCD take 44 us
+// a call instead of 62.  (The words on lines of their own: no gain.  The count looked at only behind the first rows' loads, for which it has to be held in a
+// register through the loop: 1 us more.)
 constexpr int SA_NEAR = 24;
+constexpr int SA_BASE_WORD = 16, SA_TURN_WORD = 32;     // of the workspace's header: `base`; one word per slice
+static_assert(SA_TURN_WORD + SA_NEAR <= BTV_WS_HEADER / 4, "the header holds them");
+constexpr long long SA_START = 500ll;                   // 5 us
 constexpr int SA_DIRECT = 3;                            // rejections that are walked one by one in any case, one less per 32 children
                                                         // (a node of many children has no likely one among its first)
 constexpr int SA_BATCH_MIN = 10;                        // children left from which the rest is solved at once (the price of ten exchanges)
@@ -340,9 +349,11 @@ __device__ __forceinline__ void sa_move_on(uint32_t *word, uint32_t base, uint32
     __hip_atomic_compare_exchange_strong(word, &base, base + used, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint32_t *sa_turn(const SaParams &p, int slice) { return p.base + (SA_TURN_WORD - SA_BASE_WORD) + slice; }
+
 // ALONE: one workgroup (me = 0) with the whole vocabulary for a slice.  NEAR: the workgroups are dealt out so that they run on one XCD; if the first
-// exchange, which goes through memory, says so of all of them, the others stay in its L2.  Returns whether a wait has passed its limit
-// (the same in all threads; results may then be missing).
+// exchange, which goes through memory, says so of all of them, the others stay in its L2; a workgroup whose slice has been taken leaves.  Returns whether a
+// wait has passed its limit (the same in all threads; results may then be missing).
 template <bool BF16, int PT, bool OVER, bool ALONE, bool NEAR>
 __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int me, uint32_t &base)
 {
@@ -369,8 +380,8 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
     }
     if (tid == 0) {
         L.dead = 0; L.late = 0;
-        if constexpr (NEAR) L.near = 0;
     }
+    if (NEAR && tid == 0) L.near = __hip_atomic_fetch_add(sa_turn(p, me), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u ? -1 : 0;
     base = G > 1 ? __hip_atomic_load(p.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     uint32_t seq = 0;
     int cur = -1, n = 0, ui = 0, d = 0;
@@ -381,6 +392,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         atomicAdd(&L.fan[L.par[tid] + 1], 1);
     }
     __syncthreads();
+    if (NEAR && __builtin_expect(__builtin_amdgcn_readfirstlane(L.near) < 0, 0)) return false;
     for (;;) {
         forget();
         // ---- the chain from cur, this wavefront group's row of it --------------------------------------------------
@@ -984,8 +996,21 @@ __global__ __launch_bounds__(SA_T) void stochastic_walk(SaParams p)
 {
     __shared__ SaShared<PT> L;
     uint32_t base;
-    if (NEAR && (blockIdx.x & 7)) return;               // (ids that are congruent mod 8 run on one XCD)
-    if (!sa_walk<BF16, PT, OVER, false, NEAR>(p, L, NEAR ? blockIdx.x >> 3 : blockIdx.x, base)) return;
+    const int me = NEAR ? blockIdx.x >> 3 : blockIdx.x;
+    if constexpr (NEAR) {                               // (ids that are congruent mod 8 run on one XCD)
+        const int from = blockIdx.x & 7;
+        if (from != 0 && from != 1 + me % 7) return;
+        if (from != 0) {                                // a stand-in
+            if (threadIdx.x < 64) {
+                const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+                __builtin_amdgcn_s_sleep(72);           // (2 us, by which a slice is taken as a rule)
+                while (!(__hip_atomic_load(sa_turn(p, me), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u) && (long long)__builtin_amdgcn_s_memrealtime() - t0 < SA_START)
+                    __builtin_amdgcn_s_sleep(16);
+            }
+            __syncthreads();
+        }
+    }
+    if (!sa_walk<BF16, PT, OVER, false, NEAR>(p, L, me, base)) return;
     auto again = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(again));
     const SaArgs args = (SaArgs)again;
@@ -1055,7 +1080,7 @@ extern "C" int btv_tree_accept_stochastic_tuned(const void *logits, int dtype, c
     p.logits = logits; p.marg = marginals; p.uniforms = uniforms; p.parent = parent; p.token = token;
     p.path = path; p.n_acc = n_acc; p.bonus = bonus;
     p.flag = static_cast<uint32_t *>(ws);
-    p.base = static_cast<uint32_t *>(ws) + 16; p.claim = static_cast<u64 *>(ws) + 9;
+    p.base = static_cast<uint32_t *>(ws) + SA_BASE_WORD; p.claim = static_cast<u64 *>(ws) + 9;
     p.slots = reinterpret_cast<u64 *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
     p.B = B; p.M = M; p.V = V; p.G = a.G; p.per = a.per; p.wait_ticks = wait_ticks;
     if (dtype == BTV_BF16) sa_launch<true>(a, p, st);

@@ -95,6 +95,45 @@ def test_stochastic_exchanges_in_one_l2_and_through_memory(G, V, dtype):
     assert btv.btv_workspace_status(ws) == 0
 
 
+@pytest.mark.parametrize("V, walks", [(20001, 4), (40000, 2), (49152, 3), (49152, 4)])
+def test_stochastic_walks_on_several_streams(G, V, walks):
+    """Walks that are laid out for one XCD, each on a stream and a workspace of its own: the results of a walk that has the chip to itself, and none of
+    them waits for another until its limit and is done alone.  Every slice has been counted in twice per call."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    N, B, calls = 100, 4, 20
+    g = torch.Generator(device="cuda"); g.manual_seed(V)
+    marg = torch.softmax(3 * torch.randn((B, V), generator=g, device="cuda"), 1)
+    x = torch.randn((N + 1, V), generator=g, device="cuda") * 3
+    u = torch.rand(N + 1, generator=g, device="cuda")
+    parent = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    tok = marg[0].argsort(descending=True)[:N].to(torch.int32)
+    ws = [btv.alloc_workspace(btv.btv_tree_accept_workspace(N, V, True)) for _ in range(walks)]
+    out = lambda: [torch.zeros(n, dtype=torch.int32, device="cuda") for n in (N, 1, 1)]
+    ref = out()
+    btv.btv_tree_accept_stochastic(x, marg, parent, tok, u, *ref, ws[0])
+    outs = [[out() for _ in range(calls)] for _ in range(walks)]
+    streams = [torch.cuda.Stream() for _ in range(walks)]
+    sink = torch.zeros(4096, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    btv.btv_mfma_peak(256, 20000, sink)                          # (2 ms: all calls are queued behind it)
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    for k in range(calls):
+        for s, w, o in zip(streams, ws, outs):
+            with torch.cuda.stream(s):
+                btv.btv_tree_accept_stochastic(x, marg, parent, tok, u, *o[k], w)
+    torch.cuda.synchronize()
+    for w, o in zip(ws, outs):
+        for path, n, bonus in o:
+            assert int(n) == int(ref[1]) and int(bonus) == int(ref[2]) and torch.equal(path[:int(n)], ref[0][:int(n)])
+        assert w[72:80].view(torch.int32).tolist() == [0, 0]     # nobody has claimed a walk alone
+        ran = calls + (w is ws[0])
+        slices = -(-V // 2048)
+        assert w[128:256].view(torch.int32).tolist() == [2 * ran] * slices + [0] * (32 - slices)
+        assert btv.btv_workspace_status(w) == 0
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("V", [257, 300, 511, 1021, 4089, 4095, 4096, 4103, 8190, 8193, 8201, 12287])
 def test_greedy_rows_at_any_element(G, oracle, V, dtype):
