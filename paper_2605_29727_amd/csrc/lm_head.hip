@@ -393,19 +393,17 @@ int launch(const void *H, const void *W, int R, int h, int V, int share, int chu
     return BTV_OK;
 }
 
-template <int RT, int VW, int RW, int KW, int KB, int VT>
+template <int RT, int VW, int RW, int KW, int KB, int LEAST, int VT>
 int pick(int vt, const void *H, const void *W, int R, int h, int V, int share, int chunks, LmBest *part, hipStream_t st)
 {
-    if constexpr (VT > 1)
-        if (vt < VT) return pick<RT, VW, RW, KW, KB, VT - 1>(vt, H, W, R, h, V, share, chunks, part, st);
+    if constexpr (VT > LEAST)
+        if (vt < VT) return pick<RT, VW, RW, KW, KB, LEAST, VT - 1>(vt, H, W, R, h, V, share, chunks, part, st);
     // Weights that the last-level cache (256 MB) holds no useful part of from one step to the next are read past it.  us, without / with, the same matrix
     // again and again: 1050 MB, 64 nodes 182 / 162, 410 MB 58.2 / 58.5, 303 MB 49.7 / 49.1, 270 MB 48.4 / 49.7, 164 MB 30.1 / 32.6; with another one of its
     // size in between the line lies at 130 MB (390 MB 82 / 72).
     if ((size_t)V * h * 2 > ((size_t)384 << 20)) return launch<VT, RT, VW, RW, KW, KB, true>(H, W, R, h, V, share, chunks, part, st);
     return launch<VT, RT, VW, RW, KW, KB, false>(H, W, R, h, V, share, chunks, part, st);
 }
-
-}  // namespace
 
 // Which arrangement, by the rows and by the tokens of a CU (`rows`):
 //   LM_FEW   waves over the contraction: all waves have all rows, which is the fewest operand reads for few rows, and 256-byte pieces of memory
@@ -416,7 +414,7 @@ int pick(int vt, const void *H, const void *W, int R, int h, int V, int share, i
 // V = 20296 43.9 / 39.5; 116 at h = 2048, V = 24000 27.6 / 26.1; 154 at h = 3328, V = 78883 116 / 145.
 // As many tokens at once as the sums and a ring of three stages leave room for (LM_FEW, one row, V = 44928, h = 1920: 176 at once,
 // in two stages, 36.0, two times 88 34.5).
-LmShares lm_shares(int R, int V)
+constexpr LmShares shares_of(int R, int V)
 {
     const int rt = (R + 15) / 16, rows = (V + 255) / 256;
     LmShares p = {};
@@ -430,18 +428,43 @@ LmShares lm_shares(int R, int V)
     return p;
 }
 
+// The fewest tiles of 16 tokens a wave that shares of this form come to, for lo to hi tiles of 16 rows.
+constexpr int least_tiles(LmForm form, int lo, int hi)
+{
+    int least = INT_MAX;
+    for (int rt = lo; rt <= hi; ++rt)
+        for (int rows = 1; rows <= 1024; ++rows) {               // (per CU; more of them are cut into several rounds, of half of what fits at least)
+            const LmShares p = shares_of(rt * 16, rows * 256);
+            if (p.form == form) least = std::min(least, p.vt);
+        }
+    return least;
+}
+
+}  // namespace
+
+LmShares lm_shares(int R, int V) { return shares_of(R, V); }
+
 int lm_head_launch(const LmShares &p, const void *H, const void *W, int R, int h, int V, LmBest *part, hipStream_t st)
 {
     const int t = (R + 15) / 16;
-#define LM_SHARES(rows, rt, vw, rw, kw, kb, vts) if (t <= rows) return pick<rt, vw, rw, kw, kb, vts>(p.vt, H, W, R, h, V, p.share, p.chunks, part, st);
+#define LM_SHARES(form_, lo, rows, rt, vw, rw, kw, kb, least, vts)                                                                      \
+    if (t <= rows) {                                                                                                                 \
+        static_assert(least_tiles(form_, lo, rows) == least, "every kernel can be reached");                                         \
+        return pick<rt, vw, rw, kw, kb, least, vts>(p.vt, H, W, R, h, V, p.share, p.chunks, part, st);                               \
+    }
     if (p.form == LM_TALL) {
-        LM_SHARES(8, 2, 2, 4, 1, 64, 4) LM_SHARES(12, 3, 2, 4, 1, 64, 4) LM_SHARES(16, 4, 2, 4, 1, 64, 4) LM_SHARES(20, 5, 2, 4, 1, 64, 4)
+#define LM_ROWS(lo, rows, rt, least, vts) LM_SHARES(LM_TALL, lo, rows, rt, 2, 4, 1, 64, least, vts)
+        LM_ROWS(7, 8, 2, 1, 4) LM_ROWS(9, 12, 3, 1, 4) LM_ROWS(13, 16, 4, 1, 4) LM_ROWS(17, 20, 5, 1, 4)
+#undef LM_ROWS
     } else if (p.form == LM_WIDE) {
-        LM_SHARES(4, 2, 4, 2, 1, 64, 5) LM_SHARES(6, 3, 4, 2, 1, 64, 5) LM_SHARES(8, 4, 4, 2, 1, 64, 5) LM_SHARES(10, 5, 4, 2, 1, 64, 5) LM_SHARES(12, 6, 4, 2, 1, 64, 5)
-        LM_SHARES(14, 7, 4, 2, 1, 64, 5) LM_SHARES(16, 8, 4, 2, 1, 64, 5) LM_SHARES(18, 9, 4, 2, 1, 64, 4)
+#define LM_ROWS(lo, rows, rt, least, vts) LM_SHARES(LM_WIDE, lo, rows, rt, 4, 2, 1, 64, least, vts)
+        LM_ROWS(3, 4, 2, 2, 5) LM_ROWS(5, 6, 3, 1, 5) LM_ROWS(7, 8, 4, 3, 5) LM_ROWS(9, 10, 5, 3, 5) LM_ROWS(11, 12, 6, 3, 5)
+        LM_ROWS(13, 14, 7, 3, 5) LM_ROWS(15, 16, 8, 3, 5) LM_ROWS(17, 18, 9, 3, 4)
+#undef LM_ROWS
     } else {
-        LM_SHARES(1, 1, 2, 1, 4, 128, 4) LM_SHARES(2, 2, 2, 1, 4, 128, 4) LM_SHARES(3, 3, 2, 1, 4, 128, 3) LM_SHARES(4, 4, 2, 1, 4, 128, 3)
-        LM_SHARES(5, 5, 2, 1, 4, 128, 3) LM_SHARES(6, 6, 2, 1, 4, 128, 2)
+#define LM_ROWS(rows, least, vts) LM_SHARES(LM_FEW, rows, rows, rows, 2, 1, 4, 128, least, vts)
+        LM_ROWS(1, 1, 4) LM_ROWS(2, 1, 4) LM_ROWS(3, 1, 3) LM_ROWS(4, 1, 3) LM_ROWS(5, 1, 3) LM_ROWS(6, 1, 2)
+#undef LM_ROWS
     }
 #undef LM_SHARES
     return btv_fail(BTV_EINVAL, "no LM-head kernel for %d rows", R);
