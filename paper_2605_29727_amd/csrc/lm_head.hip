@@ -398,10 +398,12 @@ int pick(int vt, const void *H, const void *W, int R, int h, int V, int share, i
 {
     if constexpr (VT > LEAST)
         if (vt < VT) return pick<RT, VW, RW, KW, KB, LEAST, VT - 1>(vt, H, W, R, h, V, share, chunks, part, st);
-    // Weights that the last-level cache (256 MB) holds no useful part of from one step to the next are read past it.  us, without / with, the same matrix
-    // again and again: 1050 MB, 64 nodes 182 / 162, 410 MB 58.2 / 58.5, 303 MB 49.7 / 49.1, 270 MB 48.4 / 49.7, 164 MB 30.1 / 32.6; with another one of its
-    // size in between the line lies at 130 MB (390 MB 82 / 72).
-    if ((size_t)V * h * 2 > ((size_t)384 << 20)) return launch<VT, RT, VW, RW, KW, KB, true>(H, W, R, h, V, share, chunks, part, st);
+    // Weights of more than half of the last-level cache (256 MB) are read past it.  A step that follows another has read all layers' weights and caches in
+    // between, and then the hint gains at every size; up to half, a caller that comes back sooner finds them in the cache, and loses by the hint more than
+    // the other gains.  us, without / with it, the matrix met again at once | two others of its size in between | 1 GB of other data in between: 65 rows, 82 MB 24.0 / 26.1
+    // | 24.0 / 27.4 | 29.0 / 28.6; 102 MB 27.1 / 27.4 | 27.8 / 28.0 | 30.9 / 29.2; 131 MB 28.2 / 30.2 | 32.4 / 30.6 | 34.3 / 32.2; 164 MB 33.2 / 39.0 | 41.0 / 39.6
+    // | 42.6 / 41.2; 262 MB 47.1 / 48.3 | 53.0 / 48.4 | 54.9 / 50.7; 328 MB 64.3 / 58.2 | 63.8 / 58.4 | 65.6 / 60.6.
+    if ((size_t)V * h * 2 > ((size_t)128 << 20)) return launch<VT, RT, VW, RW, KW, KB, true>(H, W, R, h, V, share, chunks, part, st);
     return launch<VT, RT, VW, RW, KW, KB, false>(H, W, R, h, V, share, chunks, part, st);
 }
 

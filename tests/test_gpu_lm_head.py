@@ -122,6 +122,25 @@ def test_full_vocabulary_8b_shape(oracle, gpu):
     assert _check(oracle, xf, wf, parent, token, got) >= 60
 
 
+@pytest.mark.parametrize("M,h,V", [(15, 8192, 8192), (15, 8192, 8193), (70, 8192, 8199), (120, 8192, 8200), (40, 2816, 25003), (256, 2688, 33001)])
+def test_weights_read_past_the_cache(gpu, M, h, V):
+    """Weights of 128 MB and of more, in every arrangement of the waves, against fp64 sums."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    g = torch.Generator(device="cuda"); g.manual_seed(V + M)
+    W = (torch.randn((V, h), generator=g, device="cuda") * h ** -0.5).to(torch.bfloat16)
+    X = torch.randn((M + 1, h), generator=g, device="cuda").to(torch.bfloat16)
+    i32 = lambda n, x=0: torch.full((n,), x, dtype=torch.int32, device="cuda")
+    n_acc, bonus, top = i32(1), i32(1), i32(M + 1)
+    ws = btv.alloc_workspace(btv.btv_tree_accept_lm_head_workspace(M, V))
+    btv.btv_tree_accept_greedy_lm_head(X, W, i32(M, -1), i32(M, V), i32(M), n_acc, bonus, top, ws)
+    z = torch.cat([X.double() @ W[v:v + 8192].double().T.contiguous() for v in range(0, V, 8192)], 1)
+    best, mine = z.max(1).values, z.gather(1, top.long()[:, None])[:, 0]
+    assert torch.all(mine >= best - AMBIG)
+    assert torch.all((mine == best) | ((z >= best[:, None] - AMBIG).sum(1) > 1))
+    assert int(n_acc) == 0 and int(bonus) == int(top[0])
+
+
 def test_rejects_bad_arguments(gpu):
     import torch
     from paper_2605_29727_amd import binding as btv
