@@ -1799,6 +1799,9 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // 12 42.0 / 39.7 / 39.9; 14 of up to 6k, FP8 67.4 / 65.4 / 65.0.  The figures beside the choice of the form
 // (short_batch) are the whole call's, before and after.
 constexpr int WHOLE = 3, PART = 2, START = 10 * WHOLE, MARGIN = 2, SMALL = 8;
+// A halved stretch of an odd number of tiles has half a step less for its second member.  A cut one step ahead of its end would leave that
+// member's last part empty, nobody would write it, and tv_combine_batch counts it: cuts stay two steps away from the end.
+static_assert(MARGIN >= 2, "both members have tiles in every part");
 struct Stretch { int t, du, wt, sl, len; };             // tiles; whole stretches; weight of the last; length of the halved one; all
 __device__ __forceinline__ Stretch stretch_of(const AttnParams &p, const Req &q)
 {
