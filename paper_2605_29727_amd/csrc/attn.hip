@@ -1009,6 +1009,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     begun();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
     const uint32_t par_lds = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + WL::PAROFF, sets_lds = par_lds + WL::PARENTS;
+    static_assert(WAVES * 64 >= BTV_MAX_NODES, "find_ancestors: a thread per node");
     if (tree_wg && Mr > 64) find_ancestors(p, par_lds, sets_lds, Mr, tid);
     // Operand s holds the 8 channels that contraction step s takes from this lane's half: 16 s + 8 h .. + 7 for
     // bf16 K, 32 (s/2) + 16 h + 8 (s%2) .. + 7 for FP8 K (the order of its 16-byte operand reads).
