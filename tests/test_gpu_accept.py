@@ -134,6 +134,37 @@ def test_stochastic_walks_on_several_streams(G, V, walks):
         assert btv.btv_workspace_status(w) == 0
 
 
+@pytest.mark.parametrize("V, N, step", [(4097, 40, 1), (20001, 100, 1), (20001, 100, 3), (49152, 100, 1), (49152, 100, 5)])
+def test_stochastic_slices_walked_by_stand_ins(G, V, N, step):
+    """Every step-th slice looks as if it had been taken already when its workgroup starts (its count is odd), so that the workgroup leaves and the
+    stand-in on another XCD walks the slice.  The path, the bonus and the counts are those of a walk by the first workgroups."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    g = torch.Generator(device="cuda"); g.manual_seed(V)
+    marg = torch.softmax(3 * torch.randn((4, V), generator=g, device="cuda"), 1)
+    u = torch.rand(N + 1, generator=g, device="cuda")
+    parent = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    parent[N // 2:] = torch.arange(N - N // 2, dtype=torch.int32, device="cuda")
+    tok = marg[0].argsort(descending=True)[:N].to(torch.int32)
+    slices, calls = -(-V // 2048), 3
+    for scale in (3.0, 0.0):                                     # a target of its own; one that follows the draft
+        x = marg.log()[:1] * (scale == 0.0) + torch.randn((N + 1, V), generator=g, device="cuda") * max(scale, 0.2)
+        got = []
+        for odd in (0, 1):
+            ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(N, V, True))
+            turn = ws[128:256].view(torch.int32)
+            turn[:slices:step] = odd
+            want = turn + 2 * calls * (torch.arange(32, device="cuda") < slices)
+            for _ in range(calls):
+                out = [torch.zeros(n, dtype=torch.int32, device="cuda") for n in (N, 1, 1)]
+                btv.btv_tree_accept_stochastic(x, marg, parent, tok, u, *out, ws)
+                got.append([o.tolist() for o in out])
+            assert turn.tolist() == want.tolist()
+            assert ws[72:80].view(torch.int32).tolist() == [0, 0]     # nobody has claimed a walk alone
+            assert btv.btv_workspace_status(ws) == 0
+        assert all(o == got[0] for o in got)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("V", [257, 300, 511, 1021, 4089, 4095, 4096, 4103, 8190, 8193, 8201, 12287])
 def test_greedy_rows_at_any_element(G, oracle, V, dtype):
