@@ -6,11 +6,8 @@
 #include "btv_common.h"
 #include "lm_head.h"
 
-#include <atomic>
-
 #include <algorithm>
 #include <climits>
-#include <cmath>
 #include <type_traits>
 
 namespace {
