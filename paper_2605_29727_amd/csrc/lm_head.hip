@@ -414,8 +414,11 @@ int pick(int vt, const void *H, const void *W, int R, int h, int V, int share, i
 // us, FEW / WIDE: 40 rows, h = 2944, V = 12933 20.2 / 25.7; 65 at h = 2560, V = 22326 26.6 / 29.2; 77 at h = 3328, V = 24774 49 / 40.8; 55
 // at h = 2176, V = 41403 47 / 39.8; 91 at h = 3840, V = 8110 24.1 / 31.3; 81 at h = 1024, V = 16000 16.8 / 15.1.  WIDE / TALL: 247 at h = 2304,
 // V = 20296 43.9 / 39.5; 116 at h = 2048, V = 24000 27.6 / 26.1; 154 at h = 3328, V = 78883 116 / 145.
-// As many tokens at once as the sums and a ring of three stages leave room for (LM_FEW, one row, V = 44928, h = 1920: 176 at once,
-// in two stages, 36.0, two times 88 34.5).
+// As many tokens at once as the sums leave room for.  LM_FEW also leaves room for a ring of three stages (one row, V = 44928, h = 1920: 176 at once,
+// in two stages, 36.0, two times 88 34.5).  LM_WIDE does not: its widest shares (up to 320 tokens, above 96 rows) have two stages, and from 193 rows
+// on some operands in scratch memory, and are faster so than in two rounds.  us, as it is / 256 tokens at most above 96 rows / no more than three stages leave room for: h = 4096, V = 72000,
+// 100 rows 134 / 147 / 147, 120 rows 134 / 140 / 136, 160 rows 144 / 164 / 160, 250 rows 187 / 204 / 213; h = 2048, V = 80000, 120 rows 74.4 / 73.7 / 74.4, 250 rows 106 / 117 / 122;
+// h = 4096, V = 128256, 257 rows 290 / 296 / 327.
 constexpr LmShares shares_of(int R, int V)
 {
     const int rt = (R + 15) / 16, rows = (V + 255) / 256;
