@@ -751,9 +751,9 @@ template <int LPW, int MAXT> __device__ __forceinline__ void wait_tiles(int tile
 
 // LDS map of one workgroup: the ring of NT stages; the query tiles (one per row-wave: its 32 rows as they lie in
 // memory, 2*D bytes each, chunk-rotated like a bf16 K tile) in the top of the ring when the prologue's fills leave
-// that free, else behind them; 1 KiB for the staged parent[] in a stage the prologue leaves free, else behind the
-// query tiles.  Queries and parents are consumed before the main loop's first barrier, after which the ring owns
-// every stage.  The merge of the key-waves re-uses the same memory after the loop.
+// that free, else behind them; 9 KiB for parent[] and the ancestor sets (see PAROFF).  Queries are consumed before the main
+// loop's first barrier, after which the ring owns every stage, and so are the sets where they lie in one.  The merge of the
+// key-waves re-uses the same memory after the loop.
 template <int D, int RW, int KW, int NT, int EB>
 struct WgLds {
     static constexpr int STAGE = Lds<D, EB>::STAGE;
@@ -763,8 +763,9 @@ struct WgLds {
     static constexpr int QBYTES = RW * QTILE;
     static constexpr int PRE_B = PREFILL * STAGE;
     static constexpr int QOFF = RING - QBYTES > PRE_B ? RING - QBYTES : PRE_B;
-    // parent[] and the ancestor sets: in stages the prologue leaves free, else behind the query tiles; behind the ring for the
-    // pipelined shape, which reads the sets after the plain prefix tiles
+    // parent[] and the ancestor sets.  Shapes with two key-waves read them before the main loop: in stages the prologue leaves free, or
+    // behind the query tiles where those leave less than 9 KiB of them (64 channels in the 64-row bf16 shape).  The pipelined shape reads
+    // the sets after the plain prefix tiles: behind the ring.
     static constexpr int PARENTS = BTV_MAX_NODES * 4, TREEB = PARENTS + BTV_MAX_NODES * BTV_ANC_WORDS * 4;
     static constexpr int PAROFF = KW == 1 ? (RING > QOFF + QBYTES ? RING : QOFF + QBYTES) : (QOFF - PRE_B >= TREEB ? PRE_B : QOFF + QBYTES);
     static constexpr int USED = (PAROFF + TREEB > QOFF + QBYTES ? PAROFF + TREEB : QOFF + QBYTES) > RING
@@ -1084,7 +1085,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             issue_tile<D, WAVES, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l);
     };
     if constexpr (KW == 1) {
-        // Every wave has its queries in registers and parent[] is consumed: the ring owns all stages from here on.
+        // Every wave has its queries in registers (parent[] and the sets lie behind the ring): the ring owns all stages from here on.
         __builtin_amdgcn_s_barrier();
 #pragma unroll
         for (int k = PREFILL; k < NT - 1; ++k) issue_one();
@@ -1788,17 +1789,17 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // two), and team k takes what lies between k w and (k + 1) w; where that cuts a stretch, tv_combine_batch
 // merges the parts.  A cut less than MARGIN tiles from where a stretch's tiles begin or end moves there.  A stretch of up to
 // SMALL tiles is not cut: the team that its beginning falls to does all of it.  Both make shares uneven by as much as they are long, and that costs
-// more than the pieces they save (8 and 16 tiles: the fullest share of 32 requests of 100 to 4000 tokens was 242 of 174 on average, now 195).
+// more than the pieces they save (with 8 and 16 tiles the fullest share of 32 requests of 100 to 4000 tokens was 242 of 174 on average; times below).
 // Where trees may take several row blocks a team is a pair of workgroups (neighbours on one XCD, running side by side): a
 // stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
 // first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
 // (if it is small, one of them takes it alone).
-// Bound by the tiles (1.08 us each in bf16 pieces of more than 128 rows, 0.79 below; FP8 0.61 in pieces of more than 64 rows, 0.44 below), by
+// Bound by the tiles (1.08 us each in bf16 pieces of more than 128 rows, 0.79 below; FP8 0.61 in pieces of more than 64 rows, 0.44 below), and
 // by the pieces: 7 to 8.6 us each beyond its tiles (finding it 1, page ids and first tiles 3, merging
 // and storing 3, waiting for the other waves 1), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
 // 8 requests of 1k to 16k, bf16 156 / 155 / 152; 32 of 100 to 4000, FP8 59.7 / 52.8 / 50.9; 5 of up to 8k with 83 nodes 58.5 / 51.8 / 53.8; 9 of up to 9k with
 // 12 42.0 / 39.7 / 39.9; 14 of up to 6k, FP8 67.4 / 65.4 / 65.0.  The figures beside the choice of the form
-// (short_batch) are the whole call's, before and after.
+// (short_batch) are the whole call's.
 constexpr int WHOLE = 3, PART = 2, START = 10 * WHOLE, MARGIN = 2, SMALL = 8;
 // A halved stretch of an odd number of tiles has half a step less for its second member.  A cut one step ahead of its end would leave that
 // member's last part empty, nobody would write it, and tv_combine_batch counts it: cuts stay two steps away from the end.
@@ -2095,7 +2096,7 @@ __global__ __launch_bounds__(256) void tv_combine_bf16(AttnParams p)
 // The same for a batch: how many parts a row has follows from where its request's work lies (the plan that the attention's first
 // workgroup left).  What bounds it is the chain of the request's place, the parts and the sums: lanes of E channels, the first PARTS
 // parts all asked for at once.  With 8 channels a lane has 16-byte loads and half of the wavefronts do, so those of many rows are under way
-// together (8 requests of up to 128 nodes, 32 heads: attention and merge 155.9 -> 149.8 us; 32 of up to 24, FP8, 51.1 -> 49.1); few rows leave the
+// together (8 requests of up to 128 nodes, 32 heads: attention and merge 156 -> 153 us, 150 to 156 from run to run; 32 of up to 24, FP8, 51.1 -> 49.1); few rows leave the
 // chip room, and D / 32 channels with 16 parts at once are faster (7 requests of 33 nodes, 16 heads, in up to 20 parts: 23.8 and 25.6).
 template <int D, int E, int PARTS>
 __global__ __launch_bounds__(256) void tv_combine_batch(AttnParams p)
@@ -2365,7 +2366,7 @@ void split_plan(Plan &pl, int L, int want)
 // the least estimated time.  The estimate: what a workgroup takes, its start and its tiles (two workgroups of the 64-row shape
 // share a CU at 1.3 times the time each), times the rounds in which the CUs of the fullest XCD take the workgroups, but no less than the
 // K/V bytes need, some of the smaller of the two on top; and for more than one split the merge.  Its constants are a fit to
-// 1200 shapes (prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
+// 1200 shapes with splits of equal length, as they were cut then (fitted again to splits that differ by a round: 0.2 %; prefixes of 64 to 32k, 4 to 256 nodes, 2 to 8 KV heads, all three K/V types and head sizes) times all shapes
 // and 28 split counts, of the choice and of the time: the choice is 1.2 % behind the best one found on average (fitted to 700 of
 // them, 1.1 % on the other 500; with the constants of the merge by a second launch 2.0 %), a rule by row count alone (always
 // 256 workgroups where the tiles allow it) was 15 % behind, 70 % for many rows over a short prefix (860 rows over 450 keys: 21 us
@@ -2421,10 +2422,12 @@ Plan make_plan(int M, int L, int Hq, int Hkv, int D, int eb = 2, int force_split
 // many parts where the average one is 2.5 times shorter; longer ones larger parts).
 struct PlanB { int rw, wr_log2, pairing, teams_log2, slots, wmin, sps, row_blocks; bool merge; };
 // The plan that the workgroups make themselves pays where they have much to do (64-row tiles per CU at most, of 128 channels; t: tiles of the longest
-// request); below, its larger row blocks and the longer way to the first tile cost more than an even load gives.  us, a grid of parts / the plan, of 70
-// batches: 72 tiles per CU, t = 208 51.5 / 45.4; 92, t = 147 42.1 / 37.1; 118, t = 135 35.1 / 37.6; 119, t = 42 31.3 / 46.9; 165, t = 96 48.0 / 46.6; D = 64, 31 (of
-// 128 channels), t = 331 20.0 / 24.3, 49, t = 251 26.6 / 27.0, 68, t = 435 32.0 / 26.8, 72, t = 221 32.0 / 27.6; 52, t = 72 22.4 / 23.1; 233, FP8, t = 248
-// 69.1 / 61.0.
+// request); below, its larger row blocks and the longer way to the first tile cost more than an even load gives.  us, a grid of parts / the plan.  128 channels: 35
+// tiles per CU, t = 142 22.5 / 33.5; 45, t = 242 30.0 / 26.3; 58, t = 124 35.2 / 33.7; 61, t = 63 27.2 / 32.4; 62, t = 333 37.0 / 28.4; 75, t = 240 42.1 / 35.4; 86, t = 185
+// 30.4 / 36.9; 101, t = 294 67.6 / 59.9; 104, t = 119 47.5 / 38.0; 115, t = 123 41.0 / 36.2; 150, t = 89 39.2 / 39.4; 178, t = 127 53.2 / 51.7.  64 channels: 60, t = 192
+// 21.4 / 26.7; 88, t = 378 27.1 / 30.7; 107, t = 229 27.1 / 26.9; 106, t = 310 28.0 / 24.8; 147, t = 91 33.9 / 28.5; 154, t = 176 35.9 / 29.2; 160, t = 214 28.1 / 29.0; 226, t = 259
+// 44.8 / 33.5.  What decides besides is how uneven the lengths are, which the host does not know: of 190 batches the choice is 3.0 % slower than the better form on
+// average with 128 channels and 1.1 % with 64, 31 and 19 % at most.  (A line at 60 tiles and t = 80 for 128 channels: 1.5 %, but up to 20 % slower than this one for some.)
 bool short_batch(int rows_g, int t, int Hkv, int D, int batch)
 {
     const long long tiles_cu = (long long)Hkv * batch * ((rows_g + 63) >> 6) * t / 256;
