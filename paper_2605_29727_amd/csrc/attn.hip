@@ -201,20 +201,38 @@ template <int D, int EB = 2> __device__ __forceinline__ int swz_v(int row)
 
 #define BTV_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
+// 16 bytes of every lane straight to LDS, lane after lane from dst on (uniform)
+__device__ __forceinline__ void fill_lds(const unsigned char *src, unsigned char *dst)
+{
+    __builtin_amdgcn_global_load_lds(src, BTV_LDS_PTR(dst), 16, 0, 0);
+}
+
 // Per-wave, loop-invariant part of the ring fills.  A wave issues LPW fills per tile; fill jj of wave w is
 // instruction j = w*LPW + jj of the tile (K part first).  Lane l of it fills LDS row r, physical chunk pc, with
-// source row key_off (relative to the tile's first key) and source chunk pc ^ swizzle(r).
+// source row key_off (relative to the tile's first key) and source chunk pc ^ swizzle(r).  A wave's fills of a tile are ROWS rows of K
+// or of V, all in the same half of the tile (the permutation of the K rows stays within 16), so in a paged cache of one page.
 template <int D, int WAVES, bool PAGED, int EB = 2>
 struct Fill {
-    static constexpr int LPW = Lds<D, EB>::INSTR / WAVES;
+    static constexpr int LPW = Lds<D, EB>::INSTR / WAVES, ROWS = 64 / WAVES;
     static_assert(LPW >= 1 && LPW * WAVES == Lds<D, EB>::INSTR, "fills must divide evenly over the waves");
-    const unsigned char *base[LPW]; // K or V base of this KV head for fill jj (wave-uniform)
+    static_assert(ROWS <= 16 && BTV_PAGE == 16, "a wave's rows are of one half of the tile: of one page");
+    const unsigned char *base;      // K or V of this KV head (wave-uniform)
     const int32_t *block_table;     // row of this request (paged)
-    uint32_t pages;                 // paged, lane l: page 2 * page_tile + l of the request (a window of 32 tiles; PGV)
-    int page_tile;
-    int num_blocks, S;
+    uint32_t pages;                 // paged, lane l: page of this wave's rows in tile l of a window of 32 (PGV)
+    int num_blocks, S, half;
     uint32_t row_bytes;             // Hkv * D * EB: distance between consecutive keys
     uint32_t lane_off[LPW];         // contiguous: key_off*row_bytes + chunk*16;  paged: (key_off & 15)*row_bytes + chunk*16
+    // where the 16 rows of a page begin (an id from the block table is clamped, so that no access can leave the pool)
+    __device__ __forceinline__ int valid_page(int id) const { return min(max(id, 0), num_blocks - 1); }
+    // The page of the wave's rows in tile st (constant space: a scalar load, so that the vector-memory counter only ever counts the LDS
+    // fills).  Past the end it is the last page: rows of the tile's upper half re-read the lower half's last row then.
+    __device__ __forceinline__ int page_id(int st) const
+    {
+        typedef const __attribute__((address_space(4))) int32_t *const_i32;
+        const const_i32 bt = reinterpret_cast<const_i32>(reinterpret_cast<uintptr_t>(block_table));
+        return bt[__builtin_amdgcn_readfirstlane(min(2 * st + half, (S - 1) >> 4))];
+    }
+    __device__ __forceinline__ const unsigned char *page(int id) const { return base + (size_t)(uint32_t)id * (BTV_PAGE * row_bytes); }
 };
 
 template <int D, int WAVES, bool PAGED, int EB = 2>
@@ -224,16 +242,14 @@ __device__ __forceinline__ Fill<D, WAVES, PAGED, EB> make_fill(const void *K, co
     using LD = Lds<D, EB>;
     constexpr int CH = LD::CHUNKS, RPI = 1024 / LD::ROWB;
     Fill<D, WAVES, PAGED, EB> f;
-    const uintptr_t Kb = reinterpret_cast<uintptr_t>(K) + (size_t)g * D * EB, Vb = reinterpret_cast<uintptr_t>(V) + (size_t)g * D * EB;
+    const bool isv = w >= WAVES / 2;                 // (uniform)
+    f.base = static_cast<const unsigned char *>(isv ? V : K) + (size_t)g * D * EB;
     f.block_table = bt; f.num_blocks = num_blocks; f.S = S;
+    f.half = (w * f.ROWS & 16) >> 4;
     f.row_bytes = (uint32_t)Hkv * D * EB;
 #pragma unroll
     for (int jj = 0; jj < f.LPW; ++jj) {
-        const int j = w * f.LPW + jj;
-        const bool isv = j >= LD::TILEB / 1024;      // wave-uniform: this fill belongs to the V part
-        f.base[jj] = reinterpret_cast<const unsigned char *>(isv ? Vb : Kb);
-        const int jt = isv ? j - LD::TILEB / 1024 : j;
-        const int r = jt * RPI + l / CH, pc = l % CH;
+        const int r = (w * f.LPW + jj) * RPI % 32 + l / CH, pc = l % CH;
         const int key_off = isv ? r : swap_bits_2_3(r);
         const int chunk = pc ^ (isv ? swz_v<D, EB>(r) : swz_k<D, EB>(r));
         f.lane_off[jj] = (uint32_t)(PAGED ? (key_off & 15) : key_off) * f.row_bytes + chunk * 16;
@@ -242,82 +258,47 @@ __device__ __forceinline__ Fill<D, WAVES, PAGED, EB> make_fill(const void *K, co
 }
 
 // Source row (relative to the tile's first key) of lane l in fill jj of wave w: recomputed where it is needed (the
-// clamped last tile, paged addressing) rather than kept in registers through the main loop.
+// clamped last tile) rather than kept in registers through the main loop.
 template <int D, int WAVES, int EB>
 __device__ __forceinline__ int fill_key_off(int w, int jj, int l)
 {
     using LD = Lds<D, EB>;
     constexpr int CH = LD::CHUNKS, RPI = 1024 / LD::ROWB, LPW = LD::INSTR / WAVES;
-    const int j = w * LPW + jj;
-    const bool isv = j >= LD::TILEB / 1024;
-    const int r = (isv ? j - LD::TILEB / 1024 : j) * RPI + l / CH;
-    return isv ? r : swap_bits_2_3(r);
+    const int r = (w * LPW + jj) * RPI % 32 + l / CH;
+    return w >= WAVES / 2 ? r : swap_bits_2_3(r);
 }
 
 // Issue this wave's share of the direct-to-LDS loads of tile `st` (keys 32*st ..) into ring slot `slot`.
 // Keys past the end of the sequence re-read the last valid row (finite data; their scores are masked).
 // JB .. JE - 1: which of the wave's LPW fills (all by default; the pipelined loop issues them one by one, each behind a
 // group of MFMAs, because an issue holds its wave for about a hundred cycles).
-// PGV: the page ids come from the window in f.pages (which must hold the tile's), else from scalar loads.
+// PGV: the page comes from lane `at` of the window in f.pages, else from a scalar load.
 template <int D, int WAVES, bool PAGED, int EB = 2, int JB = 0, int JE = Lds<D, EB>::INSTR / WAVES, bool PGV = false>
-__device__ __forceinline__ void issue_tile(const Fill<D, WAVES, PAGED, EB> &f, unsigned char *smem, int slot, int st, int w, int l)
+__device__ __forceinline__ void issue_tile(const Fill<D, WAVES, PAGED, EB> &f, unsigned char *smem, int slot, int st, int w, int l, int at = 0)
 {
     using LD = Lds<D, EB>;
     const int kb = st * 32;
     const bool whole = kb + 32 <= f.S;       // uniform: no key of this tile needs clamping
-    if (!PAGED) {
-        const size_t tile_off = (size_t)kb * f.row_bytes;
+    const unsigned char *src;                // uniform
+    if constexpr (!PAGED) src = f.base + (size_t)kb * f.row_bytes;
+    else if constexpr (PGV) src = f.page(__builtin_amdgcn_readlane((int)f.pages, at));
+    else {
+        src = f.page(f.valid_page(f.page_id(st)));
+    }
+    uint32_t off[JE];
+#pragma unroll
+    for (int jj = JB; jj < JE; ++jj) off[jj] = f.lane_off[jj];
+    if (!whole) {
 #pragma unroll
         for (int jj = JB; jj < JE; ++jj) {
-            const unsigned char *base = f.base[jj] + tile_off;          // uniform
-            uint32_t off = f.lane_off[jj];
-            if (!whole) {
-                const int ko = fill_key_off<D, WAVES, EB>(w, jj, l);
-                off = off - (uint32_t)ko * f.row_bytes + (uint32_t)(min(kb + ko, f.S - 1) - kb) * f.row_bytes;
-            }
-            __builtin_amdgcn_global_load_lds(base + off, BTV_LDS_PTR(smem + slot * LD::STAGE + (w * f.LPW + jj) * 1024), 16, 0, 0);
+            const int ko = fill_key_off<D, WAVES, EB>(w, jj, l), kc = min(kb + ko, f.S - 1) - kb;
+            off[jj] += (uint32_t)(PAGED ? (kc & 15) - (ko & 15) : kc - ko) * f.row_bytes;
         }
-    } else {
-        // a 32-key tile spans two 16-token pages; their ids are wave-uniform (scalar loads, or lanes of the window, so the
-        // vector-memory counter only ever counts the LDS fills)
-        int id0, id1;
-        if constexpr (PGV) {
-            const int at = 2 * (st - f.page_tile);               // (uniform)
-            id0 = __builtin_amdgcn_readlane((int)f.pages, at);
-            id1 = __builtin_amdgcn_readlane((int)f.pages, at + 1);
-        } else {
-            const int last_page = (f.S - 1) >> 4;
-            typedef const __attribute__((address_space(4))) int32_t *const_i32;   // constant space: scalar loads
-            const_i32 bt = reinterpret_cast<const_i32>(reinterpret_cast<uintptr_t>(f.block_table));
-            const int i0 = __builtin_amdgcn_readfirstlane(min(2 * st, last_page));
-            const int i1 = __builtin_amdgcn_readfirstlane(min(2 * st + 1, last_page));
-            id0 = bt[i0]; id1 = bt[i1];
-            asm volatile("" ::"s"(id0), "s"(id1));               // both loads are issued before either id is used: one wait, not two
-        }
-        const size_t page0 = (size_t)min(max(id0, 0), f.num_blocks - 1) * BTV_PAGE * f.row_bytes;
-        const size_t page1 = (size_t)min(max(id1, 0), f.num_blocks - 1) * BTV_PAGE * f.row_bytes;
-        if (whole) {
-            // The rows of one fill instruction all lie in the same half of the tile (an instruction covers 4 or 8
-            // consecutive LDS rows, and the permutation of the K rows stays within 16), so the page is the
-            // instruction's, not the lane's: a scalar base plus the lane's fixed offset, as in the contiguous form.
+    }
 #pragma unroll
-            for (int jj = JB; jj < JE; ++jj) {
-                const unsigned char *b = f.base[jj];
-                const int row0 = fill_key_off<D, WAVES, EB>(w, jj, 0);      // (uniform: the key of the instruction's first lane)
-                const unsigned char *src = b + ((row0 & 16) ? page1 : page0) + f.lane_off[jj];
-                __builtin_amdgcn_global_load_lds(src, BTV_LDS_PTR(smem + slot * LD::STAGE + (w * f.LPW + jj) * 1024), 16, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int jj = JB; jj < JE; ++jj) {
-                const unsigned char *b = f.base[jj];
-                const int ko = fill_key_off<D, WAVES, EB>(w, jj, l);
-                const int kc = min(kb + ko, f.S - 1) - kb;
-                const uint32_t off = f.lane_off[jj] - (uint32_t)(ko & 15) * f.row_bytes + (uint32_t)(kc & 15) * f.row_bytes;
-                const unsigned char *src = b + ((kc & 16) ? page1 : page0) + off;
-                __builtin_amdgcn_global_load_lds(src, BTV_LDS_PTR(smem + slot * LD::STAGE + (w * f.LPW + jj) * 1024), 16, 0, 0);
-            }
-        }
+    for (int jj = JB; jj < JE; ++jj) {
+        asm volatile("" : "+v"(off[jj]));    // (one branch for all of them: else there is one for each)
+        fill_lds(src + off[jj], smem + slot * LD::STAGE + (w * f.LPW + jj) * 1024);
     }
 }
 
@@ -504,20 +485,23 @@ __device__ __forceinline__ void pv_tile(const bf16x4 (&va)[DT][2][2], const bf16
 // tree mask of a tile that touches tree rows (or the end of the sequence)
 __device__ __forceinline__ void mask_tile(f32x16 &s, uint32_t vis, int h)
 {
+    vis >>= 8 * h;
+    asm volatile("" : "+v"(vis));            // (what follows from the lane alone would be worked out ahead of the loop, in calls without a mask too)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int bit = 16 * (v >> 3) + 8 * h + (v & 7);
+        const int bit = 16 * (v >> 3) + (v & 7);
         if (!((vis >> bit) & 1u)) s[v] = -INFINITY;
     }
 }
 
 // One whole tile, step after step (no overlap between the steps): used for the tiles that need the mask and
-// by the workgroup shapes whose wave pairs alternate over the tiles.
-template <int D>
+// by the workgroup shapes whose wave pairs alternate over the tiles.  PLAIN: prefix rows only, and not the wave's first tile;
+// `exact` (see probabilities) else.
+template <int D, bool PLAIN>
 __device__ __forceinline__ void do_tile(uint32_t stage, int kb, int Lr, int l,
                                         const uint32_t (&anc_i)[BTV_ANC_WORDS],
                                         const bf16x8 (&qreg)[D / 16], float &m_run, float &l_run, f32x16 (&oacc)[D / 32],
-                                        float &base, f32x16 &negb, bool first)
+                                        float &base, f32x16 &negb, bool exact)
 {
     constexpr int DS = D / 16, DT = D / 32;
     u32x4 ka[DS];
@@ -528,10 +512,9 @@ __device__ __forceinline__ void do_tile(uint32_t stage, int kb, int Lr, int l,
     lds_wait_k<DS, DT * 2>(ka);          // the counter completes in order: K has landed when 2*DT reads remain
     lds_read_vt<D, 1>(va_addr, va);
     f32x16 s = qk_tile<DS>(ka, qreg, negb);
-    const bool masked = kb + 32 > Lr;
-    if (masked) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
+    if (!PLAIN && kb + 32 > Lr) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
     bf16x8 pb[2];
-    probabilities<DT>(s, first || masked, base, negb, m_run, l_run, oacc, pb);
+    probabilities<DT>(s, !PLAIN && exact, base, negb, m_run, l_run, oacc, pb);
     lds_wait_vt<DT>(va);
     pv_tile<DT>(va, pb, oacc);
 }
@@ -610,11 +593,11 @@ __device__ __forceinline__ void lds_wait_vt8(u32x2 (&v8)[4][2])
 }
 
 // One whole tile of an FP8 cache: the same steps as do_tile with half the operand reads and the conversions.
-template <int D>
+template <int D, bool PLAIN>
 __device__ __forceinline__ void do_tile8(uint32_t stage, int kb, int Lr, int l,
                                          const uint32_t (&anc_i)[BTV_ANC_WORDS],
                                          const bf16x8 (&qreg)[D / 16], float &m_run, float &l_run, f32x16 (&oacc)[D / 32],
-                                         float &base, f32x16 &negb, bool first)
+                                         float &base, f32x16 &negb, bool exact)
 {
     static_assert(D == 128, "FP8 K/V: head dimension 128 only");
     constexpr int DS = D / 16, DT = D / 32;
@@ -631,10 +614,9 @@ __device__ __forceinline__ void do_tile8(uint32_t stage, int kb, int Lr, int l,
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp8x8_to_bf16x8(k8[k][0], k8[k][1]), qreg[2 * k], s, 0, 0, 0);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp8x8_to_bf16x8(k8[k][2], k8[k][3]), qreg[2 * k + 1], s, 0, 0, 0);
     }
-    const bool masked = kb + 32 > Lr;
-    if (masked) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
+    if (!PLAIN && kb + 32 > Lr) mask_tile(s, vis_word(anc_i, kb, Lr), l >> 5);
     bf16x8 pb[2];
-    probabilities<DT>(s, first || masked, base, negb, m_run, l_run, oacc, pb);
+    probabilities<DT>(s, !PLAIN && exact, base, negb, m_run, l_run, oacc, pb);
     lds_wait_vt8(v8);
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm)
@@ -997,15 +979,44 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     auto turn_window = [&]() {
         if constexpr (PGV) {
             const int g_ = (issued - st0) >> 5;
-            uint32_t v;
+            int v;
             asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)"
-                         : "=v"(v) : "v"((uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + PL::BASE + (uint32_t)((g_ & 3) * 256 + l * 4)) : "memory");
-            fill.pages = v;
-            fill.page_tile = st0 + 32 * g_;
+                         : "=v"(v) : "v"((uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + PL::BASE + (uint32_t)((g_ & 3) * 256 + (l & 31) * 8 + fill.half * 4)) : "memory");
+            fill.pages = (uint32_t)fill.valid_page(v);
             if (g_ > 0 && wu == 0) load_window(g_ + 1);
         }
     };
     auto next_window = [&]() { if (PGV && ((issued - st0) & 31) == 0) turn_window(); };
+    // Where tiles follow each other of which all keys exist, a fill is a scalar base, the lane's fixed offset and a stage's address: nothing is tested
+    // and, with a page per wave and tile, one id is looked up.  With a test for every fill and both pages of a tile worked out for each, fills
+    // were 90 of a trip's 250 instructions in the pipelined loop of a paged cache and several branches (8 requests of 1k to 16k, a layer 163 -> 146 us; FP8
+    // 171 -> 149), and 60 of a round's 300 in the contiguous shapes with two key-waves (64 nodes, 2048 keys 11.0 -> 10.6 us; FP8, 5000 keys 14.7 -> 13.5).
+    const uint32_t tile_bytes = 32 * fill.row_bytes;
+    const unsigned char *ahead = nullptr;                // contiguous: tile `issued`, where whole tiles follow each other
+    int ids[KW] = {};                                    // paged without a window: the pages of the next KW tiles, asked for a round ahead
+    auto whole_src = [&]() {                             // where this wave's rows of tile `issued` lie, if all of its keys exist
+        if constexpr (!PAGED) {
+            const unsigned char *src = ahead;
+            ahead += tile_bytes;
+            asm volatile("" : "+s"(src));                // (a scalar base and the lane's offset; else a pointer per fill and lane is carried along)
+            return src;
+        } else if constexpr (PGV) {
+            const unsigned char *src = fill.page(__builtin_amdgcn_readlane((int)fill.pages, (issued - st0) & 31));
+            asm volatile("" : "+s"(src));
+            return src;
+        } else {
+            const unsigned char *src = fill.page(fill.valid_page(ids[0]));
+            if (KW > 1) ids[0] = ids[KW - 1];
+            ids[KW - 1] = fill.page_id(issued + KW);
+            return src;
+        }
+    };
+    auto whole_tiles = [&]() {                           // ahead of the first of a row of them
+        if constexpr (!PAGED) ahead = fill.base + (size_t)issued * tile_bytes;
+        else if constexpr (!PGV)
+#pragma unroll
+            for (int k = 0; k < KW; ++k) ids[k] = fill.page_id(issued + k);
+    };
     turn_window();
     begun();
     const bool tree_wg = st1 * 32 > Lr;              // this workgroup's keys reach the tree rows
@@ -1072,7 +1083,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
     auto issue_one = [&]() {                             // the next tile of this split, if there is one
         if (issued < st1) {
             next_window();
-            issue_tile<D, WAVES, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
+            issue_tile<D, WAVES, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l, (issued - st0) & 31);
             ++issued;
             if (++islot == NT) islot = 0;
         }
@@ -1082,7 +1093,15 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
         constexpr int P = decltype(part)::value;
         constexpr int MID = (LPW + 1) / 2, JB = P == 0 ? 0 : MID, JE = P == 0 ? MID : LPW;
         if constexpr (JB < JE)
-            issue_tile<D, WAVES, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l);
+            issue_tile<D, WAVES, PAGED, EB, JB, JE, PGV>(fill, smem, islot, issued, wu, l, (issued - st0) & 31);
+    };
+    // the same of a tile whose 32 keys all exist; src: its first row, or that of the wave's page of it
+    auto issue_whole = [&](auto part, auto parts, int slot, const unsigned char *src) {
+        constexpr int P = decltype(part)::value, N = decltype(parts)::value;
+#pragma unroll
+        for (int jj = 0; jj < LPW; ++jj)
+            if (N == 1 || (P == 0) == (jj < (LPW + 1) / 2))
+                fill_lds(src + fill.lane_off[jj], smem + slot * LD::STAGE + (wu * LPW + jj) * 1024);
     };
     if constexpr (KW == 1) {
         // Every wave has its queries in registers (parent[] and the sets lie behind the ring): the ring owns all stages from here on.
@@ -1090,6 +1109,17 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
         for (int k = PREFILL; k < NT - 1; ++k) issue_one();
     }
+    // At the top of the round starting at tile st (KW > 1), tiles st+KW .. issued-1 may still be in flight.  The
+    // barrier also tells that every wave is done with the previous round, whose KW ring slots the next
+    // issues overwrite (in front of the first round: with the queries' tiles and the ancestor sets).
+    auto begin_round = [&](int st) {
+        if (issued - st - KW == AHEAD) wait_vmcnt<AHEAD * LPW>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int k = 0; k < KW; ++k) issue_one();
+    };
+    if constexpr (KW > 1) begin_round(st0);              // (ahead of the queries' scaling: the loads are on their way 0.2 us earlier)
     // The queries take the softmax scale and the change of base once (rounded to bf16 again, to nearest even: a
     // relative 2^-9 per element, as if the caller's projection had produced the scaled queries): scores then
     // are in log2 units and a probability costs no multiply.
@@ -1214,16 +1244,31 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                 if constexpr (S < 4) read_v_half<D, S, MM>(av, vh); else read_v_half<D, S - 4, MM>(avh, vh);
             };
             // ph: the trip's tile number modulo 8 as a constant, or -1 for a trip with its addresses in registers
-            auto iter = [&](bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], int i, auto ph) {
+            // steady: the tile that this trip asks for exists, and so do all of its keys
+            auto iter = [&](bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], int i, auto ph, auto steady) {
                 constexpr int PH = decltype(ph)::value;
+                constexpr bool STEADY = decltype(steady)::value;
                 using C0 = std::integral_constant<int, 0>;
                 using C1 = std::integral_constant<int, 1>;
                 // tiles <= i+2 are read in this iteration; the barrier also tells that every wave is done with
                 // iteration i-1, i.e. with tile i-2, whose slot the next fill takes
-                wait_tiles<LPW, 3>(issued - st0 - i - 3);
-                __builtin_amdgcn_s_barrier();
-                const bool fill_now = issued < st1;              // tile i+6 goes into the slot tile i-2 left
-                if (fill_now) next_window();
+                const unsigned char *src = nullptr;
+                bool fill_now = true;                            // tile i+6 goes into the slot tile i-2 left
+                if constexpr (STEADY) {
+                    wait_vmcnt<3 * LPW>();
+                    __builtin_amdgcn_s_barrier();
+                    if constexpr (((PH + 6) & 7) == 0) next_window();
+                    src = whole_src();
+                } else {
+                    wait_tiles<LPW, 3>(issued - st0 - i - 3);
+                    __builtin_amdgcn_s_barrier();
+                    fill_now = issued < st1;
+                    if (fill_now) next_window();
+                }
+                auto fill_half = [&](auto part) {
+                    if constexpr (STEADY) issue_whole(part, std::integral_constant<int, 2>{}, (PH + 6) & 7, src);
+                    else if (fill_now) issue_part(part);
+                };
                 uint32_t k1 = 0, k2 = 0, v0 = 0, v1 = 0;
                 if constexpr (PH < 0) {
                     k1 = kbase + slot_off(i + 1); k2 = kbase + slot_off(i + 2);
@@ -1232,7 +1277,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                 float ts = 0.f;
                 wait_v_half<DT, KH>(vh);                          // V(i-1) first half
                 pv_half<DT>(vh, pprev[0], oacc);
-                if (fill_now) issue_part(std::integral_constant<int, 0>{});      // behind four MFMAs: its issue stall is covered
+                fill_half(C0{});                                  // behind four MFMAs: its issue stall is covered
                 if constexpr (PH < 0) read_v_half_at<D, 1>(v0, vh);                     // V(i-1) second half  queue: K(i+1)lo, V(i-1)b
                 else rv(std::integral_constant<int, PH + 7>{}, C1{});
                 __builtin_amdgcn_sched_barrier(0);
@@ -1241,7 +1286,7 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                 __builtin_amdgcn_sched_barrier(0);
                 wait_v_half<DT, 0>(vh);                           // V(i-1) second half (and K(i+1) low)
                 pv_half<DT>(vh, pprev[1], oacc);
-                if (fill_now) issue_part(std::integral_constant<int, 1>{});
+                fill_half(C1{});
                 if constexpr (PH < 0) read_v_half_at<D, 0>(v1, vh);                     // V(i) first half     queue: V(i)a
                 else rv(std::integral_constant<int, PH>{}, C0{});
                 __builtin_amdgcn_sched_barrier(0);
@@ -1258,7 +1303,8 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
                 x = qk_half<DS, 1>(kh, qreg, x);
                 if constexpr (PH < 0) read_k_half_at<D, 0>(k2, kh);                     // K(i+2) low          queue: K(i+2)lo (V(i)a has landed)
                 else rk(std::integral_constant<int, PH + 2>{}, C0{});
-                if (fill_now) { ++issued; if (++islot == NT) islot = 0; }
+                if constexpr (STEADY) ++issued;
+                else if (fill_now) { ++issued; if (++islot == NT) islot = 0; }
             };
             // ---- epilogue: tile e = Tf - 1 has its scores, tile e-1 its probabilities (pp); nothing left to overlap ----
             auto drain = [&](bf16x8 (&pp)[2], bf16x8 (&pn)[2]) {
@@ -1286,16 +1332,26 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
             // One iteration per trip, the new probabilities copied into place at its end (8 moves): with the roles of
             // two register sets alternating over an unrolled pair the allocator shuffles tuples and spills.
             int i = 1;
-            for (; i + 7 <= Tf - 2; i += 8) {                    // tile i is in ring slot 1 here: eight trips, one per slot
-                // (the two probability buffers swap roles from trip to trip: no copies inside the group)
-                // (one barrier for two trips, with the fills one tile less ahead, measured the same)
-#define BTV_TRIP(k, slot, from, to) iter(from, to, i + k, std::integral_constant<int, slot>{});
-                BTV_TRIP(0, 1, pa, pc) BTV_TRIP(1, 2, pc, pa) BTV_TRIP(2, 3, pa, pc) BTV_TRIP(3, 4, pc, pa)
-                BTV_TRIP(4, 5, pa, pc) BTV_TRIP(5, 6, pc, pa) BTV_TRIP(6, 7, pa, pc) BTV_TRIP(7, 0, pc, pa)
-#undef BTV_TRIP
+            // (the two probability buffers swap roles from trip to trip: no copies inside a group of eight)
+            // (one barrier for two trips, with the fills one tile less ahead, measured the same)
+#define BTV_TRIP(k, slot, from, to) iter(from, to, i + k, std::integral_constant<int, slot>{}, steady);
+#define BTV_TRIPS                                                                                                             \
+            BTV_TRIP(0, 1, pa, pc) BTV_TRIP(1, 2, pc, pa) BTV_TRIP(2, 3, pa, pc) BTV_TRIP(3, 4, pc, pa)                       \
+            BTV_TRIP(4, 5, pa, pc) BTV_TRIP(5, 6, pc, pa) BTV_TRIP(6, 7, pa, pc) BTV_TRIP(7, 0, pc, pa)
+            const int whole = min(st1, S / 32) - st0;            // tiles of this split with all keys
+            whole_tiles();
+            for (; i + 7 <= Tf - 2 && i + 13 < whole; i += 8) {  // tile i is in ring slot 1 here: eight trips, one per slot
+                constexpr std::true_type steady;
+                BTV_TRIPS
             }
+            for (; i + 7 <= Tf - 2; i += 8) {
+                constexpr std::false_type steady;
+                BTV_TRIPS
+            }
+#undef BTV_TRIPS
+#undef BTV_TRIP
             for (; i <= Tf - 2; ++i) {
-                iter(pa, pc, i, std::integral_constant<int, -1>{});
+                iter(pa, pc, i, std::integral_constant<int, -1>{}, std::false_type{});
 #pragma unroll
                 for (int mm = 0; mm < 2; ++mm) pa[mm] = pc[mm];
             }
@@ -1315,38 +1371,48 @@ __device__ __forceinline__ void attn_piece(const AttnParams &p, unsigned char *s
 #pragma unroll
             for (int k = 0; k < 2; ++k)
                 if (issued - st0 - j < NT) issue_one();
-            do_tile<D>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, true);
+            do_tile<D, false>(ring + (j & 7) * LD::STAGE, (st0 + j) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, true);
         }
         if constexpr (PAGED) wait_vmcnt<0>();
     } else {
         // ---- main loop: one barrier per round of KW tiles, wave kw takes tile number kw of the round ------
-        // At the top of the round starting at tile st, tiles st+KW .. issued-1 may still be in flight.  The
-        // barrier also tells that every wave is done with the previous round, whose KW ring slots the next
-        // issues overwrite.
         // (a wave whose 32 rows all lie past the last one only fills)
         const bool live = by * WR + __builtin_amdgcn_readfirstlane(rw) * 32 < rows_g;
         const int kwu = wu % KW;                                 // (kw, as a scalar)
-        int cslot = kwu;
-        for (int st = st0; st < st1; st += KW) {
-            if (issued - st - KW == AHEAD) wait_vmcnt<AHEAD * LPW>();
-            else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
-#pragma unroll
-            for (int k = 0; k < KW; ++k)
-                if (issued < st1) {
-                    next_window();
-                    issue_tile<D, WAVES, PAGED, EB, 0, LPW, PGV>(fill, smem, islot, issued, wu, l);
-                    ++issued;
-                    if (++islot == NT) islot = 0;
-                }
-            if (live && st + kwu < st1) {
-                if constexpr (EB == 2)
-                    do_tile<D>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, st == st0);
-                else
-                    do_tile8<D>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, st == st0);
-            }
+        int cslot = kwu, st = st0;
+        auto tile = [&](auto plain) {                            // this wave's tile of the round
+            constexpr bool PLAIN = decltype(plain)::value;
+            const bool exact = !PLAIN && (st == st0 || (st + kwu) * 32 + 32 > Lr);      // (constant in the first round)
+            if constexpr (EB == 2)
+                do_tile<D, PLAIN>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, exact);
+            else
+                do_tile8<D, PLAIN>(ring + cslot * LD::STAGE, (st + kwu) * 32, Lr, l, anc_i, qreg, m_run, l_run, oacc, base, negb, exact);
+        };
+        auto next_round = [&]() {
+            st += KW;
             cslot += KW;
             if (cslot >= NT) cslot -= NT;
+        };
+        // Rounds that ask for KW tiles of the prefix with all their keys, and so only take such, have nothing to test for.
+        const int plain = min(st1, Lr / 32);
+        if (live && st + kwu < st1) tile(std::false_type{});     // (on its own: nothing has to be cleared ahead of it)
+        next_round();
+        whole_tiles();
+        for (; issued + KW <= plain; next_round()) {
+            wait_vmcnt<AHEAD * LPW>();
+            __builtin_amdgcn_s_barrier();
+#pragma unroll
+            for (int k = 0; k < KW; ++k) {
+                next_window();
+                issue_whole(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, islot, whole_src());
+                ++issued;
+                if (++islot == NT) islot = 0;
+            }
+            if (live) tile(std::true_type{});
+        }
+        for (; st < st1; next_round()) {
+            begin_round(st);
+            if (live && st + kwu < st1) tile(std::false_type{});
         }
     }
     const LaneRow lrow = lane_row(p, by * WR + rw * 32 + c, rows_g, g, rq_.q0);

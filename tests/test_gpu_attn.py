@@ -282,6 +282,27 @@ def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed):
         assert np.abs(o - ref).max() <= TOL_BF16, r
 
 
+@pytest.mark.parametrize("shape_id", [1, 2, 3])
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_around_the_rings_and_the_trips(G, oracle, shape_id, D):
+    """One part of as many tiles as the ring's stages, the rounds of two and the groups of eight trips make different paths of (all keys there
+    or not, prefix rows only or not), whole tiles at the end of the prefix, of the sequence, and neither."""
+    for tiles in (3, 4, 5, 6, 7, 8, 9, 10, 14, 15, 16, 17, 22, 23, 24, 25, 31):
+        for L, M in ((32 * tiles, 3), (32 * tiles - 3, 3), (32 * tiles - 17, 5)):
+            parent = synth.tree_parents(tiles, M, "random")
+            t = synth.qkv(91, M, L, 2, 1, D, "bf16", tag=f"{L}")
+            ref = oracle.tree_attn(t["Qf"], t["Kf"], t["Vf"], parent, L)
+            out = G.run_verify_attn(t, parent, L, "bf16", nsplit=1, shape=shape_id)
+            assert np.abs(out - ref).max() <= TOL_BF16, (L, M, np.abs(out - ref).max())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_paged_around_the_windows_of_pages(G, oracle, D):
+    """Requests of 31 to 34 and 63 to 66 tiles (a window of page ids is 32), ending in either half of a tile and with it."""
+    for tiles in (31, 33, 64):
+        _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, D, seed=92 + tiles)
+
+
 def test_paged_ragged_small(G, oracle):
     _paged_case(G, oracle, [100, 0, 333, 17, 1025], [9, 5, 33, 1, 64], 8, 2, 128, seed=61)
     _paged_case(G, oracle, [640, 64], [70, 130], 8, 2, 64, seed=62)

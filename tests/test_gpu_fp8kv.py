@@ -212,6 +212,24 @@ def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, seed):
         assert np.abs(o - ref).max() <= TOL, r
 
 
+def test_paged_around_the_windows_of_pages(G, oracle):
+    """Requests of 31 to 34 and 63 to 66 tiles (a window of page ids is 32), ending in either half of a tile and with it."""
+    for tiles in (31, 33, 64):
+        _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, seed=92 + tiles)
+
+
+@pytest.mark.parametrize("shape_id", [1, 2])
+def test_around_the_ring_of_tiles(G, oracle, shape_id):
+    """One part of as many tiles as the ring's stages and the rounds of two make different paths of."""
+    for tiles in (3, 4, 5, 6, 7, 8, 9, 10, 15, 16, 17):
+        for L, M in ((32 * tiles, 3), (32 * tiles - 3, 3), (32 * tiles - 17, 5)):
+            parent = synth.tree_parents(tiles, M, "random")
+            q, kv = _inputs(93, M, L, 2, 1, tag=f"{L}")
+            ref = _oracle(oracle, q, kv, parent, L)
+            out = G.run_verify_attn_fp8kv(q["Q"], kv, parent, L, nsplit=1, shape=shape_id)
+            assert np.abs(out - ref).max() <= TOL, (L, M, np.abs(out - ref).max())
+
+
 def test_paged_ragged(G, oracle):
     _paged_case(G, oracle, [100, 0, 333, 17, 1025], [9, 5, 33, 1, 64], 8, 2, seed=81)
     _paged_case(G, oracle, [5000, 300, 2500, 4097, 64, 9000], [40, 64, 7, 100, 130, 16], 8, 2, seed=83)
