@@ -107,8 +107,9 @@ __global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, i
         m1 = umax(m1, b);
     };
     // All of a thread's loads are in flight at once: none lies behind a branch that its lanes may take apart, for which the compiler would wait each time
-    // (8 round trips, 32 where the row is not aligned to 16 bytes: the whole call for 16 x 128256 marginals and 16 nodes 12.7 us, now 11.7; 16 x 128255 15.2 and 11.7).  A load of four floats needs the
-    // alignment of one.
+    // (8 round trips, 32 where the row is not aligned to 16 bytes: the whole call for 16 x 128256 marginals and 16 nodes 12.7 us, then 11.7; 16 x 128255 15.2 and 11.7).  A load of four floats needs the
+    // alignment of one.  The row's last chunk, a sixteenth of the workgroups, ends with the others so: by single floats, four times as many loads,
+    // it was what the launch waited for (16 x 128256 and 16 nodes 11.6 -> 11.0 us, 256 nodes 25.0 -> 24.3; 128 rows of 128256 4 us less).
     constexpr int PIECES = (1 << LGE) / 4;
     struct alignas(4) Four { float x[4]; };
     const int first = slot_first(LGE, chunk, tid);               // coalesced: a wave reads 1 KiB per load
@@ -120,12 +121,22 @@ __global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, i
         for (int j = 0; j < PIECES; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i) see(prob_bits(a[j].x[i]), 4 * j + i);
-    } else {                                                     // the row's last chunk
-        float a[PIECES * 4];
+    } else {                                                     // the row's last chunk: as many loads, the last of them moved back into the row
+        Four a[PIECES];
 #pragma unroll
-        for (int k = 0; k < PIECES * 4; ++k) a[k] = src[min(first + (k >> 2) * 1024 + (k & 3), V - 1)];
+        for (int j = 0; j < PIECES; ++j) a[j] = *reinterpret_cast<const Four *>(src + min(first + j * 1024, V - 4));      // (V > 4096 here)
 #pragma unroll
-        for (int k = 0; k < PIECES * 4; ++k) see(first + (k >> 2) * 1024 + (k & 3) < V ? prob_bits(a[k]) : 0u, k);      // (0 changes nothing)
+        for (int j = 0; j < PIECES; ++j) {
+            const int past = first + j * 1024 - (V - 4);         // so many places forward
+            float x[4] = { a[j].x[0], a[j].x[1], a[j].x[2], a[j].x[3] };
+            if (past > 0) {                                      // (0 changes nothing)
+                if (past & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = 0.f; }
+                if (past & 2) { x[0] = x[2]; x[1] = x[3]; x[2] = x[3] = 0.f; }
+                if (past > 3) x[0] = x[1] = x[2] = x[3] = 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) see(prob_bits(x[i]), 4 * j + i);
+        }
     }
     part[((size_t)row * chunks + chunk) * 256 + tid] = make_uint2(m1, (m2 & ~31u) | k1);
 }

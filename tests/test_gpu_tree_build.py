@@ -97,6 +97,17 @@ def test_vocabularies_around_the_slot_sizes(G, oracle, V):
         _check(G, oracle, synth.marginals(70 + seed, B, V, sigma), N)
 
 
+@pytest.mark.parametrize("V", [4097, 4098, 4099, 5119, 5121, 6146, 16383, 20481, 65539, 70001, 131069])
+def test_rows_that_end_with_their_best_tokens(G, oracle, V):
+    """The last tokens of a row, in a chunk whose loads are moved back into the row, are the largest, in rising and falling order and tied."""
+    rng = np.random.default_rng(V)
+    marg = (rng.random((3, V)) * 1e-5).astype(np.float32)
+    marg[0, -9:] = np.linspace(0.05, 0.2, 9)
+    marg[1, -9:] = np.linspace(0.2, 0.05, 9)
+    marg[2, -9:] = 0.1
+    _check(G, oracle, marg, 24)
+
+
 @pytest.mark.parametrize("N", [1, 2, 40, 97, 256])
 @pytest.mark.parametrize("step", [-1, 0, 1])
 def test_star_and_its_first_deeper_node(G, oracle, N, step):
