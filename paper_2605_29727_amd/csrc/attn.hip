@@ -1866,9 +1866,9 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
 // first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
 // (if it is small, one of them takes it alone).
-// Bound by the tiles (1.08 us each in bf16 pieces of more than 128 rows, 0.79 below; FP8 0.61 in pieces of more than 64 rows, 0.44 below), and
-// by the pieces: 7 to 8.6 us each beyond its tiles (finding it 1, page ids and first tiles 3, merging
-// and storing 3, waiting for the other waves 1), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
+// Bound by the tiles (0.84 us each in bf16 pieces of more than 128 rows, 0.58 below; FP8 0.51 in pieces of more than 64 rows, 0.33 below), and
+// by the pieces: 5.5 to 8 us each beyond its tiles (finding it 0.5, page ids and first tiles 3, merging
+// and storing 2, waiting for the other waves 0.5), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
 // 8 requests of 1k to 16k, bf16 156 / 155 / 152; 32 of 100 to 4000, FP8 59.7 / 52.8 / 50.9; 5 of up to 8k with 83 nodes 58.5 / 51.8 / 53.8; 9 of up to 9k with
 // 12 42.0 / 39.7 / 39.9; 14 of up to 6k, FP8 67.4 / 65.4 / 65.0.  The figures beside the choice of the form
 // (short_batch) are the whole call's.
@@ -1920,6 +1920,26 @@ __device__ __forceinline__ Chunk load_chunk(const AttnParams &p, int c0, int lan
     c.s = stretch_of(p, q);
     c.bad = in && !q.ok;
     c.incl = wave_incl_scan_len(in ? c.s.len : 0) + cum;
+    return c;
+}
+// The first chunk is kept in LDS from one piece to the next.  Loaded again it cost 1.1 us a piece (1.4 to 1.8 pieces a workgroup): its loads
+// wait behind the last piece's stores; from LDS 0.5.  8 requests of 1k to 16k, two layers and trees, 303 -> 299 us; 32 of 100 to 4000, FP8, 119.4 -> 115.9; 20 of 1k to
+// 6k with 64 channels 181 -> 176.  (Looking for the next piece during this one's first loads, by one wavefront that tells the others: +-1 %.)  Raw
+// instructions: ahead of ordinary reads the compiler waits for the stores as well.
+constexpr int CHUNK_BYTES = 64 * 32;
+__device__ __forceinline__ void keep_chunk(uint32_t kept, int lane, const Chunk &c)
+{
+    const u32x4 a = { (uint32_t)c.s.t, (uint32_t)c.s.du, (uint32_t)c.s.wt, (uint32_t)c.s.sl }, b = { (uint32_t)c.s.len, (uint32_t)c.incl, (uint32_t)(c.incl >> 32), 0 };
+    asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %0, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" :: "v"(kept + (uint32_t)lane * 32), "v"(a), "v"(b) : "memory");
+}
+__device__ __forceinline__ Chunk kept_chunk(uint32_t kept, int lane)
+{
+    u32x4 a, b;
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(a), "=&v"(b) : "v"(kept + (uint32_t)lane * 32) : "memory");
+    Chunk c;
+    c.s.t = (int)a[0]; c.s.du = (int)a[1]; c.s.wt = (int)a[2]; c.s.sl = (int)a[3]; c.s.len = (int)b[0];
+    c.incl = (long long)((unsigned long long)b[2] << 32 | b[1]);
+    c.bad = false;
     return c;
 }
 __device__ __forceinline__ long long last_lane(long long x)
@@ -2025,10 +2045,15 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_batch(AttnParams p)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, member = slot & p.pairing;
     Chunk c;
     Walk k = share_out(p, xcd, slot >> p.pairing, threadIdx.x & 63, blockIdx.x == 0 && threadIdx.x < 64, c);
+    const uint32_t kept = (uint32_t)(uintptr_t)BTV_LDS_PTR(smem) + PageLds<D, RW, KW, NT, true, EB>::BYTES;
+    if (threadIdx.x < 64) keep_chunk(kept, threadIdx.x, c);     // (barriers before it is read: those of the first piece)
     for (bool again = false;; again = true) {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));                   // keeps what derives from it (all addresses) from being carried across pieces
-        if (again) c = load_chunk(p, 0, tid & 63, 0);
+        if (again) {
+            if (k.pos >= k.end) break;
+            c = kept_chunk(kept, tid & 63);
+        }
         Piece pc = {};
         if (!next_piece(p, k, member, tid & 63, c, pc)) break;
         attn_piece<D, RW, KW, NT, true, EB>(p, smem, tid, load_req<true>(p, pc.rq), pc, [] {});
@@ -2608,7 +2633,8 @@ enum Form { ONE_REQUEST, ONE_MERGED, SHORT_BATCH, LONG_BATCH };
 template <int D, int RW, int KW, int NT, Form FORM, int EB = 2>
 int launch_bf16(const AttnParams &p, dim3 grid, hipStream_t st)
 {
-    constexpr int LDS_BYTES = PageLds<D, RW, KW, NT, (FORM > ONE_MERGED), EB>::BYTES;
+    constexpr int LDS_BYTES = PageLds<D, RW, KW, NT, (FORM > ONE_MERGED), EB>::BYTES + (FORM == LONG_BATCH ? CHUNK_BYTES : 0);
+    static_assert(LDS_BYTES * (RW * KW <= 4 ? 2 : 1) <= 160 * 1024, "LDS budget");
     static std::atomic<bool> configured{false};         // (one GPU per process: the attribute is set once)
     void (*kern)(AttnParams);
     if constexpr (FORM == LONG_BATCH) kern = tv_attn_batch<D, RW, KW, NT, EB>;

@@ -347,6 +347,14 @@ def test_paged_batches_around_stretches_that_are_cut(G, oracle, batch, M_max, L_
     _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=67)
 
 
+@pytest.mark.parametrize("batch, M_max, Hq, Hkv, D", [(64, 33, 16, 2, 128), (65, 16, 16, 2, 128), (65, 16, 16, 4, 64)])
+def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max, Hq, Hkv, D):
+    """Several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones, before and behind a long request."""
+    Ls, Ns = long_batch(batch, M_max, 3300, batch - 1)
+    Ls[0] = 2500
+    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=69)
+
+
 @pytest.mark.parametrize("batch, M_max, L, Hq, Hkv, D", [(6, 128, 700, 16, 2, 64), (7, 110, 710, 16, 2, 64), (6, 128, 700, 16, 2, 128), (7, 110, 710, 16, 2, 128),
                                                          (2, 8, 5000, 8, 1, 128), (2, 9, 5100, 8, 1, 64)])
 def test_paged_batches_of_parts(G, oracle, batch, M_max, L, Hq, Hkv, D):

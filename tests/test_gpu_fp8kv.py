@@ -246,6 +246,15 @@ def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long):
     _paged_case(G, oracle, Ls, Ns, 16, 2, seed=84)
 
 
+@pytest.mark.parametrize("batch, M_max", [(64, 16), (65, 33)])
+def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max):
+    """Several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones."""
+    Ls = [(63, 64, 200, 490, 511, 513, 530, 700, 900)[r % 9] for r in range(batch)]
+    Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
+    Ls[0], Ls[-1] = 2500, 3300
+    _paged_case(G, oracle, Ls, Ns, 16, 2, seed=85)
+
+
 def test_config4_ragged_paged_full_size(G, oracle):
     Ls, Ns = synth.c4_request_shapes()
     _paged_case(G, oracle, Ls, Ns, 32, 8, seed=synth.C4.seed)
