@@ -42,7 +42,7 @@
 // 128 points), the row loads in front of it (2 us), code that runs once per call.  Measured
 // at V = 128256 (MI355X, one call after the other): 127 children under the root, all rejected, fp32: 124 -> 39 us against
 // one workgroup that walked a row sorted by four launches ahead of it; a drafter whose target follows it for 7 to 12
-// levels, bf16: 860 .. 1280 -> 31 .. 36 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
+// levels, bf16: 860 .. 1280 -> 29 .. 33 us against that workgroup's passes over every row (110 us per level).  Slices of 4096
 // tokens instead of 2048 (half the workgroups): 52 and 48 .. 52 us at the same two.
 #include "btv_common.h"
 
@@ -204,15 +204,19 @@ __device__ __forceinline__ float load_logit(const void *logits, size_t idx)
 
 // N tokens of a row in pieces of four, v + step * i .. + 3 for i < N / 4; those from v1 on come as `pad`.  vec: the row allows
 // whole pieces (then v and v1 are multiples of four, and a piece is in or out).  All loads are issued before the first is
-// looked at.
+// looked at.  A chain's rows are bound by how many loads 16 wavefronts issue: pieces are of the compiler's own vector types, because of float4, a
+// structure, it takes the four floats and merges their loads with the other path's, four of 4 bytes for one of 16 (a draft followed over 7 to 12
+// levels, 128256 tokens: bf16 35.8 -> 32.7 us, fp32 40.4 -> 32.9; a fan of 127 39.4 -> 38.8; 20 nodes, 3000 tokens 21.2 -> 20.2).
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16, int N>
 __device__ __forceinline__ void load_tokens(const void *row, int v, int step, int v1, bool vec, float pad, float (&x)[N])
 {
     if (vec) {
         if constexpr (BF16) {
-            uint2 w[N / 4];
+            u32x2 w[N / 4];
 #pragma unroll
-            for (int i = 0; i < N / 4; ++i) w[i] = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(row) + (v + step * i < v1 ? v + step * i : 0));
+            for (int i = 0; i < N / 4; ++i) w[i] = *reinterpret_cast<const u32x2 *>(static_cast<const uint16_t *>(row) + (v + step * i < v1 ? v + step * i : 0));
 #pragma unroll
             for (int i = 0; i < N / 4; ++i) {
                 x[4 * i] = __uint_as_float(w[i].x << 16); x[4 * i + 1] = __uint_as_float(w[i].x & 0xFFFF0000u);
@@ -221,7 +225,7 @@ __device__ __forceinline__ void load_tokens(const void *row, int v, int step, in
         } else {
 #pragma unroll
             for (int i = 0; i < N / 4; ++i) {
-                const float4 w = *reinterpret_cast<const float4 *>(static_cast<const float *>(row) + (v + step * i < v1 ? v + step * i : 0));
+                const f32x4 w = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(row) + (v + step * i < v1 ? v + step * i : 0));
                 x[4 * i] = w.x; x[4 * i + 1] = w.y; x[4 * i + 2] = w.z; x[4 * i + 3] = w.w;
             }
         }

@@ -487,6 +487,40 @@ def test_stochastic_slices(G, oracle, V, logit_dtype):
     assert checked >= 1
 
 
+@pytest.mark.parametrize("V", [5000, 5001, 5002, 9996])
+@pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
+def test_stochastic_rows_at_any_element(G, oracle, V, logit_dtype):
+    """Rows that begin on any element and end in any part of a piece of four (pieces are loaded whole where everything is aligned to them):
+    the same walk as from aligned arrays, and the oracle's."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    marg = synth.marginals(71, 6, V, 4.0)
+    tree = oracle.tree_build(marg, 24)
+    M = len(tree["parent"])
+    z = np.log(np.maximum(marg[np.minimum(np.concatenate([[0], tree["depth"]]), 5)].astype(np.float64), 1e-30)) + synth.normal(72, "noise", (M + 1, V), 0.3)
+    store, xf = synth.round_to_dtype(z, logit_dtype)
+    u = synth.uniform(73, "u", (M + 1,)).astype(np.float32)
+    ref = oracle.accept_stochastic(xf, marg, tree["parent"], tree["token"], tree["depth"], u)
+    whole = G.run_accept_stochastic(store, logit_dtype == "bf16", marg, tree["parent"], tree["token"], u)
+    if not _ambiguous(ref):
+        assert whole["n_acc"] == ref["n_acc"] and np.array_equal(whole["path"], ref["path"]) and whole["bonus"] == ref["bonus"]
+    x, m = G.dev(store, logit_dtype == "bf16"), G.dev(marg.astype(np.float32))
+    par, tok, uni = G.dev(np.asarray(tree["parent"], dtype=np.int32)), G.dev(np.asarray(tree["token"], dtype=np.int32)), G.dev(u)
+    ws = btv.alloc_workspace(btv.btv_tree_accept_workspace(M, V, True))
+
+    def at(t, off):                                  # a copy that begins `off` elements behind an aligned address
+        flat = torch.zeros(t.numel() + 16, dtype=t.dtype, device="cuda")
+        flat[off:off + t.numel()] = t.flatten()
+        return flat[off:off + t.numel()].view(t.shape)
+
+    for dx, dm in ((1, 0), (2, 0), (4, 0), (8, 1), (0, 2), (4, 4), (3, 3)):
+        out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (M, 1, 1)]
+        btv.btv_tree_accept_stochastic(at(x, dx), at(m, dm), par, tok, uni, *out, ws)
+        n = int(out[1].item())
+        assert n == whole["n_acc"] and out[2].item() == whole["bonus"], (dx, dm)
+        assert np.array_equal(out[0].cpu().numpy()[:n], whole["path"]), (dx, dm)
+
+
 def test_stochastic_token_outside_vocabulary_is_flagged_not_faulting():
     """A token id outside [0, V) is never used as an index: that child counts as rejected, the data flag is raised,
     and the walk goes on with the valid children."""
