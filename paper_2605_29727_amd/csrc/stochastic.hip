@@ -202,42 +202,57 @@ __device__ __forceinline__ float load_logit(const void *logits, size_t idx)
     return static_cast<const float *>(logits)[idx];
 }
 
-// N tokens of a row in pieces of four, v + step * i .. + 3 for i < N / 4; those from v1 on come as `pad`.  vec: the row allows
-// whole pieces (then v and v1 are multiples of four, and a piece is in or out).  All loads are issued before the first is
-// looked at.  A chain's rows are bound by how many loads 16 wavefronts issue: pieces are of the compiler's own vector types, because of float4, a
+// N tokens of a row and of its marginals in pieces of four, v + step * i .. + 3 for i < N / 4; logits from v1 on come as -inf, marginals from
+// vq on as 0.  vec: the rows allow whole pieces (then v, v1 and vq are multiples of four, and a piece is in or out).  All loads are issued before the
+// first is looked at.  A chain's rows are bound by how many loads 16 wavefronts issue: pieces are of the compiler's own vector types, because of float4, a
 // structure, it takes the four floats and merges their loads with the other path's, four of 4 bytes for one of 16 (a draft followed over 7 to 12
-// levels, 128256 tokens: bf16 35.8 -> 32.7 us, fp32 40.4 -> 32.9; a fan of 127 39.4 -> 38.8; 20 nodes, 3000 tokens 21.2 -> 20.2).
+// levels, 128256 tokens: bf16 35.8 -> 32.7 us, fp32 40.4 -> 32.9; a fan of 127 39.4 -> 38.8; 60000 tokens 30.4 -> 25.8).
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16, int N>
-__device__ __forceinline__ void load_tokens(const void *row, int v, int step, int v1, bool vec, float pad, float (&x)[N])
+__device__ __forceinline__ void load_tokens(const void *row, const float *marg, int v, int step, int v1, int vq, bool vec, float (&e)[N], float (&q)[N])
 {
     if (vec) {
-        if constexpr (BF16) {
-            u32x2 w[N / 4];
+        u32x2 wb[N / 4];
+        f32x4 wf[N / 4], wq[N / 4];
 #pragma unroll
-            for (int i = 0; i < N / 4; ++i) w[i] = *reinterpret_cast<const u32x2 *>(static_cast<const uint16_t *>(row) + (v + step * i < v1 ? v + step * i : 0));
+        for (int i = 0; i < N / 4; ++i) {
+            const int at = v + step * i < v1 ? v + step * i : 0;
+            if constexpr (BF16) wb[i] = *reinterpret_cast<const u32x2 *>(static_cast<const uint16_t *>(row) + at);
+            else wf[i] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(row) + at);
+        }
 #pragma unroll
-            for (int i = 0; i < N / 4; ++i) {
-                x[4 * i] = __uint_as_float(w[i].x << 16); x[4 * i + 1] = __uint_as_float(w[i].x & 0xFFFF0000u);
-                x[4 * i + 2] = __uint_as_float(w[i].y << 16); x[4 * i + 3] = __uint_as_float(w[i].y & 0xFFFF0000u);
-            }
-        } else {
+        for (int i = 0; i < N / 4; ++i) wq[i] = *reinterpret_cast<const f32x4 *>(marg + (v + step * i < vq ? v + step * i : 0));
 #pragma unroll
-            for (int i = 0; i < N / 4; ++i) {
-                const f32x4 w = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(row) + (v + step * i < v1 ? v + step * i : 0));
-                x[4 * i] = w.x; x[4 * i + 1] = w.y; x[4 * i + 2] = w.z; x[4 * i + 3] = w.w;
+        for (int i = 0; i < N / 4; ++i) {
+            const bool in = v + step * i < v1, in_q = v + step * i < vq;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float x;
+                if constexpr (BF16) x = __uint_as_float(k & 1 ? wb[i][k / 2] & 0xFFFF0000u : wb[i][k / 2] << 16);
+                else x = wf[i][k];
+                e[4 * i + k] = in ? x : -INFINITY;
+                q[4 * i + k] = in_q ? wq[i][k] : 0.f;
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int t = v + step * (i / 4) + i % 4;
-            x[i] = load_logit<BF16>(row, t < v1 ? t : 0);
+            e[i] = load_logit<BF16>(row, t < v1 ? t : 0);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int t = v + step * (i / 4) + i % 4;
+            q[i] = marg[t < vq ? t : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int t = v + step * (i / 4) + i % 4;
+            e[i] = t < v1 ? e[i] : -INFINITY;
+            q[i] = t < vq ? q[i] : 0.f;
         }
     }
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = v + step * (i / 4) + i % 4 < v1 ? x[i] : pad;
 }
 
 // e^x for x <= 0 to about one ulp: 2^(x log2(e)) with the rounding of the product, and of the constant, brought back in to
@@ -316,10 +331,10 @@ template <int PT>
 struct SaShared {
     static constexpr int BT = PT < 4 ? 4 : PT;
     int par[BTV_MAX_NODES], tok[BTV_MAX_NODES];
-    int first[BTV_MAX_NODES + 1], fan[BTV_MAX_NODES + 1];       // first child of node c (INT_MAX: none), and how many, at c + 1
+    int2 kids[BTV_MAX_NODES + 1];                       // first child of node c (INT_MAX: none), and how many, at c + 1
     float uni[BTV_MAX_NODES + 1];
     int kcnt[SA_CHAIN][BTV_MAX_NODES / 64];             // children of chain row r among the nodes of wavefront w
-    int kid_node[BTV_MAX_NODES], kid_tok[BTV_MAX_NODES];
+    int kid_node[BTV_MAX_NODES], kid_slice[BTV_MAX_NODES];
     float kid_x[BTV_MAX_NODES];                         // the chain rows' children, row after row, in node order
     double kid_q[BTV_MAX_NODES], kid_e[BTV_MAX_NODES];
     float wm[SA_WAVES];
@@ -339,6 +354,7 @@ struct SaShared {
                                                         // below 64 KB is addressed with the instructions' own offsets)
     static constexpr bool KEEP = BT == 4;               // (e, q) in the row's order, kept through a fan (8 tokens a thread leave no room for it)
     float2 row[KEEP ? SA_T * BT : 1];
+    int koff[SA_CHAIN + 1];                             // where the children of chain row r begin
     int near;                                           // (last: the places of the others matter, 8 bytes further on they cost 0.4 us of 37)
 };
 
@@ -377,8 +393,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
     const int v0 = min(me * per, V), v1 = min(v0 + per, V);
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(p.logits) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.marg) & 15) == 0;
     for (int c = tid; c <= BTV_MAX_NODES; c += SA_T) {
-        L.first[c] = INT_MAX;
-        L.fan[c] = 0;
+        L.kids[c] = make_int2(INT_MAX, 0);
         if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
         if (c <= M) L.uni[c] = p.uniforms[c];
     }
@@ -392,8 +407,8 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
     bool dead = false, near = false;
     __syncthreads();
     if (tid < M && L.par[tid] >= -1 && L.par[tid] < M) {
-        atomicMin(&L.first[L.par[tid] + 1], tid);
-        atomicAdd(&L.fan[L.par[tid] + 1], 1);
+        atomicMin(&L.kids[L.par[tid] + 1].x, tid);
+        atomicAdd(&L.kids[L.par[tid] + 1].y, 1);
     }
     __syncthreads();
     if (NEAR && __builtin_expect(__builtin_amdgcn_readfirstlane(L.near) < 0, 0)) return false;
@@ -404,8 +419,12 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         node[0] = cur;
 #pragma unroll
         for (int r = 1; r < SA_CHAIN; ++r) {
-            node[r] = nch == r && d + r - 1 < p.B && __builtin_amdgcn_readfirstlane(L.fan[node[r - 1] + 1]) <= SA_CHAIN_FAN ?
-                      __builtin_amdgcn_readfirstlane(L.first[node[r - 1] + 1]) : INT_MAX;
+            node[r] = INT_MAX;
+            if (nch == r && d + r - 1 < p.B) {
+                const int2 k = L.kids[node[r - 1] + 1];
+                const int first = __builtin_amdgcn_readfirstlane(k.x), fan = __builtin_amdgcn_readfirstlane(k.y);
+                node[r] = fan <= SA_CHAIN_FAN ? first : INT_MAX;
+            }
             if (node[r] != INT_MAX) ++nch;
             else node[r] = cur;
         }
@@ -423,14 +442,13 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         const int ve = has_row ? v1 : v0, vr = OVER ? min(v0 + TS * PT, ve) : ve;
         float e[TG], q[TG];
         auto load_row = [&]() {
-            load_tokens<BF16, TG>(xrow, tv, TS, vr, vec, -INFINITY, e);
-            load_tokens<false, TG>(q0, tv, TS, row_q ? vr : v0, vec, 0.f, q);
+            load_tokens<BF16, TG>(xrow, q0, tv, TS, vr, row_q ? vr : v0, vec, e, q);
         };
         load_row();
         // this lane's node, if it is a child of a chain row's: what it needs of the rows is asked for behind them
         u64 bal[SA_CHAIN];
         float kid_q = 0.f, kid_x = -INFINITY;
-        int kid_tok = -1;
+        int kid_tok = -1, kid_slice = 0;
         if (wv < KW) {
             int at = -1, above = cur;
 #pragma unroll
@@ -441,6 +459,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
                 if (lane == 0) L.kcnt[r][wv] = __builtin_popcountll(bal[r]);
             }
             kid_tok = L.tok[tid & (BTV_MAX_NODES - 1)];
+            kid_slice = (int)((uint32_t)kid_tok / (uint32_t)per);
             if (at >= 0 && kid_tok >= 0 && kid_tok < V) {
                 kid_q = p.marg[(size_t)at * V + kid_tok];
                 kid_x = load_logit<BF16>(p.logits, (size_t)(above + 1) * V + kid_tok);
@@ -454,21 +473,27 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         mx = wave_max(mx);
         if (lane == 0) L.wm[wv] = mx;
         __syncthreads();
+        // What all 16 wavefronts do between two exchanges is bound by issue, four on a SIMD at some 5 cycles an instruction: the children's offsets are worked out by
+        // the four that hold nodes, first children that are taken are counted by one ballot, a node's first child and its fan are one read (each by
+        // all, and in steps: a followed draft 32.7 -> 31.0 us, fp32 32.9 -> 30.9; with the padding by pieces 29.9; 30 nodes, 32000 tokens 25.9 -> 24.6).
         int koff[SA_CHAIN + 1];
         koff[0] = 0;
+        if (wv < KW) {
 #pragma unroll
-        for (int r = 0; r < SA_CHAIN; ++r) {
-            const int4 c = *reinterpret_cast<const int4 *>(L.kcnt[r]);
-            static_assert(KW == 4, "four counts");
-            if (wv < KW && ((bal[r] >> lane) & 1)) {
-                const int j = koff[r] + (wv > 0 ? c.x : 0) + (wv > 1 ? c.y : 0) + (wv > 2 ? c.z : 0) + __builtin_popcountll(bal[r] & ((1ull << lane) - 1ull));
-                const bool ok = kid_tok >= 0 && kid_tok < V;      // not a vocabulary id: rejected, its uniform spent, nothing indexed
-                L.kid_node[j] = ok ? tid : -1 - tid;
-                L.kid_tok[j] = ok ? kid_tok : 0;
-                L.kid_q[j] = (double)kid_q;
-                L.kid_x[j] = kid_x;
+            for (int r = 0; r < SA_CHAIN; ++r) {
+                const int4 c = *reinterpret_cast<const int4 *>(L.kcnt[r]);
+                static_assert(KW == 4, "four counts");
+                if ((bal[r] >> lane) & 1) {
+                    const int j = koff[r] + (wv > 0 ? c.x : 0) + (wv > 1 ? c.y : 0) + (wv > 2 ? c.z : 0) + __builtin_popcountll(bal[r] & ((1ull << lane) - 1ull));
+                    const bool ok = kid_tok >= 0 && kid_tok < V;      // not a vocabulary id: rejected, its uniform spent, nothing indexed
+                    L.kid_node[j] = ok ? tid : -1 - tid;
+                    L.kid_slice[j] = ok ? kid_slice : 0;
+                    L.kid_q[j] = (double)kid_q;
+                    L.kid_x[j] = kid_x;
+                }
+                koff[r + 1] = __builtin_amdgcn_readfirstlane(koff[r] + c.x + c.y + c.z + c.w);
             }
-            koff[r + 1] = __builtin_amdgcn_readfirstlane(koff[r] + c.x + c.y + c.z + c.w);
+            if (tid <= SA_CHAIN) L.koff[tid] = tid == 0 ? 0 : tid == 1 ? koff[1] : tid == 2 ? koff[2] : tid == 3 ? koff[3] : koff[4];
         }
         float m_own;
         {
@@ -532,7 +557,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
             bool acc0 = false;                          // is the first child accepted, if the rows above took theirs?
 #pragma nounroll
             for (int j = k0 + lane; j < k1; j += 64) {  // a child's e exactly as its slice's owner has it
-                const int w = L.kid_tok[j] / per;
+                const int w = L.kid_slice[j];
                 const float x = L.kid_x[j];
                 const double ek = x == -INFINITY ? 0.0 : L.F[r][w] * (double)exp_neg(x - L.Mx[r][w]);
                 L.kid_e[j] = ek;
@@ -544,23 +569,22 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         if (L.dead) { dead = true; break; }
         if (NEAR) near = __builtin_amdgcn_readfirstlane(L.near) != 0;
         // ---- first children, as far as they are accepted -------------------------------------------------------------
-        int r = 0;
+        int r;
         {
-            const int4 a = *reinterpret_cast<const int4 *>(L.acc0);
-            const int acc0[SA_CHAIN] = { a.x, a.y, a.z, a.w };
-            const int next = __builtin_amdgcn_readfirstlane(L.first[(nch > 3 ? node[3] : nch > 2 ? node[2] : nch > 1 ? node[1] : node[0]) + 1]);
-#pragma unroll
-            for (int k = 0; k < SA_CHAIN; ++k) {
-                if (r != k || k >= nch || n >= M || __builtin_amdgcn_readfirstlane(acc0[k]) == 0) break;
-                cur = k + 1 < SA_CHAIN && k + 1 < nch ? node[(k + 1) % SA_CHAIN] : next;
-                if (me == 0 && tid == 0) p.path[n] = cur;
-                ++n; ++d; ++ui; ++r;
+            const int next = __builtin_amdgcn_readfirstlane(L.kids[(nch > 3 ? node[3] : nch > 2 ? node[2] : nch > 1 ? node[1] : node[0]) + 1].x);
+            const uint32_t taken = (uint32_t)__builtin_amdgcn_ballot_w64(L.acc0[lane & (SA_CHAIN - 1)] != 0);
+            r = min(min(__builtin_ctz(~taken | 1u << SA_CHAIN), nch), M - n);
+            auto below = [&](int k) { return k >= nch ? next : k == 1 ? node[1] : k == 2 ? node[2] : node[3]; };     // chain row k - 1's first child
+            if (r > 0) {
+                if (me == 0 && tid < r) p.path[n + tid] = below(tid + 1);
+                cur = __builtin_amdgcn_readfirstlane(below(r));
+                n += r; d += r; ui += r;
             }
         }
         if (r == nch) continue;
         // ---- row r: its first child is rejected, or it has none ---------------------------------------------------------
-        const int k0 = __builtin_amdgcn_readfirstlane(r == 0 ? koff[0] : r == 1 ? koff[1] : r == 2 ? koff[2] : koff[3]);
-        const int nk = __builtin_amdgcn_readfirstlane((r == 0 ? koff[1] : r == 1 ? koff[2] : r == 2 ? koff[3] : koff[4]) - k0);
+        const int k0 = __builtin_amdgcn_readfirstlane(L.koff[r]);
+        const int nk = __builtin_amdgcn_readfirstlane(L.koff[r + 1]) - k0;
         const bool here = grp == r;                     // this wavefront holds the row's tokens
         double s = 0.0, Gs = L.z[r], T = L.tq[r];
         const double f = L.F[r][me], invf = f > 0.0 ? 1.0 / f : 0.0;

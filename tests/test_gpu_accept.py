@@ -487,6 +487,39 @@ def test_stochastic_slices(G, oracle, V, logit_dtype):
     assert checked >= 1
 
 
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 7, 8, 9, 13])
+def test_stochastic_first_children_taken_to_any_depth(G, oracle, M):
+    """Chains (read four rows at a time) of M nodes, with a second child at the root in half of them, that are followed to the end, or to the child
+    whose uniform rejects it, at every level: the last row of a read, the first of the next, the end of the tree."""
+    V, B = 3000, 14
+    marg = synth.marginals(74, B, V, 3.0)
+    order = np.argsort(-marg, axis=1, kind="stable")
+    for second in (False, True):
+        parent = [-1] + [i for i in range(M - 1)]
+        depth = list(range(M))
+        if second and M > 1:
+            parent[1:] = [-1] + [0 if i == 2 else i - 1 for i in range(2, M)]
+            depth = [0, 0] + [i - 1 for i in range(2, M)]
+        token = [int(order[min(d, B - 1), 1 if (second and i == 1) else 0]) for i, d in enumerate(depth)]
+        z = np.log(np.maximum(marg[np.minimum(np.concatenate([[0], np.asarray(depth) + 1]), B - 1)].astype(np.float64), 1e-30))
+        store, xf = synth.round_to_dtype(z, "fp32")
+        for stop in range(M + 1):
+            u = np.full(M + 1, 0.25, dtype=np.float32)
+            if stop < M:
+                u[stop] = 0.99999
+                xf2, store2 = xf.copy(), store.copy()
+                row = parent[stop] + 1                   # this row's target has little on that child
+                store2[row, token[stop]] -= 6
+                xf2[row, token[stop]] -= 6
+            else:
+                xf2, store2 = xf, store
+            ref = oracle.accept_stochastic(xf2, marg, np.asarray(parent, dtype=np.int32), np.asarray(token, dtype=np.int32), np.asarray(depth, dtype=np.int32), u)
+            if _ambiguous(ref):
+                continue
+            got = G.run_accept_stochastic(store2, False, marg, parent, token, u)
+            assert got["n_acc"] == ref["n_acc"] and np.array_equal(got["path"], ref["path"]) and got["bonus"] == ref["bonus"], (second, stop)
+
+
 @pytest.mark.parametrize("V", [5000, 5001, 5002, 9996])
 @pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
 def test_stochastic_rows_at_any_element(G, oracle, V, logit_dtype):
