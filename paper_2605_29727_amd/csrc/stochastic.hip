@@ -203,54 +203,69 @@ __device__ __forceinline__ float load_logit(const void *logits, size_t idx)
 }
 
 // N tokens of a row and of its marginals in pieces of four, v + step * i .. + 3 for i < N / 4; logits from v1 on come as -inf, marginals from
-// vq on as 0.  vec: the rows allow whole pieces (then v, v1 and vq are multiples of four, and a piece is in or out).  All loads are issued before the
-// first is looked at.  A chain's rows are bound by how many loads 16 wavefronts issue: pieces are of the compiler's own vector types, because of float4, a
-// structure, it takes the four floats and merges their loads with the other path's, four of 4 bytes for one of 16 (a draft followed over 7 to 12
-// levels, 128256 tokens: bf16 35.8 -> 32.7 us, fp32 40.4 -> 32.9; a fan of 127 39.4 -> 38.8; 60000 tokens 30.4 -> 25.8).
+// vq on as 0.  v is a multiple of four, and so are v1 and vq unless they are the row's end: there the piece that the end cuts is loaded from V - 4 on
+// and moved into place.  A row may begin at any element (the hardware takes such addresses).  All loads are issued before the first is looked at.
+// A chain's rows are bound by how many loads 16 wavefronts issue: pieces are of the compiler's own vector types, because of float4, a structure, it
+// takes the four floats, and merged their loads with those of a path by single tokens, four of 4 bytes for one of 16 (a draft followed over 7
+// to 12 levels, 128256 tokens: bf16 35.8 -> 32.7 us, fp32 40.4 -> 32.9; a fan of 127 39.4 -> 38.8).  Rows of 128255 tokens by single tokens / by
+// pieces: bf16 33.5 / 27.6, fp32 34.4 / 27.5; 60002 32.8 / 26.1; 3001 21.8 / 19.3; and with no second path 128256 took 31.0 / 30.1.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 template <bool BF16, int N>
-__device__ __forceinline__ void load_tokens(const void *row, const float *marg, int v, int step, int v1, int vq, bool vec, float (&e)[N], float (&q)[N])
+__device__ __forceinline__ void load_tokens(const void *row, const float *marg, int v, int step, int v1, int vq, int V, float (&e)[N], float (&q)[N])
 {
-    if (vec) {
+    if (__builtin_expect(V >= 4, 1)) {                          // (uniform)
         u32x2 wb[N / 4];
         f32x4 wf[N / 4], wq[N / 4];
 #pragma unroll
         for (int i = 0; i < N / 4; ++i) {
-            const int at = v + step * i < v1 ? v + step * i : 0;
-            if constexpr (BF16) wb[i] = *reinterpret_cast<const u32x2 *>(static_cast<const uint16_t *>(row) + at);
-            else wf[i] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(row) + at);
+            const int at = v + step * i < v1 ? min(v + step * i, V - 4) : 0;
+            if constexpr (BF16) wb[i] = *reinterpret_cast<const u32x2_any *>(static_cast<const uint16_t *>(row) + at);
+            else wf[i] = *reinterpret_cast<const f32x4_any *>(static_cast<const float *>(row) + at);
         }
 #pragma unroll
-        for (int i = 0; i < N / 4; ++i) wq[i] = *reinterpret_cast<const f32x4 *>(marg + (v + step * i < vq ? v + step * i : 0));
+        for (int i = 0; i < N / 4; ++i) wq[i] = *reinterpret_cast<const f32x4_any *>(marg + (v + step * i < vq ? min(v + step * i, V - 4) : 0));
+        const bool ragged = (V & 3) != 0 && v1 == V;           // (uniform) the row's last piece was loaded from V - 4 on
 #pragma unroll
         for (int i = 0; i < N / 4; ++i) {
-            const bool in = v + step * i < v1, in_q = v + step * i < vq;
+            const int at = v + step * i;
+            float x[4], y[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                float x;
-                if constexpr (BF16) x = __uint_as_float(k & 1 ? wb[i][k / 2] & 0xFFFF0000u : wb[i][k / 2] << 16);
-                else x = wf[i][k];
-                e[4 * i + k] = in ? x : -INFINITY;
-                q[4 * i + k] = in_q ? wq[i][k] : 0.f;
+                if constexpr (BF16) x[k] = __uint_as_float(k & 1 ? wb[i][k / 2] & 0xFFFF0000u : wb[i][k / 2] << 16);
+                else x[k] = wf[i][k];
+                y[k] = wq[i][k];
+            }
+            if (ragged) {
+#pragma unroll
+                for (int s = 4; s > 1; --s)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const bool on = at + s > V;
+                        x[k] = on ? x[k + 1] : x[k];
+                        y[k] = on ? y[k + 1] : y[k];
+                    }
+#pragma unroll
+                for (int k = 1; k < 4; ++k) {
+                    x[k] = at + k < v1 ? x[k] : -INFINITY;
+                    y[k] = at + k < vq ? y[k] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                e[4 * i + k] = at < v1 ? x[k] : -INFINITY;
+                q[4 * i + k] = at < vq ? y[k] : 0.f;
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int t = v + step * (i / 4) + i % 4;
-            e[i] = load_logit<BF16>(row, t < v1 ? t : 0);
-        }
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int t = v + step * (i / 4) + i % 4;
-            q[i] = marg[t < vq ? t : 0];
-        }
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int t = v + step * (i / 4) + i % 4;
-            e[i] = t < v1 ? e[i] : -INFINITY;
-            q[i] = t < vq ? q[i] : 0.f;
+            const float x = load_logit<BF16>(row, t < v1 ? t : 0), y = marg[t < vq ? t : 0];
+            e[i] = t < v1 ? x : -INFINITY;
+            q[i] = t < vq ? y : 0.f;
         }
     }
 }
@@ -391,7 +406,6 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     };
     const int v0 = min(me * per, V), v1 = min(v0 + per, V);
-    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(p.logits) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.marg) & 15) == 0;
     for (int c = tid; c <= BTV_MAX_NODES; c += SA_T) {
         L.kids[c] = make_int2(INT_MAX, 0);
         if (c < BTV_MAX_NODES) { L.par[c] = c < M ? p.parent[c] : INT_MIN; L.tok[c] = c < M ? p.token[c] : -1; }
@@ -442,7 +456,7 @@ __device__ __forceinline__ bool sa_walk(const SaParams &p, SaShared<PT> &L, int 
         const int ve = has_row ? v1 : v0, vr = OVER ? min(v0 + TS * PT, ve) : ve;
         float e[TG], q[TG];
         auto load_row = [&]() {
-            load_tokens<BF16, TG>(xrow, q0, tv, TS, vr, row_q ? vr : v0, vec, e, q);
+            load_tokens<BF16, TG>(xrow, q0, tv, TS, vr, row_q ? vr : v0, V, e, q);
         };
         load_row();
         // this lane's node, if it is a child of a chain row's: what it needs of the rows is asked for behind them

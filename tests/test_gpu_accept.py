@@ -520,10 +520,10 @@ def test_stochastic_first_children_taken_to_any_depth(G, oracle, M):
             assert got["n_acc"] == ref["n_acc"] and np.array_equal(got["path"], ref["path"]) and got["bonus"] == ref["bonus"], (second, stop)
 
 
-@pytest.mark.parametrize("V", [5000, 5001, 5002, 9996])
+@pytest.mark.parametrize("V", [3, 4, 6, 7, 2049, 5000, 5001, 5002, 5003, 9996])
 @pytest.mark.parametrize("logit_dtype", ["fp32", "bf16"])
 def test_stochastic_rows_at_any_element(G, oracle, V, logit_dtype):
-    """Rows that begin on any element and end in any part of a piece of four (pieces are loaded whole where everything is aligned to them):
+    """Rows that begin on any element and end in any part of a piece of four (the last one is loaded from V - 4 on), in one slice and in several:
     the same walk as from aligned arrays, and the oracle's."""
     import torch
     from paper_2605_29727_amd import binding as btv
