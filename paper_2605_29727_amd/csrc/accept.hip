@@ -47,33 +47,41 @@ __device__ __forceinline__ float load_one(const void *logits, size_t idx)
 // bound.  Elements equal to the start value, -inf, are not taken that way: where a thread ends without a place its wavefront goes through them again.
 // us, before (rows of unaligned vocabularies by one element per load) -> now: 65 rows of 128255 bf16 12.8 -> 8.4, 21 of 30001 10.4 -> 5.9; batches of 8 requests: 520 rows
 // of 128255 89.8 -> 27.6, 168 of 20001 14.2 -> 6.6 (and aligned: 65 of 128256 8.9 -> 8.2, 520 of them 29.8 -> 27.6).
-template <bool BF16, int T, int U>
+// STREAM: read with the non-temporal hint.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_piece(const u32x4 *x)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load(x);
+    else return *x;
+}
+template <bool BF16, int T, int U, bool STREAM>
 __device__ __forceinline__ Best span_scan(const void *logits, size_t base, int v0, int v1, int tid)
 {
     constexpr int ES = BF16 ? 2 : 4, PER = 16 / ES;              // element size, elements per piece
     const unsigned char *first = static_cast<const unsigned char *>(logits) + (base + v0) * ES;
     const int n = v1 - v0, head = min((PER - (int)((reinterpret_cast<uintptr_t>(first) & 15) / ES)) & (PER - 1), n);
     const int P = (n - head) / PER, tail = n - head - P * PER;
-    const uint4 *x = reinterpret_cast<const uint4 *>(first + head * ES);
+    const u32x4 *x = reinterpret_cast<const u32x4 *>(first + head * ES);
     const int ve = tid < head ? v0 + tid : tid < head + tail ? v1 - tail + tid - head : v0;
     const float edge = load_one<BF16>(logits, base + ve);
     Best b = { -INFINITY, INT_MAX };
     auto pass = [&](auto exact) {
         for (int h = 0; h < P; h += U * T) {                     // (uniform)
-            uint4 q[U];
+            u32x4 q[U];
             if (h + U * T <= P) {
 #pragma unroll
-                for (int j = 0; j < U; ++j) q[j] = x[h + j * T + tid];
+                for (int j = 0; j < U; ++j) q[j] = load_piece<STREAM>(x + h + j * T + tid);
             } else {
 #pragma unroll
-                for (int j = 0; j < U; ++j) q[j] = x[min(h + j * T + tid, P - 1)];
+                for (int j = 0; j < U; ++j) q[j] = load_piece<STREAM>(x + min(h + j * T + tid, P - 1));
             }
             auto place = [&](int k) { return v0 + head + min(h + k / PER * T + tid, P - 1) * PER + k % PER; };
             float bv = b.v;
             int bk = -1;
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const uint32_t wds[4] = { q[j].x, q[j].y, q[j].z, q[j].w };
+                const uint32_t wds[4] = { q[j][0], q[j][1], q[j][2], q[j][3] };
 #pragma unroll
                 for (int e = 0; e < PER; ++e) {
                     const float f = !BF16 ? __uint_as_float(wds[e & 3]) : e & 1 ? __uint_as_float(wds[e / 2] & 0xFFFF0000u) : __uint_as_float(wds[e / 2] << 16);
@@ -94,12 +102,12 @@ __device__ __forceinline__ Best span_scan(const void *logits, size_t base, int v
 }
 
 // grid = (chunks, rows).  part[(row*chunks + chunk)] = best of the chunk.
-template <bool BF16>
+template <bool BF16, bool STREAM>
 __global__ __launch_bounds__(256) void argmax_chunks(const void *logits, int V, Best *part)
 {
     __shared__ Best wb[4];
     const int tid = threadIdx.x, chunk = blockIdx.x, row = blockIdx.y;
-    Best b = best_wave(span_scan<BF16, 256, BF16 ? 4 : 8>(logits, (size_t)row * V, chunk * ACHUNK, min(chunk * ACHUNK + ACHUNK, V), tid));
+    Best b = best_wave(span_scan<BF16, 256, BF16 ? 4 : 8, STREAM>(logits, (size_t)row * V, chunk * ACHUNK, min(chunk * ACHUNK + ACHUNK, V), tid));
     if ((tid & 63) == 0) wb[tid >> 6] = b;
     __syncthreads();
     if (tid == 0) {
@@ -204,7 +212,7 @@ __global__ __launch_bounds__(OL_WAVES * 64) void accept_greedy_one_launch(
         if (u < units) {
             row = u / chunks;
             const int chunk = u - row * chunks;
-            b = best_wave(span_scan<BF16, 64, 8>(logits, (size_t)row * V, chunk * WCHUNK, min(chunk * WCHUNK + WCHUNK, V), lane));
+            b = best_wave(span_scan<BF16, 64, 8, false>(logits, (size_t)row * V, chunk * WCHUNK, min(chunk * WCHUNK + WCHUNK, V), lane));
         }
         if (lane == 0) { wbest[wave] = b; wrow[wave] = row; }
         if (collector)
@@ -584,8 +592,15 @@ int btv_tree_accept_greedy_batch(const void *logits, int dtype, const int32_t *p
     hipStream_t st = static_cast<hipStream_t>(stream);
     Best *part = reinterpret_cast<Best *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
     const int chunks = (V + ACHUNK - 1) / ACHUNK, rows = total_M + batch;
-    if (dtype == BTV_BF16) hipLaunchKernelGGL(argmax_chunks<true>, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
-    else hipLaunchKernelGGL(argmax_chunks<false>, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
+    // Logits of more than 64 MB are read past the caches.  The product that wrote them has put its weights through the last-level cache since, and most of
+    // them come from memory.  us, without / with the hint, behind that product | other buffers in between | the same logits again at once: 35 MB 14.3 / 14.7 | 11.5 /
+    // 11.3 | 9.8 / 10.3; 62 MB - | 16.5 / 15.6 | 15.4 / 14.2; 84 MB 22.3 / 22.0; 133 MB 30.2 / 29.1 | 27.7 / 26.0 | 25.3 / 24.4; 166 MB 37.2 / 35.2 | 33.3 / 31.1 | 30.2 / 29.4; 257 MB 51.5 /
+    // 48.6 | 48.1 / 44.1 | 42.0 / 43.0; 373 MB 70.5 / 65.2; 415 MB - | 73.7 / 67.8 | 74.0 / 66.5.  (Behind an elementwise pass over the logits themselves, which leaves them in the caches, up
+    // to 259 MB 3 to 4 more with it; 415 MB 97 / 49.)  One request's logits, 132 MB at most, gained nothing behind the product.
+    const bool stream_read = (unsigned long long)rows * V * (dtype == BTV_BF16 ? 2 : 4) > (64ull << 20);
+    const auto scan = dtype == BTV_BF16 ? (stream_read ? argmax_chunks<true, true> : argmax_chunks<true, false>)
+                                        : (stream_read ? argmax_chunks<false, true> : argmax_chunks<false, false>);
+    hipLaunchKernelGGL(scan, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
     BTV_HIP(hipGetLastError());
     hipLaunchKernelGGL(greedy_walk, dim3(batch), dim3(GW_WAVES * 64), 0, st, part, chunks, parent, token, M_max, path, n_acc, bonus,
                        argmax_out, q_offset, total_M, static_cast<uint32_t *>(ws));

@@ -96,6 +96,47 @@ def test_accept_batch_matches_oracle(oracle, dtype):
         assert np.array_equal(am[o + r:o + r + M + 1], ref["argmax"])
 
 
+@pytest.mark.parametrize("V", [131072, 131073])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_accept_batch_around_the_size_read_past_the_caches(V, dtype):
+    """64 MB of logits and a little more: every row's argmax and every walk as one call per request gives them."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    rows = (64 << 20) // (131072 * (2 if dtype == "bf16" else 4))
+    Ms = [rows // 2 - 1, 1, rows // 2 - 3]                      # with the three roots: `rows` in all
+    off = np.concatenate([[0], np.cumsum(Ms)]).astype(np.int32)
+    total = int(off[-1])
+    assert total + len(Ms) == rows
+    x = torch.randn((rows, V), generator=torch.Generator(device="cuda").manual_seed(V), device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    x[3] = float("-inf")
+    x[5, V - 1] = x[6, 0] = x[rows - 1, V - 1] = 9.0
+    x[7, 8191] = x[7, 8192] = 9.0
+    parents = [synth.tree_parents(r, M, "random") for r, M in enumerate(Ms)]
+    one = []
+    tokens = []
+    for r, M in enumerate(Ms):
+        lg = x[int(off[r]) + r:int(off[r + 1]) + r + 1].contiguous()
+        best = lg.float().argmax(1).to(torch.int32)
+        par = torch.from_numpy(parents[r]).cuda()
+        tok = best[(par + 1).long()].contiguous()                # (every node is its parent's argmax: the walk takes first children to the end)
+        tokens.append(tok)
+        o = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (M, 1, 1, M + 1)]
+        btv.btv_tree_accept_greedy(lg, par, tok, *o, btv.alloc_workspace(btv.btv_tree_accept_workspace(M, V, False)))
+        one.append([t.cpu().numpy() for t in o])
+    o = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (total, len(Ms), len(Ms), rows)]
+    ws = btv.alloc_workspace(btv.btv_tree_accept_batch_workspace(len(Ms), total, V))
+    btv.btv_tree_accept_greedy_batch(x, torch.from_numpy(np.concatenate(parents)).cuda(), torch.cat(tokens), torch.from_numpy(off).cuda(), max(Ms), *o, ws)
+    torch.cuda.synchronize()
+    assert btv.btv_workspace_status(ws) == 0
+    path, n_acc, bonus, am = [t.cpu().numpy() for t in o]
+    assert am[3] == 0 and am[5] == V - 1 and am[6] == 0 and am[7] == 8191 and am[rows - 1] == V - 1
+    for r, (p1, n1, b1, a1) in enumerate(one):
+        n = int(n1[0])
+        assert n_acc[r] == n and bonus[r] == b1[0]
+        assert np.array_equal(path[off[r]:off[r] + n], p1[:n])
+        assert np.array_equal(am[off[r] + r:off[r + 1] + r + 1], a1)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_accept_batch_neg_inf_in_whole_chunks(oracle, dtype):
     """Rows that are -inf nearly everywhere over two whole argmax chunks and a ragged one: a thread that saw
