@@ -95,7 +95,8 @@ constexpr u64 NO_TOKEN = 0xFFFFFFFFull;      // the key of probability 0, token 
 // ------------------------------------------------------------------------------------------------
 struct TbCounters { int done; };            // zero between calls
 
-template <int LGE>
+// STREAM: read with the non-temporal hint.
+template <int LGE, bool STREAM>
 __global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, int chunks, uint2 *part)
 {
     const int tid = threadIdx.x, chunk = blockIdx.x, row = blockIdx.y;
@@ -111,24 +112,30 @@ __global__ __launch_bounds__(256) void tb_thread_max(const float *marg, int V, i
     // alignment of one.  The row's last chunk, a sixteenth of the workgroups, ends with the others so: by single floats, four times as many loads,
     // it was what the launch waited for (16 x 128256 and 16 nodes 11.6 -> 11.0 us, 256 nodes 25.0 -> 24.3; 128 rows of 128256 4 us less).
     constexpr int PIECES = (1 << LGE) / 4;
-    struct alignas(4) Four { float x[4]; };
+    typedef float Four __attribute__((ext_vector_type(4)));
+    typedef Four Four_any __attribute__((aligned(4)));
+    auto load = [&](int at) {
+        const Four_any *x = reinterpret_cast<const Four_any *>(src + at);
+        if constexpr (STREAM) return (Four)__builtin_nontemporal_load(x);
+        else return (Four)*x;
+    };
     const int first = slot_first(LGE, chunk, tid);               // coalesced: a wave reads 1 KiB per load
     if ((chunk + 1) << (8 + LGE) <= V) {                         // (uniform)
         Four a[PIECES];
 #pragma unroll
-        for (int j = 0; j < PIECES; ++j) a[j] = *reinterpret_cast<const Four *>(src + first + j * 1024);
+        for (int j = 0; j < PIECES; ++j) a[j] = load(first + j * 1024);
 #pragma unroll
         for (int j = 0; j < PIECES; ++j)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) see(prob_bits(a[j].x[i]), 4 * j + i);
+            for (int i = 0; i < 4; ++i) see(prob_bits(a[j][i]), 4 * j + i);
     } else {                                                     // the row's last chunk: as many loads, the last of them moved back into the row
         Four a[PIECES];
 #pragma unroll
-        for (int j = 0; j < PIECES; ++j) a[j] = *reinterpret_cast<const Four *>(src + min(first + j * 1024, V - 4));      // (V > 4096 here)
+        for (int j = 0; j < PIECES; ++j) a[j] = load(min(first + j * 1024, V - 4));      // (V > 4096 here)
 #pragma unroll
         for (int j = 0; j < PIECES; ++j) {
             const int past = first + j * 1024 - (V - 4);         // so many places forward
-            float x[4] = { a[j].x[0], a[j].x[1], a[j].x[2], a[j].x[3] };
+            float x[4] = { a[j][0], a[j][1], a[j][2], a[j][3] };
             if (past > 0) {                                      // (0 changes nothing)
                 if (past & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = 0.f; }
                 if (past & 2) { x[0] = x[2]; x[1] = x[3]; x[2] = x[3] = 0.f; }
@@ -1524,10 +1531,19 @@ static int tree_build_launch(const float *marginals, int batch, int B, int V, in
     ad.flag = reinterpret_cast<uint32_t *>(base);
     bt.flag = reinterpret_cast<uint32_t *>(base);
     const dim3 scan_grid(t.chunks, B * batch);
-    if (t.lge == 2) hipLaunchKernelGGL(tb_thread_max<2>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
-    else if (t.lge == 3) hipLaunchKernelGGL(tb_thread_max<3>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
-    else if (t.lge == 4) hipLaunchKernelGGL(tb_thread_max<4>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
-    else if (t.lge == 5) hipLaunchKernelGGL(tb_thread_max<5>, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
+    auto scan = [&](auto lge) {
+        constexpr int LGE = decltype(lge)::value;
+        // Marginals that the last-level cache (256 MB) cannot hold are read past it: read through it, rows that are still there make way for others.  us, without /
+        // with the hint, behind the softmax that wrote them | other buffers in between | the same marginals again at once: 394 MB 116 / 98 | 99.7 / 94.8 | 99.9 / 94.7; 525 MB
+        // - | 131.7 / 122.6 | 131.4 / 122.4; but 131 MB 36.9 / 38.2 | 39.2 / 38.2 | 35.1 / 37.7; 263 MB 68.8 / 67.5 | 68.3 / 65.8 | 60.4 / 65.3.
+        const bool stream_read = (unsigned long long)batch * B * V * sizeof(float) > (256ull << 20);
+        const auto kern = stream_read ? tb_thread_max<LGE, true> : tb_thread_max<LGE, false>;
+        hipLaunchKernelGGL(kern, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
+    };
+    if (t.lge == 2) scan(std::integral_constant<int, 2>{});
+    else if (t.lge == 3) scan(std::integral_constant<int, 3>{});
+    else if (t.lge == 4) scan(std::integral_constant<int, 4>{});
+    else if (t.lge == 5) scan(std::integral_constant<int, 5>{});
     BTV_HIP(hipGetLastError());
     const int solo = solo_plan(B, V);
     const auto rank_expand = solo ? tb_rank_expand<true> : tb_rank_expand<false>;

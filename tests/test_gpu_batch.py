@@ -49,6 +49,32 @@ def test_tree_build_batch_matches_oracle(oracle, batch, B, V, N_max, slack):
         assert np.all(got["parent"][o + n:int(q_offset[r + 1])] == -7)        # nothing written past the request's nodes
 
 
+@pytest.mark.parametrize("V", [4097, 16387, 65537, 131072, 131073])
+def test_tree_build_batch_around_the_size_read_past_the_caches(V):
+    """256 MB of marginals and a little more: every request's tree is bit for bit that of a call of its own."""
+    import torch
+    from paper_2605_29727_amd import binding as btv
+    B, N = 16, 24
+    batch = (256 << 20) // (B * V * 4) + (V != 131072)           # (131072: 256 MB exactly)
+    m = torch.softmax(torch.randn((batch, B, V), generator=torch.Generator(device="cuda").manual_seed(V), device="cuda") * 3.0, dim=-1)
+    m[1, :, V - 1] = 2.0                                         # the last token of a row is its best
+    def out(total, n):
+        return [torch.full((k,), -7, dtype=t, device="cuda") for k, t in ((total, torch.int32), (total, torch.int32), (total, torch.int32), (total, torch.float32),
+                                                                           (n, torch.int32), (n, torch.float32))]
+    all_of = out(batch * N, batch)
+    ws = btv.alloc_workspace(btv.btv_tree_build_batch_workspace(batch, B, V, N))
+    btv.btv_tree_build_batch(m, torch.full((batch,), N, dtype=torch.int32, device="cuda"), torch.arange(batch + 1, dtype=torch.int32, device="cuda") * N, N, *all_of, ws)
+    torch.cuda.synchronize()
+    assert btv.btv_workspace_status(ws) == 0
+    one_ws = btv.alloc_workspace(btv.btv_tree_build_workspace(B, V, N))
+    for r in sorted({0, 1, batch // 2, batch - 1}):
+        one = out(N, 1)
+        btv.btv_tree_build(m[r], N, *one, one_ws)
+        for a, b in zip(all_of, one):
+            k = b.numel()
+            assert torch.equal(a[r * k:(r + 1) * k], b), r
+
+
 def test_tree_build_batch_flags_bad_requests(oracle):
     marg = np.stack([synth.marginals(950 + r, 4, 100, 2.0) for r in range(3)])
     q_offset = np.array([0, 10, 20, 30], dtype=np.int32)
