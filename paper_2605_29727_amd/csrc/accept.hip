@@ -592,12 +592,14 @@ int btv_tree_accept_greedy_batch(const void *logits, int dtype, const int32_t *p
     hipStream_t st = static_cast<hipStream_t>(stream);
     Best *part = reinterpret_cast<Best *>(static_cast<unsigned char *>(ws) + BTV_WS_HEADER);
     const int chunks = (V + ACHUNK - 1) / ACHUNK, rows = total_M + batch;
-    // Logits of more than 64 MB are read past the caches.  The product that wrote them has put its weights through the last-level cache since, and most of
-    // them come from memory.  us, without / with the hint, behind that product | other buffers in between | the same logits again at once: 35 MB 14.3 / 14.7 | 11.5 /
-    // 11.3 | 9.8 / 10.3; 62 MB - | 16.5 / 15.6 | 15.4 / 14.2; 84 MB 22.3 / 22.0; 133 MB 30.2 / 29.1 | 27.7 / 26.0 | 25.3 / 24.4; 166 MB 37.2 / 35.2 | 33.3 / 31.1 | 30.2 / 29.4; 257 MB 51.5 /
-    // 48.6 | 48.1 / 44.1 | 42.0 / 43.0; 373 MB 70.5 / 65.2; 415 MB - | 73.7 / 67.8 | 74.0 / 66.5.  (Behind an elementwise pass over the logits themselves, which leaves them in the caches, up
-    // to 259 MB 3 to 4 more with it; 415 MB 97 / 49.)  One request's logits, 132 MB at most, gained nothing behind the product.
-    const bool stream_read = (unsigned long long)rows * V * (dtype == BTV_BF16 ? 2 : 4) > (64ull << 20);
+    // Logits of 64 to 160 MiB, and of more than 288, are read past the caches.  us, through them / past them.  The product that wrote the logits has put its weights through the
+    // last-level cache (256 MB) since, and most of them come from memory: 90 MB 24.4 / 24.2, 130 MB 29.7 / 29.5, 150 MB 33.8 / 32.3, 165 MB 36.0 / 34.4 (a vocabulary of 32000: 38.2 / 33.5), 310 MB
+    // 62.7 / 54.9, 410 MB 78.1 / 71.9.  Passes over them in place in between (a scale, a bias, a mask, a cap) leave what fits in the cache: 90 MB 23.8 / 23.3, 165 MB 34.1 / 33.7, 310 MB 70.3 to 75.5 / 54.2
+    // to 64.5.  From 190 to 285 MB it is a matter of the pass, which the call cannot know: behind the product 43.2 / 40.5 (210 MB), 52.3 / 47.4 (260 MB), but behind a scale or a division that follows it
+    // 42.9 / 45.7 (230 MB), 46.9 / 54.6 (260 MB), 49.2 / 58.5 (275 MB), fp32 35.6 / 40.1 (190 MB), and where they are met again at once 35.5 / 37.0 (200 MB, 32000).  Below 64 MiB nothing is gained
+    // behind the product (51 MB 18.1 / 18.4; 64 MB 20.2 / 20.0).  One request's logits (257 rows of 128256 floats are 132 MB) gained nothing behind it either.
+    const unsigned long long bytes = (unsigned long long)rows * V * (dtype == BTV_BF16 ? 2 : 4);
+    const bool stream_read = (bytes > (64ull << 20) && bytes <= (160ull << 20)) || bytes > (288ull << 20);
     const auto scan = dtype == BTV_BF16 ? (stream_read ? argmax_chunks<true, true> : argmax_chunks<true, false>)
                                         : (stream_read ? argmax_chunks<false, true> : argmax_chunks<false, false>);
     hipLaunchKernelGGL(scan, dim3(chunks, rows), dim3(256), 0, st, logits, V, part);
