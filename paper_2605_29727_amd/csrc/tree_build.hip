@@ -1533,10 +1533,12 @@ static int tree_build_launch(const float *marginals, int batch, int B, int V, in
     const dim3 scan_grid(t.chunks, B * batch);
     auto scan = [&](auto lge) {
         constexpr int LGE = decltype(lge)::value;
-        // Marginals that the last-level cache (256 MB) cannot hold are read past it: read through it, rows that are still there make way for others.  us, without /
-        // with the hint, behind the softmax that wrote them | other buffers in between | the same marginals again at once: 394 MB 116 / 98 | 99.7 / 94.8 | 99.9 / 94.7; 525 MB
-        // - | 131.7 / 122.6 | 131.4 / 122.4; but 131 MB 36.9 / 38.2 | 39.2 / 38.2 | 35.1 / 37.7; 263 MB 68.8 / 67.5 | 68.3 / 65.8 | 60.4 / 65.3.
-        const bool stream_read = (unsigned long long)batch * B * V * sizeof(float) > (256ull << 20);
+        // Marginals that the last-level cache (256 MB) cannot hold are read past it: read through it, rows that are still there make way for others.  us, through it / past it,
+        // behind the softmax that wrote them | a pass over them in place | other buffers in between | the same marginals again at once: 312 MB 90.0 / 80.5 | 96.7 / 75.4 | 82.8 / 80.3 |
+        // 81.3 / 79.4; 394 MB 118 / 98 | 138 / 94 | 102 / 97 | 103 / 98; 525 MB 163 / 131 | 180 / 129 | 138 / 129 | 138 / 127.  Just above the cache's size much of them is still there, and
+        // some calls lose: 271 MB 75.1 / 73.2 | 67.0 / 68.9 | 74.0 / 71.9 | 66.9 / 71.8; 279 MB 77.4 / 73.1 | 66.5 / 67.1 | 75.2 / 72.0 | 68.2 / 72.1; 296 MB 84.7 / 78.4 | 83.7 / 71.0 | 79.7 / 76.1 |
+        // 73.1 / 75.2.  Below: 131 MB 36.9 / 38.2 | - | 39.2 / 38.2 | 35.1 / 37.7; 263 MB 69.7 / 69.8 | 64.6 / 64.5 | 71.7 / 69.6 | 63.3 / 69.3.
+        const bool stream_read = (unsigned long long)batch * B * V * sizeof(float) > (288ull << 20);
         const auto kern = stream_read ? tb_thread_max<LGE, true> : tb_thread_max<LGE, false>;
         hipLaunchKernelGGL(kern, scan_grid, dim3(256), 0, st, marginals, V, t.chunks, part);
     };
