@@ -54,6 +54,26 @@ def run_verify_attn_fp8kv(Q_bits: np.ndarray, kv: dict, parent: np.ndarray, L: i
     return host(O).astype(np.float64)
 
 
+def batch_plan(ws) -> tuple:
+    """(a team's share, one KV head's work) of a batched attention call that used this workspace, zeroed, as its first.  Workgroups that share the work out leave both
+    behind the workspace's header and the 128 KiB of the merge's words; a grid of parts leaves (0, 0)."""
+    at = (256 + 128 * 1024) // 8
+    return tuple(ws[:(at + 2) * 8].cpu().numpy().view(np.int64)[at:].tolist())
+
+
+# Tiles of 32 keys of two requests that together are one share: around the ends of the windows of 32 tiles whose page ids a piece keeps.
+SHARES_OF_TWO = ((31, 97), (32, 96), (33, 95), (64, 64), (63, 65))
+
+
+def whole_shares(batch: int, N_lo: int, N_hi: int):
+    """Context lengths and trees of a batch whose teams, batch / 2 per KV head, each take two whole requests: they begin at tile 0, and end with a tile, one key behind it or
+    ahead of it, and in either half."""
+    Ns = [N_lo + r % (N_hi - N_lo + 1) for r in range(batch)]
+    ends = (0, 1, 15, 16, 17, 31)
+    Ls = [32 * SHARES_OF_TWO[r // 2 % 5][r % 2] - ends[(r + r // 10) % 6] - Ns[r] for r in range(batch)]
+    return Ls, Ns
+
+
 def run_tree_build(marg: np.ndarray, N: int, algo: int = 0) -> dict:
     """algo 0: btv_tree_build; 1 / 2: the tuned entry point with the one-wavefront / level-synchronous expansion."""
     m = dev(marg.astype(np.float32))

@@ -241,7 +241,9 @@ def test_bf16_long_prefix_many_rows_elementwise(G, oracle, dims, kind):
     assert np.abs(out - ref).max() <= TOL_BF16, (dims, kind, np.abs(out - ref).max())
 
 
-def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed):
+def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed, alike=1):
+    """Every element against the oracle.  alike: so many times these heads, all with the same queries, keys and values, and so the same results.
+    Returns what the workgroups left of their plan (G.batch_plan)."""
     import torch
     from paper_2605_29727_amd import binding as btv
     batch = len(Ls)
@@ -265,21 +267,24 @@ def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed):
         Qall[qoff[r]:qoff[r + 1]] = t["Q"]
         parents[qoff[r]:qoff[r + 1]] = parent
         reqs.append((t, parent))
-    Q, K, V = G.dev(Qall, True), G.dev(Kp, True), G.dev(Vp, True)
+    Q, K, V = (G.dev(x, True).repeat(*(1,) * (x.ndim - 2), alike, 1) for x in (Qall, Kp, Vp))
     O = torch.full_like(Q, float("nan"))
     M_max, L_max = max(Ns), max(Ls)
-    ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_workspace(batch, M_max, L_max, Hq, Hkv, D))
+    ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_workspace(batch, M_max, L_max, Hq * alike, Hkv * alike, D))
     btv.btv_tree_verify_attn_paged(Q, K, V, G.dev(bt), G.dev(qoff), G.dev(np.asarray(Ls, dtype=np.int32)),
                                    G.dev(parents), M_max, L_max, O, ws)
     torch.cuda.synchronize()
     assert btv.btv_workspace_status(ws) == 0
     out = G.host(O).astype(np.float64)
     assert np.isfinite(out).all()
+    assert np.array_equal(out, np.tile(out[:, :Hq], (1, alike, 1)))
+    out = out[:, :Hq]
     Kpf, Vpf = synth.bf16_bits_to_f32(Kp), synth.bf16_bits_to_f32(Vp)
     for r, (t, parent) in enumerate(reqs):
         o = out[qoff[r]:qoff[r + 1]]
         ref = oracle.tree_attn(t["Qf"], Kpf, Vpf, parent, Ls[r], block_table=bt[r], page=synth.PAGE)
         assert np.abs(o - ref).max() <= TOL_BF16, r
+    return G.batch_plan(ws)
 
 
 @pytest.mark.parametrize("shape_id", [1, 2, 3])
@@ -298,9 +303,21 @@ def test_bf16_around_the_rings_and_the_trips(G, oracle, shape_id, D):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_paged_around_the_windows_of_pages(G, oracle, D):
-    """Requests of 31 to 34 and 63 to 66 tiles (a window of page ids is 32), ending in either half of a tile and with it."""
+    """A grid of parts, and in it requests of 31 to 34 and 63 to 66 tiles, ending in either half of a tile and with it: with 64 channels around the windows of 32 tiles
+    whose page ids are kept, with 128, which leave no room for them, with ids loaded one by one."""
     for tiles in (31, 33, 64):
-        _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, D, seed=92 + tiles)
+        plan = _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, D, seed=92 + tiles)
+        assert plan == (0, 0)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N_lo, N_hi", [(33, 36), (20, 24)])         # 256-row blocks, the pipelined loop; 128-row blocks, two key-waves
+def test_paged_around_the_windows_of_pages_of_whole_requests(G, oracle, N_lo, N_hi, D):
+    """The work shared out, two whole requests a share: pieces of 31 to 33, 63 to 65 and 95 to 97 tiles, where the windows of 32 tiles' page ids turn with all loads in flight
+    and at the ends of the requests."""
+    Ls, Ns = G.whole_shares(64, N_lo, N_hi)
+    share, head = _paged_case(G, oracle, Ls, Ns, 4, 1, D, seed=95, alike=8)
+    assert head == 32 * share > 0                                     # (256 teams, none of which begins or ends within a request)
 
 
 def test_paged_ragged_small(G, oracle):
@@ -336,7 +353,7 @@ def long_batch(batch, M_max, L_long, long_at):
 ])
 def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long, long_at, Hq, Hkv, D):
     Ls, Ns = long_batch(batch, M_max, L_long, long_at)
-    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=65)
+    assert _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=65)[0] > 0
 
 
 @pytest.mark.parametrize("batch, M_max, L_long, long_at, Hq, Hkv, D", [(66, 33, 3200, 60, 16, 2, 128), (70, 16, 8100, 0, 16, 2, 128), (130, 9, 8100, 64, 16, 4, 64)])
@@ -344,15 +361,18 @@ def test_paged_batches_around_stretches_that_are_cut(G, oracle, batch, M_max, L_
     """Stretches of 6 to 13 tiles: up to 8 are not cut, a cut within two of an end moves there, beside one that many workgroups share."""
     Ls, Ns = long_batch(batch, M_max, L_long, long_at)
     Ls = [(180, 222, 230, 255, 256, 270, 289, 320, 350, 383, 400)[r % 11] if r != long_at else l for r, l in enumerate(Ls)]
-    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=67)
+    assert _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=67)[0] > 0
 
 
-@pytest.mark.parametrize("batch, M_max, Hq, Hkv, D", [(64, 33, 16, 2, 128), (65, 16, 16, 2, 128), (65, 16, 16, 4, 64)])
-def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max, Hq, Hkv, D):
-    """Several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones, before and behind a long request."""
-    Ls, Ns = long_batch(batch, M_max, 3300, batch - 1)
+@pytest.mark.parametrize("batch, M_max, L_long, Hq, Hkv, D, shared", [
+    (64, 33, 3300, 16, 2, 128, True), (65, 33, 3300, 16, 2, 128, True), (130, 33, 3300, 16, 2, 64, True), (65, 16, 8100, 16, 2, 128, True), (130, 16, 8100, 16, 2, 64, True),
+    (65, 16, 3300, 16, 2, 128, False), (65, 16, 3300, 16, 4, 64, False)])
+def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max, L_long, Hq, Hkv, D, shared):
+    """The work shared out: several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones, before and behind a long request.  And
+    as many requests in a grid of parts."""
+    Ls, Ns = long_batch(batch, M_max, L_long, batch - 1)
     Ls[0] = 2500
-    _paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=69)
+    assert (_paged_case(G, oracle, Ls, Ns, Hq, Hkv, D, seed=69)[0] > 0) == shared
 
 
 @pytest.mark.parametrize("batch, M_max, L, Hq, Hkv, D", [(6, 128, 700, 16, 2, 64), (7, 110, 710, 16, 2, 64), (6, 128, 700, 16, 2, 128), (7, 110, 710, 16, 2, 128),
@@ -365,7 +385,7 @@ def test_paged_batches_of_parts(G, oracle, batch, M_max, L, Hq, Hkv, D):
 
 @pytest.mark.parametrize("M, L", [(1, 24000), (9, 9000), (130, 24000)])     # many parts; more than 32; the work shared out
 def test_paged_batch_of_one(G, oracle, M, L):
-    _paged_case(G, oracle, [L], [M], 16, 2, 128, seed=66)
+    assert (_paged_case(G, oracle, [L], [M], 16, 2, 128, seed=66)[0] > 0) == (M == 130)
 
 
 def test_paged_bad_requests_are_skipped_where_the_work_is_shared_out(G):

@@ -173,7 +173,9 @@ def test_full_size_configurations(G, oracle, which):
     assert np.abs(out).max() <= 448.0 * kv["v_scale"] + 1e-2          # convex combinations of V rows
 
 
-def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, seed):
+def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, seed, alike=1):
+    """Every element against the oracle.  alike: so many times these heads, all with the same queries, keys and values, and so the same results.
+    Returns what the workgroups left of their plan (G.batch_plan)."""
     import torch
     from paper_2605_29727_amd import binding as btv
     batch = len(Ls)
@@ -196,26 +198,39 @@ def _paged_case(G, oracle, Ls, Ns, Hq, Hkv, seed):
         Qall[qoff[r]:qoff[r + 1]] = q["Q"]
         parents[qoff[r]:qoff[r + 1]] = parent
         reqs.append((q, parent))
-    Q, K, V = G.dev(Qall, True), G.dev(Kp), G.dev(Vp)
+    Q, K, V = (x.repeat(*(1,) * (x.ndim - 2), alike, 1) for x in (G.dev(Qall, True), G.dev(Kp), G.dev(Vp)))
     O = torch.full_like(Q, float("nan"))
     M_max, L_max = max(Ns), max(Ls)
-    ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_fp8kv_workspace(batch, M_max, L_max, Hq, Hkv, D))
+    ws = btv.alloc_workspace(btv.btv_tree_verify_attn_paged_fp8kv_workspace(batch, M_max, L_max, Hq * alike, Hkv * alike, D))
     btv.btv_tree_verify_attn_paged_fp8kv(Q, K, V, ks, vs, G.dev(bt), G.dev(qoff), G.dev(np.asarray(Ls, dtype=np.int32)),
                                          G.dev(parents), M_max, L_max, O, ws)
     torch.cuda.synchronize()
     assert btv.btv_workspace_status(ws) == 0
     out = G.host(O).astype(np.float64)
     assert np.isfinite(out).all()
+    assert np.array_equal(out, np.tile(out[:, :Hq], (1, alike, 1)))
     for r, (q, parent) in enumerate(reqs):
-        o = out[qoff[r]:qoff[r + 1]]
-        ref = oracle.tree_attn_fp8kv(q["Qf"], Kp, Vp, ks, vs, parent, Ls[r], block_table=bt[r], page=synth.PAGE)
+        o = out[qoff[r]:qoff[r + 1], :Hq]
+        own = bt[r][bt[r] >= 0]                                  # (the oracle decodes the pool that it is given, each time)
+        ref = oracle.tree_attn_fp8kv(q["Qf"], Kp[own], Vp[own], ks, vs, parent, Ls[r], block_table=np.arange(len(own), dtype=np.int32), page=synth.PAGE)
         assert np.abs(o - ref).max() <= TOL, r
+    return G.batch_plan(ws)
 
 
 def test_paged_around_the_windows_of_pages(G, oracle):
-    """Requests of 31 to 34 and 63 to 66 tiles (a window of page ids is 32), ending in either half of a tile and with it."""
+    """A grid of parts, and in it requests of 31 to 34 and 63 to 66 tiles (a window of page ids is 32), ending in either half of a tile and with it."""
     for tiles in (31, 33, 64):
-        _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, seed=92 + tiles)
+        plan = _paged_case(G, oracle, [32 * tiles - 3, 32 * tiles + 13, 32 * tiles + 29, 32 * tiles + 45], [3, 3, 3, 19], 4, 1, seed=92 + tiles)
+        assert plan == (0, 0)
+
+
+@pytest.mark.parametrize("batch, N_lo, N_hi", [(64, 20, 24), (128, 9, 16)])       # 128-row blocks; 64-row blocks and two chunks of requests
+def test_paged_around_the_windows_of_pages_of_whole_requests(G, oracle, batch, N_lo, N_hi):
+    """The work shared out, two whole requests a share: pieces of 31 to 33, 63 to 65 and 95 to 97 tiles, where the windows of 32 tiles' page ids turn with all loads in flight
+    and at the ends of the requests."""
+    Ls, Ns = G.whole_shares(batch, N_lo, N_hi)
+    share, head = _paged_case(G, oracle, Ls, Ns, 4, 1, seed=95, alike=8)
+    assert head == batch // 2 * share > 0                             # (as many teams, none of which begins or ends within a request)
 
 
 @pytest.mark.parametrize("shape_id", [1, 2])
@@ -243,16 +258,16 @@ def test_paged_batches_that_share_the_work_out(G, oracle, batch, M_max, L_long):
     Ls = [(63, 64, 200, 490, 511, 513, 530, 700, 900)[r % 9] for r in range(batch)]   # (a few keys alone give values that bf16 itself rounds by 0.016)
     Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
     Ls[64] = L_long
-    _paged_case(G, oracle, Ls, Ns, 16, 2, seed=84)
+    assert _paged_case(G, oracle, Ls, Ns, 16, 2, seed=84)[0] > 0
 
 
-@pytest.mark.parametrize("batch, M_max", [(64, 16), (65, 33)])
-def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max):
-    """Several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones."""
+@pytest.mark.parametrize("batch, M_max, L_long, shared", [(65, 33, 3300, True), (130, 8, 8100, True), (64, 16, 3300, False)])
+def test_paged_batches_around_a_chunk_of_requests(G, oracle, batch, M_max, L_long, shared):
+    """The work shared out: several small pieces a workgroup, found in the first chunk of 64 requests (kept in LDS) and in later ones.  And as many requests in a grid of parts."""
     Ls = [(63, 64, 200, 490, 511, 513, 530, 700, 900)[r % 9] for r in range(batch)]
     Ns = [(1, 2, M_max // 2, M_max // 2 + 1, M_max)[r % 5] for r in range(batch)]
-    Ls[0], Ls[-1] = 2500, 3300
-    _paged_case(G, oracle, Ls, Ns, 16, 2, seed=85)
+    Ls[0], Ls[-1] = 2500, L_long
+    assert (_paged_case(G, oracle, Ls, Ns, 16, 2, seed=85)[0] > 0) == shared
 
 
 def test_config4_ragged_paged_full_size(G, oracle):
