@@ -1866,9 +1866,9 @@ __global__ __launch_bounds__(RW * KW * 64, 2) void tv_attn_short(AttnParams p)
 // stretch stands for two row blocks then, one for each member, over the same tiles, so that the second finds the K/V of the
 // first in their L2; an odd last row block is a stretch of half its tiles, each member taking half of every part
 // (if it is small, one of them takes it alone).
-// Bound by the tiles (0.84 us each in bf16 pieces of more than 128 rows, 0.58 below; FP8 0.51 in pieces of more than 64 rows, 0.33 below), and
-// by the pieces: 5.5 to 8 us each beyond its tiles (finding it 0.5, page ids and first tiles 3, merging
-// and storing 2, waiting for the other waves 0.5), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
+// Bound by the tiles (0.84 to 0.91 us each in bf16 pieces of more than 128 rows, 0.58 to 0.61 below; FP8 0.49 to 0.51 in pieces of more than 64 rows, 0.32 to 0.34 below), and
+// by the pieces: 6 (FP8) to 10.5 us each beyond its tiles (the plan and finding it 1.2 to 1.8, page ids and first tiles 2 to 2.7, the rest of the prologue 1.1, merging
+// and storing 1.3 to 2, waiting for the other waves 0.1 to 0.8, the way into and out of the loop 0.5 to 3.2), START comes from that.  us, with START, MARGIN and SMALL of 8, 8 and 16 tiles / 8, 2 and 8 / 10, 2 and 8:
 // 8 requests of 1k to 16k, bf16 156 / 155 / 152; 32 of 100 to 4000, FP8 59.7 / 52.8 / 50.9; 5 of up to 8k with 83 nodes 58.5 / 51.8 / 53.8; 9 of up to 9k with
 // 12 42.0 / 39.7 / 39.9; 14 of up to 6k, FP8 67.4 / 65.4 / 65.0.  The figures beside the choice of the form
 // (short_batch) are the whole call's.
